@@ -409,6 +409,9 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.rows_per_group = (pl.schedule == VS_SCHED_RESIDENT ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
     p.total_wgs = pl.total_wgs;
     p.bal_chunks = pl.bal_chunks;
+    // a launch of more whole sequences than run at once hands out the longest first (a lane per sequence)
+    p.by_length = pl.schedule == VS_SCHED_PIPELINED && pl.num_splits == 1 && desc->B >= 2 && desc->B <= kBalMaxSeqs &&
+                  pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2);
     if (need > 0) {
         const size_t prow = partial_rows(desc, pl);
         p.part_o = (uint16_t*)workspace;

@@ -673,6 +673,28 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     }; // run_piece
 
     if constexpr (!BAL) {
+        if (p.by_length) {
+            // More workgroups than run at once, one per (sequence, KV head, row group): the longest
+            // sequences first. Workgroup slot j of an XCD is handed out when the ones before it run or are
+            // done, so the second round's work goes to the CUs in the order in which they fall free - the
+            // shortest of the first round takes the longest of the rest. In sequence order the launch lasted
+            // as long as its unluckiest CU (64 paged sequences of 1024 .. 8191 keys, 28 / 4 heads: 421 us
+            // against 354 us). The cost is the wait for the lengths before the first tile can be requested.
+            const int j = blockIdx.x >> 3;
+            const int rg = j % p.row_groups;
+            const int k = (j / p.row_groups) * 8 + (blockIdx.x & 7); // units by rank of their sequence, dealt over the XCDs
+            if (k >= p.B * p.Hkv) return;
+            const int rank = k / p.Hkv;
+            const int len = lane < p.B ? p.prefix_len[lane] : INT32_MIN; // out-of-range lengths sort like any other
+            int above = 0; // sequences that come before this lane's
+            for (int i = 0; i < p.B; ++i) {
+                const int li = __builtin_amdgcn_readlane(len, i);
+                above += (li > len || (li == len && i < lane)) ? 1 : 0;
+            }
+            const int b = __builtin_ctzll(__ballot(lane < p.B && above == rank));
+            run_piece(b, k % p.Hkv, rg, 0, p.keys_per_split, 0, true);
+            return;
+        }
         // workgroup id -> (sequence, KV head, row group, split), XCD-aware (see attention_mfma.hip)
         const int per_xcd = (p.total_wgs + 7) >> 3;
         const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -721,7 +743,7 @@ hipError_t launch_pipe(const AttnParams& p, hipStream_t s) {
         else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, true>), grid, dim3(NW * kWave), 0, s, p);
         return hipGetLastError();
     }
-    const dim3 grid(((p.total_wgs + 7) / 8) * 8);
+    const dim3 grid(p.by_length ? (p.B * p.Hkv + 7) / 8 * 8 * p.row_groups : (p.total_wgs + 7) / 8 * 8);
     if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, false>), grid, dim3(NW * kWave), 0, s, p);
     else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, false>), grid, dim3(NW * kWave), 0, s, p);
     return hipGetLastError();

@@ -59,6 +59,7 @@ struct AttnParams {
     int32_t row_groups;
     int32_t rows_per_group;     // waves_per_group * row blocks per wave * kRowBlock
     int32_t total_wgs;          // B * Hkv * num_splits * row_groups
+    int32_t by_length;          // pipelined kernel without key splits: workgroups take the sequences longest first
     int32_t* bal_table;         // balanced schedule: 64 words of workspace, the share boundaries (main kernel -> combine)
     int32_t bal_chunks;         // balanced schedule: equal shares of the batch's keys per (KV head, row group); else 0.
                                 // num_splits then counts partial-result slots per KV head (shares + sequences)
