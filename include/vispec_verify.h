@@ -77,7 +77,8 @@ typedef enum vs_status {
 
 typedef enum vs_dtype { VS_BF16 = 0, VS_F32 = 1 } vs_dtype;
 
-/* Which attention kernel to run. AUTO picks MFMA for bf16 and GENERIC for fp32. */
+/* Which attention kernel to run. AUTO picks MFMA for bf16 and GENERIC for fp32 (whose kernel uses the fp32
+ * matrix cores; for bf16 storage GENERIC is the cross-check without them). */
 typedef enum vs_attn_impl { VS_IMPL_AUTO = 0, VS_IMPL_GENERIC = 1, VS_IMPL_MFMA = 2 } vs_attn_impl;
 
 /* How the MFMA kernels are scheduled. LOOP streams 64-key tiles through LDS and runs a tile's

@@ -49,6 +49,7 @@ namespace {
 struct Plan {
     int32_t impl, rpw, waves, row_groups, rows, rows_pad, num_splits, keys_per_split, total_wgs, schedule;
     int32_t bal_chunks; // balanced schedule: shares per (KV head, row group); num_splits = slots per KV head
+    int32_t f32_rows; // fp32 storage: query rows per workgroup
     int32_t res_rb; // resident schedule: row blocks per workgroup (4, 2 or 1)
 };
 
@@ -114,12 +115,18 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     pl.rows_pad = (pl.rows + kRowBlock - 1) / kRowBlock * kRowBlock;
     pl.impl = d->impl == VS_IMPL_AUTO ? (d->dtype == VS_BF16 ? VS_IMPL_MFMA : VS_IMPL_GENERIC) : d->impl;
     if (pl.impl == VS_IMPL_GENERIC) {
+        // fp32 storage: eight waves share eight rows, or four where that keeps to one workgroup per CU (2 x 31
+        // nodes, 8 / 2 heads of 128 channels, 600 keys: 124 workgroups of four rows 12 us, 62 of eight 19 us; with
+        // more workgroups than CUs the second read of K and V costs more: 280 of four 26.8, 140 of eight 25.0 us);
+        // bf16 storage: a wave per row
+        const bool f32 = d->dtype == VS_F32;
+        pl.f32_rows = (int64_t)d->B * d->Hkv * ((pl.rows + 3) / 4) <= kNumCUs ? 4 : 8;
         pl.rpw = 0;
-        pl.waves = 1;
-        pl.row_groups = 1;
+        pl.waves = f32 ? 8 : 1;
+        pl.row_groups = f32 ? (pl.rows + pl.f32_rows - 1) / pl.f32_rows : 1;
         pl.num_splits = 1;
         pl.keys_per_split = 0;
-        pl.total_wgs = d->B * d->T * d->Hq;
+        pl.total_wgs = f32 ? d->B * d->Hkv * pl.row_groups : d->B * d->T * d->Hq;
         return pl;
     }
     const int nrb = pl.rows_pad / kRowBlock;
@@ -406,7 +413,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.num_splits = pl.num_splits;
     p.keys_per_split = pl.keys_per_split;
     p.row_groups = pl.row_groups;
-    p.rows_per_group = (pl.schedule == VS_SCHED_RESIDENT ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
+    p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.schedule == VS_SCHED_RESIDENT ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
     p.total_wgs = pl.total_wgs;
     p.bal_chunks = pl.bal_chunks;
     // a launch of more whole sequences than run at once hands out the longest first (a lane per sequence)
@@ -421,7 +428,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (pl.impl == VS_IMPL_GENERIC) {
-        e = launch_attention_generic(p, desc->dtype, s);
+        e = desc->dtype == VS_F32 ? launch_attention_f32(p, s) : launch_attention_generic(p, s);
     } else {
         e = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) ? launch_attention_mfma_pipe(p, pl.rpw, pl.waves, s)
             : pl.schedule == VS_SCHED_RESIDENT ? launch_attention_mfma_resident(p, pl.res_rb, s)
