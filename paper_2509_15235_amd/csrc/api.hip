@@ -280,11 +280,19 @@ size_t partial_rows(const vs_attn_desc* d, const Plan& pl) {
     return (size_t)(pl.bal_chunks > 0 ? 1 : d->B) * d->Hkv * pl.num_splits * pl.rows_pad;
 }
 
+// Splits merged by their own workgroups instead of a combine kernel: they wait for each other, so only where
+// all of them run at once (given an idle device; with a busy one the wait is bounded)
+bool merges_inside(const Plan& pl) {
+    return pl.schedule == VS_SCHED_RESIDENT && pl.num_splits > 1 && pl.num_splits <= kMergeMaxSplits && pl.total_wgs <= kNumCUs &&
+           pl.rows_pad <= (1 << 16); // offsets inside a row group's partial results are 32 bits wide
+}
+
 size_t workspace_bytes(const vs_attn_desc* d, const Plan& pl) {
     if (pl.impl != VS_IMPL_MFMA || pl.num_splits <= 1) return 0;
     const size_t prow = partial_rows(d, pl);
     return align_up(prow * d->d * sizeof(uint16_t)) + align_up(prow * 2 * sizeof(float)) +
-           (pl.bal_chunks > 0 ? align_up(kBalMaxChunks * sizeof(int32_t)) : 0);
+           (pl.bal_chunks > 0 ? align_up(kBalMaxChunks * sizeof(int32_t)) : 0) +
+           (merges_inside(pl) ? align_up((size_t)d->B * d->Hkv * pl.row_groups * kGateWords * sizeof(uint64_t)) : 0);
 }
 
 constexpr int kArgmaxChunk = kAcceptChunk;
@@ -394,6 +402,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.Hkv = desc->Hkv;
     p.d = desc->d;
     p.group = desc->Hq / desc->Hkv;
+    p.inv_group = 1.f / (float)p.group;
     p.rows = pl.rows;
     p.rows_pad = pl.rows_pad;
     p.max_prefix_len = desc->max_prefix_len;
@@ -423,7 +432,9 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         const size_t prow = partial_rows(desc, pl);
         p.part_o = (uint16_t*)workspace;
         p.part_ml = (float*)((char*)workspace + align_up(prow * desc->d * sizeof(uint16_t)));
-        if (pl.bal_chunks > 0) p.bal_table = (int32_t*)((char*)p.part_ml + align_up(prow * 2 * sizeof(float)));
+        char* behind = (char*)p.part_ml + align_up(prow * 2 * sizeof(float));
+        if (pl.bal_chunks > 0) p.bal_table = (int32_t*)behind;
+        if (merges_inside(pl)) p.gates = (uint64_t*)behind;
     }
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
@@ -433,7 +444,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         e = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) ? launch_attention_mfma_pipe(p, pl.rpw, pl.waves, s)
             : pl.schedule == VS_SCHED_RESIDENT ? launch_attention_mfma_resident(p, pl.res_rb, s)
                                                : launch_attention_mfma(p, pl.rpw, pl.waves, s);
-        if (e == hipSuccess && pl.num_splits > 1) e = launch_attention_combine(p, desc->dtype, s);
+        if (e == hipSuccess && pl.num_splits > 1 && !p.gates) e = launch_attention_combine(p, desc->dtype, s);
     }
     return e == hipSuccess ? VS_OK : VS_ERR_HIP;
 }

@@ -458,11 +458,10 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const AttnParams p) 
                 }
         } else {
             if (row_base + rb * kRowBlock >= p.rows) continue; // whole block is padding
-            const int64_t blk = part_block(p, (int64_t)b * p.Hkv + kvh, split, (row_base >> 5) + rb);
-            uint16_t* po = p.part_o + blk * (kRowBlock * D);
+            uint16_t* po = p.part_o + part_block<D>(p, (int64_t)b * p.Hkv + kvh, split, (row_base >> 5) + rb);
             const float inv = l > 0.f ? 1.f / l : 0.f; // no visible key in this split: zeros, weight 0
 #pragma unroll
-            for (int db = 0; db < DB; ++db) store_partial<D>(po, db, lane, acc[rb][db], inv);
+            for (int db = 0; db < DB; ++db) store_partial(p, po, db, lane, acc[rb][db], inv);
             if (half == 0) {
                 const f32x2 ml = {m2[rb], l};
                 const int64_t mlb = ml_block(p, (int64_t)b * p.Hkv + kvh, split, (row_base >> 5) + rb);
@@ -513,9 +512,7 @@ __global__ __launch_bounds__(kWave) void attn_combine_kernel(const AttnParams p)
     const int32_t S = BAL ? 0 : p.prefix_len[b];
     const int64_t punit = BAL ? kvh : unit; // whose partial-result slots these are
     const f32x2* gml = (const f32x2*)p.part_ml + ml_block(p, punit, 0, rbk) + col; // + slot * kRowBlock
-    const int64_t blk0 = part_block(p, punit, 0, rbk);
-    const int64_t blk_stride = p.rows_pad / kRowBlock; // blocks per slot
-    const uint16_t* po0 = p.part_o + blk0 * (kRowBlock * D) + ((db * 2) * 64 + lane) * 8;
+    const uint16_t* po0 = p.part_o + part_block<D>(p, punit, 0, rbk) + (db * 2) * piece_stride(p) + lane * 8;
 
     float den = 0.f, M = -INFINITY;
     f32x4 num[4];
@@ -551,9 +548,9 @@ __global__ __launch_bounds__(kWave) void attn_combine_kernel(const AttnParams p)
 #pragma unroll
         for (int u = 0; u < BATCH; ++u)
             if (s0 + u < nload) {
-                const uint16_t* po = po0 + slot_of(s0 + u) * blk_stride * (kRowBlock * D);
+                const uint16_t* po = po0 + slot_of(s0 + u) * 512;
 #pragma unroll
-                for (int hp = 0; hp < 2; ++hp) o[u][hp] = __builtin_nontemporal_load((const u32x4*)(po + hp * 512));
+                for (int hp = 0; hp < 2; ++hp) o[u][hp] = __builtin_nontemporal_load((const u32x4*)(po + hp * piece_stride(p)));
             }
         if (!BAL && s0 == 0) {
             if (!prefix_ok(p, S)) return;

@@ -45,7 +45,8 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     constexpr int SPW = (KQ * BPS + kResWaves - 1) / kResWaves; // copy blocks per wave, stage and tensor
     constexpr int TILE_BYTES = 2 * NT * SUB * 2;
     constexpr int MERGE_BYTES = kResWaves * (DB * 1024 + 128) * 4; // every wave's exchange area: accumulators, max, sum
-    constexpr int SMEM_ELEMS = (TILE_BYTES > MERGE_BYTES ? TILE_BYTES : MERGE_BYTES) / 2;
+    constexpr int Q_BYTES = NRB * kRowBlock * D * 2;
+    constexpr int SMEM_ELEMS = (TILE_BYTES + Q_BYTES > MERGE_BYTES ? TILE_BYTES + Q_BYTES : MERGE_BYTES) / 2;
     static_assert(NT >= 1 && NT <= kResMaxTiles, "a split holds at most kResidentMaxKeys keys");
 
     // tiles: K[t] at smem + t*SUB, V[t] at smem + (NT + t)*SUB; after the last tile has been
@@ -55,6 +56,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     __shared__ int32_t sflag;
     uint16_t* sK = smem;
     uint16_t* sV = smem + NT * SUB;
+    uint16_t* sQ = smem + 2 * NT * SUB; // queries: row blocks of D-channel rows (see load_q_piece)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -136,14 +138,12 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     const int row_base = rg * (NRB * kRowBlock) + rbw * kRowBlock;
     const bool wave_active = row_base < p.rows;
     const int r = min(row_base + col, p.rows - 1); // rows past the end repeat the last row (results discarded)
-    const int node = r / p.group;
-    const int hq = kvh * p.group + (r - node * p.group);
-    bf16x8 qf[KS];
-    {
-        const uint16_t* qr = (const uint16_t*)p.q + (((int64_t)b * p.T + node) * p.Hq + hq) * D + half * 8;
+    const int node = row_node(p, r);
+    // the waves of a row block share the fetch of its queries
+    constexpr int QPW = (KS + KQ - 1) / KQ; // pieces per wave
+    u32x4 qreg[QPW];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qr + ks * 16));
-    }
+    for (int i = 0; i < QPW; ++i) qreg[i] = load_q_piece<D>(p, b, kvh, row_base, min(kq * QPW + i, KS - 1), lane);
     // the row's ancestor mask, when the caller supplies the masks: requested ahead of the later stages
     uint64_t mask_given = 0;
     if (p.tree_mask && p.tree_keys != 0) mask_given = p.tree_mask[(int64_t)b * p.T + node];
@@ -168,6 +168,10 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
 
     const int nk = S + p.tree_keys;
     if (k0 >= nk) return;
+    const bool final_rows = p.num_splits == 1;
+    const bool merge = p.gates != nullptr; // uniform over the launch
+    MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, 0};
+    if (merge && tid == 0) merge_open(gate);
     const int k1 = min(nk, k0 + p.keys_per_split);
     const int nt = (k1 - k0 + kTileKeys - 1) / kTileKeys; // tiles of this split, <= kResMaxTiles
 
@@ -185,6 +189,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     const int t16 = lane & 15;
     const int v_lane = half * 128 + (t16 >> 2) * 32 + ((lane >> 4) & 1) * 16 + ((t16 >> 1) & 1) * 8 + (t16 & 1) * 4;
 
+    bf16x8 qf[KS];
     auto tile = [&](auto masked_tag, int t) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         const uint16_t* kt_ = sK + t * SUB;
@@ -275,7 +280,15 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
                 *(u32x4*)((char*)(sV + t * SUB) + vo) = live ? vreg[j][u] : zero;
             }
         }
+        if (j == 0) {
+#pragma unroll
+            for (int i = 0; i < QPW; ++i) store_q_piece<D>(sQ + rbw * (kRowBlock * D), qreg[i], min(kq * QPW + i, KS - 1), lane);
+        }
         __syncthreads();
+        if (j == 0) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) qf[ks] = read_q_frag<D>(sQ + rbw * (kRowBlock * D), ks, col, half);
+        }
         const int t = kq * PPM + j;
         if (wave_active && t < nt) {
             if (t < n_plain) tile(std::false_type{}, t);
@@ -317,7 +330,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
         mine[NP * 512 + 64 + lane] = lsum;
     }
     __syncthreads();
-    if (!wave_active || kq >= OWNERS) return;
+    if (wave_active && kq < OWNERS) {
 
     // reference and sum over all key parts, the same arithmetic in every wave of the row block
     float mo[KQ], lo[KQ];
@@ -339,10 +352,9 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     }
     const float l = half_sum(lall);
     const int r_local = row_base + col;
-    const bool final_rows = p.num_splits == 1;
     const float inv = final_rows ? 1.f / l : (l > 0.f ? 1.f / l : 0.f); // partials: no visible key in this split -> zeros, weight 0
-    uint16_t* orow = (uint16_t*)p.out + (((int64_t)b * p.T + node) * p.Hq + hq) * D;
-    uint16_t* po = p.part_o + part_block(p, (int64_t)b * p.Hkv + kvh, split, row_base >> 5) * (kRowBlock * D);
+    uint16_t* orow = (uint16_t*)p.out + row_offset(p, b, kvh, r, node);
+    uint16_t* po = p.part_o + part_block<D>(p, (int64_t)b * p.Hkv + kvh, split, row_base >> 5);
 
     // this wave's pieces: lane (col, half) holds, for row `col`, channels db*32 + 8*(q/4) + 4*half + q%4
     auto finish = [&](auto kq_tag) __attribute__((always_inline)) {
@@ -381,7 +393,9 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
             } else {
                 const u32x2 w0 = pack_partial(r[0], r[1], r[2], r[3], inv), w1 = pack_partial(r[4], r[5], r[6], r[7], inv);
                 const u32x4 w = {w0[0], w0[1], w1[0], w1[1]};
-                *(u32x4*)(po + (pc * 64 + lane) * 8) = w;
+                uint16_t* dst = po + pc * piece_stride(p);
+                if (merge) __builtin_amdgcn_raw_buffer_store_b128(w, span_of(dst), lane * 16, 0, kDeviceScope);
+                else *(u32x4*)(dst + lane * 8) = w;
             }
         }
     };
@@ -398,7 +412,15 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     if (!final_rows && kq == 0 && half == 0) {
         const f32x2 ml = {M, l};
         const int64_t mlb = ml_block(p, (int64_t)b * p.Hkv + kvh, split, row_base >> 5);
-        *(f32x2*)(p.part_ml + (mlb + col) * 2) = ml;
+        float* dst = p.part_ml + mlb * 2;
+        if (merge) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), span_of(dst), col * 8, 0, kDeviceScope);
+        else *(f32x2*)(dst + col * 2) = ml;
+    }
+    }
+    if (merge) {
+        const int nrb = p.rows_pad / kRowBlock, rb0 = rg * NRB;
+        merge_splits<D>(p, gate, b, kvh, rb0, min(rb0 + NRB, nrb), split, (nk + p.keys_per_split - 1) / p.keys_per_split, kResWaves,
+                        (uint32_t*)sp);
     }
 }
 

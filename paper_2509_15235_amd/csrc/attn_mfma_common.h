@@ -34,11 +34,48 @@ __device__ __forceinline__ float half_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// node of query row r (r / group): the quotient is below 64, so the fp32 product is off by less than one
+__device__ __forceinline__ int row_node(const AttnParams& p, int r) {
+    int n = (int)((float)r * p.inv_group);
+    const int rem = r - n * p.group;
+    n += (rem >= p.group) - (rem < 0);
+    return n;
+}
+// element offset of query row r of (sequence b, KV head kvh) in q and out
+__device__ __forceinline__ int64_t row_offset(const AttnParams& p, int b, int kvh, int r, int node) {
+    return (((int64_t)b * p.T + node) * p.Hq + kvh * p.group + (r - node * p.group)) * p.d;
+}
+
+// ---- Queries through LDS. As MFMA operands neighbouring lanes hold different rows; read like that from
+// memory every four lanes touch four cache lines, and the eight loads of a 32-row block keep the CU's address
+// units busy for 0.2 us - with eight waves that is 1.7 us in which no key can be requested. So a row
+// block is fetched in whole rows (one load instruction = 1 KB of consecutive rows), stored with chunk c of
+// row r at position c ^ r % (chunks per row) - conflict-free both ways - and read back as operands.
+// Piece i of D / 16 pieces; the row block starts at row_base (rows past the end repeat the last one).
+template <int D>
+__device__ __forceinline__ u32x4 load_q_piece(const AttnParams& p, int b, int kvh, int row_base, int i, int lane) {
+    constexpr int LPR = D / 8, RPI = 64 / LPR;
+    const int r = min(row_base + RPI * i + lane / LPR, p.rows - 1);
+    return *(const u32x4*)((const uint16_t*)p.q + row_offset(p, b, kvh, r, row_node(p, r)) + (lane % LPR) * 8);
+}
+template <int D>
+__device__ __forceinline__ void store_q_piece(uint16_t* sq, u32x4 v, int i, int lane) {
+    constexpr int LPR = D / 8, RPI = 64 / LPR;
+    const int r = RPI * i + lane / LPR;
+    *(u32x4*)(sq + r * D + ((lane % LPR) ^ (r % LPR)) * 8) = v;
+}
+template <int D>
+__device__ __forceinline__ bf16x8 read_q_frag(const uint16_t* sq, int ks, int col, int half) {
+    constexpr int LPR = D / 8;
+    return __builtin_bit_cast(bf16x8, *(const u32x4*)(sq + col * D + ((2 * ks + half) ^ (col % LPR)) * 8));
+}
+
 // Partial results of one (sequence, KV head, split, 32-row block): D/32 accumulator blocks,
-// each stored as 2 x [64 lanes x 8 values] (register r = 4*q4 + e of lane l at
-// ((db*2 + q4/2)*64 + l)*8 + (q4%2)*4 + e: a lane's eight values are one 16-byte piece, a wave's
-// store or load of a piece is 1 KB of consecutive memory), followed elsewhere by 32 x (max, sum)
-// in fp32. A partial output
+// each stored as 2 pieces of [64 lanes x 8 values] (register r = 4*q4 + e of lane l in piece
+// db*2 + q4/2 at l*8 + (q4%2)*4 + e: a wave's store or load of a piece is 1 KB of consecutive memory),
+// and 32 x (max, sum) in fp32. The splits of a piece lie next to each other - [unit][row block][piece]
+// [split] - as do a row block's (max, sum) pairs: what a wave gathers when it merges a piece is one run of
+// memory, in one page instead of one page per split. A partial output
 // row is divided by its own sum before it is rounded: a convex combination of V rows, as large
 // as the largest visible |V| and no larger. It is stored as bf16, which has V's own exponent
 // range (fp16 would turn any |v| > 65504 into infinity) and costs half the bytes of fp32: what a
@@ -57,25 +94,200 @@ __device__ __forceinline__ f32x4 unpack_partial(u32x2 w) {
                      __uint_as_float(w[1] & 0xffff0000u)};
     return r;
 }
-// One 32-channel accumulator block of a row block, divided by the rows' sums: two 16-byte pieces per
-// lane. `blk` = start of the (unit, split, row block) partial block, db = channel block.
+// elements: piece 0 of (unit, split, row block), and from one piece to the next
 template <int D>
-__device__ __forceinline__ void store_partial(uint16_t* blk, int db, int lane, const f32x16& a, float inv) {
+__device__ __forceinline__ int64_t part_block(const AttnParams& p, int64_t unit, int split, int rbk) {
+    return ((unit * (p.rows_pad / kRowBlock) + rbk) * (D / 16) * p.num_splits + split) * 512;
+}
+__device__ __forceinline__ int64_t piece_stride(const AttnParams& p) { return (int64_t)p.num_splits * 512; }
+
+// Partial results travel between workgroups on different XCDs: stores that write through to memory and loads
+// that do not stop at this XCD's L2 (cache policy bit sc1 = device scope).
+constexpr int kDeviceScope = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t span_of(const void* base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00027000);
+}
+
+// One 32-channel accumulator block of a row block, divided by the rows' sums: two 16-byte pieces per
+// lane. `blk` = piece 0 of the (unit, split, row block), db = channel block.
+template <bool MERGE = false>
+__device__ __forceinline__ void store_partial(const AttnParams& p, uint16_t* blk, int db, int lane, const f32x16& a, float inv) {
 #pragma unroll
     for (int hp = 0; hp < 2; ++hp) {
         const u32x2 lo = pack_partial(a[8 * hp], a[8 * hp + 1], a[8 * hp + 2], a[8 * hp + 3], inv);
         const u32x2 hi = pack_partial(a[8 * hp + 4], a[8 * hp + 5], a[8 * hp + 6], a[8 * hp + 7], inv);
         const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
-        *(u32x4*)(blk + ((db * 2 + hp) * 64 + lane) * 8) = w;
+        uint16_t* dst = blk + (db * 2 + hp) * piece_stride(p);
+        if constexpr (MERGE) __builtin_amdgcn_raw_buffer_store_b128(w, span_of(dst), lane * 16, 0, kDeviceScope);
+        else *(u32x4*)(dst + lane * 8) = w;
     }
-}
-__device__ __forceinline__ int64_t part_block(const AttnParams& p, int64_t unit, int split, int rbk) {
-    return (unit * p.num_splits + split) * (int64_t)(p.rows_pad / kRowBlock) + rbk;
 }
 // (max, sum) pairs are grouped per row block with the splits adjacent: index of the
 // first of the 32 rows of (unit, rbk, split), in pairs.
 __device__ __forceinline__ int64_t ml_block(const AttnParams& p, int64_t unit, int split, int rbk) {
     return ((unit * (p.rows_pad / kRowBlock) + rbk) * p.num_splits + split) * (int64_t)kRowBlock;
+}
+
+// ---- Merging key splits inside the kernel that computes them.
+// The workgroups of a row group (same sequence, KV head and rows, n live splits of the keys) meet at a
+// barrier in the workspace and then merge the row group together, every one a share of the row blocks' pieces: one
+// trip to memory for the partials of n splits, spread over n CUs, in place of a second kernel (launch,
+// arguments, lengths, the same trip, drain: 5 us). A barrier between workgroups only ends when all of
+// them get to run, which nobody promises while other streams hold CUs. So the wait is bounded: who waits
+// longer than kMergeWait hands its share over to the workgroup that arrives last and leaves.
+//   word 0  kMergeTag << 40 | abandoned shares << 8 | arrivals. Anything else (first use of the workspace)
+//           counts as zero and is replaced before the first arrival; the last arrival puts it back to zero.
+//   word 1  changes when all have arrived (any initial value)
+// The call before on the same workspace has ended (calls that share one are ordered), so both words are at rest.
+static_assert(kMergeMaxSplits == 32, "bits of the abandoned set");
+constexpr uint64_t kMergeTag = 0xffc3a5ull;           // no partial result or (max, sum) pair looks like this (a NaN)
+constexpr uint64_t kMergeZero = kMergeTag << 40;
+constexpr uint64_t kMergeWait = 2000;                 // 20 us of the 100 MHz clock
+
+struct MergeGate {
+    uint64_t* word; // null: the splits are merged by the combine kernel
+    uint64_t gen;   // word 1 before anybody arrived (thread 0)
+};
+__device__ __forceinline__ uint64_t gate_load(const uint64_t* w) {
+    return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Thread 0 of every workgroup of the row group, any time before it arrives.
+__device__ __forceinline__ void merge_open(MergeGate& g) {
+    g.gen = gate_load(g.word + kGateFlag);
+    uint64_t w = gate_load(g.word);
+    if ((w >> 40) != kMergeTag) // lost to another workgroup: then it did the same
+        __hip_atomic_compare_exchange_strong(g.word, &w, kMergeZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Thread 0, after every wave's partial results are in memory. Returns the splits whose shares this workgroup
+// has to merge besides its own; `go` false: its own share was handed over.
+__device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, int split, int n, bool& go) {
+    go = true;
+    const uint64_t old = __hip_atomic_fetch_add(g.word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((int)(old & 0xff) == n - 1) {
+        __hip_atomic_store(g.word, kMergeZero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(g.word + kGateFlag, g.gen + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return (uint32_t)(old >> 8);
+    }
+    const uint64_t t0 = wall_clock64();
+    while (gate_load(g.word + kGateFlag) == g.gen) {
+        __builtin_amdgcn_s_sleep(1);
+        if (wall_clock64() - t0 > kMergeWait) {
+            uint64_t w = gate_load(g.word);
+            // zero or n arrivals: the last one has come in the meantime
+            while ((int)(w & 0xff) != 0 && (int)(w & 0xff) != n) {
+                if (__hip_atomic_compare_exchange_strong(g.word, &w, w | (256ull << split), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT)) {
+                    go = false;
+                    return 0;
+                }
+            }
+            break;
+        }
+    }
+    return 0;
+}
+// Half a piece (eight channels of the 32 rows of a row block, see store_partial: the 32 lanes of one half of the
+// accumulators): where it is read and written. The addresses are worked out before the wait, the rest after it.
+struct MergeItem {
+    const float* ml;
+    const uint16_t* po;
+    uint16_t* out; // null: a row past the last one
+};
+template <int D>
+__device__ __forceinline__ MergeItem merge_item(const AttnParams& p, int b, int kvh, int rbk, int half_piece, int lane) {
+    const int64_t unit = (int64_t)b * p.Hkv + kvh;
+    const int piece = half_piece >> 1, hl = half_piece & 1;
+    MergeItem it;
+    it.ml = p.part_ml + ml_block(p, unit, 0, rbk) * 2;
+    it.po = p.part_o + part_block<D>(p, unit, 0, rbk) + piece * piece_stride(p) + hl * 256;
+    const int r = rbk * kRowBlock + (lane & 31);
+    it.out = r < p.rows ? (uint16_t*)p.out + row_offset(p, b, kvh, r, row_node(p, r)) + piece * 16 + 4 * hl + 8 * (lane >> 5) : nullptr;
+    return it;
+}
+// log-sum-exp of the item over n splits, then the final rows' channels. One wave: lanes r and r + 32 share row r
+// and take every other split. BATCH pairs of splits are in flight together; there is no branch around a load
+// (past the last split the last one is read again, with weight 0).
+template <int BATCH>
+__device__ __forceinline__ void merge_run_by(const MergeItem& it, int n) {
+    const __amdgpu_buffer_rsrc_t ml = span_of(it.ml), po = span_of(it.po);
+    const int row = threadIdx.x & 31, odd = (threadIdx.x >> 5) & 1;
+    float M = -INFINITY, den = 0.f, num[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) num[e] = 0.f;
+    for (int s0 = 0; s0 < n; s0 += 2 * BATCH) {
+        u32x2 w[BATCH];
+        u32x4 o[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int s = min(s0 + 2 * u + odd, n - 1);
+            w[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(ml, s * (kRowBlock * 8) + row * 8, 0, kDeviceScope));
+            o[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(po, s * 1024 + row * 16, 0, kDeviceScope));
+        }
+        float Mb = M;
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) Mb = fmaxf(Mb, __uint_as_float(w[u][0]));
+        Mb = half_max(Mb);
+        const float Ms = Mb == -INFINITY ? 0.f : Mb; // no visible key so far: all weights are 2^-inf = 0
+        if (s0 > 0) {
+            const float resc = __builtin_amdgcn_exp2f(M - Ms);
+            den *= resc;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) num[e] *= resc;
+        }
+        M = Mb;
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const float f = __builtin_amdgcn_exp2f(__uint_as_float(w[u][0]) - Ms) * (s0 + 2 * u + odd < n ? __uint_as_float(w[u][1]) : 0.f);
+            den += f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                num[2 * e] += f * __uint_as_float(o[u][e] << 16);
+                num[2 * e + 1] += f * __uint_as_float(o[u][e] & 0xffff0000u);
+            }
+        }
+    }
+    den = half_sum(den);
+    float r[4]; // lower half: channels 0 .. 3 of both halves added up, upper half: channels 4 .. 7
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const u32x2 x = __builtin_amdgcn_permlane32_swap(__float_as_uint(num[e]), __float_as_uint(num[4 + e]), false, false);
+        r[e] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    }
+    if (it.out) *(u32x2*)it.out = pack_partial(r[0], r[1], r[2], r[3], 1.f / den);
+}
+__device__ __forceinline__ void merge_run(const MergeItem& it, int n) {
+    if (n <= 4) merge_run_by<2>(it, n);
+    else if (n <= 8) merge_run_by<4>(it, n);
+    else merge_run_by<8>(it, n);
+}
+// The end of a split's workgroup: all waves, after their last partial store. Row blocks rb0 .. rb1 - 1 belong to
+// the row group; `s_word` is two words of LDS that nobody else uses any more.
+template <int D>
+__device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGate& g, int b, int kvh, int rb0, int rb1, int split, int n,
+                                             int waves, uint32_t* s_word) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int NP = D / 8; // half pieces per row block
+    const int items = (rb1 - rb0) * NP;
+    int i = split + n * wave;
+    MergeItem it{};
+    if (i < items) it = merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane);
+    __builtin_amdgcn_s_waitcnt(wait_vm(0)); // this wave's partial results are in memory
+    __syncthreads();
+    if (tid == 0) {
+        bool go;
+        s_word[0] = merge_meet(g, split, n, go);
+        s_word[1] = go;
+    }
+    __syncthreads();
+    if (s_word[1] == 0) return;
+    while (i < items) {
+        merge_run(it, n);
+        i += n * waves;
+        if (i < items) it = merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane);
+    }
+    for (uint32_t shares = s_word[0]; shares; shares &= shares - 1) // handed over by workgroups that left
+        for (i = __builtin_ctz(shares) + n * wave; i < items; i += n * waves)
+            merge_run(merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane), n);
 }
 
 // ---- Balanced schedule: the key ranges of a whole ragged batch, cut into shares of equal cost.

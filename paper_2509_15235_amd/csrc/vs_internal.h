@@ -27,6 +27,10 @@ constexpr int kArgmaxBlock = 256;
 constexpr int kAcceptChunk = 4096; // floats of a logits row per workgroup of the scans: 256 threads x 4 x 16 bytes
 constexpr int kBalMaxSeqs = 64;   // balanced schedule: sequences per call (a lane each)
 constexpr int kBalMaxChunks = 64; // ... and shares per (KV head, row group)
+constexpr int kMergeMaxSplits = 32; // key splits that the workgroups themselves merge (attn_mfma_common.h)
+constexpr int kGateWords = 32;      // 64-bit words of a row group's gate: two cache lines, so that neither gates nor the two words of one
+                                    // gate wait for each other
+constexpr int kGateFlag = 16;       // its second word
 constexpr int kResidentMaxKeys = 192; // keys of one split that the resident attention kernel keeps in LDS (six 32-key tiles:
                                       // with eight, its four-row-block form runs out of registers)
 
@@ -41,8 +45,10 @@ struct AttnParams {
     const uint64_t* tree_mask;  // may be null
     const int32_t* block_table; // paged only
     int32_t* status;            // may be null
-    uint16_t* part_o;           // [unit][split][rows_pad][d] partial outputs, each row normalised by its own sum, bf16
-    float* part_ml;             // [unit][split][rows_pad][2] running max (log2 domain), sum
+    uint16_t* part_o;           // partial outputs, each row normalised by its own sum, bf16 (layout: attn_mfma_common.h)
+    float* part_ml;             // [unit][row block][split][32][2] running max (log2 domain), sum
+    uint64_t* gates;            // two words per (unit, row group): the splits are merged by the workgroups that
+                                // computed them (attn_mfma_common.h); null: by the combine kernel
     int32_t B, T, Hq, Hkv, d, group;
     int32_t tree_keys;          // T when the queries' own K/V sit behind the prefix (verification), 0 when they
                                 // attend to the prefix alone (the vision adaptor's compression attention)
@@ -52,6 +58,7 @@ struct AttnParams {
     int32_t paged, block_size, block_shift, max_blocks, num_blocks;
     int64_t capacity;
     int64_t stride_seq, stride_block, stride_head, stride_tok;
+    float inv_group;            // 1 / group (row_node)
     float scale;                // softmax scale
     float scale_log2;           // softmax scale * log2(e)
     int32_t num_splits;         // grid extent over key splits
