@@ -175,13 +175,10 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     const int k1 = min(nk, k0 + p.keys_per_split);
     const int nt = (k1 - k0 + kTileKeys - 1) / kTileKeys; // tiles of this split, <= kResMaxTiles
 
-    // ---- this wave's key part: tiles kq * PPM + j, j = 0 .. PPM - 1 (those below nt)
-    float m2 = -INFINITY, lsum = 0.f; // running reference (log2 domain, scaled) and this lane's share of the sum
-    f32x16 acc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[db][q] = 0.f;
+    // ---- this wave's key part: tiles kq * PPM + j, j = 0 .. PPM - 1 (those below nt). The scores of a stage are
+    // computed as soon as it is in LDS; the softmax comes once, over all of the part's keys (no running
+    // reference, nothing to rescale, and its independent halves hide each other's latency), and then the output.
+    // (Tile after tile, each with its own softmax, the same work took 0.8 us longer per layer.)
 
     // per-lane LDS offsets (elements); everything else is a compile-time immediate
     const int k_lane[2] = {(col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (4 * half)) * 8,
@@ -190,78 +187,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     const int v_lane = half * 128 + (t16 >> 2) * 32 + ((lane >> 4) & 1) * 16 + ((t16 >> 1) & 1) * 8 + (t16 & 1) * 4;
 
     bf16x8 qf[KS];
-    auto tile = [&](auto masked_tag, int t) __attribute__((always_inline)) {
-        constexpr bool MASKED = decltype(masked_tag)::value;
-        const uint16_t* kt_ = sK + t * SUB;
-        const uint16_t* vt_ = sV + t * SUB + v_lane;
-        // S^T = K . Q^T: lane (col, half) gets keys 8*(q/4) + 4*half + q%4 of row `col`
-        f32x16 s;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) s[q] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, *(const u32x4*)(kt_ + k_lane[ks & 1] + ks * 256));
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s, 0, 0, 0);
-        }
-        if constexpr (MASKED) {
-            const int rel = k0 + t * kTileKeys + 4 * half - S; // tree slot of this lane's key 0 (negative: prefix)
-            const uint32_t tree_end = (uint32_t)(k1 - S);
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int sh = rel + 8 * (q >> 2) + (q & 3);
-                const uint32_t bit = (uint32_t)(mask >> (sh & 63)) & 1u;
-                const bool vis = (sh < 0) | (((uint32_t)sh < tree_end) & (bit != 0));
-                s[q] = vis ? s[q] : -INFINITY;
-            }
-        }
-        float mx = max3(s[0], s[1], s[2]);
-#pragma unroll
-        for (int q = 3; q < 15; q += 2) mx = max3(mx, s[q], s[q + 1]);
-        mx = fmaxf(mx, s[15]);
-        mx = half_max(mx);
-        // lazy reference: moves only when the tile's maximum exceeds it by more than kLazy
-        const float mt = mx * p.scale_log2;
-        const float m_new = (mt > m2 + kLazy) ? mt : m2;
-        const float m_use = (MASKED && m_new == -INFINITY) ? 0.f : m_new; // no visible key yet
-        const float alpha = __builtin_amdgcn_exp2f(m2 - m_use);
-        m2 = m_new;
-        float ps0 = 0.f, ps1 = 0.f;
-#pragma unroll
-        for (int q = 0; q < 16; q += 2) {
-            s[q] = __builtin_amdgcn_exp2f(fmaf(s[q], p.scale_log2, -m_use)); // exp2(-inf) = 0
-            s[q + 1] = __builtin_amdgcn_exp2f(fmaf(s[q + 1], p.scale_log2, -m_use));
-            ps0 += s[q];
-            ps1 += s[q + 1];
-        }
-        lsum = lsum * alpha + (ps0 + ps1);
-        if (__any(alpha != 1.f)) {
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) acc[db][q] *= alpha;
-        }
-        bf16x8 pf[2];
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            u32x4 w;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const f32x2 pr = {s[8 * sl + 2 * e], s[8 * sl + 2 * e + 1]};
-                w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
-            }
-            pf[sl] = __builtin_bit_cast(bf16x8, w);
-        }
-        // O^T += V^T . P^T: the A operand comes from two transposing reads of 4 keys x 16 channels
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512 + 256));
-                const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[sl], acc[db], 0, 0, 0);
-            }
-    };
+    f32x16 s[PPM];
     // tiles that end at or before min(S, k1) hold prefix keys only
     const int n_plain = max(0, min(S, k1) - k0) / kTileKeys;
 #pragma unroll
@@ -289,11 +215,74 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) qf[ks] = read_q_frag<D>(sQ + rbw * (kRowBlock * D), ks, col, half);
         }
-        const int t = kq * PPM + j;
-        if (wave_active && t < nt) {
-            if (t < n_plain) tile(std::false_type{}, t);
-            else tile(std::true_type{}, t);
+        // S^T = K . Q^T: lane (col, half) gets keys 8*(q/4) + 4*half + q%4 of row `col`
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s[j][q] = 0.f;
+        const int t = min(kq * PPM + j, NT - 1);
+        const uint16_t* kt_ = sK + t * SUB;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 a = __builtin_bit_cast(bf16x8, *(const u32x4*)(kt_ + k_lane[ks & 1] + ks * 256));
+            s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[j], 0, 0, 0);
         }
+    }
+    const int my_tiles = max(0, min(PPM, nt - kq * PPM)); // tiles past the split's last one were zeros or a repeat
+    if (kq * PPM + PPM > n_plain) { // uniform: tree slots, the end of the range, or no such tile
+#pragma unroll
+        for (int j = 0; j < PPM; ++j) {
+            const int first = k0 + (kq * PPM + j) * kTileKeys;
+            const uint32_t w = tile_visible(mask, first - S, j < my_tiles ? k1 - first : 0) >> (4 * half);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s[j][q] = visible_or_inf(s[j][q], w, 8 * (q >> 2) + (q & 3));
+        }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < PPM; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; q += 2) mx = max3(mx, s[j][q], s[j][q + 1]);
+    const float m2 = half_max(mx) * p.scale_log2; // reference (log2 domain); -inf: no visible key
+    const float m_use = m2 == -INFINITY ? 0.f : m2;
+    float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+    for (int j = 0; j < PPM; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; q += 2) {
+            s[j][q] = __builtin_amdgcn_exp2f(fmaf(s[j][q], p.scale_log2, -m_use)); // exp2(-inf) = 0
+            s[j][q + 1] = __builtin_amdgcn_exp2f(fmaf(s[j][q + 1], p.scale_log2, -m_use));
+            ps0 += s[j][q];
+            ps1 += s[j][q + 1];
+        }
+    const float lsum = ps0 + ps1; // this lane's share of the sum
+    // O^T += V^T . P^T: the A operand comes from two transposing reads of 4 keys x 16 channels
+    f32x16 acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[db][q] = 0.f;
+#pragma unroll
+    for (int j = 0; j < PPM; ++j) {
+        const uint16_t* vt_ = sV + min(kq * PPM + j, NT - 1) * SUB + v_lane;
+        bf16x8 pf[2];
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            u32x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f32x2 pr = {s[j][8 * sl + 2 * e], s[j][8 * sl + 2 * e + 1]};
+                w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
+            }
+            pf[sl] = __builtin_bit_cast(bf16x8, w);
+        }
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512 + 256));
+                const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[sl], acc[db], 0, 0, 0);
+            }
     }
 
     // ---- merge the key parts through LDS (log-sum-exp) and write the rows. The work is shared: a row
@@ -352,48 +341,51 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     }
     const float l = half_sum(lall);
     const int r_local = row_base + col;
-    const float inv = final_rows ? 1.f / l : (l > 0.f ? 1.f / l : 0.f); // partials: no visible key in this split -> zeros, weight 0
+    const float inv = l > 0.f ? 1.f / l : 0.f; // no visible key in this split (partials only): zeros, weight 0
     uint16_t* orow = (uint16_t*)p.out + row_offset(p, b, kvh, r, node);
     uint16_t* po = p.part_o + part_block<D>(p, (int64_t)b * p.Hkv + kvh, split, row_base >> 5);
 
-    // this wave's pieces: lane (col, half) holds, for row `col`, channels db*32 + 8*(q/4) + 4*half + q%4
+    // this wave's pieces: lane (col, half) holds, for row `col`, channels db*32 + 8*(q/4) + 4*half + q%4. All of
+    // them are read and added up before the first store (one trip through LDS, not one per piece).
     auto finish = [&](auto kq_tag) __attribute__((always_inline)) {
         constexpr int MY = decltype(kq_tag)::value;
+        float r[PPK][8];
 #pragma unroll
         for (int i = 0; i < PPK; ++i) {
             const int pc = MY * PPK + i, db = pc >> 1, hp = pc & 1;
-            float r[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) r[e] = 0.f;
+            for (int e = 0; e < 8; ++e) r[i][e] = 0.f;
 #pragma unroll
             for (int o = 0; o < KQ; ++o) {
                 if (o == MY) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) r[e] += fo[o] * acc[db][8 * hp + e];
+                    for (int e = 0; e < 8; ++e) r[i][e] += fo[o] * acc[db][8 * hp + e];
                 } else {
                     const float* src = sm + (rbw * KQ + o) * XCH + pc * 512 + lane * 4;
                     const f32x4 a0 = *(const f32x4*)src, a1 = *(const f32x4*)(src + 256);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        r[e] += fo[o] * a0[e];
-                        r[4 + e] += fo[o] * a1[e];
+                        r[i][e] += fo[o] * a0[e];
+                        r[i][4 + e] += fo[o] * a1[e];
                     }
                 }
             }
-            if (final_rows) {
-                if (r_local < p.rows) {
+        }
+        if (final_rows) {
+            if (r_local < p.rows) {
 #pragma unroll
-                    for (int hh = 0; hh < 2; ++hh) {
-                        u32x2 w;
-                        w[0] = pack_bf16x2(r[4 * hh] * inv, r[4 * hh + 1] * inv);
-                        w[1] = pack_bf16x2(r[4 * hh + 2] * inv, r[4 * hh + 3] * inv);
-                        *(u32x2*)(orow + db * 32 + 8 * (2 * hp + hh) + 4 * half) = w;
-                    }
-                }
-            } else {
-                const u32x2 w0 = pack_partial(r[0], r[1], r[2], r[3], inv), w1 = pack_partial(r[4], r[5], r[6], r[7], inv);
+                for (int i = 0; i < PPK; ++i)
+#pragma unroll
+                    for (int hh = 0; hh < 2; ++hh)
+                        *(u32x2*)(orow + (MY * PPK + i) * 16 + 8 * hh + 4 * half) =
+                            pack_partial(r[i][4 * hh], r[i][4 * hh + 1], r[i][4 * hh + 2], r[i][4 * hh + 3], inv);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < PPK; ++i) {
+                const u32x2 w0 = pack_partial(r[i][0], r[i][1], r[i][2], r[i][3], inv), w1 = pack_partial(r[i][4], r[i][5], r[i][6], r[i][7], inv);
                 const u32x4 w = {w0[0], w0[1], w1[0], w1[1]};
-                uint16_t* dst = po + pc * piece_stride(p);
+                uint16_t* dst = po + (MY * PPK + i) * piece_stride(p);
                 if (merge) __builtin_amdgcn_raw_buffer_store_b128(w, span_of(dst), lane * 16, 0, kDeviceScope);
                 else *(u32x4*)(dst + lane * 8) = w;
             }

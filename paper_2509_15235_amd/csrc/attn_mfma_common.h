@@ -34,6 +34,23 @@ __device__ __forceinline__ float half_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Which keys of a 32-key tile a row may see, one bit per key. rel: tree slot of the tile's first key (negative:
+// prefix), keys: keys of the tile that exist (both uniform). One word per tile and a bit-field extract and
+// insert per score; tests on the 64-bit mask cost four times as many instructions, and in a launch
+// that waits for its slowest wave the waves with tree slots are that wave.
+__device__ __forceinline__ uint32_t tile_visible(uint64_t mask, int rel, int keys) {
+    uint32_t w;
+    if (rel >= 0) w = rel < 64 ? (uint32_t)(mask >> rel) : 0u;
+    else if (rel > -32) w = (uint32_t)(mask << -rel) | ((1u << -rel) - 1u);
+    else w = ~0u;
+    return keys >= 32 ? w : (keys <= 0 ? 0u : w & ((1u << keys) - 1u));
+}
+// s where bit `bit` (a constant) of w is set, else -inf
+__device__ __forceinline__ float visible_or_inf(float s, uint32_t w, int bit) {
+    const uint32_t m = (uint32_t)((int32_t)(w << (31 - bit)) >> 31);
+    return __uint_as_float((__float_as_uint(s) & m) | (0xff800000u & ~m));
+}
+
 // node of query row r (r / group): the quotient is below 64, so the fp32 product is off by less than one
 __device__ __forceinline__ int row_node(const AttnParams& p, int r) {
     int n = (int)((float)r * p.inv_group);
