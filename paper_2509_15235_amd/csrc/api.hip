@@ -50,6 +50,7 @@ struct Plan {
     int32_t impl, rpw, waves, row_groups, rows, rows_pad, num_splits, keys_per_split, total_wgs, schedule;
     int32_t bal_chunks; // balanced schedule: shares per (KV head, row group); num_splits = slots per KV head
     int32_t f32_rows; // fp32 storage: query rows per workgroup
+    int32_t rounds; // loop schedule on the LDS-resident kernel's form: splits in rounds of 128 keys
     int32_t res_rb; // resident schedule: row blocks per workgroup (4, 2 or 1)
 };
 
@@ -190,8 +191,21 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     const bool balanced_ok = many && pipe_ok && splits <= 0 && d->B >= 2 && d->B <= kBalMaxSeqs &&
                              (bal_wgs * 32 < bal_places * 25 || (bal_wgs > bal_places && bal_wgs < 2 * bal_places)) &&
                              bal_w_auto >= 2 && (int64_t)d->B * tiles >= 32 * (int64_t)bal_w_auto;
+    // Rounds: the resident kernel's form (keys split among the waves too) on splits of any length, 128 keys in LDS at
+    // a time. Where a unit's rows are at most one workgroup (two to four row blocks) and all workgroups run at
+    // once, or too few units for the pipelined kernel: us per call, pipelined with its combine kernel / rounds
+    //   4 x 16 nodes, 28 / 4 heads, 1300 keys 16.7 / 11.4; 16 x the same, up to 8191 keys 68.3 / 57.2
+    //   8 x 31 nodes, 32 / 8 heads of 64, up to 2047 keys 18.1 / 16.6; 4 x 60 nodes, 32 / 32 heads, 3400 keys 51.2 / 47.6
+    // and straight loop / rounds 2 x 60 nodes, 28 / 4 heads, 1696 keys 17.6 / 14.2, one of 6684 keys 25.2 / 18.4.
+    // More workgroups than CUs: 16 x 60 nodes, 32 / 32 heads, 1000 keys 61.4 / 64.1. One sequence of many KV heads
+    // with two row blocks stays with the pipelined kernel (20.1 / 18.9).
+    const int rnd_rb = nrb >= 3 ? 4 : 2;
+    const int rnd_wgs = units0 * ((nrb + rnd_rb - 1) / rnd_rb);
+    const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
+    const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || (nrb <= 4 && (nrb > 2 || d->B > 1)));
     pl.schedule = d->schedule != VS_SCHED_AUTO ? d->schedule
                   : balanced_ok                ? VS_SCHED_BALANCED
+                  : many && rounds_ok          ? VS_SCHED_LOOP
                   : many && pipe_ok            ? VS_SCHED_PIPELINED
                   : resident_ok                ? VS_SCHED_RESIDENT
                                                : VS_SCHED_LOOP;
@@ -217,6 +231,23 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
         int tps = (tiles + splits - 1) / splits;
         if (tps > max_tiles) tps = max_tiles;
         if (tps < 1) tps = 1;
+        pl.keys_per_split = tps * kIterKeys;
+        pl.num_splits = (tiles + tps - 1) / tps;
+        pl.total_wgs = units0 * pl.row_groups * pl.num_splits;
+        return pl;
+    }
+    if (pl.schedule == VS_SCHED_LOOP && rounds_ok) {
+        pl.rounds = 1;
+        pl.rpw = 1;
+        pl.waves = 8;
+        pl.res_rb = rnd_rb;
+        pl.row_groups = (nrb + pl.res_rb - 1) / pl.res_rb;
+        splits = kNumCUs / (units0 * pl.row_groups);
+        const int most = (tiles + 1) / 2;
+        if (splits > most) splits = most;
+        if (splits > kMergeMaxSplits) splits = kMergeMaxSplits;
+        if (splits < 1) splits = 1;
+        const int tps = (tiles + splits - 1) / splits;
         pl.keys_per_split = tps * kIterKeys;
         pl.num_splits = (tiles + tps - 1) / tps;
         pl.total_wgs = units0 * pl.row_groups * pl.num_splits;
@@ -283,7 +314,8 @@ size_t partial_rows(const vs_attn_desc* d, const Plan& pl) {
 // Splits merged by their own workgroups instead of a combine kernel: they wait for each other, so only where
 // all of them run at once (given an idle device; with a busy one the wait is bounded)
 bool merges_inside(const Plan& pl) {
-    return pl.schedule == VS_SCHED_RESIDENT && pl.num_splits > 1 && pl.num_splits <= kMergeMaxSplits && pl.total_wgs <= kNumCUs &&
+    return (pl.schedule == VS_SCHED_RESIDENT || pl.schedule == VS_SCHED_PIPELINED || pl.rounds) && pl.num_splits > 1 &&
+           pl.num_splits <= kMergeMaxSplits && pl.total_wgs <= kNumCUs &&
            pl.rows_pad <= (1 << 16); // offsets inside a row group's partial results are 32 bits wide
 }
 
@@ -422,7 +454,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.num_splits = pl.num_splits;
     p.keys_per_split = pl.keys_per_split;
     p.row_groups = pl.row_groups;
-    p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.schedule == VS_SCHED_RESIDENT ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
+    p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.res_rb ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
     p.total_wgs = pl.total_wgs;
     p.bal_chunks = pl.bal_chunks;
     // a launch of more whole sequences than run at once hands out the longest first (a lane per sequence)
@@ -442,6 +474,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         e = desc->dtype == VS_F32 ? launch_attention_f32(p, s) : launch_attention_generic(p, s);
     } else {
         e = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) ? launch_attention_mfma_pipe(p, pl.rpw, pl.waves, s)
+            : pl.rounds ? launch_attention_mfma_rounds(p, pl.res_rb, s)
             : pl.schedule == VS_SCHED_RESIDENT ? launch_attention_mfma_resident(p, pl.res_rb, s)
                                                : launch_attention_mfma(p, pl.rpw, pl.waves, s);
         if (e == hipSuccess && pl.num_splits > 1 && !p.gates) e = launch_attention_combine(p, desc->dtype, s);

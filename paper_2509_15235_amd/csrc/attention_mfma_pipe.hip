@@ -48,6 +48,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     __shared__ __attribute__((aligned(1024))) uint16_t sV[NSLOT][SUB];
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
+    __shared__ uint64_t sgen;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -129,14 +130,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     for (int rb = 0; rb < RPW; ++rb) {
         // rows past the end repeat the last row (finite data, results discarded)
         const int r = min(row_base + rb * kRowBlock + col, p.rows - 1);
-        const int node = r / p.group;
-        const int hq = kvh * p.group + (r - node * p.group);
-        node_of[rb] = node;
-        const uint16_t* qr = (const uint16_t*)p.q + (((int64_t)b * p.T + node) * p.Hq + hq) * D + half * 8;
-        if (wave_active) {
+        node_of[rb] = row_node(p, r);
+    }
+    static_assert(RPW == 1 && NW <= 2 * NSLOT, "a row block's queries take a tile slot");
+    // through the tile slot of this wave's number (nothing is in the rings yet)
+    uint16_t* sq = wave < NSLOT ? sK[wave & (NSLOT - 1)] : sV[wave & (NSLOT - 1)];
+    {
+        int ql = lane;
+        if (BAL) asm volatile("" : "+v"(ql)); // keeps the addresses (the same for every piece) from living in registers
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) qf[rb][ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qr + ks * 16));
-        }
+        for (int i = 0; i < KS; ++i) copy_q_piece<D>(p, b, kvh, row_base, sq, i, ql);
     }
 
     int32_t tree_code = VS_STATUS_OK;
@@ -152,6 +155,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
 
     const int nk = S + p.tree_keys;
     if (k0 >= nk) return;
+    const bool merge = !BAL && p.gates != nullptr; // uniform over the launch
+    const MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
+    if (merge && tid == 0) merge_open(gate);
     const int k1 = min(nk, k0 + klen);
     const int n = (k1 - k0 + kTileKeys - 1) / kTileKeys; // tiles of this split
 
@@ -329,15 +335,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         for (int rb = 0; rb < RPW; ++rb) {
             f32x16& s = sc[rb];
             if constexpr (MASKED) {
-                const int rel = kt + 4 * half - S; // tree slot of this lane's key 0 (negative: prefix)
-                const uint32_t tree_end = (uint32_t)(k1 - S);
+                const uint32_t w = tile_visible(mask[rb], kt - S, k1 - kt) >> (4 * half);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int sh = rel + 8 * (r >> 2) + (r & 3);
-                    const uint32_t bit = (uint32_t)(mask[rb] >> (sh & 63)) & 1u;
-                    const bool vis = (sh < 0) | (((uint32_t)sh < tree_end) & (bit != 0));
-                    s[r] = vis ? s[r] : -INFINITY;
-                }
+                for (int r = 0; r < 16; ++r) s[r] = visible_or_inf(s[r], w, 8 * (r >> 2) + (r & 3));
             }
             float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
@@ -524,6 +524,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     // outside any branch, also keeps the compiler from re-waiting for the query registers
     // inside the loop, where such a wait would drain the tile copies in flight.
     __builtin_amdgcn_s_waitcnt(wait_vm(0));
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[0][ks] = read_q_frag<D>(sq, ks, col, half);
+    __syncthreads(); // every wave has its queries: the rings may be filled
     {
         // the early tiles: rows at or past k1 become zeros
         auto stash_tile_live = [&](auto is_v, uint16_t* slot, const u32x4(&r)[BPW], int t) __attribute__((always_inline)) {
@@ -632,7 +635,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         iteration(F{}, F{}, S0{}, ta);
         if (ta + 2 < n) iteration(F{}, F{}, S1{}, ta + 2);
     }
-    if (!wave_active) return;
+    if (wave_active) {
     if ((n & 1) == 0) pv(sV[(n - 1) & 3], pb);
 
     // ---- epilogue: lane (col, half) holds, for row `col`, channels db*32 + 8*(r/4) + 4*half + r%4
@@ -642,18 +645,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         const float l = half_sum(lsum[rb]);
         if (whole) {
             if (r_local >= p.rows) continue;
-            const int node = r_local / p.group;
-            const int hq = kvh * p.group + (r_local - node * p.group);
-            uint16_t* o = (uint16_t*)p.out + (((int64_t)b * p.T + node) * p.Hq + hq) * D;
+            uint16_t* o = (uint16_t*)p.out + row_offset(p, b, kvh, r_local, row_node(p, r_local));
             const float inv = 1.f / l;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
-                    u32x2 w;
-                    w[0] = pack_bf16x2(acc[rb][db][4 * q4] * inv, acc[rb][db][4 * q4 + 1] * inv);
-                    w[1] = pack_bf16x2(acc[rb][db][4 * q4 + 2] * inv, acc[rb][db][4 * q4 + 3] * inv);
-                    *(u32x2*)(o + db * 32 + 8 * q4 + 4 * half) = w;
+                    *(u32x2*)(o + db * 32 + 8 * q4 + 4 * half) =
+                        pack_partial(acc[rb][db][4 * q4], acc[rb][db][4 * q4 + 1], acc[rb][db][4 * q4 + 2], acc[rb][db][4 * q4 + 3], inv);
                 }
         } else {
             if (row_base + rb * kRowBlock >= p.rows) continue; // whole block is padding
@@ -661,13 +660,23 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
             uint16_t* po = p.part_o + part_block<D>(p, unit, slot, (row_base >> 5) + rb);
             const float inv = l > 0.f ? 1.f / l : 0.f; // no visible key in this split: zeros, weight 0
 #pragma unroll
-            for (int db = 0; db < DB; ++db) store_partial(p, po, db, lane, acc[rb][db], inv);
+            for (int db = 0; db < DB; ++db) {
+                if (merge) store_partial<true>(p, po, db, lane, acc[rb][db], inv);
+                else store_partial(p, po, db, lane, acc[rb][db], inv);
+            }
             if (half == 0) {
                 const f32x2 ml = {m2[rb], l};
-                const int64_t mlb = ml_block(p, unit, slot, (row_base >> 5) + rb);
-                *(f32x2*)(p.part_ml + (mlb + col) * 2) = ml;
+                float* dst = p.part_ml + ml_block(p, unit, slot, (row_base >> 5) + rb) * 2;
+                if (merge) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), span_of(dst), col * 8, 0, kDeviceScope);
+                else *(f32x2*)(dst + col * 2) = ml;
             }
         }
+    }
+    }
+    if (merge) {
+        const int rb0 = rg * (p.rows_per_group / kRowBlock);
+        merge_splits<D>(p, gate, b, kvh, rb0, min(rb0 + NW * RPW, p.rows_pad / kRowBlock), slot, (nk + p.keys_per_split - 1) / p.keys_per_split,
+                        NW, (uint32_t*)sp);
     }
     }; // run_piece
 

@@ -32,7 +32,7 @@ namespace {
 constexpr int kResWaves = 8;
 constexpr int kResMaxTiles = kResidentMaxKeys / kTileKeys; // 32-key tiles of one split
 
-template <int D, int NRB, int NT>
+template <int D, int NRB, int NT, bool STREAM>
 __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(const AttnParams p) {
     constexpr int KS = D / 16;          // k-steps of the S^T product
     constexpr int DB = D / 32;          // 32-channel blocks of the output
@@ -46,17 +46,23 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     constexpr int TILE_BYTES = 2 * NT * SUB * 2;
     constexpr int MERGE_BYTES = kResWaves * (DB * 1024 + 128) * 4; // every wave's exchange area: accumulators, max, sum
     constexpr int Q_BYTES = NRB * kRowBlock * D * 2;
-    constexpr int SMEM_ELEMS = (TILE_BYTES + Q_BYTES > MERGE_BYTES ? TILE_BYTES + Q_BYTES : MERGE_BYTES) / 2;
-    static_assert(NT >= 1 && NT <= kResMaxTiles, "a split holds at most kResidentMaxKeys keys");
+    // the queries lie behind the tiles: where a second round's tiles go when they have been read (stages of round 0
+    // end in barriers, so with two of them nobody can still be reading)
+    constexpr int KEEP_BYTES = !STREAM ? TILE_BYTES + Q_BYTES : (PPM >= 2 && Q_BYTES <= TILE_BYTES ? 2 * TILE_BYTES : 2 * TILE_BYTES + Q_BYTES);
+    constexpr int Q_AT = STREAM && PPM == 1 ? 2 * TILE_BYTES : TILE_BYTES;
+    constexpr int SMEM_ELEMS = (KEEP_BYTES > MERGE_BYTES ? KEEP_BYTES : MERGE_BYTES) / 2;
+    static_assert(NT >= 1 && NT <= kResMaxTiles, "a round holds at most kResidentMaxKeys keys");
+    static_assert(SMEM_ELEMS * 2 + 512 <= kLdsBytesPerCU, "LDS");
 
-    // tiles: K[t] at smem + t*SUB, V[t] at smem + (NT + t)*SUB; after the last tile has been
-    // consumed the same memory carries the key parts' results to the merging waves
+    // tiles of a round: K[t] at smem + t*SUB, V[t] at smem + (NT + t)*SUB, odd rounds TILE_BYTES further; after the
+    // last tile has been consumed the same memory carries the key parts' results to the merging waves
     __shared__ __attribute__((aligned(1024))) uint16_t smem[SMEM_ELEMS];
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
+    __shared__ uint64_t sgen;
     uint16_t* sK = smem;
     uint16_t* sV = smem + NT * SUB;
-    uint16_t* sQ = smem + 2 * NT * SUB; // queries: row blocks of D-channel rows (see load_q_piece)
+    uint16_t* sQ = smem + Q_AT / 2; // queries: row blocks of D-channel rows (see load_q_piece)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -81,7 +87,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
 
     const int32_t S = p.prefix_len[b]; // requested first, needed last: everything below is issued before it arrives
 
-    // ---- copy the split's keys and values. Stage j = tile j of every key part (tile kq * PPM + j);
+    // ---- copy the first round's keys and values. Stage j = one tile of every key part (tile j * KQ + kq);
     // inside a stage, copy block i = (key part i / BPS, rows RPI * (i % BPS) ..) and wave w takes
     // blocks w, w + 8, ...; one load instruction reads RPI whole rows (1 KB of consecutive memory).
     // The loads do not wait for the prefix length: they are clamped to the cache (not to the
@@ -108,7 +114,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     // stage's last one (KQ * BPS not a multiple of the wave count) repeat its last block
     auto block_tile = [&](int j, int u) __attribute__((always_inline)) {
         const int i = min(wave + kResWaves * u, KQ * BPS - 1);
-        return min((i / BPS) * PPM + j, NT - 1);
+        return min(j * KQ + i / BPS, NT - 1);
     };
     auto block_row = [&](int u) __attribute__((always_inline)) {
         const int i = min(wave + kResWaves * u, KQ * BPS - 1);
@@ -131,6 +137,35 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
             if constexpr (ISV) vreg[j][u] = *(const u32x4*)(vbase + base + off);
             else kreg[j][u] = *(const u32x4*)(kbase + base + off);
         }
+    };
+    // Later rounds (the sequence's length is known by then, tokens past the split's last one repeat it). Paged
+    // caches: the ids of the next 64 blocks sit one per lane (see attention_mfma_pipe.hip).
+    int bt_base = k0 >> p.block_shift;
+    int32_t bt_win = 0;
+    auto bt_fetch = [&]() __attribute__((always_inline)) { bt_win = p.block_table[(int64_t)b * p.max_blocks + min(bt_base + lane, p.max_blocks - 1)]; };
+    if (STREAM && p.paged) bt_fetch();
+    auto issue_round = [&](int kr, int last) __attribute__((always_inline)) {
+        if (p.paged && ((kr + NT * kTileKeys - 1) >> p.block_shift) >= bt_base + 64) { // uniform
+            bt_base = kr >> p.block_shift;
+            bt_fetch();
+        }
+#pragma unroll
+        for (int j = 0; j < PPM; ++j)
+#pragma unroll
+            for (int u = 0; u < SPW; ++u) {
+                const int r0 = min(kr + kTileKeys * block_tile(j, u) + block_row(u), last);
+                int tok = min(r0 + lrow, last);
+                int64_t base = head_base;
+                if (p.paged) {
+                    int32_t blk = __builtin_amdgcn_readlane(bt_win, (r0 >> p.block_shift) - bt_base);
+                    if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
+                    base += (int64_t)blk * p.stride_block;
+                    tok &= p.block_size - 1;
+                }
+                const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
+                kreg[j][u] = *(const u32x4*)(kbase + base + off);
+                vreg[j][u] = *(const u32x4*)(vbase + base + off);
+            }
     };
     issue_stage(std::false_type{}, 0); // the first keys lead: the first scores need them and the queries
 
@@ -170,42 +205,127 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     if (k0 >= nk) return;
     const bool final_rows = p.num_splits == 1;
     const bool merge = p.gates != nullptr; // uniform over the launch
-    MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, 0};
+    const MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
     if (merge && tid == 0) merge_open(gate);
     const int k1 = min(nk, k0 + p.keys_per_split);
-    const int nt = (k1 - k0 + kTileKeys - 1) / kTileKeys; // tiles of this split, <= kResMaxTiles
-
-    // ---- this wave's key part: tiles kq * PPM + j, j = 0 .. PPM - 1 (those below nt). The scores of a stage are
-    // computed as soon as it is in LDS; the softmax comes once, over all of the part's keys (no running
-    // reference, nothing to rescale, and its independent halves hide each other's latency), and then the output.
-    // (Tile after tile, each with its own softmax, the same work took 0.8 us longer per layer.)
 
     // per-lane LDS offsets (elements); everything else is a compile-time immediate
     const int k_lane[2] = {(col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (4 * half)) * 8,
                            (col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (8 + 4 * half)) * 8};
     const int t16 = lane & 15;
     const int v_lane = half * 128 + (t16 >> 2) * 32 + ((lane >> 4) & 1) * 16 + ((t16 >> 1) & 1) * 8 + (t16 & 1) * 4;
-
-    bf16x8 qf[KS];
-    f32x16 s[PPM];
-    // tiles that end at or before min(S, k1) hold prefix keys only
-    const int n_plain = max(0, min(S, k1) - k0) / kTileKeys;
-#pragma unroll
-    for (int j = 0; j < PPM; ++j) {
-        // stage j has arrived once at most the later stages' loads are outstanding (loads return in
-        // order; the compiler counts them and waits for exactly that before the first use below)
+    // the staged copy blocks of stage j -> LDS; LIVE: rows past the split's last key become zeros
+    auto stash_stage = [&](auto live_tag, int j, int at) __attribute__((always_inline)) {
+        constexpr bool LIVE = decltype(live_tag)::value;
 #pragma unroll
         for (int u = 0; u < SPW; ++u) {
             if (SPW * kResWaves == KQ * BPS || wave + kResWaves * u < KQ * BPS) { // uniform per wave
                 const int t = block_tile(j, u), rr = block_row(u) + lrow, c = lchunk;
-                const bool live = k0 + kTileKeys * t + rr < k1;
+                const bool live = !LIVE || k0 + kTileKeys * t + rr < k1;
                 const u32x4 zero = {0u, 0u, 0u, 0u};
                 const uint32_t ko = (uint32_t)(((rr >> 4) * DB + (c >> 2)) * 1024 + (c & 3) * 256 + (((rr & 15) ^ (4 * (c & 3))) * 16));
                 const uint32_t vo = (uint32_t)(((rr >> 4) * DB + (c >> 2)) * 1024 + (4 * (rr & 15) + (c & 3)) * 16);
-                *(u32x4*)((char*)(sK + t * SUB) + ko) = live ? kreg[j][u] : zero;
-                *(u32x4*)((char*)(sV + t * SUB) + vo) = live ? vreg[j][u] : zero;
+                *(u32x4*)((char*)(sK + at + t * SUB) + ko) = live ? kreg[j][u] : zero;
+                *(u32x4*)((char*)(sV + at + t * SUB) + vo) = live ? vreg[j][u] : zero;
             }
         }
+    };
+
+    // ---- this wave's key part: tiles j * KQ + kq of every round. The softmax comes once per round, over all of
+    // the part's tiles of it (its independent halves hide each other's latency), and then the output.
+    bf16x8 qf[KS];
+    f32x16 s[PPM];
+    // S^T = K . Q^T: lane (col, half) gets keys 8*(q/4) + 4*half + q%4 of row `col`
+    auto scores = [&](int j, int at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s[j][q] = 0.f;
+        const uint16_t* kt_ = sK + at + min(j * KQ + kq, NT - 1) * SUB;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 a = __builtin_bit_cast(bf16x8, *(const u32x4*)(kt_ + k_lane[ks & 1] + ks * 256));
+            s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[j], 0, 0, 0);
+        }
+    };
+    float m2 = -INFINITY, lsum = 0.f; // reference (log2 domain, scaled; -inf: no visible key yet), this lane's share of the sum
+    f32x16 acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[db][q] = 0.f;
+    auto output = [&](auto first_tag, int kr, int at) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        // uniform: tree slots, the end of the range, or a last stage without a tile for this key part
+        if (kr + NT * kTileKeys > min(S, k1) || (PPM - 1) * KQ + kq >= NT) {
+#pragma unroll
+            for (int j = 0; j < PPM; ++j) {
+                const int first = kr + (j * KQ + kq) * kTileKeys;
+                const uint32_t w = tile_visible(mask, first - S, j * KQ + kq < NT ? k1 - first : 0) >> (4 * half);
+#pragma unroll
+                for (int q = 0; q < 16; ++q) s[j][q] = visible_or_inf(s[j][q], w, 8 * (q >> 2) + (q & 3));
+            }
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < PPM; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; q += 2) mx = max3(mx, s[j][q], s[j][q + 1]);
+        const float mt = half_max(mx) * p.scale_log2;
+        const float m_new = FIRST ? mt : (mt > m2 + kLazy ? mt : m2); // lazy: moves in steps of more than 2^8
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+        for (int j = 0; j < PPM; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; q += 2) {
+                s[j][q] = __builtin_amdgcn_exp2f(fmaf(s[j][q], p.scale_log2, -m_use)); // exp2(-inf) = 0
+                s[j][q + 1] = __builtin_amdgcn_exp2f(fmaf(s[j][q + 1], p.scale_log2, -m_use));
+                ps0 += s[j][q];
+                ps1 += s[j][q + 1];
+            }
+        if constexpr (!FIRST) {
+            const float alpha = __builtin_amdgcn_exp2f(m2 - m_use);
+            lsum *= alpha;
+            if (__any(alpha != 1.f)) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) acc[db][q] *= alpha;
+            }
+        }
+        lsum += ps0 + ps1;
+        m2 = m_new;
+        // O^T += V^T . P^T: the A operand comes from two transposing reads of 4 keys x 16 channels
+#pragma unroll
+        for (int j = 0; j < PPM; ++j) {
+            const uint16_t* vt_ = sV + at + min(j * KQ + kq, NT - 1) * SUB + v_lane;
+            bf16x8 pf[2];
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl) {
+                u32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const f32x2 pr = {s[j][8 * sl + 2 * e], s[j][8 * sl + 2 * e + 1]};
+                    w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
+                }
+                pf[sl] = __builtin_bit_cast(bf16x8, w);
+            }
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512 + 256));
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                    acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[sl], acc[db], 0, 0, 0);
+                }
+        }
+    };
+
+    // ---- round 0, stage by stage as the loads arrive (they return in order; the compiler counts them and waits
+    // for exactly the stage's before their first use)
+#pragma unroll
+    for (int j = 0; j < PPM; ++j) {
+        stash_stage(std::true_type{}, j, 0);
         if (j == 0) {
 #pragma unroll
             for (int i = 0; i < QPW; ++i) store_q_piece<D>(sQ + rbw * (kRowBlock * D), qreg[i], min(kq * QPW + i, KS - 1), lane);
@@ -215,74 +335,25 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) qf[ks] = read_q_frag<D>(sQ + rbw * (kRowBlock * D), ks, col, half);
         }
-        // S^T = K . Q^T: lane (col, half) gets keys 8*(q/4) + 4*half + q%4 of row `col`
-#pragma unroll
-        for (int q = 0; q < 16; ++q) s[j][q] = 0.f;
-        const int t = min(kq * PPM + j, NT - 1);
-        const uint16_t* kt_ = sK + t * SUB;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, *(const u32x4*)(kt_ + k_lane[ks & 1] + ks * 256));
-            s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[j], 0, 0, 0);
-        }
+        scores(j, 0);
     }
-    const int my_tiles = max(0, min(PPM, nt - kq * PPM)); // tiles past the split's last one were zeros or a repeat
-    if (kq * PPM + PPM > n_plain) { // uniform: tree slots, the end of the range, or no such tile
+    constexpr int ROUND = NT * kTileKeys;
+    if (STREAM && k0 + ROUND < k1) issue_round(k0 + ROUND, k1 - 1);
+    output(std::true_type{}, k0, 0);
+    // ---- the other rounds: two sets of tiles in LDS, one barrier per round. A round is requested when the one
+    // before it has left the staging registers.
+    if constexpr (STREAM) {
+        int at = TILE_BYTES / 2;
+        for (int kr = k0 + ROUND; kr < k1; kr += ROUND) {
 #pragma unroll
-        for (int j = 0; j < PPM; ++j) {
-            const int first = k0 + (kq * PPM + j) * kTileKeys;
-            const uint32_t w = tile_visible(mask, first - S, j < my_tiles ? k1 - first : 0) >> (4 * half);
+            for (int j = 0; j < PPM; ++j) stash_stage(std::false_type{}, j, at);
+            __syncthreads();
+            if (kr + ROUND < k1) issue_round(kr + ROUND, k1 - 1);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) s[j][q] = visible_or_inf(s[j][q], w, 8 * (q >> 2) + (q & 3));
+            for (int j = 0; j < PPM; ++j) scores(j, at);
+            output(std::false_type{}, kr, at);
+            at = TILE_BYTES / 2 - at;
         }
-    }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < PPM; ++j)
-#pragma unroll
-        for (int q = 0; q < 16; q += 2) mx = max3(mx, s[j][q], s[j][q + 1]);
-    const float m2 = half_max(mx) * p.scale_log2; // reference (log2 domain); -inf: no visible key
-    const float m_use = m2 == -INFINITY ? 0.f : m2;
-    float ps0 = 0.f, ps1 = 0.f;
-#pragma unroll
-    for (int j = 0; j < PPM; ++j)
-#pragma unroll
-        for (int q = 0; q < 16; q += 2) {
-            s[j][q] = __builtin_amdgcn_exp2f(fmaf(s[j][q], p.scale_log2, -m_use)); // exp2(-inf) = 0
-            s[j][q + 1] = __builtin_amdgcn_exp2f(fmaf(s[j][q + 1], p.scale_log2, -m_use));
-            ps0 += s[j][q];
-            ps1 += s[j][q + 1];
-        }
-    const float lsum = ps0 + ps1; // this lane's share of the sum
-    // O^T += V^T . P^T: the A operand comes from two transposing reads of 4 keys x 16 channels
-    f32x16 acc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[db][q] = 0.f;
-#pragma unroll
-    for (int j = 0; j < PPM; ++j) {
-        const uint16_t* vt_ = sV + min(kq * PPM + j, NT - 1) * SUB + v_lane;
-        bf16x8 pf[2];
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            u32x4 w;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const f32x2 pr = {s[j][8 * sl + 2 * e], s[j][8 * sl + 2 * e + 1]};
-                w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
-            }
-            pf[sl] = __builtin_bit_cast(bf16x8, w);
-        }
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512 + 256));
-                const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[sl], acc[db], 0, 0, 0);
-            }
     }
 
     // ---- merge the key parts through LDS (log-sum-exp) and write the rows. The work is shared: a row
@@ -416,10 +487,10 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     }
 }
 
-template <int D, int NRB, int NT>
+template <int D, int NRB, int NT, bool STREAM = false>
 hipError_t launch_res(const AttnParams& p, hipStream_t s) {
     const dim3 grid(((p.total_wgs + 7) / 8) * 8);
-    hipLaunchKernelGGL((attn_mfma_resident_kernel<D, NRB, NT>), grid, dim3(kResWaves * kWave), 0, s, p);
+    hipLaunchKernelGGL((attn_mfma_resident_kernel<D, NRB, NT, STREAM>), grid, dim3(kResWaves * kWave), 0, s, p);
     return hipGetLastError();
 }
 
@@ -445,6 +516,14 @@ hipError_t launch_attention_mfma_resident(const AttnParams& p, int row_blocks, h
     if (p.d == 64) {
         return row_blocks == 4 ? launch_res_nt<64, 4>(p, s) : (row_blocks == 2 ? launch_res_nt<64, 2>(p, s) : launch_res_nt<64, 1>(p, s));
     }
+    return hipErrorInvalidValue;
+}
+
+// Splits of any length, in rounds of four tiles; four or two row blocks per workgroup.
+hipError_t launch_attention_mfma_rounds(const AttnParams& p, int row_blocks, hipStream_t s) {
+    if ((row_blocks != 4 && row_blocks != 2) || p.keys_per_split % kIterKeys) return hipErrorInvalidValue;
+    if (p.d == 128) return row_blocks == 4 ? launch_res<128, 4, 4, true>(p, s) : launch_res<128, 2, 4, true>(p, s);
+    if (p.d == 64) return row_blocks == 4 ? launch_res<64, 4, 4, true>(p, s) : launch_res<64, 2, 4, true>(p, s);
     return hipErrorInvalidValue;
 }
 

@@ -81,6 +81,15 @@ __device__ __forceinline__ void store_q_piece(uint16_t* sq, u32x4 v, int i, int 
     const int r = RPI * i + lane / LPR;
     *(u32x4*)(sq + r * D + ((lane % LPR) ^ (r % LPR)) * 8) = v;
 }
+// The same piece without a stop in registers: the fetching lanes take the chunks in the order they are stored in.
+// `sq` is uniform; the piece has arrived after a wait for the vector-memory counter.
+template <int D>
+__device__ __forceinline__ void copy_q_piece(const AttnParams& p, int b, int kvh, int row_base, uint16_t* sq, int i, int lane) {
+    constexpr int LPR = D / 8, RPI = 64 / LPR;
+    const int rl = RPI * i + lane / LPR, r = min(row_base + rl, p.rows - 1);
+    const uint16_t* src = (const uint16_t*)p.q + row_offset(p, b, kvh, r, row_node(p, r)) + ((lane % LPR) ^ (rl % LPR)) * 8;
+    __builtin_amdgcn_global_load_lds(src, (lds_void*)(sq + i * 512), 16, 0, 0);
+}
 template <int D>
 __device__ __forceinline__ bf16x8 read_q_frag(const uint16_t* sq, int ks, int col, int half) {
     constexpr int LPR = D / 8;
@@ -163,14 +172,14 @@ constexpr uint64_t kMergeWait = 2000;                 // 20 us of the 100 MHz cl
 
 struct MergeGate {
     uint64_t* word; // null: the splits are merged by the combine kernel
-    uint64_t gen;   // word 1 before anybody arrived (thread 0)
+    uint64_t* gen;  // LDS: word 1 before anybody arrived (thread 0 only)
 };
 __device__ __forceinline__ uint64_t gate_load(const uint64_t* w) {
     return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Thread 0 of every workgroup of the row group, any time before it arrives.
-__device__ __forceinline__ void merge_open(MergeGate& g) {
-    g.gen = gate_load(g.word + kGateFlag);
+__device__ __forceinline__ void merge_open(const MergeGate& g) {
+    *g.gen = gate_load(g.word + kGateFlag);
     uint64_t w = gate_load(g.word);
     if ((w >> 40) != kMergeTag) // lost to another workgroup: then it did the same
         __hip_atomic_compare_exchange_strong(g.word, &w, kMergeZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -179,14 +188,15 @@ __device__ __forceinline__ void merge_open(MergeGate& g) {
 // has to merge besides its own; `go` false: its own share was handed over.
 __device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, int split, int n, bool& go) {
     go = true;
+    const uint64_t gen = *g.gen;
     const uint64_t old = __hip_atomic_fetch_add(g.word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((int)(old & 0xff) == n - 1) {
         __hip_atomic_store(g.word, kMergeZero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(g.word + kGateFlag, g.gen + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(g.word + kGateFlag, gen + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return (uint32_t)(old >> 8);
     }
     const uint64_t t0 = wall_clock64();
-    while (gate_load(g.word + kGateFlag) == g.gen) {
+    while (gate_load(g.word + kGateFlag) == gen) {
         __builtin_amdgcn_s_sleep(1);
         if (wall_clock64() - t0 > kMergeWait) {
             uint64_t w = gate_load(g.word);

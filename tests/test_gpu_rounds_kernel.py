@@ -1,0 +1,72 @@
+"""GPU parity of the attention kernel that runs a split in rounds of 128 keys (the planner's choice for few units
+or few row blocks): lengths around rounds and splits, one to several row groups, block-table windows, and the
+merge of the splits by their own workgroups on a workspace full of garbage."""
+import numpy as np
+import pytest
+
+import gen
+import paper_2509_15235_amd as vs
+
+pytestmark = pytest.mark.gpu
+
+TIGHT_LONG = (1.5e-3, 6e-3)
+TIGHT_SHORT = (1.2e-2, 6e-3)
+
+
+@pytest.mark.parametrize("B,T,Hq,Hkv,d,paged,lens", [
+    (2, 60, 28, 4, 128, False, [1696, 1500]),                    # four row groups, two rounds per split
+    (2, 60, 28, 4, 128, True, [1600, 1]),                        # most splits without a key
+    (4, 33, 12, 4, 64, False, [700, 127, 128, 129]),             # four row blocks, 64 channels
+    (4, 16, 28, 4, 128, True, [1296, 1000, 3, 511]),
+    (2, 50, 8, 8, 128, False, [2000, 1234]),                     # two row blocks
+    (3, 33, 6, 6, 64, True, [900, 77, 640]),
+    (1, 9, 8, 1, 128, True, [40001]),                            # splits beyond a block-table window
+    (1, 9, 8, 1, 64, True, [33000]),
+    (1, 64, 9, 1, 128, False, [5000]),                           # five row groups
+    (16, 20, 16, 4, 128, False, [37 * i + 1 for i in range(16)]),  # one split per unit or a few, ends everywhere
+])
+def test_rounds(oracle_mod, B, T, Hq, Hkv, d, paged, lens):
+    import gpu_util as gu
+    cfg = gen.Config("rounds", B, Hq, Hkv, d, T, min(6, T - 1), 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2),
+                     paged=paged)
+    inp = gen.attention_inputs(cfg, 900 + T, prefix_len=np.array(lens, dtype=np.int32))
+    da = gu.DeviceAttn(inp)
+    assert da.plan().schedule == vs.VS_SCHED_LOOP and da.plan().waves_per_group == 8
+    da.ws.random_(0, 256)                                        # the merge's words start as anything
+    got = da.run()
+    assert (da.status.cpu().numpy() == 0).all()
+    ref = oracle_mod.tree_attention(inp, threads=8)
+    for b in range(B):
+        gu.check_close(got[b], ref[b], *(TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT), what=f"sequence {b} of {lens[b]}")
+    for _ in range(3):
+        np.testing.assert_array_equal(got, da.run())
+
+
+def test_merge_words_between_calls(oracle_mod):
+    """Calls of different shapes and lengths in turn on one workspace (the words of one lie in the partial results
+    of the other), sequences with a bad length or tree among them, then the good ones again."""
+    import torch
+    import gpu_util as gu
+    runs = []
+    for k, (B, T, Hq, Hkv, lens) in enumerate([(2, 60, 28, 4, [1696, 900]), (1, 60, 28, 4, [1696]), (3, 24, 8, 2, [400, 50, 1111])]):
+        cfg = gen.Config("mix", B, Hq, Hkv, 128, T, 5, 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2), paged=False)
+        inp = gen.attention_inputs(cfg, 950 + k, prefix_len=np.array(lens, dtype=np.int32))
+        runs.append((gu.DeviceAttn(inp), oracle_mod.tree_attention(inp, threads=8)))
+    ws = torch.zeros(max(da.ws_bytes for da, _ in runs), device="cuda", dtype=torch.uint8)
+    good = None
+    for rep in range(4):
+        for da, ref in runs:
+            da.ws = ws
+            if rep == 2:
+                good = da.prefix.clone(), da.parent.clone()
+                da.prefix[0] = -5
+                da.parent[-1, 0] = 3
+            got = da.run()
+            if rep == 2:
+                st = da.status.cpu().numpy()
+                assert (st[0] == 3 or len(st) == 1) and st[-1] in (1, 3)
+                da.prefix.copy_(good[0])
+                da.parent.copy_(good[1])
+            else:
+                for b in range(len(ref)):
+                    gu.check_close(got[b], ref[b], *TIGHT_SHORT, what=f"pass {rep} sequence {b}")
