@@ -160,7 +160,7 @@ __device__ __forceinline__ int64_t ml_block(const AttnParams& p, int64_t unit, i
 // trip to memory for the partials of n splits, spread over n CUs, in place of a second kernel (launch,
 // arguments, lengths, the same trip, drain: 5 us). A barrier between workgroups only ends when all of
 // them get to run, which nobody promises while other streams hold CUs. So the wait is bounded: who waits
-// longer than kMergeWait hands its share over to the workgroup that arrives last and leaves.
+// longer than p.merge_wait hands its share over to the workgroup that arrives last and leaves.
 //   word 0  kMergeTag << 40 | abandoned shares << 8 | arrivals. Anything else (first use of the workspace)
 //           counts as zero and is replaced before the first arrival; the last arrival puts it back to zero.
 //   word 1  changes when all have arrived (any initial value)
@@ -168,7 +168,6 @@ __device__ __forceinline__ int64_t ml_block(const AttnParams& p, int64_t unit, i
 static_assert(kMergeMaxSplits == 32, "bits of the abandoned set");
 constexpr uint64_t kMergeTag = 0xffc3a5ull;           // no partial result or (max, sum) pair looks like this (a NaN)
 constexpr uint64_t kMergeZero = kMergeTag << 40;
-constexpr uint64_t kMergeWait = 2000;                 // 20 us of the 100 MHz clock
 
 struct MergeGate {
     uint64_t* word; // null: the splits are merged by the combine kernel
@@ -186,7 +185,7 @@ __device__ __forceinline__ void merge_open(const MergeGate& g) {
 }
 // Thread 0, after every wave's partial results are in memory. Returns the splits whose shares this workgroup
 // has to merge besides its own; `go` false: its own share was handed over.
-__device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, int split, int n, bool& go) {
+__device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, uint32_t wait, int split, int n, bool& go) {
     go = true;
     const uint64_t gen = *g.gen;
     const uint64_t old = __hip_atomic_fetch_add(g.word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -198,7 +197,7 @@ __device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, int split, in
     const uint64_t t0 = wall_clock64();
     while (gate_load(g.word + kGateFlag) == gen) {
         __builtin_amdgcn_s_sleep(1);
-        if (wall_clock64() - t0 > kMergeWait) {
+        if (wall_clock64() - t0 > wait) {
             uint64_t w = gate_load(g.word);
             // zero or n arrivals: the last one has come in the meantime
             while ((int)(w & 0xff) != 0 && (int)(w & 0xff) != n) {
@@ -302,7 +301,7 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
     __syncthreads();
     if (tid == 0) {
         bool go;
-        s_word[0] = merge_meet(g, split, n, go);
+        s_word[0] = merge_meet(g, p.merge_wait, split, n, go);
         s_word[1] = go;
     }
     __syncthreads();

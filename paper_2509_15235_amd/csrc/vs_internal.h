@@ -49,6 +49,7 @@ struct AttnParams {
     float* part_ml;             // [unit][row block][split][32][2] running max (log2 domain), sum
     uint64_t* gates;            // two words per (unit, row group): the splits are merged by the workgroups that
                                 // computed them (attn_mfma_common.h); null: by the combine kernel
+    uint32_t merge_wait;        // how long a workgroup waits for the others at a gate (ticks of 10 ns)
     int32_t B, T, Hq, Hkv, d, group;
     int32_t tree_keys;          // T when the queries' own K/V sit behind the prefix (verification), 0 when they
                                 // attend to the prefix alone (the vision adaptor's compression attention)
@@ -176,6 +177,9 @@ inline int32_t validate_tree_host(const int32_t* parent, int32_t T) {
         if (parent[i] < 0 || parent[i] >= i) return VS_STATUS_BAD_PARENT;
     return VS_STATUS_OK;
 }
+
+// How long a workgroup waits at a gate before it hands its share over: 20 us. Tests set it to 0.
+extern "C" void vs_internal_set_merge_wait(uint32_t ticks);
 
 int32_t check_device(); // VS_OK when the current device is a gfx950, else VS_ERR_NO_DEVICE (api.hip)
 

@@ -70,3 +70,22 @@ def test_merge_words_between_calls(oracle_mod):
             else:
                 for b in range(len(ref)):
                     gu.check_close(got[b], ref[b], *TIGHT_SHORT, what=f"pass {rep} sequence {b}")
+
+
+@pytest.mark.parametrize("kw", [{}, dict(schedule=vs.VS_SCHED_RESIDENT), dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=8),
+                                dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=4)])
+def test_shares_handed_over(oracle_mod, kw):
+    """Nobody waits at the gate: every workgroup but a row group's last one leaves its share of the merge to it."""
+    import gpu_util as gu
+    cfg = gen.Config("handover", 2, 28, 4, 128, 60, 6, 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2), paged=False)
+    inp = gen.attention_inputs(cfg, 970, prefix_len=np.array([1100, 421], dtype=np.int32))
+    da = gu.DeviceAttn(inp, **kw)
+    assert da.plan().num_splits > 1 and da.plan().combine == 1
+    want = da.run()
+    try:
+        vs.lib().vs_internal_set_merge_wait(0)
+        for _ in range(4):
+            np.testing.assert_array_equal(da.run(), want)
+    finally:
+        vs.lib().vs_internal_set_merge_wait(2000)
+    np.testing.assert_array_equal(da.run(), want)
