@@ -37,13 +37,10 @@ __device__ __forceinline__ void take(Best& b, float v, int32_t i) {
 }
 
 __device__ __forceinline__ Best wave_best(Best b) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(b.v, o);
-        const int32_t oi = __shfl_xor(b.i, o);
-        take(b, ov, oi);
-    }
-    return b;
+    return wave_all(b, [](Best x, Best y) {
+        take(x, y.v, y.i);
+        return x;
+    });
 }
 
 // grid = B*T*chunks, block = 256. Writes one (value, index) pair per (row, chunk).
@@ -56,43 +53,34 @@ __global__ __launch_bounds__(kArgmaxBlock) void argmax_partial_kernel(const Acce
     const float* __restrict__ lg = p.logits + row * p.ld;
     const int begin = chunk * p.chunk_elems;
     const int end = min(p.V, begin + p.chunk_elems);
-    Best best = {-INFINITY, INT32_MAX};
-    if (p.vec_ok) {
-        // chunk_elems = 4 * kArgmaxBlock * kVecPerThread: every thread's loads are issued
-        // before the first compare. The maximum is found on values alone (one v_max per
-        // element); the index is recovered afterwards as the lowest position that equals the
-        // wave's maximum. NaN never equals anything and never survives fmaxf, -0 == +0.
-        const int nvec = (end - begin) >> 2;
-        const f32x4* __restrict__ lv = (const f32x4*)(lg + begin);
-        f32x4 a[kVecPerThread];
+    // chunk_elems = 4 * kArgmaxBlock * kVecPerThread: every thread's loads are issued
+    // before the first compare. The maximum is found on values alone (one v_max per
+    // element); the index is recovered afterwards as the lowest position that equals the
+    // wave's maximum. NaN never equals anything and never survives fmaxf, -0 == +0.
+    const int nvec = (end - begin) >> 2;
+    f32x4 a[kVecPerThread];
 #pragma unroll
-        for (int j = 0; j < kVecPerThread; ++j) {
-            const int k = threadIdx.x + j * kArgmaxBlock;
-            a[j] = (k < nvec) ? __builtin_nontemporal_load(lv + k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        }
-        float m = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < kVecPerThread; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) m = fmaxf(m, a[j][e]);
-        for (int t = begin + 4 * nvec + threadIdx.x; t < end; t += kArgmaxBlock) m = fmaxf(m, lg[t]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-        int32_t idx = INT32_MAX;
-        for (int t = begin + 4 * nvec + threadIdx.x; t < end; t += kArgmaxBlock)
-            if (lg[t] == m) idx = min(idx, t);
-#pragma unroll
-        for (int j = kVecPerThread - 1; j >= 0; --j) {
-            const int k = threadIdx.x + j * kArgmaxBlock;
-#pragma unroll
-            for (int e = 3; e >= 0; --e)
-                if (k < nvec && a[j][e] == m) idx = begin + 4 * k + e;
-        }
-        best.v = m;       // the wave's maximum; lanes without it keep INT32_MAX and lose the tie
-        best.i = idx;
-    } else {
-        for (int t = begin + threadIdx.x; t < end; t += kArgmaxBlock) take(best, lg[t], t);
+    for (int j = 0; j < kVecPerThread; ++j) {
+        const int k = threadIdx.x + j * kArgmaxBlock;
+        a[j] = (k < nvec) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     }
+    const int tail = begin + 4 * nvec + threadIdx.x; // at most three floats behind the last four
+    const float at = tail < end ? lg[tail] : -INFINITY;
+    float m = at;
+#pragma unroll
+    for (int j = 0; j < kVecPerThread; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m = fmaxf(m, a[j][e]);
+    m = wave_max(m);
+    int32_t idx = (tail < end && at == m) ? tail : INT32_MAX;
+#pragma unroll
+    for (int j = kVecPerThread - 1; j >= 0; --j) {
+        const int k = threadIdx.x + j * kArgmaxBlock;
+#pragma unroll
+        for (int e = 3; e >= 0; --e)
+            if (k < nvec && a[j][e] == m) idx = begin + 4 * k + e;
+    }
+    Best best = {m, idx}; // the wave's maximum; lanes without it keep INT32_MAX and lose the tie
     best = wave_best(best);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
@@ -151,12 +139,8 @@ __global__ __launch_bounds__(256) void accept_walk_kernel(const AcceptParams p) 
 #pragma unroll
             for (int q = 0; q < kPre; ++q) take(best, v[q], x[q]);
         }
-#pragma unroll
-        for (int o = 1; o <= 2; o <<= 1) {
-            const float ov = __shfl_xor(best.v, o);
-            const int32_t oi = __shfl_xor(best.i, o);
-            take(best, ov, oi);
-        }
+        take(best, __uint_as_float(dpp<kDppXor1>(__float_as_uint(best.v))), (int32_t)dpp<kDppXor1>(best.i));
+        take(best, __uint_as_float(dpp<kDppXor2>(__float_as_uint(best.v))), (int32_t)dpp<kDppXor2>(best.i));
         if (i < T && sub == 0) {
             // what a left-to-right '>' scan returns: a NaN in column 0 is never displaced,
             // and a row with nothing above -inf keeps index 0
@@ -184,8 +168,7 @@ __global__ __launch_bounds__(256) void accept_walk_kernel(const AcceptParams p) 
             }
             if (ok) key = dep * 64 + (63 - lane); // deepest first, then lowest index
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o));
+        key = wave_max(key);
         best_node = 63 - (key & 63); // the root is always accepted, so key >= 63
         alen = key >> 6;
         if (lane == 0) {
@@ -270,7 +253,6 @@ extern "C" int32_t vs_tree_accept_noalloc(const float* logits, int64_t ld_logits
     p.status = status;
     p.chunks = chunks;
     p.chunk_elems = kAcceptChunk;
-    p.vec_ok = (((uintptr_t)logits & 15u) == 0 && ld_logits % 4 == 0) ? 1 : 0;
     p.part_val = (float*)ws;
     p.part_idx = (int32_t*)(ws + (n * sizeof(float) + 255) / 256 * 256);
     return launch_accept(p, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;

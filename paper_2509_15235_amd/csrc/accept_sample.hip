@@ -24,17 +24,6 @@ constexpr int kKeepStats = 4096;          // (max, sum) pairs the walk kernel ca
 constexpr int kPerThread = 16;           // chunk elements per thread of the walk kernel
 static_assert(kWalkThreads * kPerThread == 4096, "the walk kernel scans one 4096-float chunk at a time");
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
 // grid = (chunks, B*T), block = 256: (max of the raw logits, sum of 2^((l - max) * k)) per chunk,
 // k = log2(e) / temperature.
 __global__ __launch_bounds__(kArgmaxBlock) void softmax_stats_partial_kernel(const SampleParams p) {
@@ -48,13 +37,12 @@ __global__ __launch_bounds__(kArgmaxBlock) void softmax_stats_partial_kernel(con
     const int end = min(p.V, begin + p.chunk_elems);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     f32x4 a[kVec];
-    const int nvec = p.vec_ok ? (end - begin) >> 2 : 0;
-    const f32x4* __restrict__ lv = (const f32x4*)(lg + begin);
+    const int nvec = (end - begin) >> 2;
     float m = -INFINITY;
 #pragma unroll
     for (int j = 0; j < kVec; ++j) {
         const int k = threadIdx.x + j * kArgmaxBlock;
-        a[j] = (k < nvec) ? __builtin_nontemporal_load(lv + k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        a[j] = (k < nvec) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
         for (int e = 0; e < 4; ++e) m = fmaxf(m, a[j][e]);
     }
@@ -214,11 +202,10 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
         const float* lg = p.logits + ((int64_t)b * T + node) * p.ld;
         const float M = sM[node];
         const int j0 = c * p.chunk_elems + tid * kPerThread;
-        if (p.vec_ok && j0 + kPerThread <= p.V) {
-            const f32x4* lv = (const f32x4*)(lg + j0);
+        if (j0 + kPerThread <= p.V) {
 #pragma unroll
             for (int q = 0; q < kPerThread / 4; ++q) {
-                const f32x4 a = lv[q];
+                const f32x4 a = *(const f32x4_any*)(lg + j0 + 4 * q);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[4 * q + e] = __builtin_amdgcn_exp2f((a[e] - M) * p.k_log2);
             }
@@ -380,9 +367,7 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
         for (int e = 0; e < kPerThread; ++e)
             if (w[e] > 0.f) last = j0 + e;
         // one LDS atomic per wave, not per thread (256 atomics on one address take microseconds)
-        int wlast = last;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) wlast = max(wlast, __shfl_xor(wlast, o));
+        const int wlast = wave_max(last);
         if (lane == 0 && wlast >= 0) atomicMax(&slast, wlast);
         int cand = INT32_MAX;
         if (inc > local && last >= 0) {
@@ -397,8 +382,7 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
             }
             if (cand < 0) cand = last;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) cand = min(cand, __shfl_xor(cand, o));
+        cand = wave_min(cand);
         if (lane == 0 && cand != INT32_MAX) atomicMin(&spick, cand);
     }
     __syncthreads();

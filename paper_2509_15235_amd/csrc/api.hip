@@ -331,6 +331,7 @@ size_t workspace_bytes(const vs_attn_desc* d, const Plan& pl) {
 
 constexpr int kArgmaxChunk = kAcceptChunk;
 
+int32_t draft_chunks(int32_t V) { return (int32_t)(((int64_t)V + kDraftChunk - 1) / kDraftChunk); }
 int32_t accept_chunks(int32_t V) { return (V + kArgmaxChunk - 1) / kArgmaxChunk; }
 
 } // namespace
@@ -541,7 +542,6 @@ int32_t vs_tree_accept(const float* logits, int64_t ld_logits, int32_t V, const 
     p.status = status;
     p.chunks = accept_chunks(V);
     p.chunk_elems = kArgmaxChunk;
-    p.vec_ok = (aligned16(logits) && ld_logits % 4 == 0) ? 1 : 0;
     const size_t n = (size_t)B * T * p.chunks;
     p.part_val = (float*)workspace;
     p.part_idx = (int32_t*)((char*)workspace + align_up(n * sizeof(float)));
@@ -584,7 +584,6 @@ int32_t vs_tree_accept_sample(const float* logits, int64_t ld_logits, int32_t V,
     p.k_log2 = 1.4426950408889634f / temperature;
     p.chunks = accept_chunks(V);
     p.chunk_elems = kArgmaxChunk;
-    p.vec_ok = (aligned16(logits) && ld_logits % 4 == 0) ? 1 : 0;
     const size_t n = (size_t)B * T * p.chunks;
     p.part_m = (float*)workspace;
     p.part_s = (float*)((char*)workspace + align_up(n * sizeof(float)));
@@ -593,8 +592,8 @@ int32_t vs_tree_accept_sample(const float* logits, int64_t ld_logits, int32_t V,
 
 size_t vs_draft_expand_workspace_bytes(int32_t B, int32_t F, int32_t V, int32_t K) {
     if (B < 1 || F < 1 || F > VS_MAX_TREE || K < 1 || K > kMaxDraftK || F * K > kMaxDraftCand || V < K) return 0;
-    const size_t n = (size_t)B * F * accept_chunks(V);
-    return 2 * align_up(n * sizeof(float)) + 2 * align_up(n * K * sizeof(float));
+    const size_t n = (size_t)B * F * accept_chunks(V); // (what it was with 4096-float chunks; a quarter of it is used)
+    return 2 * align_up(n * sizeof(float)) + 2 * align_up(n * K * sizeof(float)) + (size_t)B * kArrivalWords * sizeof(uint64_t);
 }
 
 int32_t vs_draft_expand(const float* logits, int64_t ld_logits, int32_t V, const float* cum_in,
@@ -625,9 +624,7 @@ int32_t vs_draft_expand(const float* logits, int64_t ld_logits, int32_t V, const
     p.cand_parent = cand_parent;
     p.next_frontier_cand = next_frontier_cand;
     p.next_cum = next_cum;
-    p.chunks = accept_chunks(V);
-    p.chunk_elems = kArgmaxChunk;
-    p.vec_ok = (aligned16(logits) && ld_logits % 4 == 0) ? 1 : 0;
+    p.chunks = draft_chunks(V);
     const size_t n = (size_t)B * F * p.chunks;
     char* w = (char*)workspace;
     p.part_m = (float*)w;
@@ -637,6 +634,8 @@ int32_t vs_draft_expand(const float* logits, int64_t ld_logits, int32_t V, const
     p.part_tv = (float*)w;
     w += align_up(n * K * sizeof(float));
     p.part_ti = (int32_t*)w;
+    w += align_up(n * K * sizeof(float));
+    p.arrivals = (uint64_t*)w;
     return launch_draft_expand(p, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
 }
 

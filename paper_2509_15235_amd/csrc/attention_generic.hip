@@ -6,15 +6,6 @@
 
 namespace vs {
 
-__device__ __forceinline__ float wave_max(float v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
 // grid = (T, Hq, B), block = 64. Lane j scores key j0 + j of each 64-key chunk; for the
 // value product lane c owns channels c, c + 64, ...
 template <int D>

@@ -5,24 +5,26 @@
 // children as the next frontier; at the end the N best-scored candidates of all levels are
 // the tree. The draft model's forward pass is not part of this: its logits are inputs.
 //
-// Three kernels: (1) a bandwidth-bound scan that reduces every 4096-float chunk of a logits
-// row to (maximum, sum of exp, the chunk's K largest entries); (2) one workgroup per sequence
-// that merges the chunks into each row's top K and log-sum-exp, scores the F*K candidates and
-// picks the next frontier; (3) one workgroup per sequence for the final selection, which
-// ranks candidates by counting and emits parent[] / tokens[] in candidate order.
+// Two kernels. (1) An expansion: every workgroup reduces a 16384-float chunk of a logits row to (maximum, sum of
+// exp, the chunk's K largest entries); the workgroup of a sequence that finishes last merges the chunks into each
+// row's top K and log-sum-exp, scores the F*K candidates and picks the next frontier. (That second part used to
+// be a kernel of its own: 7.8 us for one trip to memory and half a microsecond of work, three times per tree.)
+// (2) One workgroup per sequence for the final selection, which emits parent[] / tokens[] in candidate order.
 //
-// Selection without bookkeeping: entries are extracted in the strict total order
-// (value descending, index ascending), so "the next one" is simply the best entry that comes
-// strictly after the previous winner in that order - nothing has to be marked as taken.
+// Selection without bookkeeping: entries are taken in the strict total order (value descending, index
+// ascending). A bound that at least K entries reach is found bit by bit with ballots, the few entries at or
+// above it are compacted and ranked by counting; nothing has to be marked as taken.
 #include "vs_device.h"
 
 namespace vs {
 
 namespace {
 
-constexpr int kVec = 4;          // 16-byte loads per thread and chunk (chunk = 4096 floats)
+constexpr int kVec = 4;          // 16-byte loads per thread and chunk
 constexpr int kSelThreads = 256;
 constexpr int kExpandThreads = 1024;
+constexpr int kExpandWaves = kExpandThreads / kWave;
+static_assert(kDraftChunk == kExpandThreads * kVec * 4, "a chunk is one set of loads");
 
 struct Ent {
     float v;
@@ -35,22 +37,7 @@ __device__ __forceinline__ bool before(float av, int32_t ai, float bv, int32_t b
 }
 
 __device__ __forceinline__ Ent wave_first(Ent e) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(e.v, o);
-        const int32_t oi = __shfl_xor(e.i, o);
-        if (before(ov, oi, e.v, e.i)) {
-            e.v = ov;
-            e.i = oi;
-        }
-    }
-    return e;
-}
-
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
+    return wave_all(e, [](Ent x, Ent y) { return before(y.v, y.i, x.v, x.i) ? y : x; });
 }
 
 constexpr int32_t kNone = INT32_MAX; // index of "no entry": loses every comparison at value -inf
@@ -101,12 +88,23 @@ __device__ __forceinline__ void wave_topk(const float (&v)[NE], const int32_t (&
     }
     if (n <= kCandCap) {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the list is read by other lanes of this wave
-        for (int t = lane; t < n; t += kWave) {
-            const float tv = cv[t];
-            const int32_t ti = ci[t];
+        if (n <= kWave) { // one entry per lane, the others' by v_readlane
+            const float tv = lane < n ? cv[lane] : -INFINITY;
+            const int32_t ti = lane < n ? ci[lane] : kNone;
             int rank = 0;
-            for (int o = 0; o < n; ++o) rank += before(cv[o], ci[o], tv, ti) ? 1 : 0;
-            if (rank < K) emit(rank, tv, ti);
+            for (int o = 0; o < n; ++o) {
+                const float ov = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, tv), o));
+                rank += before(ov, __builtin_amdgcn_readlane(ti, o), tv, ti) ? 1 : 0;
+            }
+            if (lane < n && rank < K) emit(rank, tv, ti);
+        } else {
+            for (int t = lane; t < n; t += kWave) {
+                const float tv = cv[t];
+                const int32_t ti = ci[t];
+                int rank = 0;
+                for (int o = 0; o < n; ++o) rank += before(cv[o], ci[o], tv, ti) ? 1 : 0;
+                if (rank < K) emit(rank, tv, ti);
+            }
         }
         for (int r = n + lane; r < K; r += kWave) emit(r, -INFINITY, kNone);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // reads done before the list is reused
@@ -127,136 +125,107 @@ __device__ __forceinline__ void wave_topk(const float (&v)[NE], const int32_t (&
     }
 }
 
-// grid = (chunks, B*F), block = 256.
-__global__ __launch_bounds__(kArgmaxBlock) void draft_topk_partial_kernel(const DraftExpandParams p) {
-    __shared__ float sv[kArgmaxBlock / kWave];
-    __shared__ float ss[kArgmaxBlock / kWave];
-    __shared__ float s_cv[(kArgmaxBlock / kWave) * kCandCap];
-    __shared__ int32_t s_ci[(kArgmaxBlock / kWave) * kCandCap];
-    __shared__ float s_wv[(kArgmaxBlock / kWave) * kMaxDraftK];
-    __shared__ int32_t s_wi[(kArgmaxBlock / kWave) * kMaxDraftK];
-    // one-dimensional grid: workgroup id = row * chunks + chunk (the host keeps the product below 2^31)
-    const int64_t row = blockIdx.x / (uint32_t)p.chunks;
-    const int chunk = (int)(blockIdx.x - (uint32_t)row * (uint32_t)p.chunks);
-    const float* __restrict__ lg = p.logits + row * p.ld;
-    const int begin = chunk * p.chunk_elems;
-    const int end = min(p.V, begin + p.chunk_elems);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // every thread holds 16 entries: from 16-byte loads when rows are aligned, else scalar
-    float a[4 * kVec];
-    int32_t base_idx[kVec]; // index of a[4*j]; entries 4*j .. 4*j+3 are consecutive
-    int32_t lim[kVec];      // how many of the four are real entries of this chunk
-    const int nvec = (end - begin) >> 2;
-    if (p.vec_ok) {
-        const f32x4* __restrict__ lv = (const f32x4*)(lg + begin);
-#pragma unroll
-        for (int j = 0; j < kVec; ++j) {
-            const int k = threadIdx.x + j * kArgmaxBlock;
-            const f32x4 x = (k < nvec) ? __builtin_nontemporal_load(lv + k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-            base_idx[j] = begin + 4 * k;
-            lim[j] = (k < nvec) ? 4 : 0; // the chunk's last 1-3 floats (V % 4) are the scalar tail below
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[4 * j + e] = x[e];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kVec; ++j) {
-            const int k = threadIdx.x + j * kArgmaxBlock;
-            base_idx[j] = begin + 4 * k;
-            lim[j] = max(0, min(4, end - (begin + 4 * k)));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[4 * j + e] = (begin + 4 * k + e < end) ? lg[begin + 4 * k + e] : -INFINITY;
-        }
-    }
-    // scalar tail of the vector path: at most 3 entries, owned by the threads 0..2
-    float tail_v = -INFINITY;
-    int32_t tail_i = kNone;
-    if (p.vec_ok) {
-        const int t = begin + 4 * nvec + threadIdx.x;
-        if (t < end) {
-            tail_v = lg[t];
-            tail_i = t;
-        }
-    }
-    auto valid = [&](int j, int e) { return e < lim[j]; };
-
-    // ---- maximum and sum of exp
-    float m = tail_v;
-#pragma unroll
-    for (int q = 0; q < 4 * kVec; ++q) m = fmaxf(m, a[q]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (lane == 0) sv[wave] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-    float s = 0.f;
-    if (m > -INFINITY) {
-#pragma unroll
-        for (int q = 0; q < 4 * kVec; ++q) s += __builtin_amdgcn_exp2f((a[q] - m) * 1.4426950408889634f);
-        if (tail_i != kNone) s += __builtin_amdgcn_exp2f((tail_v - m) * 1.4426950408889634f);
-    }
-    s = wave_sum(s);
-    if (lane == 0) ss[wave] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        p.part_m[row * p.chunks + chunk] = m;
-        p.part_s[row * p.chunks + chunk] = (ss[0] + ss[1]) + (ss[2] + ss[3]);
-    }
-
-    // ---- the chunk's K first entries in (value descending, index ascending): per wave, then merged
+// grid = B * F * chunks, block = 1024.
+__global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const DraftExpandParams p) {
+    __shared__ float s_m[kExpandWaves], s_s[kExpandWaves];
+    __shared__ float s_cv[kExpandWaves * kCandCap];
+    __shared__ int32_t s_ci[kExpandWaves * kCandCap];
+    __shared__ float s_wv[kExpandWaves * kMaxDraftK];
+    __shared__ int32_t s_wi[kExpandWaves * kMaxDraftK];
+    __shared__ float s_score[kMaxDraftCand];
+    __shared__ int32_t s_token[kMaxDraftCand];
+    __shared__ uint8_t s_keep[kMaxDraftCand];
+    __shared__ int32_t s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int F = p.F, K = p.K;
+    int b;
     {
+        // workgroup id = row * chunks + chunk (the host keeps the product below 2^31)
+        const int64_t row = blockIdx.x / (uint32_t)p.chunks;
+        const int chunk = (int)(blockIdx.x - (uint32_t)row * (uint32_t)p.chunks);
+        b = (int)(row / F);
+        const float* __restrict__ lg = p.logits + row * p.ld;
+        const int begin = chunk * kDraftChunk;
+        const int end = min(p.V, begin + kDraftChunk);
+        // every thread holds 16 entries and perhaps one of the up to three behind the last four
+        const int nvec = (end - begin) >> 2;
         float ev[4 * kVec + 1];
         int32_t ei[4 * kVec + 1];
 #pragma unroll
-        for (int j = 0; j < kVec; ++j)
+        for (int j = 0; j < kVec; ++j) {
+            const int k = tid + j * kExpandThreads;
+            const f32x4 x = (k < nvec) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                ev[4 * j + e] = a[4 * j + e];
-                ei[4 * j + e] = valid(j, e) ? base_idx[j] + e : kNone;
+                ev[4 * j + e] = x[e];
+                ei[4 * j + e] = k < nvec ? begin + 4 * k + e : kNone;
             }
-        ev[4 * kVec] = tail_v;
-        ei[4 * kVec] = tail_i;
-        const int K = p.K;
+        }
+        const int tail = begin + 4 * nvec + tid;
+        ev[4 * kVec] = tail < end ? lg[tail] : -INFINITY;
+        ei[4 * kVec] = tail < end ? tail : kNone;
+        if (tid == 0) arrival_open(p.arrivals + (int64_t)b * kArrivalWords);
+
+        // ---- per wave: maximum, sum of exp, the K first entries; one barrier, then wave 0 merges the waves
+        float m = ev[0];
+#pragma unroll
+        for (int q = 1; q <= 4 * kVec; ++q) m = fmaxf(m, ev[q]);
+        m = wave_max(m);
+        float s = 0.f;
+        if (m > -INFINITY) {
+#pragma unroll
+            for (int q = 0; q <= 4 * kVec; ++q) s += __builtin_amdgcn_exp2f((ev[q] - m) * 1.4426950408889634f); // exp2(-inf) = 0
+        }
+        s = wave_sum(s);
+        if (lane == 0) {
+            s_m[wave] = m;
+            s_s[wave] = s;
+        }
         wave_topk(ev, ei, K, s_cv + wave * kCandCap, s_ci + wave * kCandCap, [&](int r, float v, int32_t i) {
             s_wv[wave * kMaxDraftK + r] = v;
             s_wi[wave * kMaxDraftK + r] = i;
         });
         __syncthreads();
         if (wave == 0) {
-            constexpr int kWaves = kArgmaxBlock / kWave;
-            float mv[1];
-            int32_t mi[1];
-            const int w = lane / K, r = lane - w * K; // lane < kWaves * K <= 64 holds wave w's r-th entry
-            const bool has = lane < kWaves * K;
-            mv[0] = has ? s_wv[w * kMaxDraftK + r] : -INFINITY;
-            mi[0] = has ? s_wi[w * kMaxDraftK + r] : kNone;
+            const float wm = lane < kExpandWaves ? s_m[lane] : -INFINITY;
+            const float cm = wave_max(wm);
+            const float cs = wave_sum(wm > -INFINITY ? s_s[lane & (kExpandWaves - 1)] * __builtin_amdgcn_exp2f((wm - cm) * 1.4426950408889634f) : 0.f);
+            if (lane == 0) {
+                store_device(p.part_m + row * p.chunks + chunk, cm);
+                store_device(p.part_s + row * p.chunks + chunk, cs);
+            }
+            constexpr int NE = kExpandWaves * kMaxDraftK / kWave;
+            float mv[NE];
+            int32_t mi[NE];
+#pragma unroll
+            for (int q = 0; q < NE; ++q) { // entry (wave w, rank r) = w * K + r
+                const int e = lane + q * kWave, w = e / K, r = e - w * K;
+                const bool has = w < kExpandWaves;
+                mv[q] = has ? s_wv[w * kMaxDraftK + r] : -INFINITY;
+                mi[q] = has ? s_wi[w * kMaxDraftK + r] : kNone;
+            }
             float* out_v = p.part_tv + (row * p.chunks + chunk) * K;
             int32_t* out_i = p.part_ti + (row * p.chunks + chunk) * K;
             wave_topk(mv, mi, K, s_cv, s_ci, [&](int rr, float v, int32_t i) {
-                out_v[rr] = v;
-                out_i[rr] = i; // kNone when the chunk has fewer than rr+1 entries
+                store_device(out_v + rr, v);
+                store_device(out_i + rr, i); // kNone when the chunk has fewer than rr+1 entries
             });
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this chunk's results are in memory
+            if (lane == 0) s_last = arrival_last(p.arrivals + (int64_t)b * kArrivalWords, (uint32_t)(F * p.chunks)) ? 1 : 0;
         }
+        __syncthreads();
+        if (s_last == 0) return;
     }
-}
 
-// grid = B, block = 1024: one wave per frontier row (rows beyond sixteen take turns).
-__global__ __launch_bounds__(kExpandThreads) void draft_expand_select_kernel(const DraftExpandParams p) {
-    __shared__ float s_score[kMaxDraftCand];
-    __shared__ int32_t s_token[kMaxDraftCand];
-    __shared__ uint8_t s_keep[kMaxDraftCand];
-    __shared__ float s_cv[(kExpandThreads / kWave) * kCandCap];
-    __shared__ int32_t s_ci[(kExpandThreads / kWave) * kCandCap];
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int F = p.F, K = p.K, C = F * K;
+    // ---- the sequence's last workgroup: one wave per frontier row (rows beyond sixteen take turns)
+    const int C = F * K;
     const int keep = min(K, C);
     // candidate tid's parent (the frontier row it extends): requested now, written out at the end
     // (C <= kMaxDraftCand = the block size, so a thread owns at most one candidate)
     const int32_t par_own = (tid < C && p.frontier_cand) ? p.frontier_cand[(int64_t)b * F + tid / K] : -1;
 
     // ---- per row: log-sum-exp and the K first entries of the merged chunk lists
-    for (int f = wave; f < F; f += kExpandThreads / kWave) {
+    for (int f = wave; f < F; f += kExpandWaves) {
         const int64_t row = (int64_t)b * F + f;
         const float* pm = p.part_m + row * p.chunks;
         const float* ps = p.part_s + row * p.chunks;
@@ -267,25 +236,24 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_select_kernel(con
         // 64 chunks; a longer row loops below), the chunk lists when they fit in registers, the score
         constexpr int kRegEnt = 8;
         const bool in_regs = n <= kWave * kRegEnt;
-        float m0 = (lane < p.chunks) ? pm[lane] : -INFINITY;
-        float s0 = (lane < p.chunks) ? ps[lane] : 0.f;
+        float m0 = (lane < p.chunks) ? load_device(pm + lane) : -INFINITY;
+        float s0 = (lane < p.chunks) ? load_device(ps + lane) : 0.f;
         float rv[kRegEnt];
         int32_t ri[kRegEnt];
 #pragma unroll
         for (int q = 0; q < kRegEnt; ++q) {
             const int e = lane + q * kWave;
-            rv[q] = (in_regs && e < n) ? tv[e] : -INFINITY;
-            ri[q] = (in_regs && e < n) ? ti[e] : kNone;
+            rv[q] = (in_regs && e < n) ? load_device(tv + e) : -INFINITY;
+            ri[q] = (in_regs && e < n) ? load_device(ti + e) : kNone;
         }
         const float cum = p.cum_in ? p.cum_in[row] : 0.f;
         float m = m0;
-        for (int c = lane + kWave; c < p.chunks; c += kWave) m = fmaxf(m, pm[c]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+        for (int c = lane + kWave; c < p.chunks; c += kWave) m = fmaxf(m, load_device(pm + c));
+        m = wave_max(m);
         float z = (m0 > -INFINITY) ? s0 * __builtin_amdgcn_exp2f((m0 - m) * 1.4426950408889634f) : 0.f;
         for (int c = lane + kWave; c < p.chunks; c += kWave) {
-            const float mc = pm[c];
-            if (mc > -INFINITY) z += ps[c] * __builtin_amdgcn_exp2f((mc - m) * 1.4426950408889634f);
+            const float mc = load_device(pm + c);
+            if (mc > -INFINITY) z += load_device(ps + c) * __builtin_amdgcn_exp2f((mc - m) * 1.4426950408889634f);
         }
         z = wave_sum(z);
         const float lse = m + __logf(z);
@@ -295,14 +263,14 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_select_kernel(con
         };
         if (in_regs) {
             wave_topk(rv, ri, K, s_cv + wave * kCandCap, s_ci + wave * kCandCap, emit);
-        } else { // very long rows: the lists are re-read from the workspace (L2) for every extracted entry
+        } else { // very long rows: the lists are re-read from the workspace for every extracted entry
             float last_v = INFINITY;
             int32_t last_i = -1;
             for (int r = 0; r < K; ++r) {
                 Ent mine = {-INFINITY, kNone};
                 for (int q = lane; q < n; q += kWave) {
-                    const float v = tv[q];
-                    const int32_t i = ti[q];
+                    const float v = load_device(tv + q);
+                    const int32_t i = load_device(ti + q);
                     if (i != kNone && before(last_v, last_i, v, i) && before(v, i, mine.v, mine.i)) mine = {v, i};
                 }
                 const Ent w = wave_first(mine);
@@ -365,11 +333,18 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_select_kernel(con
 // grid = B, block = 256.
 __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const DraftBuildParams p) {
     constexpr int kWords = kMaxDraftTotal / 64;
+    constexpr int kRounds = kMaxDraftTotal / kSelThreads; // candidates per thread, at most
+    constexpr int kSelWaves = kSelThreads / kWave;
+    constexpr int kList = 256;                            // candidates that can be ranked among themselves
     __shared__ __attribute__((aligned(16))) float s_score[kMaxDraftTotal + 4];
     __shared__ int32_t s_parent[kMaxDraftTotal];
     __shared__ uint64_t s_mask[kWords];   // picked candidates, one bit each
     __shared__ int32_t s_before[kWords];  // picked candidates below word w
     __shared__ int32_t s_bad;
+    __shared__ uint32_t s_top[kSelThreads];               // every thread's largest key
+    __shared__ __attribute__((aligned(16))) float s_lv[kList];
+    __shared__ __attribute__((aligned(16))) int32_t s_li[kList];
+    __shared__ int32_t s_n;
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int M = p.M, N = p.N;
@@ -377,35 +352,114 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
     const int32_t* tok = p.cand_token + (int64_t)b * p.cand_capacity;
     const float* score = p.cand_score + (int64_t)b * p.cand_capacity;
     const int32_t* par = p.cand_parent + (int64_t)b * p.cand_capacity;
-    const int rounds = (M + kSelThreads - 1) / kSelThreads; // every thread runs all rounds: the ballots need whole waves
-    if (tid == 0) s_bad = 0;
-    __syncthreads();
+    float v[kRounds];
+    int32_t pc_own[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) { // candidate r * 256 + tid
+        const int c = r * kSelThreads + tid;
+        v[r] = c < M ? score[c] : -INFINITY;
+        pc_own[r] = c < M ? par[c] : -1;
+    }
+    if (tid == 0) {
+        s_bad = 0;
+        s_n = 0;
+    }
+    if (tid < kWords) s_mask[tid] = 0;
+    uint32_t top = 0;
+    bool bad_own = false;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int c = r * kSelThreads + tid;
+        if (c < M) {
+            s_score[c] = v[r];
+            s_parent[c] = pc_own[r];
+            bad_own |= pc_own[r] < -1 || pc_own[r] >= c;
+            top = max(top, order_key(v[r]));
+        }
+    }
+    s_top[tid] = top;
     if (tid < ((M + 3) & ~3) - M) s_score[M + tid] = -INFINITY; // padding of the last group of four
-    for (int c = tid; c < M; c += kSelThreads) {
-        s_score[c] = score[c];
-        const int32_t pc = par[c];
-        s_parent[c] = pc;
-        if (pc < -1 || pc >= c) atomicOr(&s_bad, 1);
+    __syncthreads();
+    if (__ballot(bad_own) && lane == 0) atomicOr(&s_bad, 1);
+    // The `take`-th largest of the threads' own largest scores is a bound that at least `take` candidates reach
+    // (none if fewer threads hold a candidate); those that reach it are few. Every wave finds it for itself.
+    // (Ranking all candidates among all took 85 us at 800 candidates.)
+    uint32_t tops[kSelWaves];
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) tops[w] = s_top[w * kWave + lane];
+    uint32_t bound = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t trial = bound | (1u << bit);
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < kSelWaves; ++w) n += __popcll(__ballot(tops[w] >= trial));
+        if (n >= take) bound = trial;
+    }
+    int base = 0;
+    bool in[kRounds];
+    {
+        int mine = 0;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int c = r * kSelThreads + tid;
+            in[r] = c < M && order_key(v[r]) >= bound;
+            mine += __popcll(__ballot(in[r]));
+        }
+        if (lane == 0) base = atomicAdd(&s_n, mine); // the order of the list does not matter
+        base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const uint64_t m = __ballot(in[r]);
+            const int pos = base + __popcll(m & ((1ull << lane) - 1ull));
+            if (in[r] && pos < kList) {
+                s_lv[pos] = v[r];
+                s_li[pos] = r * kSelThreads + tid;
+            }
+            base += __popcll(m);
+        }
     }
     __syncthreads();
-    // rank by counting (four scores per LDS read; a padding entry is -inf at an index >= M > c,
-    // which comes before nothing), picked = rank < take, one bit per candidate
-    const int M4 = (M + 3) & ~3;
-    for (int r = 0; r < rounds; ++r) {
-        const int c = r * kSelThreads + tid;
-        bool pick = false;
-        if (c < M) {
-            const float sc = s_score[c];
-            int rank = 0;
-            for (int o = 0; o < M4; o += 4) {
-                const f32x4 so = *(const f32x4*)&s_score[o];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rank += before(so[e], o + e, sc, c) ? 1 : 0;
-            }
-            pick = rank < take;
+    const int n = s_n;
+    if (n <= kList) {
+        // rank by counting among the list, picked = rank < take, one bit per candidate
+        if (tid < ((n + 3) & ~3) - n) { // (n is a multiple of four at kList)
+            s_lv[n + tid] = -INFINITY;
+            s_li[n + tid] = kNone;
         }
-        const uint64_t m = __ballot(pick);
-        if (lane == 0) s_mask[c >> 6] = m;
+        __syncthreads();
+        if (tid < n) {
+            const float sc = s_lv[tid];
+            const int c = s_li[tid];
+            int rank = 0;
+#pragma unroll 4
+            for (int o = 0; o < n; o += 4) {
+                const f32x4 so = *(const f32x4*)&s_lv[o];
+                const u32x4 io = *(const u32x4*)&s_li[o];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rank += before(so[e], (int32_t)io[e], sc, c) ? 1 : 0;
+            }
+            if (rank < take) atomicOr((unsigned long long*)&s_mask[c >> 6], 1ull << (c & 63));
+        }
+    } else {
+        // a plateau of equal scores: rank every candidate among all (four scores per LDS read; a padding entry
+        // is -inf at an index >= M > c, which comes before nothing)
+        const int M4 = (M + 3) & ~3;
+        for (int r = 0; r < kRounds && r * kSelThreads < M; ++r) { // every thread runs all rounds: the ballots need whole waves
+            const int c = r * kSelThreads + tid;
+            bool pick = false;
+            if (c < M) {
+                const float sc = s_score[c];
+                int rank = 0;
+                for (int o = 0; o < M4; o += 4) {
+                    const f32x4 so = *(const f32x4*)&s_score[o];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) rank += before(so[e], o + e, sc, c) ? 1 : 0;
+                }
+                pick = rank < take;
+            }
+            const uint64_t m = __ballot(pick);
+            if (lane == 0) s_mask[c >> 6] = m;
+        }
     }
     __syncthreads();
     const int words = (M + 63) >> 6;
@@ -453,10 +507,7 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
 } // namespace
 
 hipError_t launch_draft_expand(const DraftExpandParams& p, hipStream_t s) {
-    hipLaunchKernelGGL(draft_topk_partial_kernel, dim3((unsigned)((int64_t)p.chunks * p.B * p.F)), dim3(kArgmaxBlock), 0, s, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(draft_expand_select_kernel, dim3(p.B), dim3(kExpandThreads), 0, s, p);
+    hipLaunchKernelGGL(draft_expand_kernel, dim3((unsigned)((int64_t)p.chunks * p.B * p.F)), dim3(kExpandThreads), 0, s, p);
     return hipGetLastError();
 }
 

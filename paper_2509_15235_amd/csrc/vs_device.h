@@ -29,6 +29,102 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return (uint32_t)float_to_bf16_bits(lo) | ((uint32_t)float_to_bf16_bits(hi) << 16);
 }
 
+// ---- Wave-wide reductions on the vector ALU (DPP and lane swaps; a shuffle goes through LDS and takes ten times
+// as long, six in a row about 0.3 us). Lanes pair up as in a xor butterfly from 32 down to 1.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B, kDppXor7 = 0x141, kDppXor8 = 0x128;
+// op over all 64 lanes, in every lane; T: one or more 32-bit words; op is commutative and associative
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_all(T x, Op op) {
+    constexpr int W = sizeof(T) / 4;
+    typedef __attribute__((ext_vector_type(W))) uint32_t words;
+    words w = __builtin_bit_cast(words, x), lo, hi;
+    auto join = [&]() __attribute__((always_inline)) {
+        w = __builtin_bit_cast(words, op(__builtin_bit_cast(T, lo), __builtin_bit_cast(T, hi)));
+    };
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const u32x2 r = __builtin_amdgcn_permlane32_swap(w[i], w[i], false, false);
+        lo[i] = r[0];
+        hi[i] = r[1];
+    }
+    join();
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const u32x2 r = __builtin_amdgcn_permlane16_swap(w[i], w[i], false, false);
+        lo[i] = r[0];
+        hi[i] = r[1];
+    }
+    join();
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        lo[i] = w[i];
+        hi[i] = dpp<kDppXor8>(w[i]);
+    }
+    join();
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        lo[i] = w[i];
+        hi[i] = dpp<kDppXor7>(dpp<kDppXor3>(w[i])); // xor 4
+    }
+    join();
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        lo[i] = w[i];
+        hi[i] = dpp<kDppXor2>(w[i]);
+    }
+    join();
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        lo[i] = w[i];
+        hi[i] = dpp<kDppXor1>(w[i]);
+    }
+    join();
+    return __builtin_bit_cast(T, w);
+}
+__device__ __forceinline__ float wave_max(float x) {
+    return wave_all(x, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float wave_sum(float x) {
+    return wave_all(x, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ int32_t wave_max(int32_t x) {
+    return wave_all(x, [](int32_t a, int32_t b) { return max(a, b); });
+}
+__device__ __forceinline__ int32_t wave_min(int32_t x) {
+    return wave_all(x, [](int32_t a, int32_t b) { return min(a, b); });
+}
+
+// Sixteen bytes at any address that is a multiple of four (a row of logits need not start at a multiple of sixteen).
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+__device__ __forceinline__ f32x4 load4_stream(const float* p) { return __builtin_nontemporal_load((const f32x4_any*)p); }
+
+// ---- Results that workgroups hand to each other inside a kernel: device scope, past this XCD's L2.
+template <typename T>
+__device__ __forceinline__ void store_device(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T load_device(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Who of n workgroups comes last. The word may hold anything before its first use (a value without the tag counts as
+// zero and is replaced before the first arrival) and is back at zero when the last one has come.
+constexpr uint64_t kArrivalZero = 0xffc3a57bull << 32; // a NaN: no partial result looks like this
+__device__ __forceinline__ void arrival_open(uint64_t* w) { // one thread of each, any time before it arrives
+    uint64_t v = load_device(w);
+    if ((v >> 32) != (kArrivalZero >> 32))
+        __hip_atomic_compare_exchange_strong(w, &v, kArrivalZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool arrival_last(uint64_t* w, uint32_t n) { // that thread, when its workgroup's results are in memory
+    const bool last = (uint32_t)__hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    if (last) store_device(w, kArrivalZero);
+    return last;
+}
+
 // Loads one tree's parent row into LDS and checks it (parent[0] == -1, 0 <= parent[i] < i).
 // Every thread of the workgroup must call it; blockDim.x >= T. Returns the vs_status.
 __device__ __forceinline__ int32_t load_tree(const int32_t* __restrict__ parent_row, int T,

@@ -89,7 +89,6 @@ struct AcceptParams {
     int32_t* part_idx;   // [B*T][chunks]
     int32_t chunks;
     int32_t chunk_elems; // multiple of 4
-    int32_t vec_ok;      // rows are 16-byte aligned → float4 loads
 };
 
 constexpr int kMaxSampleChunks = 2048; // chunk sums of one logits row kept in LDS by the sampling walk
@@ -112,9 +111,10 @@ struct SampleParams {
     float k_log2;          // log2(e) / temperature
     int32_t chunks;
     int32_t chunk_elems;   // 4096
-    int32_t vec_ok;        // rows are 16-byte aligned → float4 loads
 };
 
+constexpr int kDraftChunk = 16384;    // floats of a logits row per workgroup of an expansion: 1024 threads x 4 x 16 bytes
+constexpr int kArrivalWords = 16;     // 64-bit words from one arrival counter to the next: a cache line
 constexpr int kMaxDraftK = 16;        // children per frontier node
 constexpr int kMaxDraftCand = 1024;   // F * K candidates of one expansion step
 constexpr int kMaxDraftTotal = 2048;  // candidates of all levels at the final selection
@@ -136,7 +136,8 @@ struct DraftExpandParams {
     float* part_s;
     float* part_tv;               // [B*F][chunks][K]
     int32_t* part_ti;
-    int32_t chunks, chunk_elems, vec_ok;
+    uint64_t* arrivals;           // a word per sequence, kArrivalWords apart
+    int32_t chunks;
 };
 
 struct DraftBuildParams {
