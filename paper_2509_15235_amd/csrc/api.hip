@@ -592,7 +592,7 @@ int32_t vs_tree_accept_sample(const float* logits, int64_t ld_logits, int32_t V,
 
 size_t vs_draft_expand_workspace_bytes(int32_t B, int32_t F, int32_t V, int32_t K) {
     if (B < 1 || F < 1 || F > VS_MAX_TREE || K < 1 || K > kMaxDraftK || F * K > kMaxDraftCand || V < K) return 0;
-    const size_t n = (size_t)B * F * accept_chunks(V); // (what it was with 4096-float chunks; a quarter of it is used)
+    const size_t n = (size_t)B * F * accept_chunks(V); // (what it was with 4096-float chunks; half of it is used)
     return 2 * align_up(n * sizeof(float)) + 2 * align_up(n * K * sizeof(float)) + (size_t)B * kArrivalWords * sizeof(uint64_t);
 }
 

@@ -5,7 +5,7 @@
 // children as the next frontier; at the end the N best-scored candidates of all levels are
 // the tree. The draft model's forward pass is not part of this: its logits are inputs.
 //
-// Two kernels. (1) An expansion: every workgroup reduces a 16384-float chunk of a logits row to (maximum, sum of
+// Two kernels. (1) An expansion: every workgroup reduces an 8192-float chunk of a logits row to (maximum, sum of
 // exp, the chunk's K largest entries); the workgroup of a sequence that finishes last merges the chunks into each
 // row's top K and log-sum-exp, scores the F*K candidates and picks the next frontier. (That second part used to
 // be a kernel of its own: 7.8 us for one trip to memory and half a microsecond of work, three times per tree.)
@@ -14,6 +14,8 @@
 // Selection without bookkeeping: entries are taken in the strict total order (value descending, index
 // ascending). A bound that at least K entries reach is found bit by bit with ballots, the few entries at or
 // above it are compacted and ranked by counting; nothing has to be marked as taken.
+#include <type_traits>
+
 #include "vs_device.h"
 
 namespace vs {
@@ -22,7 +24,7 @@ namespace {
 
 constexpr int kVec = 4;          // 16-byte loads per thread and chunk
 constexpr int kSelThreads = 256;
-constexpr int kExpandThreads = 1024;
+constexpr int kExpandThreads = 512;
 constexpr int kExpandWaves = kExpandThreads / kWave;
 static_assert(kDraftChunk == kExpandThreads * kVec * 4, "a chunk is one set of loads");
 
@@ -52,58 +54,61 @@ __device__ __forceinline__ float key_value(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
+// An entry as one integer: larger = earlier in (value descending, index ascending). Signed zeros are equal.
+__device__ __forceinline__ uint64_t entry_key(float v, int32_t i) { return ((uint64_t)order_key(v + 0.f) << 32) | (uint32_t)~i; }
+__device__ __forceinline__ float entry_value(uint64_t k) { return key_value((uint32_t)(k >> 32)); }
+__device__ __forceinline__ int32_t entry_index(uint64_t k) { return (int32_t)~(uint32_t)k; }
+
 // The first K of a wave's entries in (value descending, index ascending); every lane passes NE
-// entries (index kNone = none). emit(rank, value, index) is called once per rank 0..K-1 by
+// entries v[e] with index idx(e) (kNone = none). emit(rank, value, index) is called once per rank 0..K-1 by
 // some lane; ranks past the number of entries get (-inf, kNone).
 // How: the K-th largest of the lanes' own maxima (found bit by bit with ballots) is a lower
 // bound of the K-th largest entry, so the entries at or above it are a small superset of the
 // answer; they are compacted into the wave's LDS list and ranked by counting. A plateau of
 // equal values or a nearly empty wave can overflow the list: then the entries are extracted
-// one by one instead. No workgroup barrier inside; cv / ci are private to the wave.
-template <int NE, typename Emit>
-__device__ __forceinline__ void wave_topk(const float (&v)[NE], const int32_t (&i)[NE], int K, float* cv,
-                                          int32_t* ci, Emit emit) {
+// one by one instead. No workgroup barrier inside; the list is private to the wave.
+template <int NE, typename Idx, typename Emit>
+__device__ __forceinline__ void wave_topk(const float (&v)[NE], Idx idx, int K, uint64_t* list, Emit emit) {
     const int lane = threadIdx.x & 63;
     uint32_t best = 0;
 #pragma unroll
     for (int e = 0; e < NE; ++e)
-        if (i[e] != kNone) best = max(best, order_key(v[e]));
+        if (idx(e) != kNone) best = max(best, order_key(v[e]));
+    // (the upper sixteen bits of the bound are enough: it only has to be one that K lanes reach and few entries do)
     uint32_t res = 0;
-    for (int bit = 31; bit >= 0; --bit) {
+#pragma unroll
+    for (int bit = 31; bit >= 16; --bit) {
         const uint32_t trial = res | (1u << bit);
         if (__popcll(__ballot(best >= trial)) >= K) res = trial;
     }
-    const float tau = res ? key_value(res) : -INFINITY; // res == 0: fewer than K lanes hold entries
+    // res below the key of -inf: fewer than K lanes hold entries, or nothing above -inf bounds them
+    const float tau = res > 0x007fffffu ? key_value(res) : -INFINITY;
     int n = 0;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
-        const bool pred = i[e] != kNone && v[e] >= tau;
+        const bool pred = v[e] >= tau && idx(e) != kNone;
         const uint64_t mask = __ballot(pred);
+        if (mask == 0) continue; // most of the time
         const int pos = n + __popcll(mask & ((1ull << lane) - 1ull));
-        if (pred && pos < kCandCap) {
-            cv[pos] = v[e];
-            ci[pos] = i[e];
-        }
+        if (pred && pos < kCandCap) list[pos] = entry_key(v[e], idx(e));
         n += __popcll(mask);
     }
     if (n <= kCandCap) {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the list is read by other lanes of this wave
         if (n <= kWave) { // one entry per lane, the others' by v_readlane
-            const float tv = lane < n ? cv[lane] : -INFINITY;
-            const int32_t ti = lane < n ? ci[lane] : kNone;
+            const uint64_t k = lane < n ? list[lane] : 0;
             int rank = 0;
             for (int o = 0; o < n; ++o) {
-                const float ov = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, tv), o));
-                rank += before(ov, __builtin_amdgcn_readlane(ti, o), tv, ti) ? 1 : 0;
+                const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)k, o), hi = __builtin_amdgcn_readlane((uint32_t)(k >> 32), o);
+                rank += (((uint64_t)hi << 32) | lo) > k ? 1 : 0;
             }
-            if (lane < n && rank < K) emit(rank, tv, ti);
+            if (lane < n && rank < K) emit(rank, entry_value(k), entry_index(k));
         } else {
             for (int t = lane; t < n; t += kWave) {
-                const float tv = cv[t];
-                const int32_t ti = ci[t];
+                const uint64_t k = list[t];
                 int rank = 0;
-                for (int o = 0; o < n; ++o) rank += before(cv[o], ci[o], tv, ti) ? 1 : 0;
-                if (rank < K) emit(rank, tv, ti);
+                for (int o = 0; o < n; ++o) rank += list[o] > k ? 1 : 0;
+                if (rank < K) emit(rank, entry_value(k), entry_index(k));
             }
         }
         for (int r = n + lane; r < K; r += kWave) emit(r, -INFINITY, kNone);
@@ -115,8 +120,8 @@ __device__ __forceinline__ void wave_topk(const float (&v)[NE], const int32_t (&
             Ent mine = {-INFINITY, kNone};
 #pragma unroll
             for (int e = 0; e < NE; ++e)
-                if (i[e] != kNone && before(last_v, last_i, v[e], i[e]) && before(v[e], i[e], mine.v, mine.i))
-                    mine = {v[e], i[e]};
+                if (idx(e) != kNone && before(last_v, last_i, v[e], idx(e)) && before(v[e], idx(e), mine.v, mine.i))
+                    mine = {v[e], idx(e)};
             const Ent w = wave_first(mine);
             if (lane == 0) emit(r, w.v, w.i);
             last_v = w.v;
@@ -125,16 +130,14 @@ __device__ __forceinline__ void wave_topk(const float (&v)[NE], const int32_t (&
     }
 }
 
-// grid = B * F * chunks, block = 1024.
+// grid = B * F * chunks, block = 512.
 __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const DraftExpandParams p) {
     __shared__ float s_m[kExpandWaves], s_s[kExpandWaves];
-    __shared__ float s_cv[kExpandWaves * kCandCap];
-    __shared__ int32_t s_ci[kExpandWaves * kCandCap];
+    __shared__ uint64_t s_list[kExpandWaves * kCandCap];
     __shared__ float s_wv[kExpandWaves * kMaxDraftK];
     __shared__ int32_t s_wi[kExpandWaves * kMaxDraftK];
     __shared__ float s_score[kMaxDraftCand];
     __shared__ int32_t s_token[kMaxDraftCand];
-    __shared__ uint8_t s_keep[kMaxDraftCand];
     __shared__ int32_t s_last;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int F = p.F, K = p.K;
@@ -150,20 +153,20 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         // every thread holds 16 entries and perhaps one of the up to three behind the last four
         const int nvec = (end - begin) >> 2;
         float ev[4 * kVec + 1];
-        int32_t ei[4 * kVec + 1];
 #pragma unroll
         for (int j = 0; j < kVec; ++j) {
             const int k = tid + j * kExpandThreads;
             const f32x4 x = (k < nvec) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                ev[4 * j + e] = x[e];
-                ei[4 * j + e] = k < nvec ? begin + 4 * k + e : kNone;
-            }
+            for (int e = 0; e < 4; ++e) ev[4 * j + e] = x[e];
         }
         const int tail = begin + 4 * nvec + tid;
         ev[4 * kVec] = tail < end ? lg[tail] : -INFINITY;
-        ei[4 * kVec] = tail < end ? tail : kNone;
+        auto index = [&](int e) { // of ev[e]
+            if (e == 4 * kVec) return tail < end ? tail : kNone;
+            const int k = tid + (e >> 2) * kExpandThreads;
+            return k < nvec ? begin + 4 * k + (e & 3) : kNone;
+        };
         if (tid == 0) arrival_open(p.arrivals + (int64_t)b * kArrivalWords);
 
         // ---- per wave: maximum, sum of exp, the K first entries; one barrier, then wave 0 merges the waves
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
             s_m[wave] = m;
             s_s[wave] = s;
         }
-        wave_topk(ev, ei, K, s_cv + wave * kCandCap, s_ci + wave * kCandCap, [&](int r, float v, int32_t i) {
+        wave_topk(ev, index, K, s_list + wave * kCandCap, [&](int r, float v, int32_t i) {
             s_wv[wave * kMaxDraftK + r] = v;
             s_wi[wave * kMaxDraftK + r] = i;
         });
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
             }
             float* out_v = p.part_tv + (row * p.chunks + chunk) * K;
             int32_t* out_i = p.part_ti + (row * p.chunks + chunk) * K;
-            wave_topk(mv, mi, K, s_cv, s_ci, [&](int rr, float v, int32_t i) {
+            wave_topk(mv, [&](int e) { return mi[e]; }, K, s_list, [&](int rr, float v, int32_t i) {
                 store_device(out_v + rr, v);
                 store_device(out_i + rr, i); // kNone when the chunk has fewer than rr+1 entries
             });
@@ -217,36 +220,50 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         if (s_last == 0) return;
     }
 
-    // ---- the sequence's last workgroup: one wave per frontier row (rows beyond sixteen take turns)
+    // ---- the sequence's last workgroup: one wave per frontier row (rows beyond eight take turns)
     const int C = F * K;
     const int keep = min(K, C);
-    // candidate tid's parent (the frontier row it extends): requested now, written out at the end
-    // (C <= kMaxDraftCand = the block size, so a thread owns at most one candidate)
-    const int32_t par_own = (tid < C && p.frontier_cand) ? p.frontier_cand[(int64_t)b * F + tid / K] : -1;
+    // candidates' parents (the frontier rows they extend): requested now, written out at the end
+    constexpr int CPT = kMaxDraftCand / kExpandThreads; // candidates per thread, at most
+    int32_t par_own[CPT];
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+        const int c = tid + i * kExpandThreads;
+        par_own[i] = (c < C && p.frontier_cand) ? p.frontier_cand[(int64_t)b * F + c / K] : -1;
+    }
 
     // ---- per row: log-sum-exp and the K first entries of the merged chunk lists
+    // (chunk statistics, score and the first 256 list entries are requested before anything is used; longer
+    // lists come in further batches, the K best so far among them)
+    const int n = p.chunks * K;
     for (int f = wave; f < F; f += kExpandWaves) {
         const int64_t row = (int64_t)b * F + f;
         const float* pm = p.part_m + row * p.chunks;
         const float* ps = p.part_s + row * p.chunks;
-        const float* tv = p.part_tv + row * p.chunks * K;
-        const int32_t* ti = p.part_ti + row * p.chunks * K;
-        const int n = p.chunks * K;
-        // everything the row needs is requested before anything is used: chunk statistics (the first
-        // 64 chunks; a longer row loops below), the chunk lists when they fit in registers, the score
-        constexpr int kRegEnt = 8;
-        const bool in_regs = n <= kWave * kRegEnt;
-        float m0 = (lane < p.chunks) ? load_device(pm + lane) : -INFINITY;
-        float s0 = (lane < p.chunks) ? load_device(ps + lane) : 0.f;
-        float rv[kRegEnt];
-        int32_t ri[kRegEnt];
+        const float* tv = p.part_tv + row * n;
+        const int32_t* ti = p.part_ti + row * n;
+        constexpr int NE = 4;
+        float v[NE + 1];
+        int32_t idx[NE + 1];
+        auto fetch = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < kRegEnt; ++q) {
-            const int e = lane + q * kWave;
-            rv[q] = (in_regs && e < n) ? load_device(tv + e) : -INFINITY;
-            ri[q] = (in_regs && e < n) ? load_device(ti + e) : kNone;
-        }
+            for (int q = 0; q < NE; ++q) {
+                const int e = e0 + lane + q * kWave;
+                v[q] = -INFINITY;
+                idx[q] = kNone;
+                if (e0 + q * kWave < n) { // uniform
+                    const float x = load_device(tv + min(e, n - 1));
+                    const int32_t i = load_device(ti + min(e, n - 1));
+                    v[q] = e < n ? x : -INFINITY;
+                    idx[q] = e < n ? i : kNone;
+                }
+            }
+        };
+        float m0 = load_device(pm + min(lane, p.chunks - 1)); // (no branch around a load)
+        const float s0 = load_device(ps + min(lane, p.chunks - 1));
+        fetch(0);
         const float cum = p.cum_in ? p.cum_in[row] : 0.f;
+        if (lane >= p.chunks) m0 = -INFINITY;
         float m = m0;
         for (int c = lane + kWave; c < p.chunks; c += kWave) m = fmaxf(m, load_device(pm + c));
         m = wave_max(m);
@@ -257,76 +274,93 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         }
         z = wave_sum(z);
         const float lse = m + __logf(z);
-        auto emit = [&](int r, float v, int32_t i) {
-            s_token[f * K + r] = i;
-            s_score[f * K + r] = cum + (v - lse);
-        };
-        if (in_regs) {
-            wave_topk(rv, ri, K, s_cv + wave * kCandCap, s_ci + wave * kCandCap, emit);
-        } else { // very long rows: the lists are re-read from the workspace for every extracted entry
-            float last_v = INFINITY;
-            int32_t last_i = -1;
-            for (int r = 0; r < K; ++r) {
-                Ent mine = {-INFINITY, kNone};
-                for (int q = lane; q < n; q += kWave) {
-                    const float v = load_device(tv + q);
-                    const int32_t i = load_device(ti + q);
-                    if (i != kNone && before(last_v, last_i, v, i) && before(v, i, mine.v, mine.i)) mine = {v, i};
-                }
-                const Ent w = wave_first(mine);
-                if (lane == 0) emit(r, w.v, w.i);
-                last_v = w.v;
-                last_i = w.i;
-            }
+        float* best_v = s_wv + wave * kMaxDraftK;
+        int32_t* best_i = s_wi + wave * kMaxDraftK;
+        for (int e0 = 0; e0 < n; e0 += NE * kWave) {
+            if (e0 > 0) fetch(e0);
+            const bool more = e0 > 0 && lane < K;
+            v[NE] = more ? best_v[lane] : -INFINITY;
+            idx[NE] = more ? best_i[lane] : kNone;
+            wave_topk(v, [&](int e) { return idx[e]; }, K, s_list + wave * kCandCap, [&](int r, float x, int32_t i) {
+                best_v[r] = x;
+                best_i[r] = i;
+            });
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by other lanes of this wave
+        }
+        if (lane < K) {
+            s_token[f * K + lane] = best_i[lane];
+            s_score[f * K + lane] = cum + (best_v[lane] - lse);
         }
     }
     __syncthreads();
 
-    // ---- next frontier: the `keep` first candidates in (score descending, index ascending), by counting
-    if (C <= kWave) {
-        // one wave, registers only: lane c holds candidate c, the others' scores come by v_readlane,
-        // the position among the kept ones is a population count of a ballot
-        if (wave != 0) return;
-        const float sc = (lane < C) ? s_score[lane] : -INFINITY;
-        int rank = 0;
-        for (int o = 0; o < C; ++o) {
-            const float so = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, sc), o));
-            rank += before(so, o, sc, lane) ? 1 : 0;
+    // ---- the candidates, and the next frontier: the `keep` first of them in (score descending, index ascending),
+    // listed in ascending index
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+        const int c = tid + i * kExpandThreads;
+        if (c < C) {
+            const int64_t g = (int64_t)b * p.cand_capacity + p.cand_base + c;
+            p.cand_token[g] = s_token[c];
+            p.cand_score[g] = s_score[c];
+            p.cand_parent[g] = par_own[i];
         }
-        const bool kept = lane < C && rank < keep;
-        const uint64_t kept_mask = __ballot(kept);
-        if (lane < C) {
-            const int64_t g = (int64_t)b * p.cand_capacity + p.cand_base + lane;
-            p.cand_token[g] = s_token[lane];
-            p.cand_score[g] = sc;
-            p.cand_parent[g] = par_own;
-            const int pos = __builtin_popcountll(kept_mask & ((1ull << lane) - 1ull));
-            if (kept && pos < keep) { // pos >= keep: only NaN scores can rank more than `keep` candidates first
-                p.next_frontier_cand[(int64_t)b * keep + pos] = p.cand_base + lane;
-                p.next_cum[(int64_t)b * keep + pos] = sc;
-            }
+    }
+    if (keep == C) { // one row, or one child per row: all of them
+        if (tid < C) {
+            p.next_frontier_cand[(int64_t)b * keep + tid] = p.cand_base + tid;
+            p.next_cum[(int64_t)b * keep + tid] = s_score[tid];
         }
         return;
     }
-    for (int c = tid; c < C; c += kExpandThreads) {
-        const float sc = s_score[c];
-        int rank = 0;
-        for (int o = 0; o < C; ++o) rank += before(s_score[o], o, sc, c) ? 1 : 0;
-        s_keep[c] = rank < keep ? 1 : 0;
-    }
-    __syncthreads();
-    for (int c = tid; c < C; c += kExpandThreads) {
-        const int64_t g = (int64_t)b * p.cand_capacity + p.cand_base + c;
-        p.cand_token[g] = s_token[c];
-        p.cand_score[g] = s_score[c];
-        p.cand_parent[g] = par_own;
-        if (s_keep[c]) {
-            int pos = 0;
-            for (int o = 0; o < c; ++o) pos += s_keep[o];
-            if (pos >= keep) continue; // only NaN scores can rank more than `keep` candidates first
-            p.next_frontier_cand[(int64_t)b * keep + pos] = p.cand_base + c;
-            p.next_cum[(int64_t)b * keep + pos] = s_score[c];
+    uint64_t* const list = s_list + wave * kCandCap;
+    if (C > kWave) { // every wave's share first
+        constexpr int NE = kMaxDraftCand / kExpandThreads;
+        float fv[NE];
+        int32_t fi[NE];
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int c = tid + q * kExpandThreads;
+            fv[q] = c < C ? s_score[c] : -INFINITY;
+            fi[q] = c < C ? c : kNone;
         }
+        wave_topk(fv, [&](int e) { return fi[e]; }, keep, list, [&](int r, float v, int32_t i) {
+            s_wv[wave * kMaxDraftK + r] = v;
+            s_wi[wave * kMaxDraftK + r] = i;
+        });
+        __syncthreads();
+    }
+    if (wave != 0) return;
+    {
+        constexpr int NE = kExpandWaves * kMaxDraftK / kWave;
+        float fv[NE];
+        int32_t fi[NE];
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int e = lane + q * kWave;
+            if (C > kWave) {
+                const bool has = (e & (kMaxDraftK - 1)) < keep;
+                fv[q] = has ? s_wv[e] : -INFINITY;
+                fi[q] = has ? s_wi[e] : kNone;
+            } else {
+                fv[q] = e < C ? s_score[e] : -INFINITY;
+                fi[q] = e < C ? e : kNone;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the lists have been read
+        wave_topk(fv, [&](int e) { return fi[e]; }, keep, list, [&](int r, float v, int32_t i) {
+            s_wv[r] = v;
+            s_wi[r] = i;
+        });
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    const int32_t c = lane < keep ? s_wi[lane] : kNone;
+    const float sc = lane < keep ? s_wv[lane] : 0.f;
+    int pos = 0;
+    for (int o = 0; o < keep; ++o) pos += __builtin_amdgcn_readlane(c, o) < c ? 1 : 0;
+    if (c != kNone) {
+        p.next_frontier_cand[(int64_t)b * keep + pos] = p.cand_base + c;
+        p.next_cum[(int64_t)b * keep + pos] = sc;
     }
 }
 
@@ -342,8 +376,7 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
     __shared__ int32_t s_before[kWords];  // picked candidates below word w
     __shared__ int32_t s_bad;
     __shared__ uint32_t s_top[kSelThreads];               // every thread's largest key
-    __shared__ __attribute__((aligned(16))) float s_lv[kList];
-    __shared__ __attribute__((aligned(16))) int32_t s_li[kList];
+    __shared__ __attribute__((aligned(16))) uint64_t s_list[kList];
     __shared__ int32_t s_n;
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -388,7 +421,8 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
 #pragma unroll
     for (int w = 0; w < kSelWaves; ++w) tops[w] = s_top[w * kWave + lane];
     uint32_t bound = 0;
-    for (int bit = 31; bit >= 0; --bit) {
+#pragma unroll
+    for (int bit = 31; bit >= 16; --bit) {
         const uint32_t trial = bound | (1u << bit);
         int n = 0;
 #pragma unroll
@@ -411,10 +445,7 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
         for (int r = 0; r < kRounds; ++r) {
             const uint64_t m = __ballot(in[r]);
             const int pos = base + __popcll(m & ((1ull << lane) - 1ull));
-            if (in[r] && pos < kList) {
-                s_lv[pos] = v[r];
-                s_li[pos] = r * kSelThreads + tid;
-            }
+            if (in[r] && pos < kList) s_list[pos] = entry_key(v[r], r * kSelThreads + tid);
             base += __popcll(m);
         }
     }
@@ -422,21 +453,17 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
     const int n = s_n;
     if (n <= kList) {
         // rank by counting among the list, picked = rank < take, one bit per candidate
-        if (tid < ((n + 3) & ~3) - n) { // (n is a multiple of four at kList)
-            s_lv[n + tid] = -INFINITY;
-            s_li[n + tid] = kNone;
-        }
+        if (tid < (n & 1)) s_list[n + tid] = 0; // comes before nothing (n is even at kList)
         __syncthreads();
         if (tid < n) {
-            const float sc = s_lv[tid];
-            const int c = s_li[tid];
+            const uint64_t k = s_list[tid];
+            const int c = entry_index(k);
+            typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
             int rank = 0;
 #pragma unroll 4
-            for (int o = 0; o < n; o += 4) {
-                const f32x4 so = *(const f32x4*)&s_lv[o];
-                const u32x4 io = *(const u32x4*)&s_li[o];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rank += before(so[e], (int32_t)io[e], sc, c) ? 1 : 0;
+            for (int o = 0; o < n; o += 2) {
+                const u64x2 ko = *(const u64x2*)&s_list[o];
+                rank += (ko[0] > k ? 1 : 0) + (ko[1] > k ? 1 : 0);
             }
             if (rank < take) atomicOr((unsigned long long*)&s_mask[c >> 6], 1ull << (c & 63));
         }

@@ -113,7 +113,7 @@ struct SampleParams {
     int32_t chunk_elems;   // 4096
 };
 
-constexpr int kDraftChunk = 16384;    // floats of a logits row per workgroup of an expansion: 1024 threads x 4 x 16 bytes
+constexpr int kDraftChunk = 8192;     // floats of a logits row per workgroup of an expansion: 512 threads x 4 x 16 bytes
 constexpr int kArrivalWords = 16;     // 64-bit words from one arrival counter to the next: a cache line
 constexpr int kMaxDraftK = 16;        // children per frontier node
 constexpr int kMaxDraftCand = 1024;   // F * K candidates of one expansion step
