@@ -60,7 +60,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     // [k0, k0 + klen) of that sequence (k0 lies inside the cache). `whole`: no other piece shares these
     // rows, they leave as final output; else as the partial result of slot `slot`.
     auto run_piece = [&](const int b, const int kvh, const int rg, const int k0, const int klen, const int slot,
-                         const bool whole) __attribute__((always_inline)) {
+                         bool whole) __attribute__((always_inline)) {
     const int32_t S = p.prefix_len[b]; // requested first, needed last: the first tiles and the queries are requested before it arrives
 
     // ---- tile copies. One load instruction of a wave fetches 1 KB of consecutive memory:
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     static_assert(RPW == 1 && NW <= 2 * NSLOT, "a row block's queries take a tile slot");
     // through the tile slot of this wave's number (nothing is in the rings yet)
     uint16_t* sq = wave < NSLOT ? sK[wave & (NSLOT - 1)] : sV[wave & (NSLOT - 1)];
-    {
+    if (wave_active) {
         int ql = lane;
         if (BAL) asm volatile("" : "+v"(ql)); // keeps the addresses (the same for every piece) from living in registers
 #pragma unroll
@@ -155,7 +155,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
 
     const int nk = S + p.tree_keys;
     if (k0 >= nk) return;
-    const bool merge = !BAL && p.gates != nullptr; // uniform over the launch
+    if (!BAL && p.gates && nk <= klen) whole = true; // a sequence of one split has nothing to merge
+    const bool merge = !BAL && p.gates && !whole;
     const MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
     if (merge && tid == 0) merge_open(gate);
     const int k1 = min(nk, k0 + klen);

@@ -203,8 +203,8 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
 
     const int nk = S + p.tree_keys;
     if (k0 >= nk) return;
-    const bool final_rows = p.num_splits == 1;
-    const bool merge = p.gates != nullptr; // uniform over the launch
+    const bool final_rows = p.num_splits == 1 || (p.gates && nk <= p.keys_per_split); // a sequence of one split has nothing to merge
+    const bool merge = p.gates && !final_rows;
     const MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
     if (merge && tid == 0) merge_open(gate);
     const int k1 = min(nk, k0 + p.keys_per_split);

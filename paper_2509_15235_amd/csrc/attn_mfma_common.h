@@ -214,6 +214,7 @@ __device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, uint32_t wait
 }
 // Half a piece (eight channels of the 32 rows of a row block, see store_partial: the 32 lanes of one half of the
 // accumulators): where it is read and written. The addresses are worked out before the wait, the rest after it.
+constexpr int kMergeGroup = 4; // items a wave merges at once, at most
 struct MergeItem {
     const float* ml;
     const uint16_t* po;
@@ -230,73 +231,94 @@ __device__ __forceinline__ MergeItem merge_item(const AttnParams& p, int b, int 
     it.out = r < p.rows ? (uint16_t*)p.out + row_offset(p, b, kvh, r, row_node(p, r)) + piece * 16 + 4 * hl + 8 * (lane >> 5) : nullptr;
     return it;
 }
-// log-sum-exp of the item over n splits, then the final rows' channels. One wave: lanes r and r + 32 share row r
-// and take every other split. BATCH pairs of splits are in flight together; there is no branch around a load
-// (past the last split the last one is read again, with weight 0).
-template <int BATCH>
-__device__ __forceinline__ void merge_run_by(const MergeItem& it, int n) {
-    const __amdgpu_buffer_rsrc_t ml = span_of(it.ml), po = span_of(it.po);
+// log-sum-exp of G items over n splits, then the final rows' channels. One wave: lanes r and r + 32 share row r
+// and take every other split. BATCH pairs of splits of every item are in flight together; there is no branch around
+// a load (past the last split the last one is read again, with weight 0).
+template <int BATCH, int G>
+__device__ __forceinline__ void merge_run_by(const MergeItem (&it)[kMergeGroup], int n) {
     const int row = threadIdx.x & 31, odd = (threadIdx.x >> 5) & 1;
-    float M = -INFINITY, den = 0.f, num[8];
+    float M[G], den[G], num[G][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) num[e] = 0.f;
+    for (int g = 0; g < G; ++g) {
+        M[g] = -INFINITY;
+        den[g] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) num[g][e] = 0.f;
+    }
     for (int s0 = 0; s0 < n; s0 += 2 * BATCH) {
-        u32x2 w[BATCH];
-        u32x4 o[BATCH];
+        u32x2 w[G][BATCH];
+        u32x4 o[G][BATCH];
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int s = min(s0 + 2 * u + odd, n - 1);
-            w[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(ml, s * (kRowBlock * 8) + row * 8, 0, kDeviceScope));
-            o[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(po, s * 1024 + row * 16, 0, kDeviceScope));
+        for (int g = 0; g < G; ++g) {
+            const __amdgpu_buffer_rsrc_t ml = span_of(it[g].ml), po = span_of(it[g].po);
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int s = min(s0 + 2 * u + odd, n - 1);
+                w[g][u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(ml, s * (kRowBlock * 8) + row * 8, 0, kDeviceScope));
+                o[g][u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(po, s * 1024 + row * 16, 0, kDeviceScope));
+            }
         }
-        float Mb = M;
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) Mb = fmaxf(Mb, __uint_as_float(w[u][0]));
-        Mb = half_max(Mb);
-        const float Ms = Mb == -INFINITY ? 0.f : Mb; // no visible key so far: all weights are 2^-inf = 0
-        if (s0 > 0) {
-            const float resc = __builtin_amdgcn_exp2f(M - Ms);
-            den *= resc;
+        for (int g = 0; g < G; ++g) {
+            float Mb = M[g];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) num[e] *= resc;
-        }
-        M = Mb;
+            for (int u = 0; u < BATCH; ++u) Mb = fmaxf(Mb, __uint_as_float(w[g][u][0]));
+            Mb = half_max(Mb);
+            const float Ms = Mb == -INFINITY ? 0.f : Mb; // no visible key so far: all weights are 2^-inf = 0
+            if (s0 > 0) {
+                const float resc = __builtin_amdgcn_exp2f(M[g] - Ms);
+                den[g] *= resc;
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const float f = __builtin_amdgcn_exp2f(__uint_as_float(w[u][0]) - Ms) * (s0 + 2 * u + odd < n ? __uint_as_float(w[u][1]) : 0.f);
-            den += f;
+                for (int e = 0; e < 8; ++e) num[g][e] *= resc;
+            }
+            M[g] = Mb;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                num[2 * e] += f * __uint_as_float(o[u][e] << 16);
-                num[2 * e + 1] += f * __uint_as_float(o[u][e] & 0xffff0000u);
+            for (int u = 0; u < BATCH; ++u) {
+                const float f = __builtin_amdgcn_exp2f(__uint_as_float(w[g][u][0]) - Ms) * (s0 + 2 * u + odd < n ? __uint_as_float(w[g][u][1]) : 0.f);
+                den[g] += f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    num[g][2 * e] += f * __uint_as_float(o[g][u][e] << 16);
+                    num[g][2 * e + 1] += f * __uint_as_float(o[g][u][e] & 0xffff0000u);
+                }
             }
         }
     }
-    den = half_sum(den);
-    float r[4]; // lower half: channels 0 .. 3 of both halves added up, upper half: channels 4 .. 7
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const u32x2 x = __builtin_amdgcn_permlane32_swap(__float_as_uint(num[e]), __float_as_uint(num[4 + e]), false, false);
-        r[e] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    for (int g = 0; g < G; ++g) {
+        const float sum = half_sum(den[g]);
+        float r[4]; // lower half: channels 0 .. 3 of both halves added up, upper half: channels 4 .. 7
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const u32x2 x = __builtin_amdgcn_permlane32_swap(__float_as_uint(num[g][e]), __float_as_uint(num[g][4 + e]), false, false);
+            r[e] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+        }
+        if (it[g].out) *(u32x2*)it[g].out = pack_partial(r[0], r[1], r[2], r[3], 1.f / sum);
     }
-    if (it.out) *(u32x2*)it.out = pack_partial(r[0], r[1], r[2], r[3], 1.f / den);
-}
-__device__ __forceinline__ void merge_run(const MergeItem& it, int n) {
-    if (n <= 4) merge_run_by<2>(it, n);
-    else if (n <= 8) merge_run_by<4>(it, n);
-    else merge_run_by<8>(it, n);
 }
 // The end of a split's workgroup: all waves, after their last partial store. Row blocks rb0 .. rb1 - 1 belong to
-// the row group; `s_word` is two words of LDS that nobody else uses any more.
+// the row group, n >= 2; `s_word` is two words of LDS that nobody else uses any more. What an item costs is the trip
+// to memory (0.7 us), so a wave that has several - few splits, many rows - takes up to four at once: 192 rows in two
+// splits 23.6 -> 19.2 us (23 sequences of up to 290 keys); one sequence of five row blocks and splits 12.3 -> 11.4.
 template <int D>
 __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGate& g, int b, int kvh, int rb0, int rb1, int split, int n,
                                              int waves, uint32_t* s_word) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int NP = D / 8; // half pieces per row block
-    const int items = (rb1 - rb0) * NP;
+    const int items = (rb1 - rb0) * NP, step = n * waves;
+    const int most = n <= 4 ? kMergeGroup : n <= 8 ? 2 : 1; // items at once
+    MergeItem it[kMergeGroup] = {};
+    auto gather = [&](int i) __attribute__((always_inline)) { // items i, i + step, ...; the last of them again past the end
+        it[0] = merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane);
+        if (most == 1 || i + step >= items) return;
+#pragma unroll
+        for (int k = 1; k < kMergeGroup; ++k) {
+            const int at = min(i + k * step, items - 1);
+            it[k] = merge_item<D>(p, b, kvh, rb0 + at / NP, at % NP, lane);
+        }
+    };
     int i = split + n * wave;
-    MergeItem it{};
-    if (i < items) it = merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane);
+    if (i < items) gather(i);
     __builtin_amdgcn_s_waitcnt(wait_vm(0)); // this wave's partial results are in memory
     __syncthreads();
     if (tid == 0) {
@@ -306,14 +328,22 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
     }
     __syncthreads();
     if (s_word[1] == 0) return;
-    while (i < items) {
-        merge_run(it, n);
-        i += n * waves;
-        if (i < items) it = merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane);
+    uint32_t shares = s_word[0]; // handed over by workgroups that left
+    for (;;) {
+        while (i < items) {
+            const bool one = i + step >= items;
+            if (n <= 2) one ? merge_run_by<1, 1>(it, n) : merge_run_by<1, kMergeGroup>(it, n);
+            else if (n <= 4) one ? merge_run_by<2, 1>(it, n) : merge_run_by<2, kMergeGroup>(it, n);
+            else if (n <= 8) one ? merge_run_by<4, 1>(it, n) : merge_run_by<4, 2>(it, n);
+            else merge_run_by<8, 1>(it, n);
+            i += most * step;
+            if (i < items) gather(i);
+        }
+        if (shares == 0) break;
+        i = __builtin_ctz(shares) + n * wave;
+        shares &= shares - 1;
+        if (i < items) gather(i);
     }
-    for (uint32_t shares = s_word[0]; shares; shares &= shares - 1) // handed over by workgroups that left
-        for (i = __builtin_ctz(shares) + n * wave; i < items; i += n * waves)
-            merge_run(merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane), n);
 }
 
 // ---- Balanced schedule: the key ranges of a whole ragged batch, cut into shares of equal cost.
