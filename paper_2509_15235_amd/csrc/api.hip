@@ -50,6 +50,7 @@ std::atomic<uint32_t> merge_wait{2000};
 
 struct Plan {
     int32_t impl, rpw, waves, row_groups, rows, rows_pad, num_splits, keys_per_split, total_wgs, schedule;
+    int32_t own_tiles;  // every wave has key tiles of its own (attention_mfma_rows.hip)
     int32_t bal_chunks; // balanced schedule: shares per (KV head, row group); num_splits = slots per KV head
     int32_t f32_rows; // fp32 storage: query rows per workgroup
     int32_t rounds; // loop schedule on the LDS-resident kernel's form: splits in rounds of 128 keys
@@ -205,7 +206,16 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     const int rnd_wgs = units0 * ((nrb + rnd_rb - 1) / rnd_rb);
     const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
     const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || (nrb <= 4 && (nrb > 2 || d->B > 1)));
+    // One row block: tiles of the wave's own (attention_mfma_rows.hip), for any number of units: splits of at least 192
+    // keys while CUs are free (28 / 4 heads, 4 nodes: 700 keys in one split 9.7 us, in four 8.8; 400 keys 8.2 / 9.1 in
+    // three); past one workgroup of eight waves per CU whole sequences, two workgroups of four waves (32 x 20
+    // nodes, 32 / 32 heads, 818 keys: pipelined 90, these 81 us). Two row blocks of 128 channels: the rounds' finer
+    // splits win while there are CUs for them (2 x 9 nodes, 1700 keys 9.8 / 12.6 us), from splits of 1024 keys on, and
+    // for one split of at most 320 keys, the waves' own tiles do (16 x 9 nodes, up to 8191 keys 47.8 / 43.2; 200 keys 11.1 / 8.9).
+    const bool own_ok = !knobs && (nrb == 1 || (nrb == 2 && d->d == 128 && units0 <= kNumCUs && !balanced_ok &&
+                                                ((many && (int64_t)units0 * tiles >= 16 * kNumCUs) || tiles <= 5)));
     pl.schedule = d->schedule != VS_SCHED_AUTO ? d->schedule
+                  : own_ok                     ? VS_SCHED_LOOP
                   : balanced_ok                ? VS_SCHED_BALANCED
                   : many && rounds_ok          ? VS_SCHED_LOOP
                   : many && pipe_ok            ? VS_SCHED_PIPELINED
@@ -236,6 +246,21 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
         pl.keys_per_split = tps * kIterKeys;
         pl.num_splits = (tiles + tps - 1) / tps;
         pl.total_wgs = units0 * pl.row_groups * pl.num_splits;
+        return pl;
+    }
+    if (pl.schedule == VS_SCHED_LOOP && own_ok) {
+        pl.own_tiles = 1;
+        pl.rpw = 1;
+        pl.row_groups = 1;
+        pl.waves = units0 > kNumCUs ? 4 : 8;
+        splits = tiles <= 8 ? 1 : tiles / 3;
+        if (splits > kNumCUs / units0) splits = kNumCUs / units0;
+        if (splits > kMergeMaxSplits) splits = kMergeMaxSplits;
+        if (splits < 1) splits = 1;
+        const int tps = (tiles + splits - 1) / splits;
+        pl.keys_per_split = tps * kIterKeys;
+        pl.num_splits = (tiles + tps - 1) / tps;
+        pl.total_wgs = units0 * pl.num_splits;
         return pl;
     }
     if (pl.schedule == VS_SCHED_LOOP && rounds_ok) {
@@ -319,7 +344,7 @@ size_t partial_rows(const vs_attn_desc* d, const Plan& pl) {
 // (merge_splits) 2 splits of 192 rows took 19.2 us against 18.0.
 bool merges_inside(const vs_attn_desc* d, const Plan& pl) {
     const int blocks = pl.rows_pad / kRowBlock, in_group = (blocks + pl.row_groups - 1) / pl.row_groups;
-    return (pl.schedule == VS_SCHED_RESIDENT || pl.schedule == VS_SCHED_PIPELINED || pl.rounds) && pl.num_splits > 1 &&
+    return (pl.schedule == VS_SCHED_RESIDENT || pl.schedule == VS_SCHED_PIPELINED || pl.rounds || pl.own_tiles) && pl.num_splits > 1 &&
            pl.num_splits <= kMergeMaxSplits && pl.total_wgs <= kNumCUs &&
            in_group * (d->d / 8) <= 4 * pl.num_splits * pl.waves &&
            pl.rows_pad <= (1 << 16); // offsets inside a row group's partial results are 32 bits wide
@@ -466,8 +491,9 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.res_rb ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
     p.total_wgs = pl.total_wgs;
     p.bal_chunks = pl.bal_chunks;
-    // a launch of more whole sequences than run at once hands out the longest first (a lane per sequence)
-    p.by_length = pl.schedule == VS_SCHED_PIPELINED && pl.num_splits == 1 && desc->B >= 2 && desc->B <= kBalMaxSeqs &&
+    // a launch of more whole sequences than run at once hands out the longest first (a lane per sequence) - but not where the sequences are so short that the wait for all lengths costs more (64 x 20 nodes, 32 / 32 heads,
+    // 30 .. 249 keys: 45 us in order, 56 longest first)
+    p.by_length = (pl.schedule == VS_SCHED_PIPELINED || (pl.own_tiles && desc->max_prefix_len >= 1024)) && pl.num_splits == 1 && desc->B >= 2 && desc->B <= kBalMaxSeqs &&
                   pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2);
     if (need > 0) {
         const size_t prow = partial_rows(desc, pl);
@@ -484,6 +510,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         e = desc->dtype == VS_F32 ? launch_attention_f32(p, s) : launch_attention_generic(p, s);
     } else {
         e = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) ? launch_attention_mfma_pipe(p, pl.rpw, pl.waves, s)
+            : pl.own_tiles ? launch_attention_mfma_rows(p, pl.waves, s)
             : pl.rounds ? launch_attention_mfma_rounds(p, pl.res_rb, s)
             : pl.schedule == VS_SCHED_RESIDENT ? launch_attention_mfma_resident(p, pl.res_rb, s)
                                                : launch_attention_mfma(p, pl.rpw, pl.waves, s);

@@ -693,15 +693,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
             const int rg = j % p.row_groups;
             const int k = (j / p.row_groups) * 8 + (blockIdx.x & 7); // units by rank of their sequence, dealt over the XCDs
             if (k >= p.B * p.Hkv) return;
-            const int rank = k / p.Hkv;
-            const int len = lane < p.B ? p.prefix_len[lane] : INT32_MIN; // out-of-range lengths sort like any other
-            int above = 0; // sequences that come before this lane's
-            for (int i = 0; i < p.B; ++i) {
-                const int li = __builtin_amdgcn_readlane(len, i);
-                above += (li > len || (li == len && i < lane)) ? 1 : 0;
-            }
-            const int b = __builtin_ctzll(__ballot(lane < p.B && above == rank));
-            run_piece(b, k % p.Hkv, rg, 0, p.keys_per_split, 0, true);
+            run_piece(sequence_by_rank(p, k / p.Hkv, lane), k % p.Hkv, rg, 0, p.keys_per_split, 0, true);
             return;
         }
         // workgroup id -> (sequence, KV head, row group, split), XCD-aware (see attention_mfma.hip)

@@ -63,6 +63,18 @@ __device__ __forceinline__ int64_t row_offset(const AttnParams& p, int b, int kv
     return (((int64_t)b * p.T + node) * p.Hq + kvh * p.group + (r - node * p.group)) * p.d;
 }
 
+// The sequence of rank `rank` when the longest come first (at most 64 sequences, a lane each; out-of-range lengths sort
+// like any other). The whole wave calls it.
+__device__ __forceinline__ int sequence_by_rank(const AttnParams& p, int rank, int lane) {
+    const int len = lane < p.B ? p.prefix_len[lane] : INT32_MIN;
+    int above = 0; // sequences that come before this lane's
+    for (int i = 0; i < p.B; ++i) {
+        const int li = __builtin_amdgcn_readlane(len, i);
+        above += (li > len || (li == len && i < lane)) ? 1 : 0;
+    }
+    return __builtin_ctzll(__ballot(lane < p.B && above == rank));
+}
+
 // ---- Queries through LDS. As MFMA operands neighbouring lanes hold different rows; read like that from
 // memory every four lanes touch four cache lines, and the eight loads of a 32-row block keep the CU's address
 // units busy for 0.2 us - with eight waves that is 1.7 us in which no key can be requested. So a row
@@ -305,7 +317,8 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
                                              int waves, uint32_t* s_word) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int NP = D / 8; // half pieces per row block
-    const int items = (rb1 - rb0) * NP, step = n * waves;
+    const int items = (rb1 - rb0) * NP;
+    int step = n * waves;
     const int most = n <= 4 ? kMergeGroup : n <= 8 ? 2 : 1; // items at once
     MergeItem it[kMergeGroup] = {};
     auto gather = [&](int i) __attribute__((always_inline)) { // items i, i + step, ...; the last of them again past the end
@@ -329,6 +342,12 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
     __syncthreads();
     if (s_word[1] == 0) return;
     uint32_t shares = s_word[0]; // handed over by workgroups that left
+    if (shares && shares == ((uint32_t)((1ull << n) - 1) & ~(1u << split))) { // by all of them: one share
+        shares = 0;
+        step = waves;
+        i = wave;
+        if (i < items) gather(i);
+    }
     for (;;) {
         while (i < items) {
             const bool one = i + step >= items;

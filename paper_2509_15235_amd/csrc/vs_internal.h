@@ -193,6 +193,7 @@ bool attention_pipe_supported(int rpw, int waves);
 hipError_t launch_attention_mfma_pipe(const AttnParams& p, int rpw, int waves, hipStream_t s);
 bool attention_resident_supported(int row_blocks);
 hipError_t launch_attention_mfma_resident(const AttnParams& p, int row_blocks, hipStream_t s);
+hipError_t launch_attention_mfma_rows(const AttnParams& p, int waves, hipStream_t s);
 hipError_t launch_attention_mfma_rounds(const AttnParams& p, int row_blocks, hipStream_t s);
 hipError_t launch_attention_combine(const AttnParams& p, int dtype, hipStream_t s);
 hipError_t launch_accept(const AcceptParams& p, hipStream_t s);
