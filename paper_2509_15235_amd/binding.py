@@ -1,4 +1,7 @@
-"""ctypes binding: same names and argument order as include/vispec_verify.h."""
+"""Binding of the C ABI: same names and argument order as include/vispec_verify.h.
+
+The calls of a decoding step go through a small CPython module (csrc/pycall.cpp), everything else
+through ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -143,6 +146,35 @@ def _ptr(x):
     return ctypes.cast(x, ctypes.c_void_p).value
 
 
+# vs_tree_mask_build(parent, B, T, mask, depth, status=None, stream=None) -> int and so on: parameters as in the header,
+# pointers as _ptr takes them, the trailing optional ones None / 0 by default
+_NATIVE = ("vs_tree_mask_build", "vs_tree_verify_attention", "vs_compress_attention", "vs_tree_accept", "vs_tree_accept_noalloc",
+           "vs_tree_accept_sample", "vs_draft_expand", "vs_draft_tree_build", "vs_tree_kv_commit")
+
+
+def _load_native():
+    loaded = lib()
+    _native.bind({name: ctypes.cast(getattr(loaded, name), ctypes.c_void_p).value for name in _NATIVE})
+
+
+def _missing(name):
+    def call(*args, **kwargs):
+        raise FileNotFoundError(f"{os.path.join(_HERE, '_native.so')} is missing: build it with `python -m paper_2509_15235_amd.build`")
+    call.__name__ = name
+    return call
+
+
+try:
+    from . import _native
+except ImportError:
+    if os.path.exists(os.path.join(_HERE, "_native.so")):
+        raise
+    globals().update({name: _missing(name) for name in _NATIVE})
+else:
+    _native.setup(_load_native, _ptr, ctypes.ArgumentError, AttnDesc, KVDesc)
+    globals().update({name: getattr(_native, name) for name in _NATIVE})
+
+
 def vs_version() -> int:
     return lib().vs_version()
 
@@ -160,10 +192,6 @@ def vs_tree_validate_host(parent, T: int) -> int:
     return lib().vs_tree_validate_host(_ptr(parent), T)
 
 
-def vs_tree_mask_build(parent, B, T, mask, depth, status=None, stream=None) -> int:
-    return lib().vs_tree_mask_build(_ptr(parent), B, T, _ptr(mask), _ptr(depth), _ptr(status), _ptr(stream))
-
-
 def vs_attention_plan(desc: AttnDesc):
     plan = AttnPlan()
     rc = lib().vs_attention_plan(ctypes.byref(desc), ctypes.byref(plan))
@@ -174,78 +202,20 @@ def vs_attention_workspace_bytes(desc: AttnDesc) -> int:
     return lib().vs_attention_workspace_bytes(ctypes.byref(desc))
 
 
-def vs_tree_verify_attention(desc: AttnDesc, q, k_cache, v_cache, prefix_len, tree_parent, tree_mask, out,
-                             status=None, workspace=None, workspace_bytes=0, stream=None) -> int:
-    return lib().vs_tree_verify_attention(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                          _ptr(prefix_len), _ptr(tree_parent), _ptr(tree_mask), _ptr(out),
-                                          _ptr(status), _ptr(workspace), workspace_bytes, _ptr(stream))
-
-
 def vs_compress_attention_workspace_bytes(desc: AttnDesc) -> int:
     return lib().vs_compress_attention_workspace_bytes(ctypes.byref(desc))
-
-
-def vs_compress_attention(desc: AttnDesc, q, k, v, kv_len, out, status=None, workspace=None, workspace_bytes=0,
-                          stream=None) -> int:
-    return lib().vs_compress_attention(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(kv_len), _ptr(out),
-                                       _ptr(status), _ptr(workspace), workspace_bytes, _ptr(stream))
 
 
 def vs_accept_workspace_bytes(B: int, T: int, V: int) -> int:
     return lib().vs_accept_workspace_bytes(B, T, V)
 
 
-def vs_tree_accept(logits, ld_logits, V, draft_tokens, parent, B, T, accepted_len, path, bonus_token,
-                   row_argmax=None, status=None, workspace=None, workspace_bytes=0, stream=None) -> int:
-    return lib().vs_tree_accept(_ptr(logits), ld_logits, V, _ptr(draft_tokens), _ptr(parent), B, T,
-                                _ptr(accepted_len), _ptr(path), _ptr(bonus_token), _ptr(row_argmax),
-                                _ptr(status), _ptr(workspace), workspace_bytes, _ptr(stream))
-
-
-def vs_tree_accept_noalloc(logits, ld_logits, V, draft_tokens, parent, B, T, accepted_len, path, bonus_token,
-                           row_argmax=None, status=None, stream=None) -> int:
-    return lib().vs_tree_accept_noalloc(_ptr(logits), ld_logits, V, _ptr(draft_tokens), _ptr(parent), B, T,
-                                        _ptr(accepted_len), _ptr(path), _ptr(bonus_token), _ptr(row_argmax),
-                                        _ptr(status), _ptr(stream))
-
-
 def vs_accept_sample_workspace_bytes(B: int, T: int, V: int) -> int:
     return lib().vs_accept_sample_workspace_bytes(B, T, V)
 
 
-def vs_tree_accept_sample(logits, ld_logits, V, temperature, draft_tokens, parent, u_accept, u_bonus, B, T,
-                          accepted_len, path, bonus_token, status=None, workspace=None, workspace_bytes=0,
-                          stream=None) -> int:
-    return lib().vs_tree_accept_sample(_ptr(logits), ld_logits, V, temperature, _ptr(draft_tokens), _ptr(parent),
-                                       _ptr(u_accept), _ptr(u_bonus), B, T, _ptr(accepted_len), _ptr(path),
-                                       _ptr(bonus_token), _ptr(status), _ptr(workspace), workspace_bytes,
-                                       _ptr(stream))
-
-
 def vs_draft_expand_workspace_bytes(B: int, F: int, V: int, K: int) -> int:
     return lib().vs_draft_expand_workspace_bytes(B, F, V, K)
-
-
-def vs_draft_expand(logits, ld_logits, V, cum_in, frontier_cand, B, F, K, cand_base, cand_capacity, cand_token,
-                    cand_score, cand_parent, next_frontier_cand, next_cum, workspace=None, workspace_bytes=0,
-                    stream=None) -> int:
-    return lib().vs_draft_expand(_ptr(logits), ld_logits, V, _ptr(cum_in), _ptr(frontier_cand), B, F, K, cand_base,
-                                 cand_capacity, _ptr(cand_token), _ptr(cand_score), _ptr(cand_parent),
-                                 _ptr(next_frontier_cand), _ptr(next_cum), _ptr(workspace), workspace_bytes,
-                                 _ptr(stream))
-
-
-def vs_draft_tree_build(cand_token, cand_score, cand_parent, B, M, cand_capacity, N, root_token, parent,
-                        draft_tokens, node_cand, num_nodes, status=None, stream=None) -> int:
-    return lib().vs_draft_tree_build(_ptr(cand_token), _ptr(cand_score), _ptr(cand_parent), B, M, cand_capacity, N,
-                                     _ptr(root_token), _ptr(parent), _ptr(draft_tokens), _ptr(node_cand),
-                                     _ptr(num_nodes), _ptr(status), _ptr(stream))
-
-
-def vs_tree_kv_commit(desc: KVDesc, k_cache, v_cache, prefix_len, path, accepted_len, new_prefix_len,
-                      status=None, stream=None) -> int:
-    return lib().vs_tree_kv_commit(ctypes.byref(desc), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_len), _ptr(path),
-                                   _ptr(accepted_len), _ptr(new_prefix_len), _ptr(status), _ptr(stream))
 
 
 def vs_peak_hbm_read(src, nbytes: int, sink, workgroups: int, stream=None) -> int:

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -61,6 +62,10 @@ def build_library(verbose: bool = False, extra=(), sanitize_host: bool = False) 
     if sanitize_host:
         cmd += ["-fsanitize=address", "-fsanitize=undefined", "-fno-gpu-sanitize", "-shared-libsan"]
     subprocess.check_call(cmd)
+    # the Python entry points (host code only; loads whichever build of the library binding.py names)
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(ROOT, "include"),
+                           os.path.join(CSRC, "pycall.cpp"), "-o", os.path.join(HERE, "_native.so")])
     return out
 
 
