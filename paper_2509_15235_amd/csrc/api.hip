@@ -204,6 +204,10 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // with two row blocks stays with the pipelined kernel (20.1 / 18.9).
     const int rnd_rb = nrb >= 3 ? 4 : 2;
     const int rnd_wgs = units0 * ((nrb + rnd_rb - 1) / rnd_rb);
+    // With few KV heads the 64 shares do not fill the places, and the kernels that split the keys among the waves take
+    // over: us per call, shares / they: 64 x 30 nodes, 8 / 2 heads, 1000 .. 7999 keys 188 / 98; 64 x 14, 8 / 1 heads
+    // 176 / 56; 64 x 16, 28 / 4 heads, 8000 keys 278 / 221, 1024 .. 8191 keys 197 / 175; 20 x 13, 4096 .. 8191 keys 89 / 71.
+    const bool bal_capped = bal_w_auto * d->Hkv * bal_rg < bal_places * 7 / 8;
     const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
     const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || (nrb <= 4 && (nrb > 2 || d->B > 1)));
     // One row block: tiles of the wave's own (attention_mfma_rows.hip), for any number of units: splits of at least 192
@@ -212,11 +216,11 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // nodes, 32 / 32 heads, 818 keys: pipelined 90, these 81 us). Two row blocks of 128 channels: the rounds' finer
     // splits win while there are CUs for them (2 x 9 nodes, 1700 keys 9.8 / 12.6 us), from splits of 1024 keys on, and
     // for one split of at most 320 keys, the waves' own tiles do (16 x 9 nodes, up to 8191 keys 47.8 / 43.2; 200 keys 11.1 / 8.9).
-    const bool own_ok = !knobs && (nrb == 1 || (nrb == 2 && d->d == 128 && units0 <= kNumCUs && !balanced_ok &&
+    const bool own_ok = !knobs && (nrb == 1 || (nrb == 2 && d->d == 128 && units0 <= kNumCUs && (!balanced_ok || bal_capped) &&
                                                 ((many && (int64_t)units0 * tiles >= 16 * kNumCUs) || tiles <= 5)));
     pl.schedule = d->schedule != VS_SCHED_AUTO ? d->schedule
                   : own_ok                     ? VS_SCHED_LOOP
-                  : balanced_ok                ? VS_SCHED_BALANCED
+                  : balanced_ok && !(bal_capped && rounds_ok) ? VS_SCHED_BALANCED
                   : many && rounds_ok          ? VS_SCHED_LOOP
                   : many && pipe_ok            ? VS_SCHED_PIPELINED
                   : resident_ok                ? VS_SCHED_RESIDENT
@@ -272,6 +276,10 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
         splits = kNumCUs / (units0 * pl.row_groups);
         const int most = (tiles + 1) / 2;
         if (splits > most) splits = most;
+        // long sequences that would leave CUs idle: five short rounds, handed out as CUs fall free (28 / 4 heads, 40 x 18
+        // nodes: 1024 .. 8191 keys one split 162, three 132, five 132, eight 139, balanced shares 130 us; all of 4000
+        // keys 92 / 88 / 107 / 105 / 122; 33 x 18 nodes 1024 .. 8191 keys: three 128, five 107, shares 115)
+        if (splits == 1 && balanced_ok && rnd_wgs < 240) splits = 5;
         if (splits > kMergeMaxSplits) splits = kMergeMaxSplits;
         if (splits < 1) splits = 1;
         const int tps = (tiles + splits - 1) / splits;
