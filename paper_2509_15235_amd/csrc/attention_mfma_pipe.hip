@@ -168,32 +168,38 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     const char* vfast = (const char*)(vbase + head_base + (int64_t)k0 * stride_tok);
     // LFAST: a full tile, so the address is a wave-uniform base plus a per-lane constant and nothing
     // needs clamping.
-    // Paged caches: the block ids of the tiles to come sit one per lane in two registers (a window of
-    // 128 consecutive table entries, fetched with two coalesced loads and moved along as the tiles
-    // advance), so a tile copy gets its block id with v_readlane instead of a scalar load per copy -
-    // whose result the copy would have to wait for, together with every LDS read in flight (scalar
-    // loads and LDS share one wait counter).
+    // Paged caches: where the blocks of the tiles to come lie sits one per lane - a window of 64 consecutive table
+    // entries, fetched with one coalesced load and moved along by 32 as the tiles advance - so a tile copy gets
+    // it with v_readlane instead of a scalar load per copy (whose result the copy would have to wait for, together with
+    // every LDS read in flight: scalar loads and LDS share one wait counter). The clamp and the product are done once
+    // per window, by all lanes at once, and the loaded register is only touched where the window moves: with ids in
+    // a window of 128 read twice per lookup 28 x 60 nodes of 28 / 4 heads over 1696 keys took 62.1 us, so 59.3 (54.8 unpaged).
     const int32_t* bt_row = PAGED ? p.block_table + (int64_t)b * p.max_blocks : nullptr;
-    int bt_base = k0 >> p.block_shift; // logical block of lane 0 of the first window register
-    int32_t bt_win0 = 0, bt_win1 = 0;
+    int bt_base = k0 >> p.block_shift; // logical block of lane 0
+    uint32_t bt_lo = 0, bt_hi = 0;     // element offset of the lane's block
+    int32_t bt_next = 0;               // block id of lane 0 + 32 + lane, on its way
     auto bt_fetch = [&](int first) __attribute__((always_inline)) { return bt_row[min(first + lane, p.max_blocks - 1)]; };
+    auto bt_set = [&](int32_t blk) __attribute__((always_inline)) {
+        if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
+        const int64_t off = (int64_t)blk * p.stride_block;
+        bt_lo = (uint32_t)off;
+        bt_hi = (uint32_t)(off >> 32);
+    };
     if (PAGED) {
-        bt_win0 = bt_fetch(bt_base);
-        bt_win1 = bt_fetch(bt_base + 64);
+        bt_set(bt_fetch(bt_base));
+        bt_next = bt_fetch(bt_base + 32);
     }
-    // moves the window so that it starts at or before logical block `lb_min` (called once per iteration)
+    // moves the window so that it starts less than 32 blocks before logical block `lb_min` (called once per iteration)
     auto bt_advance = [&](int lb_min) __attribute__((always_inline)) {
-        if (PAGED && lb_min >= bt_base + 64) { // uniform
-            bt_base += 64;
-            bt_win0 = bt_win1;
-            bt_win1 = bt_fetch(bt_base + 64);
+        if (PAGED && lb_min >= bt_base + 32) { // uniform
+            bt_base += 32;
+            bt_set(bt_next);
+            bt_next = bt_fetch(bt_base + 32);
         }
     };
     auto bt_lookup = [&](int lb) __attribute__((always_inline)) {
-        const int rel = lb - bt_base; // 0 .. 127 by construction
-        int32_t blk = rel < 64 ? __builtin_amdgcn_readlane(bt_win0, rel & 63) : __builtin_amdgcn_readlane(bt_win1, rel & 63);
-        if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-        return blk;
+        const int rel = lb - bt_base; // 0 .. 63 by construction
+        return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bt_hi, rel) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)bt_lo, rel));
     };
     auto load_tile = [&](auto lfast_tag, auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
         constexpr bool LFAST = decltype(lfast_tag)::value;
@@ -207,7 +213,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
                 const int i = wave * BPW + j; // uniform per wave
                 if (NW * BPW == BPS || i < BPS) {
                     const int r0 = k0 + t * kTileKeys + RPI * i;
-                    const int64_t sbase = head_base + (int64_t)bt_lookup(r0 >> p.block_shift) * p.stride_block +
+                    const int64_t sbase = head_base + bt_lookup(r0 >> p.block_shift) +
                                           (int64_t)((r0 & (p.block_size - 1)) * stride_tok);
                     r[j] = *(const u32x4*)((const char*)((ISV ? vbase : kbase) + sbase) + lane_off);
                 }
@@ -232,7 +238,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
                     int tok = min(r0 + lrow, k1 - 1);
                     int64_t base = head_base;
                     if (PAGED) {
-                        base += (int64_t)bt_lookup(min(r0, k1 - 1) >> p.block_shift) * p.stride_block;
+                        base += bt_lookup(min(r0, k1 - 1) >> p.block_shift);
                         tok &= p.block_size - 1;
                     }
                     const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
@@ -561,7 +567,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
 
     // Iteration g handles tiles ta = 2g and tb = 2g + 1. CFAST iterations have every
     // neighbour tile present and only prefix keys; the general form checks and masks.
-    auto iteration = [&](auto cfast_tag, auto lfast_tag, auto set_tag, int ta) __attribute__((always_inline)) {
+    auto iteration = [&](auto active, auto cfast_tag, auto lfast_tag, auto set_tag, int ta) __attribute__((always_inline)) {
         constexpr bool FAST = decltype(cfast_tag)::value;
         // set_tag: the register set of the copy group that this iteration stashes
         using masked_t = std::integral_constant<bool, !FAST>;
@@ -570,7 +576,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         // this iteration requests group g + 2 = tiles 2g + 5 .. 2g + 8
         bt_advance(min(k0 + (2 * g + 5) * kTileKeys, k1 - 1) >> p.block_shift);
         // first tile: S(tb), O(ta - 1) | P(ta)
-        if (wave_active) {
+        if (active) {
             float alpha[RPW];
             if constexpr (FAST) {
                 // the very first step applies all-zero probabilities to V(0)
@@ -590,12 +596,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         // waves without rows have no such step and copy here)
         // (with four waves a tile is two blocks per wave and the interleaved form runs out of registers)
         constexpr bool SPREAD = FAST && BPW == 1;
-        if (!SPREAD || !wave_active) {
+        if (!SPREAD || !active) {
             stash_group(set_tag, g);
             load_group(lfast_tag, set_tag, g + 2);
         }
         // second tile: S(ta + 2), O(ta) | P(tb)
-        if (wave_active) {
+        if (active) {
             float alpha[RPW];
             if constexpr (FAST) {
                 using copy_t = std::conditional_t<SPREAD, decltype(set_tag), std::integral_constant<int, -1>>;
@@ -623,19 +629,29 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     // forms only ever get more general as ta grows (prefix tiles first, copies near the end
     // of the range last), so three loops in a row cover every case. Iteration ta loads
     // group ta/2 + 2 = tiles up to ta + 8.
-    int ta = 0;
-    for (; ta + 2 < fast_end && ta + 10 < n_full; ta += 4) {
-        iteration(T{}, T{}, S0{}, ta);
-        iteration(T{}, T{}, S1{}, ta + 2);
-    }
-    for (; ta + 2 < fast_end; ta += 4) {
-        iteration(T{}, F{}, S0{}, ta);
-        iteration(T{}, F{}, S1{}, ta + 2);
-    }
-    for (; ta < n; ta += 4) {
-        iteration(F{}, F{}, S0{}, ta);
-        if (ta + 2 < n) iteration(F{}, F{}, S1{}, ta + 2);
-    }
+    auto all_tiles = [&](auto active) __attribute__((always_inline)) {
+        int ta = 0;
+        for (; ta + 2 < fast_end && ta + 10 < n_full; ta += 4) {
+            iteration(active, T{}, T{}, S0{}, ta);
+            iteration(active, T{}, T{}, S1{}, ta + 2);
+        }
+        for (; ta + 2 < fast_end; ta += 4) {
+            iteration(active, T{}, F{}, S0{}, ta);
+            iteration(active, T{}, F{}, S1{}, ta + 2);
+        }
+        for (; ta < n; ta += 4) {
+            iteration(active, F{}, F{}, S0{}, ta);
+            if (ta + 2 < n) iteration(active, F{}, F{}, S1{}, ta + 2);
+        }
+    };
+    // Waves without rows only copy, in loops of their own: where both kinds pass through the same code, the compiler
+    // cannot tell which copies are still on their way and waits for all of them in every iteration, the ones just
+    // requested included (12 x 60 nodes, 16 / 16 heads of 64 channels, up to 8000 keys 68 -> 57 us; eight waves
+    // of 128 channels 1 %). Four waves of 128 channels run out of registers that way (32 x 60 nodes of 32 / 32
+    // heads, 3136 keys 304 -> 377 us) and are bound by memory, not by its latency.
+    if constexpr (D == 128 && NW == 4) all_tiles(wave_active);
+    else if (wave_active) all_tiles(T{});
+    else all_tiles(F{});
     if (wave_active) {
     if ((n & 1) == 0) pv(sV[(n - 1) & 3], pb);
 
