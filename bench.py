@@ -150,7 +150,7 @@ def other_config_leg(vs, gen, torch, dev, stream, gtorch, name, seed, check, num
              vs.VS_SCHED_RESIDENT: "attn_mfma_resident_kernel"}.get(plan.schedule, "attn_mfma_kernel")
     blk.update({"traffic": None, "workload": cfg.name, "launch": launch, "us_per_launch": round(ms * 1e3, 2),
                 "tflops": round(tf, 2), "hbm_gbs": round(gbs, 1), "workgroups": plan.workgroups, "num_splits": plan.num_splits,
-                "kernel": sched + (" + attn_combine_kernel" if plan.combine else ""),
+                "kernel": sched + (" + merge of the splits" if plan.combine else ""),
                 "layers_per_launch": layers_per_call, "buffer_sets": nsets, "data": "device-generated N(0,1)"})
     del sets
     torch.cuda.empty_cache()
@@ -537,7 +537,7 @@ def main():
     def kernel_name(pl):
         k = {vs.VS_SCHED_PIPELINED: "attn_mfma_pipe_kernel", vs.VS_SCHED_RESIDENT: "attn_mfma_resident_kernel"}.get(
             pl.schedule, "attn_mfma_kernel")
-        return k + (" + attn_combine_kernel" if pl.combine else "")
+        return k + (" + merge of the splits" if pl.combine else "")
 
     roofline.update({"kernel": kernel_name(planL),
                      "launch": f"B={L} proxy: the step's {L} layers folded into one launch as independent batch entries "
@@ -568,7 +568,7 @@ def main():
     draft_bytes = draft_rows * V * 4
     draft = {"bound": "latency", "us_per_tree": round(ms_draft * 1e3, 2), "bytes": draft_bytes,
              "gbs": round(draft_bytes / (ms_draft * 1e-3) / 1e9, 1),
-             "note": f"{DD} x vs_draft_expand (K={DK}) + vs_draft_tree_build (N={DN}) = 7 dependent kernels over "
+             "note": f"{DD} x vs_draft_expand (K={DK}) + vs_draft_tree_build (N={DN}) = {DD + 1} dependent kernels over "
                      f"{draft_rows} logits rows; the draft model between the expansions is not included"}
 
     compress = {"bound": "latency", "us_per_launch": round(ms_compress * 1e3, 2), "queries": T, "image_embeddings": n_img,

@@ -175,7 +175,7 @@ typedef struct vs_attn_plan {
     int32_t waves_per_group;
     int32_t rows_per_wave;   /* 32-row blocks per wave (MFMA path) */
     int32_t workgroups;      /* main kernel grid size */
-    int32_t combine;         /* 1 if a split-combine kernel follows */
+    int32_t combine;         /* 1 if partial results of key splits are merged (by the kernel itself or one behind it) */
     int32_t schedule;        /* VS_SCHED_LOOP, _PIPELINED, _RESIDENT or _BALANCED (MFMA path), else 0 */
 } vs_attn_plan;
 
