@@ -160,9 +160,14 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // workgroups than CUs) it loses to the loop, and for 5000+ keys its 192-key limit forces too
     // many partial results.
     const int res_rg = (nrb + 3) / 4;
-    const int res_tps = (int64_t)units0 * res_rg * ((tiles + 1) / 2) <= kNumCUs ? 2 : 3; // 64-key tiles per split
+    // Short sequences: one split where it is at most the kernel's 192 keys, then splits of 64 keys where those find a CU
+    // each (with few splits the merge's items queue up in few waves: 1 x 60 nodes, 28 / 4 heads, 400 keys in splits of 128 12.3 us, of
+    // 64 9.3; 650 keys 11.0 / 9.8; 2 x 17 nodes, 1400 keys 11.5 / 10.7), and then for any number of units (4 x 14 nodes,
+    // 120 keys: rounds 11.7, one split 9.7; 12 x 62 nodes, 76 keys: pipelined 14.8, one split 11.0).
+    const int res_short = tiles <= 3 ? 1 : (tiles <= 32 && (int64_t)units0 * res_rg * tiles <= kNumCUs ? tiles : 0);
+    const int res_tps = res_short ? tiles / res_short : (int64_t)units0 * res_rg * ((tiles + 1) / 2) <= kNumCUs ? 2 : 3; // 64-key tiles per split
     const int res_splits = splits > 0 ? splits : (tiles + res_tps - 1) / res_tps;
-    const bool resident_ok = !many && nrb >= 3 && tiles <= 32 && (rpw == 0 || rpw == 1) && (waves == 0 || waves == 8) &&
+    const bool resident_ok = (!many || (res_short && splits <= 0)) && nrb >= 2 && tiles <= 32 && (rpw == 0 || rpw == 1) && (waves == 0 || waves == 8) &&
                              (splits <= 0 || (tiles + splits - 1) / splits <= kResidentMaxKeys / kIterKeys) &&
                              (int64_t)units0 * res_rg * res_splits <= kNumCUs;
     // The pipelined kernel takes over from twelve units on (three C3 sequences, or one MHA
@@ -201,7 +206,7 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     //   8 x 31 nodes, 32 / 8 heads of 64, up to 2047 keys 18.1 / 16.6; 4 x 60 nodes, 32 / 32 heads, 3400 keys 51.2 / 47.6
     // and straight loop / rounds 2 x 60 nodes, 28 / 4 heads, 1696 keys 17.6 / 14.2, one of 6684 keys 25.2 / 18.4.
     // More workgroups than CUs: 16 x 60 nodes, 32 / 32 heads, 1000 keys 61.4 / 64.1. One sequence of many KV heads
-    // with two row blocks stays with the pipelined kernel (20.1 / 18.9).
+    // with two row blocks of 128 channels: 700 keys 15.8 / 10.6, 1300 keys 15.9 / 12.5, 3136 keys 18.9 / 20.1.
     const int rnd_rb = nrb >= 3 ? 4 : 2;
     const int rnd_wgs = units0 * ((nrb + rnd_rb - 1) / rnd_rb);
     // With few KV heads the 64 shares do not fill the places, and the kernels that split the keys among the waves take
@@ -209,7 +214,7 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // 176 / 56; 64 x 16, 28 / 4 heads, 8000 keys 278 / 221, 1024 .. 8191 keys 197 / 175; 20 x 13, 4096 .. 8191 keys 89 / 71.
     const bool bal_capped = bal_w_auto * d->Hkv * bal_rg < bal_places * 7 / 8;
     const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
-    const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || (nrb <= 4 && (nrb > 2 || d->B > 1)));
+    const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || (nrb <= 4 && (nrb > 2 || d->B > 1 || d->d == 64 || tiles <= 24)));
     // One row block: tiles of the wave's own (attention_mfma_rows.hip), for any number of units: splits of at least 192
     // keys while CUs are free (28 / 4 heads, 4 nodes: 700 keys in one split 9.7 us, in four 8.8; 400 keys 8.2 / 9.1 in
     // three); past one workgroup of eight waves per CU whole sequences, two workgroups of four waves (32 x 20
@@ -221,6 +226,7 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     pl.schedule = d->schedule != VS_SCHED_AUTO ? d->schedule
                   : own_ok                     ? VS_SCHED_LOOP
                   : balanced_ok && !(bal_capped && rounds_ok) ? VS_SCHED_BALANCED
+                  : many && resident_ok        ? VS_SCHED_RESIDENT
                   : many && rounds_ok          ? VS_SCHED_LOOP
                   : many && pipe_ok            ? VS_SCHED_PIPELINED
                   : resident_ok                ? VS_SCHED_RESIDENT

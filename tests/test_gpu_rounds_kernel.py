@@ -16,7 +16,7 @@ TIGHT_SHORT = (1.2e-2, 6e-3)
 @pytest.mark.parametrize("B,T,Hq,Hkv,d,paged,lens", [
     (2, 60, 28, 4, 128, False, [1696, 1500]),                    # four row groups, two rounds per split
     (2, 60, 28, 4, 128, True, [1600, 1]),                        # most splits without a key
-    (4, 33, 12, 4, 64, False, [700, 127, 128, 129]),             # four row blocks, 64 channels
+    (4, 33, 12, 4, 64, False, [1100, 127, 128, 129]),             # four row blocks, 64 channels
     (4, 16, 28, 4, 128, True, [1296, 1000, 3, 511]),
     (2, 50, 8, 8, 128, False, [2000, 1234]),                     # two row blocks
     (3, 33, 6, 6, 64, True, [900, 77, 640]),
@@ -33,6 +33,33 @@ def test_rounds(oracle_mod, B, T, Hq, Hkv, d, paged, lens):
     da = gu.DeviceAttn(inp)
     assert da.plan().schedule == vs.VS_SCHED_LOOP and da.plan().waves_per_group == 8
     da.ws.random_(0, 256)                                        # the merge's words start as anything
+    got = da.run()
+    assert (da.status.cpu().numpy() == 0).all()
+    ref = oracle_mod.tree_attention(inp, threads=8)
+    for b in range(B):
+        gu.check_close(got[b], ref[b], *(TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT), what=f"sequence {b} of {lens[b]}")
+    for _ in range(3):
+        np.testing.assert_array_equal(got, da.run())
+
+
+@pytest.mark.parametrize("B,T,Hq,Hkv,d,paged,lens", [
+    (12, 62, 28, 4, 128, False, [76, 1, 130, 40, 64, 100, 2, 99, 63, 65, 128, 127]),  # one split, many units
+    (4, 14, 28, 4, 128, True, [120, 0, 178, 33]),
+    (8, 10, 32, 8, 64, False, [120, 1, 60, 182, 64, 65, 100, 3]),                      # two row blocks
+    (1, 60, 28, 4, 128, True, [400]),                                                  # splits of 64 keys
+    (2, 9, 28, 4, 128, False, [1400, 70]),
+    (1, 19, 8, 1, 64, True, [2029]),                                                   # 32 of them
+])
+def test_short_sequences(oracle_mod, B, T, Hq, Hkv, d, paged, lens):
+    """The resident kernel with one split, or splits of 64 keys."""
+    import gpu_util as gu
+    cfg = gen.Config("short", B, Hq, Hkv, d, T, min(6, T - 1), 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2), paged=paged)
+    inp = gen.attention_inputs(cfg, 800 + T, prefix_len=np.array(lens, dtype=np.int32))
+    da = gu.DeviceAttn(inp)
+    pl = da.plan()
+    tiles = (max(lens) + T + 63) // 64
+    assert pl.schedule == vs.VS_SCHED_RESIDENT and pl.num_splits == (1 if tiles <= 3 else tiles)
+    da.ws.random_(0, 256)
     got = da.run()
     assert (da.status.cpu().numpy() == 0).all()
     ref = oracle_mod.tree_attention(inp, threads=8)
