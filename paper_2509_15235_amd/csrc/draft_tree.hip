@@ -45,7 +45,7 @@ __device__ __forceinline__ Ent wave_first(Ent e) {
 constexpr int32_t kNone = INT32_MAX; // index of "no entry": loses every comparison at value -inf
 constexpr int kCandCap = 128;        // entries of a wave's candidate list in LDS
 
-// Larger float -> larger key (no NaN); every real key is > 0, which stands for "no entry".
+// Larger float -> larger key (no NaN), -0 below +0; every real key is > 0, which stands for "no entry".
 __device__ __forceinline__ uint32_t order_key(float v) {
     const uint32_t u = __float_as_uint(v);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
@@ -54,8 +54,10 @@ __device__ __forceinline__ float key_value(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// An entry as one integer: larger = earlier in (value descending, index ascending). Signed zeros are equal.
-__device__ __forceinline__ uint64_t entry_key(float v, int32_t i) { return ((uint64_t)order_key(v + 0.f) << 32) | (uint32_t)~i; }
+// The same with signed zeros equal (-0 + 0 = +0), as `before` has them: for keys that are compared with each other.
+__device__ __forceinline__ uint32_t rank_key(float v) { return order_key(v + 0.f); }
+// An entry as one integer: larger = earlier in (value descending, index ascending).
+__device__ __forceinline__ uint64_t entry_key(float v, int32_t i) { return ((uint64_t)rank_key(v) << 32) | (uint32_t)~i; }
 __device__ __forceinline__ float entry_value(uint64_t k) { return key_value((uint32_t)(k >> 32)); }
 __device__ __forceinline__ int32_t entry_index(uint64_t k) { return (int32_t)~(uint32_t)k; }
 
@@ -407,7 +409,7 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
             s_score[c] = v[r];
             s_parent[c] = pc_own[r];
             bad_own |= pc_own[r] < -1 || pc_own[r] >= c;
-            top = max(top, order_key(v[r]));
+            top = max(top, rank_key(v[r]));
         }
     }
     s_top[tid] = top;
@@ -436,7 +438,7 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
             const int c = r * kSelThreads + tid;
-            in[r] = c < M && order_key(v[r]) >= bound;
+            in[r] = c < M && rank_key(v[r]) >= bound;
             mine += __popcll(__ballot(in[r]));
         }
         if (lane == 0) base = atomicAdd(&s_n, mine); // the order of the list does not matter

@@ -66,3 +66,23 @@ def test_selection_bounds(gu, oracle_mod, M, N, kind):
     dd.score.copy_(gu.dev(sc))
     dd.par.copy_(gu.dev(np.full((1, M), -1, np.int32)))
     _check_build(gu, oracle_mod, dd, N)
+
+
+@pytest.mark.parametrize("scores,N", [
+    ([-0.0, 0.0, 0.0, -1.0], 2),                                 # the first two of three equal scores
+    ([-0.0] * 70 + [0.0] * 70, 63),
+    ([0.0, -0.0] * 1024, 63),                                    # a plateau of more entries than are ranked as a list
+    ([-1.0] * 300 + [0.0, -0.0, -0.0, 0.0, -0.0] * 9, 40),
+])
+def test_signed_zero_scores(gu, oracle_mod, scores, N):
+    """Scores -0 and +0 are equal: the earlier candidate comes first whichever sign it has, also as the
+    parent of a later one."""
+    M = len(scores)
+    dd = gu.DeviceDraft(1, 4, M)
+    dd.M = M
+    par = np.full((1, M), -1, np.int32)
+    par[0, M // 2:] = np.arange(M - M // 2) // 2 if M <= 4 else -1
+    dd.tok.copy_(gu.dev(np.arange(M, dtype=np.int32)[None]))
+    dd.score.copy_(gu.dev(np.array([scores], np.float32)))
+    dd.par.copy_(gu.dev(par))
+    _check_build(gu, oracle_mod, dd, N)
