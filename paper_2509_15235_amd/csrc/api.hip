@@ -164,7 +164,13 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // each (with few splits the merge's items queue up in few waves: 1 x 60 nodes, 28 / 4 heads, 400 keys in splits of 128 12.3 us, of
     // 64 9.3; 650 keys 11.0 / 9.8; 2 x 17 nodes, 1400 keys 11.5 / 10.7), and then for any number of units (4 x 14 nodes,
     // 120 keys: rounds 11.7, one split 9.7; 12 x 62 nodes, 76 keys: pipelined 14.8, one split 11.0).
-    const int res_short = tiles <= 3 ? 1 : (tiles <= 32 && (int64_t)units0 * res_rg * tiles <= kNumCUs ? tiles : 0);
+    // Four tiles (193 .. 256 keys) of twelve units or more stay one split too, as two rounds (below): their sums then remain fp32
+    // up to the one final rounding. Splits store bf16 partial rows - relative error of N(0, 1) inputs 2.6e-3 in four splits
+    // of 64 keys, 2.2e-3 in one - and are hardly faster: 28 / 4 heads, 190 .. 240 keys, us in one split / in four (one of
+    // the pipelined kernel's): 3 x 60 nodes 11.4 / 11.6 (16.6), 16 x 14 nodes 11.2 / 12.1 (13.3); 32 / 8 heads of 64, 2 x 31 nodes
+    // 8.1 / 7.9 (9.7), 16 x 31 8.9 / 11.6 in two (10.6).
+    const bool one_split = many && tiles == 4;
+    const int res_short = tiles <= 3 ? 1 : (tiles <= 32 && !one_split && (int64_t)units0 * res_rg * tiles <= kNumCUs ? tiles : 0);
     const int res_tps = res_short ? tiles / res_short : (int64_t)units0 * res_rg * ((tiles + 1) / 2) <= kNumCUs ? 2 : 3; // 64-key tiles per split
     const int res_splits = splits > 0 ? splits : (tiles + res_tps - 1) / res_tps;
     const bool resident_ok = (!many || (res_short && splits <= 0)) && nrb >= 2 && tiles <= 32 && (rpw == 0 || rpw == 1) && (waves == 0 || waves == 8) &&
@@ -214,7 +220,7 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // 176 / 56; 64 x 16, 28 / 4 heads, 8000 keys 278 / 221, 1024 .. 8191 keys 197 / 175; 20 x 13, 4096 .. 8191 keys 89 / 71.
     const bool bal_capped = bal_w_auto * d->Hkv * bal_rg < bal_places * 7 / 8;
     const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
-    const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || (nrb <= 4 && (nrb > 2 || d->B > 1 || d->d == 64 || tiles <= 24)));
+    const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || one_split || (nrb <= 4 && (nrb > 2 || d->B > 1 || d->d == 64 || tiles <= 24)));
     // One row block: tiles of the wave's own (attention_mfma_rows.hip), for any number of units: splits of at least 192
     // keys while CUs are free (28 / 4 heads, 4 nodes: 700 keys in one split 9.7 us, in four 8.8; 400 keys 8.2 / 9.1 in
     // three); past one workgroup of eight waves per CU whole sequences, two workgroups of four waves (32 x 20
@@ -280,7 +286,7 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
         pl.res_rb = rnd_rb;
         pl.row_groups = (nrb + pl.res_rb - 1) / pl.res_rb;
         splits = kNumCUs / (units0 * pl.row_groups);
-        const int most = (tiles + 1) / 2;
+        const int most = one_split ? 1 : (tiles + 1) / 2;
         if (splits > most) splits = most;
         // long sequences that would leave CUs idle: five short rounds, handed out as CUs fall free (28 / 4 heads, 40 x 18
         // nodes: 1024 .. 8191 keys one split 162, three 132, five 132, eight 139, balanced shares 130 us; all of 4000

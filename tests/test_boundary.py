@@ -194,6 +194,20 @@ def test_plan_and_workspace_sizes():
     assert pm.schedule == vs.VS_SCHED_PIPELINED and pm.waves_per_group == 4 and pm.num_splits == 8 and pm.workgroups == 256
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,B,T", [(28, 4, 128, 3, 60), (28, 4, 128, 8, 60), (28, 4, 128, 16, 14), (32, 32, 128, 1, 60), (32, 32, 128, 4, 64),
+                                          (32, 8, 64, 2, 31), (32, 8, 64, 16, 31), (16, 16, 64, 8, 60), (8, 1, 128, 12, 60), (8, 2, 128, 6, 1)])
+def test_up_to_256_keys_of_many_units_are_one_split(Hq, Hkv, d, B, T):
+    """Twelve (sequence, KV head) units or more and at most 256 visible keys: no split, hence no bf16 partial rows
+    between the fp32 sums and the final rounding."""
+    for keys in (129, 192, 193, 255, 256):
+        desc = _desc(B=B, T=T, Hq=Hq, Hkv=Hkv, d=d, max_prefix_len=keys - T, capacity=300, stride_seq=Hkv * 300 * d, stride_head=300 * d,
+                     stride_tok=d)
+        rc, plan = vs.vs_attention_plan(desc)
+        assert rc == 0 and plan.num_splits == 1 and plan.combine == 0 and vs.vs_attention_workspace_bytes(desc) == 0
+        desc.max_prefix_len = keys                                # the same keys without a tree behind them
+        assert vs.vs_compress_attention_workspace_bytes(desc) == 0
+
+
 def test_calls_reject_bad_arguments_before_any_launch():
     d = _desc()
     good = 4096  # never dereferenced: every call below fails validation first

@@ -24,6 +24,8 @@ TIGHT_SHORT = (1.2e-2, 6e-3)
     (1, 9, 8, 1, 64, True, [33000]),
     (1, 64, 9, 1, 128, False, [5000]),                           # five row groups
     (16, 20, 16, 4, 128, False, [37 * i + 1 for i in range(16)]),  # one split per unit or a few, ends everywhere
+    (3, 60, 28, 4, 128, False, [196, 133, 0]),                   # one split of two rounds, four row groups
+    (8, 31, 32, 8, 64, True, [225, 162, 163, 96, 97, 98, 1, 33]),  # ... four row blocks of 64 channels, ends around a round
 ])
 def test_rounds(oracle_mod, B, T, Hq, Hkv, d, paged, lens):
     import gpu_util as gu
