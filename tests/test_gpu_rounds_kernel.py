@@ -118,3 +118,30 @@ def test_shares_handed_over(oracle_mod, kw):
     finally:
         vs.lib().vs_internal_set_merge_wait(2000)
     np.testing.assert_array_equal(da.run(), want)
+
+
+@pytest.mark.parametrize("Hq,Hkv,T,lens,wgs", [(28, 4, 60, [1100, 421, 2000], 216),      # eight waves, nine splits, two row groups
+                                               (28, 4, 60, [3000, 421, 64, 1100, 2900, 2100, 3136, 1], 256),  # four splits
+                                               (32, 32, 60, [2900], 256)])                # four waves
+def test_shares_of_the_pipelined_kernel_handed_over(oracle_mod, Hq, Hkv, T, lens, wgs):
+    """The same where the planner lets the pipelined kernel merge its own splits."""
+    import gpu_util as gu
+    cfg = gen.Config("handover", len(lens), Hq, Hkv, 128, T, 6, 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2), paged=False)
+    inp = gen.attention_inputs(cfg, 971, prefix_len=np.array(lens, dtype=np.int32))
+    da = gu.DeviceAttn(inp)
+    pl = da.plan()
+    assert pl.schedule == vs.VS_SCHED_PIPELINED and pl.workgroups == wgs and pl.combine == 1
+    partials = len(lens) * Hkv * pl.num_splits * (-(-T * Hq // Hkv // 32) * 32) * (128 * 2 + 8)
+    assert da.ws_bytes == partials + len(lens) * Hkv * pl.row_groups * 256   # the gates
+    da.ws.random_(0, 256)
+    want = da.run()
+    ref = oracle_mod.tree_attention(inp, threads=8)
+    for b in range(len(lens)):
+        gu.check_close(want[b], ref[b], *(TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT), what=f"sequence {b} of {lens[b]}")
+    try:
+        vs.lib().vs_internal_set_merge_wait(0)
+        for _ in range(4):
+            np.testing.assert_array_equal(da.run(), want)
+    finally:
+        vs.lib().vs_internal_set_merge_wait(2000)
+    np.testing.assert_array_equal(da.run(), want)
