@@ -518,10 +518,15 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.res_rb ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
     p.total_wgs = pl.total_wgs;
     p.bal_chunks = pl.bal_chunks;
-    // a launch of more whole sequences than run at once hands out the longest first (a lane per sequence) - but not where the sequences are so short that the wait for all lengths costs more (64 x 20 nodes, 32 / 32 heads,
-    // 30 .. 249 keys: 45 us in order, 56 longest first)
-    p.by_length = (pl.schedule == VS_SCHED_PIPELINED || (pl.own_tiles && desc->max_prefix_len >= 1024)) && pl.num_splits == 1 && desc->B >= 2 && desc->B <= kBalMaxSeqs &&
-                  pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2);
+    // A launch of more whole sequences than run at once hands out the longest first (a lane per sequence), unless even the longest is
+    // so short that the wait for all lengths costs more than it brings. us per call, longest first / in order:
+    // pipelined kernel, 28 / 4 heads, 60 nodes, 64 sequences, all of 100 keys 41.6 / 36.1, 250 51.8 / 46.3, 500 65.0 / 60.0, 1000 93.2 / 89.1;
+    // 1/8 .. 1 of 100 38.8 / 33.3, 250 42.7 / 40.5, 500 51.1 / 50.4, 1000 69.1 / 71.5, 2000 105.6 / 120.6; 40 sequences, 1/8 .. 1 of 500
+    // 41.8 / 41.1, 1000 54.4 / 65.8; 20 of 32 / 32 heads, 1/8 .. 1 of 250 32.2 / 33.2, 500 39.1 / 42.0, 1000 57.5 / 61.6, all of 500 54.2 / 53.0
+    // own tiles: 64 x 20 nodes, 32 / 32 heads, 30 .. 249 keys 56 / 45
+    const int64_t by_length_from = pl.schedule == VS_SCHED_PIPELINED ? 768 : 1024; // longest allowed prefix
+    p.by_length = (pl.schedule == VS_SCHED_PIPELINED || pl.own_tiles) && desc->max_prefix_len >= by_length_from && pl.num_splits == 1 &&
+                  desc->B >= 2 && desc->B <= kBalMaxSeqs && pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2);
     if (need > 0) {
         const size_t prow = partial_rows(desc, pl);
         p.part_o = (uint16_t*)workspace;

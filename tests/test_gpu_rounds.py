@@ -19,6 +19,7 @@ def test_longest_first(oracle_mod, B, T, Hq, Hkv, d, paged, lens):
     import gpu_util as gu
     r = np.random.default_rng(B + T)
     S = r.integers(1, 400, size=B).astype(np.int32) if lens != "ties" else r.choice([7, 130, 131], size=B).astype(np.int32)
+    S[B // 3] = 800                                    # shorter ones are taken in order
     cfg = gen.Config("rounds", B, Hq, Hkv, d, T, min(6, T - 1), 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 400),
                      paged=paged)
     inp = gen.attention_inputs(cfg, 700 + B, prefix_len=S)
