@@ -53,14 +53,19 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5;
-    const int col = lane & 31;
 
     // One piece of work: the rows of row group `rg` of (sequence b, KV head kvh) against the keys
     // [k0, k0 + klen) of that sequence (k0 lies inside the cache). `whole`: no other piece shares these
     // rows, they leave as final output; else as the partial result of slot `slot`.
     auto run_piece = [&](const int b, const int kvh, const int rg, const int k0, const int klen, const int slot,
                          bool whole) __attribute__((always_inline)) {
+    int tid = threadIdx.x;
+    // What depends on the lane alone is worked out for every piece: kept from one piece to the next it takes registers that the loop
+    // needs. Four waves of 128 channels had 41 of them in scratch memory, and the wait for a spilled value in the
+    // loop waits for all tile copies in flight: 20 x 60 nodes, 32 / 32 heads, 250 .. 2000 keys 131 us, so 117
+    // (8 of 1024 .. 8191 keys 159 / 147, paged 163 / 154; eight waves: no spills either, 1 %).
+    if (BAL) asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int32_t S = p.prefix_len[b]; // requested first, needed last: the first tiles and the queries are requested before it arrives
 
     // ---- tile copies. One load instruction of a wave fetches 1 KB of consecutive memory:
@@ -136,10 +141,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     // through the tile slot of this wave's number (nothing is in the rings yet)
     uint16_t* sq = wave < NSLOT ? sK[wave & (NSLOT - 1)] : sV[wave & (NSLOT - 1)];
     if (wave_active) {
-        int ql = lane;
-        if (BAL) asm volatile("" : "+v"(ql)); // keeps the addresses (the same for every piece) from living in registers
 #pragma unroll
-        for (int i = 0; i < KS; ++i) copy_q_piece<D>(p, b, kvh, row_base, sq, i, ql);
+        for (int i = 0; i < KS; ++i) copy_q_piece<D>(p, b, kvh, row_base, sq, i, lane);
     }
 
     int32_t tree_code = VS_STATUS_OK;
@@ -201,6 +204,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         const int rel = lb - bt_base; // 0 .. 63 by construction
         return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bt_hi, rel) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)bt_lo, rel));
     };
+    // this lane's 16 bytes of the block at a uniform address: a scalar address plus lane_off (left to itself the compiler adds
+    // them up first, and the copies' addresses take two registers each)
+    auto load_at = [&](const void* block) __attribute__((always_inline)) {
+        const __attribute__((address_space(1))) char* base = (const __attribute__((address_space(1))) char*)block;
+        asm("" : "+s"(base));
+        return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
+    };
     auto load_tile = [&](auto lfast_tag, auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
         constexpr bool LFAST = decltype(lfast_tag)::value;
         constexpr bool ISV = decltype(is_v)::value;
@@ -215,7 +225,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
                     const int r0 = k0 + t * kTileKeys + RPI * i;
                     const int64_t sbase = head_base + bt_lookup(r0 >> p.block_shift) +
                                           (int64_t)((r0 & (p.block_size - 1)) * stride_tok);
-                    r[j] = *(const u32x4*)((const char*)((ISV ? vbase : kbase) + sbase) + lane_off);
+                    r[j] = load_at((ISV ? vbase : kbase) + sbase);
                 }
             }
         } else if constexpr (LFAST) {
@@ -224,7 +234,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
                 const int i = wave * BPW + j; // uniform per wave
                 if (NW * BPW == BPS || i < BPS) {
                     const uint32_t off = (uint32_t)((t * kTileKeys + RPI * i) * stride_tok) * 2u;
-                    r[j] = *(const u32x4*)((ISV ? vfast : kfast) + off + lane_off);
+                    r[j] = load_at((ISV ? vfast : kfast) + off);
                 }
             }
         } else {
@@ -698,6 +708,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     }; // run_piece
 
     if constexpr (!BAL) {
+        int b, kvh, rg, split = 0;
         if (p.by_length) {
             // More workgroups than run at once, one per (sequence, KV head, row group): the longest
             // sequences first. Workgroup slot j of an XCD is handed out when the ones before it run or are
@@ -706,22 +717,23 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
             // as long as its unluckiest CU (64 paged sequences of 1024 .. 8191 keys, 28 / 4 heads: 421 us
             // against 354 us). The cost is the wait for the lengths before the first tile can be requested.
             const int j = blockIdx.x >> 3;
-            const int rg = j % p.row_groups;
+            rg = j % p.row_groups;
             const int k = (j / p.row_groups) * 8 + (blockIdx.x & 7); // units by rank of their sequence, dealt over the XCDs
             if (k >= p.B * p.Hkv) return;
-            run_piece(sequence_by_rank(p, k / p.Hkv, lane), k % p.Hkv, rg, 0, p.keys_per_split, 0, true);
-            return;
+            b = sequence_by_rank(p, k / p.Hkv, lane);
+            kvh = k % p.Hkv;
+        } else {
+            // workgroup id -> (sequence, KV head, row group, split), XCD-aware (see attention_mfma.hip)
+            const int per_xcd = (p.total_wgs + 7) >> 3;
+            const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+            if (v >= p.total_wgs) return;
+            split = v % p.num_splits; // splits fastest, see attention_mfma.hip
+            int rest = v / p.num_splits;
+            rg = rest % p.row_groups;
+            rest /= p.row_groups;
+            kvh = rest % p.Hkv;
+            b = rest / p.Hkv;
         }
-        // workgroup id -> (sequence, KV head, row group, split), XCD-aware (see attention_mfma.hip)
-        const int per_xcd = (p.total_wgs + 7) >> 3;
-        const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-        if (v >= p.total_wgs) return;
-        const int split = v % p.num_splits; // splits fastest, see attention_mfma.hip
-        int rest = v / p.num_splits;
-        const int rg = rest % p.row_groups;
-        rest /= p.row_groups;
-        const int kvh = rest % p.Hkv;
-        const int b = rest / p.Hkv;
         // the host keeps every split's first key below max_prefix_len + tree_keys, hence inside the cache
         run_piece(b, kvh, rg, split * p.keys_per_split, p.keys_per_split, split, p.num_splits == 1);
     } else {
@@ -741,8 +753,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         if (c == 0 && kvh == 0 && rg == 0 && wave == 0) p.bal_table[lane] = bounds; // for the combine kernel
         const int lo = __builtin_amdgcn_readlane(bounds, c);
         const int hi = c + 1 < p.bal_chunks ? __builtin_amdgcn_readlane(bounds, c + 1) : total;
+        // (in LDS, every wave its own copy: two registers that the loop over the tiles needs)
+        __shared__ int32_t s_start[NW][kBalMaxSeqs], s_steps[NW][kBalMaxSeqs];
+        s_start[wave][lane] = start;
+        s_steps[wave][lane] = steps;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by all lanes of this wave
         for (int i = 0; i < p.B; ++i) {
-            const int s0 = __builtin_amdgcn_readlane(start, i), t = __builtin_amdgcn_readlane(steps, i);
+            const int s0 = __builtin_amdgcn_readfirstlane(s_start[wave][i]), t = __builtin_amdgcn_readfirstlane(s_steps[wave][i]);
             int t0, t1;
             if (bal_piece(lo, hi, s0, t, t0, t1)) { // uniform
                 __syncthreads(); // the previous piece's last reads of the tile rings, the tree and the flag
