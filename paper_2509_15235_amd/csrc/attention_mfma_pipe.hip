@@ -43,6 +43,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     constexpr int BPS = SUB * 2 / 1024;        // 1 KB blocks (16 keys x 32 channels) per tile
     constexpr int BPW = (BPS + NW - 1) / NW;   // ... copied by each wave
     constexpr int NSLOT = 4;
+    // Eight waves of 64 channels are twice as many as a tile has blocks: the lower half copies K, the upper half V, one block
+    // of every tile each. (With all copies on the lower half, behind a branch per copy, the compiler cannot count the
+    // loads in flight and waits for all of them in front of every LDS write, the one just requested included: us per call,
+    // so / now, 60 nodes, 32 / 8 heads, 18 x 1000 keys 38.1 / 28.2, 48 x 250 .. 2000 101 / 77, 24 x 1000 .. 8000 paged 155 / 112.)
+    constexpr bool HALVES = NW == 2 * BPS;
+    static_assert(HALVES || NW * BPW == BPS, "the waves' blocks make up a tile");
 
     __shared__ __attribute__((aligned(1024))) uint16_t sK[NSLOT][SUB];
     __shared__ __attribute__((aligned(1024))) uint16_t sV[NSLOT][SUB];
@@ -86,10 +92,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     const int stride_tok = (int)p.stride_tok; // host guarantees 32-bit lane offsets
     const int lrow = lane / LPR, lchunk = lane % LPR;
     const uint32_t lane_off = (uint32_t)(lrow * stride_tok + lchunk * 8) * 2u; // bytes
+    const int block0 = HALVES ? wave % BPS : wave * BPW; // this wave's first block of a tile
+    const bool upper = HALVES && wave >= BPS;
     uint32_t k_st[BPW], v_st[BPW]; // this lane's LDS byte offsets inside a tile slot, per block
 #pragma unroll
     for (int j = 0; j < BPW; ++j) {
-        const int r = (wave * BPW + j) * RPI + lrow, c = lchunk;
+        const int r = (block0 + j) * RPI + lrow, c = lchunk;
         k_st[j] = (uint32_t)(((r >> 4) * DB + (c >> 2)) * 1024 + (c & 3) * 256 + (((r & 15) ^ (4 * (c & 3))) * 16));
         v_st[j] = (uint32_t)(((r >> 4) * DB + (c >> 2)) * 1024 + (4 * (r & 15) + (c & 3)) * 16);
     }
@@ -105,25 +113,24 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
             const uint16_t* gbase = decltype(is_v)::value ? vbase : kbase;
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
-                const int i = wave * BPW + j;
-                if (NW * BPW == BPS || i < BPS) {
-                    const int r0 = min(k0 + t * kTileKeys + RPI * i, kend - 1); // RPI divides 16: one cache block in paged mode
-                    int tok = min(r0 + lrow, kend - 1);
-                    int64_t base = head_base;
-                    if (PAGED) {
-                        int32_t blk = p.block_table[(int64_t)b * p.max_blocks + (r0 >> p.block_shift)];
-                        if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-                        base += (int64_t)blk * p.stride_block;
-                        tok &= p.block_size - 1;
-                    }
-                    r[j] = *(const u32x4*)(gbase + base + (uint32_t)(tok * stride_tok + lchunk * 8));
+                const int r0 = min(k0 + t * kTileKeys + RPI * (block0 + j), kend - 1); // RPI divides 16: one cache block in paged mode
+                int tok = min(r0 + lrow, kend - 1);
+                int64_t base = head_base;
+                if (PAGED) {
+                    int32_t blk = p.block_table[(int64_t)b * p.max_blocks + (r0 >> p.block_shift)];
+                    if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
+                    base += (int64_t)blk * p.stride_block;
+                    tok &= p.block_size - 1;
                 }
+                r[j] = *(const u32x4*)(gbase + base + (uint32_t)(tok * stride_tok + lchunk * 8));
             }
         };
-        load_tile_early(std::false_type{}, 0, stage[1][0]);
-        load_tile_early(std::false_type{}, 1, stage[1][1]);
-        load_tile_early(std::false_type{}, 2, stage[1][2]);
-        load_tile_early(std::true_type{}, 0, stage[1][3]);
+        if (!upper) {
+            load_tile_early(std::false_type{}, 0, stage[1][0]);
+            load_tile_early(std::false_type{}, 1, stage[1][1]);
+            load_tile_early(std::false_type{}, 2, stage[1][2]);
+        }
+        if (!HALVES || upper) load_tile_early(std::true_type{}, 0, stage[1][3]);
     }
 
     // ---- this wave's rows and queries (in flight together with the first tiles)
@@ -211,77 +218,77 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
         asm("" : "+s"(base));
         return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
     };
+    // is_v: a constant or, with HALVES, `upper`
     auto load_tile = [&](auto lfast_tag, auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
         constexpr bool LFAST = decltype(lfast_tag)::value;
-        constexpr bool ISV = decltype(is_v)::value;
+        const bool ISV = is_v;
         if constexpr (LFAST && PAGED) {
             // a full tile of a paged cache: the RPI rows of a copy block lie in one cache block, so the
             // address is a wave-uniform base (block id from the window, KV head, first row inside the
             // block - all scalar arithmetic) plus the same per-lane constant as for a contiguous cache
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
-                const int i = wave * BPW + j; // uniform per wave
-                if (NW * BPW == BPS || i < BPS) {
-                    const int r0 = k0 + t * kTileKeys + RPI * i;
-                    const int64_t sbase = head_base + bt_lookup(r0 >> p.block_shift) +
-                                          (int64_t)((r0 & (p.block_size - 1)) * stride_tok);
-                    r[j] = load_at((ISV ? vbase : kbase) + sbase);
-                }
+                const int r0 = k0 + t * kTileKeys + RPI * (block0 + j); // uniform per wave
+                const int64_t sbase = head_base + bt_lookup(r0 >> p.block_shift) + (int64_t)((r0 & (p.block_size - 1)) * stride_tok);
+                r[j] = load_at((ISV ? vbase : kbase) + sbase);
             }
         } else if constexpr (LFAST) {
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
-                const int i = wave * BPW + j; // uniform per wave
-                if (NW * BPW == BPS || i < BPS) {
-                    const uint32_t off = (uint32_t)((t * kTileKeys + RPI * i) * stride_tok) * 2u;
-                    r[j] = load_at((ISV ? vfast : kfast) + off);
-                }
+                const uint32_t off = (uint32_t)((t * kTileKeys + RPI * (block0 + j)) * stride_tok) * 2u; // uniform per wave
+                r[j] = load_at((ISV ? vfast : kfast) + off);
             }
         } else {
             const uint16_t* gbase = ISV ? vbase : kbase;
             if (k0 + t * kTileKeys >= k1) return; // no such tile: its LDS image is never used
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
-                const int i = wave * BPW + j;
-                if (i < BPS) {
-                    const int r0 = k0 + t * kTileKeys + RPI * i; // RPI divides 16: one cache block in paged mode
-                    int tok = min(r0 + lrow, k1 - 1);
-                    int64_t base = head_base;
-                    if (PAGED) {
-                        base += bt_lookup(min(r0, k1 - 1) >> p.block_shift);
-                        tok &= p.block_size - 1;
-                    }
-                    const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
-                    r[j] = *(const u32x4*)(gbase + base + off);
+                const int r0 = k0 + t * kTileKeys + RPI * (block0 + j); // RPI divides 16: one cache block in paged mode
+                int tok = min(r0 + lrow, k1 - 1);
+                int64_t base = head_base;
+                if (PAGED) {
+                    base += bt_lookup(min(r0, k1 - 1) >> p.block_shift);
+                    tok &= p.block_size - 1;
                 }
+                const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
+                r[j] = *(const u32x4*)(gbase + base + off);
             }
         }
     };
-    auto stash_tile = [&](auto is_v, uint16_t* slot, const u32x4(&r)[BPW]) __attribute__((always_inline)) {
-        constexpr bool ISV = decltype(is_v)::value;
+    auto stash_tile = [&](auto is_v, int t, const u32x4(&r)[BPW]) __attribute__((always_inline)) {
+        const bool ISV = is_v;
+        char* slot = (char*)(ISV ? sV[t & 3] : sK[t & 3]);
 #pragma unroll
-        for (int j = 0; j < BPW; ++j) {
-            const int i = wave * BPW + j;
-            if (NW * BPW == BPS || i < BPS) *(u32x4*)((char*)slot + (ISV ? v_st[j] : k_st[j])) = r[j];
-        }
+        for (int j = 0; j < BPW; ++j) *(u32x4*)(slot + (ISV ? v_st[j] : k_st[j])) = r[j];
     };
     // Copies are grouped per iteration: group g = K(2g+3), K(2g+4), V(2g+1), V(2g+2) is what
     // iteration g writes to LDS. Its loads are issued in iteration g - 2, so two groups are
     // in flight and alternate between two register sets.
+    // Part 0 .. 3 of a group (HALVES: 0 and 2, this wave's first and second tile): what do(is_v, tile, registers) gets.
+    auto part_of = [&](auto part_tag, auto set_tag, int g, auto what) __attribute__((always_inline)) {
+        constexpr int PART = decltype(part_tag)::value, SET = decltype(set_tag)::value;
+        if constexpr (HALVES) {
+            if constexpr (PART % 2 == 0) what(upper, 2 * g + (upper ? 1 : 3) + PART / 2, stage[SET][PART / 2]);
+        } else if constexpr (PART < 2) {
+            what(std::false_type{}, 2 * g + 3 + PART, stage[SET][PART]);
+        } else {
+            what(std::true_type{}, 2 * g - 1 + PART, stage[SET][PART]);
+        }
+    };
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    using P2 = std::integral_constant<int, 2>;
+    using P3 = std::integral_constant<int, 3>;
+    auto each_part = [&](auto set_tag, int g, auto what) __attribute__((always_inline)) {
+        part_of(P0{}, set_tag, g, what);
+        part_of(P1{}, set_tag, g, what);
+        part_of(P2{}, set_tag, g, what);
+        part_of(P3{}, set_tag, g, what);
+    };
     auto load_group = [&](auto lfast_tag, auto set_tag, int g) __attribute__((always_inline)) {
-        constexpr int SET = decltype(set_tag)::value;
-        load_tile(lfast_tag, std::false_type{}, 2 * g + 3, stage[SET][0]);
-        load_tile(lfast_tag, std::false_type{}, 2 * g + 4, stage[SET][1]);
-        load_tile(lfast_tag, std::true_type{}, 2 * g + 1, stage[SET][2]);
-        load_tile(lfast_tag, std::true_type{}, 2 * g + 2, stage[SET][3]);
+        each_part(set_tag, g, [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) { load_tile(lfast_tag, is_v, t, r); });
     };
-    auto stash_group = [&](auto set_tag, int g) __attribute__((always_inline)) {
-        constexpr int SET = decltype(set_tag)::value;
-        stash_tile(std::false_type{}, sK[(2 * g + 3) & 3], stage[SET][0]);
-        stash_tile(std::false_type{}, sK[(2 * g + 4) & 3], stage[SET][1]);
-        stash_tile(std::true_type{}, sV[(2 * g + 1) & 3], stage[SET][2]);
-        stash_tile(std::true_type{}, sV[(2 * g + 2) & 3], stage[SET][3]);
-    };
+    auto stash_group = [&](auto set_tag, int g) __attribute__((always_inline)) { each_part(set_tag, g, stash_tile); };
 
     // the rest of the prologue copies: group 0 (set 0)
     load_group(std::false_type{}, std::integral_constant<int, 0>{}, 0);
@@ -505,21 +512,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
                 for (int sg = f * GPS; sg < (f + 1) * GPS; ++sg) softmax_group(rb, sg);
                 if constexpr (CSET >= 0) {
                     if (rb == 0 && f % (NF / 4) == 1) {
-                        constexpr int SETC = CSET >= 0 ? CSET : 0;
-                        const int part = f / (NF / 4); // 0, 1: K(2g+3), K(2g+4); 2, 3: V(2g+1), V(2g+2)
-                        if (part == 0) {
-                            stash_tile(std::false_type{}, sK[(2 * g + 3) & 3], stage[SETC][0]);
-                            load_tile(lfast_tag, std::false_type{}, 2 * (g + 2) + 3, stage[SETC][0]);
-                        } else if (part == 1) {
-                            stash_tile(std::false_type{}, sK[(2 * g + 4) & 3], stage[SETC][1]);
-                            load_tile(lfast_tag, std::false_type{}, 2 * (g + 2) + 4, stage[SETC][1]);
-                        } else if (part == 2) {
-                            stash_tile(std::true_type{}, sV[(2 * g + 1) & 3], stage[SETC][2]);
-                            load_tile(lfast_tag, std::true_type{}, 2 * (g + 2) + 1, stage[SETC][2]);
-                        } else {
-                            stash_tile(std::true_type{}, sV[(2 * g + 2) & 3], stage[SETC][3]);
-                            load_tile(lfast_tag, std::true_type{}, 2 * (g + 2) + 2, stage[SETC][3]);
-                        }
+                        auto renew = [&](auto part_tag) __attribute__((always_inline)) {
+                            part_of(part_tag, copy_tag, g, stash_tile);
+                            part_of(part_tag, copy_tag, g + 2, [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
+                                load_tile(lfast_tag, is_v, t, r);
+                            });
+                        };
+                        const int part = f / (NF / 4); // known after unrolling
+                        if (part == 0) renew(P0{});
+                        else if (part == 1) renew(P1{});
+                        else if (part == 2) renew(P2{});
+                        else renew(P3{});
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -550,18 +553,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
             constexpr bool ISV = decltype(is_v)::value;
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
-                const int i = wave * BPW + j;
-                if (NW * BPW == BPS || i < BPS) {
-                    const bool live = k0 + t * kTileKeys + RPI * i + lrow < k1;
-                    const u32x4 zero = {0u, 0u, 0u, 0u};
-                    *(u32x4*)((char*)slot + (ISV ? v_st[j] : k_st[j])) = live ? r[j] : zero;
-                }
+                const bool live = k0 + t * kTileKeys + RPI * (block0 + j) + lrow < k1;
+                const u32x4 zero = {0u, 0u, 0u, 0u};
+                *(u32x4*)((char*)slot + (ISV ? v_st[j] : k_st[j])) = live ? r[j] : zero;
             }
         };
-        stash_tile_live(std::false_type{}, sK[0], stage[1][0], 0);
-        stash_tile_live(std::false_type{}, sK[1], stage[1][1], 1);
-        stash_tile_live(std::false_type{}, sK[2], stage[1][2], 2);
-        stash_tile_live(std::true_type{}, sV[0], stage[1][3], 0);
+        if (!upper) {
+            stash_tile_live(std::false_type{}, sK[0], stage[1][0], 0);
+            stash_tile_live(std::false_type{}, sK[1], stage[1][1], 1);
+            stash_tile_live(std::false_type{}, sK[2], stage[1][2], 2);
+        }
+        if (!HALVES || upper) stash_tile_live(std::true_type{}, sV[0], stage[1][3], 0);
     }
     load_group(std::false_type{}, std::integral_constant<int, 1>{}, 1);
     __syncthreads();
