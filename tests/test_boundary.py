@@ -208,16 +208,16 @@ def test_up_to_256_keys_of_many_units_are_one_split(Hq, Hkv, d, B, T):
         assert vs.vs_compress_attention_workspace_bytes(desc) == 0
 
 
-@pytest.mark.parametrize("B,S,wgs,gates", [(3, 1000, 120, 0), (4, 1000, 160, 0), (8, 700, 192, 0), (5, 1000, 200, 1), (3, 2000, 216, 1),
-                                           (8, 3136, 256, 1)])
-def test_what_merges_the_splits_of_the_pipelined_kernel(B, S, wgs, gates):
-    """The splits' own workgroups (their gates take workspace) where they are most of the chip and have few items
-    each, else the combine kernel."""
+@pytest.mark.parametrize("B,T,S,wgs,gates", [(3, 60, 1000, 120, 0), (4, 60, 1000, 160, 0), (8, 60, 700, 192, 0), (5, 60, 1000, 200, 1),
+                                             (3, 60, 2000, 216, 1), (8, 60, 3136, 256, 1), (3, 35, 2019, 108, 1), (3, 31, 3000, 144, 1)])
+def test_what_merges_the_splits_of_the_pipelined_kernel(B, T, S, wgs, gates):
+    """The splits' own workgroups (their gates take workspace) where they have few items each and are many splits or most
+    of the chip, else the combine kernel."""
     cap = S + 64
-    desc = _desc(B=B, max_prefix_len=S, capacity=cap, stride_seq=4 * cap * 128, stride_head=cap * 128)
+    desc = _desc(B=B, T=T, max_prefix_len=S, capacity=cap, stride_seq=4 * cap * 128, stride_head=cap * 128)
     rc, plan = vs.vs_attention_plan(desc)
     assert rc == 0 and plan.schedule == vs.VS_SCHED_PIPELINED and plan.workgroups == wgs and plan.combine == 1
-    partials = B * 4 * plan.num_splits * 448 * (128 * 2 + 8)
+    partials = B * 4 * plan.num_splits * (-(-7 * T // 32) * 32) * (128 * 2 + 8)
     assert vs.vs_attention_workspace_bytes(desc) == partials + gates * B * 4 * plan.row_groups * 32 * 8
 
 
