@@ -529,7 +529,8 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     // own tiles: 64 x 20 nodes, 32 / 32 heads, 30 .. 249 keys 56 / 45
     const int64_t by_length_from = pl.schedule == VS_SCHED_PIPELINED ? 768 : 1024; // longest allowed prefix
     p.by_length = (pl.schedule == VS_SCHED_PIPELINED || pl.own_tiles) && desc->max_prefix_len >= by_length_from && pl.num_splits == 1 &&
-                  desc->B >= 2 && desc->B <= kBalMaxSeqs && pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2);
+                  desc->B >= 2 && desc->B <= kBalMaxSeqs && pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2) &&
+                  !(pl.schedule == VS_SCHED_PIPELINED && pipe_three_per_cu(desc->d, pl.waves, pl.total_wgs));
     if (need > 0) {
         const size_t prow = partial_rows(desc, pl);
         p.part_o = (uint16_t*)workspace;

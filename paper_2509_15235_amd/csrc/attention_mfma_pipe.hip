@@ -35,8 +35,12 @@ namespace vs {
 
 namespace {
 
-template <int D, int RPW, int NW, bool PAGED, bool BAL>
-__global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnParams p) {
+// WPS: waves of a SIMD that have registers at the same time. Three workgroups of four waves and 64 channels on a CU
+// instead of two where that makes one round of a launch that is one and a half: us per call in two / three, 16 / 16 heads,
+// 33 x 43 nodes (528 workgroups), 450 keys 27.4 / 21.2, 1500 paged 71.1 / 55.1; 46 x 60 (736), 200 .. 450 paged 33.1 / 25.6; outside
+// those 256 workgroups two have the faster loop (below): 20 x 60 (320), 1500 paged 42.1 / 47.2, 50 x 60 (800), 450 34.9 / 38.5.
+template <int D, int RPW, int NW, bool PAGED, bool BAL, int WPS = 2>
+__global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const AttnParams p) {
     constexpr int KS = D / 16;                 // k-steps of the S^T product
     constexpr int DB = D / 32;                 // 32-channel blocks of the output
     constexpr int SUB = kTileKeys * D;         // elements per 32-key tile of K (or V)
@@ -660,8 +664,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_pipe_kernel(const AttnPa
     // cannot tell which copies are still on their way and waits for all of them in every iteration, the ones just
     // requested included (12 x 60 nodes, 16 / 16 heads of 64 channels, up to 8000 keys 68 -> 57 us; eight waves
     // of 128 channels 1 %). Four waves of 128 channels run out of registers that way (32 x 60 nodes of 32 / 32
-    // heads, 3136 keys 304 -> 377 us) and are bound by memory, not by its latency.
-    if constexpr (D == 128 && NW == 4) all_tiles(wave_active);
+    // heads, 3136 keys 304 -> 377 us) and are bound by memory, not by its latency; so do three waves per SIMD.
+    if constexpr ((D == 128 && NW == 4) || WPS == 3) all_tiles(wave_active);
     else if (wave_active) all_tiles(T{});
     else all_tiles(F{});
     if (wave_active) {
@@ -780,6 +784,13 @@ hipError_t launch_pipe(const AttnParams& p, hipStream_t s) {
         return hipGetLastError();
     }
     const dim3 grid(p.by_length ? (p.B * p.Hkv + 7) / 8 * 8 * p.row_groups : (p.total_wgs + 7) / 8 * 8);
+    if constexpr (D == 64 && NW == 4) {
+        if (pipe_three_per_cu(D, NW, p.total_wgs)) {
+            if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, false, 3>), grid, dim3(NW * kWave), 0, s, p);
+            else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, false, 3>), grid, dim3(NW * kWave), 0, s, p);
+            return hipGetLastError();
+        }
+    }
     if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, false>), grid, dim3(NW * kWave), 0, s, p);
     else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, false>), grid, dim3(NW * kWave), 0, s, p);
     return hipGetLastError();

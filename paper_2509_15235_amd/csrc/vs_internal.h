@@ -190,6 +190,8 @@ hipError_t launch_attention_generic(const AttnParams& p, hipStream_t s);
 hipError_t launch_attention_f32(const AttnParams& p, hipStream_t s);
 hipError_t launch_attention_mfma(const AttnParams& p, int rpw, int waves, hipStream_t s);
 bool attention_pipe_supported(int rpw, int waves);
+// Does this launch of the pipelined kernel put three workgroups on a CU, all of them at once? (attention_mfma_pipe.hip)
+inline bool pipe_three_per_cu(int d, int waves, int total_wgs) { return d == 64 && waves == 4 && total_wgs > 2 * kNumCUs && total_wgs <= 3 * kNumCUs; }
 hipError_t launch_attention_mfma_pipe(const AttnParams& p, int rpw, int waves, hipStream_t s);
 bool attention_resident_supported(int row_blocks);
 hipError_t launch_attention_mfma_resident(const AttnParams& p, int row_blocks, hipStream_t s);
