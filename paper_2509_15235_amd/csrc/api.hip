@@ -218,7 +218,13 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // With few KV heads the 64 shares do not fill the places, and the kernels that split the keys among the waves take
     // over: us per call, shares / they: 64 x 30 nodes, 8 / 2 heads, 1000 .. 7999 keys 188 / 98; 64 x 14, 8 / 1 heads
     // 176 / 56; 64 x 16, 28 / 4 heads, 8000 keys 278 / 221, 1024 .. 8191 keys 197 / 175; 20 x 13, 4096 .. 8191 keys 89 / 71.
+    // - as long as they find a place for two splits of every sequence, or a whole one fills the chip. In between, us per call,
+    // whole sequences / five splits of each / shares: 40 x 18 nodes, 28 / 4 heads, 1024 .. 8191 keys 162 / 132 / -; 36 x 18, 687 .. 5500
+    // - / 89 / 68, 2750 .. 5500 - / 101 / 91, all of 5500 - / 112 / 118; 33 x 11, 1000 .. 8000 - / 121 / 95, all of 8000 - / 132 / 122;
+    // 52 x 11, 4000 .. 8000 - / 181 / 161; 58 x 18, 1000 .. 8000 - / 181 / 154, all of 8000 - / 241 / 241; and from 240 workgroups on 62 x 18, 400 .. 3200
+    // 79 / - / 96, 1000 .. 8000 168 / - / 153, all of 8000 216 / - / 236.
     const bool bal_capped = bal_w_auto * d->Hkv * bal_rg < bal_places * 7 / 8;
+    const bool rnd_fills = 2 * rnd_wgs <= kNumCUs || rnd_wgs >= 240;
     const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
     const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || one_split || (nrb <= 4 && (nrb > 2 || d->B > 1 || d->d == 64 || tiles <= 24)));
     // One row block: tiles of the wave's own (attention_mfma_rows.hip), for any number of units: splits of at least 192
@@ -231,7 +237,7 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
                                                 ((many && (int64_t)units0 * tiles >= 16 * kNumCUs) || tiles <= 5)));
     pl.schedule = d->schedule != VS_SCHED_AUTO ? d->schedule
                   : own_ok                     ? VS_SCHED_LOOP
-                  : balanced_ok && !(bal_capped && rounds_ok) ? VS_SCHED_BALANCED
+                  : balanced_ok && !(bal_capped && rounds_ok && rnd_fills) ? VS_SCHED_BALANCED
                   : many && resident_ok        ? VS_SCHED_RESIDENT
                   : many && rounds_ok          ? VS_SCHED_LOOP
                   : many && pipe_ok            ? VS_SCHED_PIPELINED
@@ -288,10 +294,6 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
         splits = kNumCUs / (units0 * pl.row_groups);
         const int most = one_split ? 1 : (tiles + 1) / 2;
         if (splits > most) splits = most;
-        // long sequences that would leave CUs idle: five short rounds, handed out as CUs fall free (28 / 4 heads, 40 x 18
-        // nodes: 1024 .. 8191 keys one split 162, three 132, five 132, eight 139, balanced shares 130 us; all of 4000
-        // keys 92 / 88 / 107 / 105 / 122; 33 x 18 nodes 1024 .. 8191 keys: three 128, five 107, shares 115)
-        if (splits == 1 && balanced_ok && rnd_wgs < 240) splits = 5;
         if (splits > kMergeMaxSplits) splits = kMergeMaxSplits;
         if (splits < 1) splits = 1;
         const int tps = (tiles + splits - 1) / splits;

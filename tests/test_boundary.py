@@ -221,6 +221,15 @@ def test_what_merges_the_splits_of_the_pipelined_kernel(B, T, S, wgs, gates):
     assert vs.vs_attention_workspace_bytes(desc) == partials + gates * B * 4 * plan.row_groups * 32 * 8
 
 
+@pytest.mark.parametrize("B,T,schedule,splits", [(24, 18, vs.VS_SCHED_LOOP, 2), (32, 18, vs.VS_SCHED_LOOP, 2), (33, 18, vs.VS_SCHED_BALANCED, 64),
+                                                 (58, 11, vs.VS_SCHED_BALANCED, 64), (59, 18, vs.VS_SCHED_BALANCED, 64), (60, 18, vs.VS_SCHED_LOOP, 1)])
+def test_long_ragged_batches_of_few_row_blocks(B, T, schedule, splits):
+    """Rounds where they find a place for two splits of every sequence or for nearly one per CU; in between balanced shares."""
+    desc = _desc(B=B, T=T, max_prefix_len=8000, capacity=8100, stride_seq=4 * 8100 * 128, stride_head=8100 * 128)
+    rc, plan = vs.vs_attention_plan(desc)
+    assert rc == 0 and plan.schedule == schedule and plan.num_splits == splits
+
+
 def test_calls_reject_bad_arguments_before_any_launch():
     d = _desc()
     good = 4096  # never dereferenced: every call below fails validation first
