@@ -146,6 +146,24 @@ def _ptr(x):
     return ctypes.cast(x, ctypes.c_void_p).value
 
 
+_SCALARS = {"i": ctypes.c_int32, "q": ctypes.c_int64, "N": ctypes.c_size_t, "f": ctypes.c_float, "P": ctypes.c_void_p}
+
+
+def _scalar(code, x):
+    """What a ctypes parameter of this type makes of x, for values that are neither an int nor, for a float, a number."""
+    type_ = _SCALARS[code]
+    if code == "P":
+        return ctypes.cast(x, type_).value
+    if isinstance(x, type_):
+        return x.value
+    try:
+        return type_(x).value
+    except Exception:
+        if not hasattr(x, "_as_parameter_"):
+            raise TypeError("wrong type") from None
+    return _scalar(code, x._as_parameter_)
+
+
 # vs_tree_mask_build(parent, B, T, mask, depth, status=None, stream=None) -> int and so on: parameters as in the header,
 # pointers as _ptr takes them, the trailing optional ones None / 0 by default
 _NATIVE = ("vs_tree_mask_build", "vs_tree_verify_attention", "vs_compress_attention", "vs_tree_accept", "vs_tree_accept_noalloc",
@@ -171,7 +189,7 @@ except ImportError:
         raise
     globals().update({name: _missing(name) for name in _NATIVE})
 else:
-    _native.setup(_load_native, _ptr, ctypes.ArgumentError, AttnDesc, KVDesc)
+    _native.setup(_load_native, _ptr, _scalar, ctypes.byref, ctypes.ArgumentError, AttnDesc, KVDesc)
     globals().update({name: getattr(_native, name) for name in _NATIVE})
 
 

@@ -1,10 +1,12 @@
 // CPython entry points of the calls that a decoding step makes: arguments straight to the C ABI.
 //
-// A step of a small model is bound by what the host spends per call. Through ctypes a call of eleven arguments took
-// 4.1 us (ten attribute tests and data_ptr() calls in Python, then ctypes' own conversions) beside the 2 - 3 us of
-// a kernel launch; here it takes 0.8 us. Accepted arguments, their conversions and defaults are those of the ctypes
-// binding: None, an integer, or anything with data_ptr() (or what binding._ptr makes an address of) for a
-// pointer, integers of any size cut to their parameter's width, ctypes.ArgumentError for what converts to neither. The
+// A step of a small model is bound by what the host spends per call beside the 2 - 3 us of a kernel launch. A call of
+// vs_tree_verify_attention that is refused at once takes, with nine tensors / nine plain addresses, 6.3 / 3.6 us through ctypes (ten
+// attribute tests and data_ptr() calls in Python, then ctypes' own conversions) and 1.3 / 0.3 us here. Accepted arguments,
+// their conversions and defaults are those of the ctypes functions (tests/test_pycall.py compares the two): for a pointer None, an
+// integer, anything with data_ptr(), or what binding._ptr makes an address of; for a scalar a number, a ctypes scalar of the
+// parameter's own type or an object with _as_parameter_ that leads to one, integers of any size cut to the
+// parameter's width; ctypes.ArgumentError for what converts to neither. The
 // interpreter lock is released around the call. The library is not linked: binding.lib() loads it at the first call
 // and hands its addresses over, so that the same module serves any build of it.
 #define PY_SSIZE_T_CLEAN
@@ -18,7 +20,7 @@
 
 namespace {
 
-PyObject *s_data_ptr, *g_load, *g_ptr, *g_error, *g_attn_desc, *g_kv_desc; // setup()
+PyObject *s_data_ptr, *g_load, *g_ptr, *g_scalar, *g_struct, *g_error, *g_attn_desc, *g_kv_desc; // setup()
 
 constexpr int kMaxArgs = 20;
 struct Entry {
@@ -30,19 +32,29 @@ struct Entry {
     PyObject* names[kMaxArgs];
 };
 
-bool argument_error(int i, const char* what) {
-    if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_TypeError)) return false;
-    PyErr_Clear();
-    PyErr_Format(g_error, "argument %d: %s", i + 1, what);
+// whatever was raised becomes an ArgumentError that names the argument
+bool argument_error(int i) {
+    if (!PyErr_ExceptionMatches(PyExc_Exception)) return false;
+    PyObject *type, *value, *trace;
+    PyErr_Fetch(&type, &value, &trace);
+    PyErr_NormalizeException(&type, &value, &trace);
+    PyErr_Format(g_error, "argument %d: %S: %S", i + 1, type, value);
+    Py_XDECREF(type);
+    Py_XDECREF(value);
+    Py_XDECREF(trace);
     return false;
 }
-bool to_integer(PyObject* o, int i, uint64_t& x) {
+bool to_integer(PyObject* o, int i, char code, uint64_t& x) {
     if (PyLong_Check(o)) {
         x = PyLong_AsUnsignedLongLongMask(o);
         return true;
     }
     PyObject* n = PyNumber_Index(o);
-    if (!n) return argument_error(i, "an integer is required");
+    if (!n) { // a ctypes scalar, an object that stands for one, or an error
+        PyErr_Clear();
+        n = PyObject_CallFunction(g_scalar, "CO", (int)code, o);
+        if (!n) return argument_error(i);
+    }
     x = PyLong_AsUnsignedLongLongMask(n);
     Py_DECREF(n);
     return true;
@@ -50,49 +62,73 @@ bool to_integer(PyObject* o, int i, uint64_t& x) {
 bool to_address(PyObject* o, int i, uint64_t& x) {
     x = 0;
     if (o == Py_None) return true;
-    if (PyLong_Check(o)) return to_integer(o, i, x);
-    PyObject* a = PyObject_CallMethodNoArgs(o, s_data_ptr);
-    if (!a) {
+    PyObject* a = nullptr;
+    if (PyLong_Check(o)) {
+        a = o;
+        Py_INCREF(a);
+    } else if (!(a = PyObject_CallMethodNoArgs(o, s_data_ptr))) {
         if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
         PyErr_Clear();
         a = PyObject_CallOneArg(g_ptr, o);
         if (!a) return false;
     }
-    const bool ok = a == Py_None || to_integer(a, i, x);
+    bool ok = a == Py_None;
+    if (!ok && PyLong_Check(a)) {
+        x = PyLong_AsUnsignedLongLongMask(a);
+        ok = true;
+    } else if (!ok) { // data_ptr() gave something else
+        PyObject* n = PyObject_CallFunction(g_scalar, "CO", 'P', a);
+        if (n && n != Py_None) x = PyLong_AsUnsignedLongLongMask(n);
+        ok = n || argument_error(i);
+        Py_XDECREF(n);
+    }
     Py_DECREF(a);
     return ok;
 }
 bool to_struct(PyObject* o, int i, PyObject* type, size_t bytes, uint64_t& x) {
     Py_buffer b;
-    if (!PyObject_TypeCheck(o, (PyTypeObject*)type)) return argument_error(i, "a descriptor is required");
+    if (!PyObject_TypeCheck(o, (PyTypeObject*)type)) {
+        PyObject* n = PyObject_CallOneArg(g_struct, o); // TypeError if it is no ctypes object at all
+        if (!n) return false;
+        Py_DECREF(n);
+        PyErr_Format(g_error, "argument %d: expected %s instance instead of %s", i + 1, ((PyTypeObject*)type)->tp_name, Py_TYPE(o)->tp_name);
+        return false;
+    }
     if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) < 0) return false;
     const bool ok = (size_t)b.len >= bytes;
     x = (uint64_t)(uintptr_t)b.buf; // the caller holds the object for the whole call
     PyBuffer_Release(&b);
-    return ok || argument_error(i, "a descriptor is required");
+    if (!ok) PyErr_Format(g_error, "argument %d: a descriptor of %zu bytes is required", i + 1, bytes);
+    return ok;
 }
 
 bool convert(PyObject* o, int i, int32_t& x) {
     uint64_t v;
-    if (!to_integer(o, i, v)) return false;
+    if (!to_integer(o, i, 'i', v)) return false;
     x = (int32_t)v;
     return true;
 }
 bool convert(PyObject* o, int i, int64_t& x) {
     uint64_t v;
-    if (!to_integer(o, i, v)) return false;
+    if (!to_integer(o, i, 'q', v)) return false;
     x = (int64_t)v;
     return true;
 }
 bool convert(PyObject* o, int i, size_t& x) {
     uint64_t v;
-    if (!to_integer(o, i, v)) return false;
+    if (!to_integer(o, i, 'N', v)) return false;
     x = (size_t)v;
     return true;
 }
 bool convert(PyObject* o, int i, float& x) {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) return argument_error(i, "a number is required");
+    double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) {
+        PyErr_Clear();
+        PyObject* n = PyObject_CallFunction(g_scalar, "CO", 'f', o);
+        if (!n) return argument_error(i);
+        v = PyFloat_AsDouble(n);
+        Py_DECREF(n);
+    }
     x = (float)v;
     return true;
 }
@@ -202,10 +238,11 @@ VS_ENTRY(6, vs_draft_expand)
 VS_ENTRY(7, vs_draft_tree_build)
 VS_ENTRY(8, vs_tree_kv_commit)
 
-// setup(load, ptr, ArgumentError, AttnDesc, KVDesc)
+// setup(load, ptr, scalar, byref, ArgumentError, AttnDesc, KVDesc)
 PyObject* setup(PyObject*, PyObject* args) {
-    if (!PyArg_ParseTuple(args, "OOOO!O!", &g_load, &g_ptr, &g_error, &PyType_Type, &g_attn_desc, &PyType_Type, &g_kv_desc)) return nullptr;
-    for (PyObject* o : {g_load, g_ptr, g_error, g_attn_desc, g_kv_desc}) Py_INCREF(o); // for good
+    if (!PyArg_ParseTuple(args, "OOOOOO!O!", &g_load, &g_ptr, &g_scalar, &g_struct, &g_error, &PyType_Type, &g_attn_desc, &PyType_Type, &g_kv_desc))
+        return nullptr;
+    for (PyObject* o : {g_load, g_ptr, g_scalar, g_struct, g_error, g_attn_desc, g_kv_desc}) Py_INCREF(o); // for good
     Py_RETURN_NONE;
 }
 // bind({name: address})
