@@ -38,6 +38,10 @@ __device__ __forceinline__ float sum_cg(float x) {
     return x;
 }
 
+// x of lane J of every four
+template <int J>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t x) { return dpp<J * 0x55>(x); }
+
 // op over the sixteen lanes (kb, cg) that share j, in every lane
 template <typename Op>
 __device__ __forceinline__ float row_all(float x, Op op) {
@@ -250,6 +254,45 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void attn_f32_kernel(const At
                 for (int m = 0; m < VM; ++m)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) vf[r][m][e] = t0 + 4 * kb + r < n ? vf[r][m][e] : 0.f;
+        }
+        // A value that is not finite must not meet the zero weight of a row that does not see its key. Only tree slots are hidden
+        // from some rows: where one of their tiles holds such a value, the rows that see it get it here and the product a zero.
+        if (t0 + kF32Tile > S) { // uniform
+            f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int m = 0; m < VM; ++m)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z[e] = fmaf(vf[r][m][e], 0.f, z[e]);
+            const float any = (z[0] + z[1]) + (z[2] + z[3]);
+            if (__any(any != any)) {
+                auto infinite = [](float x) { return !(fabsf(x) < INFINITY); }; // or NaN
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int sh = t0 + 4 * kb + r - S;
+                    bool sees[SETS]; // this lane's row
+#pragma unroll
+                    for (int s = 0; s < SETS; ++s) sees[s] = (sh < 0) | ((sh < p.tree_keys) & (((uint32_t)(mask[s] >> (sh & 63)) & 1u) != 0));
+#pragma unroll
+                    for (int m = 0; m < VM; ++m)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const uint32_t raw = __float_as_uint(vf[r][m][e]);
+                            auto channel = [&](int i, uint32_t bits) __attribute__((always_inline)) { // register i holds the channel that lane i of four fetched
+                                const float x = __uint_as_float(bits);
+#pragma unroll
+                                for (int s = 0; s < SETS; ++s)
+                                    if (infinite(x) && sees[s]) acc[s][m][e][i] = fmaf(x, pr[s][r], acc[s][m][e][i]);
+                            };
+                            channel(0, quad_lane<0>(raw));
+                            channel(1, quad_lane<1>(raw));
+                            channel(2, quad_lane<2>(raw));
+                            channel(3, quad_lane<3>(raw));
+                            if (infinite(vf[r][m][e])) vf[r][m][e] = 0.f;
+                        }
+                }
+            }
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)

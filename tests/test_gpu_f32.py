@@ -42,3 +42,34 @@ def test_bad_inputs_are_reported_and_isolated(oracle_mod):
     got = da.run()
     assert list(da.status.cpu().numpy()) == [3, 4, 0]
     gu.check_close(got[2], oracle_mod.tree_attention(inp, threads=4)[2], *TIGHT_F32, what="the good sequence")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,paged", [(1, 4, 1, False), (6, 32, 8, True)])   # four rows per workgroup, eight
+@pytest.mark.parametrize("S", [300, 6, 0])                                        # the tree in two tiles, from a tile's middle on
+def test_non_finite_values_stay_with_the_rows_that_see_them(oracle_mod, d, B, Hq, Hkv, paged, S):
+    """K and V rows of tree slots with Inf and NaN: a node that does not see such a slot is as if it held zeros."""
+    import gpu_util as gu
+    T = 24
+    cfg = gen.Config("f32", B, Hq, Hkv, d, T, 5, 3, 100, 0.5, 1, "f32", prefix=None, prefix_range=(1, 2), paged=paged)
+    inp = gen.attention_inputs(cfg, 812, prefix_len=np.full(B, S, dtype=np.int32))
+    _, mask, _ = oracle_mod.tree_mask(inp.parent[0])
+    slots = [T - 2, T - 9]
+    hides = [i for i in range(T) if not any(int(mask[i]) >> x & 1 for x in slots)]
+    sees = [i for i in range(T) if i not in hides]
+    assert hides and sees
+    for x, k, v in zip(slots, (1.0, np.nan), (np.inf, -np.inf)):
+        at = (0, slice(None), S + x) if not paged else (inp.block_table[0, (S + x) // cfg.block_size], slice(None), (S + x) % cfg.block_size)
+        inp.k_cache[at] *= np.float32(k)
+        inp.v_cache[at + (7,)] = v
+        inp.v_cache[at + (d - 1,)] = np.nan
+    ref = oracle_mod.tree_attention(inp, threads=8)
+    got = gu.DeviceAttn(inp).run()
+    gu.check_close(got[0, hides], ref[0, hides], *TIGHT_F32, what="rows that do not see the slots")
+    assert np.isnan(got[0, sees][..., d - 1]).all() and not np.isfinite(got[0, sees][..., 7]).any()
+    only = [i for i in sees if not int(mask[i]) >> slots[1] & 1]                   # an ordinary key with an infinite value
+    other = [c for c in range(d) if c not in (7, d - 1)]
+    gu.check_close(got[0, only][..., other], ref[0, only][..., other], *TIGHT_F32, what="their other channels")
+    assert (got[0, only][..., 7] == np.inf).all()
+    if B > 1:
+        gu.check_close(got[1:], ref[1:], *TIGHT_F32, what="the other sequences")
