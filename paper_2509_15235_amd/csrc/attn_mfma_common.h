@@ -178,7 +178,8 @@ __device__ __forceinline__ int64_t ml_block(const AttnParams& p, int64_t unit, i
 //   word 1  changes when all have arrived (any initial value)
 // The call before on the same workspace has ended (calls that share one are ordered), so both words are at rest.
 static_assert(kMergeMaxSplits == 32, "bits of the abandoned set");
-constexpr uint64_t kMergeTag = 0xffc3a5ull;           // no partial result or (max, sum) pair looks like this (a NaN)
+constexpr uint64_t kMergeTag = 0xffc3a9ull;           // no partial result or (max, sum) pair looks like this (a NaN)
+static_assert(kMergeTag != kArrivalZero >> 40, "an arrival word that vs_draft_expand left in a shared workspace is no gate");
 constexpr uint64_t kMergeZero = kMergeTag << 40;
 
 struct MergeGate {
