@@ -46,7 +46,8 @@ int32_t check_device() {
 
 namespace {
 
-std::atomic<uint32_t> merge_wait{2000};
+// of this thread's next launches (vs_internal_set_merge_wait)
+thread_local uint32_t merge_wait = 2000;
 
 struct Plan {
     int32_t impl, rpw, waves, row_groups, rows, rows_pad, num_splits, keys_per_split, total_wgs, schedule;
@@ -399,7 +400,7 @@ int32_t accept_chunks(int32_t V) { return (V + kArgmaxChunk - 1) / kArgmaxChunk;
 
 extern "C" {
 
-void vs_internal_set_merge_wait(uint32_t ticks) { merge_wait.store(ticks, std::memory_order_relaxed); }
+void vs_internal_set_merge_wait(uint32_t ticks) { merge_wait = ticks; }
 
 int32_t vs_version(void) { return VS_VERSION; }
 
@@ -540,7 +541,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         char* behind = (char*)p.part_ml + align_up(prow * 2 * sizeof(float));
         if (pl.bal_chunks > 0) p.bal_table = (int32_t*)behind;
         if (merges_inside(desc, pl)) p.gates = (uint64_t*)behind;
-        p.merge_wait = merge_wait.load(std::memory_order_relaxed);
+        p.merge_wait = merge_wait;
     }
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;

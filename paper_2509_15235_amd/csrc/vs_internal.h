@@ -179,7 +179,7 @@ inline int32_t validate_tree_host(const int32_t* parent, int32_t T) {
     return VS_STATUS_OK;
 }
 
-// How long a workgroup waits at a gate before it hands its share over: 20 us. Tests set it to 0.
+// How long a workgroup waits at a gate before it hands its share over, in launches of the calling thread: 20 us. Tests set it to 0.
 extern "C" void vs_internal_set_merge_wait(uint32_t ticks);
 
 int32_t check_device(); // VS_OK when the current device is a gfx950, else VS_ERR_NO_DEVICE (api.hip)
