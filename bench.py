@@ -50,6 +50,15 @@ def parse():
     return ap.parse_args()
 
 
+def kernel_name(vs, plan, auto):
+    """The kernel behind a plan. LOOP in a plan that AUTO made without other knobs: the kernel of rounds, or the one
+    with tiles of the wave's own (one row group, few rows); else the straight loop."""
+    loop = "attn_mfma_resident_kernel (rounds) or attn_mfma_rows_kernel" if auto else "attn_mfma_kernel"
+    k = {vs.VS_SCHED_PIPELINED: "attn_mfma_pipe_kernel", vs.VS_SCHED_BALANCED: "attn_mfma_pipe_kernel (balanced shares)",
+         vs.VS_SCHED_RESIDENT: "attn_mfma_resident_kernel"}.get(plan.schedule, loop)
+    return k + (" + merge of the splits" if plan.combine else "")
+
+
 def other_config_leg(vs, gen, torch, dev, stream, gtorch, name, seed, check, num_splits=0, schedule=0):
     """Attention of one of the other configurations on device-generated data; returns a roofline block.
     C2 / C4: the L layers folded into one launch (contiguous caches); C5: one layer of the ragged batch
@@ -146,11 +155,9 @@ def other_config_leg(vs, gen, torch, dev, stream, gtorch, name, seed, check, num
         blk.update({"achieved": round(tf, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4)})
     else:
         blk.update({"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4)})
-    sched = {vs.VS_SCHED_PIPELINED: "attn_mfma_pipe_kernel", vs.VS_SCHED_BALANCED: "attn_mfma_pipe_kernel (balanced shares)",
-             vs.VS_SCHED_RESIDENT: "attn_mfma_resident_kernel"}.get(plan.schedule, "attn_mfma_kernel")
     blk.update({"traffic": None, "workload": cfg.name, "launch": launch, "us_per_launch": round(ms * 1e3, 2),
                 "tflops": round(tf, 2), "hbm_gbs": round(gbs, 1), "workgroups": plan.workgroups, "num_splits": plan.num_splits,
-                "kernel": sched + (" + merge of the splits" if plan.combine else ""),
+                "kernel": kernel_name(vs, plan, auto=schedule == 0 and num_splits == 0),
                 "layers_per_launch": layers_per_call, "buffer_sets": nsets, "data": "device-generated N(0,1)"})
     del sets
     torch.cuda.empty_cache()
@@ -534,12 +541,8 @@ def main():
     except OSError:
         traffic = {}
         roofline["traffic_source"] = "not measured"
-    def kernel_name(pl):
-        k = {vs.VS_SCHED_PIPELINED: "attn_mfma_pipe_kernel", vs.VS_SCHED_RESIDENT: "attn_mfma_resident_kernel"}.get(
-            pl.schedule, "attn_mfma_kernel")
-        return k + (" + merge of the splits" if pl.combine else "")
 
-    roofline.update({"kernel": kernel_name(planL),
+    roofline.update({"kernel": kernel_name(vs, planL, auto=args.folded_splits == 0),
                      "launch": f"B={L} proxy: the step's {L} layers folded into one launch as independent batch entries "
                                "(same per-layer shape; layers of a real model are sequentially dependent, so the timed "
                                "step issues `per_layer_call` instead)",
@@ -550,7 +553,7 @@ def main():
                      "frac_of_hbm_peak": round(bytes_layer * L / (ms_folded * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)})
     per_layer = roof(ms_single, 1)
     per_layer.update({"launch": "one layer, B=1: the call the timed step issues once per layer", "us_per_launch": round(ms_single * 1e3, 2),
-                      "workgroups": plan1.workgroups, "num_splits": plan1.num_splits, "kernel": kernel_name(plan1),
+                      "workgroups": plan1.workgroups, "num_splits": plan1.num_splits, "kernel": kernel_name(vs, plan1, auto=args.num_splits == 0),
                       "algorithmic_bytes": int(bytes_layer), "workspace_bytes": int(vs.vs_attention_workspace_bytes(desc1))})
     per_layer["traffic"] = traffic.get(args.config, {}).get("per_layer_call_bytes")
     per_layer["traffic_source"] = roofline["traffic_source"]

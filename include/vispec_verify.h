@@ -82,7 +82,10 @@ typedef enum vs_dtype { VS_BF16 = 0, VS_F32 = 1 } vs_dtype;
 typedef enum vs_attn_impl { VS_IMPL_AUTO = 0, VS_IMPL_GENERIC = 1, VS_IMPL_MFMA = 2 } vs_attn_impl;
 
 /* How the MFMA kernels are scheduled. LOOP streams 64-key tiles through LDS and runs a tile's
- * three stages (scores, softmax, output update) back to back; PIPELINED overlaps the matrix-core
+ * three stages (scores, softmax, output update) back to back (a plan that AUTO made reports LOOP for all
+ * its kernels whose workgroups walk the keys step by step without that overlap: also the one with key tiles of
+ * every wave's own, for few query rows, and the one that runs a split in rounds of 128 keys. Only AUTO without
+ * any other knob takes those two; a descriptor that names LOOP gets the straight loop); PIPELINED overlaps the matrix-core
  * work of the neighbouring tiles with the current tile's softmax (launches with many units);
  * RESIDENT keeps a split's whole key range (at most 192 keys) in LDS and splits the
  * keys once more among the waves of a workgroup (latency-bound launches with few units);
@@ -176,7 +179,7 @@ typedef struct vs_attn_plan {
     int32_t rows_per_wave;   /* 32-row blocks per wave (MFMA path) */
     int32_t workgroups;      /* main kernel grid size */
     int32_t combine;         /* 1 if partial results of key splits are merged (by the kernel itself or one behind it) */
-    int32_t schedule;        /* VS_SCHED_LOOP, _PIPELINED, _RESIDENT or _BALANCED (MFMA path), else 0 */
+    int32_t schedule;        /* VS_SCHED_LOOP (see vs_attn_schedule), _PIPELINED, _RESIDENT or _BALANCED (MFMA path), else 0 */
 } vs_attn_plan;
 
 int32_t vs_attention_plan(const vs_attn_desc* desc, vs_attn_plan* plan); /* both host */
@@ -333,7 +336,7 @@ int32_t vs_tree_accept_sample(const float* logits, int64_t ld_logits, int32_t V,
  *                 index ascending), listed in ascending candidate index
  *   next_cum      [B,min(K,F*K)] fp32 out: their scores (the next step's cum_in)
  *   workspace     at least vs_draft_expand_workspace_bytes(B,F,V,K) bytes, 256-byte aligned
- * Tokens are exact; scores are fp32 (log-sum-exp over 4096-entry chunks), so two candidates
+ * Tokens are exact; scores are fp32 (log-sum-exp over 8192-entry chunks), so two candidates
  * whose exact scores differ by less than ~1e-5 may swap places at the cut.
  *
  * vs_draft_tree_build, the final selection over the first M candidates (1 <= M <= 2048,

@@ -137,29 +137,25 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     const int nrb = pl.rows_pad / kRowBlock;
     const int tiles = ((int64_t)d->max_prefix_len + (tree ? d->T : 0) + kIterKeys - 1) / kIterKeys;
     const int units0 = d->B * d->Hkv;
-    // Launch shape, from measurements on MI355X (C2..C5-shaped inputs):
-    //  * few units (one layer of one sequence): latency-bound; straight-loop kernel, one
-    //    row block per wave, at most four waves, more row groups and about 1.5 workgroups
-    //    per CU;
-    //  * many units: the software-pipelined kernel with one row block per wave, the rows
-    //    split over row groups of eight (or four) waves, and key splits only when units x
-    //    row groups leave CUs empty. No partial results when that alone fills the machine.
-    //  * a caller who fixes rows_per_wave = 2 or a wave count the pipelined kernel does not
-    //    have gets the straight loop: one row block per wave unless told otherwise, up to four
-    //    waves for small launches and eight for large ones.
+    // Which kernel: the first that applies (the figures stand at each predicate; a "unit" is a (sequence, KV head)).
+    //  * one row block, and some launches of two: key tiles of the wave's own (own_ok)
+    //  * long batches whose sequences may differ in length: balanced shares (balanced_ok, bal_capped, rnd_fills)
+    //  * short sequences and, below twelve units, up to 2048 keys: a split's keys resident in LDS (resident_ok)
+    //  * up to four row blocks, or few units: splits of any length in rounds of 128 keys (rounds_ok)
+    //  * twelve units and more: the software-pipelined kernel, one row block per wave, the rows split over row groups of
+    //    eight (or four) waves, and key splits only when units x row groups leave CUs empty
+    //  * the straight loop: AUTO without other knobs reaches it only with fewer than twelve units of more than 256 workgroups' rows
+    // A caller's schedule is taken as it is. With other knobs set AUTO leaves out own tiles and rounds; rows_per_wave = 2 or a wave
+    // count that the pipelined kernel does not have mean the straight loop: one row block per wave unless told otherwise,
+    // up to four waves for small launches and eight for large ones.
     const bool big = units0 >= kManyUnits;
     int rpw = d->rows_per_wave, waves = d->waves_per_group, splits = d->num_splits;
     const bool pipe_ok = (rpw == 0 || rpw == 1) && (waves == 0 || waves == 4 || waves == 8);
     const bool many = units0 >= 12; // enough (sequence, KV head) units for the pipelined kernel, see below
-    // few units, several row blocks, a short sequence (at most 2048 keys) and no caller's
-    // choice that it cannot honour: the LDS-resident kernel, whose second split of the keys
-    // among the waves shortens each workgroup's loop - as long as all its workgroups (up to 96 KB
-    // of LDS each: one per CU) run at once. Splits of two 64-key tiles when that fits, else
-    // three. Measured on C3-sized layers replayed from a HIP graph over 400 MB of K/V (every
-    // layer cold in the caches), per layer: 14 splits of 128 keys 15.8 us, 10 splits of 192 keys
-    // 16.7 us; the streaming loop with the same splits 15.7 / 16.9 us. With two sequences (more
-    // workgroups than CUs) it loses to the loop, and for 5000+ keys its 192-key limit forces too
-    // many partial results.
+    // Below twelve units the LDS-resident kernel for up to 2048 keys, as long as all its workgroups (up to 96 KB of LDS each: one
+    // per CU) run at once: splits of two 64-key tiles when that fits, else three (28 / 4 heads, 60 nodes, 1696 keys, every
+    // layer cold in the caches: 14 splits of 128 keys 15.8 us, 10 of 192 16.7, with a combine kernel behind both). For 5000
+    // keys and more its 192-key limit forces too many partial results.
     const int res_rg = (nrb + 3) / 4;
     // Short sequences: one split where it is at most the kernel's 192 keys, then splits of 64 keys where those find a CU
     // each (with few splits the merge's items queue up in few waves: 1 x 60 nodes, 28 / 4 heads, 400 keys in splits of 128 12.3 us, of
@@ -177,10 +173,8 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     const bool resident_ok = (!many || (res_short && splits <= 0)) && nrb >= 2 && tiles <= 32 && (rpw == 0 || rpw == 1) && (waves == 0 || waves == 8) &&
                              (splits <= 0 || (tiles + splits - 1) / splits <= kResidentMaxKeys / kIterKeys) &&
                              (int64_t)units0 * res_rg * res_splits <= kNumCUs;
-    // The pipelined kernel takes over from twelve units on (three C3 sequences, or one MHA
-    // layer): A/B per call, loop against pipelined, 3 sequences 26.3 / 24.9 us, 4: 28.6 / 26.9,
-    // 6: 34.0 / 29.7, 8: 39.9 / 31.4, 11: 50.9 / 39.9, one C2 (MHA) layer 25.4 / 23.3; below
-    // that the loop wins (one C3 sequence 19.1 / 22.5, two 21.7 / 23.3).
+    // Twelve units: from there on the pipelined kernel beats the straight loop (us per call, loop / pipelined, 28 / 4 heads, 60 nodes,
+    // 1696 keys: 2 sequences 21.7 / 23.3, 3: 26.3 / 24.9, 4: 28.6 / 26.9, 8: 39.9 / 31.4, 11: 50.9 / 39.9).
     // Balanced shares instead of equal splits per sequence: for batches whose sequences may differ in
     // length (the host only knows the longest allowed one). As many workgroups as the CUs hold at once
     // (one of eight waves, two of four). Taken when the launch would need key splits to fill those
@@ -189,9 +183,9 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // be 32 steps of 64 keys if every sequence had the longest allowed length (reading the lengths and
     // cutting the shares costs each kernel a dependent load and a few microseconds).
     // Paged batches, one layer, planner's other choice / balanced shares, lengths drawn from 1024 .. 8192
-    // unless stated. Qwen-7B heads (28 / 4), 16 sequences: 138 / 118, 135 / 107, 138 / 106, 127 / 96 us; all
+    // unless stated. 28 / 4 heads, 16 sequences: 138 / 118, 135 / 107, 138 / 106, 127 / 96 us; all
     // 4600 keys: 93 / 98; all 8000: 150 / 156; 256 .. 2048 keys: 50 / 57; 32 sequences: 242 / 192;
-    // 40: 279 / 226, all 3000 keys 202 / 162; 64: 418 / 340, all 3000 keys 227 / 237. LLaVA-7B heads (32 / 32),
+    // 40: 279 / 226, all 3000 keys 202 / 162; 64: 418 / 340, all 3000 keys 227 / 237. 32 / 32 heads,
     // 4 sequences: 120 / 77; 8: 237 / 168; 12: 262 / 201; 24: 422 / 361; 32: 518 / 487, and 32 folded layers
     // of 3136 keys 308 / 334.
     // A launch that is one full round of whole sequences is left alone: unequal lengths would gain
