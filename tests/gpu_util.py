@@ -164,8 +164,8 @@ class DeviceDraft:
         self.par = torch.full((B, capacity), -7, device="cuda", dtype=torch.int32)
         self.M = 0
 
-    def expand(self, logits: np.ndarray, cum_in, frontier_cand, ld=None, offset_elems=0):
-        """logits [B,F,V] numpy; cum_in / frontier_cand device tensors [B,F] or None.
+    def expand(self, logits: np.ndarray, cum_in, frontier_cand, ld=None, offset_elems=0, garbage=False):
+        """logits [B,F,V] numpy; cum_in / frontier_cand device tensors [B,F] or None; garbage: random bytes in the workspace.
         Returns device tensors (next_frontier_cand [B,keep], next_cum [B,keep])."""
         B, F, V = logits.shape
         K = self.K
@@ -179,6 +179,8 @@ class DeviceDraft:
         nbytes = vs.vs_draft_expand_workspace_bytes(B, F, V, K)
         assert nbytes > 0
         ws = torch.empty(nbytes, device="cuda", dtype=torch.uint8)
+        if garbage:
+            ws.random_(0, 256)
         rc = vs.vs_draft_expand(view.data_ptr(), ld, V, cum_in, frontier_cand, B, F, K, self.M, self.cap, self.tok,
                                 self.score, self.par, nf, nc, ws, nbytes, stream_ptr())
         assert rc == 0, vs.vs_strerror(rc)

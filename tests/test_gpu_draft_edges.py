@@ -26,17 +26,11 @@ def test_chunk_edges(gu, oracle_mod, V, K, D, N, ld, offset):
 
 def test_largest_frontier(gu, oracle_mod):
     """64 rows of 16 children: 1024 candidates in one step, on a workspace full of garbage."""
-    import torch
     F, K, V = 64, 16, 700
     dd = gu.DeviceDraft(2, K, F * K)
     logits = np.stack([gen.draft_logits(31, b, 1, F, V) for b in range(2)])
     cum = -np.arange(F, dtype=np.float32)[None].repeat(2, 0) * 0.01
-    keep = torch.empty
-    torch.empty = lambda *a, **k: keep(*a, **k).random_(0, 256) if k.get("dtype") == torch.uint8 else keep(*a, **k)
-    try:
-        nf, nc = dd.expand(logits, gu.dev(cum), gu.dev(np.arange(2 * F, dtype=np.int32).reshape(2, F)))
-    finally:
-        torch.empty = keep
+    nf, nc = dd.expand(logits, gu.dev(cum), gu.dev(np.arange(2 * F, dtype=np.int32).reshape(2, F)), garbage=True)
     for b in range(2):
         rc, tok, sc, fr, gap = oracle_mod.draft_expand_seq(logits[b], cum[b], K)
         assert rc == 0
