@@ -101,15 +101,17 @@ def test_merge_words_between_calls(oracle_mod):
                     gu.check_close(got[b], ref[b], *TIGHT_SHORT, what=f"pass {rep} sequence {b}")
 
 
-@pytest.mark.parametrize("kw", [{}, dict(schedule=vs.VS_SCHED_RESIDENT), dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=8),
-                                dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=4)])
+@pytest.mark.parametrize("kw", [{}, dict(schedule=vs.VS_SCHED_RESIDENT), dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=8, num_splits=10),
+                                dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=4, num_splits=7)])
 def test_shares_handed_over(oracle_mod, kw):
     """Nobody waits at the gate: every workgroup but a row group's last one leaves its share of the merge to it."""
     import gpu_util as gu
     cfg = gen.Config("handover", 2, 28, 4, 128, 60, 6, 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2), paged=False)
     inp = gen.attention_inputs(cfg, 970, prefix_len=np.array([1100, 421], dtype=np.int32))
     da = gu.DeviceAttn(inp, **kw)
-    assert da.plan().num_splits > 1 and da.plan().combine == 1
+    pl = da.plan()
+    assert pl.num_splits > 1 and pl.combine == 1
+    assert da.ws_bytes == 2 * 4 * pl.num_splits * 448 * (128 * 2 + 8) + 2 * 4 * pl.row_groups * 256   # partial results and gates
     want = da.run()
     try:
         vs.lib().vs_internal_set_merge_wait(0)
