@@ -501,7 +501,7 @@ def main():
     del cal_dst
 
     # ---------------------------------------------------------------- the other configurations' attention
-    # Shapes of the benchmark's other configurations on device-generated N(0,1) data (their parity is
+    # Shapes of the other configurations on device-generated N(0,1) data (their parity is
     # the GPU tests' business): C2 and C4 with their layers folded into one launch like `roofline`,
     # C5 as it is (16 ragged sequences over a paged cache need no folding: one layer is one launch).
     others = {}
