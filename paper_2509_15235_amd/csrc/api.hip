@@ -357,23 +357,26 @@ size_t partial_rows(const vs_attn_desc* d, const Plan& pl) {
 
 // Splits merged by their own workgroups instead of a combine kernel: they wait for each other, so only where
 // all of them run at once (given an idle device; with a busy one the wait is bounded). Few splits of many rows stay with
-// the combine kernel, which spreads them over the whole chip: from five items for a wave (merge_splits) on
+// the combine kernel, which spreads them over the whole chip: with six items for a wave (merge_splits)
 // 2 splits of 192 rows took 19.2 us against 18.0.
 // A workgroup of the pipelined kernel has up to eight row blocks and often few splits, so that its waves have several items, more
 // than they take at once; the merge then only pays where most of the chip takes part in it. us per call, inside / combine
 // kernel (sequences x nodes, keys, splits x workgroups; 28 / 4 heads of 128 channels unless stated):
 //   from seven splits on: 3 x 35, 2019, 9 x 108 19.7 / 20.9; 3 x 27, 4036, 16 x 192 19.7 / 23.0; 3 x 60, 3136, 10 x 240 22.4 / 25.5;
 //     32 / 8 heads of 64, 2 x 35, 1770, 8 x 128 13.9 / 15.9
-//   fewer, most of the chip: 5 x 60, 1000, 5 x 200 21.6 / 21.8; 8 x 35, 1247, 6 x 192 20.9 / 21.6; 8 x 60, 3136, 4 x 256 36.5 / 40.8;
-//     12 x 56, 58 .. 466, 32 / 8 heads of 64, 2 x 192 17.3 / 18.9; but 8 x 39, 85 .. 684, 3 x 192 21.9 / 21.1
-//   fewer of both: 3 x 60, 1000, 5 x 120 20.3 / 19.5; 4 x 60, 1000, 5 x 160 20.8 / 20.1; 3 x 60, 1400, 6 x 144 20.4 / 20.1; 4 x 53, 502,
-//     3 x 96 19.8 / 18.0; 32 / 8 heads of 64, 2 x 52, 527, 3 x 48 16.0 / 15.0
+//   fewer, on 11/16 of the CUs: 9 x 22, 148 .. 1186, 5 x 180 20.2 / 21.2; 5 x 60, 1000, 5 x 200 21.6 / 21.8; 8 x 35, 1247, 6 x 192 20.9 / 21.6; 8 x 60,
+//     3136, 4 x 256 36.5 / 40.8; 9 x 36 (40 / 8 heads), 2166, 3 x 216 34.1 / 37.2; but 8 x 39, 85 .. 684, 3 x 192 21.9 / 21.1;
+//     on fewer: 3 x 60, 1000, 5 x 120 20.3 / 19.5; 4 x 60, 1000, 5 x 160 20.8 / 20.1; 3 x 60, 1400, 6 x 144 20.4 / 20.1; 5 x 46 (28 / 4
+//     heads of 64), 919, 4 x 160 17.1 / 16.6
+//   two and three with at most three items already on 9/16 (heads of 64): 11 x 48 (32 / 8), 1744, 2 x 176 26.8 / 27.8; 6 x 50 (32 / 8),
+//     261 .. 523, 3 x 144 14.9 / 15.3; on fewer: 5 x 44 (28 / 4), 650, 3 x 120 16.1 / 15.6; 2 x 52 (32 / 8), 527, 3 x 48 16.0 / 15.0
 bool merges_inside(const vs_attn_desc* d, const Plan& pl) {
     const int blocks = pl.rows_pad / kRowBlock, in_group = (blocks + pl.row_groups - 1) / pl.row_groups;
-    const bool pipelined = pl.schedule == VS_SCHED_PIPELINED && (pl.num_splits >= 7 || pl.total_wgs >= kNumCUs * 3 / 4);
+    const int items = in_group * (d->d / 8), takers = pl.num_splits * pl.waves;
+    const bool few_items = pl.num_splits <= 3 && items <= 3 * takers;
+    const bool pipelined = pl.schedule == VS_SCHED_PIPELINED && (pl.num_splits >= 7 || pl.total_wgs >= kNumCUs * (few_items ? 9 : 11) / 16);
     return (pl.schedule == VS_SCHED_RESIDENT || pipelined || pl.rounds || pl.own_tiles) && pl.num_splits > 1 &&
-           pl.num_splits <= kMergeMaxSplits && pl.total_wgs <= kNumCUs &&
-           in_group * (d->d / 8) <= 4 * pl.num_splits * pl.waves &&
+           pl.num_splits <= kMergeMaxSplits && pl.total_wgs <= kNumCUs && items <= 4 * takers &&
            pl.rows_pad <= (1 << 16); // offsets inside a row group's partial results are 32 bits wide
 }
 

@@ -208,17 +208,22 @@ def test_up_to_256_keys_of_many_units_are_one_split(Hq, Hkv, d, B, T):
         assert vs.vs_compress_attention_workspace_bytes(desc) == 0
 
 
-@pytest.mark.parametrize("B,T,S,wgs,gates", [(3, 60, 1000, 120, 0), (4, 60, 1000, 160, 0), (8, 60, 700, 192, 0), (5, 60, 1000, 200, 1),
-                                             (3, 60, 2000, 216, 1), (8, 60, 3136, 256, 1), (3, 35, 2019, 108, 1), (3, 31, 3000, 144, 1)])
-def test_what_merges_the_splits_of_the_pipelined_kernel(B, T, S, wgs, gates):
+@pytest.mark.parametrize("heads,B,T,S,wgs,gates", [
+    ((28, 4, 128), 3, 60, 1000, 120, 0), ((28, 4, 128), 4, 60, 1000, 160, 0), ((28, 4, 128), 5, 60, 1000, 200, 1),        # four to six splits
+    ((28, 4, 128), 8, 60, 3136, 256, 1), ((28, 4, 128), 9, 22, 1186, 180, 1),
+    ((28, 4, 128), 3, 35, 2019, 108, 1), ((28, 4, 128), 3, 31, 3000, 144, 1), ((28, 4, 128), 3, 60, 2000, 216, 1),        # more
+    ((28, 4, 128), 8, 60, 700, 192, 0), ((28, 4, 128), 8, 39, 684, 192, 1), ((28, 4, 64), 5, 44, 650, 120, 0),            # three
+    ((32, 8, 64), 6, 50, 523, 144, 1), ((32, 8, 64), 11, 48, 1744, 176, 1)])                                             # ..., two
+def test_what_merges_the_splits_of_the_pipelined_kernel(heads, B, T, S, wgs, gates):
     """The splits' own workgroups (their gates take workspace) where they have few items each and are many splits or most
     of the chip, else the combine kernel."""
+    Hq, Hkv, d = heads
     cap = S + 64
-    desc = _desc(B=B, T=T, max_prefix_len=S, capacity=cap, stride_seq=4 * cap * 128, stride_head=cap * 128)
+    desc = _desc(B=B, T=T, Hq=Hq, Hkv=Hkv, d=d, max_prefix_len=S, capacity=cap, stride_seq=Hkv * cap * d, stride_head=cap * d, stride_tok=d)
     rc, plan = vs.vs_attention_plan(desc)
     assert rc == 0 and plan.schedule == vs.VS_SCHED_PIPELINED and plan.workgroups == wgs and plan.combine == 1
-    partials = B * 4 * plan.num_splits * (-(-7 * T // 32) * 32) * (128 * 2 + 8)
-    assert vs.vs_attention_workspace_bytes(desc) == partials + gates * B * 4 * plan.row_groups * 32 * 8
+    partials = B * Hkv * plan.num_splits * (-(-Hq // Hkv * T // 32) * 32) * (d * 2 + 8)
+    assert vs.vs_attention_workspace_bytes(desc) == partials + gates * B * Hkv * plan.row_groups * 32 * 8
 
 
 @pytest.mark.parametrize("B,T,schedule,splits", [(24, 18, vs.VS_SCHED_LOOP, 2), (32, 18, vs.VS_SCHED_LOOP, 2), (33, 18, vs.VS_SCHED_BALANCED, 64),
