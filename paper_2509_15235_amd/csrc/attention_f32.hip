@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void attn_f32_kernel(const At
 #pragma unroll
                     for (int e = 0; e < 4; ++e) z[e] = fmaf(vf[r][m][e], 0.f, z[e]);
             const float any = (z[0] + z[1]) + (z[2] + z[3]);
-            if (__any(any != any)) {
+            if (__builtin_expect(__any(any != any), 0)) {
                 auto infinite = [](float x) { return !(fabsf(x) < INFINITY); }; // or NaN
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
