@@ -265,6 +265,37 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
         pl.total_wgs = units0 * pl.row_groups * pl.num_splits;
         return pl;
     }
+    if (pl.schedule == VS_SCHED_LOOP && own_ok && units0 <= kNumCUs) {
+        // ... in the resident kernel where the splits fit it and all run at once: one split of up to 256 keys, or (where own
+        // tiles would be split too) splits of 64, 128 or 192. us per call, own tiles / resident, 28 / 4 heads unless stated:
+        //   one split: 4 x 3 nodes, 60 keys 6.1 / 4.9, 150 keys 6.6 / 6.2; 4 x 8 nodes (two row blocks), 60 keys 8.4 / 6.0, 150 keys 9.1 / 7.2
+        //   one row block, split: 1 x 3, 600 keys 9.0 in three / 7.5 in ten of 64; 4 x 3, 1200 10.4 / 9.0 in ten of 128;
+        //     16 x 3, 600 11.4 / 10.4 in four of 192; 32 / 8 heads of 64, 4 x 6, 600 8.3 / 7.4 in five of 128
+        // From seventeen splits on a merge takes a second trip to memory (0.55 us); 128 keys a split cost 0.2 us over 64, 192 0.7.
+        // (Own tiles keep one row block over 256 keys, a tile for every wave: paged 6.6 / 6.9; and splits of 192 beyond sixteen: 7 x 3
+        // nodes, 8 / 2 heads, 3152 keys 11.5 / 11.7.)
+        int tps = tiles <= 3 || (tiles == 4 && nrb == 2) ? tiles : 0;
+        float best = INFINITY;
+        for (int t = 1; t <= 3 && tiles > 8; ++t) {
+            const int n = (tiles + t - 1) / t;
+            const float cost = (t == 1 ? 0.f : t == 2 ? 0.2f : 0.7f) + (n > 16 ? 0.55f : 0.f);
+            if (n <= (t == 3 ? 16 : kMergeMaxSplits) && units0 * n <= kNumCUs && cost < best) {
+                best = cost;
+                tps = t;
+            }
+        }
+        if (tps > 0) {
+            pl.rounds = 1;
+            pl.rpw = 1;
+            pl.waves = 8;
+            pl.res_rb = nrb;
+            pl.row_groups = 1;
+            pl.keys_per_split = tps * kIterKeys;
+            pl.num_splits = (tiles + tps - 1) / tps;
+            pl.total_wgs = units0 * pl.num_splits;
+            return pl;
+        }
+    }
     if (pl.schedule == VS_SCHED_LOOP && own_ok) {
         pl.own_tiles = 1;
         pl.rpw = 1;
@@ -499,6 +530,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.d = desc->d;
     p.group = desc->Hq / desc->Hkv;
     p.inv_group = 1.f / (float)p.group;
+    p.node_stride = (int64_t)(desc->Hq - p.group) * desc->d;
     p.rows = pl.rows;
     p.rows_pad = pl.rows_pad;
     p.max_prefix_len = desc->max_prefix_len;
@@ -520,6 +552,11 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.row_groups = pl.row_groups;
     p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.res_rb ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
     p.total_wgs = pl.total_wgs;
+    if (pl.num_splits > 0 && pl.row_groups > 0) {
+        p.by_splits = fast_div_by(pl.num_splits);
+        p.by_groups = fast_div_by(pl.row_groups);
+        p.by_heads = fast_div_by(desc->Hkv);
+    }
     p.bal_chunks = pl.bal_chunks;
     // A launch of more whole sequences than run at once hands out the longest first (a lane per sequence), unless even the longest is
     // so short that the wait for all lengths costs more than it brings. us per call, longest first / in order:

@@ -672,6 +672,10 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     if ((n & 1) == 0) pv(sV[(n - 1) & 3], pb);
 
     // ---- epilogue: lane (col, half) holds, for row `col`, channels db*32 + 8*(r/4) + 4*half + r%4
+    // (what depends on the lane alone is worked out again: kept over the loop it takes registers)
+    int tid_end = threadIdx.x;
+    asm volatile("" : "+v"(tid_end));
+    const int lane = tid_end & 63, half = lane >> 5, col = lane & 31;
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb) {
         const int r_local = row_base + rb * kRowBlock + col;
@@ -729,16 +733,12 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
             b = sequence_by_rank(p, k / p.Hkv, lane);
             kvh = k % p.Hkv;
         } else {
-            // workgroup id -> (sequence, KV head, row group, split), XCD-aware (see attention_mfma.hip)
-            const int per_xcd = (p.total_wgs + 7) >> 3;
-            const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-            if (v >= p.total_wgs) return;
-            split = v % p.num_splits; // splits fastest, see attention_mfma.hip
-            int rest = v / p.num_splits;
-            rg = rest % p.row_groups;
-            rest /= p.row_groups;
-            kvh = rest % p.Hkv;
-            b = rest / p.Hkv;
+            const WorkItem at = work_item(p);
+            if (at.none) return;
+            b = at.b;
+            kvh = at.kvh;
+            rg = at.rg;
+            split = at.split;
         }
         // the host keeps every split's first key below max_prefix_len + tree_keys, hence inside the cache
         run_piece(b, kvh, rg, split * p.keys_per_split, p.keys_per_split, split, p.num_splits == 1);

@@ -1,26 +1,22 @@
-// Tree-masked attention for small launches (one layer of one sequence): the whole key range
-// of a split is resident in LDS and the keys are split once more inside the workgroup.
+// Tree-masked attention for small launches (one layer of one sequence, short sequences): the whole key range of a
+// split (at most 192 keys, 256 with one or two row blocks) is resident in LDS, and the workgroup's waves share first the keys and then the channels.
 //
-// Math and MFMA layouts are those of attention_mfma.hip (paper Eq. 1 with a softmax scale over
-// the prefix plus the ancestor-or-self tree slots, Section 3.1): S^T = K . Q^T with
-// v_mfma_f32_32x32x16_bf16, a lane holds 16 keys of ONE query row, the probabilities are the
-// B operand of O^T += V^T . P^T, V is transposed by ds_read_b64_tr_b16 on its way out of LDS.
+// Math and MFMA layouts are those of attention_mfma.hip (paper Eq. 1 with a softmax scale over the prefix plus the
+// ancestor-or-self tree slots, Section 3.1): S^T = K . Q^T with v_mfma_f32_32x32x16_bf16, a lane holds 16 keys of
+// ONE query row, the probabilities are the B operand of O^T += V^T . P^T, V is transposed by ds_read_b64_tr_b16 on its
+// way out of LDS.
 //
-// Why another schedule. A launch with few (sequence, KV head) units is latency-bound: with one
-// wave per SIMD the streaming kernel spends 2 us per 64-key iteration of which the matrix cores
-// work 0.4 us - the rest is a single wave issuing its tile copy, LDS writes, barrier and
-// softmax one dependent instruction after the other. Here a workgroup of eight waves owns
-// NRB row blocks x KQ = 8 / NRB key parts of a split of NT 32-key tiles (at most 192 keys,
-// 96 KB). Every load of the split is issued at once, before anything is waited for, ordered by
-// stage: stage j holds the j-th tile of every key part. As soon as a stage has arrived it goes
-// into LDS (one barrier) and every wave runs that tile for its row block while the later stages
-// are still on their way (wall-clock stamps of the earlier form - all loads, one barrier, then
-// all tiles - showed 3.4 us until the data was there, 1.5 us to put it into LDS and 2.2 - 3.4 us
-// of tiles, one after the other). Tiles never share an LDS slot, so one barrier per stage is all
-// the synchronisation there is; two waves per SIMD cover each other's stalls; the key parts are
-// merged through LDS (log-sum-exp, like the combine kernel does for the splits). Split partials
-// and final rows leave as in the streaming kernels, so the combine kernel and the workspace
-// layout are shared.
+// What bounds it: latency. Every wave runs its instructions once, one after the other, at 8 to 10 cycles each (a
+// dependent vector instruction 8.5, a scalar one 8.4, an independent vector one 5.5, instructions fetched for the first
+// time 2 more), so 250 of them are a microsecond; the matrix cores work for 0.3 us of ten.
+// Hence: eight waves = NRB row blocks x KQ key parts. A wave scores its row block against its part of the keys and writes
+// the probabilities, relative to the part's own maximum, to LDS as ready-made operands (1 KB per 16 keys, read back
+// by lane); then it multiplies ALL keys with its share of the channels, part by part. Exchanging probabilities takes
+// a third of the instructions of exchanging accumulators (a form that did: 0.8 us to hand them over, 1.0 to add
+// them up and store). Keys are requested before the queries, values last: they arrive while the scores are
+// worked out. What can be had without the sequence's length is requested before it arrives.
+// (One reference for all parts would save the weights at the end, but a probability of 1 is exact in bf16, and the
+// largest of every part being so is worth 2 - 4 % of the error.)
 #include <type_traits>
 
 #include "attn_mfma_common.h"
@@ -30,39 +26,38 @@ namespace vs {
 namespace {
 
 constexpr int kResWaves = 8;
-constexpr int kResMaxTiles = kResidentMaxKeys / kTileKeys; // 32-key tiles of one split
 
-template <int D, int NRB, int NT, bool STREAM>
+template <int D, int NRB, int NT, bool PAGED>
 __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(const AttnParams p) {
     constexpr int KS = D / 16;          // k-steps of the S^T product
     constexpr int DB = D / 32;          // 32-channel blocks of the output
     constexpr int KQ = kResWaves / NRB; // key parts inside the workgroup
-    constexpr int PPM = (NT + KQ - 1) / KQ; // tiles per key part = stages
+    constexpr int PPM = (NT + KQ - 1) / KQ; // tiles per key part: j * KQ + part
+    constexpr int OWN = KQ < DB ? KQ : DB;  // waves of a row block that have channels
+    constexpr int DBW = DB / OWN;           // their channel blocks each
     constexpr int SUB = kTileKeys * D;  // elements per 32-key tile of K (or V)
-    constexpr int BPS = SUB * 2 / 1024; // 1 KB copy blocks per tile
     constexpr int LPR = D / 8;          // lanes (16-byte chunks) per row
     constexpr int RPI = 64 / LPR;       // rows per load instruction
-    constexpr int SPW = (KQ * BPS + kResWaves - 1) / kResWaves; // copy blocks per wave, stage and tensor
-    constexpr int TILE_BYTES = 2 * NT * SUB * 2;
-    constexpr int MERGE_BYTES = kResWaves * (DB * 1024 + 128) * 4; // every wave's exchange area: accumulators, max, sum
-    constexpr int Q_BYTES = NRB * kRowBlock * D * 2;
-    // the queries lie behind the tiles: where a second round's tiles go when they have been read (stages of round 0
-    // end in barriers, so with two of them nobody can still be reading)
-    constexpr int KEEP_BYTES = !STREAM ? TILE_BYTES + Q_BYTES : (PPM >= 2 && Q_BYTES <= TILE_BYTES ? 2 * TILE_BYTES : 2 * TILE_BYTES + Q_BYTES);
-    constexpr int Q_AT = STREAM && PPM == 1 ? 2 * TILE_BYTES : TILE_BYTES;
-    constexpr int SMEM_ELEMS = (KEEP_BYTES > MERGE_BYTES ? KEEP_BYTES : MERGE_BYTES) / 2;
-    static_assert(NT >= 1 && NT <= kResMaxTiles, "a round holds at most kResidentMaxKeys keys");
-    static_assert(SMEM_ELEMS * 2 + 512 <= kLdsBytesPerCU, "LDS");
+    constexpr int RPB = RPI * kResWaves; // rows that one load instruction of every wave fetches
+    constexpr int NB = NT * kTileKeys / RPB; // such loads per tensor
+    constexpr int P_ELEMS = NRB * NT * 1024;  // probabilities: [row block][tile][16-key half][64 lanes][8]
+    constexpr int Q_AT = 2 * NT * SUB, Q_ELEMS = NRB * kRowBlock * D;
+    constexpr bool P_OVER_K = (Q_AT + Q_ELEMS + P_ELEMS) * 2 + 8192 > kLdsBytesPerCU; // 192 keys, four row blocks of 128 channels
+    constexpr int P_AT = P_OVER_K ? 0 : Q_AT + Q_ELEMS;
+    constexpr int SMEM_ELEMS = Q_AT + Q_ELEMS + (P_OVER_K ? 0 : P_ELEMS);
+    static_assert(NT * kTileKeys <= resident_max_keys(NRB) && NB * RPB == NT * kTileKeys, "keys of a split");
+    static_assert(DB % OWN == 0 && (!P_OVER_K || P_ELEMS <= NT * SUB) && SMEM_ELEMS * 2 + 8192 <= kLdsBytesPerCU, "LDS");
 
-    // tiles of a round: K[t] at smem + t*SUB, V[t] at smem + (NT + t)*SUB, odd rounds TILE_BYTES further; after the
-    // last tile has been consumed the same memory carries the key parts' results to the merging waves
+    // K[t] at smem + t * SUB, V[t] at smem + (NT + t) * SUB, behind them the queries: row blocks of D-channel rows
     __shared__ __attribute__((aligned(1024))) uint16_t smem[SMEM_ELEMS];
+    __shared__ float s_max[NRB][KQ][kRowBlock], s_sum[NRB][KQ][kRowBlock]; // every part's maxima and sums
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
     __shared__ uint64_t sgen;
     uint16_t* sK = smem;
     uint16_t* sV = smem + NT * SUB;
-    uint16_t* sQ = smem + Q_AT / 2; // queries: row blocks of D-channel rows (see load_q_piece)
+    uint16_t* sQ = smem + Q_AT;
+    uint16_t* sP = smem + P_AT;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -72,233 +67,171 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     const int rbw = wave % NRB; // row block inside the group
     const int kq = wave / NRB;  // key part
 
-    // workgroup id -> (sequence, KV head, row group, split); same XCD-aware remap as the other kernels
-    const int per_xcd = (p.total_wgs + 7) >> 3;
-    const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (v >= p.total_wgs) return;
-    // splits fastest: all key splits of a (sequence, KV head, row group) run on one XCD, the one
-    // that the combine workgroups of those rows are placed on by the same remap (see attention_mfma.hip)
-    const int split = v % p.num_splits;
-    int rest = v / p.num_splits;
-    const int rg = rest % p.row_groups;
-    rest /= p.row_groups;
-    const int kvh = rest % p.Hkv;
-    const int b = rest / p.Hkv;
+    const WorkItem at = work_item(p);
+    if (at.none) return;
+    const int b = at.b, kvh = at.kvh, rg = at.rg, split = at.split;
 
     const int32_t S = p.prefix_len[b]; // requested first, needed last: everything below is issued before it arrives
 
-    // ---- copy the first round's keys and values. Stage j = one tile of every key part (tile j * KQ + kq);
-    // inside a stage, copy block i = (key part i / BPS, rows RPI * (i % BPS) ..) and wave w takes
-    // blocks w, w + 8, ...; one load instruction reads RPI whole rows (1 KB of consecutive memory).
-    // The loads do not wait for the prefix length: they are clamped to the cache (not to the
-    // sequence), and rows that turn out to lie past the sequence's last key are zeroed on their
-    // way into LDS (whatever the cache holds there - NaN included - must not meet a zero
-    // probability in the V product). A block-table entry outside the pool reads block 0. Chunk c
-    // of tile row r lands where the fragment reads expect it (same placement as the streaming
-    // kernel):
-    //   K: ((r/16)*DB + c/4) * 1024 + (c%4) * 256 + ((r%16) ^ 4*(c%4)) * 16
-    //   V: ((r/16)*DB + c/4) * 1024 + (4*(r%16) + c%4) * 16
-    // (No branch around a block's loads or stores: a conditional assignment of the staging
-    // array makes the compiler spill the whole array at every branch. Slots of tiles past the
-    // split's last one receive zeros and are never read.)
+    // ---- request the split's keys. Load u of wave w fetches rows u * RPB + w * RPI .. + RPI - 1 of the split, 1 KB of
+    // consecutive memory. The loads do not wait for the prefix length: they are bounded by the cache (not by the
+    // sequence). A block-table entry outside the pool reads block 0 (reported through status).
     const uint16_t* kbase = (const uint16_t*)p.k;
     const uint16_t* vbase = (const uint16_t*)p.v;
-    const int64_t head_base = (p.paged ? 0 : (int64_t)b * p.stride_seq) + (int64_t)kvh * p.stride_head;
-    const int stride_tok = (int)p.stride_tok;
     const int lrow = lane / LPR, lchunk = lane % LPR;
     const int k0 = split * p.keys_per_split; // the host keeps k0 below max_prefix_len + tree_keys, hence inside the cache
-    const int64_t cache_tokens = p.paged ? (int64_t)p.max_blocks * p.block_size : p.capacity;
-    const int kend = (int)(cache_tokens < (int64_t)k0 + p.keys_per_split ? cache_tokens : (int64_t)k0 + p.keys_per_split);
-    u32x4 kreg[PPM][SPW], vreg[PPM][SPW];
-    // tile and first row (inside the tile) of this wave's u-th copy block of stage j; blocks past the
-    // stage's last one (KQ * BPS not a multiple of the wave count) repeat its last block
-    auto block_tile = [&](int j, int u) __attribute__((always_inline)) {
-        const int i = min(wave + kResWaves * u, KQ * BPS - 1);
-        return min(j * KQ + i / BPS, NT - 1);
-    };
-    auto block_row = [&](int u) __attribute__((always_inline)) {
-        const int i = min(wave + kResWaves * u, KQ * BPS - 1);
-        return (i % BPS) * RPI;
-    };
-    auto issue_stage = [&](auto is_v, int j) __attribute__((always_inline)) {
-        constexpr bool ISV = decltype(is_v)::value;
+    const int64_t head_base = (PAGED ? 0 : (int64_t)b * p.stride_seq) + (int64_t)kvh * p.stride_head;
+    const uint32_t stride = (uint32_t)p.stride_tok * 2u; // bytes; the host keeps a slice's offsets below 2^31 bytes
+    u32x4 kreg[NB], vreg[NB];
+    int64_t blk_base[PAGED ? NB : 1];
+    uint32_t lane_off;
+    if constexpr (PAGED) {
+        // the RPI rows of a load lie in one cache block; past the table's last rows those are read again
+        int32_t id[NB];
+        int r0[NB];
+        const int64_t cache_tokens = (int64_t)p.max_blocks * p.block_size, end = (int64_t)k0 + NT * kTileKeys;
+        const int last = (int)(cache_tokens < end ? cache_tokens : end) - RPI;
 #pragma unroll
-        for (int u = 0; u < SPW; ++u) {
-            const int r0 = min(k0 + kTileKeys * block_tile(j, u) + block_row(u), kend - 1); // RPI divides 16: one cache block in paged mode
-            int tok = min(r0 + lrow, kend - 1);
-            int64_t base = head_base;
-            if (p.paged) {
-                int32_t blk = p.block_table[(int64_t)b * p.max_blocks + (r0 >> p.block_shift)];
-                if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-                base += (int64_t)blk * p.stride_block;
-                tok &= p.block_size - 1;
-            }
-            const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
-            if constexpr (ISV) vreg[j][u] = *(const u32x4*)(vbase + base + off);
-            else kreg[j][u] = *(const u32x4*)(kbase + base + off);
+        for (int u = 0; u < NB; ++u) {
+            r0[u] = min(k0 + u * RPB + wave * RPI, last);
+            id[u] = p.block_table[(int64_t)b * p.max_blocks + (r0[u] >> p.block_shift)];
         }
-    };
-    // Later rounds (the sequence's length is known by then, tokens past the split's last one repeat it). Paged
-    // caches: the ids of the next 64 blocks sit one per lane (see attention_mfma_pipe.hip).
-    int bt_base = k0 >> p.block_shift;
-    int32_t bt_win = 0;
-    auto bt_fetch = [&]() __attribute__((always_inline)) { bt_win = p.block_table[(int64_t)b * p.max_blocks + min(bt_base + lane, p.max_blocks - 1)]; };
-    if (STREAM && p.paged) bt_fetch();
-    auto issue_round = [&](int kr, int last) __attribute__((always_inline)) {
-        if (p.paged && ((kr + NT * kTileKeys - 1) >> p.block_shift) >= bt_base + 64) { // uniform
-            bt_base = kr >> p.block_shift;
-            bt_fetch();
+        lane_off = (uint32_t)lrow * stride + lchunk * 16;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int32_t blk = (uint32_t)id[u] < (uint32_t)p.num_blocks ? id[u] : 0;
+            blk_base[u] = ((int64_t)blk * p.stride_block + head_base) * 2 + (uint32_t)(r0[u] & (p.block_size - 1)) * stride;
+            kreg[u] = *(const u32x4*)((const char*)kbase + blk_base[u] + lane_off);
         }
+    } else {
+        lane_off = (uint32_t)(wave * RPI + lrow) * stride + lchunk * 16;
+    }
+    // contiguous caches: rows past the cache's end read as zeros
+    const __amdgpu_buffer_rsrc_t krs = slice_of(kbase + head_base, k0, p, stride), vrs = slice_of(vbase + head_base, k0, p, stride);
+    if constexpr (!PAGED) {
 #pragma unroll
-        for (int j = 0; j < PPM; ++j)
-#pragma unroll
-            for (int u = 0; u < SPW; ++u) {
-                const int r0 = min(kr + kTileKeys * block_tile(j, u) + block_row(u), last);
-                int tok = min(r0 + lrow, last);
-                int64_t base = head_base;
-                if (p.paged) {
-                    int32_t blk = __builtin_amdgcn_readlane(bt_win, (r0 >> p.block_shift) - bt_base);
-                    if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-                    base += (int64_t)blk * p.stride_block;
-                    tok &= p.block_size - 1;
-                }
-                const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
-                kreg[j][u] = *(const u32x4*)(kbase + base + off);
-                vreg[j][u] = *(const u32x4*)(vbase + base + off);
-            }
-    };
-    issue_stage(std::false_type{}, 0); // the first keys lead: the first scores need them and the queries
-
-    // ---- this wave's rows, mask and queries (in flight together with the tiles)
+        for (int u = 0; u < NB; ++u)
+            kreg[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(krs, lane_off + (uint32_t)(u * RPB) * stride, 0, 0));
+    }
+    // ---- this wave's share of its row block's queries
     const int row_base = rg * (NRB * kRowBlock) + rbw * kRowBlock;
     const bool wave_active = row_base < p.rows;
-    const int r = min(row_base + col, p.rows - 1); // rows past the end repeat the last row (results discarded)
-    const int node = row_node(p, r);
-    // the waves of a row block share the fetch of its queries
     constexpr int QPW = (KS + KQ - 1) / KQ; // pieces per wave
     u32x4 qreg[QPW];
 #pragma unroll
     for (int i = 0; i < QPW; ++i) qreg[i] = load_q_piece<D>(p, b, kvh, row_base, min(kq * QPW + i, KS - 1), lane);
-    // the row's ancestor mask, when the caller supplies the masks: requested ahead of the later stages
-    uint64_t mask_given = 0;
-    if (p.tree_mask && p.tree_keys != 0) mask_given = p.tree_mask[(int64_t)b * p.T + node];
-    issue_stage(std::true_type{}, 0);
+    // the gate of the row group (thread 0 opens it below)
+    const MergeGate gate{p.gates ? p.gates + kGateWords * (int64_t)((b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
+    MergeSeen seen{};
+    if (p.gates && wave == 0) seen = merge_look(gate);
+    // the row's ancestor mask, when the caller supplies the masks
+    const int r = min(row_base + col, p.rows - 1); // rows past the end repeat the last row (results discarded)
+    const int node = row_node(p, r);
+    uint64_t mask = 0;
+    if (p.tree_mask && p.tree_keys != 0) mask = p.tree_mask[(int64_t)b * p.T + node];
 #pragma unroll
-    for (int j = 1; j < PPM; ++j) {
-        issue_stage(std::false_type{}, j);
-        issue_stage(std::true_type{}, j);
+    for (int u = 0; u < NB; ++u) {
+        if constexpr (PAGED) vreg[u] = *(const u32x4*)((const char*)vbase + blk_base[u] + lane_off);
+        else vreg[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(vrs, lane_off + (uint32_t)(u * RPB) * stride, 0, 0));
     }
 
+    const bool reports = kvh == 0 && split == 0 && rg == 0;
     int32_t tree_code = VS_STATUS_OK;
-    if (p.tree_mask || p.tree_keys == 0) {
+    if (!p.tree_mask && p.tree_keys != 0) {
+        tree_code = load_tree(p.parent + (int64_t)b * p.T, p.T, sp, &sflag);
+        if (tree_code == VS_STATUS_OK) mask = ancestor_mask(sp, node);
+    } else if (reports) {
         if (tid == 0) sflag = 0;
         __syncthreads();
-    } else {
-        tree_code = load_tree(p.parent + (int64_t)b * p.T, p.T, sp, &sflag);
     }
-    const uint64_t mask = p.tree_keys == 0 ? 0ull : (p.tree_mask ? mask_given : (tree_code == VS_STATUS_OK ? ancestor_mask(sp, node) : 0ull));
     const bool s_ok = prefix_ok(p, S);
-    if (kvh == 0 && split == 0 && rg == 0) report_status(p, b, tree_code, s_ok, S, &sflag);
+    if (reports) report_status(p, b, tree_code, s_ok, S, &sflag);
     if (tree_code != VS_STATUS_OK || !s_ok) return;
 
     const int nk = S + p.tree_keys;
     if (k0 >= nk) return;
     const bool final_rows = p.num_splits == 1 || (p.gates && nk <= p.keys_per_split); // a sequence of one split has nothing to merge
     const bool merge = p.gates && !final_rows;
-    const MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
-    if (merge && tid == 0) merge_open(gate);
+    if (merge && tid == 0) merge_open(gate, seen);
     const int k1 = min(nk, k0 + p.keys_per_split);
 
-    // per-lane LDS offsets (elements); everything else is a compile-time immediate
-    const int k_lane[2] = {(col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (4 * half)) * 8,
-                           (col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (8 + 4 * half)) * 8};
-    const int t16 = lane & 15;
-    const int v_lane = half * 128 + (t16 >> 2) * 32 + ((lane >> 4) & 1) * 16 + ((t16 >> 1) & 1) * 8 + (t16 & 1) * 4;
-    // the staged copy blocks of stage j -> LDS; LIVE: rows past the split's last key become zeros
-    auto stash_stage = [&](auto live_tag, int j, int at) __attribute__((always_inline)) {
-        constexpr bool LIVE = decltype(live_tag)::value;
+    // ---- keys and queries into LDS. Chunk c of tile row r lands where the fragment reads expect it (same placement as
+    // the streaming kernels):
+    //   K: ((r/16)*DB + c/4) * 1024 + (c%4) * 256 + ((r%16) ^ 4*(c%4)) * 16
+    //   V: ((r/16)*DB + c/4) * 1024 + (4*(r%16) + c%4) * 16
+    const int srow = wave * RPI + lrow, rr = srow & (kTileKeys - 1); // (RPB is a multiple of a tile)
+    {
+        const uint32_t ko = (uint32_t)((srow / kTileKeys) * (SUB * 2) + ((rr >> 4) * DB + (lchunk >> 2)) * 1024 + (lchunk & 3) * 256 + (((rr & 15) ^ (4 * (lchunk & 3))) * 16));
 #pragma unroll
-        for (int u = 0; u < SPW; ++u) {
-            if (SPW * kResWaves == KQ * BPS || wave + kResWaves * u < KQ * BPS) { // uniform per wave
-                const int t = block_tile(j, u), rr = block_row(u) + lrow, c = lchunk;
-                const bool live = !LIVE || k0 + kTileKeys * t + rr < k1;
-                const u32x4 zero = {0u, 0u, 0u, 0u};
-                const uint32_t ko = (uint32_t)(((rr >> 4) * DB + (c >> 2)) * 1024 + (c & 3) * 256 + (((rr & 15) ^ (4 * (c & 3))) * 16));
-                const uint32_t vo = (uint32_t)(((rr >> 4) * DB + (c >> 2)) * 1024 + (4 * (rr & 15) + (c & 3)) * 16);
-                *(u32x4*)((char*)(sK + at + t * SUB) + ko) = live ? kreg[j][u] : zero;
-                *(u32x4*)((char*)(sV + at + t * SUB) + vo) = live ? vreg[j][u] : zero;
-            }
-        }
-    };
+        for (int u = 0; u < NB; ++u) *(u32x4*)((char*)sK + ko + u * (RPB / kTileKeys * SUB * 2)) = kreg[u];
+    }
+#pragma unroll
+    for (int i = 0; i < QPW; ++i) store_q_piece<D>(sQ + rbw * (kRowBlock * D), qreg[i], min(kq * QPW + i, KS - 1), lane);
+    __syncthreads();
 
-    // ---- this wave's key part: tiles j * KQ + kq of every round. The softmax comes once per round, over all of
-    // the part's tiles of it (its independent halves hide each other's latency), and then the output.
-    bf16x8 qf[KS];
+    // ---- S^T = K . Q^T of this wave's key part: lane (col, half) gets keys 8*(q/4) + 4*half + q%4 of row `col`
     f32x16 s[PPM];
-    // S^T = K . Q^T: lane (col, half) gets keys 8*(q/4) + 4*half + q%4 of row `col`
-    auto scores = [&](int j, int at) __attribute__((always_inline)) {
+    {
+        const int k_lane[2] = {(col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (4 * half)) * 8,
+                               (col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (8 + 4 * half)) * 8};
+        bf16x8 qf[KS];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) s[j][q] = 0.f;
-        const uint16_t* kt_ = sK + at + min(j * KQ + kq, NT - 1) * SUB;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, *(const u32x4*)(kt_ + k_lane[ks & 1] + ks * 256));
-            s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[j], 0, 0, 0);
-        }
-    };
-    float m2 = -INFINITY, lsum = 0.f; // reference (log2 domain, scaled; -inf: no visible key yet), this lane's share of the sum
-    f32x16 acc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[db][q] = 0.f;
-    auto output = [&](auto first_tag, int kr, int at) __attribute__((always_inline)) {
-        constexpr bool FIRST = decltype(first_tag)::value;
-        // uniform: tree slots, the end of the range, or a last stage without a tile for this key part
-        if (kr + NT * kTileKeys > min(S, k1) || (PPM - 1) * KQ + kq >= NT) {
-#pragma unroll
-            for (int j = 0; j < PPM; ++j) {
-                const int first = kr + (j * KQ + kq) * kTileKeys;
-                const uint32_t w = tile_visible(mask, first - S, j * KQ + kq < NT ? k1 - first : 0) >> (4 * half);
-#pragma unroll
-                for (int q = 0; q < 16; ++q) s[j][q] = visible_or_inf(s[j][q], w, 8 * (q >> 2) + (q & 3));
-            }
-        }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < PPM; ++j)
-#pragma unroll
-            for (int q = 0; q < 16; q += 2) mx = max3(mx, s[j][q], s[j][q + 1]);
-        const float mt = half_max(mx) * p.scale_log2;
-        const float m_new = FIRST ? mt : (mt > m2 + kLazy ? mt : m2); // lazy: moves in steps of more than 2^8
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        float ps0 = 0.f, ps1 = 0.f;
-#pragma unroll
-        for (int j = 0; j < PPM; ++j)
-#pragma unroll
-            for (int q = 0; q < 16; q += 2) {
-                s[j][q] = __builtin_amdgcn_exp2f(fmaf(s[j][q], p.scale_log2, -m_use)); // exp2(-inf) = 0
-                s[j][q + 1] = __builtin_amdgcn_exp2f(fmaf(s[j][q + 1], p.scale_log2, -m_use));
-                ps0 += s[j][q];
-                ps1 += s[j][q + 1];
-            }
-        if constexpr (!FIRST) {
-            const float alpha = __builtin_amdgcn_exp2f(m2 - m_use);
-            lsum *= alpha;
-            if (__any(alpha != 1.f)) {
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) acc[db][q] *= alpha;
-            }
-        }
-        lsum += ps0 + ps1;
-        m2 = m_new;
-        // O^T += V^T . P^T: the A operand comes from two transposing reads of 4 keys x 16 channels
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = read_q_frag<D>(sQ + rbw * (kRowBlock * D), ks, col, half);
 #pragma unroll
         for (int j = 0; j < PPM; ++j) {
-            const uint16_t* vt_ = sV + at + min(j * KQ + kq, NT - 1) * SUB + v_lane;
-            bf16x8 pf[2];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s[j][q] = 0.f;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int j = 0; j < PPM; ++j) {
+                const uint16_t* kt = sK + min(j * KQ + kq, NT - 1) * SUB;
+                const bf16x8 a = __builtin_bit_cast(bf16x8, *(const u32x4*)(kt + k_lane[ks & 1] + ks * 256));
+                s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s[j], 0, 0, 0);
+            }
+    }
+    // the values have arrived meanwhile; rows past the split's last key become zeros (whatever the cache holds there,
+    // NaN included, must not meet a zero probability; a key of that kind only spoils its own score, which is masked)
+    {
+        const uint32_t vo = (uint32_t)((srow / kTileKeys) * (SUB * 2) + ((rr >> 4) * DB + (lchunk >> 2)) * 1024 + (4 * (rr & 15) + (lchunk & 3)) * 16);
+        if (k0 + NT * kTileKeys > k1) { // uniform
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int u = 0; u < NB; ++u) vreg[u] = k0 + u * RPB + srow < k1 ? vreg[u] : zero;
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) *(u32x4*)((char*)sV + vo + u * (RPB / kTileKeys * SUB * 2)) = vreg[u];
+    }
+    // uniform: tree slots, the end of the range, or a last tile that this key part does not have
+    if (k0 + NT * kTileKeys > min(S, k1) || (PPM - 1) * KQ + kq >= NT) {
+#pragma unroll
+        for (int j = 0; j < PPM; ++j) {
+            const int first = k0 + (j * KQ + kq) * kTileKeys;
+            const uint32_t w = tile_visible(mask, first - S, j * KQ + kq < NT ? k1 - first : 0) >> (4 * half);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s[j][q] = visible_or_inf(s[j][q], w, 8 * (q >> 2) + (q & 3));
+        }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < PPM; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; q += 2) mx = max3(mx, s[j][q], s[j][q + 1]);
+    const float m2 = half_max(mx) * p.scale_log2;    // this part's reference (log2 domain, scaled); -inf: no visible key in it
+    const float m_use = m2 == -INFINITY ? 0.f : m2;
+    if (P_OVER_K) __syncthreads(); // the keys have been read
+    float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+    for (int j = 0; j < PPM; ++j) {
+#pragma unroll
+        for (int q = 0; q < 16; q += 2) {
+            s[j][q] = __builtin_amdgcn_exp2f(fmaf(s[j][q], p.scale_log2, -m_use)); // exp2(-inf) = 0
+            s[j][q + 1] = __builtin_amdgcn_exp2f(fmaf(s[j][q + 1], p.scale_log2, -m_use));
+            ps0 += s[j][q];
+            ps1 += s[j][q + 1];
+        }
+        if (j * KQ + kq < NT) { // uniform; a part without this tile has added zeros
 #pragma unroll
             for (int sl = 0; sl < 2; ++sl) {
                 u32x4 w;
@@ -307,178 +240,85 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
                     const f32x2 pr = {s[j][8 * sl + 2 * e], s[j][8 * sl + 2 * e + 1]};
                     w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
                 }
-                pf[sl] = __builtin_bit_cast(bf16x8, w);
-            }
-#pragma unroll
-            for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt_ + sl * (DB * 512) + db * 512 + 256));
-                    const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                    acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[sl], acc[db], 0, 0, 0);
-                }
-        }
-    };
-
-    // ---- round 0, stage by stage as the loads arrive (they return in order; the compiler counts them and waits
-    // for exactly the stage's before their first use)
-#pragma unroll
-    for (int j = 0; j < PPM; ++j) {
-        stash_stage(std::true_type{}, j, 0);
-        if (j == 0) {
-#pragma unroll
-            for (int i = 0; i < QPW; ++i) store_q_piece<D>(sQ + rbw * (kRowBlock * D), qreg[i], min(kq * QPW + i, KS - 1), lane);
-        }
-        __syncthreads();
-        if (j == 0) {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) qf[ks] = read_q_frag<D>(sQ + rbw * (kRowBlock * D), ks, col, half);
-        }
-        scores(j, 0);
-    }
-    constexpr int ROUND = NT * kTileKeys;
-    if (STREAM && k0 + ROUND < k1) issue_round(k0 + ROUND, k1 - 1);
-    output(std::true_type{}, k0, 0);
-    // ---- the other rounds: two sets of tiles in LDS, one barrier per round. A round is requested when the one
-    // before it has left the staging registers.
-    if constexpr (STREAM) {
-        int at = TILE_BYTES / 2;
-        for (int kr = k0 + ROUND; kr < k1; kr += ROUND) {
-#pragma unroll
-            for (int j = 0; j < PPM; ++j) stash_stage(std::false_type{}, j, at);
-            __syncthreads();
-            if (kr + ROUND < k1) issue_round(kr + ROUND, k1 - 1);
-#pragma unroll
-            for (int j = 0; j < PPM; ++j) scores(j, at);
-            output(std::false_type{}, kr, at);
-            at = TILE_BYTES / 2 - at;
-        }
-    }
-
-    // ---- merge the key parts through LDS (log-sum-exp) and write the rows. The work is shared: a row
-    // block's accumulators are 2 * DB pieces of eight registers (piece = channel block * 2 + half of
-    // its registers, the 16-byte unit of the partial-result layout); key part k owns pieces
-    // k * PPK .. (k + 1) * PPK - 1, receives the other parts' versions of those, merges them in ascending
-    // part order (so every wave of a row block computes the same sum) and stores them. Every wave
-    // hands (8 - PPK pieces, max, sum) over and takes as much back, instead of part 0 doing all of it.
-    __syncthreads(); // every wave is done with the tiles
-    float* sm = (float*)smem;
-    constexpr int NP = 2 * DB;                    // pieces per row block
-    constexpr int PPK = NP / KQ > 0 ? NP / KQ : 1; // pieces owned by a key part
-    constexpr int OWNERS = NP / PPK;              // key parts that own pieces (all of them unless KQ > NP)
-    constexpr int XCH = NP * 512 + 128;           // floats a wave's exchange area holds: pieces [piece][2][64 lanes][4], max[64], sum[64]
-    static_assert(kResWaves * XCH * 4 <= SMEM_ELEMS * 2, "exchange area fits");
-    float* mine = sm + (rbw * KQ + kq) * XCH;
-    auto piece_owner = [](int pc) { return pc / PPK; };
-    if (wave_active) {
-#pragma unroll
-        for (int pc = 0; pc < NP; ++pc) {
-            // written by everybody but the owner; which pieces those are depends on kq, the registers
-            // they come from do not
-            if (piece_owner(pc) != kq) {
-                const int db = pc >> 1, hp = pc & 1;
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) {
-                    const f32x4 w = {acc[db][8 * hp + 4 * hh], acc[db][8 * hp + 4 * hh + 1], acc[db][8 * hp + 4 * hh + 2],
-                                     acc[db][8 * hp + 4 * hh + 3]};
-                    *(f32x4*)(mine + pc * 512 + hh * 256 + lane * 4) = w;
-                }
+                *(u32x4*)(sP + ((rbw * NT + j * KQ + kq) * 2 + sl) * 512 + lane * 8) = w;
             }
         }
-        mine[NP * 512 + lane] = m2;
-        mine[NP * 512 + 64 + lane] = lsum;
+    }
+    const float psum = half_sum(ps0 + ps1);
+    if (half == 0) {
+        s_max[rbw][kq][col] = m2;
+        s_sum[rbw][kq][col] = psum;
     }
     __syncthreads();
-    if (wave_active && kq < OWNERS) {
 
-    // reference and sum over all key parts, the same arithmetic in every wave of the row block
-    float mo[KQ], lo[KQ];
+    // ---- O^T = V^T . P^T over all keys, for this wave's channel blocks; the rows leave as they are. Lane (col, half)
+    // holds, for row `col`, channels db*32 + 8*(q/4) + 4*half + q%4.
+    if (wave_active && kq < OWN) {
+        const int t16 = lane & 15;
+        const int v_lane = half * 128 + (t16 >> 2) * 32 + ((lane >> 4) & 1) * 16 + ((t16 >> 1) & 1) * 8 + (t16 & 1) * 4 + kq * (DBW * 512);
+        float f[KQ], M = -INFINITY, l = 0.f; // the parts' weights, the rows' reference and sum
 #pragma unroll
-    for (int o = 0; o < KQ; ++o) {
-        const float* src = sm + (rbw * KQ + o) * XCH;
-        mo[o] = src[NP * 512 + lane];
-        lo[o] = src[NP * 512 + 64 + lane];
-    }
-    float M = mo[0];
+        for (int o = 0; o < KQ; ++o) {
+            f[o] = s_max[rbw][o][col];
+            M = fmaxf(M, f[o]);
+        }
+        const float Ms = M == -INFINITY ? 0.f : M; // no visible key in this split: every weight is 2^-inf = 0
 #pragma unroll
-    for (int o = 1; o < KQ; ++o) M = fmaxf(M, mo[o]);
-    const float Ms = (M == -INFINITY) ? 0.f : M; // no part has seen a visible key: every factor below is 2^-inf = 0
-    float fo[KQ], lall = 0.f;
+        for (int o = 0; o < KQ; ++o) {
+            f[o] = __builtin_amdgcn_exp2f(f[o] - Ms);
+            l += f[o] * s_sum[rbw][o][col];
+        }
+        f32x16 acc[DBW], part[DBW];
 #pragma unroll
-    for (int o = 0; o < KQ; ++o) {
-        fo[o] = __builtin_amdgcn_exp2f(mo[o] - Ms);
-        lall += lo[o] * fo[o];
-    }
-    const float l = half_sum(lall);
-    const int r_local = row_base + col;
-    const float inv = l > 0.f ? 1.f / l : 0.f; // no visible key in this split (partials only): zeros, weight 0
-    uint16_t* orow = (uint16_t*)p.out + row_offset(p, b, kvh, r, node);
-    uint16_t* po = p.part_o + part_block<D>(p, (int64_t)b * p.Hkv + kvh, split, row_base >> 5);
-
-    // this wave's pieces: lane (col, half) holds, for row `col`, channels db*32 + 8*(q/4) + 4*half + q%4. All of
-    // them are read and added up before the first store (one trip through LDS, not one per piece).
-    auto finish = [&](auto kq_tag) __attribute__((always_inline)) {
-        constexpr int MY = decltype(kq_tag)::value;
-        float r[PPK][8];
+        for (int o = 0; o < KQ && o < NT; ++o) {
 #pragma unroll
-        for (int i = 0; i < PPK; ++i) {
-            const int pc = MY * PPK + i, db = pc >> 1, hp = pc & 1;
+            for (int db = 0; db < DBW; ++db)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) r[i][e] = 0.f;
+                for (int q = 0; q < 16; ++q) part[db][q] = 0.f;
 #pragma unroll
-            for (int o = 0; o < KQ; ++o) {
-                if (o == MY) {
+            for (int t = o; t < NT; t += KQ)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) r[i][e] += fo[o] * acc[db][8 * hp + e];
-                } else {
-                    const float* src = sm + (rbw * KQ + o) * XCH + pc * 512 + lane * 4;
-                    const f32x4 a0 = *(const f32x4*)src, a1 = *(const f32x4*)(src + 256);
+                for (int sl = 0; sl < 2; ++sl) {
+                    const bf16x8 pf = __builtin_bit_cast(bf16x8, *(const u32x4*)(sP + ((rbw * NT + t) * 2 + sl) * 512 + lane * 8));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        r[i][e] += fo[o] * a0[e];
-                        r[i][4 + e] += fo[o] * a1[e];
+                    for (int db = 0; db < DBW; ++db) {
+                        const uint16_t* vt = sV + t * SUB + sl * (DB * 512) + db * 512 + v_lane;
+                        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)vt);
+                        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + 256));
+                        const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                        part[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf, part[db], 0, 0, 0);
                     }
                 }
-            }
+#pragma unroll
+            for (int db = 0; db < DBW; ++db)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) acc[db][q] = o == 0 ? f[o] * part[db][q] : acc[db][q] + f[o] * part[db][q];
         }
+        const float inv = l > 0.f ? 1.f / l : 0.f; // no visible key in this split (partials only): zeros, weight 0
         if (final_rows) {
-            if (r_local < p.rows) {
+            if (row_base + col < p.rows) {
+                uint16_t* orow = (uint16_t*)p.out + row_offset(p, b, kvh, r, node) + kq * (DBW * 32) + 4 * half;
 #pragma unroll
-                for (int i = 0; i < PPK; ++i)
+                for (int db = 0; db < DBW; ++db)
 #pragma unroll
-                    for (int hh = 0; hh < 2; ++hh)
-                        *(u32x2*)(orow + (MY * PPK + i) * 16 + 8 * hh + 4 * half) =
-                            pack_partial(r[i][4 * hh], r[i][4 * hh + 1], r[i][4 * hh + 2], r[i][4 * hh + 3], inv);
+                    for (int q4 = 0; q4 < 4; ++q4)
+                        *(u32x2*)(orow + db * 32 + 8 * q4) = pack_partial(acc[db][4 * q4], acc[db][4 * q4 + 1], acc[db][4 * q4 + 2], acc[db][4 * q4 + 3], inv);
             }
         } else {
+            const int64_t unit = (int64_t)b * p.Hkv + kvh;
+            uint16_t* po = p.part_o + part_block<D>(p, unit, split, row_base >> 5) + kq * DBW * 2 * piece_stride(p);
 #pragma unroll
-            for (int i = 0; i < PPK; ++i) {
-                const u32x2 w0 = pack_partial(r[i][0], r[i][1], r[i][2], r[i][3], inv), w1 = pack_partial(r[i][4], r[i][5], r[i][6], r[i][7], inv);
-                const u32x4 w = {w0[0], w0[1], w1[0], w1[1]};
-                uint16_t* dst = po + (MY * PPK + i) * piece_stride(p);
-                if (merge) __builtin_amdgcn_raw_buffer_store_b128(w, span_of(dst), lane * 16, 0, kDeviceScope);
-                else *(u32x4*)(dst + lane * 8) = w;
+            for (int db = 0; db < DBW; ++db) {
+                if (merge) store_partial<true>(p, po, db, lane, acc[db], inv);
+                else store_partial(p, po, db, lane, acc[db], inv);
+            }
+            if (kq == 0 && half == 0) {
+                const f32x2 ml = {M, l};
+                float* dst = p.part_ml + ml_block(p, unit, split, row_base >> 5) * 2;
+                if (merge) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), span_of(dst), col * 8, 0, kDeviceScope);
+                else *(f32x2*)(dst + col * 2) = ml;
             }
         }
-    };
-    switch (kq) { // uniform per wave; the case fixes which registers are this wave's
-    case 0: finish(std::integral_constant<int, 0>{}); break;
-    case 1: finish(std::integral_constant<int, 1 % OWNERS>{}); break;
-    case 2: finish(std::integral_constant<int, 2 % OWNERS>{}); break;
-    case 3: finish(std::integral_constant<int, 3 % OWNERS>{}); break;
-    case 4: finish(std::integral_constant<int, 4 % OWNERS>{}); break;
-    case 5: finish(std::integral_constant<int, 5 % OWNERS>{}); break;
-    case 6: finish(std::integral_constant<int, 6 % OWNERS>{}); break;
-    default: finish(std::integral_constant<int, 7 % OWNERS>{}); break;
-    }
-    if (!final_rows && kq == 0 && half == 0) {
-        const f32x2 ml = {M, l};
-        const int64_t mlb = ml_block(p, (int64_t)b * p.Hkv + kvh, split, row_base >> 5);
-        float* dst = p.part_ml + mlb * 2;
-        if (merge) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), span_of(dst), col * 8, 0, kDeviceScope);
-        else *(f32x2*)(dst + col * 2) = ml;
-    }
     }
     if (merge) {
         const int nrb = p.rows_pad / kRowBlock, rb0 = rg * NRB;
@@ -487,20 +327,20 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     }
 }
 
-template <int D, int NRB, int NT, bool STREAM = false>
+// NT = tiles per split (2, 4, 6 or 8 tiles of 32 keys)
+template <int D, int NRB, bool PAGED>
 hipError_t launch_res(const AttnParams& p, hipStream_t s) {
-    const dim3 grid(((p.total_wgs + 7) / 8) * 8);
-    hipLaunchKernelGGL((attn_mfma_resident_kernel<D, NRB, NT, STREAM>), grid, dim3(kResWaves * kWave), 0, s, p);
+    const dim3 grid(((p.total_wgs + 7) / 8) * 8), block(kResWaves * kWave);
+    const int nt = p.keys_per_split / kTileKeys;
+    if (nt <= 2) hipLaunchKernelGGL((attn_mfma_resident_kernel<D, NRB, 2, PAGED>), grid, block, 0, s, p);
+    else if (nt <= 4) hipLaunchKernelGGL((attn_mfma_resident_kernel<D, NRB, 4, PAGED>), grid, block, 0, s, p);
+    else if (nt <= 6) hipLaunchKernelGGL((attn_mfma_resident_kernel<D, NRB, 6, PAGED>), grid, block, 0, s, p);
+    else if constexpr (resident_max_keys(NRB) >= 8 * kTileKeys) hipLaunchKernelGGL((attn_mfma_resident_kernel<D, NRB, 8, PAGED>), grid, block, 0, s, p);
     return hipGetLastError();
 }
-
-// NT = tiles per split (2, 4 or 6 tiles of 32 keys)
-template <int D, int NRB>
-hipError_t launch_res_nt(const AttnParams& p, hipStream_t s) {
-    const int nt = p.keys_per_split / kTileKeys;
-    if (nt <= 2) return launch_res<D, NRB, 2>(p, s);
-    if (nt <= 4) return launch_res<D, NRB, 4>(p, s);
-    return launch_res<D, NRB, 6>(p, s);
+template <int D, bool PAGED>
+hipError_t launch_res_rb(const AttnParams& p, int row_blocks, hipStream_t s) {
+    return row_blocks == 4 ? launch_res<D, 4, PAGED>(p, s) : row_blocks == 2 ? launch_res<D, 2, PAGED>(p, s) : launch_res<D, 1, PAGED>(p, s);
 }
 
 } // namespace
@@ -509,21 +349,9 @@ hipError_t launch_res_nt(const AttnParams& p, hipStream_t s) {
 bool attention_resident_supported(int row_blocks) { return row_blocks == 4 || row_blocks == 2 || row_blocks == 1; }
 
 hipError_t launch_attention_mfma_resident(const AttnParams& p, int row_blocks, hipStream_t s) {
-    if (!attention_resident_supported(row_blocks) || p.keys_per_split > kResidentMaxKeys || p.keys_per_split % kIterKeys) return hipErrorInvalidValue;
-    if (p.d == 128) {
-        return row_blocks == 4 ? launch_res_nt<128, 4>(p, s) : (row_blocks == 2 ? launch_res_nt<128, 2>(p, s) : launch_res_nt<128, 1>(p, s));
-    }
-    if (p.d == 64) {
-        return row_blocks == 4 ? launch_res_nt<64, 4>(p, s) : (row_blocks == 2 ? launch_res_nt<64, 2>(p, s) : launch_res_nt<64, 1>(p, s));
-    }
-    return hipErrorInvalidValue;
-}
-
-// Splits of any length, in rounds of four tiles; four or two row blocks per workgroup.
-hipError_t launch_attention_mfma_rounds(const AttnParams& p, int row_blocks, hipStream_t s) {
-    if ((row_blocks != 4 && row_blocks != 2) || p.keys_per_split % kIterKeys) return hipErrorInvalidValue;
-    if (p.d == 128) return row_blocks == 4 ? launch_res<128, 4, 4, true>(p, s) : launch_res<128, 2, 4, true>(p, s);
-    if (p.d == 64) return row_blocks == 4 ? launch_res<64, 4, 4, true>(p, s) : launch_res<64, 2, 4, true>(p, s);
+    if (!attention_resident_supported(row_blocks) || p.keys_per_split > resident_max_keys(row_blocks) || p.keys_per_split % kIterKeys) return hipErrorInvalidValue;
+    if (p.d == 128) return p.paged ? launch_res_rb<128, true>(p, row_blocks, s) : launch_res_rb<128, false>(p, row_blocks, s);
+    if (p.d == 64) return p.paged ? launch_res_rb<64, true>(p, row_blocks, s) : launch_res_rb<64, false>(p, row_blocks, s);
     return hipErrorInvalidValue;
 }
 

@@ -74,13 +74,19 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
 
     // workgroup id -> (sequence, KV head, split), splits fastest; same XCD-aware remap as the other kernels. More whole
     // sequences than run at once: the longest first, dealt over the XCDs (see attention_mfma_pipe.hip).
-    const int per_xcd = (p.total_wgs + 7) >> 3;
-    const int v = p.by_length ? blockIdx.x : (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (v >= p.total_wgs) return;
-    const int split = v % p.num_splits;
-    const int kvh = v / p.num_splits % p.Hkv;
-    int b = v / p.num_splits / p.Hkv;
-    if (p.by_length) b = sequence_by_rank(p, b, lane);
+    int b, kvh, split = 0;
+    if (p.by_length) { // one split each
+        if (blockIdx.x >= (uint32_t)p.total_wgs) return;
+        uint32_t head;
+        b = sequence_by_rank(p, (int)fast_div(blockIdx.x, p.by_heads, head), lane);
+        kvh = (int)head;
+    } else {
+        const WorkItem at = work_item(p);
+        if (at.none) return;
+        b = at.b;
+        kvh = at.kvh;
+        split = at.split;
+    }
     const int unit = b * p.Hkv + kvh;
 
     const int32_t S = p.prefix_len[b]; // requested first, needed last: the first tiles are requested before it arrives
@@ -112,23 +118,40 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     // an operand read takes lie in different banks. vx(r): the transposing reads take 4 rows x 2 (4) chunks per 16
     // (32) lanes, which then lie in different banks too.
     auto vx = [](int r) __attribute__((always_inline)) { return D == 128 ? 4 * (r & 3) ^ 2 * ((r ^ (r >> 1)) & 1) : 2 * (r & 3); };
-    const uint32_t k_chunk = (uint32_t)(lchunk ^ (lrow % LPR)) * 16u, v_chunk = (uint32_t)(lchunk ^ vx(lrow)) * 16u; // bytes
+    // This lane's bytes from a load's first row on, per load: the keys' chunk depends on the row (KV of them differ).
+    constexpr int KV = LPR / RPI > 0 ? LPR / RPI : 1;
+    const uint32_t stride = (uint32_t)stride_tok * 2u;
+    uint32_t k_off[KV], v_off = (uint32_t)lrow * stride + (uint32_t)(lchunk ^ vx(lrow)) * 16u;
+#pragma unroll
+    for (int j = 0; j < KV; ++j) k_off[j] = (uint32_t)lrow * stride + (uint32_t)(lchunk ^ ((RPI * j + lrow) % LPR)) * 16u;
     // tile at key kt into LDS, keys past `last` repeat it; kt <= last
     auto issue = [&](auto is_v, uint16_t* to, int kt, int last) __attribute__((always_inline)) {
         constexpr bool ISV = decltype(is_v)::value;
         const uint16_t* g = (ISV ? vbase : kbase) + head_base;
         const uint16_t* base[2] = {g, g};
+        int row0[2] = {kt, kt + kTileKeys / 2}; // of the tile's halves
         if (p.paged) {
             const int at = (kt - bt_from) / ROUND * 2;
             base[0] += (int64_t)__builtin_amdgcn_readlane(bt_win, at) * p.stride_block;
             base[1] += (int64_t)__builtin_amdgcn_readlane(bt_win, at + (kt + 16 <= last)) * p.stride_block;
+            row0[0] &= p.block_size - 1;
+            row0[1] &= p.block_size - 1;
         }
         const uint32_t lds = (uint32_t)(uintptr_t)(lds_void*)to;
+        if (kt + kTileKeys - 1 <= last) { // uniform: every row is there, so a load's address is uniform but for the lane's bytes
 #pragma unroll
-        for (int i = 0; i < BPS; ++i) {
-            int tok = min(kt + RPI * i + lrow, last);
-            if (p.paged) tok &= p.block_size - 1;
-            load_to_lds(lds + 1024 * i, base[2 * i / BPS], (uint32_t)(tok * stride_tok) * 2u + (ISV ? v_chunk : k_chunk ^ (uint32_t)(RPI * i % LPR * 16)));
+            for (int i = 0; i < BPS; ++i) {
+                const int h = 2 * i / BPS;
+                const char* from = (const char*)base[h] + (uint32_t)(row0[h] + RPI * (i % (BPS / 2))) * stride;
+                load_to_lds(lds + 1024 * i, from, ISV ? v_off : k_off[i % KV]);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < BPS; ++i) {
+                int tok = min(kt + RPI * i + lrow, last);
+                if (p.paged) tok &= p.block_size - 1;
+                load_to_lds(lds + 1024 * i, base[2 * i / BPS], (uint32_t)(tok - lrow) * stride + (ISV ? v_off : k_off[i % KV]));
+            }
         }
     };
     // ---- queries (every wave fetches its share of the pieces), rows, masks: requested ahead of
@@ -147,6 +170,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
         node[rb] = row_node(p, min(rb * kRowBlock + col, p.rows - 1)); // rows past the end repeat the last row
         mask[rb] = p.tree_mask && p.tree_keys != 0 ? p.tree_mask[(int64_t)b * p.T + node[rb]] : 0ull;
     }
+    // the gate of the (sequence, KV head), opened below
+    const MergeGate gate{p.gates ? p.gates + kGateWords * (int64_t)unit : nullptr, &sgen};
+    MergeSeen seen{};
+    if (p.gates && wave == 0) seen = merge_look(gate);
     if (first < kend) { // uniform per wave
         issue(std::false_type{}, sK, first, kend - 1);
         issue(std::true_type{}, sV, first, kend - 1);
@@ -170,8 +197,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     if (k0 >= nk) return;
     const bool final_rows = p.num_splits == 1 || (p.gates && nk <= p.keys_per_split); // a sequence of one split has nothing to merge
     const bool merge = p.gates && !final_rows;
-    const MergeGate gate{merge ? p.gates + kGateWords * (int64_t)unit : nullptr, &sgen};
-    if (merge && tid == 0) merge_open(gate);
+    if (merge && tid == 0) merge_open(gate, seen);
     const int k1 = min(nk, k0 + p.keys_per_split);
 
 #pragma unroll

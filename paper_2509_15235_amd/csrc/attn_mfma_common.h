@@ -51,16 +51,50 @@ __device__ __forceinline__ float visible_or_inf(float s, uint32_t w, int bit) {
     return __uint_as_float((__float_as_uint(s) & m) | (0xff800000u & ~m));
 }
 
-// node of query row r (r / group): the quotient is below 64, so the fp32 product is off by less than one
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv by, uint32_t& rem) {
+    uint32_t q = __umulhi(n, by.m);
+    rem = n - q * by.d;
+    if (rem >= by.d) {
+        rem -= by.d;
+        ++q;
+    }
+    return q;
+}
+// What a workgroup of a launch with equal splits works on. Consecutive ids go round-robin over the XCDs; the remap gives
+// every XCD a contiguous range, splits fastest: row groups and neighbouring splits of a (sequence, KV head) share its L2.
+struct WorkItem {
+    int b, kvh, rg, split;
+    bool none; // the last workgroups of a launch that is no multiple of eight
+};
+__device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
+    const uint32_t v = (blockIdx.x & 7) * (uint32_t)((p.total_wgs + 7) >> 3) + (blockIdx.x >> 3);
+    uint32_t split, rg, kvh;
+    const uint32_t b = fast_div(fast_div(fast_div(v, p.by_splits, split), p.by_groups, rg), p.by_heads, kvh);
+    return {(int)b, (int)kvh, (int)rg, (int)split, v >= (uint32_t)p.total_wgs};
+}
+
+// node of query row r (r / group). (r + 1/2) / group is 1 / (2 group) or more away from a whole number and the quotient is
+// below 64, so up to 16384 rows a node the fp32 error, 64 * 2^-23, is too small to matter; beyond, it is off by less than one.
 __device__ __forceinline__ int row_node(const AttnParams& p, int r) {
+    if (p.group <= 16384) return (int)fmaf((float)r, p.inv_group, 0.5f * p.inv_group);
     int n = (int)((float)r * p.inv_group);
     const int rem = r - n * p.group;
     n += (rem >= p.group) - (rem < 0);
     return n;
 }
-// element offset of query row r of (sequence b, KV head kvh) in q and out
+// Element offset of (sequence b, KV head kvh)'s first query row in q and out, uniform, and from there to 16-byte chunk `chunk`
+// of row r. A node's rows are adjacent, `node_stride` lies between two nodes' beyond that.
+template <int D>
+__device__ __forceinline__ int64_t row_start(const AttnParams& p, int b, int kvh) {
+    return ((int64_t)b * p.T * p.Hq + (int64_t)kvh * p.group) * D;
+}
+template <int D>
+__device__ __forceinline__ int64_t row_in(const AttnParams& p, int r, int node, int chunk) {
+    return (int64_t)((uint64_t)(uint32_t)node * (uint64_t)p.node_stride + (uint64_t)(uint32_t)(r * D + chunk * 8));
+}
+// the same as one offset
 __device__ __forceinline__ int64_t row_offset(const AttnParams& p, int b, int kvh, int r, int node) {
-    return (((int64_t)b * p.T + node) * p.Hq + kvh * p.group + (r - node * p.group)) * p.d;
+    return (((int64_t)b * p.T) * p.Hq + (int64_t)kvh * p.group) * p.d + ((int64_t)node * p.node_stride + (int64_t)r * p.d);
 }
 
 // The sequence of rank `rank` when the longest come first (at most 64 sequences, a lane each; out-of-range lengths sort
@@ -85,7 +119,7 @@ template <int D>
 __device__ __forceinline__ u32x4 load_q_piece(const AttnParams& p, int b, int kvh, int row_base, int i, int lane) {
     constexpr int LPR = D / 8, RPI = 64 / LPR;
     const int r = min(row_base + RPI * i + lane / LPR, p.rows - 1);
-    return *(const u32x4*)((const uint16_t*)p.q + row_offset(p, b, kvh, r, row_node(p, r)) + (lane % LPR) * 8);
+    return *(const u32x4*)((const uint16_t*)p.q + row_start<D>(p, b, kvh) + row_in<D>(p, r, row_node(p, r), lane % LPR));
 }
 template <int D>
 __device__ __forceinline__ void store_q_piece(uint16_t* sq, u32x4 v, int i, int lane) {
@@ -99,7 +133,7 @@ template <int D>
 __device__ __forceinline__ void copy_q_piece(const AttnParams& p, int b, int kvh, int row_base, uint16_t* sq, int i, int lane) {
     constexpr int LPR = D / 8, RPI = 64 / LPR;
     const int rl = RPI * i + lane / LPR, r = min(row_base + rl, p.rows - 1);
-    const uint16_t* src = (const uint16_t*)p.q + row_offset(p, b, kvh, r, row_node(p, r)) + ((lane % LPR) ^ (rl % LPR)) * 8;
+    const uint16_t* src = (const uint16_t*)p.q + row_start<D>(p, b, kvh) + row_in<D>(p, r, row_node(p, r), (lane % LPR) ^ (rl % LPR));
     __builtin_amdgcn_global_load_lds(src, (lds_void*)(sq + i * 512), 16, 0, 0);
 }
 template <int D>
@@ -146,6 +180,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_of(const void* base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00027000);
 }
 
+// The rows of a contiguous cache's slice (one sequence's KV head) from k0 on, at most a split and no further than the cache;
+// what lies past them reads as zeros. stride: bytes from row to row.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_of(const uint16_t* slice, int k0, const AttnParams& p, uint32_t stride) {
+    const int64_t left = p.capacity - k0;
+    const uint32_t rows = left < p.keys_per_split ? (uint32_t)left : (uint32_t)p.keys_per_split;
+    return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(slice) + (int64_t)k0 * stride, 0, (int)((rows - 1) * stride + (uint32_t)p.d * 2), 0x00027000);
+}
+
 // One 32-channel accumulator block of a row block, divided by the rows' sums: two 16-byte pieces per
 // lane. `blk` = piece 0 of the (unit, split, row block), db = channel block.
 template <bool MERGE = false>
@@ -189,10 +231,15 @@ struct MergeGate {
 __device__ __forceinline__ uint64_t gate_load(const uint64_t* w) {
     return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Thread 0 of every workgroup of the row group, any time before it arrives.
-__device__ __forceinline__ void merge_open(const MergeGate& g) {
-    *g.gen = gate_load(g.word + kGateFlag);
-    uint64_t w = gate_load(g.word);
+// Thread 0 of every workgroup of the row group, any time before it arrives. In two parts, because loads return in order:
+// asked for behind the tiles, the words come behind the tiles.
+struct MergeSeen {
+    uint64_t gen, word;
+};
+__device__ __forceinline__ MergeSeen merge_look(const MergeGate& g) { return {gate_load(g.word + kGateFlag), gate_load(g.word)}; }
+__device__ __forceinline__ void merge_open(const MergeGate& g, MergeSeen seen) {
+    *g.gen = seen.gen;
+    uint64_t w = seen.word;
     if ((w >> 40) != kMergeTag) // lost to another workgroup: then it did the same
         __hip_atomic_compare_exchange_strong(g.word, &w, kMergeZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -225,31 +272,48 @@ __device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, uint32_t wait
     }
     return 0;
 }
+__device__ __forceinline__ void merge_open(const MergeGate& g) { merge_open(g, merge_look(g)); }
 // Half a piece (eight channels of the 32 rows of a row block, see store_partial: the 32 lanes of one half of the
 // accumulators): where it is read and written. The addresses are worked out before the wait, the rest after it.
 constexpr int kMergeGroup = 4; // items a wave merges at once, at most
 struct MergeItem {
-    const float* ml;
-    const uint16_t* po;
-    uint16_t* out; // null: a row past the last one
+    uint32_t ml, po; // byte offsets in the row group's (max, sum) pairs and partial rows, uniform
+    uint16_t* out;   // null: a row past the last one
 };
 template <int D>
-__device__ __forceinline__ MergeItem merge_item(const AttnParams& p, int b, int kvh, int rbk, int half_piece, int lane) {
-    const int64_t unit = (int64_t)b * p.Hkv + kvh;
-    const int piece = half_piece >> 1, hl = half_piece & 1;
+__device__ __forceinline__ MergeItem merge_item(const AttnParams& p, int b, int kvh, int rb0, int i, int lane) {
+    constexpr int NP = D / 8; // half pieces per row block
+    const int rb = i / NP, piece = (i % NP) >> 1, hl = i & 1;
     MergeItem it;
-    it.ml = p.part_ml + ml_block(p, unit, 0, rbk) * 2;
-    it.po = p.part_o + part_block<D>(p, unit, 0, rbk) + piece * piece_stride(p) + hl * 256;
-    const int r = rbk * kRowBlock + (lane & 31);
+    it.ml = (uint32_t)(rb * p.num_splits) * (kRowBlock * 8);
+    it.po = (uint32_t)((rb * (D / 16) + piece) * p.num_splits) * 1024 + hl * 512;
+    const int r = (rb0 + rb) * kRowBlock + (lane & 31);
     it.out = r < p.rows ? (uint16_t*)p.out + row_offset(p, b, kvh, r, row_node(p, r)) + piece * 16 + 4 * hl + 8 * (lane >> 5) : nullptr;
     return it;
 }
-// log-sum-exp of G items over n splits, then the final rows' channels. One wave: lanes r and r + 32 share row r
-// and take every other split. BATCH pairs of splits of every item are in flight together; there is no branch around
-// a load (past the last split the last one is read again, with weight 0).
-template <int BATCH, int G>
-__device__ __forceinline__ void merge_run_by(const MergeItem (&it)[kMergeGroup], int n) {
+// Where a lane finds its splits of any item: lanes r and r + 32 share row r and take every other split (past the last
+// one the last is read again, with weight 0). Worked out before the wait, like the items.
+constexpr int kMergePairs = 8; // pairs of splits in flight, at most
+struct MergeLane {
+    uint32_t ml[kMergePairs], po[kMergePairs]; // byte offsets
+};
+__device__ __forceinline__ MergeLane merge_lane(int s0, int n) {
     const int row = threadIdx.x & 31, odd = (threadIdx.x >> 5) & 1;
+    MergeLane at;
+#pragma unroll
+    for (int u = 0; u < kMergePairs; ++u) {
+        const uint32_t s = (uint32_t)min(s0 + 2 * u + odd, n - 1);
+        at.ml[u] = s * (kRowBlock * 8) + row * 8;
+        at.po[u] = s * 1024 + row * 16;
+        asm("" : "+v"(at.ml[u]), "+v"(at.po[u]));
+    }
+    return at;
+}
+// log-sum-exp of G items over n splits, then the final rows' channels. One wave. BATCH pairs of splits of every item are
+// in flight together; there is no branch around a load.
+template <int BATCH, int G>
+__device__ __forceinline__ void merge_run_by(const MergeItem (&it)[kMergeGroup], const float* ml, const uint16_t* po, MergeLane at, int n) {
+    const int odd = (threadIdx.x >> 5) & 1;
     float M[G], den[G], num[G][8];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -258,18 +322,15 @@ __device__ __forceinline__ void merge_run_by(const MergeItem (&it)[kMergeGroup],
 #pragma unroll
         for (int e = 0; e < 8; ++e) num[g][e] = 0.f;
     }
-    for (int s0 = 0; s0 < n; s0 += 2 * BATCH) {
+    for (int s0 = 0;;) {
         u32x2 w[G][BATCH];
         u32x4 o[G][BATCH];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const __amdgpu_buffer_rsrc_t ml = span_of(it[g].ml), po = span_of(it[g].po);
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const int s = min(s0 + 2 * u + odd, n - 1);
-                w[g][u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(ml, s * (kRowBlock * 8) + row * 8, 0, kDeviceScope));
-                o[g][u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(po, s * 1024 + row * 16, 0, kDeviceScope));
-            }
+            for (int u = 0; u < BATCH; ++u) w[g][u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(span_of(ml), at.ml[u], it[g].ml, kDeviceScope));
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) o[g][u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(span_of(po), at.po[u], it[g].po, kDeviceScope));
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -296,6 +357,9 @@ __device__ __forceinline__ void merge_run_by(const MergeItem (&it)[kMergeGroup],
                 }
             }
         }
+        s0 += 2 * BATCH;
+        if (BATCH < kMergePairs || s0 >= n) break;
+        at = merge_lane(s0, n);
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -308,6 +372,13 @@ __device__ __forceinline__ void merge_run_by(const MergeItem (&it)[kMergeGroup],
         }
         if (it[g].out) *(u32x2*)it[g].out = pack_partial(r[0], r[1], r[2], r[3], 1.f / sum);
     }
+}
+template <int BATCH>
+__device__ __forceinline__ void merge_run_few(const MergeItem (&it)[kMergeGroup], int got, const float* ml, const uint16_t* po, MergeLane at, int n) {
+    if (got == 1) merge_run_by<BATCH, 1>(it, ml, po, at, n);
+    else if (got == 2) merge_run_by<BATCH, 2>(it, ml, po, at, n);
+    else if (got == 3) merge_run_by<BATCH, 3>(it, ml, po, at, n);
+    else merge_run_by<BATCH, 4>(it, ml, po, at, n);
 }
 // The end of a split's workgroup: all waves, after their last partial store. Row blocks rb0 .. rb1 - 1 belong to
 // the row group, n >= 2; `s_word` is two words of LDS that nobody else uses any more. What an item costs is the trip
@@ -322,15 +393,22 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
     int step = n * waves;
     const int most = n <= 4 ? kMergeGroup : n <= 8 ? 2 : 1; // items at once
     MergeItem it[kMergeGroup] = {};
-    auto gather = [&](int i) __attribute__((always_inline)) { // items i, i + step, ...; the last of them again past the end
-        it[0] = merge_item<D>(p, b, kvh, rb0 + i / NP, i % NP, lane);
-        if (most == 1 || i + step >= items) return;
+    int got = 0;
+    auto gather = [&](int i) __attribute__((always_inline)) { // items i, i + step, ... as far as there are
+        it[0] = merge_item<D>(p, b, kvh, rb0, i, lane);
+        got = 1;
 #pragma unroll
         for (int k = 1; k < kMergeGroup; ++k) {
-            const int at = min(i + k * step, items - 1);
-            it[k] = merge_item<D>(p, b, kvh, rb0 + at / NP, at % NP, lane);
+            const int at = i + k * step;
+            if (k >= most || at >= items) return;
+            it[k] = merge_item<D>(p, b, kvh, rb0, at, lane);
+            got = k + 1;
         }
     };
+    const MergeLane at = merge_lane(0, n);
+    const int64_t unit = (int64_t)b * p.Hkv + kvh;
+    const float* ml = p.part_ml + ml_block(p, unit, 0, rb0) * 2;
+    const uint16_t* po = p.part_o + part_block<D>(p, unit, 0, rb0);
     int i = split + n * wave;
     if (i < items) gather(i);
     __builtin_amdgcn_s_waitcnt(wait_vm(0)); // this wave's partial results are in memory
@@ -351,11 +429,10 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
     }
     for (;;) {
         while (i < items) {
-            const bool one = i + step >= items;
-            if (n <= 2) one ? merge_run_by<1, 1>(it, n) : merge_run_by<1, kMergeGroup>(it, n);
-            else if (n <= 4) one ? merge_run_by<2, 1>(it, n) : merge_run_by<2, kMergeGroup>(it, n);
-            else if (n <= 8) one ? merge_run_by<4, 1>(it, n) : merge_run_by<4, 2>(it, n);
-            else merge_run_by<8, 1>(it, n);
+            if (n > 8) merge_run_by<8, 1>(it, ml, po, at, n);
+            else if (n > 4) got == 1 ? merge_run_by<4, 1>(it, ml, po, at, n) : merge_run_by<4, 2>(it, ml, po, at, n);
+            else if (n > 2) merge_run_few<2>(it, got, ml, po, at, n);
+            else merge_run_few<1>(it, got, ml, po, at, n);
             i += most * step;
             if (i < items) gather(i);
         }

@@ -31,8 +31,16 @@ constexpr int kMergeMaxSplits = 32; // key splits that the workgroups themselves
 constexpr int kGateWords = 32;      // 64-bit words of a row group's gate: two cache lines, so that neither gates nor the two words of one
                                     // gate wait for each other
 constexpr int kGateFlag = 16;       // its second word
-constexpr int kResidentMaxKeys = 192; // keys of one split that the resident attention kernel keeps in LDS (six 32-key tiles:
-                                      // with eight, its four-row-block form runs out of registers)
+constexpr int kRoundKeys = 128;       // keys of a round (attention_mfma_rounds.hip)
+constexpr int kResidentMaxKeys = 192; // keys of one split that the resident attention kernel keeps in LDS
+constexpr int resident_max_keys(int row_blocks) { return row_blocks <= 2 ? 256 : kResidentMaxKeys; } // ... with so many row blocks to a workgroup
+
+// Division by a number that the host knows: one multiplication and one correction instead of the 45 instructions of a
+// 32-bit division (m = floor((2^32 - 1) / d): the product's upper half is the quotient or one less, for any n).
+struct FastDiv {
+    uint32_t d, m;
+};
+inline FastDiv fast_div_by(int32_t d) { return {(uint32_t)d, 0xffffffffu / (uint32_t)d}; }
 
 // Everything the attention kernels need, passed by value.
 struct AttnParams {
@@ -60,6 +68,7 @@ struct AttnParams {
     int64_t capacity;
     int64_t stride_seq, stride_block, stride_head, stride_tok;
     float inv_group;            // 1 / group (row_node)
+    int64_t node_stride;        // (Hq - group) * d (row_offset)
     float scale;                // softmax scale
     float scale_log2;           // softmax scale * log2(e)
     int32_t num_splits;         // grid extent over key splits
@@ -67,6 +76,7 @@ struct AttnParams {
     int32_t row_groups;
     int32_t rows_per_group;     // waves_per_group * row blocks per wave * kRowBlock
     int32_t total_wgs;          // B * Hkv * num_splits * row_groups
+    FastDiv by_splits, by_groups, by_heads; // workgroup id -> (sequence, KV head, row group, split)
     int32_t by_length;          // pipelined kernel without key splits: workgroups take the sequences longest first
     int32_t* bal_table;         // balanced schedule: 64 words of workspace, the share boundaries (main kernel -> combine)
     int32_t bal_chunks;         // balanced schedule: equal shares of the batch's keys per (KV head, row group); else 0.
