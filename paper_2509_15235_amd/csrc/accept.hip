@@ -2,12 +2,11 @@
 // survives iff it equals the target's argmax at its parent; the deepest surviving node
 // ends the accepted path and its own argmax is the bonus token.
 //
-// Two kernels: (1) a bandwidth-bound scan that reduces each logits row to per-chunk
-// (max, first index) pairs, (2) one workgroup per sequence that finishes the row argmax
-// and walks the tree.
+// Two kernels: (1) a bandwidth-bound scan that reduces every chunk of a logits row to (max, first index), (2) one workgroup
+// per sequence that finishes the row argmax and walks the tree.
 #include <atomic>
 
-#include "vs_device.h"
+#include "logits_scan.h"
 
 // Scratch of vs_tree_accept_noalloc: the per-(row, chunk) results that vs_tree_accept keeps in the
 // caller's workspace. One copy per GPU, held until the process ends. In host code the array's
@@ -19,8 +18,6 @@ static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
 namespace vs {
 
 namespace {
-
-constexpr int kVecPerThread = 4; // 16-byte loads per thread and chunk
 
 struct Best {
     float v;
@@ -43,149 +40,106 @@ __device__ __forceinline__ Best wave_best(Best b) {
     });
 }
 
-// grid = B*T*chunks, block = 256. Writes one (value, index) pair per (row, chunk).
-__global__ __launch_bounds__(kArgmaxBlock) void argmax_partial_kernel(const AcceptParams p) {
-    __shared__ float sv[kArgmaxBlock / kWave];
-    __shared__ int32_t si[kArgmaxBlock / kWave];
-    // one-dimensional grid: workgroup id = row * chunks + chunk (the host keeps the product below 2^31)
-    const int64_t row = blockIdx.x / (uint32_t)p.chunks;
-    const int chunk = (int)(blockIdx.x - (uint32_t)row * (uint32_t)p.chunks);
-    const float* __restrict__ lg = p.logits + row * p.ld;
-    const int begin = chunk * p.chunk_elems;
-    const int end = min(p.V, begin + p.chunk_elems);
-    // chunk_elems = 4 * kArgmaxBlock * kVecPerThread: every thread's loads are issued
-    // before the first compare. The maximum is found on values alone (one v_max per
-    // element); the index is recovered afterwards as the lowest position that equals the
-    // wave's maximum. NaN never equals anything and never survives fmaxf, -0 == +0.
-    const int nvec = (end - begin) >> 2;
-    f32x4 a[kVecPerThread];
+constexpr int kRowThreads = kScanThreads / VS_MAX_TREE; // threads of the walk that share a row's chunks
+static_assert(kRowThreads == 8, "three steps of a butterfly");
+
+// grid = B*T*chunks, block = THREADS: (max, first index) of a chunk. The maximum is found on values alone (one v_max per element);
+// the index is recovered afterwards as the lowest position that equals the wave's maximum. NaN never equals anything
+// and never survives fmaxf, -0 == +0.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const AcceptParams p) {
+    __shared__ float sv[THREADS / kWave];
+    __shared__ int32_t si[THREADS / kWave];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const ScanItem it = scan_item(p.chunks);
+    const ScanChunk c = scan_load<THREADS>(p.logits + (int64_t)it.row * p.ld, it.chunk, p.V);
+    float m = c.tail;
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j) {
-        const int k = threadIdx.x + j * kArgmaxBlock;
-        a[j] = (k < nvec) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    }
-    const int tail = begin + 4 * nvec + threadIdx.x; // at most three floats behind the last four
-    const float at = tail < end ? lg[tail] : -INFINITY;
-    float m = at;
+    for (int j = 0; j < kScanVec; ++j)
 #pragma unroll
-    for (int j = 0; j < kVecPerThread; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m = fmaxf(m, a[j][e]);
+        for (int e = 0; e < 4; ++e) m = fmaxf(m, c.a[j][e]);
     m = wave_max(m);
-    int32_t idx = (tail < end && at == m) ? tail : INT32_MAX;
+    int32_t idx = (c.tail_at != INT32_MAX && c.tail == m) ? c.tail_at : INT32_MAX;
 #pragma unroll
-    for (int j = kVecPerThread - 1; j >= 0; --j) {
-        const int k = threadIdx.x + j * kArgmaxBlock;
+    for (int j = kScanVec - 1; j >= 0; --j) {
+        const int k = tid + j * THREADS;
 #pragma unroll
         for (int e = 3; e >= 0; --e)
-            if (k < nvec && a[j][e] == m) idx = begin + 4 * k + e;
+            if (k < c.nvec && c.a[j][e] == m) idx = c.begin + 4 * k + e;
     }
-    Best best = {m, idx}; // the wave's maximum; lanes without it keep INT32_MAX and lose the tie
+    // a left-to-right '>' scan never displaces a NaN in column 0
+    const float first = c.nvec > 0 ? c.a[0][0] : c.tail;
+    if (it.chunk == 0 && tid == 0 && first != first) {
+        m = INFINITY;
+        idx = 0;
+    }
+    Best best = {m, idx}; // lanes without the wave's maximum keep INT32_MAX and lose the tie
     best = wave_best(best);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
         sv[wave] = best.v;
         si[wave] = best.i;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
 #pragma unroll
-        for (int w = 1; w < kArgmaxBlock / kWave; ++w) take(best, sv[w], si[w]);
-        p.part_val[row * p.chunks + chunk] = best.v;
-        p.part_idx[row * p.chunks + chunk] = best.i;
+        for (int w = 1; w < THREADS / kWave; ++w) take(best, sv[w], si[w]);
+        p.pairs[(int64_t)it.row * p.chunks + it.chunk] = ((uint64_t)(uint32_t)best.i << 32) | __float_as_uint(best.v);
     }
 }
 
-// grid = B, block = 256. Finishes the argmax of the sequence's T rows, then wave 0 walks
-// the tree (one lane per node).
-__global__ __launch_bounds__(256) void accept_walk_kernel(const AcceptParams p) {
-    __shared__ int32_t sp[VS_MAX_TREE];
-    __shared__ int32_t sflag;
+// grid = B, block = 512. Eight threads share a row's chunks, four pairs each in flight; the first wave holds the tree, a lane
+// per node, asked for with the pairs.
+__global__ __launch_bounds__(kScanThreads) void accept_walk_kernel(const AcceptParams p) {
     __shared__ int32_t samax[VS_MAX_TREE];
-    __shared__ int32_t spath[VS_MAX_TREE];
-    __shared__ int32_t sdraft[VS_MAX_TREE];
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int T = p.T;
-    // four threads per row share the row's chunk results (T <= 64 rows, 256 threads). Nothing here
-    // depends on the tree, so everything is requested before the tree is waited for (one memory
-    // round trip instead of two): the row's first logit (NaN rule), the draft tokens, and sixteen
-    // chunk results per thread (all of them for vocabularies up to 64 chunks).
-    constexpr int kPre = 16;
-    const int i = tid >> 2, sub = tid & 3;
-    const int64_t row = (int64_t)b * T + i;
-    const float* pv = p.part_val + row * p.chunks;
-    const int32_t* pi = p.part_idx + row * p.chunks;
-    float v[kPre];
-    int32_t x[kPre];
-    auto fetch = [&](int c0) {
-#pragma unroll
-        for (int q = 0; q < kPre; ++q) {
-            const int c = c0 + 4 * q;
-            const bool ok = i < T && c < p.chunks;
-            v[q] = ok ? pv[c] : -INFINITY;
-            x[q] = ok ? pi[c] : INT32_MAX;
-        }
-    };
-    fetch(sub);
-    const float first = (i < T && sub == 0) ? p.logits[row * p.ld] : 0.f;
-    const int32_t draft_own = (tid < T) ? p.draft[(int64_t)b * T + tid] : -1;
-    const int32_t tree_code = load_tree(p.parent + (int64_t)b * T, T, sp, &sflag);
-    if (tid < T) sdraft[tid] = draft_own;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int T = p.T, i = tid / kRowThreads, sub = tid % kRowThreads;
+    int32_t parent = -2, draft = -1;
+    if (tid < kWave) {
+        parent = tree_lane(p.parent + (int64_t)b * T, T);
+        draft = p.draft[(int64_t)b * T + min(lane, T - 1)];
+    }
     {
+        constexpr int kPre = 4;
+        const uint64_t* pairs = p.pairs + ((int64_t)b * T + min(i, T - 1)) * p.chunks;
         Best best = {-INFINITY, INT32_MAX};
-        for (int c0 = sub; c0 < p.chunks; c0 += 4 * kPre) {
-            if (c0 != sub) fetch(c0);
+        for (int c0 = sub; c0 < p.chunks; c0 += kRowThreads * kPre) {
+            uint64_t w[kPre];
 #pragma unroll
-            for (int q = 0; q < kPre; ++q) take(best, v[q], x[q]);
+            for (int q = 0; q < kPre; ++q) w[q] = pairs[min(c0 + kRowThreads * q, p.chunks - 1)]; // (the last one again: no harm)
+#pragma unroll
+            for (int q = 0; q < kPre; ++q) take(best, __uint_as_float((uint32_t)w[q]), (int32_t)(w[q] >> 32));
         }
         take(best, __uint_as_float(dpp<kDppXor1>(__float_as_uint(best.v))), (int32_t)dpp<kDppXor1>(best.i));
         take(best, __uint_as_float(dpp<kDppXor2>(__float_as_uint(best.v))), (int32_t)dpp<kDppXor2>(best.i));
+        take(best, __uint_as_float(dpp<kDppXor7>(dpp<kDppXor3>(__float_as_uint(best.v)))), (int32_t)dpp<kDppXor7>(dpp<kDppXor3>(best.i)));
         if (i < T && sub == 0) {
-            // what a left-to-right '>' scan returns: a NaN in column 0 is never displaced,
-            // and a row with nothing above -inf keeps index 0
-            int32_t idx = best.i;
-            if (first != first || idx == INT32_MAX) idx = 0;
+            const int32_t idx = best.i == INT32_MAX ? 0 : best.i; // nothing above -inf: index 0
             samax[i] = idx;
-            if (p.row_argmax) p.row_argmax[row] = idx;
-        }
-    }
-    if (tid < T) spath[tid] = -1;
-    __syncthreads();
-
-    int32_t best_node = 0, alen = 0;
-    if (wave == 0 && tree_code == VS_STATUS_OK) {
-        int32_t key = -1;
-        if (lane < T) {
-            bool ok = true;
-            int32_t dep = 0;
-            int j = lane;
-            while (j > 0) {
-                const int pj = sp[j];
-                ok = ok && (sdraft[j] == samax[pj]);
-                j = pj;
-                ++dep;
-            }
-            if (ok) key = dep * 64 + (63 - lane); // deepest first, then lowest index
-        }
-        key = wave_max(key);
-        best_node = 63 - (key & 63); // the root is always accepted, so key >= 63
-        alen = key >> 6;
-        if (lane == 0) {
-            int j = best_node;
-            for (int k = alen; k >= 0 && j >= 0; --k) {
-                spath[k] = j;
-                j = sp[j];
-            }
+            if (p.row_argmax) p.row_argmax[(int64_t)b * T + i] = idx;
         }
     }
     __syncthreads();
-    if (tid < T) p.path[(int64_t)b * T + tid] = spath[tid];
-    if (tid == 0) {
-        if (p.status) p.status[b] = tree_code;
-        const bool good = tree_code == VS_STATUS_OK;
-        p.accepted_len[b] = good ? alen : 0;
-        p.bonus[b] = good ? samax[best_node] : -1;
+    if (tid >= kWave) return;
+    const int32_t code = tree_check(parent, T);
+    int node = 0, alen = 0;
+    if (code == VS_STATUS_OK) {
+        // level by level: a node is accepted iff its token is its parent's argmax and its parent is accepted. The deepest
+        // accepted node ends the path, the lowest of several.
+        const bool match = lane > 0 && lane < T && draft == samax[parent < 0 ? 0 : parent];
+        uint64_t level = 1;
+        for (;;) {
+            level = __ballot(match && ((level >> (parent & 63)) & 1));
+            if (level == 0) break;
+            node = __builtin_ctzll(level);
+            ++alen;
+        }
+    }
+    const int32_t path = code == VS_STATUS_OK ? tree_path(parent, node, alen) : -1;
+    if (lane < T) p.path[(int64_t)b * T + lane] = path;
+    if (lane == 0) {
+        if (p.status) p.status[b] = code;
+        p.accepted_len[b] = alen;
+        p.bonus[b] = code == VS_STATUS_OK ? samax[node] : -1;
     }
 }
 
@@ -212,11 +166,16 @@ void* scratch_address() {
 
 } // namespace
 
-hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
-    hipLaunchKernelGGL(argmax_partial_kernel, dim3((unsigned)((int64_t)p.chunks * p.B * p.T)), dim3(kArgmaxBlock), 0, s, p);
-    hipError_t e = hipGetLastError();
+// workspace: 8 bytes per (row, chunk); sized by chunks half as long, it holds them with room to spare
+hipError_t launch_accept(AcceptParams p, void* workspace, hipStream_t s) {
+    p.chunks = (int32_t)(((int64_t)p.V + kScanChunk - 1) / kScanChunk);
+    p.pairs = (uint64_t*)workspace;
+    const dim3 grid((unsigned)((int64_t)p.chunks * p.B * p.T));
+    if (p.V <= kScanChunk / 2) hipLaunchKernelGGL(argmax_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);
+    else hipLaunchKernelGGL(argmax_partial_kernel<kScanThreads>, grid, dim3(kScanThreads), 0, s, p);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(accept_walk_kernel, dim3(p.B), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(accept_walk_kernel, dim3(p.B), dim3(kScanThreads), 0, s, p);
     return hipGetLastError();
 }
 
@@ -234,10 +193,6 @@ extern "C" int32_t vs_tree_accept_noalloc(const float* logits, int64_t ld_logits
     if (const int32_t dc = check_device()) return dc;
     unsigned char* ws = (unsigned char*)scratch_address();
     if (!ws) return VS_ERR_HIP;
-    // same layout as vs_tree_accept's workspace: values, then (256-byte aligned) indices. Nothing
-    // has to start at zero: the scan writes every pair the walk reads.
-    const int32_t chunks = (V + kAcceptChunk - 1) / kAcceptChunk;
-    const size_t n = (size_t)B * T * chunks;
     AcceptParams p{};
     p.logits = logits;
     p.ld = ld_logits;
@@ -251,9 +206,5 @@ extern "C" int32_t vs_tree_accept_noalloc(const float* logits, int64_t ld_logits
     p.bonus = bonus_token;
     p.row_argmax = row_argmax;
     p.status = status;
-    p.chunks = chunks;
-    p.chunk_elems = kAcceptChunk;
-    p.part_val = (float*)ws;
-    p.part_idx = (int32_t*)(ws + (n * sizeof(float) + 255) / 256 * 256);
-    return launch_accept(p, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
+    return launch_accept(p, ws, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
 }

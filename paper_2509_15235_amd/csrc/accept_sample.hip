@@ -5,217 +5,202 @@
 // with token x is accepted iff u_accept[c] < r(x), r being the target softmax at the
 // current node with the tokens rejected so far removed and the rest renormalised.
 //
-// Two kernels: (1) a bandwidth-bound scan that reduces each logits row to per-chunk
-// (maximum, sum of exp) pairs; (2) one workgroup per sequence that walks the tree on those
-// pairs alone - removing a token subtracts its weight from its chunk - and draws the bonus
-// token by inverting the residual's cumulative sum in index order: chunk sums first, then
-// one scan inside the chunk that holds the target. The second kernel touches the logits
-// only for the candidates' own entries, for that one chunk, and for a chunk whose sum a
-// removal cancelled (re-summed without the removed tokens).
-#include "vs_device.h"
+// Two kernels: (1) a bandwidth-bound scan that reduces every chunk of a logits row to (maximum, sum of exp); (2) one
+// workgroup per sequence that walks the tree on those pairs alone - removing a token subtracts its weight from its
+// chunk - and draws the bonus token by inverting the residual's cumulative sum in index order: chunk sums first,
+// then one scan inside the chunk that holds the target. The second kernel touches the logits only for the
+// candidates' own entries, for that one chunk, and for a chunk whose sum a removal cancelled (re-summed
+// without the removed tokens).
+#include "logits_scan.h"
 
 namespace vs {
 
 namespace {
 
-constexpr int kVec = 4;                  // 16-byte loads per thread and chunk (chunk = 4096 floats)
-constexpr int kWalkThreads = 256;
-constexpr int kKeepStats = 4096;          // (max, sum) pairs the walk kernel can keep in LDS (32 KB)
-constexpr int kPerThread = 16;           // chunk elements per thread of the walk kernel
-static_assert(kWalkThreads * kPerThread == 4096, "the walk kernel scans one 4096-float chunk at a time");
+constexpr int kScanWaves = kScanThreads / kWave;
+constexpr int kRowThreads = kScanThreads / VS_MAX_TREE; // threads of the walk that share a row's chunks
+static_assert(kRowThreads == 8, "three steps of a butterfly");
+constexpr int kKeepStats = 1536;          // pairs of a sequence that the walk keeps in LDS (12 KB: five workgroups on a CU still)
+constexpr int kPerThread = 16;            // chunk elements per thread of the walk
+static_assert(kScanThreads * kPerThread == kScanChunk && kScanChunk == 1 << 13, "the walk takes one chunk at a time");
 
-// grid = (chunks, B*T), block = 256: (max of the raw logits, sum of 2^((l - max) * k)) per chunk,
-// k = log2(e) / temperature.
-__global__ __launch_bounds__(kArgmaxBlock) void softmax_stats_partial_kernel(const SampleParams p) {
-    __shared__ float sm[kArgmaxBlock / kWave];
-    __shared__ float ss[kArgmaxBlock / kWave];
-    // one-dimensional grid: workgroup id = row * chunks + chunk (the host keeps the product below 2^31)
-    const int64_t row = blockIdx.x / (uint32_t)p.chunks;
-    const int chunk = (int)(blockIdx.x - (uint32_t)row * (uint32_t)p.chunks);
-    const float* __restrict__ lg = p.logits + row * p.ld;
-    const int begin = chunk * p.chunk_elems;
-    const int end = min(p.V, begin + p.chunk_elems);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    f32x4 a[kVec];
-    const int nvec = (end - begin) >> 2;
-    float m = -INFINITY;
+// grid = B*T*chunks, block = THREADS: (max of the raw logits, sum of 2^((l - max) * k)) of a chunk, k = log2(e) / temperature.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void softmax_stats_partial_kernel(const SampleParams p) {
+    constexpr int kWaves = THREADS / kWave;
+    __shared__ float sred[2][kWaves];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const ScanItem it = scan_item(p.chunks);
+    const ScanChunk c = scan_load<THREADS>(p.logits + (int64_t)it.row * p.ld, it.chunk, p.V);
+    float m = c.tail;
 #pragma unroll
-    for (int j = 0; j < kVec; ++j) {
-        const int k = threadIdx.x + j * kArgmaxBlock;
-        a[j] = (k < nvec) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int j = 0; j < kScanVec; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) m = fmaxf(m, a[j][e]);
-    }
-    for (int t = begin + 4 * nvec + threadIdx.x; t < end; t += kArgmaxBlock) m = fmaxf(m, lg[t]);
+        for (int e = 0; e < 4; ++e) m = fmaxf(m, c.a[j][e]);
     m = wave_max(m);
-    if (lane == 0) sm[wave] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
-    float s = 0.f;
+    float s = 0.f; // relative to the wave's maximum: one barrier for both
     if (m > -INFINITY) {
 #pragma unroll
-        for (int j = 0; j < kVec; ++j)
+        for (int j = 0; j < kScanVec; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s += __builtin_amdgcn_exp2f((a[j][e] - m) * p.k_log2); // exp2(-inf) = 0
-        for (int t = begin + 4 * nvec + threadIdx.x; t < end; t += kArgmaxBlock)
-            s += __builtin_amdgcn_exp2f((lg[t] - m) * p.k_log2);
+            for (int e = 0; e < 4; ++e) s += __builtin_amdgcn_exp2f((c.a[j][e] - m) * p.k_log2); // exp2(-inf) = 0
+        s += __builtin_amdgcn_exp2f((c.tail - m) * p.k_log2);
     }
     s = wave_sum(s);
-    if (lane == 0) ss[wave] = s;
+    if (lane == 0) {
+        sred[0][wave] = m;
+        sred[1][wave] = s;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        p.part_m[row * p.chunks + chunk] = m;
-        p.part_s[row * p.chunks + chunk] = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+    if (wave == 0) {
+        const float wm = lane < kWaves ? sred[0][lane] : -INFINITY;
+        m = wave_max(wm);
+        s = wave_sum(wm > -INFINITY ? sred[1][lane & (kWaves - 1)] * __builtin_amdgcn_exp2f((wm - m) * p.k_log2) : 0.f);
+        if (lane == 0) p.pairs[(int64_t)it.row * p.chunks + it.chunk] = ((uint64_t)__float_as_uint(s) << 32) | __float_as_uint(m);
     }
 }
 
-// grid = B, block = 256. Every thread runs the (short, sequential) walk on the same LDS
-// data, so its branches are uniform and the whole workgroup can turn to a chunk-wide pass
-// when one is needed. Everything the walk compares is fetched up front (row maxima and
-// masses, the uniforms, every candidate's weight in its parent's row), so a step of the walk
-// costs no memory round trip: removing a rejected token just lowers the row's mass. Only when
-// that subtraction would cancel (the rejected token held > 95 % of the mass), and once at the
-// end for the bonus draw, the row's per-chunk masses are needed - from the copy of all rows'
-// chunk statistics in LDS when those fit, else from memory.
-__global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const SampleParams p) {
-    __shared__ int32_t sp[VS_MAX_TREE];
-    __shared__ int32_t sflag;
+// grid = B, block = 512. Every wave runs the (short, sequential) walk on the same registers, so its branches are uniform and
+// the whole workgroup can turn to a chunk-wide pass when one is needed. Everything the walk compares is fetched up front
+// (row maxima and masses, the uniforms, every candidate's weight in its parent's row), so a step of the walk costs no
+// memory round trip: removing a rejected token just lowers the row's mass. Only when that subtraction would cancel (the
+// rejected token held > 95 % of the mass), and once at the end for the bonus draw, the row's per-chunk masses are
+// needed - from the copy of all rows' chunk statistics in LDS when those fit, else from memory.
+__global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const SampleParams p) {
+    __shared__ float sred[kScanWaves];
     __shared__ float sM[VS_MAX_TREE];      // row maxima
     __shared__ float sZ[VS_MAX_TREE];      // row masses relative to the maxima
-    __shared__ float sex[VS_MAX_TREE];     // weight of node c's token in its parent's row
-    __shared__ float su[VS_MAX_TREE];      // u_accept
-    __shared__ int32_t sdraft[VS_MAX_TREE];
-    __shared__ int32_t sremoved[VS_MAX_TREE];
-    __shared__ float sremoved_ex[VS_MAX_TREE];
-    __shared__ float sred[kWalkThreads / kWave];
+    __shared__ float slogit[VS_MAX_TREE];  // logit of node c's token in its parent's row
+    __shared__ float su[VS_MAX_TREE];
+    __shared__ int32_t sparent[VS_MAX_TREE], stoken[VS_MAX_TREE];
     __shared__ float sch[kMaxSampleChunks]; // residual weight per chunk of the current row
-    __shared__ float skeep_m[kKeepStats], skeep_s[kKeepStats]; // every row's chunk statistics, when they fit
-    __shared__ int32_t spick, slast;
+    __shared__ uint64_t skeep[kKeepStats];  // every row's chunk statistics, when they fit
+    __shared__ int32_t spick[kScanWaves], slast[kScanWaves];
     const int b = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T = p.T;
-    // Everything that does not depend on the tree is requested before the tree is waited for: the
-    // bonus uniform (used at the very end), this thread's draft token and acceptance uniform, and
-    // the first sixteen chunk statistics of this thread's row (four threads per row; one memory
-    // round trip covers vocabularies up to 64 chunks). Malformed trees are reported below; none
-    // of these addresses depends on the tree's contents.
+    // the first wave holds the tree and its draws, a lane per node, asked for ahead of the statistics
+    int32_t own_parent = -2, own_token = -1;
+    float own_u = 2.f;
+    if (wave == 0) {
+        own_parent = tree_lane(p.parent + (int64_t)b * T, T);
+        own_token = p.draft[(int64_t)b * T + min(lane, T - 1)];
+        own_u = p.u_accept[(int64_t)b * T + min(lane, T - 1)];
+    }
     const float u_bonus = p.u_bonus[b];
-    constexpr int kPre = 16;
-    const int ri = tid >> 2, sub = tid & 3;
-    const int64_t rrow = (int64_t)b * T + ri;
-    float pm[kPre], ps[kPre];
-    auto fetch_stats = [&](int c0) {
+    const int ri = tid / kRowThreads, sub = tid % kRowThreads;
+    const uint64_t* pairs = p.pairs + (int64_t)b * T * p.chunks;
+    constexpr int kPre = 4;
+    uint64_t w[kPre];
+    auto fetch = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < kPre; ++q) {
-            const int c = c0 + 4 * q;
-            const bool ok = ri < T && c < p.chunks;
-            pm[q] = ok ? p.part_m[rrow * p.chunks + c] : -INFINITY;
-            ps[q] = ok ? p.part_s[rrow * p.chunks + c] : 0.f;
-        }
+        for (int q = 0; q < kPre; ++q) w[q] = pairs[min(ri, T - 1) * p.chunks + min(c0 + kRowThreads * q, p.chunks - 1)];
     };
-    fetch_stats(sub);
-    const int32_t x_own = (tid < T) ? p.draft[(int64_t)b * T + tid] : -1;
-    const float u_own = (tid < T) ? p.u_accept[(int64_t)b * T + tid] : 0.f;
-    const int32_t tree_code = load_tree(p.parent + (int64_t)b * T, T, sp, &sflag);
-    // node tid's logit in the parent's row (parent index clamped: a malformed tree is reported
-    // below and must not steer a load out of bounds)
-    const bool has_logit = tid >= 1 && tid < T && x_own >= 0 && x_own < p.V;
-    float l_own = 0.f;
-    if (has_logit) {
-        const int par = min(max(sp[tid], 0), T - 1);
-        l_own = p.logits[((int64_t)b * T + par) * p.ld + x_own];
+    fetch(sub);
+    if (wave == 0) {
+        // the candidates' logits (parent index clamped: a malformed tree is reported below and must not steer a load out of bounds)
+        const bool has = lane >= 1 && lane < T && own_token >= 0 && own_token < p.V;
+        float l = -INFINITY;
+        if (has) l = p.logits[((int64_t)b * T + min(max(own_parent, 0), T - 1)) * p.ld + own_token];
+        sparent[lane] = own_parent;
+        stoken[lane] = has ? own_token : -1; // no candidate: weight 0, nothing to remove
+        su[lane] = own_u;
+        slogit[lane] = l;
     }
 
-    // ---- row maxima and masses, merged online. When all rows' chunk statistics fit (T * chunks
-    // <= kKeepStats) they also stay in LDS, so that the per-chunk masses a rejection or the bonus
-    // draw needs later cost no second trip to memory.
-    const bool keep = T * p.chunks <= kKeepStats;
+    // ---- row maxima and masses, merged online. When all rows' chunk statistics fit they also stay in LDS, so that the
+    // per-chunk masses a rejection or the bonus draw needs later cost no second trip to memory.
+    const bool keep = T * (int64_t)p.chunks <= kKeepStats;
     {
         float m = -INFINITY, z = 0.f;
-        for (int c0 = sub; c0 < p.chunks; c0 += 4 * kPre) {
-            if (c0 != sub) fetch_stats(c0);
-            if (keep) {
+        for (int c0 = sub; c0 < p.chunks; c0 += kRowThreads * kPre) {
+            if (c0 != sub) fetch(c0);
+            float pm[kPre], bm = m;
 #pragma unroll
-                for (int q = 0; q < kPre; ++q) {
-                    const int c = c0 + 4 * q;
-                    if (ri < T && c < p.chunks) {
-                        skeep_m[ri * p.chunks + c] = pm[q];
-                        skeep_s[ri * p.chunks + c] = ps[q];
-                    }
-                }
+            for (int q = 0; q < kPre; ++q) {
+                const int c = c0 + kRowThreads * q;
+                const bool ok = ri < T && c < p.chunks;
+                if (ok && keep) skeep[ri * p.chunks + c] = w[q];
+                pm[q] = ok ? __uint_as_float((uint32_t)w[q]) : -INFINITY;
+                bm = fmaxf(bm, pm[q]);
             }
-            float bm = m;
-#pragma unroll
-            for (int q = 0; q < kPre; ++q) bm = fmaxf(bm, pm[q]);
             if (bm > -INFINITY) {
                 z *= __builtin_amdgcn_exp2f((m - bm) * p.k_log2); // m = -inf: z is 0 and stays 0
 #pragma unroll
                 for (int q = 0; q < kPre; ++q)
-                    if (pm[q] > -INFINITY) z += ps[q] * __builtin_amdgcn_exp2f((pm[q] - bm) * p.k_log2);
+                    if (pm[q] > -INFINITY) z += __uint_as_float((uint32_t)(w[q] >> 32)) * __builtin_amdgcn_exp2f((pm[q] - bm) * p.k_log2);
                 m = bm;
             }
         }
-        float mm = fmaxf(m, __shfl_xor(m, 1));
-        mm = fmaxf(mm, __shfl_xor(mm, 2));
+        auto from = [](float x, auto step) __attribute__((always_inline)) { return __uint_as_float(step(__float_as_uint(x))); };
+        auto x1 = [](uint32_t x) __attribute__((always_inline)) { return dpp<kDppXor1>(x); };
+        auto x2 = [](uint32_t x) __attribute__((always_inline)) { return dpp<kDppXor2>(x); };
+        auto x4 = [](uint32_t x) __attribute__((always_inline)) { return dpp<kDppXor7>(dpp<kDppXor3>(x)); };
+        float mm = fmaxf(m, from(m, x1));
+        mm = fmaxf(mm, from(mm, x2));
+        mm = fmaxf(mm, from(mm, x4));
         if (m > -INFINITY) z *= __builtin_amdgcn_exp2f((m - mm) * p.k_log2);
-        z += __shfl_xor(z, 1);
-        z += __shfl_xor(z, 2);
+        z += from(z, x1);
+        z += from(z, x2);
+        z += from(z, x4);
         if (ri < T && sub == 0) {
             sM[ri] = mm;
             sZ[ri] = z;
         }
     }
-    if (tid < T) {
-        su[tid] = u_own;
-        sdraft[tid] = x_own;
-    }
     __syncthreads();
-    if (tree_code != VS_STATUS_OK) {
-        if (tid < T) p.path[(int64_t)b * T + tid] = -1;
-        if (tid == 0) {
+    const int32_t parent = sparent[lane], token = stoken[lane];
+    const int32_t tree_code = tree_check(parent, T);
+    if (tree_code != VS_STATUS_OK) { // uniform
+        if (wave != 0) return;
+        if (lane < T) p.path[(int64_t)b * T + lane] = -1;
+        if (lane == 0) {
             if (p.status) p.status[b] = tree_code;
             p.accepted_len[b] = 0;
             p.bonus[b] = -1;
         }
         return;
     }
-    // ---- every candidate's weight in its parent's row, one thread per node (the logit itself was
-    // requested at the top, together with the chunk statistics)
-    if (tid >= 1 && tid < T) {
-        const float Mp = sM[sp[tid]];
-        sex[tid] = (has_logit && Mp > -INFINITY) ? __builtin_amdgcn_exp2f((l_own - Mp) * p.k_log2) : 0.f;
-    }
-    __syncthreads();
+    // every candidate's weight in its parent's row
+    const float Mp = sM[max(parent, 0)], u_acc = su[lane];
+    const float ex_own = (token >= 0 && Mp > -INFINITY) ? __builtin_amdgcn_exp2f((slogit[lane] - Mp) * p.k_log2) : 0.f;
+    const float Z_own = sZ[min(lane, T - 1)];
+    auto lane_of = [](float x, int c) __attribute__((always_inline)) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, x), c)); };
 
-    // Sum of sch[0..chunks), the same value in every thread. Two barriers.
-    auto chunk_total = [&]() -> float {
-        float s = 0.f;
-        for (int c = tid; c < p.chunks; c += kWalkThreads) s += sch[c];
-        s = wave_sum(s);
-        __syncthreads(); // sred is free again
-        if (lane == 0) sred[wave] = s;
-        __syncthreads();
-        return (sred[0] + sred[1]) + (sred[2] + sred[3]);
-    };
-    // This thread's 16 consecutive weights of chunk c of row `node`, the first nrem removed tokens zeroed.
-    auto load_weights = [&](int node, int c, int nrem, float (&w)[kPerThread]) {
+    // This thread's 16 consecutive weights of chunk c of row `node`; the tokens of the nodes in `removed` weigh nothing.
+    auto load_weights = [&](int node, int c, uint64_t removed, float (&w)[kPerThread]) {
         const float* lg = p.logits + ((int64_t)b * T + node) * p.ld;
         const float M = sM[node];
-        const int j0 = c * p.chunk_elems + tid * kPerThread;
-        if (j0 + kPerThread <= p.V) {
+        const int j0 = c * kScanChunk + tid * kPerThread;
+        if (p.V >= 4) {
+            // four at a time, the row's last four at its end: there the wanted ones are moved to the front
+            f32x4 a[kPerThread / 4];
 #pragma unroll
-            for (int q = 0; q < kPerThread / 4; ++q) {
-                const f32x4 a = *(const f32x4_any*)(lg + j0 + 4 * q);
+            for (int q = 0; q < kPerThread / 4; ++q) a[q] = *(const f32x4_any*)(lg + min(j0 + 4 * q, p.V - 4));
+            if (__any(j0 + kPerThread > p.V)) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[4 * q + e] = __builtin_amdgcn_exp2f((a[e] - M) * p.k_log2);
+                for (int q = 0; q < kPerThread / 4; ++q) {
+                    const int by = j0 + 4 * q - (p.V - 4); // so many of the four lie before the wanted ones
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float x = by <= 0 ? a[q][e] : -INFINITY;
+#pragma unroll
+                        for (int d = 1; d < 4 - e; ++d) x = by == d ? a[q][e + d] : x;
+                        a[q][e] = x;
+                    }
+                }
             }
+#pragma unroll
+            for (int q = 0; q < kPerThread / 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[4 * q + e] = __builtin_amdgcn_exp2f((a[q][e] - M) * p.k_log2); // exp2(-inf) = 0
         } else {
 #pragma unroll
             for (int e = 0; e < kPerThread; ++e)
                 w[e] = (j0 + e < p.V) ? __builtin_amdgcn_exp2f((lg[j0 + e] - M) * p.k_log2) : 0.f;
         }
-        for (int r = 0; r < nrem; ++r) {
-            const int off = sremoved[r] - j0;
+        for (; removed != 0; removed &= removed - 1) {
+            const int off = __builtin_amdgcn_readlane(token, __builtin_ctzll(removed)) - j0;
             if ((unsigned)off < (unsigned)kPerThread) {
 #pragma unroll
                 for (int e = 0; e < kPerThread; ++e)
@@ -223,15 +208,27 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
             }
         }
     };
-    // Takes removed token r out of its chunk's mass (tokens 0..r are gone at that point).
-    auto remove_from_chunks = [&](int node, int r) {
-        const int xc = sremoved[r] / p.chunk_elems;
+    // Mass of chunk c of row `node`, nothing removed.
+    auto chunk_mass = [&](int node, int c) -> float {
+        const uint64_t ms = keep ? skeep[node * p.chunks + c] : pairs[(int64_t)node * p.chunks + c];
+        const float mc = __uint_as_float((uint32_t)ms);
+        return (mc > -INFINITY) ? __uint_as_float((uint32_t)(ms >> 32)) * __builtin_amdgcn_exp2f((mc - sM[node]) * p.k_log2) : 0.f;
+    };
+    // Sum of sch[0..chunks), the same value in every wave.
+    auto chunk_total = [&]() -> float {
+        float s = 0.f;
+        for (int c = lane; c < p.chunks; c += kWave) s += sch[c];
+        return wave_sum(s);
+    };
+    // Takes node c's token out of its chunk's mass in sch; `removed`: the nodes whose tokens are gone by then, c among them.
+    auto remove_from_chunks = [&](int node, int c, uint64_t removed) {
+        const int xc = __builtin_amdgcn_readlane(token, c) / kScanChunk;
         const float old = sch[xc];
-        float fresh = old - sremoved_ex[r];
+        float fresh = old - lane_of(ex_own, c);
         if (!(fresh >= 0.25f * old)) {
             // the subtraction cancelled most of the chunk: sum it again without the removed tokens
             float w[kPerThread];
-            load_weights(node, xc, r + 1, w);
+            load_weights(node, xc, removed, w);
             float s = 0.f;
 #pragma unroll
             for (int e = 0; e < kPerThread; ++e) s += w[e];
@@ -239,136 +236,149 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
             __syncthreads();
             if (lane == 0) sred[wave] = s;
             __syncthreads();
-            fresh = (sred[0] + sred[1]) + (sred[2] + sred[3]);
+            fresh = 0.f;
+#pragma unroll
+            for (int q = 0; q < kScanWaves; ++q) fresh += sred[q];
         }
         __syncthreads(); // every thread has read the old value
         if (tid == 0) sch[xc] = fresh;
         __syncthreads();
     };
-    // Per-chunk masses of row `node` with the first nrem removed tokens taken out; returns their sum.
-    auto materialize = [&](int node, int nrem) -> float {
-        const int64_t row = (int64_t)b * T + node;
-        const float M = sM[node];
+    // Per-chunk masses of row `node` in sch with the tokens of `removed` taken out in order; returns their sum.
+    auto materialize = [&](int node, uint64_t removed) -> float {
+        __syncthreads(); // sch may still be read
+        for (int c = tid; c < p.chunks; c += kScanThreads) sch[c] = chunk_mass(node, c);
         __syncthreads();
-        for (int c = tid; c < p.chunks; c += kWalkThreads) {
-            const float mc = keep ? skeep_m[node * p.chunks + c] : p.part_m[row * p.chunks + c];
-            const float sc = keep ? skeep_s[node * p.chunks + c] : p.part_s[row * p.chunks + c];
-            sch[c] = (mc > -INFINITY) ? sc * __builtin_amdgcn_exp2f((mc - M) * p.k_log2) : 0.f;
+        uint64_t gone = 0;
+        for (uint64_t r = removed; r != 0; r &= r - 1) {
+            gone |= r & -r;
+            remove_from_chunks(node, __builtin_ctzll(r), gone);
         }
-        __syncthreads();
-        for (int r = 0; r < nrem; ++r) remove_from_chunks(node, r);
         return chunk_total();
     };
 
-    // ---- the walk. Every wave runs it on registers: lane c holds node c's parent, draft token,
-    // weight and uniform (T <= 64), the children of the current node are a ballot, and a child's
-    // values are read with v_readlane - no LDS access and no dependent address per candidate
-    // (a scan over LDS copies cost ~100 clocks per tree node and step). The removed tokens of
-    // the current node sit one per lane for the duplicate check; LDS keeps the copy that the
-    // chunk-wide passes read.
-    const int32_t par_c = (lane < T) ? sp[lane] : -2;
-    const int32_t x_c = (lane < T) ? sdraft[lane] : -1;
-    const float ex_c = (lane >= 1 && lane < T) ? sex[lane] : 0.f;
-    const float u_c = (lane < T) ? su[lane] : 2.f;
-    int cur = 0, alen = 0, nrem = 0;
+    // ---- the walk: a lane per node. The children of the current node are considered in order, and all that come before
+    // the first accepted one are rejected: so the mass that each of them sees is the row's less a prefix sum over its
+    // earlier siblings, and the first that its uniform accepts is a ballot.
+    int cur = 0, alen = 0;
+    uint64_t removed = 0; // the rejected children of the current node whose tokens are out of its mass
     float Z = 0.f;
-    bool have_chunks = false;
+    bool have_chunks = false; // sch holds the current node's masses
     for (;;) {
-        Z = sZ[cur];
-        nrem = 0;
+        Z = lane_of(Z_own, cur);
         have_chunks = false;
-        int32_t rem_x = 0; // lane r < nrem: the r-th removed token
-        int next = -1;
-        uint64_t kids = __ballot(par_c == cur); // children in increasing node order
-        while (kids != 0 && next < 0) {
-            const int c = __builtin_ctzll(kids);
-            kids &= kids - 1;
-            const int32_t x = __builtin_amdgcn_readlane(x_c, c);
-            bool gone = x < 0 || x >= p.V;
-            gone = gone || __ballot(lane < nrem && rem_x == x) != 0;
-            const float ex = gone ? 0.f : __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, ex_c), c));
-            const float u = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, u_c), c));
-            const float prob = (Z > 0.f) ? ex / Z : 0.f;
-            if (u < prob) {
-                next = c;
-            } else if (!gone) {
-                __syncthreads(); // every thread has read the list
-                if (tid == 0) {
-                    sremoved[nrem] = x;
-                    sremoved_ex[nrem] = ex;
-                }
-                if (lane == nrem) rem_x = x;
-                ++nrem;
-                __syncthreads();
-                if (have_chunks) {
-                    remove_from_chunks(cur, nrem - 1);
-                    Z = chunk_total();
-                } else if (Z - ex >= 0.05f * Z) {
-                    Z -= ex;
-                } else {
-                    Z = materialize(cur, nrem);
-                    have_chunks = true;
+        const bool kid = parent == cur;
+        const uint64_t kids = __ballot(kid);
+        if (kids == 0) {
+            removed = 0;
+            break;
+        }
+        bool live = kid && token >= 0; // a token that an earlier sibling has is gone already
+        for (uint64_t k = kids & (kids - 1); k != 0; k &= k - 1) {
+            const int c = __builtin_ctzll(k);
+            if (__ballot(kid && lane < c && token == __builtin_amdgcn_readlane(token, c)) && lane == c) live = false;
+        }
+        const float ex = live ? ex_own : 0.f;
+        const float before = Z - (wave_scan(ex) - ex);
+        const float prob = before > 0.f ? ex / before : 0.f;
+        const uint64_t accepted = __ballot(kid && u_acc < prob);
+        const int first = accepted ? __builtin_ctzll(accepted) : kWave;
+        const uint64_t rejected = __ballot(live) & (accepted ? (1ull << first) - 1 : ~0ull);
+        int next = accepted ? first : -1;
+        if (rejected & __ballot(!(before - ex >= 0.05f * before))) {
+            // a rejected token holds almost all of what was left: one child after the other, the masses by chunk from there on
+            next = -1;
+            removed = 0;
+            for (uint64_t k = kids; k != 0 && next < 0; k &= k - 1) {
+                const int c = __builtin_ctzll(k);
+                const float e = lane_of(ex, c), pr = (Z > 0.f) ? e / Z : 0.f;
+                if (lane_of(u_acc, c) < pr) {
+                    next = c;
+                } else if ((__ballot(live) >> c) & 1) {
+                    removed |= 1ull << c;
+                    if (have_chunks) {
+                        remove_from_chunks(cur, c, removed);
+                        Z = chunk_total();
+                    } else if (Z - e >= 0.05f * Z) {
+                        Z -= e;
+                    } else {
+                        Z = materialize(cur, removed);
+                        have_chunks = true;
+                    }
                 }
             }
+        } else {
+            removed = rejected;
         }
         if (next < 0) break;
         cur = next;
         ++alen;
     }
-    if (!have_chunks) Z = materialize(cur, nrem);
 
-    // ---- bonus token: inverse of the residual's cumulative sum, index order
-    const float target = u_bonus * Z;
-    int kb = -1;
-    float before = 0.f;
-    {
-        // every thread scans the chunk sums the same way
-        float acc = 0.f;
-        int last_pos = -1;
-        for (int k = 0; k < p.chunks; ++k) {
-            const float cs = sch[k];
-            if (cs > 0.f) last_pos = k;
-            if (kb < 0 && acc + cs > target) {
-                kb = k;
-                before = acc;
+    // ---- bonus token: inverse of the residual's cumulative sum, index order. First the chunk; every wave finds it for itself,
+    // up to 64 chunks in registers unless a removal cancels one of them.
+    int kb = -1, last_pos = -1;
+    float target = 0.f, before = 0.f;
+    auto find_chunk = [&](float cs, int c0, float carry) __attribute__((always_inline)) { // returns the carry behind these chunks
+        const float inc = carry + wave_scan(cs);
+        const uint64_t pos = __ballot(cs > 0.f), over = __ballot(cs > 0.f && inc > target);
+        if (pos) last_pos = c0 + 63 - __builtin_clzll(pos);
+        if (over) {
+            const int l = __builtin_ctzll(over);
+            kb = c0 + l;
+            before = l == 0 ? carry : lane_of(inc, l - 1);
+        }
+        return lane_of(inc, 63);
+    };
+    bool in_lanes = p.chunks <= kWave && !have_chunks;
+    if (in_lanes) {
+        float cs = lane < p.chunks ? chunk_mass(cur, lane) : 0.f;
+        bool cancelled = false;
+        for (uint64_t r = removed; r != 0; r &= r - 1) {
+            const int c = __builtin_ctzll(r);
+            if (lane == __builtin_amdgcn_readlane(token, c) / kScanChunk) {
+                const float fresh = cs - lane_of(ex_own, c);
+                cancelled = cancelled || !(fresh >= 0.25f * cs);
+                cs = fresh;
             }
-            acc += cs;
         }
-        if (kb < 0) { // u * total rounded up to the whole mass: last token with weight
-            kb = last_pos;
-            before = -INFINITY;
+        in_lanes = !__any(cancelled);
+        if (in_lanes) {
+            target = u_bonus * wave_sum(cs);
+            find_chunk(cs, 0, 0.f);
         }
     }
-    if (tid == 0) {
-        spick = INT32_MAX;
-        slast = -1;
+    if (!in_lanes) {
+        if (!have_chunks) Z = materialize(cur, removed);
+        target = u_bonus * Z;
+        float carry = 0.f;
+        for (int c0 = 0; c0 < p.chunks && kb < 0; c0 += kWave) carry = find_chunk(c0 + lane < p.chunks ? sch[c0 + lane] : 0.f, c0, carry);
     }
-    __syncthreads();
+    if (kb < 0) { // u * total rounded up to the whole mass: last token with weight
+        kb = last_pos;
+        before = -INFINITY;
+    }
+    int32_t pick = -1;
     if (kb >= 0) {
         float w[kPerThread];
-        load_weights(cur, kb, nrem, w);
+        load_weights(cur, kb, removed, w);
         float s = 0.f;
+        int last = -1;
+        const int j0 = kb * kScanChunk + tid * kPerThread;
 #pragma unroll
-        for (int e = 0; e < kPerThread; ++e) s += w[e];
-        // inclusive scan of the threads' sums: inside the wave, then across the four waves
-        float inc = s;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const float up = __shfl_up(inc, o);
-            if (lane >= o) inc += up;
+        for (int e = 0; e < kPerThread; ++e) {
+            s += w[e];
+            if (w[e] > 0.f) last = j0 + e;
         }
+        // inclusive scan of the threads' sums: inside the wave, then across the waves
+        float inc = wave_scan(s);
+        __syncthreads(); // sred is free
         if (lane == 63) sred[wave] = inc;
         __syncthreads();
-        for (int wv = 0; wv < wave; ++wv) inc += sred[wv];
-        const float local = target - before; // +inf when the whole mass is below the target
-        const int j0 = kb * p.chunk_elems + tid * kPerThread;
-        int last = -1;
 #pragma unroll
-        for (int e = 0; e < kPerThread; ++e)
-            if (w[e] > 0.f) last = j0 + e;
-        // one LDS atomic per wave, not per thread (256 atomics on one address take microseconds)
-        const int wlast = wave_max(last);
-        if (lane == 0 && wlast >= 0) atomicMax(&slast, wlast);
+        for (int wv = 0; wv < kScanWaves; ++wv)
+            if (wv < wave) inc += sred[wv];
+        const float local = target - before; // +inf when the whole mass is below the target
         int cand = INT32_MAX;
         if (inc > local && last >= 0) {
             // first element of this thread whose running sum passes the target; the scan's and
@@ -382,23 +392,22 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
             }
             if (cand < 0) cand = last;
         }
-        cand = wave_min(cand);
-        if (lane == 0 && cand != INT32_MAX) atomicMin(&spick, cand);
-    }
-    __syncthreads();
-    // ---- results
-    if (tid < T) {
-        // path[k] = the ancestor of cur at depth k (cur's depth is alen)
-        int32_t node = -1;
-        if (tid <= alen) {
-            node = cur;
-            for (int k = alen; k > tid; --k) node = sp[node];
+        const int wcand = wave_min(cand), wlast = wave_max(last);
+        if (lane == 0) {
+            spick[wave] = wcand;
+            slast[wave] = wlast;
         }
-        p.path[(int64_t)b * T + tid] = node;
+        __syncthreads();
+        if (wave == 0) {
+            pick = wave_min(lane < kScanWaves ? spick[lane] : INT32_MAX);
+            if (pick == INT32_MAX) pick = wave_max(lane < kScanWaves ? slast[lane] : -1); // -1: no token carries weight (inputs must be finite)
+        }
     }
-    if (tid == 0) {
-        int32_t pick = spick;
-        if (pick == INT32_MAX) pick = slast; // -1: no token carries weight (inputs must be finite)
+    // ---- results
+    if (wave != 0) return;
+    const int32_t path = tree_path(parent, cur, alen);
+    if (lane < T) p.path[(int64_t)b * T + lane] = path;
+    if (lane == 0) {
         if (p.status) p.status[b] = VS_STATUS_OK;
         p.accepted_len[b] = alen;
         p.bonus[b] = pick;
@@ -407,11 +416,16 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
 
 } // namespace
 
-hipError_t launch_accept_sample(const SampleParams& p, hipStream_t s) {
-    hipLaunchKernelGGL(softmax_stats_partial_kernel, dim3((unsigned)((int64_t)p.chunks * p.B * p.T)), dim3(kArgmaxBlock), 0, s, p);
-    hipError_t e = hipGetLastError();
+// workspace: 8 bytes per (row, chunk); sized by chunks half as long, it holds them with room to spare
+hipError_t launch_accept_sample(SampleParams p, void* workspace, hipStream_t s) {
+    p.chunks = (p.V + kScanChunk - 1) / kScanChunk;
+    p.pairs = (uint64_t*)workspace;
+    const dim3 grid((unsigned)((int64_t)p.chunks * p.B * p.T));
+    if (p.V <= kScanChunk / 2) hipLaunchKernelGGL(softmax_stats_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);
+    else hipLaunchKernelGGL(softmax_stats_partial_kernel<kScanThreads>, grid, dim3(kScanThreads), 0, s, p);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(accept_sample_walk_kernel, dim3(p.B), dim3(kWalkThreads), 0, s, p);
+    hipLaunchKernelGGL(accept_sample_walk_kernel, dim3(p.B), dim3(kScanThreads), 0, s, p);
     return hipGetLastError();
 }
 

@@ -419,10 +419,8 @@ size_t workspace_bytes(const vs_attn_desc* d, const Plan& pl) {
            (merges_inside(d, pl) ? align_up((size_t)d->B * d->Hkv * pl.row_groups * kGateWords * sizeof(uint64_t)) : 0);
 }
 
-constexpr int kArgmaxChunk = kAcceptChunk;
-
 int32_t draft_chunks(int32_t V) { return (int32_t)(((int64_t)V + kDraftChunk - 1) / kDraftChunk); }
-int32_t accept_chunks(int32_t V) { return (V + kArgmaxChunk - 1) / kArgmaxChunk; }
+int32_t accept_chunks(int32_t V) { return (V + kAcceptChunk - 1) / kAcceptChunk; }
 
 } // namespace
 
@@ -644,16 +642,11 @@ int32_t vs_tree_accept(const float* logits, int64_t ld_logits, int32_t V, const 
     p.bonus = bonus_token;
     p.row_argmax = row_argmax;
     p.status = status;
-    p.chunks = accept_chunks(V);
-    p.chunk_elems = kArgmaxChunk;
-    const size_t n = (size_t)B * T * p.chunks;
-    p.part_val = (float*)workspace;
-    p.part_idx = (int32_t*)((char*)workspace + align_up(n * sizeof(float)));
-    return launch_accept(p, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
+    return launch_accept(p, workspace, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
 }
 
 size_t vs_accept_sample_workspace_bytes(int32_t B, int32_t T, int32_t V) {
-    if (B < 1 || T < 1 || T > VS_MAX_TREE || V < 1 || accept_chunks(V) > kMaxSampleChunks) return 0;
+    if (B < 1 || T < 1 || T > VS_MAX_TREE || V < 1 || accept_chunks(V) > 2 * kMaxSampleChunks) return 0;
     const size_t n = (size_t)B * T * accept_chunks(V);
     return 2 * align_up(n * sizeof(float));
 }
@@ -666,7 +659,7 @@ int32_t vs_tree_accept_sample(const float* logits, int64_t ld_logits, int32_t V,
     if (!logits || !draft_tokens || !parent || !u_accept || !u_bonus || !accepted_len || !path || !bonus_token)
         return VS_ERR_NULL;
     if (B < 1 || T < 1 || T > VS_MAX_TREE || V < 1 || ld_logits < V) return VS_ERR_SHAPE;
-    if (accept_chunks(V) > kMaxSampleChunks || (int64_t)B * T * accept_chunks(V) > kMaxGridX) return VS_ERR_SHAPE;
+    if (accept_chunks(V) > 2 * kMaxSampleChunks || (int64_t)B * T * accept_chunks(V) > kMaxGridX) return VS_ERR_SHAPE;
     if (!(temperature > 0.f) || !(temperature < INFINITY)) return VS_ERR_SHAPE;
     const size_t need = vs_accept_sample_workspace_bytes(B, T, V);
     if (!workspace || workspace_bytes_given < need || ((uintptr_t)workspace & (kAlign - 1))) return VS_ERR_WORKSPACE;
@@ -686,12 +679,7 @@ int32_t vs_tree_accept_sample(const float* logits, int64_t ld_logits, int32_t V,
     p.bonus = bonus_token;
     p.status = status;
     p.k_log2 = 1.4426950408889634f / temperature;
-    p.chunks = accept_chunks(V);
-    p.chunk_elems = kArgmaxChunk;
-    const size_t n = (size_t)B * T * p.chunks;
-    p.part_m = (float*)workspace;
-    p.part_s = (float*)((char*)workspace + align_up(n * sizeof(float)));
-    return launch_accept_sample(p, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
+    return launch_accept_sample(p, workspace, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
 }
 
 size_t vs_draft_expand_workspace_bytes(int32_t B, int32_t F, int32_t V, int32_t K) {

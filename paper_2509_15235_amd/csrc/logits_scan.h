@@ -1,0 +1,69 @@
+// What greedy and stochastic acceptance share: the scan of a logits row by workgroups of 8192 floats and the tree in
+// registers. Each is two kernels, the scan and a walk of one workgroup per sequence.
+// Chunks of 8192 floats on 512 threads: half as many results to merge as 4096 on 256 (16 x 60 x 152064 logits 99.1 -> 90.6 us greedy,
+// 107 -> 97 stochastic; 4 x 31 x 32003 9.4 -> 8.4 and 14.3 -> 13.4). One kernel, the last workgroup of a sequence walking its
+// tree, was 3 - 4 % faster still up to 256 workgroups and up to 60 % slower from 1024 on, where each lives longer than its loads
+// take (pair acknowledged, counter, end): not worth a second form.
+#pragma once
+
+#include "vs_device.h"
+
+namespace vs {
+
+// Workgroup id = row * chunks + chunk (the host keeps the product below 2^31); row counts over all sequences.
+struct ScanItem {
+    int row, chunk;
+};
+__device__ __forceinline__ ScanItem scan_item(int chunks) {
+    const uint32_t row = blockIdx.x / (uint32_t)chunks;
+    return {(int)row, (int)(blockIdx.x - row * (uint32_t)chunks)};
+}
+
+// A chunk of a row (THREADS: of the workgroup; a row of up to 4096 logits needs 256, and launches half as many waves): every
+// thread has 16 entries and perhaps one of the up to three behind the last four.
+struct ScanChunk {
+    f32x4 a[kScanVec];
+    float tail;
+    int32_t begin, nvec, tail_at; // tail_at: >= end when this thread has none
+};
+template <int THREADS>
+__device__ __forceinline__ ScanChunk scan_load(const float* lg, int chunk, int V) {
+    ScanChunk c;
+    c.begin = chunk * kScanChunk;
+    const int end = V - c.begin < kScanChunk ? V : c.begin + kScanChunk;
+    c.nvec = (end - c.begin) >> 2;
+#pragma unroll
+    for (int j = 0; j < kScanVec; ++j) {
+        const int k = threadIdx.x + j * THREADS;
+        c.a[j] = k < c.nvec ? load4_stream(lg + c.begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+    c.tail_at = c.begin + 4 * c.nvec + threadIdx.x;
+    c.tail = c.tail_at < end ? lg[c.tail_at] : -INFINITY;
+    if (c.tail_at >= end) c.tail_at = INT32_MAX;
+    return c;
+}
+
+// The tree, a lane per node, in every wave that asks. Rows past the tree: parent -2.
+__device__ __forceinline__ int32_t tree_lane(const int32_t* parent_row, int T) {
+    const int lane = threadIdx.x & 63;
+    const int32_t p = parent_row[lane < T ? lane : 0];
+    return lane < T ? p : -2;
+}
+// parent[0] == -1, 0 <= parent[i] < i (the whole wave calls it)
+__device__ __forceinline__ int32_t tree_check(int32_t parent, int T) {
+    const int lane = threadIdx.x & 63;
+    const bool bad_root = lane == 0 && parent != -1, bad_parent = lane > 0 && lane < T && (parent < 0 || parent >= lane);
+    return __ballot(bad_root) ? VS_STATUS_BAD_ROOT : (__ballot(bad_parent) ? VS_STATUS_BAD_PARENT : VS_STATUS_OK);
+}
+// lane k <= alen: the ancestor of `node` at depth k (node's own depth is alen); others -1
+__device__ __forceinline__ int32_t tree_path(int32_t parent, int node, int alen) {
+    const int lane = threadIdx.x & 63;
+    int32_t path = -1;
+    for (int k = alen; k >= 0; --k) {
+        if (lane == k) path = node;
+        node = __builtin_amdgcn_readlane(parent, node < 0 ? 0 : node);
+    }
+    return path;
+}
+
+} // namespace vs

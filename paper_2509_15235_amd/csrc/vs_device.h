@@ -1,6 +1,8 @@
 // Device-side helpers shared by the attention and acceptance kernels.
 #pragma once
 
+#include <type_traits>
+
 #include "vs_internal.h"
 
 namespace vs {
@@ -98,6 +100,22 @@ __device__ __forceinline__ int32_t wave_min(int32_t x) {
     return wave_all(x, [](int32_t a, int32_t b) { return min(a, b); });
 }
 
+// Sum of the lanes up to and including one's own (DPP: within rows of sixteen, then across them).
+__device__ __forceinline__ float wave_scan(float x) {
+    auto add = [](float v, uint32_t u) __attribute__((always_inline)) { return v + __uint_as_float(u); };
+    auto shifted = [](float v, auto ctrl, auto rows) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    };
+    using std::integral_constant;
+    x = add(x, shifted(x, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{})); // row_shr 1, 2, 4, 8
+    x = add(x, shifted(x, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{}));
+    x = add(x, shifted(x, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{}));
+    x = add(x, shifted(x, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{}));
+    x = add(x, shifted(x, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{})); // row_bcast 15 into rows 1 and 3
+    x = add(x, shifted(x, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{})); // row_bcast 31 into rows 2 and 3
+    return x;
+}
+
 // Sixteen bytes at any address that is a multiple of four (a row of logits need not start at a multiple of sixteen).
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;
 __device__ __forceinline__ f32x4 load4_stream(const float* p) { return __builtin_nontemporal_load((const f32x4_any*)p); }
@@ -114,11 +132,11 @@ __device__ __forceinline__ T load_device(const T* p) {
 // Who of n workgroups comes last. The word may hold anything before its first use (a value without the tag counts as
 // zero and is replaced before the first arrival) and is back at zero when the last one has come.
 constexpr uint64_t kArrivalZero = 0xffc3a57bull << 32; // a NaN: no partial result looks like this
-__device__ __forceinline__ void arrival_open(uint64_t* w) { // one thread of each, any time before it arrives
-    uint64_t v = load_device(w);
-    if ((v >> 32) != (kArrivalZero >> 32))
-        __hip_atomic_compare_exchange_strong(w, &v, kArrivalZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void arrival_open(uint64_t* w, uint64_t seen) { // one thread of each, any time before it arrives; seen: *w
+    if ((seen >> 32) != (kArrivalZero >> 32))
+        __hip_atomic_compare_exchange_strong(w, &seen, kArrivalZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void arrival_open(uint64_t* w) { arrival_open(w, load_device(w)); }
 __device__ __forceinline__ bool arrival_last(uint64_t* w, uint32_t n) { // that thread, when its workgroup's results are in memory
     const bool last = (uint32_t)__hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
     if (last) store_device(w, kArrivalZero);

@@ -23,8 +23,9 @@ constexpr int kTileKeys = 32;   // keys per MFMA score block of the attention ke
 constexpr int kIterKeys = 64;   // keys staged in LDS per loop iteration (two score blocks)
 constexpr int kRowBlock = 32;   // query rows per MFMA row block
 constexpr int kMaxWaves = 8;    // waves per workgroup in the MFMA attention kernel
-constexpr int kArgmaxBlock = 256;
-constexpr int kAcceptChunk = 4096; // floats of a logits row per workgroup of the scans: 256 threads x 4 x 16 bytes
+constexpr int kAcceptChunk = 4096; // what the acceptance workspaces are sized by: 8 bytes per row and so many logits
+constexpr int kScanThreads = 512, kScanVec = 4;              // acceptance: threads of a workgroup, 16-byte loads each
+constexpr int kScanChunk = kScanThreads * kScanVec * 4;      // ... and the floats of a logits row it takes
 constexpr int kBalMaxSeqs = 64;   // balanced schedule: sequences per call (a lane each)
 constexpr int kBalMaxChunks = 64; // ... and shares per (KV head, row group)
 constexpr int kMergeMaxSplits = 32; // key splits that the workgroups themselves merge (attn_mfma_common.h)
@@ -95,13 +96,11 @@ struct AcceptParams {
     int32_t* bonus;
     int32_t* row_argmax; // may be null
     int32_t* status;     // may be null
-    float* part_val;     // [B*T][chunks]
-    int32_t* part_idx;   // [B*T][chunks]
+    uint64_t* pairs;     // [B*T][chunks] (value, index)
     int32_t chunks;
-    int32_t chunk_elems; // multiple of 4
 };
 
-constexpr int kMaxSampleChunks = 2048; // chunk sums of one logits row kept in LDS by the sampling walk
+constexpr int kMaxSampleChunks = 1024; // chunk sums of one logits row kept in LDS by the sampling walk
 
 struct SampleParams {
     const float* logits;
@@ -116,11 +115,9 @@ struct SampleParams {
     int32_t* path;
     int32_t* bonus;
     int32_t* status;       // may be null
-    float* part_m;         // [B*T][chunks] chunk maximum of the raw logits
-    float* part_s;         // [B*T][chunks] sum of 2^((l - chunk maximum) * k_log2)
+    uint64_t* pairs;       // [B*T][chunks] chunk maximum of the raw logits, sum of 2^((l - chunk maximum) * k_log2)
     float k_log2;          // log2(e) / temperature
     int32_t chunks;
-    int32_t chunk_elems;   // 4096
 };
 
 constexpr int kDraftChunk = 8192;     // floats of a logits row per workgroup of an expansion: 512 threads x 4 x 16 bytes
@@ -208,8 +205,8 @@ hipError_t launch_attention_mfma_resident(const AttnParams& p, int row_blocks, h
 hipError_t launch_attention_mfma_rows(const AttnParams& p, int waves, hipStream_t s);
 hipError_t launch_attention_mfma_rounds(const AttnParams& p, int row_blocks, hipStream_t s);
 hipError_t launch_attention_combine(const AttnParams& p, int dtype, hipStream_t s);
-hipError_t launch_accept(const AcceptParams& p, hipStream_t s);
-hipError_t launch_accept_sample(const SampleParams& p, hipStream_t s);
+hipError_t launch_accept(AcceptParams p, void* workspace, hipStream_t s);        // sets pairs, chunks
+hipError_t launch_accept_sample(SampleParams p, void* workspace, hipStream_t s); // likewise
 hipError_t launch_draft_expand(const DraftExpandParams& p, hipStream_t s);
 hipError_t launch_draft_tree_build(const DraftBuildParams& p, hipStream_t s);
 hipError_t launch_kv_commit(const CommitParams& p, hipStream_t s);
