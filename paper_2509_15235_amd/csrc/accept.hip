@@ -51,7 +51,7 @@ __global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const Accept
     __shared__ float sv[THREADS / kWave];
     __shared__ int32_t si[THREADS / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const ScanItem it = scan_item(p.chunks);
+    const ScanItem it = scan_item(p.by_chunks);
     const ScanChunk c = scan_load<THREADS>(p.logits + (int64_t)it.row * p.ld, it.chunk, p.V);
     float m = c.tail;
 #pragma unroll
@@ -169,6 +169,7 @@ void* scratch_address() {
 // workspace: 8 bytes per (row, chunk); sized by chunks half as long, it holds them with room to spare
 hipError_t launch_accept(AcceptParams p, void* workspace, hipStream_t s) {
     p.chunks = (int32_t)(((int64_t)p.V + kScanChunk - 1) / kScanChunk);
+    p.by_chunks = fast_div_by(p.chunks);
     p.pairs = (uint64_t*)workspace;
     const dim3 grid((unsigned)((int64_t)p.chunks * p.B * p.T));
     if (p.V <= kScanChunk / 2) hipLaunchKernelGGL(argmax_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(THREADS, 8) void softmax_stats_partial_kernel(const
     constexpr int kWaves = THREADS / kWave;
     __shared__ float sred[2][kWaves];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const ScanItem it = scan_item(p.chunks);
+    const ScanItem it = scan_item(p.by_chunks);
     const ScanChunk c = scan_load<THREADS>(p.logits + (int64_t)it.row * p.ld, it.chunk, p.V);
     float m = c.tail;
 #pragma unroll
@@ -419,6 +419,7 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
 // workspace: 8 bytes per (row, chunk); sized by chunks half as long, it holds them with room to spare
 hipError_t launch_accept_sample(SampleParams p, void* workspace, hipStream_t s) {
     p.chunks = (p.V + kScanChunk - 1) / kScanChunk;
+    p.by_chunks = fast_div_by(p.chunks);
     p.pairs = (uint64_t*)workspace;
     const dim3 grid((unsigned)((int64_t)p.chunks * p.B * p.T));
     if (p.V <= kScanChunk / 2) hipLaunchKernelGGL(softmax_stats_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);

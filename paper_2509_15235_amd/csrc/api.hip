@@ -717,16 +717,15 @@ int32_t vs_draft_expand(const float* logits, int64_t ld_logits, int32_t V, const
     p.next_frontier_cand = next_frontier_cand;
     p.next_cum = next_cum;
     p.chunks = draft_chunks(V);
+    p.by_chunks = fast_div_by(p.chunks);
+    p.by_F = fast_div_by(F);
+    p.by_K = fast_div_by(K);
     const size_t n = (size_t)B * F * p.chunks;
     char* w = (char*)workspace;
-    p.part_m = (float*)w;
-    w += align_up(n * sizeof(float));
-    p.part_s = (float*)w;
-    w += align_up(n * sizeof(float));
-    p.part_tv = (float*)w;
-    w += align_up(n * K * sizeof(float));
-    p.part_ti = (int32_t*)w;
-    w += align_up(n * K * sizeof(float));
+    p.part_ms = (uint64_t*)w;
+    w += align_up(n * sizeof(uint64_t));
+    p.part_top = (uint64_t*)w;
+    w += align_up(n * K * sizeof(uint64_t));
     p.arrivals = (uint64_t*)w;
     return launch_draft_expand(p, (hipStream_t)stream) == hipSuccess ? VS_OK : VS_ERR_HIP;
 }

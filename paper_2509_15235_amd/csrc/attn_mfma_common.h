@@ -51,15 +51,6 @@ __device__ __forceinline__ float visible_or_inf(float s, uint32_t w, int bit) {
     return __uint_as_float((__float_as_uint(s) & m) | (0xff800000u & ~m));
 }
 
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv by, uint32_t& rem) {
-    uint32_t q = __umulhi(n, by.m);
-    rem = n - q * by.d;
-    if (rem >= by.d) {
-        rem -= by.d;
-        ++q;
-    }
-    return q;
-}
 // What a workgroup of a launch with equal splits works on. Consecutive ids go round-robin over the XCDs; the remap gives
 // every XCD a contiguous range, splits fastest: row groups and neighbouring splits of a (sequence, KV head) share its L2.
 struct WorkItem {

@@ -12,8 +12,9 @@
 // (2) One workgroup per sequence for the final selection, which emits parent[] / tokens[] in candidate order.
 //
 // Selection without bookkeeping: entries are taken in the strict total order (value descending, index
-// ascending). A bound that at least K entries reach is found bit by bit with ballots, the few entries at or
-// above it are compacted and ranked by counting; nothing has to be marked as taken.
+// ascending), as integers of 64 bits, also between the workgroups. A bound that at least K entries reach is found
+// from the largest of every lane or group of lanes, the few entries at or above it are compacted and ranked by
+// counting; nothing has to be marked as taken.
 #include <type_traits>
 
 #include "vs_device.h"
@@ -28,22 +29,24 @@ constexpr int kExpandThreads = 512;
 constexpr int kExpandWaves = kExpandThreads / kWave;
 static_assert(kDraftChunk == kExpandThreads * kVec * 4, "a chunk is one set of loads");
 
-struct Ent {
-    float v;
-    int32_t i;
-};
-
 // a comes strictly before b in (value descending, index ascending)
 __device__ __forceinline__ bool before(float av, int32_t ai, float bv, int32_t bi) {
     return av > bv || (av == bv && ai < bi);
 }
 
-__device__ __forceinline__ Ent wave_first(Ent e) {
-    return wave_all(e, [](Ent x, Ent y) { return before(y.v, y.i, x.v, x.i) ? y : x; });
+constexpr int kGroups = kExpandThreads / 16; // rows of lanes of a workgroup
+static_assert(kMaxDraftK <= kGroups && kGroups == 32, "K groups, a lane each");
+// maximum over the 16 lanes of a row, in all of them (the first steps of wave_max, in another order)
+__device__ __forceinline__ float group_max(float x) {
+    auto with = [](float v, uint32_t u) __attribute__((always_inline)) { return fmaxf(v, __uint_as_float(u)); };
+    x = with(x, dpp<kDppXor8>(__float_as_uint(x)));
+    x = with(x, dpp<kDppXor7>(dpp<kDppXor3>(__float_as_uint(x))));
+    x = with(x, dpp<kDppXor2>(__float_as_uint(x)));
+    return with(x, dpp<kDppXor1>(__float_as_uint(x)));
 }
 
-constexpr int32_t kNone = INT32_MAX; // index of "no entry": loses every comparison at value -inf
 constexpr int kCandCap = 128;        // entries of a wave's candidate list in LDS
+constexpr int kListPad = 16, kListLen = kCandCap + kListPad;
 
 // Larger float -> larger key (no NaN), -0 below +0; every real key is > 0, which stands for "no entry".
 __device__ __forceinline__ uint32_t order_key(float v) {
@@ -56,167 +59,252 @@ __device__ __forceinline__ float key_value(uint32_t k) {
 
 // The same with signed zeros equal (-0 + 0 = +0), as `before` has them: for keys that are compared with each other.
 __device__ __forceinline__ uint32_t rank_key(float v) { return order_key(v + 0.f); }
-// An entry as one integer: larger = earlier in (value descending, index ascending).
+// An entry as one integer: larger = earlier in (value descending, index ascending); 0 is no entry.
 __device__ __forceinline__ uint64_t entry_key(float v, int32_t i) { return ((uint64_t)rank_key(v) << 32) | (uint32_t)~i; }
+// The same in an expansion, where NaN is never taken.
+__device__ __forceinline__ uint64_t child_key(float v, int32_t i) { return v == v ? entry_key(v, i) : 0; }
 __device__ __forceinline__ float entry_value(uint64_t k) { return key_value((uint32_t)(k >> 32)); }
 __device__ __forceinline__ int32_t entry_index(uint64_t k) { return (int32_t)~(uint32_t)k; }
 
-// The first K of a wave's entries in (value descending, index ascending); every lane passes NE
-// entries v[e] with index idx(e) (kNone = none). emit(rank, value, index) is called once per rank 0..K-1 by
-// some lane; ranks past the number of entries get (-inf, kNone).
-// How: the K-th largest of the lanes' own maxima (found bit by bit with ballots) is a lower
-// bound of the K-th largest entry, so the entries at or above it are a small superset of the
-// answer; they are compacted into the wave's LDS list and ranked by counting. A plateau of
-// equal values or a nearly empty wave can overflow the list: then the entries are extracted
-// one by one instead. No workgroup barrier inside; the list is private to the wave.
-template <int NE, typename Idx, typename Emit>
-__device__ __forceinline__ void wave_topk(const float (&v)[NE], Idx idx, int K, uint64_t* list, Emit emit) {
+// A key that at least K of the lanes' keys reach and that few more do; 0 if fewer than K lanes have one (keys are > 0). From
+// the largest key down in growing steps, then by halves until at most K + 8 reach it: 4 or 5 ballots for a row of logits,
+// where the bits of the bound one by one took 16. (Down to 2^16, the last seven bits of the mantissa's upper half.)
+__device__ __forceinline__ uint32_t kth_bound(uint32_t key, int K) {
+    auto reach = [&](uint32_t k) __attribute__((always_inline)) { return (int)__popcll(__ballot(key >= k)); };
+    if (reach(1) < K) return 0;
+    uint32_t hi = wave_all(key, [](uint32_t a, uint32_t b) { return max(a, b); }), lo = 0;
+    int n = kWave; // lanes that reach lo
+    for (uint32_t step = 1u << 23; hi > step; step <<= 2) {
+        const int c = reach(hi - step);
+        if (c >= K) {
+            lo = hi - step;
+            n = c;
+            break;
+        }
+        hi -= step;
+        if (step >= 1u << 29) break;
+    }
+    while (n > K + 8 && hi - lo > 0xffffu) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        const int c = reach(mid);
+        if (c >= K) {
+            lo = mid;
+            n = c;
+        } else {
+            hi = mid;
+        }
+    }
+    return lo;
+}
+// Ranks the n <= kCandCap keys of a wave's list by counting, sixteen at a time (read by all lanes at once; behind the list is
+// room for as many zeros). emit(rank, key) once per rank 0..K-1 by some lane, key 0 past the last entry.
+typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+template <typename Emit>
+__device__ __forceinline__ void rank_list(uint64_t* list, int n, int K, Emit emit) {
+    const int lane = threadIdx.x & 63;
+    if (lane < kListPad) list[n + lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the list is read by other lanes of this wave
+    for (int t = lane; t < ((n + kWave - 1) & ~(kWave - 1)); t += kWave) {
+        const uint64_t k = list[t < n ? t : n];
+        int rank = 0;
+        for (int o = 0; o < n; o += kListPad) {
+#pragma unroll
+            for (int e = 0; e < kListPad; e += 2) {
+                const u64x2 x = *(const u64x2*)&list[o + e];
+                rank += (x[0] > k ? 1 : 0) + (x[1] > k ? 1 : 0);
+            }
+        }
+        if (t < n && rank < K) emit(rank, k);
+    }
+    if (n < K && lane >= n && lane < K) emit(lane, 0);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // reads done before the list is reused
+}
+
+// The K largest of a wave's keys (every lane passes NE, 0: none): emit(rank, key) as rank_list does.
+// How: a bound that K of the lanes' own largest reach is a lower bound of the K-th largest, so the keys that reach it are a
+// small superset of the answer; they are compacted into the wave's LDS list and ranked by counting. A plateau of equal
+// values or a nearly empty wave can overflow the list: then the keys are extracted one by one instead. No workgroup barrier
+// inside; the list is private to the wave.
+template <int NE, typename Emit>
+__device__ __forceinline__ void wave_topk(const uint64_t (&key)[NE], int K, uint64_t* list, Emit emit) {
     const int lane = threadIdx.x & 63;
     uint32_t best = 0;
 #pragma unroll
-    for (int e = 0; e < NE; ++e)
-        if (idx(e) != kNone) best = max(best, order_key(v[e]));
-    // (the upper sixteen bits of the bound are enough: it only has to be one that K lanes reach and few entries do)
-    uint32_t res = 0;
-#pragma unroll
-    for (int bit = 31; bit >= 16; --bit) {
-        const uint32_t trial = res | (1u << bit);
-        if (__popcll(__ballot(best >= trial)) >= K) res = trial;
-    }
-    // res below the key of -inf: fewer than K lanes hold entries, or nothing above -inf bounds them
-    const float tau = res > 0x007fffffu ? key_value(res) : -INFINITY;
+    for (int e = 0; e < NE; ++e) best = max(best, (uint32_t)(key[e] >> 32));
+    const uint32_t bound = max(kth_bound(best, K), 1u);
     int n = 0;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
-        const bool pred = v[e] >= tau && idx(e) != kNone;
-        const uint64_t mask = __ballot(pred);
-        if (mask == 0) continue; // most of the time
+        const bool in = (uint32_t)(key[e] >> 32) >= bound;
+        const uint64_t mask = __ballot(in);
         const int pos = n + __popcll(mask & ((1ull << lane) - 1ull));
-        if (pred && pos < kCandCap) list[pos] = entry_key(v[e], idx(e));
+        if (in && pos < kCandCap) list[pos] = key[e];
         n += __popcll(mask);
     }
     if (n <= kCandCap) {
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the list is read by other lanes of this wave
-        if (n <= kWave) { // one entry per lane, the others' by v_readlane
-            const uint64_t k = lane < n ? list[lane] : 0;
-            int rank = 0;
-            for (int o = 0; o < n; ++o) {
-                const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)k, o), hi = __builtin_amdgcn_readlane((uint32_t)(k >> 32), o);
-                rank += (((uint64_t)hi << 32) | lo) > k ? 1 : 0;
-            }
-            if (lane < n && rank < K) emit(rank, entry_value(k), entry_index(k));
-        } else {
-            for (int t = lane; t < n; t += kWave) {
-                const uint64_t k = list[t];
-                int rank = 0;
-                for (int o = 0; o < n; ++o) rank += list[o] > k ? 1 : 0;
-                if (rank < K) emit(rank, entry_value(k), entry_index(k));
-            }
-        }
-        for (int r = n + lane; r < K; r += kWave) emit(r, -INFINITY, kNone);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // reads done before the list is reused
+        rank_list(list, n, K, emit);
     } else {
-        float last_v = INFINITY;
-        int32_t last_i = -1;
+        uint64_t last = ~0ull;
         for (int r = 0; r < K; ++r) {
-            Ent mine = {-INFINITY, kNone};
+            uint64_t mine = 0;
 #pragma unroll
             for (int e = 0; e < NE; ++e)
-                if (idx(e) != kNone && before(last_v, last_i, v[e], idx(e)) && before(v[e], idx(e), mine.v, mine.i))
-                    mine = {v[e], idx(e)};
-            const Ent w = wave_first(mine);
-            if (lane == 0) emit(r, w.v, w.i);
-            last_v = w.v;
-            last_i = w.i;
+                if (key[e] < last && key[e] > mine) mine = key[e];
+            last = wave_all(mine, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
+            if (lane == 0) emit(r, last);
         }
     }
 }
 
-// grid = B * F * chunks, block = 512.
+// grid = B * F * chunks, block = 512. Bound by its serial chain: a level of 2 x 8 x 152064 logits takes 12.8 us, of which the
+// logits are 2.5 at the rate of a large copy; bound and list of a chunk's first entries are about 2.5 us of the rest, the
+// last workgroup's part 4. One list for the whole workgroup with the K-th largest of 32 groups as its bound, sixteen keys
+// ranked a step and chunk lists of 64-bit keys took three such levels and the final selection from 43.2 to 37.8 us
+// (a list per wave, merged; value and index apart), 8 x 16 x 152064 in five levels from 238 to 192.
 __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const DraftExpandParams p) {
     __shared__ float s_m[kExpandWaves], s_s[kExpandWaves];
-    __shared__ uint64_t s_list[kExpandWaves * kCandCap];
-    __shared__ float s_wv[kExpandWaves * kMaxDraftK];
-    __shared__ int32_t s_wi[kExpandWaves * kMaxDraftK];
+    __shared__ __attribute__((aligned(16))) uint64_t s_list[kExpandWaves * kListLen];
+    __shared__ uint64_t s_wave[kExpandWaves * kMaxDraftK];
     __shared__ float s_score[kMaxDraftCand];
     __shared__ int32_t s_token[kMaxDraftCand];
-    __shared__ int32_t s_last;
+    __shared__ __attribute__((aligned(16))) uint32_t s_group[kGroups];
+    __shared__ int32_t s_last, s_n;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int F = p.F, K = p.K;
     int b;
     {
         // workgroup id = row * chunks + chunk (the host keeps the product below 2^31)
-        const int64_t row = blockIdx.x / (uint32_t)p.chunks;
-        const int chunk = (int)(blockIdx.x - (uint32_t)row * (uint32_t)p.chunks);
-        b = (int)(row / F);
+        uint32_t chunk_u, f_u;
+        const int64_t row = fast_div(blockIdx.x, p.by_chunks, chunk_u);
+        const int chunk = (int)chunk_u;
+        b = (int)fast_div((uint32_t)row, p.by_F, f_u);
+        uint64_t* const arrivals = p.arrivals + (int64_t)b * kArrivalWords;
+        uint64_t seen = 0;
+        if (wave == 0) seen = load_device(arrivals); // ahead of the logits: loads return in order
         const float* __restrict__ lg = p.logits + row * p.ld;
         const int begin = chunk * kDraftChunk;
         const int end = min(p.V, begin + kDraftChunk);
-        // every thread holds 16 entries and perhaps one of the up to three behind the last four
+        // every thread holds 16 entries and perhaps one of the up to three behind the last four; a chunk of at most 1024
+        // entries (the last of a row) lies in the first wave alone
         const int nvec = (end - begin) >> 2;
+        const bool one_wave = nvec <= kWave * kVec;
+        const int stride = one_wave ? kWave : kExpandThreads, nmine = one_wave && wave != 0 ? 0 : nvec;
         float ev[4 * kVec + 1];
 #pragma unroll
         for (int j = 0; j < kVec; ++j) {
-            const int k = tid + j * kExpandThreads;
-            const f32x4 x = (k < nvec) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            const int k = tid + j * stride;
+            const f32x4 x = (k < nmine) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
             for (int e = 0; e < 4; ++e) ev[4 * j + e] = x[e];
         }
         const int tail = begin + 4 * nvec + tid;
         ev[4 * kVec] = tail < end ? lg[tail] : -INFINITY;
-        auto index = [&](int e) { // of ev[e]
-            if (e == 4 * kVec) return tail < end ? tail : kNone;
-            const int k = tid + (e >> 2) * kExpandThreads;
-            return k < nvec ? begin + 4 * k + (e & 3) : kNone;
+        auto key_of = [&](int e) __attribute__((always_inline)) { // of ev[e]
+            const int k = tid + (e >> 2) * stride;
+            const bool has = e == 4 * kVec ? tail < end : k < nmine;
+            return has ? child_key(ev[e], e == 4 * kVec ? tail : begin + 4 * k + (e & 3)) : 0;
         };
-        if (tid == 0) arrival_open(p.arrivals + (int64_t)b * kArrivalWords);
+        if (tid == 0) {
+            arrival_open(arrivals, seen);
+            s_n = 0;
+        }
 
-        // ---- per wave: maximum, sum of exp, the K first entries; one barrier, then wave 0 merges the waves
-        float m = ev[0];
+        // ---- the chunk's maximum and sum of exp (per wave, then of the waves), and its K first entries: the K-th largest of
+        // the maxima of 32 groups of 256 entries is a bound that K entries reach and few others do
+        float own = ev[0];
 #pragma unroll
-        for (int q = 1; q <= 4 * kVec; ++q) m = fmaxf(m, ev[q]);
-        m = wave_max(m);
-        float s = 0.f;
-        if (m > -INFINITY) {
+        for (int q = 1; q <= 4 * kVec; ++q) own = fmaxf(own, ev[q]);
+        float m = group_max(own); // of the lane's row of 16
+        if ((lane & 15) == 0) s_group[tid >> 4] = ((m == m ? order_key(m) : 0) & ~(kGroups - 1u)) | (tid >> 4); // all different
+        if (!one_wave) {
+            m = wave_max(m);
+            float s = 0.f;
+            if (m > -INFINITY) {
 #pragma unroll
-            for (int q = 0; q <= 4 * kVec; ++q) s += __builtin_amdgcn_exp2f((ev[q] - m) * 1.4426950408889634f); // exp2(-inf) = 0
+                for (int q = 0; q <= 4 * kVec; ++q) s += __builtin_amdgcn_exp2f((ev[q] - m) * 1.4426950408889634f); // exp2(-inf) = 0
+            }
+            s = wave_sum(s);
+            if (lane == 0) {
+                s_m[wave] = m;
+                s_s[wave] = s;
+            }
+        } else if (wave == 0 || wave >= kVec) { // the same sums as of a long chunk: those of four waves
+#pragma unroll
+            for (int j = 0; j < kVec; ++j) {
+                const float last = j == 0 ? ev[4 * kVec] : -INFINITY;
+                const float mj = wave_max(fmaxf(fmaxf(fmaxf(ev[4 * j], ev[4 * j + 1]), fmaxf(ev[4 * j + 2], ev[4 * j + 3])), last));
+                float s = 0.f;
+                if (mj > -INFINITY) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) s += __builtin_amdgcn_exp2f((ev[4 * j + q] - mj) * 1.4426950408889634f);
+                    s += __builtin_amdgcn_exp2f((last - mj) * 1.4426950408889634f);
+                }
+                s = wave_sum(s);
+                if (lane == 0 && (wave == 0 || j == 0)) {
+                    s_m[wave + j] = mj;
+                    s_s[wave + j] = s;
+                }
+            }
         }
-        s = wave_sum(s);
-        if (lane == 0) {
-            s_m[wave] = m;
-            s_s[wave] = s;
-        }
-        wave_topk(ev, index, K, s_list + wave * kCandCap, [&](int r, float v, int32_t i) {
-            s_wv[wave * kMaxDraftK + r] = v;
-            s_wi[wave * kMaxDraftK + r] = i;
-        });
         __syncthreads();
+        if (!one_wave) {
+            const uint32_t g = s_group[lane & (kGroups - 1)];
+            int above = 0;
+#pragma unroll
+            for (int q = 0; q < kGroups; q += 4) {
+                const u32x4 x = *(const u32x4*)&s_group[q];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) above += x[e] > g ? 1 : 0;
+            }
+            const uint32_t bound = (uint32_t)__builtin_amdgcn_readlane(g, __builtin_ctzll(__ballot(above == K - 1))) & ~(kGroups - 1u);
+            const float tau = key_value(bound);
+            if (bound <= 0x007fffffu) { // -inf among the K
+                if (tid == 0) s_n = kCandCap + 1;
+            } else if (own >= tau) { // few lanes
+#pragma unroll
+                for (int e = 0; e <= 4 * kVec; ++e)
+                    if (ev[e] >= tau) {
+                        const int at = atomicAdd(&s_n, 1); // the order of the list does not matter
+                        if (at < kCandCap) s_list[at] = key_of(e);
+                    }
+            }
+            __syncthreads();
+        }
+        const int n = s_n;
+        auto topk_own = [&](uint64_t* list, auto emit) __attribute__((always_inline)) {
+            uint64_t key[4 * kVec + 1];
+#pragma unroll
+            for (int e = 0; e <= 4 * kVec; ++e) key[e] = key_of(e);
+            wave_topk(key, K, list, emit);
+        };
+        if (n > kCandCap) { // a plateau of equal values: every wave's first K, then those of all
+            __syncthreads();
+            topk_own(s_list + wave * kListLen, [&](int r, uint64_t k) { s_wave[wave * kMaxDraftK + r] = k; });
+            __syncthreads();
+        }
         if (wave == 0) {
             const float wm = lane < kExpandWaves ? s_m[lane] : -INFINITY;
             const float cm = wave_max(wm);
             const float cs = wave_sum(wm > -INFINITY ? s_s[lane & (kExpandWaves - 1)] * __builtin_amdgcn_exp2f((wm - cm) * 1.4426950408889634f) : 0.f);
-            if (lane == 0) {
-                store_device(p.part_m + row * p.chunks + chunk, cm);
-                store_device(p.part_s + row * p.chunks + chunk, cs);
-            }
-            constexpr int NE = kExpandWaves * kMaxDraftK / kWave;
-            float mv[NE];
-            int32_t mi[NE];
+            if (lane == 0) store_device(p.part_ms + row * p.chunks + chunk, ((uint64_t)__float_as_uint(cs) << 32) | __float_as_uint(cm));
+            uint64_t* const top = p.part_top + (row * p.chunks + chunk) * K;
+            auto out = [&](int r, uint64_t k) { store_device(top + r, k); }; // 0 when the chunk has fewer than r + 1 entries
+            if (one_wave) {
+                topk_own(s_list, out);
+            } else if (n <= kCandCap) {
+                rank_list(s_list, n, K, out);
+            } else {
+                constexpr int NE = kExpandWaves * kMaxDraftK / kWave;
+                uint64_t key[NE];
 #pragma unroll
-            for (int q = 0; q < NE; ++q) { // entry (wave w, rank r) = w * K + r
-                const int e = lane + q * kWave, w = e / K, r = e - w * K;
-                const bool has = w < kExpandWaves;
-                mv[q] = has ? s_wv[w * kMaxDraftK + r] : -INFINITY;
-                mi[q] = has ? s_wi[w * kMaxDraftK + r] : kNone;
+                for (int q = 0; q < NE; ++q) { // rank r of wave w
+                    const int e = lane + q * kWave;
+                    key[q] = (e & (kMaxDraftK - 1)) < K ? s_wave[e] : 0;
+                }
+                wave_topk(key, K, s_list, out);
             }
-            float* out_v = p.part_tv + (row * p.chunks + chunk) * K;
-            int32_t* out_i = p.part_ti + (row * p.chunks + chunk) * K;
-            wave_topk(mv, [&](int e) { return mi[e]; }, K, s_list, [&](int rr, float v, int32_t i) {
-                store_device(out_v + rr, v);
-                store_device(out_i + rr, i); // kNone when the chunk has fewer than rr+1 entries
-            });
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this chunk's results are in memory
-            if (lane == 0) s_last = arrival_last(p.arrivals + (int64_t)b * kArrivalWords, (uint32_t)(F * p.chunks)) ? 1 : 0;
+            if (lane == 0) s_last = arrival_last(arrivals, (uint32_t)(F * p.chunks)) ? 1 : 0;
         }
         __syncthreads();
         if (s_last == 0) return;
@@ -225,13 +313,13 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
     // ---- the sequence's last workgroup: one wave per frontier row (rows beyond eight take turns)
     const int C = F * K;
     const int keep = min(K, C);
-    // candidates' parents (the frontier rows they extend): requested now, written out at the end
     constexpr int CPT = kMaxDraftCand / kExpandThreads; // candidates per thread, at most
-    int32_t par_own[CPT];
+    int32_t par_own[CPT]; // the candidates' parents (the frontier rows they extend): requested now, written out at the end
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         const int c = tid + i * kExpandThreads;
-        par_own[i] = (c < C && p.frontier_cand) ? p.frontier_cand[(int64_t)b * F + c / K] : -1;
+        uint32_t r;
+        par_own[i] = (c < C && p.frontier_cand) ? p.frontier_cand[(int64_t)b * F + fast_div(c, p.by_K, r)] : -1;
     }
 
     // ---- per row: log-sum-exp and the K first entries of the merged chunk lists
@@ -240,58 +328,48 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
     const int n = p.chunks * K;
     for (int f = wave; f < F; f += kExpandWaves) {
         const int64_t row = (int64_t)b * F + f;
-        const float* pm = p.part_m + row * p.chunks;
-        const float* ps = p.part_s + row * p.chunks;
-        const float* tv = p.part_tv + row * n;
-        const int32_t* ti = p.part_ti + row * n;
+        const uint64_t* pms = p.part_ms + row * p.chunks;
+        const uint64_t* top = p.part_top + row * n;
         constexpr int NE = 4;
-        float v[NE + 1];
-        int32_t idx[NE + 1];
+        uint64_t key[NE + 1];
         auto fetch = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < NE; ++q) {
                 const int e = e0 + lane + q * kWave;
-                v[q] = -INFINITY;
-                idx[q] = kNone;
+                key[q] = 0;
                 if (e0 + q * kWave < n) { // uniform
-                    const float x = load_device(tv + min(e, n - 1));
-                    const int32_t i = load_device(ti + min(e, n - 1));
-                    v[q] = e < n ? x : -INFINITY;
-                    idx[q] = e < n ? i : kNone;
+                    const uint64_t k = load_device(top + min(e, n - 1));
+                    key[q] = e < n ? k : 0;
                 }
             }
         };
-        float m0 = load_device(pm + min(lane, p.chunks - 1)); // (no branch around a load)
-        const float s0 = load_device(ps + min(lane, p.chunks - 1));
+        auto max_of = [](uint64_t ms) { return __uint_as_float((uint32_t)ms); };
+        auto sum_of = [](uint64_t ms) { return __uint_as_float((uint32_t)(ms >> 32)); };
+        const uint64_t ms0 = load_device(pms + min(lane, p.chunks - 1)); // (no branch around a load)
         fetch(0);
         const float cum = p.cum_in ? p.cum_in[row] : 0.f;
-        if (lane >= p.chunks) m0 = -INFINITY;
+        const float m0 = lane < p.chunks ? max_of(ms0) : -INFINITY;
         float m = m0;
-        for (int c = lane + kWave; c < p.chunks; c += kWave) m = fmaxf(m, load_device(pm + c));
+        for (int c = lane + kWave; c < p.chunks; c += kWave) m = fmaxf(m, max_of(load_device(pms + c)));
         m = wave_max(m);
-        float z = (m0 > -INFINITY) ? s0 * __builtin_amdgcn_exp2f((m0 - m) * 1.4426950408889634f) : 0.f;
+        float z = (m0 > -INFINITY) ? sum_of(ms0) * __builtin_amdgcn_exp2f((m0 - m) * 1.4426950408889634f) : 0.f;
         for (int c = lane + kWave; c < p.chunks; c += kWave) {
-            const float mc = load_device(pm + c);
-            if (mc > -INFINITY) z += load_device(ps + c) * __builtin_amdgcn_exp2f((mc - m) * 1.4426950408889634f);
+            const uint64_t ms = load_device(pms + c);
+            if (max_of(ms) > -INFINITY) z += sum_of(ms) * __builtin_amdgcn_exp2f((max_of(ms) - m) * 1.4426950408889634f);
         }
         z = wave_sum(z);
         const float lse = m + __logf(z);
-        float* best_v = s_wv + wave * kMaxDraftK;
-        int32_t* best_i = s_wi + wave * kMaxDraftK;
+        uint64_t* const best = s_wave + wave * kMaxDraftK;
         for (int e0 = 0; e0 < n; e0 += NE * kWave) {
             if (e0 > 0) fetch(e0);
-            const bool more = e0 > 0 && lane < K;
-            v[NE] = more ? best_v[lane] : -INFINITY;
-            idx[NE] = more ? best_i[lane] : kNone;
-            wave_topk(v, [&](int e) { return idx[e]; }, K, s_list + wave * kCandCap, [&](int r, float x, int32_t i) {
-                best_v[r] = x;
-                best_i[r] = i;
-            });
+            key[NE] = e0 > 0 && lane < K ? best[lane] : 0;
+            wave_topk(key, K, s_list + wave * kListLen, [&](int r, uint64_t k) { best[r] = k; });
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by other lanes of this wave
         }
         if (lane < K) {
-            s_token[f * K + lane] = best_i[lane];
-            s_score[f * K + lane] = cum + (best_v[lane] - lse);
+            const uint64_t k = best[lane];
+            s_token[f * K + lane] = k != 0 ? entry_index(k) : INT32_MAX;
+            s_score[f * K + lane] = cum + ((k != 0 ? entry_value(k) : -INFINITY) - lse);
         }
     }
     __syncthreads();
@@ -315,54 +393,58 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         }
         return;
     }
-    uint64_t* const list = s_list + wave * kCandCap;
-    if (C > kWave) { // every wave's share first
-        constexpr int NE = kMaxDraftCand / kExpandThreads;
-        float fv[NE];
-        int32_t fi[NE];
-#pragma unroll
-        for (int q = 0; q < NE; ++q) {
-            const int c = tid + q * kExpandThreads;
-            fv[q] = c < C ? s_score[c] : -INFINITY;
-            fi[q] = c < C ? c : kNone;
+    if (C <= kWave) { // one wave, a lane per candidate: rank by counting, listed in the order of the lanes
+        if (wave != 0) return;
+        const float sc = lane < C ? s_score[lane] : 0.f;
+        const uint64_t k = lane < C ? child_key(sc, lane) : 0;
+        s_list[lane] = k;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by all lanes of this wave
+        int rank = 0;
+#pragma unroll 8
+        for (int o = 0; o < kWave; o += 2) {
+            const u64x2 x = *(const u64x2*)&s_list[o];
+            rank += (x[0] > k ? 1 : 0) + (x[1] > k ? 1 : 0);
         }
-        wave_topk(fv, [&](int e) { return fi[e]; }, keep, list, [&](int r, float v, int32_t i) {
-            s_wv[wave * kMaxDraftK + r] = v;
-            s_wi[wave * kMaxDraftK + r] = i;
-        });
+        const bool kept = k != 0 && rank < keep;
+        const uint64_t mask = __ballot(kept);
+        if (kept) {
+            const int pos = __popcll(mask & ((1ull << lane) - 1ull));
+            p.next_frontier_cand[(int64_t)b * keep + pos] = p.cand_base + lane;
+            p.next_cum[(int64_t)b * keep + pos] = sc;
+        }
+        return;
+    }
+    uint64_t* const list = s_list + wave * kListLen;
+    { // every wave's share first
+        uint64_t key[CPT];
+#pragma unroll
+        for (int q = 0; q < CPT; ++q) {
+            const int c = tid + q * kExpandThreads;
+            key[q] = c < C ? child_key(s_score[c], c) : 0;
+        }
+        wave_topk(key, keep, list, [&](int r, uint64_t k) { s_wave[wave * kMaxDraftK + r] = k; });
         __syncthreads();
     }
     if (wave != 0) return;
     {
         constexpr int NE = kExpandWaves * kMaxDraftK / kWave;
-        float fv[NE];
-        int32_t fi[NE];
+        uint64_t key[NE];
 #pragma unroll
         for (int q = 0; q < NE; ++q) {
             const int e = lane + q * kWave;
-            if (C > kWave) {
-                const bool has = (e & (kMaxDraftK - 1)) < keep;
-                fv[q] = has ? s_wv[e] : -INFINITY;
-                fi[q] = has ? s_wi[e] : kNone;
-            } else {
-                fv[q] = e < C ? s_score[e] : -INFINITY;
-                fi[q] = e < C ? e : kNone;
-            }
+            key[q] = (e & (kMaxDraftK - 1)) < keep ? s_wave[e] : 0;
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the lists have been read
-        wave_topk(fv, [&](int e) { return fi[e]; }, keep, list, [&](int r, float v, int32_t i) {
-            s_wv[r] = v;
-            s_wi[r] = i;
-        });
+        wave_topk(key, keep, list, [&](int r, uint64_t k) { s_wave[r] = k; });
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    const int32_t c = lane < keep ? s_wi[lane] : kNone;
-    const float sc = lane < keep ? s_wv[lane] : 0.f;
+    const uint64_t k = lane < keep ? s_wave[lane] : 0;
+    const int32_t c = k != 0 ? entry_index(k) : INT32_MAX;
     int pos = 0;
     for (int o = 0; o < keep; ++o) pos += __builtin_amdgcn_readlane(c, o) < c ? 1 : 0;
-    if (c != kNone) {
+    if (k != 0) {
         p.next_frontier_cand[(int64_t)b * keep + pos] = p.cand_base + c;
-        p.next_cum[(int64_t)b * keep + pos] = sc;
+        p.next_cum[(int64_t)b * keep + pos] = s_score[c];
     }
 }
 

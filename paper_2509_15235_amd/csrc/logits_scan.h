@@ -14,9 +14,10 @@ namespace vs {
 struct ScanItem {
     int row, chunk;
 };
-__device__ __forceinline__ ScanItem scan_item(int chunks) {
-    const uint32_t row = blockIdx.x / (uint32_t)chunks;
-    return {(int)row, (int)(blockIdx.x - row * (uint32_t)chunks)};
+__device__ __forceinline__ ScanItem scan_item(FastDiv by_chunks) {
+    uint32_t chunk;
+    const uint32_t row = fast_div(blockIdx.x, by_chunks, chunk);
+    return {(int)row, (int)chunk};
 }
 
 // A chunk of a row (THREADS: of the workgroup; a row of up to 4096 logits needs 256, and launches half as many waves): every

@@ -98,6 +98,7 @@ struct AcceptParams {
     int32_t* status;     // may be null
     uint64_t* pairs;     // [B*T][chunks] (value, index)
     int32_t chunks;
+    FastDiv by_chunks;
 };
 
 constexpr int kMaxSampleChunks = 1024; // chunk sums of one logits row kept in LDS by the sampling walk
@@ -118,6 +119,7 @@ struct SampleParams {
     uint64_t* pairs;       // [B*T][chunks] chunk maximum of the raw logits, sum of 2^((l - chunk maximum) * k_log2)
     float k_log2;          // log2(e) / temperature
     int32_t chunks;
+    FastDiv by_chunks;
 };
 
 constexpr int kDraftChunk = 8192;     // floats of a logits row per workgroup of an expansion: 512 threads x 4 x 16 bytes
@@ -139,12 +141,11 @@ struct DraftExpandParams {
     int32_t* cand_parent;
     int32_t* next_frontier_cand;  // [B][min(K, F*K)]
     float* next_cum;
-    float* part_m;                // [B*F][chunks]
-    float* part_s;
-    float* part_tv;               // [B*F][chunks][K]
-    int32_t* part_ti;
+    uint64_t* part_ms;            // [B*F][chunks]: sum of exp, maximum (two floats)
+    uint64_t* part_top;           // [B*F][chunks][K]: entry keys, 0 = none
     uint64_t* arrivals;           // a word per sequence, kArrivalWords apart
     int32_t chunks;
+    FastDiv by_chunks, by_F, by_K;
 };
 
 struct DraftBuildParams {
