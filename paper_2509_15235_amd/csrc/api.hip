@@ -415,7 +415,7 @@ size_t workspace_bytes(const vs_attn_desc* d, const Plan& pl) {
     if (pl.impl != VS_IMPL_MFMA || pl.num_splits <= 1) return 0;
     const size_t prow = partial_rows(d, pl);
     return align_up(prow * d->d * sizeof(uint16_t)) + align_up(prow * 2 * sizeof(float)) +
-           (pl.bal_chunks > 0 ? align_up(kBalMaxChunks * sizeof(int32_t)) : 0) +
+           (pl.bal_chunks > 0 ? align_up(kBalMaxChunks * sizeof(int32_t)) : 0) + // (unused: the size that callers know)
            (merges_inside(d, pl) ? align_up((size_t)d->B * d->Hkv * pl.row_groups * kGateWords * sizeof(uint64_t)) : 0);
 }
 
@@ -556,6 +556,10 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         p.by_heads = fast_div_by(desc->Hkv);
     }
     p.bal_chunks = pl.bal_chunks;
+    if (pl.bal_chunks > 0) {
+        p.by_shares = fast_div_by(pl.bal_chunks);
+        if (pl.bal_chunks % desc->B == 0) p.bal_per_seq = fast_div_by(pl.bal_chunks / desc->B);
+    }
     // A launch of more whole sequences than run at once hands out the longest first (a lane per sequence), unless even the longest is
     // so short that the wait for all lengths costs more than it brings. us per call, longest first / in order:
     // pipelined kernel, 28 / 4 heads, 60 nodes, 64 sequences, all of 100 keys 41.6 / 36.1, 250 51.8 / 46.3, 500 65.0 / 60.0, 1000 93.2 / 89.1;
@@ -571,7 +575,6 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         p.part_o = (uint16_t*)workspace;
         p.part_ml = (float*)((char*)workspace + align_up(prow * desc->d * sizeof(uint16_t)));
         char* behind = (char*)p.part_ml + align_up(prow * 2 * sizeof(float));
-        if (pl.bal_chunks > 0) p.bal_table = (int32_t*)behind;
         if (merges_inside(desc, pl)) p.gates = (uint64_t*)behind;
         p.merge_wait = merge_wait;
     }
@@ -585,7 +588,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
             : pl.rounds ? launch_attention_mfma_rounds(p, pl.res_rb, s)
             : pl.schedule == VS_SCHED_RESIDENT ? launch_attention_mfma_resident(p, pl.res_rb, s)
                                                : launch_attention_mfma(p, pl.rpw, pl.waves, s);
-        if (e == hipSuccess && pl.num_splits > 1 && !p.gates) e = launch_attention_combine(p, desc->dtype, s);
+        if (e == hipSuccess && pl.num_splits > 1 && !p.gates && pl.bal_chunks == 0) e = launch_attention_combine(p, desc->dtype, s);
     }
     return e == hipSuccess ? VS_OK : VS_ERR_HIP;
 }

@@ -64,6 +64,36 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
+    // Final rows of row block rb out of the accumulators' lanes (quad(e): this lane's channels 8 * e + 4 * half .. + 3 of its row), half of the
+    // channels at a time through this wave's eighth (quarter) of the K ring, which nobody reads behind the last tile:
+    // a store of 16 bytes a lane then touches 8 lines of 128 bytes, not 32 lines in 8-byte pieces, sixteen times over.
+    auto store_rows = [&](int b, int kvh, int rb, auto quad) __attribute__((always_inline)) {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        const int lane = t & 63, half = lane >> 5, col = lane & 31;
+        constexpr int CH = D / 16, RPS = 64 / CH, NST = kRowBlock / RPS; // 16-byte chunks of a row, rows per store, stores
+        char* const mine = (char*)&sK[0][0] + wave * (kRowBlock * D);
+        uint16_t* o[NST];
+#pragma unroll
+        for (int i = 0; i < NST; ++i) {
+            const int r = rb * kRowBlock + i * RPS + lane / CH;
+            o[i] = r < p.rows ? (uint16_t*)p.out + row_offset(p, b, kvh, r, row_node(p, r)) + (lane % CH) * 8 : nullptr;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int e = 0; e < CH; ++e) *(u32x2*)(mine + col * D + ((e ^ (col & (CH - 1))) * 16) + half * 8) = quad(h * CH + e);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by other lanes of this wave
+#pragma unroll
+            for (int i = 0; i < NST; ++i) {
+                const int r = i * RPS + lane / CH;
+                const u32x4 w = *(const u32x4*)(mine + r * D + (((lane % CH) ^ (r & (CH - 1))) * 16));
+                if (o[i]) *(u32x4*)(o[i] + h * (D / 2)) = w;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the reads are done before it is written again
+        }
+    };
+
     // One piece of work: the rows of row group `rg` of (sequence b, KV head kvh) against the keys
     // [k0, k0 + klen) of that sequence (k0 lies inside the cache). `whole`: no other piece shares these
     // rows, they leave as final output; else as the partial result of slot `slot`.
@@ -105,38 +135,33 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
         k_st[j] = (uint32_t)(((r >> 4) * DB + (c >> 2)) * 1024 + (c & 3) * 256 + (((r & 15) ^ (4 * (c & 3))) * 16));
         v_st[j] = (uint32_t)(((r >> 4) * DB + (c >> 2)) * 1024 + (4 * (r & 15) + (c & 3)) * 16);
     }
-    u32x4 stage[2][4][BPW];
-    // The first four tiles - K(0), K(1), K(2), V(0), through register set 1 - are requested before
-    // the prefix length is known: clamped to the cache instead of the sequence, and rows that
-    // turn out to lie past the sequence's last key are zeroed when the tiles go into LDS
-    // (whatever the cache holds there, NaN included, must not meet a zero probability).
-    {
-        const int64_t cache_tokens = PAGED ? (int64_t)p.max_blocks * p.block_size : p.capacity;
-        const int kend = (int)(cache_tokens < (int64_t)k0 + klen ? cache_tokens : (int64_t)k0 + klen);
-        auto load_tile_early = [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
-            const uint16_t* gbase = decltype(is_v)::value ? vbase : kbase;
-#pragma unroll
-            for (int j = 0; j < BPW; ++j) {
-                const int r0 = min(k0 + t * kTileKeys + RPI * (block0 + j), kend - 1); // RPI divides 16: one cache block in paged mode
-                int tok = min(r0 + lrow, kend - 1);
-                int64_t base = head_base;
-                if (PAGED) {
-                    int32_t blk = p.block_table[(int64_t)b * p.max_blocks + (r0 >> p.block_shift)];
-                    if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-                    base += (int64_t)blk * p.stride_block;
-                    tok &= p.block_size - 1;
-                }
-                r[j] = *(const u32x4*)(gbase + base + (uint32_t)(tok * stride_tok + lchunk * 8));
-            }
-        };
-        if (!upper) {
-            load_tile_early(std::false_type{}, 0, stage[1][0]);
-            load_tile_early(std::false_type{}, 1, stage[1][1]);
-            load_tile_early(std::false_type{}, 2, stage[1][2]);
-        }
-        if (!HALVES || upper) load_tile_early(std::true_type{}, 0, stage[1][3]);
+    // Paged caches: where the blocks of the tiles to come lie sits one per lane - a window of 64 consecutive table
+    // entries, fetched with one coalesced load and moved along by 32 as the tiles advance - so a tile copy gets
+    // it with v_readlane instead of a scalar load per copy (whose result the copy would have to wait for, together with
+    // every LDS read in flight: scalar loads and LDS share one wait counter). The clamp and the product are done once
+    // per window, by all lanes at once, and the loaded register is only touched where the window moves: with ids in
+    // a window of 128 read twice per lookup 28 x 60 nodes of 28 / 4 heads over 1696 keys took 62.1 us, so 59.3 (54.8 unpaged).
+    const int32_t* bt_row = PAGED ? p.block_table + (int64_t)b * p.max_blocks : nullptr;
+    int bt_base = k0 >> p.block_shift; // logical block of lane 0
+    uint32_t bt_lo = 0, bt_hi = 0;     // element offset of the lane's block
+    int32_t bt_next = 0;               // block id of lane 0 + 32 + lane, on its way
+    auto bt_fetch = [&](int first) __attribute__((always_inline)) { return bt_row[min(first + lane, p.max_blocks - 1)]; };
+    auto bt_set = [&](int32_t blk) __attribute__((always_inline)) {
+        if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
+        const int64_t off = (int64_t)blk * p.stride_block;
+        bt_lo = (uint32_t)off;
+        bt_hi = (uint32_t)(off >> 32);
+    };
+    int32_t bt_first = 0;
+    if (PAGED) { // (with the prefix length: one trip)
+        bt_first = bt_fetch(bt_base);
+        bt_next = bt_fetch(bt_base + 32);
     }
-
+    auto bt_lookup = [&](int lb) __attribute__((always_inline)) {
+        const int rel = lb - bt_base; // 0 .. 63 by construction
+        return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bt_hi, rel) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)bt_lo, rel));
+    };
+    u32x4 stage[2][4][BPW];
     // ---- this wave's rows and queries (in flight together with the first tiles)
     const int row_base = rg * p.rows_per_group + wave * (RPW * kRowBlock);
     const bool wave_active = row_base < p.rows;
@@ -151,10 +176,46 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     static_assert(RPW == 1 && NW <= 2 * NSLOT, "a row block's queries take a tile slot");
     // through the tile slot of this wave's number (nothing is in the rings yet)
     uint16_t* sq = wave < NSLOT ? sK[wave & (NSLOT - 1)] : sV[wave & (NSLOT - 1)];
-    if (wave_active) {
+    auto copy_queries = [&]() __attribute__((always_inline)) {
+        if (!wave_active) return;
 #pragma unroll
         for (int i = 0; i < KS; ++i) copy_q_piece<D>(p, b, kvh, row_base, sq, i, lane);
+    };
+    if (PAGED) { // the queries while the block ids are on their way
+        copy_queries();
+        bt_set(bt_first);
     }
+    constexpr bool EARLY = !(BAL && PAGED && NW == 4); // registers: 4 waves of 128 channels 188 us, so 171 (8 x 60 nodes, 32 / 32 heads, 1024 .. 8191 keys)
+    // The first four tiles - K(0), K(1), K(2), V(0), through register set 1 - are requested before
+    // the prefix length is known: clamped to the cache instead of the sequence, and rows that
+    // turn out to lie past the sequence's last key are zeroed when the tiles go into LDS
+    // (whatever the cache holds there, NaN included, must not meet a zero probability).
+    if constexpr (EARLY) {
+        const int64_t cache_tokens = PAGED ? (int64_t)p.max_blocks * p.block_size : p.capacity;
+        const int kend = (int)(cache_tokens < (int64_t)k0 + klen ? cache_tokens : (int64_t)k0 + klen);
+        auto load_tile_early = [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
+            const uint16_t* gbase = decltype(is_v)::value ? vbase : kbase;
+#pragma unroll
+            for (int j = 0; j < BPW; ++j) {
+                const int r0 = min(k0 + t * kTileKeys + RPI * (block0 + j), kend - 1); // RPI divides 16: one cache block in paged mode
+                int tok = min(r0 + lrow, kend - 1);
+                int64_t base = head_base;
+                if (PAGED) {
+                    base += bt_lookup(r0 >> p.block_shift);
+                    tok &= p.block_size - 1;
+                }
+                r[j] = *(const u32x4*)(gbase + base + (uint32_t)(tok * stride_tok + lchunk * 8));
+            }
+        };
+        if (!upper) {
+            load_tile_early(std::false_type{}, 0, stage[1][0]);
+            load_tile_early(std::false_type{}, 1, stage[1][1]);
+            load_tile_early(std::false_type{}, 2, stage[1][2]);
+        }
+        if (!HALVES || upper) load_tile_early(std::true_type{}, 0, stage[1][3]);
+    }
+
+    if (!PAGED) copy_queries();
 
     int32_t tree_code = VS_STATUS_OK;
     if (p.tree_mask || p.tree_keys == 0) {
@@ -180,29 +241,6 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     // first key of the split in this (sequence, KV head) slice; only used when not paged
     const char* kfast = (const char*)(kbase + head_base + (int64_t)k0 * stride_tok);
     const char* vfast = (const char*)(vbase + head_base + (int64_t)k0 * stride_tok);
-    // LFAST: a full tile, so the address is a wave-uniform base plus a per-lane constant and nothing
-    // needs clamping.
-    // Paged caches: where the blocks of the tiles to come lie sits one per lane - a window of 64 consecutive table
-    // entries, fetched with one coalesced load and moved along by 32 as the tiles advance - so a tile copy gets
-    // it with v_readlane instead of a scalar load per copy (whose result the copy would have to wait for, together with
-    // every LDS read in flight: scalar loads and LDS share one wait counter). The clamp and the product are done once
-    // per window, by all lanes at once, and the loaded register is only touched where the window moves: with ids in
-    // a window of 128 read twice per lookup 28 x 60 nodes of 28 / 4 heads over 1696 keys took 62.1 us, so 59.3 (54.8 unpaged).
-    const int32_t* bt_row = PAGED ? p.block_table + (int64_t)b * p.max_blocks : nullptr;
-    int bt_base = k0 >> p.block_shift; // logical block of lane 0
-    uint32_t bt_lo = 0, bt_hi = 0;     // element offset of the lane's block
-    int32_t bt_next = 0;               // block id of lane 0 + 32 + lane, on its way
-    auto bt_fetch = [&](int first) __attribute__((always_inline)) { return bt_row[min(first + lane, p.max_blocks - 1)]; };
-    auto bt_set = [&](int32_t blk) __attribute__((always_inline)) {
-        if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-        const int64_t off = (int64_t)blk * p.stride_block;
-        bt_lo = (uint32_t)off;
-        bt_hi = (uint32_t)(off >> 32);
-    };
-    if (PAGED) {
-        bt_set(bt_fetch(bt_base));
-        bt_next = bt_fetch(bt_base + 32);
-    }
     // moves the window so that it starts less than 32 blocks before logical block `lb_min` (called once per iteration)
     auto bt_advance = [&](int lb_min) __attribute__((always_inline)) {
         if (PAGED && lb_min >= bt_base + 32) { // uniform
@@ -210,10 +248,6 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
             bt_set(bt_next);
             bt_next = bt_fetch(bt_base + 32);
         }
-    };
-    auto bt_lookup = [&](int lb) __attribute__((always_inline)) {
-        const int rel = lb - bt_base; // 0 .. 63 by construction
-        return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bt_hi, rel) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)bt_lo, rel));
     };
     // this lane's 16 bytes of the block at a uniform address: a scalar address plus lane_off (left to itself the compiler adds
     // them up first, and the copies' addresses take two registers each)
@@ -223,6 +257,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
         return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
     };
     // is_v: a constant or, with HALVES, `upper`
+    // LFAST: a full tile, so the address is a wave-uniform base plus a per-lane constant and nothing
+    // needs clamping.
     auto load_tile = [&](auto lfast_tag, auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
         constexpr bool LFAST = decltype(lfast_tag)::value;
         const bool ISV = is_v;
@@ -294,6 +330,14 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     };
     auto stash_group = [&](auto set_tag, int g) __attribute__((always_inline)) { each_part(set_tag, g, stash_tile); };
 
+    if constexpr (!EARLY) {
+        if (!upper) {
+            load_tile(std::false_type{}, std::false_type{}, 0, stage[1][0]);
+            load_tile(std::false_type{}, std::false_type{}, 1, stage[1][1]);
+            load_tile(std::false_type{}, std::false_type{}, 2, stage[1][2]);
+        }
+        if (!HALVES || upper) load_tile(std::false_type{}, std::true_type{}, 0, stage[1][3]);
+    }
     // the rest of the prologue copies: group 0 (set 0)
     load_group(std::false_type{}, std::integral_constant<int, 0>{}, 0);
 
@@ -678,19 +722,30 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     const int lane = tid_end & 63, half = lane >> 5, col = lane & 31;
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb) {
-        const int r_local = row_base + rb * kRowBlock + col;
         const float l = half_sum(lsum[rb]);
         if (whole) {
-            if (r_local >= p.rows) continue;
-            uint16_t* o = (uint16_t*)p.out + row_offset(p, b, kvh, r_local, row_node(p, r_local));
-            const float inv = 1.f / l;
+            // Lines pay for eight waves of 128 channels: us per call, 8-byte pieces / lines, 60 nodes, 28 / 4 heads, 64 x 400 keys 53.4 / 48.7,
+            // 28 x 1696 59.9 / 58.6. With four waves or 64 channels the trip through LDS costs more: 12 x 35 nodes, 32 / 32
+            // heads, 90 keys 12.9 / 13.4; 56 x 9 nodes, 32 / 8 heads of 64, 152 .. 305 keys 13.2 / 13.7.
+            if constexpr (D == 128 && NW == 8) {
+                const float inv = 1.f / l;
+                store_rows(b, kvh, (row_base >> 5) + rb, [&](int e) __attribute__((always_inline)) {
+                    const f32x16& a = acc[rb][e >> 2];
+                    return pack_partial(a[4 * (e & 3)], a[4 * (e & 3) + 1], a[4 * (e & 3) + 2], a[4 * (e & 3) + 3], inv);
+                });
+            } else {
+                const int r_local = row_base + rb * kRowBlock + col;
+                if (r_local >= p.rows) continue;
+                uint16_t* o = (uint16_t*)p.out + row_offset(p, b, kvh, r_local, row_node(p, r_local));
+                const float inv = 1.f / l;
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    *(u32x2*)(o + db * 32 + 8 * q4 + 4 * half) =
-                        pack_partial(acc[rb][db][4 * q4], acc[rb][db][4 * q4 + 1], acc[rb][db][4 * q4 + 2], acc[rb][db][4 * q4 + 3], inv);
-                }
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        *(u32x2*)(o + db * 32 + 8 * q4 + 4 * half) =
+                            pack_partial(acc[rb][db][4 * q4], acc[rb][db][4 * q4 + 1], acc[rb][db][4 * q4 + 2], acc[rb][db][4 * q4 + 3], inv);
+                    }
+            }
         } else {
             if (row_base + rb * kRowBlock >= p.rows) continue; // whole block is padding
             const int64_t unit = BAL ? kvh : (int64_t)b * p.Hkv + kvh;
@@ -698,13 +753,13 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
             const float inv = l > 0.f ? 1.f / l : 0.f; // no visible key in this split: zeros, weight 0
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                if (merge) store_partial<true>(p, po, db, lane, acc[rb][db], inv);
+                if (BAL || merge) store_partial<true>(p, po, db, lane, acc[rb][db], inv);
                 else store_partial(p, po, db, lane, acc[rb][db], inv);
             }
             if (half == 0) {
                 const f32x2 ml = {m2[rb], l};
                 float* dst = p.part_ml + ml_block(p, unit, slot, (row_base >> 5) + rb) * 2;
-                if (merge) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), span_of(dst), col * 8, 0, kDeviceScope);
+                if (BAL || merge) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), span_of(dst), col * 8, 0, kDeviceScope);
                 else *(f32x2*)(dst + col * 2) = ml;
             }
         }
@@ -745,32 +800,119 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     } else {
         // workgroup id -> (share, KV head, row group): the row groups of a (share, KV head) sit next to each
         // other on one XCD (they read the same keys), consecutive (share, KV head) pairs on different ones
-        const int xj = blockIdx.x >> 3;
-        const int rg = xj % p.row_groups;
-        const int u = (xj / p.row_groups) * 8 + (blockIdx.x & 7);
-        const int c = u / p.Hkv, kvh = u % p.Hkv;
+        uint32_t rg_u, kvh_u;
+        const int u = (int)fast_div(blockIdx.x >> 3, p.by_groups, rg_u) * 8 + (blockIdx.x & 7);
+        const int c = (int)fast_div((uint32_t)u, p.by_heads, kvh_u);
+        const int rg = (int)rg_u, kvh = (int)kvh_u;
         if (c >= p.bal_chunks) return;
+        const int rb = rg * (p.rows_per_group / kRowBlock) + wave; // this wave's row block
+        const bool has_rows = rb * kRowBlock < p.rows;
+        const int32_t S = lane < p.B ? p.prefix_len[lane] : -1;
+        uint64_t* const words = (uint64_t*)(p.part_o + part_block<D>(p, kvh, p.num_splits - 1, rb)); // a word per sequence
+        uint64_t seen = 0;
+        if (has_rows) seen = load_device(words + lane);
         int start, steps, total;
-        bool usable;
-        bal_scan(p, lane, start, steps, total, usable);
+        bal_scan(p, S, start, steps, total);
         // sequences that no piece will ever visit report their bad prefix length here
-        if (c == 0 && kvh == 0 && rg == 0 && wave == 0 && lane < p.B && !usable && p.status) p.status[lane] = VS_STATUS_BAD_PREFIX;
+        if (c == 0 && kvh == 0 && rg == 0 && wave == 0 && lane < p.B && steps == 0 && !prefix_ok(p, S) && p.status) p.status[lane] = VS_STATUS_BAD_PREFIX;
         const int bounds = bal_bounds(p, lane, start, steps, total);
-        if (c == 0 && kvh == 0 && rg == 0 && wave == 0) p.bal_table[lane] = bounds; // for the combine kernel
         const int lo = __builtin_amdgcn_readlane(bounds, c);
         const int hi = c + 1 < p.bal_chunks ? __builtin_amdgcn_readlane(bounds, c + 1) : total;
-        // (in LDS, every wave its own copy: two registers that the loop over the tiles needs)
-        __shared__ int32_t s_start[NW][kBalMaxSeqs], s_steps[NW][kBalMaxSeqs];
+        // (in LDS, every wave its own copy: registers that the loop over the tiles needs)
+        __shared__ int32_t s_start[NW][kBalMaxSeqs], s_steps[NW][kBalMaxSeqs], s_bounds[NW][kBalMaxChunks + 1];
         s_start[wave][lane] = start;
         s_steps[wave][lane] = steps;
+        s_bounds[wave][lane] = lane < p.bal_chunks ? bounds : total;
+        if (lane == 0) s_bounds[wave][kBalMaxChunks] = total;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by all lanes of this wave
-        for (int i = 0; i < p.B; ++i) {
+        int p0, p1;
+        const uint64_t pieces = __ballot(bal_piece(lo, hi, start, steps, p0, p1));
+        const uint64_t shared = __ballot(bal_piece(lo, hi, start, steps, p0, p1) && !(p0 == 0 && p1 == steps)); // others have the rest
+        if (has_rows && ((shared >> lane) & 1)) arrival_open(words + lane, seen);
+        for (uint64_t left = pieces; left != 0; left &= left - 1) { // in the order of the line
+            const int i = __builtin_ctzll(left);
             const int s0 = __builtin_amdgcn_readfirstlane(s_start[wave][i]), t = __builtin_amdgcn_readfirstlane(s_steps[wave][i]);
             int t0, t1;
-            if (bal_piece(lo, hi, s0, t, t0, t1)) { // uniform
-                __syncthreads(); // the previous piece's last reads of the tile rings, the tree and the flag
-                run_piece(i, kvh, rg, t0 * kIterKeys, (t1 - t0) * kIterKeys, c + i, t0 == 0 && t1 == t);
+            bal_piece(lo, hi, s0, t, t0, t1);
+            __syncthreads(); // the previous piece's last reads of the tile rings, the tree and the flag
+            run_piece(i, kvh, rg, t0 * kIterKeys, (t1 - t0) * kIterKeys, c + i, ((shared >> i) & 1) == 0);
+        }
+        if (shared == 0 || !has_rows) return;
+
+        // ---- The wave that comes last to a sequence's pieces of its row block merges them; nobody waits. All of a share's
+        // pieces arrive at its end (the shares end together anyway, and a piece in the middle would hold up the next one
+        // for the trip of its stores). A combine kernel behind the launch took 8.5 us of 98 (16 x 60 nodes, 28 / 4 heads, 1024 ..
+        // 8191 keys); one arrival per workgroup instead of one per wave leaves a whole row group to one CU.
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int ln = tid & 63;
+        auto shares_of = [&](int i) __attribute__((always_inline)) { // the shares that hold pieces of sequence i
+            const int s0 = __builtin_amdgcn_readfirstlane(s_start[wave][i]), t = __builtin_amdgcn_readfirstlane(s_steps[wave][i]);
+            int t0, t1;
+            return __ballot(ln < p.bal_chunks && bal_piece(s_bounds[wave][ln], s_bounds[wave][ln + 1], s0, t, t0, t1));
+        };
+        int pieces_of = 0;
+        for (uint64_t left = shared; left != 0; left &= left - 1) {
+            const int i = __builtin_ctzll(left), k = __popcll(shares_of(i));
+            pieces_of = ln == i ? k : pieces_of;
+        }
+        const int col = ln & 31;
+        __builtin_amdgcn_s_waitcnt(wait_vm(0)); // this wave's partial results are in memory
+        uint64_t left = __ballot(((shared >> ln) & 1) && arrival_last((uint64_t*)(p.part_o + part_block<D>(p, kvh, p.num_splits - 1, rb)) + ln, (uint32_t)pieces_of));
+        const float* ml_row = p.part_ml + ml_block(p, kvh, 0, rb) * 2;
+        const uint16_t* po_row = p.part_o + part_block<D>(p, kvh, 0, rb);
+        for (; left != 0; left &= left - 1) {
+            const int i = __builtin_ctzll(left);
+            const uint64_t all = shares_of(i);
+            // pieces in batches of three (most sequences have two or three); the next batch's maximum joins the running one
+            float den = 0.f, M = -INFINITY;
+            f32x4 num[4 * DB];
+#pragma unroll
+            for (int e = 0; e < 4 * DB; ++e) num[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            bool first = true;
+            for (uint64_t rest = all; rest != 0;) {
+                constexpr int BATCH = 3;
+                u32x2 ml[BATCH];
+                u32x4 x[BATCH][2 * DB];
+                const int n = min(__popcll(rest), BATCH);
+#pragma unroll
+                for (int q = 0; q < BATCH; ++q)
+                    if (q < n) { // uniform
+                        const int slot = (int)__builtin_ctzll(rest) + i;
+                        rest &= rest - 1;
+                        ml[q] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(span_of(ml_row), col * 8, slot * (kRowBlock * 8), kDeviceScope));
+#pragma unroll
+                        for (int e = 0; e < 2 * DB; ++e)
+                            x[q][e] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(span_of(po_row), ln * 16, (e * p.num_splits + slot) * 1024, kDeviceScope));
+                    }
+                float Mb = M;
+#pragma unroll
+                for (int q = 0; q < BATCH; ++q)
+                    if (q < n) Mb = fmaxf(Mb, __uint_as_float(ml[q][0]));
+                if (!first) { // what was summed so far is rescaled
+                    const float resc = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
+                    den *= resc;
+#pragma unroll
+                    for (int e = 0; e < 4 * DB; ++e) num[e] *= resc;
+                }
+                first = false;
+                M = Mb;
+#pragma unroll
+                for (int q = 0; q < BATCH; ++q)
+                    if (q < n) {
+                        // a piece that saw no visible key for the row has max -inf, sum 0 and zero partials
+                        const float m = __uint_as_float(ml[q][0]);
+                        const float w = m != -INFINITY ? __builtin_amdgcn_exp2f(m - M) * __uint_as_float(ml[q][1]) : 0.f;
+                        den += w;
+#pragma unroll
+                        for (int e = 0; e < 2 * DB; ++e) {
+                            num[2 * e] += w * unpack_partial(u32x2{x[q][e][0], x[q][e][1]});
+                            num[2 * e + 1] += w * unpack_partial(u32x2{x[q][e][2], x[q][e][3]});
+                        }
+                    }
             }
+            const float inv = 1.f / den;
+            store_rows(i, kvh, rb, [&](int e) __attribute__((always_inline)) { return pack_partial(num[e][0], num[e][1], num[e][2], num[e][3], inv); });
         }
     }
 }

@@ -440,23 +440,17 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
 // into a share is a piece of work: a share that crosses from one sequence into the next is worked
 // off piece by piece. A piece costs its steps plus kBalPieceCost (queries, first tiles, the
 // pipeline's fill and drain: what happens before a piece's first and after its last step takes about
-// as long as six steps). Lane i of a wave holds sequence i (at most 64 sequences). Main and combine
-// kernel both derive the shares from the prefix lengths with the routines below, so they agree on
-// where every piece's partial result lies: slot (share + sequence) of its KV head.
+// as long as six steps). Lane i of a wave holds sequence i (at most 64 sequences). Every workgroup
+// derives the shares from the prefix lengths, so all agree on where a piece's partial result lies:
+// slot (share + sequence) of its KV head. The last slot is never a piece's; its first KB in a row group's first
+// row block holds the arrival words of the row group's pieces, one per sequence.
 constexpr int kBalPieceCost = 6;
 constexpr int kBalSnap = 3; // no piece this short (in steps) is left behind at a sequence's end
 
-// this lane's sequence: its first step on the line and its number of steps (0: not usable)
-__device__ __forceinline__ void bal_scan(const AttnParams& p, int lane, int& start, int& steps, int& total, bool& usable) {
-    const int32_t S = lane < p.B ? p.prefix_len[lane] : -1;
-    usable = lane < p.B && prefix_ok(p, S);
-    steps = usable ? (S + p.tree_keys + kIterKeys - 1) / kIterKeys : 0;
-    int inc = steps;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-    }
+// this lane's sequence (of prefix length S; -1: none): its first step on the line and its number of steps (0: not usable)
+__device__ __forceinline__ void bal_scan(const AttnParams& p, int32_t S, int& start, int& steps, int& total) {
+    steps = prefix_ok(p, S) ? (S + p.tree_keys + kIterKeys - 1) / kIterKeys : 0;
+    const int inc = wave_scan(steps);
     start = inc - steps;
     total = __builtin_amdgcn_readlane(inc, 63);
 }
@@ -468,22 +462,6 @@ __device__ __forceinline__ bool bal_piece(int lo, int hi, int s0, int t, int& a,
     return b > a;
 }
 
-// cost of the most expensive share under the boundaries held one per lane (lane c: first step of share c)
-__device__ __forceinline__ int bal_worst(const AttnParams& p, int lane, int start, int steps, int total, int bounds) {
-    const int up = __shfl_down(bounds, 1);
-    const int hi = lane + 1 < p.bal_chunks ? up : total;
-    int cost = 0;
-    for (int i = 0; i < p.B; ++i) {
-        int a, b;
-        if (bal_piece(bounds, hi, __builtin_amdgcn_readlane(start, i), __builtin_amdgcn_readlane(steps, i), a, b))
-            cost += kBalPieceCost + (b - a);
-    }
-    if (lane >= p.bal_chunks) cost = 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cost = max(cost, __shfl_xor(cost, o));
-    return cost;
-}
-
 // lane c (c < W): first step of share c; the other lanes: the end of the line.
 // Two cuts are priced (most expensive share, a piece costing its steps plus kBalPieceCost) and the
 // cheaper one is taken:
@@ -493,42 +471,43 @@ __device__ __forceinline__ int bal_worst(const AttnParams& p, int lane, int star
 //  * regular, when W is a multiple of the number of sequences: every sequence gets W / B shares of
 //    ceil(longest sequence / (W / B)) steps - what equal splits per sequence would be. Batches of
 //    (nearly) equal lengths keep their equal splits this way.
-// All lanes work side by side (a lane per share, a uniform loop over the sequences): a serial fill,
-// share after share, costs a lone wave more than ten microseconds.
+// All lanes work side by side, a lane per share. Nothing is requested before this is known, so it is kept short: where a
+// share's ends lie among the sequences is counted (their starts and ends ascend), and nothing is divided.
 __device__ __forceinline__ int bal_bounds(const AttnParams& p, int lane, int start, int steps, int total) {
     const int W = p.bal_chunks;
-    const int nseq = __popcll(__ballot(steps > 0));
+    const uint64_t usable = __ballot(steps > 0);
+    const int nseq = __popcll(usable);
     // start-up stretches in front of this lane's sequence: the usable sequences before it
-    const int before = __popcll(__ballot(steps > 0) & ((1ull << lane) - 1ull));
+    const int before = __popcll(usable & ((1ull << lane) - 1ull));
     const int lstart = start + kBalPieceCost * before; // this lane's sequence on the stretched line
     const int ltotal = total + kBalPieceCost * nseq;
-    const int raw = (int)((int64_t)min(lane, W) * ltotal / W);
-    const int snap = min(kBalSnap, ltotal / W / 4);
-    int even = lane < W ? -1 : total;
+    uint32_t part, over; // ltotal / W and what is left: lane * ltotal / W without a long division
+    part = fast_div((uint32_t)ltotal, p.by_shares, over);
+    uint32_t rem;
+    const int raw = lane < W ? (int)(lane * part + fast_div(lane * over, p.by_shares, rem)) : ltotal;
+    const int snap = min(kBalSnap, (int)part / 4);
+    int at = -1; // the last sequence that starts at or before `raw` (a usable one: no other stands alone at its place)
+    for (int i = 0; i < p.B; ++i) at += __builtin_amdgcn_readlane(lstart, i) <= raw ? 1 : 0;
+    const int l0 = __shfl(lstart, at), s0 = __shfl(start, at), t = __shfl(steps, at);
+    const int lend = l0 + kBalPieceCost + t;
+    const int even = lane >= W ? total : raw - l0 <= kBalPieceCost + snap ? s0 : lend - raw <= snap ? s0 + t : s0 + (raw - l0 - kBalPieceCost);
+    if (p.bal_per_seq.d == 0) return even;
+    uint32_t j;
+    const int b = min((int)fast_div((uint32_t)lane, p.bal_per_seq, j), p.B - 1);
+    const int k = (int)fast_div((uint32_t)wave_max(steps) + p.bal_per_seq.d - 1, p.bal_per_seq, rem);
+    const int sb = __shfl(start, b), tb = __shfl(steps, b);
+    const int regular = lane < W ? sb + (int)min(j * (uint32_t)k, (uint32_t)tb) : total;
+    // a share's pieces: the usable sequences that start before its end, without those that end at or before its start
+    const int even_hi = lane + 1 < W ? __shfl_down(even, 1) : total, regular_hi = lane + 1 < W ? __shfl_down(regular, 1) : total;
+    const int from = steps > 0 ? start : INT32_MAX, to = steps > 0 ? start + steps : INT32_MAX;
+    int even_n = 0, regular_n = 0;
     for (int i = 0; i < p.B; ++i) {
-        const int l0 = __builtin_amdgcn_readlane(lstart, i), s0 = __builtin_amdgcn_readlane(start, i);
-        const int t = __builtin_amdgcn_readlane(steps, i);
-        const int lend = l0 + kBalPieceCost + t;
-        if (t > 0 && l0 <= raw && raw < lend) {
-            if (raw - l0 <= kBalPieceCost + snap) even = s0;
-            else if (lend - raw <= snap) even = s0 + t;
-            else even = s0 + (raw - l0 - kBalPieceCost);
-        }
+        const int f = __builtin_amdgcn_readlane(from, i), e = __builtin_amdgcn_readlane(to, i);
+        even_n += (f < even_hi ? 1 : 0) - (e <= even ? 1 : 0);
+        regular_n += (f < regular_hi ? 1 : 0) - (e <= regular ? 1 : 0);
     }
-    if (even < 0) even = total; // raw == ltotal only for lanes >= W; an empty batch has no stretch to fall into
-    int bounds = even;
-    if (W % p.B == 0) {
-        const int r = W / p.B;
-        int smax = steps;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) smax = max(smax, __shfl_xor(smax, o));
-        const int k = (smax + r - 1) / r;
-        const int b = min(lane / r, p.B - 1), j = lane % r;
-        const int sb = __shfl(start, b), tb = __shfl(steps, b);
-        const int regular = lane < W ? sb + min(j * k, tb) : total;
-        if (bal_worst(p, lane, start, steps, total, regular) <= bal_worst(p, lane, start, steps, total, even)) bounds = regular;
-    }
-    return bounds;
+    auto cost = [&](int lo, int hi, int n) __attribute__((always_inline)) { return lane < W && hi > lo ? hi - lo + kBalPieceCost * n : 0; };
+    return wave_max(cost(regular, regular_hi, regular_n)) <= wave_max(cost(even, even_hi, even_n)) ? regular : even;
 }
 
 } // namespace vs

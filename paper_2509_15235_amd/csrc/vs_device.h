@@ -110,11 +110,12 @@ __device__ __forceinline__ int32_t wave_min(int32_t x) {
     return wave_all(x, [](int32_t a, int32_t b) { return min(a, b); });
 }
 
-// Sum of the lanes up to and including one's own (DPP: within rows of sixteen, then across them).
-__device__ __forceinline__ float wave_scan(float x) {
-    auto add = [](float v, uint32_t u) __attribute__((always_inline)) { return v + __uint_as_float(u); };
-    auto shifted = [](float v, auto ctrl, auto rows) __attribute__((always_inline)) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+// Sum of the lanes up to and including one's own (DPP: within rows of sixteen, then across them). T: 32 bits.
+template <typename T>
+__device__ __forceinline__ T wave_scan(T x) {
+    auto add = [](T v, uint32_t u) __attribute__((always_inline)) { return v + __builtin_bit_cast(T, u); };
+    auto shifted = [](T v, auto ctrl, auto rows) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int32_t, v), decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
     };
     using std::integral_constant;
     x = add(x, shifted(x, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{})); // row_shr 1, 2, 4, 8

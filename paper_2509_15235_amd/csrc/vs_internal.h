@@ -79,9 +79,10 @@ struct AttnParams {
     int32_t total_wgs;          // B * Hkv * num_splits * row_groups
     FastDiv by_splits, by_groups, by_heads; // workgroup id -> (sequence, KV head, row group, split)
     int32_t by_length;          // pipelined kernel without key splits: workgroups take the sequences longest first
-    int32_t* bal_table;         // balanced schedule: 64 words of workspace, the share boundaries (main kernel -> combine)
     int32_t bal_chunks;         // balanced schedule: equal shares of the batch's keys per (KV head, row group); else 0.
                                 // num_splits then counts partial-result slots per KV head (shares + sequences)
+    FastDiv by_shares;          // bal_chunks
+    FastDiv bal_per_seq;        // bal_chunks / B where that is whole; else d = 0
 };
 
 struct AcceptParams {
