@@ -6,9 +6,11 @@
 // B operand of O^T += V^T . P^T, V is transposed by ds_read_b64_tr_b16 on its way out of LDS.
 //
 // A workgroup of eight waves owns NRB row blocks x KQ = 8 / NRB key parts of a split. A round is NT = 4 tiles of 32 keys
-// in LDS; the next round is requested when this one has left the staging registers, and two sets of tiles make one
-// barrier a round enough. The first round's loads are issued before anything is waited for, ordered by stage
-// (stage j holds the j-th tile of every key part), and a stage is worked on while the later ones are still on their way.
+// in LDS; two sets of tiles make one barrier a round enough. The next two rounds are on their way in two sets of
+// staging registers (one set, us: 8 x 31 nodes, 32 / 8 heads of 64, 257 .. 2047 keys 14.9, so 14.1; 4 x 60, 32 / 32 heads, 1500 keys 27.5 /
+// 26.2; 2 x 1500 18.9 / 18.1; 60 nodes, 28 / 4 heads, 6684 keys 19.7 / 19.4). The first round's loads are issued
+// before anything is waited for, ordered by stage (stage j holds the j-th tile of every key part), and a stage is worked on while the
+// later ones are still on their way.
 // Two waves per SIMD cover each other's stalls; at the end the key parts are merged through LDS (log-sum-exp).
 // Splits that fit the resident kernel run there: its parts need no merge.
 #include <type_traits>
@@ -21,7 +23,7 @@ namespace {
 
 constexpr int kRndWaves = 8;
 
-template <int D, int NRB>
+template <int D, int NRB, bool PAGED>
 __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(const AttnParams p) {
     constexpr int NT = kRoundKeys / kTileKeys; // tiles of a round
     constexpr int KS = D / 16;          // k-steps of the S^T product
@@ -29,10 +31,11 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     constexpr int KQ = kRndWaves / NRB; // key parts inside the workgroup
     constexpr int PPM = (NT + KQ - 1) / KQ; // tiles per key part = stages
     constexpr int SUB = kTileKeys * D;  // elements per 32-key tile of K (or V)
-    constexpr int BPS = SUB * 2 / 1024; // 1 KB copy blocks per tile
     constexpr int LPR = D / 8;          // lanes (16-byte chunks) per row
     constexpr int RPI = 64 / LPR;       // rows per load instruction
-    constexpr int SPW = (KQ * BPS + kRndWaves - 1) / kRndWaves; // copy blocks per wave, stage and tensor
+    constexpr int RPB = kRndWaves * RPI;  // rows that one load of every wave fetches: one tile (128 channels) or two
+    constexpr int NB = kRoundKeys / RPB;  // loads per wave and tensor in a round
+    static_assert(RPB % kTileKeys == 0 && KQ * kTileKeys % RPB == 0, "loads lie in a stage");
     constexpr int TILE_BYTES = 2 * NT * SUB * 2;
     constexpr int MERGE_BYTES = kRndWaves * (DB * 1024 + 128) * 4; // every wave's exchange area: accumulators, max, sum
     constexpr int Q_BYTES = NRB * kRowBlock * D * 2;
@@ -67,85 +70,55 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
 
     const int32_t S = p.prefix_len[b]; // requested first, needed last: everything below is issued before it arrives
 
-    // ---- copy the first round's keys and values. Stage j = one tile of every key part (tile j * KQ + kq);
-    // inside a stage, copy block i = (key part i / BPS, rows RPI * (i % BPS) ..) and wave w takes
-    // blocks w, w + 8, ...; one load instruction reads RPI whole rows (1 KB of consecutive memory).
-    // The loads do not wait for the prefix length: they are clamped to the cache (not to the
-    // sequence), and rows that turn out to lie past the sequence's last key are zeroed on their
-    // way into LDS (whatever the cache holds there - NaN included - must not meet a zero
-    // probability in the V product). A block-table entry outside the pool reads block 0. Chunk c
-    // of tile row r lands where the fragment reads expect it (same placement as the streaming
-    // kernel):
-    //   K: ((r/16)*DB + c/4) * 1024 + (c%4) * 256 + ((r%16) ^ 4*(c%4)) * 16
-    //   V: ((r/16)*DB + c/4) * 1024 + (4*(r%16) + c%4) * 16
-    // (No branch around a block's loads or stores: a conditional assignment of the staging
-    // array makes the compiler spill the whole array at every branch. Slots of tiles past the
-    // split's last one receive zeros and are never read.)
+    // ---- request the first round's keys and values. Load u of wave w fetches rows u * RPB + w * RPI .. + RPI - 1 of the round, 1 KB
+    // of consecutive memory. The loads do not wait for the prefix length: they are bounded by the cache (not by the
+    // sequence), and values past the sequence's last key are zeroed on their way into LDS (whatever the
+    // cache holds there - NaN included - must not meet a zero probability). A block-table entry outside the pool reads
+    // block 0 (reported through status).
     const uint16_t* kbase = (const uint16_t*)p.k;
     const uint16_t* vbase = (const uint16_t*)p.v;
-    const int64_t head_base = (p.paged ? 0 : (int64_t)b * p.stride_seq) + (int64_t)kvh * p.stride_head;
-    const int stride_tok = (int)p.stride_tok;
+    const int64_t head_base = (PAGED ? 0 : (int64_t)b * p.stride_seq) + (int64_t)kvh * p.stride_head;
+    const uint32_t stride = (uint32_t)p.stride_tok * 2u; // bytes; the host keeps a slice's offsets below 2^31 bytes
     const int lrow = lane / LPR, lchunk = lane % LPR;
     const int k0 = split * p.keys_per_split; // the host keeps k0 below max_prefix_len + tree_keys, hence inside the cache
-    const int64_t cache_tokens = p.paged ? (int64_t)p.max_blocks * p.block_size : p.capacity;
+    const int srow = wave * RPI + lrow;      // this lane's row of load 0
+    u32x4 kreg[2][NB], vreg[2][NB];          // two rounds
+    // Paged caches: the offsets of the next 64 blocks sit one per lane (see attention_mfma_pipe.hip).
+    const int32_t* bt_row = PAGED ? p.block_table + (int64_t)b * p.max_blocks : nullptr;
+    int bt_base = k0 >> p.block_shift;
+    uint32_t bt_lo = 0, bt_hi = 0;
+    int32_t bt_next = 0; // block id of lane 0 + 32 + lane, on its way
+    auto bt_fetch = [&](int first) __attribute__((always_inline)) { return bt_row[min(first + lane, p.max_blocks - 1)]; };
+    auto bt_set = [&](int32_t blk) __attribute__((always_inline)) {
+        if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
+        const int64_t off = (int64_t)blk * p.stride_block;
+        bt_lo = (uint32_t)off;
+        bt_hi = (uint32_t)(off >> 32);
+    };
+    // byte offset of this lane's 16 bytes of the rows from r0 on, in one cache block; rows past `last` repeat it
+    auto paged_at = [&](int r0, int last) __attribute__((always_inline)) {
+        const int rel = (min(r0, last) >> p.block_shift) - bt_base; // 0 .. 63
+        const int64_t block = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bt_hi, rel) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)bt_lo, rel));
+        return (head_base + block) * 2 + (uint32_t)(min(r0 + lrow, last) & (p.block_size - 1)) * stride + lchunk * 16;
+    };
+    if constexpr (PAGED) {
+        const int32_t now = bt_fetch(bt_base);
+        bt_next = bt_fetch(bt_base + 32);
+        bt_set(now);
+    }
+    const uint32_t lane_off = (uint32_t)srow * stride + lchunk * 16; // contiguous caches
+    const __amdgpu_buffer_rsrc_t krs0 = slice_of(kbase + head_base, k0, p, stride), vrs0 = slice_of(vbase + head_base, k0, p, stride);
+    const int64_t cache_tokens = PAGED ? (int64_t)p.max_blocks * p.block_size : p.capacity;
     const int kend = (int)(cache_tokens < (int64_t)k0 + p.keys_per_split ? cache_tokens : (int64_t)k0 + p.keys_per_split);
-    u32x4 kreg[PPM][SPW], vreg[PPM][SPW];
-    // tile and first row (inside the tile) of this wave's u-th copy block of stage j; blocks past the
-    // stage's last one (KQ * BPS not a multiple of the wave count) repeat its last block
-    auto block_tile = [&](int j, int u) __attribute__((always_inline)) {
-        const int i = min(wave + kRndWaves * u, KQ * BPS - 1);
-        return min(j * KQ + i / BPS, NT - 1);
-    };
-    auto block_row = [&](int u) __attribute__((always_inline)) {
-        const int i = min(wave + kRndWaves * u, KQ * BPS - 1);
-        return (i % BPS) * RPI;
-    };
+    constexpr int LPS = KQ * kTileKeys / RPB; // loads per stage
     auto issue_stage = [&](auto is_v, int j) __attribute__((always_inline)) {
         constexpr bool ISV = decltype(is_v)::value;
 #pragma unroll
-        for (int u = 0; u < SPW; ++u) {
-            const int r0 = min(k0 + kTileKeys * block_tile(j, u) + block_row(u), kend - 1); // RPI divides 16: one cache block in paged mode
-            int tok = min(r0 + lrow, kend - 1);
-            int64_t base = head_base;
-            if (p.paged) {
-                int32_t blk = p.block_table[(int64_t)b * p.max_blocks + (r0 >> p.block_shift)];
-                if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-                base += (int64_t)blk * p.stride_block;
-                tok &= p.block_size - 1;
-            }
-            const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
-            if constexpr (ISV) vreg[j][u] = *(const u32x4*)(vbase + base + off);
-            else kreg[j][u] = *(const u32x4*)(kbase + base + off);
+        for (int u = j * LPS; u < (j + 1) * LPS; ++u) {
+            u32x4& to = ISV ? vreg[0][u] : kreg[0][u];
+            if constexpr (PAGED) to = *(const u32x4*)((const char*)(ISV ? vbase : kbase) + paged_at(k0 + u * RPB + wave * RPI, kend - 1));
+            else to = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ISV ? vrs0 : krs0, lane_off + (uint32_t)(u * RPB) * stride, 0, 0));
         }
-    };
-    // Later rounds (the sequence's length is known by then, tokens past the split's last one repeat it). Paged
-    // caches: the ids of the next 64 blocks sit one per lane (see attention_mfma_pipe.hip).
-    int bt_base = k0 >> p.block_shift;
-    int32_t bt_win = 0;
-    auto bt_fetch = [&]() __attribute__((always_inline)) { bt_win = p.block_table[(int64_t)b * p.max_blocks + min(bt_base + lane, p.max_blocks - 1)]; };
-    if (p.paged) bt_fetch();
-    auto issue_round = [&](int kr, int last) __attribute__((always_inline)) {
-        if (p.paged && ((kr + NT * kTileKeys - 1) >> p.block_shift) >= bt_base + 64) { // uniform
-            bt_base = kr >> p.block_shift;
-            bt_fetch();
-        }
-#pragma unroll
-        for (int j = 0; j < PPM; ++j)
-#pragma unroll
-            for (int u = 0; u < SPW; ++u) {
-                const int r0 = min(kr + kTileKeys * block_tile(j, u) + block_row(u), last);
-                int tok = min(r0 + lrow, last);
-                int64_t base = head_base;
-                if (p.paged) {
-                    int32_t blk = __builtin_amdgcn_readlane(bt_win, (r0 >> p.block_shift) - bt_base);
-                    if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-                    base += (int64_t)blk * p.stride_block;
-                    tok &= p.block_size - 1;
-                }
-                const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
-                kreg[j][u] = *(const u32x4*)(kbase + base + off);
-                vreg[j][u] = *(const u32x4*)(vbase + base + off);
-            }
     };
     issue_stage(std::false_type{}, 0); // the first keys lead: the first scores need them and the queries
 
@@ -192,25 +165,61 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     if (merge && tid == 0) merge_open(gate, seen);
     const int k1 = min(nk, k0 + p.keys_per_split);
 
+    // ---- later rounds: the sequence's length is known. Rows past the split's last key read as zeros (paged caches: repeat it). Round 1
+    // is requested whether it exists or not: behind a branch the compiler could not count these loads and would wait for them
+    // with the first round's (8 x 31 nodes, 32 / 8 heads of 64, 257 .. 2047 keys: 13.9 us, so 14.8). For the rounds behind it what
+    // such a request takes at the end of a split costs more than the wait (16 x 16 nodes, 28 / 4 heads, 1500 keys 19.2, always 21.0).
+    const uint32_t live_bytes = (uint32_t)(k1 - k0 - 1) * stride + D * 2;
+    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(kbase + head_base) + (int64_t)k0 * stride, 0, (int)live_bytes, 0x00027000);
+    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(vbase + head_base) + (int64_t)k0 * stride, 0, (int)live_bytes, 0x00027000);
+    auto issue_round = [&](auto set_tag, int kr) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_tag)::value;
+        if constexpr (PAGED) {
+            if ((min(kr, k1 - 1) >> p.block_shift) >= bt_base + 32) { // uniform
+                bt_base += 32;
+                bt_set(bt_next);
+                bt_next = bt_fetch(bt_base + 32);
+            }
+            int64_t at[NB];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) at[u] = paged_at(kr + u * RPB + wave * RPI, k1 - 1);
+#pragma unroll
+            for (int u = 0; u < NB; ++u) kreg[SET][u] = *(const u32x4*)((const char*)kbase + at[u]);
+#pragma unroll
+            for (int u = 0; u < NB; ++u) vreg[SET][u] = *(const u32x4*)((const char*)vbase + at[u]);
+        } else {
+            const uint32_t off = lane_off + (uint32_t)(kr - k0) * stride;
+#pragma unroll
+            for (int u = 0; u < NB; ++u) kreg[SET][u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(krs, off + (uint32_t)(u * RPB) * stride, 0, 0));
+#pragma unroll
+            for (int u = 0; u < NB; ++u) vreg[SET][u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(vrs, off + (uint32_t)(u * RPB) * stride, 0, 0));
+        }
+    };
+    constexpr int ROUND = NT * kTileKeys;
+    using Set0 = std::integral_constant<int, 0>;
+    using Set1 = std::integral_constant<int, 1>;
+    issue_round(Set1{}, k0 + ROUND);
+
     // per-lane LDS offsets (elements); everything else is a compile-time immediate
     const int k_lane[2] = {(col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (4 * half)) * 8,
                            (col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (8 + 4 * half)) * 8};
     const int t16 = lane & 15;
     const int v_lane = half * 128 + (t16 >> 2) * 32 + ((lane >> 4) & 1) * 16 + ((t16 >> 1) & 1) * 8 + (t16 & 1) * 4;
-    // the staged copy blocks of stage j -> LDS; LIVE: rows past the split's last key become zeros
-    auto stash_stage = [&](auto live_tag, int j, int at) __attribute__((always_inline)) {
-        constexpr bool LIVE = decltype(live_tag)::value;
+    // loads [u0, u1) of a staged round -> LDS. Chunk c of tile row r lands where the fragment reads expect it (same placement as
+    // the streaming kernels):
+    //   K: ((r/16)*DB + c/4) * 1024 + (c%4) * 256 + ((r%16) ^ 4*(c%4)) * 16
+    //   V: ((r/16)*DB + c/4) * 1024 + (4*(r%16) + c%4) * 16
+    const int rr = srow & (kTileKeys - 1); // (RPB is a multiple of a tile)
+    const uint32_t in_tiles = (uint32_t)((srow / kTileKeys) * (SUB * 2) + ((rr >> 4) * DB + (lchunk >> 2)) * 1024);
+    const uint32_t ko = in_tiles + (lchunk & 3) * 256 + (((rr & 15) ^ (4 * (lchunk & 3))) * 16), vo = in_tiles + (4 * (rr & 15) + (lchunk & 3)) * 16;
+    auto stash = [&](auto set_tag, auto first_tag, int u0, int u1, int at) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_tag)::value;
 #pragma unroll
-        for (int u = 0; u < SPW; ++u) {
-            if (SPW * kRndWaves == KQ * BPS || wave + kRndWaves * u < KQ * BPS) { // uniform per wave
-                const int t = block_tile(j, u), rr = block_row(u) + lrow, c = lchunk;
-                const bool live = !LIVE || k0 + kTileKeys * t + rr < k1;
-                const u32x4 zero = {0u, 0u, 0u, 0u};
-                const uint32_t ko = (uint32_t)(((rr >> 4) * DB + (c >> 2)) * 1024 + (c & 3) * 256 + (((rr & 15) ^ (4 * (c & 3))) * 16));
-                const uint32_t vo = (uint32_t)(((rr >> 4) * DB + (c >> 2)) * 1024 + (4 * (rr & 15) + (c & 3)) * 16);
-                *(u32x4*)((char*)(sK + at + t * SUB) + ko) = live ? kreg[j][u] : zero;
-                *(u32x4*)((char*)(sV + at + t * SUB) + vo) = live ? vreg[j][u] : zero;
-            }
+        for (int u = u0; u < u1; ++u) {
+            *(u32x4*)((char*)(sK + at) + ko + u * (RPB / kTileKeys * SUB * 2)) = kreg[SET][u];
+            u32x4 v = vreg[SET][u];
+            if (decltype(first_tag)::value && k0 + u * RPB + srow >= k1) v = u32x4{0u, 0u, 0u, 0u};
+            *(u32x4*)((char*)(sV + at) + vo + u * (RPB / kTileKeys * SUB * 2)) = v;
         }
     };
 
@@ -308,7 +317,7 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     // for exactly the stage's before their first use)
 #pragma unroll
     for (int j = 0; j < PPM; ++j) {
-        stash_stage(std::true_type{}, j, 0);
+        stash(Set0{}, std::true_type{}, j * LPS, (j + 1) * LPS, 0);
         if (j == 0) {
 #pragma unroll
             for (int i = 0; i < QPW; ++i) store_q_piece<D>(sQ + rbw * (kRowBlock * D), qreg[i], min(kq * QPW + i, KS - 1), lane);
@@ -320,23 +329,22 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
         }
         scores(j, 0);
     }
-    constexpr int ROUND = NT * kTileKeys;
-    if (k0 + ROUND < k1) issue_round(k0 + ROUND, k1 - 1);
+    if (k0 + 2 * ROUND < k1) issue_round(Set0{}, k0 + 2 * ROUND);
     output(std::true_type{}, k0, 0);
-    // ---- the other rounds: two sets of tiles in LDS, one barrier per round. A round is requested when the one
-    // before it has left the staging registers.
-    {
-        int at = TILE_BYTES / 2;
-        for (int kr = k0 + ROUND; kr < k1; kr += ROUND) {
+    // ---- the other rounds: two sets of tiles in LDS, one barrier per round
+    auto round = [&](auto set_tag, int kr) __attribute__((always_inline)) {
+        constexpr int at = decltype(set_tag)::value * (TILE_BYTES / 2);
+        stash(set_tag, std::false_type{}, 0, NB, at);
+        __syncthreads();
+        if (kr + 2 * ROUND < k1) issue_round(set_tag, kr + 2 * ROUND);
 #pragma unroll
-            for (int j = 0; j < PPM; ++j) stash_stage(std::false_type{}, j, at);
-            __syncthreads();
-            if (kr + ROUND < k1) issue_round(kr + ROUND, k1 - 1);
-#pragma unroll
-            for (int j = 0; j < PPM; ++j) scores(j, at);
-            output(std::false_type{}, kr, at);
-            at = TILE_BYTES / 2 - at;
-        }
+        for (int j = 0; j < PPM; ++j) scores(j, at);
+        output(std::false_type{}, kr, at);
+    };
+    for (int kr = k0 + ROUND; kr < k1; kr += 2 * ROUND) {
+        round(Set1{}, kr);
+        if (kr + ROUND >= k1) break;
+        round(Set0{}, kr + ROUND);
     }
 
     // ---- merge the key parts through LDS (log-sum-exp) and write the rows. The work is shared: a row
@@ -473,7 +481,8 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
 template <int D, int NRB>
 hipError_t launch_rnd(const AttnParams& p, hipStream_t s) {
     const dim3 grid(((p.total_wgs + 7) / 8) * 8);
-    hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB>), grid, dim3(kRndWaves * kWave), 0, s, p);
+    if (p.paged) hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, true>), grid, dim3(kRndWaves * kWave), 0, s, p);
+    else hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, false>), grid, dim3(kRndWaves * kWave), 0, s, p);
     return hipGetLastError();
 }
 
