@@ -2,7 +2,7 @@
 // survives iff it equals the target's argmax at its parent; the deepest surviving node
 // ends the accepted path and its own argmax is the bonus token.
 //
-// Two kernels: (1) a bandwidth-bound scan that reduces every chunk of a logits row to (max, first index), (2) one workgroup
+// Two kernels (one for few logits, below): (1) a bandwidth-bound scan that reduces every chunk of a logits row to (max, first index), (2) one workgroup
 // per sequence that finishes the row argmax and walks the tree.
 #include <atomic>
 
@@ -43,16 +43,11 @@ __device__ __forceinline__ Best wave_best(Best b) {
 constexpr int kRowThreads = kScanThreads / VS_MAX_TREE; // threads of the walk that share a row's chunks
 static_assert(kRowThreads == 8, "three steps of a butterfly");
 
-// grid = B*T*chunks, block = THREADS: (max, first index) of a chunk. The maximum is found on values alone (one v_max per element);
-// the index is recovered afterwards as the lowest position that equals the wave's maximum. NaN never equals anything
-// and never survives fmaxf, -0 == +0.
+// (max, first index) of the part of a chunk that a wave holds, in every lane. The maximum is found on values alone (one v_max
+// per element); the index is recovered afterwards as the lowest position that equals the wave's maximum. NaN never equals
+// anything and never survives fmaxf, -0 == +0.
 template <int THREADS>
-__global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const AcceptParams p) {
-    __shared__ float sv[THREADS / kWave];
-    __shared__ int32_t si[THREADS / kWave];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const ScanItem it = scan_item(p.by_chunks);
-    const ScanChunk c = scan_load<THREADS>(p.logits + (int64_t)it.row * p.ld, it.chunk, p.V);
+__device__ __forceinline__ Best chunk_best(const ScanChunk& c, int chunk, int tid) {
     float m = c.tail;
 #pragma unroll
     for (int j = 0; j < kScanVec; ++j)
@@ -69,12 +64,23 @@ __global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const Accept
     }
     // a left-to-right '>' scan never displaces a NaN in column 0
     const float first = c.nvec > 0 ? c.a[0][0] : c.tail;
-    if (it.chunk == 0 && tid == 0 && first != first) {
+    if (chunk == 0 && tid == 0 && first != first) {
         m = INFINITY;
         idx = 0;
     }
-    Best best = {m, idx}; // lanes without the wave's maximum keep INT32_MAX and lose the tie
-    best = wave_best(best);
+    return wave_best({m, idx}); // lanes without the wave's maximum keep INT32_MAX and lose the tie
+}
+__device__ __forceinline__ uint64_t pair_of(Best b) { return ((uint64_t)(uint32_t)b.i << 32) | __float_as_uint(b.v); }
+
+// grid = B*T*chunks, block = THREADS.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const AcceptParams p) {
+    __shared__ float sv[THREADS / kWave];
+    __shared__ int32_t si[THREADS / kWave];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const ScanItem it = scan_item(p.by_chunks);
+    const ScanChunk c = scan_load<THREADS>(p.logits + (int64_t)it.row * p.ld, it.chunk, p.V);
+    Best best = chunk_best<THREADS>(c, it.chunk, tid);
     if (lane == 0) {
         sv[wave] = best.v;
         si[wave] = best.i;
@@ -83,24 +89,18 @@ __global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const Accept
     if (tid == 0) {
 #pragma unroll
         for (int w = 1; w < THREADS / kWave; ++w) take(best, sv[w], si[w]);
-        p.pairs[(int64_t)it.row * p.chunks + it.chunk] = ((uint64_t)(uint32_t)best.i << 32) | __float_as_uint(best.v);
+        p.pairs[(int64_t)it.row * p.chunks + it.chunk] = pair_of(best);
     }
 }
 
-// grid = B, block = 512. Eight threads share a row's chunks, four pairs each in flight; the first wave holds the tree, a lane
-// per node, asked for with the pairs.
-__global__ __launch_bounds__(kScanThreads) void accept_walk_kernel(const AcceptParams p) {
-    __shared__ int32_t samax[VS_MAX_TREE];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+// The walk over sequence b's tree, `pairs` its rows' (all threads of a workgroup of 512 or more). Eight threads share a row's chunks,
+// four pairs each in flight; the first wave holds the tree, a lane per node, asked for before (parent, draft).
+__device__ __forceinline__ void accept_walk(const AcceptParams& p, int b, const uint64_t* pairs, int32_t parent, int32_t draft, int32_t* samax) {
+    const int tid = threadIdx.x, lane = tid & 63;
     const int T = p.T, i = tid / kRowThreads, sub = tid % kRowThreads;
-    int32_t parent = -2, draft = -1;
-    if (tid < kWave) {
-        parent = tree_lane(p.parent + (int64_t)b * T, T);
-        draft = p.draft[(int64_t)b * T + min(lane, T - 1)];
-    }
     {
         constexpr int kPre = 4;
-        const uint64_t* pairs = p.pairs + ((int64_t)b * T + min(i, T - 1)) * p.chunks;
+        pairs += (int64_t)min(i, T - 1) * p.chunks;
         Best best = {-INFINITY, INT32_MAX};
         for (int c0 = sub; c0 < p.chunks; c0 += kRowThreads * kPre) {
             uint64_t w[kPre];
@@ -143,6 +143,44 @@ __global__ __launch_bounds__(kScanThreads) void accept_walk_kernel(const AcceptP
     }
 }
 
+// grid = B, block = 512.
+__global__ __launch_bounds__(kScanThreads) void accept_walk_kernel(const AcceptParams p) {
+    __shared__ int32_t samax[VS_MAX_TREE];
+    const int b = blockIdx.x;
+    int32_t parent = -2, draft = -1;
+    if (threadIdx.x < kWave) {
+        parent = tree_lane(p.parent + (int64_t)b * p.T, p.T);
+        draft = p.draft[(int64_t)b * p.T + min((int)threadIdx.x, p.T - 1)];
+    }
+    accept_walk(p, b, p.pairs + (int64_t)b * p.T * p.chunks, parent, draft, samax);
+}
+
+// Both in one for few logits: a workgroup of sixteen waves per sequence scans all of its rows, a piece of 1024 logits a wave, and
+// walks the tree. Bound by one trip to memory; the second launch and the trip for the pairs are gone (us, two kernels /
+// one: 1 x 8 x 1000 5.7 / 4.3, 16 x 16 x 1024 6.7 / 5.5, 16 x 4 x 4000 7.0 / 5.4). With two pieces a wave it is no better (16 x 4 x 8000
+// 7.1 / 7.1), with four worse (16 x 8 x 8000 7.3 / 10.6): the waves of one CU then take turns at the index search.
+// grid = B, block = 1024.
+constexpr int kSmallThreads = 1024, kSmallItems = kSmallThreads / kWave, kSmallPiece = kWave * kScanVec * 4;
+__global__ __launch_bounds__(kSmallThreads) void accept_small_kernel(const AcceptParams p) {
+    __shared__ uint64_t s_pairs[kSmallItems];
+    __shared__ int32_t samax[VS_MAX_TREE];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int32_t parent = -2, draft = -1;
+    if (wave == 0) {
+        parent = tree_lane(p.parent + (int64_t)b * p.T, p.T);
+        draft = p.draft[(int64_t)b * p.T + min(lane, p.T - 1)];
+    }
+    if (wave < p.T * p.chunks) { // uniform
+        uint32_t piece;
+        const uint32_t row = fast_div((uint32_t)wave, p.by_chunks, piece);
+        const ScanChunk c = scan_load<kWave, kSmallPiece>(p.logits + ((int64_t)b * p.T + row) * p.ld, (int)piece, p.V, lane);
+        const Best best = chunk_best<kWave>(c, (int)piece, lane);
+        if (lane == 0) s_pairs[wave] = pair_of(best);
+    }
+    __syncthreads();
+    accept_walk(p, b, s_pairs, parent, draft, samax);
+}
+
 constexpr int kMaxDevices = 64;
 std::atomic<void*> scratch_of[kMaxDevices]; // device address of `scratch` on each device, null = not asked yet
 
@@ -168,6 +206,13 @@ void* scratch_address() {
 
 // workspace: 8 bytes per (row, chunk); sized by chunks half as long, it holds them with room to spare
 hipError_t launch_accept(AcceptParams p, void* workspace, hipStream_t s) {
+    const int64_t pieces = ((int64_t)p.V + kSmallPiece - 1) / kSmallPiece;
+    if (pieces * p.T <= kSmallItems) { // (figures at the kernel)
+        p.chunks = (int32_t)pieces;
+        p.by_chunks = fast_div_by(p.chunks);
+        hipLaunchKernelGGL(accept_small_kernel, dim3(p.B), dim3(kSmallThreads), 0, s, p);
+        return hipGetLastError();
+    }
     p.chunks = (int32_t)(((int64_t)p.V + kScanChunk - 1) / kScanChunk);
     p.by_chunks = fast_div_by(p.chunks);
     p.pairs = (uint64_t*)workspace;

@@ -27,18 +27,18 @@ struct ScanChunk {
     float tail;
     int32_t begin, nvec, tail_at; // tail_at: >= end when this thread has none
 };
-template <int THREADS>
-__device__ __forceinline__ ScanChunk scan_load(const float* lg, int chunk, int V) {
+template <int THREADS, int CHUNK = kScanChunk>
+__device__ __forceinline__ ScanChunk scan_load(const float* lg, int chunk, int V, int tid = threadIdx.x) {
     ScanChunk c;
-    c.begin = chunk * kScanChunk;
-    const int end = V - c.begin < kScanChunk ? V : c.begin + kScanChunk;
+    c.begin = chunk * CHUNK;
+    const int end = V - c.begin < CHUNK ? V : c.begin + CHUNK;
     c.nvec = (end - c.begin) >> 2;
 #pragma unroll
     for (int j = 0; j < kScanVec; ++j) {
-        const int k = threadIdx.x + j * THREADS;
+        const int k = tid + j * THREADS;
         c.a[j] = k < c.nvec ? load4_stream(lg + c.begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     }
-    c.tail_at = c.begin + 4 * c.nvec + threadIdx.x;
+    c.tail_at = c.begin + 4 * c.nvec + tid;
     c.tail = c.tail_at < end ? lg[c.tail_at] : -INFINITY;
     if (c.tail_at >= end) c.tail_at = INT32_MAX;
     return c;

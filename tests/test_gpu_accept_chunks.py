@@ -33,6 +33,29 @@ def test_greedy_at_chunk_ends(gu, oracle_mod, V):
             np.testing.assert_array_equal(g, w)
 
 
+@pytest.mark.parametrize("T,V", [(16, 1024), (16, 1023), (17, 1024), (16, 1025), (5, 3072), (5, 3073), (1, 16384), (1, 16385), (8, 2047), (3, 4099)])
+def test_greedy_of_few_logits(gu, oracle_mod, T, V):
+    """One kernel up to sixteen pieces of 1024 logits, and just beyond: chains and wide trees, maxima at the pieces' ends."""
+    r = np.random.default_rng(T * V)
+    B = 5
+    parent = np.stack([np.array([-1] + [int(r.integers(max(0, i - 1 - b), i)) for i in range(1, T)], dtype=np.int32) for b in range(B)])
+    logits = r.standard_normal((B, T, V)).astype(np.float32)
+    at = [i for k in range(0, V + 1024, 1024) for i in (k - 1, k, k + 1) if 0 <= i < V] + [V - 1]
+    for b in range(B):
+        for t in range(T):
+            logits[b, t, r.choice(at, size=min(2, len(at)), replace=False)] = 9.0
+    logits[0, T - 1, :] = -np.inf
+    logits[1, T // 2, 0] = np.nan
+    tokens = np.zeros((B, T), dtype=np.int32)
+    tokens[:, 1:] = np.take_along_axis(logits.argmax(-1), np.maximum(parent[:, 1:], 0), axis=1)
+    tokens[2, T // 2] += 1
+    for ld, off in ((V, 0), (V + 3, 1)):
+        got = gu.run_accept(logits, tokens, parent, ld=ld, offset_elems=off)
+        want = oracle_mod.tree_accept(logits, tokens, parent)
+        for g, w in zip(got, want):
+            np.testing.assert_array_equal(g, w)
+
+
 @pytest.mark.parametrize("V", EDGES)
 def test_sampling_at_chunk_ends(gu, oracle_mod, V):
     B, T = 6, 5 if V >= 5 else 1
