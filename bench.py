@@ -51,9 +51,9 @@ def parse():
 
 
 def kernel_name(vs, plan, auto):
-    """The kernel behind a plan. LOOP in a plan that AUTO made without other knobs: the kernel of rounds, or the one
-    with tiles of the wave's own (one row group, few rows); else the straight loop."""
-    loop = "attn_mfma_resident_kernel (rounds) or attn_mfma_rows_kernel" if auto else "attn_mfma_kernel"
+    """The kernel behind a plan. LOOP in a plan that AUTO made without other knobs: the kernel of rounds, the one with tiles
+    of the wave's own (few rows), or for short splits the resident one; else the straight loop."""
+    loop = "attn_mfma_rounds_kernel, attn_mfma_rows_kernel or (short splits) attn_mfma_resident_kernel" if auto else "attn_mfma_kernel"
     k = {vs.VS_SCHED_PIPELINED: "attn_mfma_pipe_kernel", vs.VS_SCHED_BALANCED: "attn_mfma_pipe_kernel (balanced shares)",
          vs.VS_SCHED_RESIDENT: "attn_mfma_resident_kernel"}.get(plan.schedule, loop)
     return k + (" + merge of the splits" if plan.combine else "")

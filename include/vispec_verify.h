@@ -84,8 +84,8 @@ typedef enum vs_attn_impl { VS_IMPL_AUTO = 0, VS_IMPL_GENERIC = 1, VS_IMPL_MFMA 
 /* How the MFMA kernels are scheduled. LOOP streams 64-key tiles through LDS and runs a tile's
  * three stages (scores, softmax, output update) back to back (a plan that AUTO made reports LOOP for all
  * its kernels whose workgroups walk the keys step by step without that overlap: also the one with key tiles of
- * every wave's own, for few query rows, and the one that runs a split in rounds of 128 keys. Only AUTO without
- * any other knob takes those two; a descriptor that names LOOP gets the straight loop); PIPELINED overlaps the matrix-core
+ * every wave's own, for few query rows, the one that runs a split in rounds of 128 keys, and RESIDENT's for short splits of
+ * few rows. Only AUTO without any other knob takes those; a descriptor that names LOOP gets the straight loop); PIPELINED overlaps the matrix-core
  * work of the neighbouring tiles with the current tile's softmax (launches with many units);
  * RESIDENT keeps a split's whole key range (at most 192 keys) in LDS and splits the
  * keys once more among the waves of a workgroup (latency-bound launches with few units);
@@ -303,7 +303,7 @@ size_t vs_accept_sample_workspace_bytes(int32_t B, int32_t T, int32_t V); /* 0 f
  *   bonus_token  [B] int32 out
  *   status       [B] int32 out, optional
  *   workspace    at least vs_accept_sample_workspace_bytes(B,T,V) bytes, 256-byte aligned
- * Arithmetic is fp32 (exp2 of the hardware, sums over 4096-entry chunks merged per row), so a
+ * Arithmetic is fp32 (exp2 of the hardware, sums over 8192-entry chunks merged per row), so a
  * uniform that lies within ~1e-5 of its threshold may fall on the other side than in exact
  * arithmetic; either outcome is a valid draw.
  */

@@ -188,10 +188,11 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     // 40: 279 / 226, all 3000 keys 202 / 162; 64: 418 / 340, all 3000 keys 227 / 237. 32 / 32 heads,
     // 4 sequences: 120 / 77; 8: 237 / 168; 12: 262 / 201; 24: 422 / 361; 32: 518 / 487, and 32 folded layers
     // of 3136 keys 308 / 334.
-    // A launch that is one full round of whole sequences is left alone: unequal lengths would gain
-    // there too, equal ones lose the second kernel and the wait for the lengths (7 us of 60), and the
-    // host cannot tell which it has - such callers ask for VS_SCHED_BALANCED themselves. Two rounds or
-    // more are left alone as well: the gain shrinks with every round and equal lengths lose 4 - 8 %.
+    // (Both with a combine kernel behind them; shares now merge their own pieces and take 0.90 of that.)
+    // A launch that is one full round of whole sequences is left alone: unequal lengths would gain there too (32 x 60 nodes, 28 / 4
+    // heads, 1000 .. 8000 keys 210 / 152), equal and short ones lose (all of 1000 44 / 48, 3000 112 / 114), and the
+    // host cannot tell which it has - such callers ask for VS_SCHED_BALANCED themselves. Two rounds or more are left alone as
+    // well: nothing is gained (64 x 1000 .. 8000 317 / 321, all of 3000 220 / 218) and 32 / 32 heads lose 5 - 15 %.
     const int bal_waves = waves ? waves : (nrb > 4 ? 8 : 4);
     const int bal_rg = (nrb + bal_waves - 1) / bal_waves;
     const int bal_places = kNumCUs * (bal_waves == 8 ? 1 : 2);
