@@ -51,10 +51,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     constexpr bool QREG = RB == 1;      // the queries stay in registers
     constexpr int TILE_ELEMS = NW * 2 * SUB;
     constexpr int NP = 2 * DB;                                 // pieces of a row block's accumulators, see below
-    constexpr int XCH = NP * 512 + 128;                        // floats a wave's exchange area holds
-    constexpr int MERGE_ELEMS = NW * XCH * 2;
     constexpr int KEEP_ELEMS = TILE_ELEMS + RB * kRowBlock * D; // tiles, queries
-    constexpr int SMEM_ELEMS = KEEP_ELEMS > MERGE_ELEMS ? KEEP_ELEMS : MERGE_ELEMS;
+    constexpr int SMEM_ELEMS = KEEP_ELEMS + NW * 256;          // ... a reference and a sum per lane
+    static_assert(NP * 512 * 4 <= 2 * SUB * 2, "a row block's accumulators take the wave's tiles' place");
     static_assert(SMEM_ELEMS * 2 + 512 <= kLdsBytesPerCU, "LDS");
 
     // wave w: its K tile at smem + w * 2 * SUB, its V tile behind it, and behind all tiles the queries
@@ -334,11 +333,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     // registers (piece = channel block * 2 + half of its registers, the 16-byte unit of the partial-result layout):
     // wave w owns pieces w * PPW .., takes the other waves' versions of them and merges in ascending order.
     constexpr int PPW = NP / NW > 0 ? NP / NW : 1;
-    float* sm = (float*)smem;
-    float* mine = sm + wave * XCH;
+    // A wave hands its first row block over in the place of its own tiles, as soon as it is done with them: the last one then
+    // writes alone, and one barrier less (us: 3 x 2 nodes, 8 / 2 heads, 330 keys 6.9, so 6.5; 18 x 1, 28 / 4 heads, 1600 keys 16.5 / 16.1; 4 x 60,
+    // 32 / 32 heads, ~3100 keys 47.9 / 47.5).
+    auto area = [&](int w) __attribute__((always_inline)) { return (float*)(smem + w * 2 * SUB); };
+    float* const ml = (float*)(smem + KEEP_ELEMS); // [wave][reference, sum][lane]
+    float* const mine = area(wave);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        __syncthreads(); // every wave is done with the tiles, or with the row block before
+        if (rb > 0) __syncthreads(); // every wave is done with the row block before
 #pragma unroll
         for (int pc = 0; pc < NP; ++pc) {
             const int db = pc >> 1, hp = pc & 1;
@@ -348,15 +351,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
                 *(f32x4*)(mine + pc * 512 + hh * 256 + lane * 4) = w;
             }
         }
-        mine[NP * 512 + lane] = m2[rb];
-        mine[NP * 512 + 64 + lane] = lsum[rb];
+        ml[wave * 128 + lane] = m2[rb];
+        ml[wave * 128 + 64 + lane] = lsum[rb];
         __syncthreads();
         if (wave * PPW < NP) {
             float mo[NW], lo[NW];
 #pragma unroll
             for (int o = 0; o < NW; ++o) {
-                mo[o] = sm[o * XCH + NP * 512 + lane];
-                lo[o] = sm[o * XCH + NP * 512 + 64 + lane];
+                mo[o] = ml[o * 128 + lane];
+                lo[o] = ml[o * 128 + 64 + lane];
             }
             float M = mo[0];
 #pragma unroll
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
                 lall += lo[o] * f;
 #pragma unroll
                 for (int i = 0; i < PPW; ++i) {
-                    const float* src = sm + o * XCH + (wave * PPW + i) * 512 + lane * 4;
+                    const float* src = area(o) + (wave * PPW + i) * 512 + lane * 4;
                     const f32x4 a0 = *(const f32x4*)src, a1 = *(const f32x4*)(src + 256);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
