@@ -187,12 +187,11 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     }
     constexpr bool EARLY = !(BAL && PAGED && NW == 4); // registers: 4 waves of 128 channels 188 us, so 171 (8 x 60 nodes, 32 / 32 heads, 1024 .. 8191 keys)
     // The first four tiles - K(0), K(1), K(2), V(0), through register set 1 - are requested before
-    // the prefix length is known: clamped to the cache instead of the sequence, and rows that
+    // the prefix length is known: clamped to the longest allowed sequence instead of this one, and rows that
     // turn out to lie past the sequence's last key are zeroed when the tiles go into LDS
     // (whatever the cache holds there, NaN included, must not meet a zero probability).
     if constexpr (EARLY) {
-        const int64_t cache_tokens = PAGED ? (int64_t)p.max_blocks * p.block_size : p.capacity;
-        const int kend = (int)(cache_tokens < (int64_t)k0 + klen ? cache_tokens : (int64_t)k0 + klen);
+        const int kend = early_end(most_keys(p), k0, klen);
         auto load_tile_early = [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
             const uint16_t* gbase = decltype(is_v)::value ? vbase : kbase;
 #pragma unroll

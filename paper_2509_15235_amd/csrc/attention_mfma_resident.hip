@@ -74,8 +74,8 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     const int32_t S = p.prefix_len[b]; // requested first, needed last: everything below is issued before it arrives
 
     // ---- request the split's keys. Load u of wave w fetches rows u * RPB + w * RPI .. + RPI - 1 of the split, 1 KB of
-    // consecutive memory. The loads do not wait for the prefix length: they are bounded by the cache (not by the
-    // sequence). A block-table entry outside the pool reads block 0 (reported through status).
+    // consecutive memory. The loads do not wait for the prefix length: they are bounded by the longest sequence that the host
+    // allows (paged: by the block table). A block-table entry outside the pool reads block 0 (reported through status).
     const uint16_t* kbase = (const uint16_t*)p.k;
     const uint16_t* vbase = (const uint16_t*)p.v;
     const int lrow = lane / LPR, lchunk = lane % LPR;
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     } else {
         lane_off = (uint32_t)(wave * RPI + lrow) * stride + lchunk * 16;
     }
-    // contiguous caches: rows past the cache's end read as zeros
+    // contiguous caches: rows past the longest allowed sequence read as zeros
     const __amdgpu_buffer_rsrc_t krs = slice_of(kbase + head_base, k0, p, stride), vrs = slice_of(vbase + head_base, k0, p, stride);
     if constexpr (!PAGED) {
 #pragma unroll

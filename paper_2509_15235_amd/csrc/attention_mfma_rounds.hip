@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     const int32_t S = p.prefix_len[b]; // requested first, needed last: everything below is issued before it arrives
 
     // ---- request the first round's keys and values. Load u of wave w fetches rows u * RPB + w * RPI .. + RPI - 1 of the round, 1 KB
-    // of consecutive memory. The loads do not wait for the prefix length: they are bounded by the cache (not by the
-    // sequence), and values past the sequence's last key are zeroed on their way into LDS (whatever the
+    // of consecutive memory. The loads do not wait for the prefix length: they are bounded by the longest sequence that the
+    // host allows, and values past the sequence's last key are zeroed on their way into LDS (whatever the
     // cache holds there - NaN included - must not meet a zero probability). A block-table entry outside the pool reads
     // block 0 (reported through status).
     const uint16_t* kbase = (const uint16_t*)p.k;
@@ -108,8 +108,7 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     }
     const uint32_t lane_off = (uint32_t)srow * stride + lchunk * 16; // contiguous caches
     const __amdgpu_buffer_rsrc_t krs0 = slice_of(kbase + head_base, k0, p, stride), vrs0 = slice_of(vbase + head_base, k0, p, stride);
-    const int64_t cache_tokens = PAGED ? (int64_t)p.max_blocks * p.block_size : p.capacity;
-    const int kend = (int)(cache_tokens < (int64_t)k0 + p.keys_per_split ? cache_tokens : (int64_t)k0 + p.keys_per_split);
+    const int kend = early_end(most_keys(p), k0, p.keys_per_split);
     constexpr int LPS = KQ * kTileKeys / RPB; // loads per stage
     auto issue_stage = [&](auto is_v, int j) __attribute__((always_inline)) {
         constexpr bool ISV = decltype(is_v)::value;

@@ -90,13 +90,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
 
     const int32_t S = p.prefix_len[b]; // requested first, needed last: the first tiles are requested before it arrives
 
-    // ---- this wave's tiles: keys first, first + ROUND, ... The first one is clamped to the cache instead of the
-    // sequence; rows that turn out to lie past the sequence's last key become zeros on their way into LDS (whatever the
+    // ---- this wave's tiles: keys first, first + ROUND, ... The first one is clamped to the longest allowed sequence instead
+    // of this one; rows that turn out to lie past the sequence's last key become zeros on their way into LDS (whatever the
     // cache holds there, NaN included, must not meet a zero probability). Later ones repeat the last key.
     const int k0 = split * p.keys_per_split; // the host keeps k0 below max_prefix_len + tree_keys, hence inside the cache
     const int first = k0 + wave * kTileKeys;
-    const int64_t cache_tokens = p.paged ? (int64_t)p.max_blocks * p.block_size : p.capacity;
-    const int kend = (int)(cache_tokens < (int64_t)k0 + p.keys_per_split ? cache_tokens : (int64_t)k0 + p.keys_per_split);
+    const int kend = early_end(most_keys(p), k0, p.keys_per_split);
     const uint16_t* kbase = (const uint16_t*)p.k;
     const uint16_t* vbase = (const uint16_t*)p.v;
     const int64_t head_base = (p.paged ? 0 : (int64_t)b * p.stride_seq) + (int64_t)kvh * p.stride_head;

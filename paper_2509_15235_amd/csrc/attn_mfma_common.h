@@ -171,12 +171,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_of(const void* base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00027000);
 }
 
-// The rows of a contiguous cache's slice (one sequence's KV head) from k0 on, at most a split and no further than the cache;
-// what lies past them reads as zeros. stride: bytes from row to row.
+// Keys of the longest sequence that the host allows: inside the cache, and token offsets up to there fit 32 bits (those of a
+// cache's further slots need not).
+__device__ __forceinline__ int64_t most_keys(const AttnParams& p) { return (int64_t)p.max_prefix_len + p.tree_keys; }
+// The rows of a contiguous cache's slice (one sequence's KV head) from k0 on, at most a split and no further than the longest
+// sequence; what lies past them reads as zeros. (Where offsets of rows behind those wrap, they read live rows: their keys are
+// masked and their values replaced by zeros all the same.) stride: bytes from row to row.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_of(const uint16_t* slice, int k0, const AttnParams& p, uint32_t stride) {
-    const int64_t left = p.capacity - k0;
-    const uint32_t rows = left < p.keys_per_split ? (uint32_t)left : (uint32_t)p.keys_per_split;
-    return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(slice) + (int64_t)k0 * stride, 0, (int)((rows - 1) * stride + (uint32_t)p.d * 2), 0x00027000);
+    const uint32_t bytes = slice_bytes(most_keys(p), k0, p.keys_per_split, stride, (uint32_t)p.d * 2);
+    return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(slice) + (int64_t)k0 * stride, 0, (int)bytes, 0x00027000);
 }
 
 // One 32-channel accumulator block of a row block, divided by the rows' sums: two 16-byte pieces per

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "index_math.h"
 #include "vispec_verify.h"
 
 namespace vs {

@@ -1,0 +1,53 @@
+"""The kernels' index arithmetic (csrc/index_math.h), compiled for the host and compared with whole numbers of any size."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SHIM = r"""
+#include "index_math.h"
+using namespace vs;
+extern "C" {
+uint32_t t_slice_bytes(int64_t most, int32_t k0, int32_t keys, uint32_t stride, uint32_t row) { return slice_bytes(most, k0, keys, stride, row); }
+int32_t t_early_end(int64_t most, int32_t k0, int32_t keys) { return early_end(most, k0, keys); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    at = tmp_path_factory.mktemp("index_math")
+    src, so = at / "shim.cpp", at / "shim.so"
+    src.write_text(SHIM)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared",
+                           "-I" + os.path.join(ROOT, "paper_2509_15235_amd", "csrc"), str(src), "-o", str(so)])
+    L = ctypes.CDLL(str(so))
+    i32, u32, i64 = ctypes.c_int32, ctypes.c_uint32, ctypes.c_int64
+    L.t_slice_bytes.argtypes, L.t_slice_bytes.restype = [i64, i32, i32, u32, u32], u32
+    L.t_early_end.argtypes, L.t_early_end.restype = [i64, i32, i32], i32
+    return L
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("most", [1, 2, 9, 21, 31, 63, 64, 65, 128, 200, 1756, 16777215])
+def test_slice_holds_every_row_that_may_live(lib, most, d):
+    """A split's slice ends with its last row that a sequence can have, for every token stride that the host accepts
+    (most * stride below 2^30 elements, a multiple of eight) and splits longer than the sequence."""
+    top = ((1 << 30) - 1) // most // 8 * 8
+    r = np.random.default_rng(most + d)
+    strides = {d, top, 34087048, *(int(x) // 8 * 8 for x in r.integers(d, max(top, d + 1), size=200))}
+    for stride in (s for s in strides if d <= s <= top):
+        for keys in (64, 128, 192, 256):
+            for k0 in {0, (most - 1) // keys * keys}:
+                rows = min(most - k0, keys)
+                assert lib.t_slice_bytes(most, k0, keys, 2 * stride, 2 * d) == (rows - 1) * 2 * stride + 2 * d < 1 << 31
+
+
+def test_early_end(lib):
+    for most, k0, keys in [(9, 0, 64), (64, 0, 64), (65, 64, 64), (1756, 1664, 128), ((1 << 31) + 62, 0, 192), ((1 << 31) + 62, (1 << 31) - 257, 192),
+                           (2147483647, 2147483584, 192)]:
+        assert lib.t_early_end(most, k0, keys) == min(most, k0 + keys)
