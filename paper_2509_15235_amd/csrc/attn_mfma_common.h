@@ -81,11 +81,11 @@ __device__ __forceinline__ int64_t row_start(const AttnParams& p, int b, int kvh
 }
 template <int D>
 __device__ __forceinline__ int64_t row_in(const AttnParams& p, int r, int node, int chunk) {
-    return (int64_t)((uint64_t)(uint32_t)node * (uint64_t)p.node_stride + (uint64_t)(uint32_t)(r * D + chunk * 8));
+    return row_elements(r, node, p.node_stride, D) + chunk * 8;
 }
 // the same as one offset
 __device__ __forceinline__ int64_t row_offset(const AttnParams& p, int b, int kvh, int r, int node) {
-    return (((int64_t)b * p.T) * p.Hq + (int64_t)kvh * p.group) * p.d + ((int64_t)node * p.node_stride + (int64_t)r * p.d);
+    return (((int64_t)b * p.T) * p.Hq + (int64_t)kvh * p.group) * p.d + row_elements(r, node, p.node_stride, p.d);
 }
 
 // The sequence of rank `rank` when the longest come first (at most 64 sequences, a lane each; out-of-range lengths sort

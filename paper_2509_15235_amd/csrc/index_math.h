@@ -21,4 +21,10 @@ constexpr int32_t early_end(int64_t most_keys, int32_t k0, int32_t keys) {
     return (int32_t)(most_keys < end ? most_keys : end);
 }
 
+// Elements from a (sequence, KV head)'s first query row to row r: a node's rows are adjacent, node_stride lies between two nodes'
+// beyond that. 64 bits: 64 nodes of many rows each pass 2^32 elements.
+constexpr int64_t row_elements(int32_t r, int32_t node, int64_t node_stride, int32_t d) {
+    return (int64_t)((uint64_t)(uint32_t)node * (uint64_t)node_stride + (uint64_t)(uint32_t)r * (uint32_t)d);
+}
+
 } // namespace vs

@@ -13,6 +13,7 @@ SHIM = r"""
 using namespace vs;
 extern "C" {
 uint32_t t_slice_bytes(int64_t most, int32_t k0, int32_t keys, uint32_t stride, uint32_t row) { return slice_bytes(most, k0, keys, stride, row); }
+int64_t t_row_elements(int32_t r, int32_t node, int64_t node_stride, int32_t d) { return row_elements(r, node, node_stride, d); }
 int32_t t_early_end(int64_t most, int32_t k0, int32_t keys) { return early_end(most, k0, keys); }
 }
 """
@@ -29,6 +30,7 @@ def lib(tmp_path_factory):
     i32, u32, i64 = ctypes.c_int32, ctypes.c_uint32, ctypes.c_int64
     L.t_slice_bytes.argtypes, L.t_slice_bytes.restype = [i64, i32, i32, u32, u32], u32
     L.t_early_end.argtypes, L.t_early_end.restype = [i64, i32, i32], i32
+    L.t_row_elements.argtypes, L.t_row_elements.restype = [i32, i32, i64, i32], i64
     return L
 
 
@@ -51,3 +53,12 @@ def test_early_end(lib):
     for most, k0, keys in [(9, 0, 64), (64, 0, 64), (65, 64, 64), (1756, 1664, 128), ((1 << 31) + 62, 0, 192), ((1 << 31) + 62, (1 << 31) - 257, 192),
                            (2147483647, 2147483584, 192)]:
         assert lib.t_early_end(most, k0, keys) == min(most, k0 + keys)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group,Hkv,T", [(1, 1, 1), (7, 4, 60), (1, 32, 64), (8, 1, 64), (16400, 1, 2), (1 << 19, 1, 64), ((1 << 19) + 3, 2, 63), (1 << 25, 1, 32)])
+def test_row_elements(lib, group, Hkv, T, d):
+    """Row r of a KV head, head r % group of node r / group, in a dense [T, Hkv * group, d] tensor, also past 2^32 elements."""
+    for node in {0, 1, T // 2, T - 1}:
+        for head in {0, group // 2, group - 1}:
+            assert lib.t_row_elements(node * group + head, node, (Hkv - 1) * group * d, d) == (node * Hkv * group + head) * d
