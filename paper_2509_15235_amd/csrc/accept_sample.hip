@@ -20,7 +20,11 @@ namespace {
 constexpr int kScanWaves = kScanThreads / kWave;
 constexpr int kRowThreads = kScanThreads / VS_MAX_TREE; // threads of the walk that share a row's chunks
 static_assert(kRowThreads == 8, "three steps of a butterfly");
-constexpr int kKeepStats = 1536;          // pairs of a sequence that the walk keeps in LDS (12 KB: five workgroups on a CU still)
+// Pairs of a sequence that the walk keeps in LDS (17 KB): 64 rows of up to 262144 logits, and everything of up to 4096 pairs
+// of half as many logits (T * ceil(V / 4096) <= 4096 means T * ceil(V / 8192) <= 2048 + T / 2).
+// Beyond, the walk reads them again from memory, which costs little where nothing has to be removed from a chunk (2 x 60 x 262144, us,
+// 1536 / 2080 kept: 29.1 / 29.1; 1 x 64 x 256000 20.35 / 20.28; smaller calls the same).
+constexpr int kKeepStats = 2048 + VS_MAX_TREE / 2;
 constexpr int kPerThread = 16;            // chunk elements per thread of the walk
 static_assert(kScanThreads * kPerThread == kScanChunk && kScanChunk == 1 << 13, "the walk takes one chunk at a time");
 

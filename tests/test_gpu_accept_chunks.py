@@ -90,3 +90,10 @@ def test_wide_trees(gu, oracle_mod, V, heavy):
     ua[:, 3] = 0.9999
     ua[: B // 2, 1:41] = np.maximum(ua[: B // 2, 1:41], np.float32(0.98))  # most are rejected
     base._check(gu, oracle_mod, logits, tokens, parent, 1.0, ua, ub, min_exact_frac=0.6)
+
+
+@pytest.mark.parametrize("T,V", [(64, 262144), (16, 130 * 8192), (16, 130 * 8192 + 1)])
+def test_sampling_at_the_end_of_the_walks_own_memory(gu, oracle_mod, T, V):
+    """The walk keeps 2080 chunk results of a sequence in LDS and reads more than that from memory: 2048, 2080 and 2096 of them."""
+    parent, tokens, logits, ua, ub = base._case(700 + T, 1, T, V)
+    base._check(gu, oracle_mod, logits, tokens, parent, 1.0, ua, ub, min_exact_frac=0.0)

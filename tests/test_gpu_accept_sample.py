@@ -7,8 +7,8 @@ the fp32 path's error of its threshold. Every GPU outcome must pass the oracle's
 comparison allowed to be off by EPS), and where the oracle's `margin` (the closest call of its
 own walk) exceeds EPS the outcome must equal the oracle's exactly. EPS bounds the fp32 error of
 a probability or of a normalised cumulative sum: hardware exp2 of an argument known to ~2e-6
-relative, sums of <= 2^23 terms in chunks of 4096 merged pairwise, ~5e-6 in all; EPS is twice
-that. Every test prints the largest deviation any comparison actually needed (`worst`).
+relative, sums of <= 2^23 terms in chunks of 8192 (sixteen a thread, then in pairs) merged pairwise, ~5e-6 in all; EPS is
+twice that. Every test prints the largest deviation any comparison actually needed (`worst`).
 With a large vocabulary single tokens weigh less than EPS (1 / 152064 = 6.6e-6), so the bonus
 token may legitimately be a neighbour of the oracle's: there the exact-match floor is the number
 of sequences whose margin exceeds EPS - which are checked one by one - and nothing more can be
