@@ -213,11 +213,13 @@ hipError_t launch_accept(AcceptParams p, void* workspace, hipStream_t s) {
         hipLaunchKernelGGL(accept_small_kernel, dim3(p.B), dim3(kSmallThreads), 0, s, p);
         return hipGetLastError();
     }
-    p.chunks = (int32_t)(((int64_t)p.V + kScanChunk - 1) / kScanChunk);
+    const bool short_chunks = scan_short_chunks(p.V, (int64_t)p.B * p.T);
+    const int chunk = short_chunks ? kScanChunk / 2 : kScanChunk;
+    p.chunks = (int32_t)(((int64_t)p.V + chunk - 1) / chunk);
     p.by_chunks = fast_div_by(p.chunks);
     p.pairs = (uint64_t*)workspace;
     const dim3 grid((unsigned)((int64_t)p.chunks * p.B * p.T));
-    if (p.V <= kScanChunk / 2) hipLaunchKernelGGL(argmax_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);
+    if (short_chunks) hipLaunchKernelGGL(argmax_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);
     else hipLaunchKernelGGL(argmax_partial_kernel<kScanThreads>, grid, dim3(kScanThreads), 0, s, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -26,7 +26,7 @@ static_assert(kRowThreads == 8, "three steps of a butterfly");
 // 1536 / 2080 kept: 29.1 / 29.1; 1 x 64 x 256000 20.35 / 20.28; smaller calls the same).
 constexpr int kKeepStats = 2048 + VS_MAX_TREE / 2;
 constexpr int kPerThread = 16;            // chunk elements per thread of the walk
-static_assert(kScanThreads * kPerThread == kScanChunk && kScanChunk == 1 << 13, "the walk takes one chunk at a time");
+static_assert(kScanThreads * kPerThread == kScanChunk && kScanChunk == 1 << 13, "the walk takes one chunk at a time, half of its threads a short one");
 
 // grid = B*T*chunks, block = THREADS: (max of the raw logits, sum of 2^((l - max) * k)) of a chunk, k = log2(e) / temperature.
 template <int THREADS>
@@ -69,7 +69,8 @@ __global__ __launch_bounds__(THREADS, 8) void softmax_stats_partial_kernel(const
 // (row maxima and masses, the uniforms, every candidate's weight in its parent's row), so a step of the walk costs no
 // memory round trip: removing a rejected token just lowers the row's mass. Only when that subtraction would cancel (the
 // rejected token held > 95 % of the mass), and once at the end for the bonus draw, the row's per-chunk masses are
-// needed - from the copy of all rows' chunk statistics in LDS when those fit, else from memory.
+// needed - from the copy of all rows' chunk statistics in LDS when those fit, else from memory. A chunk is 2^SHIFT logits.
+template <int SHIFT>
 __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const SampleParams p) {
     __shared__ float sred[kScanWaves];
     __shared__ float sM[VS_MAX_TREE];      // row maxima
@@ -171,11 +172,13 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
     const float Z_own = sZ[min(lane, T - 1)];
     auto lane_of = [](float x, int c) __attribute__((always_inline)) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, x), c)); };
 
+    // This thread's first element of chunk c; behind the row where the chunk has none for it
+    auto place = [&](int c) __attribute__((always_inline)) { return kScanChunk == 1 << SHIFT || tid * kPerThread < 1 << SHIFT ? c * (1 << SHIFT) + tid * kPerThread : p.V; };
     // This thread's 16 consecutive weights of chunk c of row `node`; the tokens of the nodes in `removed` weigh nothing.
     auto load_weights = [&](int node, int c, uint64_t removed, float (&w)[kPerThread]) {
         const float* lg = p.logits + ((int64_t)b * T + node) * p.ld;
         const float M = sM[node];
-        const int j0 = c * kScanChunk + tid * kPerThread;
+        const int j0 = place(c);
         if (p.V >= 4) {
             // four at a time, the row's last four at its end: there the wanted ones are moved to the front
             f32x4 a[kPerThread / 4];
@@ -226,7 +229,7 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
     };
     // Takes node c's token out of its chunk's mass in sch; `removed`: the nodes whose tokens are gone by then, c among them.
     auto remove_from_chunks = [&](int node, int c, uint64_t removed) {
-        const int xc = __builtin_amdgcn_readlane(token, c) / kScanChunk;
+        const int xc = __builtin_amdgcn_readlane(token, c) / (1 << SHIFT);
         const float old = sch[xc];
         float fresh = old - lane_of(ex_own, c);
         if (!(fresh >= 0.25f * old)) {
@@ -340,7 +343,7 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
         bool cancelled = false;
         for (uint64_t r = removed; r != 0; r &= r - 1) {
             const int c = __builtin_ctzll(r);
-            if (lane == __builtin_amdgcn_readlane(token, c) / kScanChunk) {
+            if (lane == __builtin_amdgcn_readlane(token, c) / (1 << SHIFT)) {
                 const float fresh = cs - lane_of(ex_own, c);
                 cancelled = cancelled || !(fresh >= 0.25f * cs);
                 cs = fresh;
@@ -368,7 +371,7 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
         load_weights(cur, kb, removed, w);
         float s = 0.f;
         int last = -1;
-        const int j0 = kb * kScanChunk + tid * kPerThread;
+        const int j0 = place(kb);
 #pragma unroll
         for (int e = 0; e < kPerThread; ++e) {
             s += w[e];
@@ -422,15 +425,18 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
 
 // workspace: 8 bytes per (row, chunk); sized by chunks half as long, it holds them with room to spare
 hipError_t launch_accept_sample(SampleParams p, void* workspace, hipStream_t s) {
-    p.chunks = (p.V + kScanChunk - 1) / kScanChunk;
+    const bool short_chunks = scan_short_chunks(p.V, (int64_t)p.B * p.T);
+    const int chunk = short_chunks ? kScanChunk / 2 : kScanChunk;
+    p.chunks = (int32_t)(((int64_t)p.V + chunk - 1) / chunk);
     p.by_chunks = fast_div_by(p.chunks);
     p.pairs = (uint64_t*)workspace;
     const dim3 grid((unsigned)((int64_t)p.chunks * p.B * p.T));
-    if (p.V <= kScanChunk / 2) hipLaunchKernelGGL(softmax_stats_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);
+    if (short_chunks) hipLaunchKernelGGL(softmax_stats_partial_kernel<kScanThreads / 2>, grid, dim3(kScanThreads / 2), 0, s, p);
     else hipLaunchKernelGGL(softmax_stats_partial_kernel<kScanThreads>, grid, dim3(kScanThreads), 0, s, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(accept_sample_walk_kernel, dim3(p.B), dim3(kScanThreads), 0, s, p);
+    if (short_chunks && p.chunks > 1) hipLaunchKernelGGL(accept_sample_walk_kernel<12>, dim3(p.B), dim3(kScanThreads), 0, s, p);
+    else hipLaunchKernelGGL(accept_sample_walk_kernel<13>, dim3(p.B), dim3(kScanThreads), 0, s, p);
     return hipGetLastError();
 }
 

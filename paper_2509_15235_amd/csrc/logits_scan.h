@@ -10,6 +10,17 @@
 
 namespace vs {
 
+// Chunks of 4096 on 256 threads? For rows of at most one of them (half the waves), and where rows end in a short chunk (at most
+// half of one), with two or eight chunks to a row, in launches of more than 1280 workgroups: with eight, ids dealt round-robin give
+// all short ones to one XCD, with two the short ones are half of the launch. us, chunks of 8192 / of 4096, greedy and stochastic:
+//   24 x 63 x 8960 16.3 / 13.8, 21.8 / 20.8; 30 x 60 x 12192 20.0 / 18.7, 26.8 / 26.0; 18 x 38 x 57509 30.9 / 28.7, 38.5 / 37.7
+// Stochastic calls lose with the shorter ones elsewhere: 200 rows of 8292 .. 12192 0 - 6 %, three and more chunks 0 - 8 %.
+inline bool scan_short_chunks(int32_t V, int64_t rows) {
+    if (V <= kScanChunk / 2) return true;
+    const int32_t chunks = (int32_t)(((int64_t)V + kScanChunk - 1) / kScanChunk), last = V - (chunks - 1) * kScanChunk;
+    return (chunks == 2 || chunks == 8) && last <= kScanChunk / 2 && rows * chunks > 5 * kNumCUs;
+}
+
 // Workgroup id = row * chunks + chunk (the host keeps the product below 2^31); row counts over all sequences.
 struct ScanItem {
     int row, chunk;
@@ -27,7 +38,7 @@ struct ScanChunk {
     float tail;
     int32_t begin, nvec, tail_at; // tail_at: >= end when this thread has none
 };
-template <int THREADS, int CHUNK = kScanChunk>
+template <int THREADS, int CHUNK = THREADS * kScanVec * 4>
 __device__ __forceinline__ ScanChunk scan_load(const float* lg, int chunk, int V, int tid = threadIdx.x) {
     ScanChunk c;
     c.begin = chunk * CHUNK;

@@ -97,3 +97,21 @@ def test_sampling_at_the_end_of_the_walks_own_memory(gu, oracle_mod, T, V):
     """The walk keeps 2080 chunk results of a sequence in LDS and reads more than that from memory: 2048, 2080 and 2096 of them."""
     parent, tokens, logits, ua, ub = base._case(700 + T, 1, T, V)
     base._check(gu, oracle_mod, logits, tokens, parent, 1.0, ua, ub, min_exact_frac=0.0)
+
+
+@pytest.mark.parametrize("B,T,V", [(11, 60, 8193), (10, 64, 8193), (11, 60, 12288), (11, 60, 12289), (11, 59, 8995), (3, 54, 57345), (3, 53, 57345),
+                                   (3, 54, 61440), (3, 54, 61441)])
+def test_large_launches_of_rows_that_end_in_a_short_chunk(gu, oracle_mod, B, T, V):
+    """Two or eight chunks of 8192 a row, the last at most half full, and more than 1280 of them in all: chunks of 4096 instead."""
+    parent, tokens, logits, ua, ub = base._case(800 + T, B, T, V)
+    r = np.random.default_rng(V)
+    ub[0], ub[1] = 0.0, np.float32(1.0 - 2.0 ** -24)
+    base._check(gu, oracle_mod, logits, tokens, parent, 1.0, ua, ub, min_exact_frac=0.6, ld=V + 3, offset_elems=1)
+    at = [i for k in range(0, V + 4096, 4096) for i in (k - 1, k, k + 1) if 0 <= i < V] + [V - 1]
+    for b in range(B):
+        for t in range(T):                                        # equal maxima around the ends: the first counts
+            logits[b, t, r.choice(at, size=2, replace=False)] = 19.0
+    tokens[:, 1:] = np.take_along_axis(logits.argmax(-1), np.maximum(parent[:, 1:], 0), axis=1)
+    got = gu.run_accept(logits, tokens, parent, ld=V + 3, offset_elems=1)
+    for g, w in zip(got, oracle_mod.tree_accept(logits, tokens, parent)):
+        np.testing.assert_array_equal(g, w)
