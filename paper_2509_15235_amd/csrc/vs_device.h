@@ -147,7 +147,6 @@ __device__ __forceinline__ void arrival_open(uint64_t* w, uint64_t seen) { // on
     if ((seen >> 32) != (kArrivalZero >> 32))
         __hip_atomic_compare_exchange_strong(w, &seen, kArrivalZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void arrival_open(uint64_t* w) { arrival_open(w, load_device(w)); }
 __device__ __forceinline__ bool arrival_last(uint64_t* w, uint32_t n) { // that thread, when its workgroup's results are in memory
     const bool last = (uint32_t)__hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
     if (last) store_device(w, kArrivalZero);
