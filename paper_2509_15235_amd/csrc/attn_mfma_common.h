@@ -64,15 +64,7 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
     return {(int)b, (int)kvh, (int)rg, (int)split, v >= (uint32_t)p.total_wgs};
 }
 
-// node of query row r (r / group). (r + 1/2) / group is 1 / (2 group) or more away from a whole number and the quotient is
-// below 64, so up to 16384 rows a node the fp32 error, 64 * 2^-23, is too small to matter; beyond, it is off by less than one.
-__device__ __forceinline__ int row_node(const AttnParams& p, int r) {
-    if (p.group <= 16384) return (int)fmaf((float)r, p.inv_group, 0.5f * p.inv_group);
-    int n = (int)((float)r * p.inv_group);
-    const int rem = r - n * p.group;
-    n += (rem >= p.group) - (rem < 0);
-    return n;
-}
+__device__ __forceinline__ int row_node(const AttnParams& p, int r) { return node_of_row(r, p.group, p.inv_group); }
 // Element offset of (sequence b, KV head kvh)'s first query row in q and out, uniform, and from there to 16-byte chunk `chunk`
 // of row r. A node's rows are adjacent, `node_stride` lies between two nodes' beyond that.
 template <int D>

@@ -6,6 +6,33 @@
 
 namespace vs {
 
+// Division by a number that the host knows: one multiplication and one correction instead of the 45 instructions of a
+// 32-bit division (m = floor((2^32 - 1) / d): the product's upper half is the quotient or one less, for any n).
+struct FastDiv {
+    uint32_t d, m;
+};
+constexpr FastDiv fast_div_by(int32_t d) { return {(uint32_t)d, 0xffffffffu / (uint32_t)d}; }
+constexpr uint32_t fast_div(uint32_t n, FastDiv by, uint32_t& rem) {
+    uint32_t q = (uint32_t)(((uint64_t)n * by.m) >> 32);
+    rem = n - q * by.d;
+    if (rem >= by.d) {
+        rem -= by.d;
+        ++q;
+    }
+    return q;
+}
+
+// Node of query row r (r / group), inv_group = 1 / group. (r + 1/2) / group is 1 / (2 group) or more away from a whole number and the
+// quotient is below 64, so up to 16384 rows a node the fp32 error, 64 * 2^-23, is too small to matter; beyond, it is off by less
+// than one.
+constexpr int32_t node_of_row(int32_t r, int32_t group, float inv_group) {
+    if (group <= 16384) return (int32_t)__builtin_fmaf((float)r, inv_group, 0.5f * inv_group);
+    int32_t n = (int32_t)((float)r * inv_group);
+    const int32_t rem = r - n * group;
+    n += (rem >= group) - (rem < 0);
+    return n;
+}
+
 // Bytes of one sequence's K (or V) rows of one KV head from key k0 on that a split may ask for before it knows its length: up to
 // the longest sequence that the host allows (most_keys > k0), not up to the cache's capacity. The host keeps most_keys * stride
 // below 2^31 bytes; the slots of a cache beyond that may lie any distance away. Rows of row_bytes, `stride` bytes apart.

@@ -31,16 +31,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return (uint32_t)float_to_bf16_bits(lo) | ((uint32_t)float_to_bf16_bits(hi) << 16);
 }
 
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv by, uint32_t& rem) {
-    uint32_t q = __umulhi(n, by.m);
-    rem = n - q * by.d;
-    if (rem >= by.d) {
-        rem -= by.d;
-        ++q;
-    }
-    return q;
-}
-
 // ---- Wave-wide reductions on the vector ALU (DPP and lane swaps; a shuffle goes through LDS and takes ten times
 // as long, six in a row about 0.3 us). Lanes pair up as in a xor butterfly from 32 down to 1.
 template <int CTRL>

@@ -37,13 +37,6 @@ constexpr int kRoundKeys = 128;       // keys of a round (attention_mfma_rounds.
 constexpr int kResidentMaxKeys = 192; // keys of one split that the resident attention kernel keeps in LDS
 constexpr int resident_max_keys(int row_blocks) { return row_blocks <= 2 ? 256 : kResidentMaxKeys; } // ... with so many row blocks to a workgroup
 
-// Division by a number that the host knows: one multiplication and one correction instead of the 45 instructions of a
-// 32-bit division (m = floor((2^32 - 1) / d): the product's upper half is the quotient or one less, for any n).
-struct FastDiv {
-    uint32_t d, m;
-};
-inline FastDiv fast_div_by(int32_t d) { return {(uint32_t)d, 0xffffffffu / (uint32_t)d}; }
-
 // Everything the attention kernels need, passed by value.
 struct AttnParams {
     const void* q;

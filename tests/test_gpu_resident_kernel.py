@@ -1,5 +1,5 @@
 """GPU parity of the attention kernel that keeps a split's keys in LDS: one, two and four row blocks, one to eight tiles of
-32 keys, ends around tiles, cached garbage behind the last key, splits of 64, 128 and 192 keys, and the row arithmetic."""
+32 keys, ends around tiles, cached garbage behind the last key, splits of 64, 128 and 192 keys."""
 import numpy as np
 import pytest
 
@@ -58,26 +58,3 @@ def test_many_rows_to_a_node(oracle_mod):
     inp = gen.attention_inputs(cfg, 650, prefix_len=np.array([70], dtype=np.int32))
     got = gu.DeviceAttn(inp).run()
     gu.check_close(got, oracle_mod.tree_attention(inp, threads=8), *TIGHT_SHORT)
-
-
-def test_row_arithmetic():
-    """(r + 1/2) * (1 / group), rounded to fp32, has the quotient r / group as its whole part: at the first and last row of
-    every node, for every group up to 16384 (the kernels' bound for this form)."""
-    g = np.arange(1, 16385)
-    inv = (np.float32(1) / g.astype(np.float32)).astype(np.float32)
-    half = (np.float32(0.5) * inv).astype(np.float32)
-    for n in range(64):
-        for r in (n * g, n * g + g - 1):
-            q = (r.astype(np.float64) * inv + half).astype(np.float32)  # one rounding, as in fma (the product is exact in fp64)
-            assert (q.astype(np.int64) == n).all()
-
-
-def test_division_by_multiplication():
-    """floor(n * floor((2^32 - 1) / d) / 2^32) is n / d or one less."""
-    r = np.random.default_rng(3)
-    d = np.concatenate([np.arange(1, 400), r.integers(1, 2 ** 31, size=4000)]).astype(np.uint64)
-    m = (2 ** 32 - 1) // d
-    for n in [np.uint64(x) for x in (0, 1, 255, 256, 2 ** 31 - 1)] + list(r.integers(0, 2 ** 31, size=200).astype(np.uint64)):
-        q = (n * m) >> np.uint64(32)
-        q = q + (n - q * d >= d)
-        assert (q == n // d).all()
