@@ -8,6 +8,7 @@ import paper_2509_15235_amd as vs
 
 pytestmark = pytest.mark.gpu
 
+TIGHT_LONG = (1.5e-3, 6e-3)
 TIGHT_SHORT = (1.2e-2, 6e-3)
 
 
@@ -15,8 +16,8 @@ def _token_major(da, cfg, need, stride, slots):
     """Moves da's contiguous caches into one buffer of `slots` tokens, `stride` elements apart, that holds every sequence's and KV
     head's K and V side by side; NaN wherever no sequence has a key."""
     B, Hkv, d = cfg.B, cfg.Hkv, cfg.d
-    assert stride >= 2 * B * Hkv * d
-    buf = torch.full((slots * stride,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    assert stride >= 2 * B * Hkv * d and slots >= need
+    buf = torch.full((slots * stride,), float("nan"), device="cuda", dtype=da.k.dtype)
     at = buf.as_strided((need, B, 2, Hkv, d), (stride, 2 * Hkv * d, Hkv * d, d, 1))
     for b in range(B):
         n = int(da.inp.prefix_len[b]) + cfg.T
@@ -24,6 +25,55 @@ def _token_major(da, cfg, need, stride, slots):
         at[:n, b, 1] = da.v[b, :, :n].transpose(0, 1)
     da.k, da.v = buf, buf[Hkv * d:]
     da.desc.capacity, da.desc.stride_seq, da.desc.stride_head, da.desc.stride_tok = slots, 2 * Hkv * d, d, stride
+
+
+def _token_major_pool(da, cfg, gap):
+    """The same for a paged cache: a block is its tokens one after the other, each with K and V of every KV head and a gap of NaN."""
+    Hkv, d, bs, blocks = cfg.Hkv, cfg.d, cfg.block_size, da.desc.num_blocks
+    stride = 2 * Hkv * d + gap
+    buf = torch.full((blocks * bs * stride,), float("nan"), device="cuda", dtype=da.k.dtype)
+    at = buf.as_strided((blocks, bs, 2, Hkv, d), (bs * stride, stride, Hkv * d, d, 1))
+    at[:, :, 0] = da.k.transpose(1, 2)
+    at[:, :, 1] = da.v.transpose(1, 2)
+    da.k, da.v = buf, buf[Hkv * d:]
+    da.desc.stride_block, da.desc.stride_head, da.desc.stride_tok = bs * stride, d, stride
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("dtype,T,Hq,Hkv,d,lens,knobs", [
+    ("bf16", 3, 28, 4, 128, [170, 61, 0], {}),                     # resident: one row block,
+    ("bf16", 9, 28, 4, 128, [240, 33], {}),                        # two,
+    ("bf16", 60, 28, 4, 128, [700], {}),                           # four in splits
+    ("bf16", 4, 28, 4, 128, [490, 300, 256], {}),                  # own tiles
+    ("bf16", 8, 32, 8, 64, [450, 7], {}),
+    ("bf16", 16, 28, 4, 128, [1300, 900, 640, 50], {}),            # rounds
+    ("bf16", 31, 32, 8, 64, [1500, 257], {}),
+    ("bf16", 60, 28, 4, 128, [1100, 900, 300, 64], {}),            # pipelined: eight waves
+    ("bf16", 60, 32, 32, 128, [500], {}),                          # ... four
+    ("bf16", 60, 32, 8, 64, [700, 40], {"schedule": vs.VS_SCHED_PIPELINED, "num_splits": 3}),
+    ("bf16", 60, 28, 4, 128, [1100, 90, 2000], {"schedule": vs.VS_SCHED_BALANCED}),
+    ("bf16", 60, 28, 4, 128, [600, 333], {"schedule": vs.VS_SCHED_LOOP}),
+    ("bf16", 60, 28, 4, 128, [600, 333], {"rows_per_wave": 2, "waves_per_group": 8}),
+    ("bf16", 5, 8, 2, 64, [77, 130], {"impl": vs.VS_IMPL_GENERIC}),
+    ("f32", 31, 8, 2, 128, [333, 90], {}),
+    ("f32", 8, 4, 1, 64, [64], {}),
+])
+def test_token_major(oracle_mod, dtype, T, Hq, Hkv, d, lens, knobs, paged):
+    import gpu_util as gu
+    B = len(lens)
+    cfg = gen.Config("strided", B, Hq, Hkv, d, T, min(6, T - 1), 4, 100, 0.5, 1, dtype, prefix=None, prefix_range=(1, 2), paged=paged)
+    inp = gen.attention_inputs(cfg, 950 + T + B, prefix_len=np.array(lens, dtype=np.int32))
+    da = gu.DeviceAttn(inp, **knobs)
+    if paged:
+        _token_major_pool(da, cfg, 24)
+    else:
+        _token_major(da, cfg, max(lens) + T, 2 * B * Hkv * d + 24, max(lens) + T + 70)
+    got = da.run()
+    assert (da.status.cpu().numpy() == 0).all()
+    ref = oracle_mod.tree_attention(inp, threads=8)
+    for b in range(B):
+        tol = (2e-5, 2e-5) if dtype == "f32" else TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT
+        gu.check_close(got[b], ref[b], *tol, what=f"sequence {b} of {lens[b]}")
 
 
 @pytest.mark.parametrize("T,Hq,Hkv,d,S,schedule", [
