@@ -104,6 +104,7 @@ int32_t check_desc(const vs_attn_desc* d, int tree = 1) {
     const bool mfma = d->impl == VS_IMPL_MFMA || (d->impl == VS_IMPL_AUTO && d->dtype == VS_BF16);
     if (mfma) {
         // token offsets inside one (sequence, KV head) slice are kept in 32 bits
+        if (d->stride_tok >= ((int64_t)1 << 30)) return VS_ERR_LAYOUT; // (the product below would wrap for some)
         const int64_t span = d->paged ? (int64_t)d->block_size * d->stride_tok : need * d->stride_tok;
         if (span >= ((int64_t)1 << 30)) return VS_ERR_LAYOUT;
         // 16-byte vector loads of 8 bf16

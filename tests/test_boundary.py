@@ -99,6 +99,14 @@ def test_attention_descriptor_validation(kw, code):
         assert vs.vs_attention_workspace_bytes(_desc(**kw)) == 0
 
 
+def test_token_strides_whose_products_wrap_are_refused():
+    """1756 keys at a stride of 2^62 are a multiple of 2^64 elements."""
+    for stride, code in (((1 << 30) // 1756 // 8 * 8, 0), ((1 << 30) // 1756 // 8 * 8 + 8, -6), (1 << 30, -6), (1 << 33, -6), (1 << 62, -6)):
+        assert vs.vs_attention_plan(_desc(stride_tok=stride))[0] == code, stride
+        paged = dict(paged=1, block_size=16, max_blocks=200, num_blocks=300, stride_block=4 * 16 * 128, block_table=4096)
+        assert vs.vs_attention_plan(_desc(stride_tok=stride, **paged))[0] == (-6 if stride >= 1 << 26 else 0), stride
+
+
 def test_plan_and_workspace_sizes():
     # one layer of one short sequence: LDS-resident splits of 128 keys, four row blocks per workgroup
     rc, plan = vs.vs_attention_plan(_desc())
