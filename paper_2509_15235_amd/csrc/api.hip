@@ -65,6 +65,8 @@ int32_t check_desc(const vs_attn_desc* d, int tree = 1) {
         return VS_ERR_SHAPE;
     if (d->d != 64 && d->d != 128) return VS_ERR_SHAPE;
     if ((int64_t)d->B * d->Hkv > kMaxGridY) return VS_ERR_SHAPE; // one grid row per (sequence, KV head) in the combine
+    // query rows are counted in 32 bits, up to a whole row block (q and out of this many would not fit the card)
+    if ((int64_t)d->T * d->Hq > (0x7fffffff - kRowBlock) / d->B) return VS_ERR_SHAPE;
     if (d->max_prefix_len < 0) return VS_ERR_SHAPE;
     if (!(d->softmax_scale > 0.f) || !isfinite(d->softmax_scale)) return VS_ERR_SHAPE;
     if (d->dtype != VS_BF16 && d->dtype != VS_F32) return VS_ERR_DTYPE;

@@ -107,6 +107,17 @@ def test_token_strides_whose_products_wrap_are_refused():
         assert vs.vs_attention_plan(_desc(stride_tok=stride, **paged))[0] == (-6 if stride >= 1 << 26 else 0), stride
 
 
+@pytest.mark.parametrize("kw,code", [
+    ({"T": 64, "Hq": 1 << 26, "Hkv": 1}, -2), ({"T": 64, "Hq": 1 << 26, "Hkv": 1, "schedule": vs.VS_SCHED_PIPELINED}, -2),
+    ({"T": 64, "Hq": 1 << 26, "Hkv": 1, "B": 2, "schedule": vs.VS_SCHED_BALANCED}, -2), ({"T": 64, "Hq": 1 << 25, "Hkv": 1}, -2),
+    ({"T": 64, "Hq": 12 << 26, "Hkv": 12, "B": 12}, -2), ({"T": 64, "Hq": 1 << 26, "Hkv": 1, "dtype": vs.VS_F32}, -2),
+    ({"T": 64, "Hq": (1 << 25) - 1, "Hkv": 1}, 0), ({"T": 64, "Hq": (1 << 24) - 1, "Hkv": 1, "B": 2}, 0), ({"T": 64, "Hq": 1 << 24, "Hkv": 1, "B": 2}, -2),
+])
+def test_more_query_rows_than_32_bits_count_are_refused(kw, code):
+    """(They made the planner divide by zero.)"""
+    assert vs.vs_attention_plan(_desc(**kw))[0] == code
+
+
 def test_plan_and_workspace_sizes():
     # one layer of one short sequence: LDS-resident splits of 128 keys, four row blocks per workgroup
     rc, plan = vs.vs_attention_plan(_desc())
