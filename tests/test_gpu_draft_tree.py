@@ -1,7 +1,7 @@
 """GPU parity: draft-tree construction (vs_draft_expand, vs_draft_tree_build) against the oracle.
 
 Tokens, parents and the final tree are integer work and must match bit for bit. Scores are
-fp32 on the GPU (log-sum-exp merged from 4096-entry chunks) and fp64 in the oracle: they must
+fp32 on the GPU (log-sum-exp merged from 8192-entry chunks) and fp64 in the oracle: they must
 agree to SCORE_TOL, derived from |score| <= ~40 with a relative error of a few fp32 ulps
 (2^-23 * 40 * 4 ~ 2e-5). The next frontier is decided by comparing scores: where the oracle's
 gap at the cut exceeds 2 * SCORE_TOL the kept set must be the oracle's; closer than that, the
