@@ -16,17 +16,16 @@
 // two slots ahead, one sixteenth of the softmax - and K and V^T fragments alternate so
 // that consecutive MFMAs never share an accumulator.
 //
-// K/V tiles travel global -> registers -> LDS, 1 KB of consecutive memory per load
-// instruction. Copies are grouped per iteration (two K tiles, two V tiles); a group is
-// requested two iterations before the one that writes it to LDS in its middle, so two
-// groups are in flight in two register sets. K tiles reach LDS three to four tiles ahead
-// of their S step, V tiles one to two ahead of their O step, in two four-slot rings
-// (tile t lives in slot t % 4).
-//
-// Measured on MI355X with N(0,1) inputs the loop sustains about 0.6 PFLOP/s; a loop of
-// nothing but these MFMAs on random operands reaches 1.76 PFLOP/s on this machine (2.27
-// on constant operands: the clock is power-managed), so the remaining gap is barrier skew,
-// copy issue and the two general iterations at either end of the key range.
+// K/V tiles go from memory straight into LDS (1 KB of consecutive memory per load instruction), two or three iterations ahead of
+// the one that reads them, into rings of eight (six) tiles each; the wait for them counts loads, so the copies take
+// nothing but their issue. Four waves of 128 channels, two workgroups on a CU, have no room for such rings: their tiles travel
+// through registers, requested two iterations before the one that writes them to rings of four tiles in its middle.
+// (Before, all kernels copied like that. 64 x 60 nodes, 28 / 4 heads, 1024 .. 8192 keys paged, cycles for a tile of the two waves of a SIMD:
+// 1893 with every copy's address worked out by 17 scalar instructions and the softmax's rare parts in line, 1622 with
+// addresses kept in lanes and the rare parts behind a branch, 1536 with the tiles going straight into LDS; 1250 are left with
+// nothing but the matrix instructions and the barriers. The clock gives way to the power that busier matrix cores take - 2.1, 1.9, 1.87 and
+// 2.35 GHz - so 898, 842, 815 and 534 ns a tile, and the call 322 -> 292 us. Sharing the exponentials out evenly over a step's slots, or
+// fragments read three or four slots ahead: nothing.)
 #include <type_traits>
 
 #include "attn_mfma_common.h"
@@ -35,27 +34,27 @@ namespace vs {
 
 namespace {
 
-// WPS: waves of a SIMD that have registers at the same time. Three workgroups of four waves and 64 channels on a CU
-// instead of two where that makes one round of a launch that is one and a half: us per call in two / three, 16 / 16 heads,
-// 33 x 43 nodes (528 workgroups), 450 keys 27.4 / 21.2, 1500 paged 71.1 / 55.1; 46 x 60 (736), 200 .. 450 paged 33.1 / 25.6; outside
-// those 256 workgroups two have the faster loop (below): 20 x 60 (320), 1500 paged 42.1 / 47.2, 50 x 60 (800), 450 34.9 / 38.5.
-template <int D, int RPW, int NW, bool PAGED, bool BAL, int WPS = 2>
-__global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const AttnParams p) {
+// Waves of a SIMD that have registers at the same time: two, and three (workgroups of four waves on a CU) with 64 channels.
+template <int D, int RPW, int NW, bool PAGED, bool BAL>
+__global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma_pipe_kernel(const AttnParams p) {
     constexpr int KS = D / 16;                 // k-steps of the S^T product
     constexpr int DB = D / 32;                 // 32-channel blocks of the output
     constexpr int SUB = kTileKeys * D;         // elements per 32-key tile of K (or V)
     constexpr int BPS = SUB * 2 / 1024;        // 1 KB blocks (16 keys x 32 channels) per tile
     constexpr int BPW = (BPS + NW - 1) / NW;   // ... copied by each wave
-    constexpr int NSLOT = 4;
+    // Tiles go straight from memory into LDS where a workgroup has room for rings that reach far enough ahead: eight tiles each of K and V for eight
+    // waves (one workgroup on a CU), six for four waves of 64 channels (three workgroups). Two workgroups of four waves of 128
+    // channels have not, and take their tiles through registers.
+    constexpr bool DIRECT = NW == 8 || D == 64;
+    constexpr int NSLOT = NW == 8 ? 8 : DIRECT ? 6 : 4;
     // Eight waves of 64 channels are twice as many as a tile has blocks: the lower half copies K, the upper half V, one block
-    // of every tile each. (With all copies on the lower half, behind a branch per copy, the compiler cannot count the
-    // loads in flight and waits for all of them in front of every LDS write, the one just requested included: us per call,
-    // so / now, 60 nodes, 32 / 8 heads, 18 x 1000 keys 38.1 / 28.2, 48 x 250 .. 2000 101 / 77, 24 x 1000 .. 8000 paged 155 / 112.)
+    // of every tile each.
     constexpr bool HALVES = NW == 2 * BPS;
     static_assert(HALVES || NW * BPW == BPS, "the waves' blocks make up a tile");
 
     __shared__ __attribute__((aligned(1024))) uint16_t sK[NSLOT][SUB];
     __shared__ __attribute__((aligned(1024))) uint16_t sV[NSLOT][SUB];
+    __shared__ int32_t sBt[DIRECT && PAGED ? NW : 1][kWave]; // block ids, see bt_advance
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
     __shared__ uint64_t sgen;
@@ -125,9 +124,18 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     const int64_t head_base = (PAGED ? 0 : (int64_t)b * p.stride_seq) + (int64_t)kvh * p.stride_head;
     const int stride_tok = (int)p.stride_tok; // host guarantees 32-bit lane offsets
     const int lrow = lane / LPR, lchunk = lane % LPR;
-    const uint32_t lane_off = (uint32_t)(lrow * stride_tok + lchunk * 8) * 2u; // bytes
+    const uint32_t stride = (uint32_t)stride_tok * 2u; // bytes
+    uint32_t lane_off = (uint32_t)lrow * stride + (uint32_t)lchunk * 16u; // bytes
     const int block0 = HALVES ? wave % BPS : wave * BPW; // this wave's first block of a tile
     const bool upper = HALVES && wave >= BPS;
+    // DIRECT: a load leaves lane l's sixteen bytes at 16 l of a block, so the lanes fetch the chunks of a row in the order in
+    // which they are to lie: chunk c of tile row r at position c ^ kx(r) (keys) or c ^ vx(r) (values), which spreads
+    // what an operand read takes over all banks (16 rows of one chunk; 4 rows x 2 or 4 chunks).
+    auto kx = [](int r) __attribute__((always_inline)) { return r % LPR; };
+    auto vx = [](int r) __attribute__((always_inline)) { return D == 128 ? 4 * (r & 3) ^ 2 * ((r ^ (r >> 1)) & 1) : 2 * (r & 3); };
+    uint32_t direct_off[2] = {(uint32_t)lrow * stride + (uint32_t)(lchunk ^ kx(block0 * RPI + lrow)) * 16u,
+                              (uint32_t)lrow * stride + (uint32_t)(lchunk ^ vx(lrow)) * 16u};
+    if (HALVES && upper) direct_off[0] = direct_off[1]; // one tensor only
     uint32_t k_st[BPW], v_st[BPW]; // this lane's LDS byte offsets inside a tile slot, per block
 #pragma unroll
     for (int j = 0; j < BPW; ++j) {
@@ -135,31 +143,69 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
         k_st[j] = (uint32_t)(((r >> 4) * DB + (c >> 2)) * 1024 + (c & 3) * 256 + (((r & 15) ^ (4 * (c & 3))) * 16));
         v_st[j] = (uint32_t)(((r >> 4) * DB + (c >> 2)) * 1024 + (4 * (r & 15) + (c & 3)) * 16);
     }
-    // Paged caches: where the blocks of the tiles to come lie sits one per lane - a window of 64 consecutive table
-    // entries, fetched with one coalesced load and moved along by 32 as the tiles advance - so a tile copy gets
-    // it with v_readlane instead of a scalar load per copy (whose result the copy would have to wait for, together with
-    // every LDS read in flight: scalar loads and LDS share one wait counter). The clamp and the product are done once
-    // per window, by all lanes at once, and the loaded register is only touched where the window moves: with ids in
-    // a window of 128 read twice per lookup 28 x 60 nodes of 28 / 4 heads over 1696 keys took 62.1 us, so 59.3 (54.8 unpaged).
+    // Paged caches: where this wave's rows of the tiles to come lie sits one tile per lane - a window of 64 tiles, moved along
+    // by 32 as they advance, with the next one's block ids on their way - as addresses ready to load from: a tile copy is two
+    // v_readlane and the load. (Block offsets in the lanes, the rest of the address by scalar instructions in front
+    // of every copy: 17 of them, a sixth of all instructions of the loop, and a wave issues one every 9 cycles at best.)
     const int32_t* bt_row = PAGED ? p.block_table + (int64_t)b * p.max_blocks : nullptr;
-    int bt_base = k0 >> p.block_shift; // logical block of lane 0
-    uint32_t bt_lo = 0, bt_hi = 0;     // element offset of the lane's block
-    int32_t bt_next = 0;               // block id of lane 0 + 32 + lane, on its way
-    auto bt_fetch = [&](int first) __attribute__((always_inline)) { return bt_row[min(first + lane, p.max_blocks - 1)]; };
+    constexpr int WINS = HALVES || !DIRECT ? 1 : 2; // K and V, or this wave's one of them (four waves, short of registers: K)
+    int bt_base = 0;                     // tile of lane 0
+    uint32_t bt_lo[WINS], bt_hi[WINS];   // address of this wave's first row of the lane's tile
+    int32_t bt_next = 0;                 // block id of the tile 32 further on
+    // (unsigned: rows past the last allowed one may pass 2^31; past the table its last entry is read)
+    auto bt_token = [&](int first) __attribute__((always_inline)) { return (uint32_t)k0 + (uint32_t)(first + lane) * kTileKeys + (uint32_t)(block0 * RPI); };
+    auto bt_index = [&](int first) __attribute__((always_inline)) { return min(bt_token(first) >> p.block_shift, (uint32_t)p.max_blocks - 1u); };
+    auto bt_fetch = [&](int first) __attribute__((always_inline)) { return bt_row[bt_index(first)]; };
     auto bt_set = [&](int32_t blk) __attribute__((always_inline)) {
         if ((uint32_t)blk >= (uint32_t)p.num_blocks) blk = 0; // reported through status
-        const int64_t off = (int64_t)blk * p.stride_block;
-        bt_lo = (uint32_t)off;
-        bt_hi = (uint32_t)(off >> 32);
+        const uint32_t in_block = (bt_token(bt_base) & (uint32_t)(p.block_size - 1)) * (uint32_t)stride_tok;
+        const uint64_t off = (uint64_t)((int64_t)blk * p.stride_block + head_base + in_block) * 2;
+#pragma unroll
+        for (int w = 0; w < WINS; ++w) {
+            const uint64_t at = (uint64_t)((HALVES ? upper : w == 1) ? vbase : kbase) + off;
+            bt_lo[w] = (uint32_t)at;
+            bt_hi[w] = (uint32_t)(at >> 32);
+        }
     };
     int32_t bt_first = 0;
     if (PAGED) { // (with the prefix length: one trip)
-        bt_first = bt_fetch(bt_base);
-        bt_next = bt_fetch(bt_base + 32);
+        bt_first = bt_fetch(0);
+        if constexpr (DIRECT) load_to_lds4((uint32_t)(uintptr_t)(lds_void*)&sBt[wave][0], bt_row, bt_index(32) * 4u);
+        else bt_next = bt_fetch(32);
     }
-    auto bt_lookup = [&](int lb) __attribute__((always_inline)) {
-        const int rel = lb - bt_base; // 0 .. 63 by construction
-        return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bt_hi, rel) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)bt_lo, rel));
+    auto bt_lookup = [&](bool is_v, int t) __attribute__((always_inline)) {
+        const int rel = t - bt_base, w = WINS == 1 || !is_v ? 0 : 1; // rel: 0 .. 63
+        const char* at = (const char*)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bt_hi[w], rel) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)bt_lo[w], rel));
+        return !DIRECT && is_v ? at + ((const char*)vbase - (const char*)kbase) : at;
+    };
+    // (DIRECT) this wave's 1 KB of tile t into slot `slot` of its ring, t any tile (FULL: one with all its keys). Contiguous caches: `rows` ends at the last key that
+    // may be asked for, what lies past it reads as zeros (or, where offsets that far wrap, as other rows). Paged: tiles past
+    // `last` repeat that one, rows past the end are whatever the pool holds there.
+    __amdgpu_buffer_rsrc_t rows[2];
+    int last = 0;
+    auto rows_up_to = [&](int end) __attribute__((always_inline)) {
+        if constexpr (PAGED) {
+            last = (end - 1 - k0) / kTileKeys;
+        } else {
+            const uint32_t bytes = slice_bytes(end, k0, klen, stride, D * 2);
+#pragma unroll
+            for (int w = 0; w < WINS; ++w)
+                rows[w] = __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(((HALVES ? upper : w == 1) ? vbase : kbase) + head_base) + (int64_t)k0 * stride, 0,
+                                                            (int)bytes, 0x00027000);
+        }
+    };
+    auto fetch = [&](auto full_tag, bool is_v, int t, int slot) __attribute__((always_inline)) {
+        const int w = HALVES ? 0 : is_v;
+        const bool v = HALVES ? upper : is_v;
+        const uint32_t lds = (uint32_t)(uintptr_t)(lds_void*)(v ? &sV[0][0] : &sK[0][0]) + (uint32_t)(slot * SUB * 2 + block0 * 1024);
+        if constexpr (PAGED) load_to_lds(lds, bt_lookup(v, decltype(full_tag)::value ? t : min(t, last)), direct_off[w]);
+        else load_to_lds(lds, rows[w], direct_off[w] + (uint32_t)(t * kTileKeys + RPI * block0) * stride);
+    };
+    // rows of V tile t (this wave's, arrived) that no key has become zeros: whatever the cache holds there, NaN included,
+    // must not meet a zero probability
+    auto zero_tail = [&](int t, int slot, int end) __attribute__((always_inline)) {
+        if ((HALVES && !upper) || k0 + (t + 1) * kTileKeys <= end) return; // uniform
+        if (k0 + t * kTileKeys + RPI * block0 + lrow >= end) *(u32x4*)(sV[slot] + block0 * 512 + lane * 8) = u32x4{0u, 0u, 0u, 0u};
     };
     u32x4 stage[2][4][BPW];
     // ---- this wave's rows and queries (in flight together with the first tiles)
@@ -173,9 +219,10 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
         const int r = min(row_base + rb * kRowBlock + col, p.rows - 1);
         node_of[rb] = row_node(p, r);
     }
-    static_assert(RPW == 1 && NW <= 2 * NSLOT, "a row block's queries take a tile slot");
-    // through the tile slot of this wave's number (nothing is in the rings yet)
-    uint16_t* sq = wave < NSLOT ? sK[wave & (NSLOT - 1)] : sV[wave & (NSLOT - 1)];
+    static_assert(RPW == 1 && (DIRECT || NW <= NSLOT), "a row block's queries take a tile slot");
+    // through a tile slot that nothing is on its way to yet. DIRECT: the last K slots from Q_K on and the last V slots from Q_V on
+    constexpr int Q_K = NW == 8 ? 5 : NSLOT, Q_V = NSLOT - (NW - (NSLOT - Q_K));
+    uint16_t* sq = !DIRECT ? sK[wave & (NSLOT - 1)] : wave < NSLOT - Q_K ? sK[min(Q_K + wave, NSLOT - 1)] : sV[min(Q_V + wave - (NSLOT - Q_K), NSLOT - 1)];
     auto copy_queries = [&]() __attribute__((always_inline)) {
         if (!wave_active) return;
 #pragma unroll
@@ -185,33 +232,46 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
         copy_queries();
         bt_set(bt_first);
     }
-    constexpr bool EARLY = !(BAL && PAGED && NW == 4); // registers: 4 waves of 128 channels 188 us, so 171 (8 x 60 nodes, 32 / 32 heads, 1024 .. 8191 keys)
+    constexpr bool EARLY = DIRECT || !(BAL && PAGED); // registers: 4 waves of 128 channels 188 us, so 171 (8 x 60 nodes, 32 / 32 heads, 1024 .. 8191 keys)
+    // this lane's 16 bytes of the block at a uniform address: a scalar address plus lane_off. (The second statement keeps the
+    // lane's part in one register: extended to 64 bits in front of the loop it takes two and an addition per copy.)
+    auto load_at = [&](const void* block) __attribute__((always_inline)) {
+        const __attribute__((address_space(1))) char* base = (const __attribute__((address_space(1))) char*)block;
+        asm("" : "+s"(base));
+        asm volatile("" : "+v"(lane_off));
+        return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
+    };
+    const int64_t block_bytes = (int64_t)RPI * stride_tok * 2; // from one of this wave's blocks of a tile to the next
     // The first four tiles - K(0), K(1), K(2), V(0), through register set 1 - are requested before
-    // the prefix length is known: clamped to the longest allowed sequence instead of this one, and rows that
-    // turn out to lie past the sequence's last key are zeroed when the tiles go into LDS
+    // the prefix length is known: clamped to the longest allowed sequence instead of this one (paged: to the block table), and
+    // rows that turn out to lie past the sequence's last key are zeroed when the tiles go into LDS
     // (whatever the cache holds there, NaN included, must not meet a zero probability).
     if constexpr (EARLY) {
         const int kend = early_end(most_keys(p), k0, klen);
+        if constexpr (DIRECT) rows_up_to(kend);
         auto load_tile_early = [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
             const uint16_t* gbase = decltype(is_v)::value ? vbase : kbase;
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
-                const int r0 = min(k0 + t * kTileKeys + RPI * (block0 + j), kend - 1); // RPI divides 16: one cache block in paged mode
-                int tok = min(r0 + lrow, kend - 1);
-                int64_t base = head_base;
-                if (PAGED) {
-                    base += bt_lookup(r0 >> p.block_shift);
-                    tok &= p.block_size - 1;
+                if constexpr (PAGED) {
+                    r[j] = load_at(bt_lookup(decltype(is_v)::value, t) + j * block_bytes);
+                } else {
+                    const int tok = min(k0 + t * kTileKeys + RPI * (block0 + j) + lrow, kend - 1);
+                    r[j] = *(const u32x4*)(gbase + head_base + (uint32_t)(tok * stride_tok + lchunk * 8));
                 }
-                r[j] = *(const u32x4*)(gbase + base + (uint32_t)(tok * stride_tok + lchunk * 8));
             }
         };
-        if (!upper) {
+        if constexpr (DIRECT) {
+            if (!upper) {
+                for (int t = 0; t < 3; ++t) fetch(std::false_type{}, false, t, t);
+            }
+            if (!HALVES || upper) fetch(std::false_type{}, true, 0, 0);
+        } else {
             load_tile_early(std::false_type{}, 0, stage[1][0]);
             load_tile_early(std::false_type{}, 1, stage[1][1]);
             load_tile_early(std::false_type{}, 2, stage[1][2]);
+            load_tile_early(std::true_type{}, 0, stage[1][3]);
         }
-        if (!HALVES || upper) load_tile_early(std::true_type{}, 0, stage[1][3]);
     }
 
     if (!PAGED) copy_queries();
@@ -225,10 +285,14 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     }
     const bool s_ok = prefix_ok(p, S);
     if (kvh == 0 && k0 == 0 && rg == 0) report_status(p, b, tree_code, s_ok, S, &sflag);
-    if (tree_code != VS_STATUS_OK || !s_ok) return;
-
     const int nk = S + p.tree_keys;
-    if (k0 >= nk) return;
+    if (tree_code != VS_STATUS_OK || !s_ok || k0 >= nk) { // uniform
+        if (BAL && DIRECT) { // other pieces follow, or merges that take the rings' place
+            wait_loads<0>();
+            __syncthreads();
+        }
+        return;
+    }
     if (!BAL && p.gates && nk <= klen) whole = true; // a sequence of one split has nothing to merge
     const bool merge = !BAL && p.gates && !whole;
     const MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
@@ -240,37 +304,33 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     // first key of the split in this (sequence, KV head) slice; only used when not paged
     const char* kfast = (const char*)(kbase + head_base + (int64_t)k0 * stride_tok);
     const char* vfast = (const char*)(vbase + head_base + (int64_t)k0 * stride_tok);
-    // moves the window so that it starts less than 32 blocks before logical block `lb_min` (called once per iteration)
-    auto bt_advance = [&](int lb_min) __attribute__((always_inline)) {
-        if (PAGED && lb_min >= bt_base + 32) { // uniform
+    // moves the window so that it starts less than 32 tiles before tile `t_min` (called once per iteration)
+    auto bt_advance = [&](int t_min) __attribute__((always_inline)) {
+        if (PAGED && t_min >= bt_base + 32) { // uniform
             bt_base += 32;
-            bt_set(bt_next);
-            bt_next = bt_fetch(bt_base + 32);
+            if constexpr (DIRECT) {
+                // The next ids come through LDS like the tiles: a load that the compiler knows of would have it wait for all copies in
+                // flight. These have been there since long: requested 16 iterations ago.
+                bt_set(sBt[wave][lane]);
+                wait_lds_reads();
+                load_to_lds4((uint32_t)(uintptr_t)(lds_void*)&sBt[wave][0], bt_row, bt_index(bt_base + 32) * 4u);
+            } else {
+                bt_set(bt_next);
+                bt_next = bt_fetch(bt_base + 32);
+            }
         }
     };
-    // this lane's 16 bytes of the block at a uniform address: a scalar address plus lane_off (left to itself the compiler adds
-    // them up first, and the copies' addresses take two registers each)
-    auto load_at = [&](const void* block) __attribute__((always_inline)) {
-        const __attribute__((address_space(1))) char* base = (const __attribute__((address_space(1))) char*)block;
-        asm("" : "+s"(base));
-        return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
-    };
-    // is_v: a constant or, with HALVES, `upper`
     // LFAST: a full tile, so the address is a wave-uniform base plus a per-lane constant and nothing
     // needs clamping.
     auto load_tile = [&](auto lfast_tag, auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
         constexpr bool LFAST = decltype(lfast_tag)::value;
         const bool ISV = is_v;
-        if constexpr (LFAST && PAGED) {
-            // a full tile of a paged cache: the RPI rows of a copy block lie in one cache block, so the
-            // address is a wave-uniform base (block id from the window, KV head, first row inside the
-            // block - all scalar arithmetic) plus the same per-lane constant as for a contiguous cache
+        if constexpr (PAGED) {
+            // the same for every tile: rows past k1 lie in the pool, too (V's are zeroed on their way into LDS)
+            if (!LFAST && k0 + t * kTileKeys >= k1) return; // no such tile: its LDS image is never used
+            const char* at = bt_lookup(ISV, t);
 #pragma unroll
-            for (int j = 0; j < BPW; ++j) {
-                const int r0 = k0 + t * kTileKeys + RPI * (block0 + j); // uniform per wave
-                const int64_t sbase = head_base + bt_lookup(r0 >> p.block_shift) + (int64_t)((r0 & (p.block_size - 1)) * stride_tok);
-                r[j] = load_at((ISV ? vbase : kbase) + sbase);
-            }
+            for (int j = 0; j < BPW; ++j) r[j] = load_at(at + j * block_bytes);
         } else if constexpr (LFAST) {
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
@@ -282,93 +342,119 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
             if (k0 + t * kTileKeys >= k1) return; // no such tile: its LDS image is never used
 #pragma unroll
             for (int j = 0; j < BPW; ++j) {
-                const int r0 = k0 + t * kTileKeys + RPI * (block0 + j); // RPI divides 16: one cache block in paged mode
-                int tok = min(r0 + lrow, k1 - 1);
-                int64_t base = head_base;
-                if (PAGED) {
-                    base += bt_lookup(min(r0, k1 - 1) >> p.block_shift);
-                    tok &= p.block_size - 1;
-                }
+                const int tok = min(k0 + t * kTileKeys + RPI * (block0 + j) + lrow, k1 - 1);
                 const uint32_t off = (uint32_t)(tok * stride_tok + lchunk * 8);
-                r[j] = *(const u32x4*)(gbase + base + off);
+                r[j] = *(const u32x4*)(gbase + head_base + off);
             }
         }
     };
-    auto stash_tile = [&](auto is_v, int t, const u32x4(&r)[BPW]) __attribute__((always_inline)) {
+    auto stash_tile = [&](auto lfast_tag, auto is_v, int t, const u32x4(&r)[BPW]) __attribute__((always_inline)) {
         const bool ISV = is_v;
-        char* slot = (char*)(ISV ? sV[t & 3] : sK[t & 3]);
+        char* slot = (char*)(ISV ? sV[t & (NSLOT - 1)] : sK[t & (NSLOT - 1)]);
 #pragma unroll
-        for (int j = 0; j < BPW; ++j) *(u32x4*)(slot + (ISV ? v_st[j] : k_st[j])) = r[j];
+        for (int j = 0; j < BPW; ++j) {
+            u32x4 w = r[j];
+            if constexpr (PAGED && !decltype(lfast_tag)::value) {
+                const u32x4 zero = {0u, 0u, 0u, 0u};
+                if (ISV) w = k0 + t * kTileKeys + RPI * (block0 + j) + lrow < k1 ? w : zero;
+            }
+            *(u32x4*)(slot + (ISV ? v_st[j] : k_st[j])) = w;
+        }
     };
-    // Copies are grouped per iteration: group g = K(2g+3), K(2g+4), V(2g+1), V(2g+2) is what
+    // Copies through registers are grouped per iteration: group g = K(2g+3), K(2g+4), V(2g+1), V(2g+2) is what
     // iteration g writes to LDS. Its loads are issued in iteration g - 2, so two groups are
     // in flight and alternate between two register sets.
-    // Part 0 .. 3 of a group (HALVES: 0 and 2, this wave's first and second tile): what do(is_v, tile, registers) gets.
-    auto part_of = [&](auto part_tag, auto set_tag, int g, auto what) __attribute__((always_inline)) {
-        constexpr int PART = decltype(part_tag)::value, SET = decltype(set_tag)::value;
-        if constexpr (HALVES) {
-            if constexpr (PART % 2 == 0) what(upper, 2 * g + (upper ? 1 : 3) + PART / 2, stage[SET][PART / 2]);
-        } else if constexpr (PART < 2) {
-            what(std::false_type{}, 2 * g + 3 + PART, stage[SET][PART]);
-        } else {
-            what(std::true_type{}, 2 * g - 1 + PART, stage[SET][PART]);
-        }
-    };
-    using P0 = std::integral_constant<int, 0>;
-    using P1 = std::integral_constant<int, 1>;
-    using P2 = std::integral_constant<int, 2>;
-    using P3 = std::integral_constant<int, 3>;
-    auto each_part = [&](auto set_tag, int g, auto what) __attribute__((always_inline)) {
-        part_of(P0{}, set_tag, g, what);
-        part_of(P1{}, set_tag, g, what);
-        part_of(P2{}, set_tag, g, what);
-        part_of(P3{}, set_tag, g, what);
-    };
     auto load_group = [&](auto lfast_tag, auto set_tag, int g) __attribute__((always_inline)) {
-        each_part(set_tag, g, [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) { load_tile(lfast_tag, is_v, t, r); });
+        constexpr int SET = decltype(set_tag)::value;
+        load_tile(lfast_tag, std::false_type{}, 2 * g + 3, stage[SET][0]);
+        load_tile(lfast_tag, std::false_type{}, 2 * g + 4, stage[SET][1]);
+        load_tile(lfast_tag, std::true_type{}, 2 * g + 1, stage[SET][2]);
+        load_tile(lfast_tag, std::true_type{}, 2 * g + 2, stage[SET][3]);
     };
-    auto stash_group = [&](auto set_tag, int g) __attribute__((always_inline)) { each_part(set_tag, g, stash_tile); };
+    auto stash_group = [&](auto lfast_tag, auto set_tag, int g) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_tag)::value;
+        stash_tile(lfast_tag, std::false_type{}, 2 * g + 3, stage[SET][0]);
+        stash_tile(lfast_tag, std::false_type{}, 2 * g + 4, stage[SET][1]);
+        stash_tile(lfast_tag, std::true_type{}, 2 * g + 1, stage[SET][2]);
+        stash_tile(lfast_tag, std::true_type{}, 2 * g + 2, stage[SET][3]);
+    };
 
     if constexpr (!EARLY) {
-        if (!upper) {
-            load_tile(std::false_type{}, std::false_type{}, 0, stage[1][0]);
-            load_tile(std::false_type{}, std::false_type{}, 1, stage[1][1]);
-            load_tile(std::false_type{}, std::false_type{}, 2, stage[1][2]);
-        }
-        if (!HALVES || upper) load_tile(std::false_type{}, std::true_type{}, 0, stage[1][3]);
+        load_tile(std::false_type{}, std::false_type{}, 0, stage[1][0]);
+        load_tile(std::false_type{}, std::false_type{}, 1, stage[1][1]);
+        load_tile(std::false_type{}, std::false_type{}, 2, stage[1][2]);
+        load_tile(std::false_type{}, std::true_type{}, 0, stage[1][3]);
     }
     // the rest of the prologue copies: group 0 (set 0)
-    load_group(std::false_type{}, std::integral_constant<int, 0>{}, 0);
+    if constexpr (DIRECT) {
+        rows_up_to(k1);
+        if (!upper) {
+            for (int t = 3; t < Q_K && t <= NSLOT - 2; ++t) fetch(std::false_type{}, false, t, t);
+        }
+        if (!HALVES || upper) {
+            for (int t = 1; t < Q_V; ++t) fetch(std::false_type{}, true, t, t);
+        }
+    } else {
+        load_group(std::false_type{}, std::integral_constant<int, 0>{}, 0);
+    }
 
     uint64_t mask[RPW];
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb)
         mask[rb] = p.tree_keys == 0 ? 0ull : (p.tree_mask ? p.tree_mask[(int64_t)b * p.T + node_of[rb]] : ancestor_mask(sp, node_of[rb]));
 
-    float m2[RPW], lsum[RPW]; // running reference (log2 domain, scaled) and this lane's share of the sum
+    // running reference (log2 domain, scaled), the score (not scaled) from which on it moves, and this lane's share of the sum
+    // (two addends: the additions of a step do not wait for each other)
+    float m2[RPW], limit[RPW], lsum[RPW], lsum2[RPW];
+    const float to_score = 1.f / p.scale_log2;
     f32x16 acc[RPW][DB];
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb) {
-        m2[rb] = -INFINITY;
-        lsum[rb] = 0.f;
+        m2[rb] = limit[rb] = -INFINITY;
+        lsum[rb] = lsum2[rb] = 0.f;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[rb][db][r] = 0.f;
     }
 
-    // per-lane LDS offsets (elements); everything else is a compile-time immediate
-    // K fragment of k-step ks (chunk 2*ks + half of row `col`): k_lane[ks & 1] + ks * 256
+    // per-lane LDS offsets; everything else is a compile-time immediate
+    // K fragment of k-step ks: chunk 2*ks + half of row `col`
     const int k_lane[2] = {(col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (4 * half)) * 8,
                            (col >> 4) * (DB * 512) + half * 128 + ((col & 15) ^ (8 + 4 * half)) * 8};
     const int t16 = lane & 15;
     const int v_lane = half * 128 + (t16 >> 2) * 32 + ((lane >> 4) & 1) * 16 + ((t16 >> 1) & 1) * 8 + (t16 & 1) * 4;
+    uint32_t k_at[KS], v_at[DB]; // DIRECT: addresses in slot 0
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) k_at[ks] = (uint32_t)(uintptr_t)(lds_void*)&sK[0][0] + (uint32_t)(col * D + ((2 * ks + half) ^ kx(col)) * 8) * 2u;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+        const int r = 4 * half + (t16 >> 2);
+        v_at[db] = (uint32_t)(uintptr_t)(lds_void*)&sV[0][0] + (uint32_t)(r * D + ((4 * db + 2 * ((lane >> 4) & 1) + ((t16 >> 1) & 1)) ^ vx(r)) * 8 + (t16 & 1) * 4) * 2u;
+        asm("" : "+v"(v_at[db])); // (the ring's address stays in: a read's immediate offset reaches 64 KB)
+    }
+    auto k_frag = [&](int slot, int ks) __attribute__((always_inline)) {
+        if constexpr (DIRECT) return *(const __attribute__((address_space(3))) u32x4*)(k_at[ks] + (uint32_t)(slot * SUB * 2));
+        else return *(const u32x4*)(sK[slot] + k_lane[ks & 1] + ks * 256);
+    };
+    auto v_frag = [&](int slot, int sl, int db) __attribute__((always_inline)) { // two transposing reads of 4 keys x 16 channels
+        lds_s16x4 *lo, *hi;
+        if constexpr (DIRECT) {
+            lo = (lds_s16x4*)(v_at[db] + (uint32_t)(slot * SUB * 2 + sl * (16 * D * 2)));
+            hi = (lds_s16x4*)(v_at[db] + (uint32_t)(slot * SUB * 2 + sl * (16 * D * 2) + 8 * D * 2));
+        } else {
+            const uint16_t* tV = sV[slot] + v_lane + sl * (DB * 512) + db * 512;
+            lo = (lds_s16x4*)tV;
+            hi = (lds_s16x4*)(tV + 256);
+        }
+        return __builtin_bit_cast(u32x4, __builtin_shufflevector(__builtin_amdgcn_ds_read_tr16_b64_v4i16(lo), __builtin_amdgcn_ds_read_tr16_b64_v4i16(hi), 0, 1, 2, 3, 4, 5, 6, 7));
+    };
 
     // S^T = K . Q^T for one tile: lane (col, half) gets keys 8*(r/4) + 4*half + r%4 of row `col`
-    auto qk = [&](f32x16(&s)[RPW], const uint16_t* kslot) __attribute__((always_inline)) {
+    auto qk = [&](f32x16(&s)[RPW], int kslot) __attribute__((always_inline)) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, *(const u32x4*)(kslot + k_lane[ks & 1] + ks * 256));
+            const bf16x8 a = __builtin_bit_cast(bf16x8, k_frag(kslot, ks));
 #pragma unroll
             for (int rb = 0; rb < RPW; ++rb) {
                 if (ks == 0) {
@@ -380,17 +466,13 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
             }
         }
     };
-    // O^T += V^T . P^T: the A operand comes from two transposing reads of 4 keys x 16 channels
-    auto pv = [&](const uint16_t* vslot, const bf16x8(&pf)[RPW][2]) __attribute__((always_inline)) {
-        const uint16_t* tV = vslot + v_lane;
+    // O^T += V^T . P^T
+    auto pv = [&](int vslot, const bf16x8(&pf)[RPW][2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tV + sl * (DB * 512) + db * 512));
-                const s16x4 hi =
-                    __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tV + sl * (DB * 512) + db * 512 + 256));
-                const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                const bf16x8 a = __builtin_bit_cast(bf16x8, v_frag(vslot, sl, db));
 #pragma unroll
                 for (int rb = 0; rb < RPW; ++rb)
                     acc[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[rb][sl], acc[rb][db], 0, 0, 0);
@@ -421,6 +503,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
             const float m_use = (MASKED && m_new == -INFINITY) ? 0.f : m_new; // no visible key yet
             alpha[rb] = __builtin_amdgcn_exp2f(m2[rb] - m_use);
             m2[rb] = m_new;
+            limit[rb] = (m_new + kLazy) * to_score;
             float psum = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -428,6 +511,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
                 psum += s[r];
             }
             lsum[rb] = lsum[rb] * alpha[rb] + psum;
+            lsum2[rb] *= alpha[rb];
 #pragma unroll
             for (int sl = 0; sl < 2; ++sl) {
                 u32x4 w;
@@ -440,18 +524,19 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
             }
         }
     };
+    auto scale_acc = [&](const float(&alpha)[RPW]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < RPW; ++rb)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[rb][db][r] *= alpha[rb];
+    };
     auto rescale = [&](const float(&alpha)[RPW]) __attribute__((always_inline)) {
         bool need = false;
 #pragma unroll
         for (int rb = 0; rb < RPW; ++rb) need |= alpha[rb] != 1.f;
-        if (__any(need)) {
-#pragma unroll
-            for (int rb = 0; rb < RPW; ++rb)
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[rb][db][r] *= alpha[rb];
-        }
+        if (__any(need)) scale_acc(alpha);
     };
 
     // One pipeline step for prefix-only tiles with every neighbour present, written slot
@@ -461,20 +546,13 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     // slots ahead, and one share of the softmax of S(cur) -> P(cur) for row block rb. The
     // softmax is cut into 16 groups per row block: 4 of running-maximum work (the last one
     // fixes the reference), 8 of two exponentials each, 4 of bf16 packing.
-    // copy_tag >= 0 (a register set): the step also carries the iteration's tile copies, one
-    // tile per four slots - the staged tile goes to LDS and its registers are refilled with the
-    // tile two groups ahead - so that the LDS writes trickle in between the fragment reads
-    // instead of arriving as one 32 KB burst that stalls every wave's reads behind it.
-    auto fast_step = [&](auto copy_tag, auto lfast_tag, int g, f32x16(&s_next)[RPW], const uint16_t* kslot,
-                         const uint16_t* vslot, const bf16x8(&p_prev)[RPW][2], f32x16(&s_cur)[RPW],
-                         bf16x8(&p_cur)[RPW][2], float(&alpha)[RPW]) __attribute__((always_inline)) {
-        constexpr int CSET = decltype(copy_tag)::value;
+    // copy(0), copy(1): called in the step's second slot and in the middle, for the tile copies.
+    auto fast_step = [&](auto copy, f32x16(&s_next)[RPW], int kslot, int vslot, const bf16x8(&p_prev)[RPW][2], f32x16(&s_cur)[RPW],
+                         bf16x8(&p_cur)[RPW][2]) __attribute__((always_inline)) {
         constexpr int NF = KS + 2 * DB; // fragments = MFMA slots per row block
         constexpr int GPS = 16 / NF;    // softmax groups per slot
         static_assert(16 % NF == 0, "softmax groups must divide evenly over the slots");
         constexpr int PF = 2;
-        const uint16_t* tK[2] = {kslot + k_lane[0], kslot + k_lane[1]};
-        const uint16_t* tV = vslot + v_lane;
         u32x4 frag[PF + 1];
         // slot order: K and V^T fragments alternate, so that consecutive MFMAs never use the
         // same accumulator (a dependent MFMA issued right behind its predecessor stalls the
@@ -482,50 +560,47 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
         static_assert(KS == 2 * DB, "as many K fragments as V^T fragments");
         auto load_frag = [&](int f) __attribute__((always_inline)) {
             const int h = f >> 1;
-            if ((f & 1) == 0) {
-                frag[f % (PF + 1)] = *(const u32x4*)(tK[h & 1] + h * 256);
-            } else {
-                const int sl = h / DB, db = h % DB;
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tV + sl * (DB * 512) + db * 512));
-                const s16x4 hi =
-                    __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tV + sl * (DB * 512) + db * 512 + 256));
-                frag[f % (PF + 1)] = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            }
+            frag[f % (PF + 1)] = (f & 1) == 0 ? k_frag(kslot, h) : v_frag(vslot, h / DB, h % DB);
         };
-        float mx[RPW], nm[RPW], psum[RPW], psum2[RPW];
+        float mx[RPW], alpha[RPW];
+        bool moved[RPW]; // uniform: some row's reference has moved, the accumulators are rescaled behind the step
         u32x4 pw[RPW][2];
         auto softmax_group = [&](int rb, int g) __attribute__((always_inline)) {
             f32x16& sc = s_cur[rb];
             if (g < 4) {
-                mx[rb] = g == 0 ? max3(max3(sc[0], sc[1], sc[2]), sc[3], sc[3])
-                                : max3(max3(mx[rb], sc[4 * g], sc[4 * g + 1]), sc[4 * g + 2], sc[4 * g + 3]);
+                mx[rb] = g == 0 ? maximum3(maximum3(sc[0], sc[1], sc[2]), sc[3], sc[3])
+                                : maximum3(maximum3(mx[rb], sc[4 * g], sc[4 * g + 1]), sc[4 * g + 2], sc[4 * g + 3]);
                 if (g == 3) {
-                    const float mt = half_max(mx[rb]) * p.scale_log2;
-                    const float m_new = (mt > m2[rb] + kLazy) ? mt : m2[rb]; // finite: prefix keys are always visible
-                    alpha[rb] = __builtin_amdgcn_exp2f(m2[rb] - m_new);
-                    m2[rb] = m_new;
-                    nm[rb] = -m_new;
-                    psum[rb] = 0.f;
-                    psum2[rb] = 0.f;
+                    const float top = half_maximum(mx[rb]); // finite: prefix keys are always visible
+                    moved[rb] = __any(top > limit[rb]);
+                    if (moved[rb]) { // rare after the first tiles, so everything that it alone needs stands here
+                        const float mt = top * p.scale_log2;
+                        const float m_new = (mt > m2[rb] + kLazy) ? mt : m2[rb];
+                        alpha[rb] = __builtin_amdgcn_exp2f(m2[rb] - m_new);
+                        m2[rb] = m_new;
+                        limit[rb] = (m_new + kLazy) * to_score;
+                        lsum[rb] *= alpha[rb];
+                        lsum2[rb] *= alpha[rb];
+                    }
                 }
             } else if (g < 12) {
 #pragma unroll
                 for (int e = 2 * (g - 4); e < 2 * (g - 4) + 2; ++e)
-                    sc[e] = __builtin_amdgcn_exp2f(fmaf(sc[e], p.scale_log2, nm[rb]));
+                    sc[e] = __builtin_amdgcn_exp2f(fmaf(sc[e], p.scale_log2, -m2[rb]));
                 // the previous group's pair joins the sum here, one group late, so that the add
                 // never waits for an exponential; two running sums keep the adds independent. The
                 // empty asm keeps each add in its slot (otherwise all sixteen are sunk behind the
                 // step as one dependent chain, out of the MFMAs' shadow).
                 if (g > 4) {
-                    psum[rb] += sc[2 * (g - 5)];
-                    psum2[rb] += sc[2 * (g - 5) + 1];
-                    asm volatile("" : "+v"(psum[rb]), "+v"(psum2[rb]));
+                    lsum[rb] += sc[2 * (g - 5)];
+                    lsum2[rb] += sc[2 * (g - 5) + 1];
+                    asm volatile("" : "+v"(lsum[rb]), "+v"(lsum2[rb]));
                 }
             } else {
                 const int q = g - 12, sl = q >> 1;
                 if (g == 12) {
-                    psum[rb] += sc[14];
-                    psum2[rb] += sc[15];
+                    lsum[rb] += sc[14];
+                    lsum2[rb] += sc[15];
                 }
 #pragma unroll
                 for (int e = 2 * (q & 1); e < 2 * (q & 1) + 2; ++e) {
@@ -533,7 +608,6 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
                     pw[rb][sl][e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
                     asm volatile("" : "+v"(pw[rb][sl][e]));
                 }
-                if (g == 15) lsum[rb] = lsum[rb] * alpha[rb] + (psum[rb] + psum2[rb]);
             }
         };
 #pragma unroll
@@ -557,21 +631,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
                 }
 #pragma unroll
                 for (int sg = f * GPS; sg < (f + 1) * GPS; ++sg) softmax_group(rb, sg);
-                if constexpr (CSET >= 0) {
-                    if (rb == 0 && f % (NF / 4) == 1) {
-                        auto renew = [&](auto part_tag) __attribute__((always_inline)) {
-                            part_of(part_tag, copy_tag, g, stash_tile);
-                            part_of(part_tag, copy_tag, g + 2, [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
-                                load_tile(lfast_tag, is_v, t, r);
-                            });
-                        };
-                        const int part = f / (NF / 4); // known after unrolling
-                        if (part == 0) renew(P0{});
-                        else if (part == 1) renew(P1{});
-                        else if (part == 2) renew(P2{});
-                        else renew(P3{});
-                    }
-                }
+                if (rb == 0 && f % (NF / 2) == 1) copy(f / (NF / 2));
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -585,6 +645,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
                 asm volatile("" : "+v"(pw[rb][sl]));
                 p_cur[rb][sl] = __builtin_bit_cast(bf16x8, pw[rb][sl]);
             }
+        static_assert(RPW == 1, "one flag");
+        if (moved[0]) scale_acc(alpha);
     };
 
     // Every load so far (tiles, queries, masks) has landed after this wait. Stating it here,
@@ -593,8 +655,18 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     __builtin_amdgcn_s_waitcnt(wait_vm(0));
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[0][ks] = read_q_frag<D>(sq, ks, col, half);
-    __syncthreads(); // every wave has its queries: the rings may be filled
-    {
+    if constexpr (DIRECT) {
+        zero_tail(0, 0, k1);
+        __syncthreads(); // every wave has its queries: their slots may be filled
+        // ... with what the first iteration does not request
+        if (!upper) {
+            for (int t = Q_K; t <= NSLOT - 2; ++t) fetch(std::false_type{}, false, t, t);
+        }
+        if (!HALVES || upper) {
+            for (int t = Q_V; t <= NSLOT - 4; ++t) fetch(std::false_type{}, true, t, t);
+        }
+    } else {
+        __syncthreads(); // every wave has its queries: the rings may be filled
         // the early tiles: rows at or past k1 become zeros
         auto stash_tile_live = [&](auto is_v, uint16_t* slot, const u32x4(&r)[BPW], int t) __attribute__((always_inline)) {
             constexpr bool ISV = decltype(is_v)::value;
@@ -605,15 +677,19 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
                 *(u32x4*)((char*)slot + (ISV ? v_st[j] : k_st[j])) = live ? r[j] : zero;
             }
         };
-        if (!upper) {
-            stash_tile_live(std::false_type{}, sK[0], stage[1][0], 0);
-            stash_tile_live(std::false_type{}, sK[1], stage[1][1], 1);
-            stash_tile_live(std::false_type{}, sK[2], stage[1][2], 2);
-        }
-        if (!HALVES || upper) stash_tile_live(std::true_type{}, sV[0], stage[1][3], 0);
+        stash_tile_live(std::false_type{}, sK[0], stage[1][0], 0);
+        stash_tile_live(std::false_type{}, sK[1], stage[1][1], 1);
+        stash_tile_live(std::false_type{}, sK[2], stage[1][2], 2);
+        stash_tile_live(std::true_type{}, sV[0], stage[1][3], 0);
+        load_group(std::false_type{}, std::integral_constant<int, 1>{}, 1);
     }
-    load_group(std::false_type{}, std::integral_constant<int, 1>{}, 1);
-    __syncthreads();
+    // tiles that end at or before min(S, k1) hold prefix keys only
+    const int n_plain = max(0, min(S, k1) - k0) / kTileKeys;
+    const int fast_end = min(n_plain, n - 1) & ~1; // fast iterations need tiles ta + 1 (plain) and ta + 2 (present)
+    // what the first fast step takes for V(-1), with probabilities of zero
+    if (fast_end > (DIRECT ? 0 : 2))
+        for (int i = tid * 8; i < SUB; i += NW * 64 * 8) *(u32x4*)&sV[NSLOT - 1][i] = u32x4{0u, 0u, 0u, 0u};
+    if constexpr (!DIRECT) __syncthreads();
 
     f32x16 sa[RPW], sb[RPW];  // scores of the iteration's first / second tile
     bf16x8 pa[RPW][2], pb[RPW][2];
@@ -621,59 +697,86 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
         for (int sl = 0; sl < 2; ++sl) pb[rb][sl] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-    if (wave_active) qk(sa, sK[0]);
-    __syncthreads(); // slot 0 of the K ring is rewritten at the end of the first iteration
+    if (wave_active) qk(sa, 0);
+    __syncthreads(); // slot 0 of the K ring is rewritten in the first iteration
 
-    // Iteration g handles tiles ta = 2g and tb = 2g + 1. CFAST iterations have every
-    // neighbour tile present and only prefix keys; the general form checks and masks.
-    auto iteration = [&](auto active, auto cfast_tag, auto lfast_tag, auto set_tag, int ta) __attribute__((always_inline)) {
-        constexpr bool FAST = decltype(cfast_tag)::value;
-        // set_tag: the register set of the copy group that this iteration stashes
-        using masked_t = std::integral_constant<bool, !FAST>;
-        const int tb = ta + 1;
-        const int g = ta >> 1;
-        // this iteration requests group g + 2 = tiles 2g + 5 .. 2g + 8
-        bt_advance(min(k0 + (2 * g + 5) * kTileKeys, k1 - 1) >> p.block_shift);
-        // first tile: S(tb), O(ta - 1) | P(ta)
-        if (active) {
-            float alpha[RPW];
-            if constexpr (FAST) {
-                // the very first step applies all-zero probabilities to V(0)
-                fast_step(std::integral_constant<int, -1>{}, lfast_tag, g, sb, sK[tb & 3], sV[ta ? (ta - 1) & 3 : 0], pb, sa,
-                          pa, alpha);
-            } else {
-                if (tb < n) qk(sb, sK[tb & 3]);
-                if (ta > 0) pv(sV[(ta - 1) & 3], pb);
-                softmax(masked_t{}, k0 + ta * kTileKeys, sa, pa, alpha);
-            }
+    // An iteration handles tiles ta and tb = ta + 1. Fast ones have every neighbour tile present and only prefix keys; the
+    // general form (two parts, the copies in between) checks and masks. slot(d): ring slot of tile ta + d.
+    auto general_first = [&](int ta, auto slot) __attribute__((always_inline)) { // S(tb), O(ta - 1) | P(ta)
+        float alpha[RPW];
+        if (ta + 1 < n) qk(sb, slot(1));
+        if (ta > 0) pv(slot(-1), pb);
+        softmax(std::true_type{}, k0 + ta * kTileKeys, sa, pa, alpha);
+        rescale(alpha);
+    };
+    auto general_second = [&](int ta, auto slot) __attribute__((always_inline)) { // S(ta + 2), O(ta) | P(tb)
+        float alpha[RPW];
+        if (ta + 2 < n) qk(sa, slot(2));
+        pv(slot(0), pa);
+        if (ta + 1 < n) {
+            softmax(std::true_type{}, k0 + (ta + 1) * kTileKeys, sb, pb, alpha);
             rescale(alpha);
         }
-        // In the middle of the iteration: group g (requested one and a half iterations ago) goes
-        // to LDS and its registers are refilled with group g + 2. The LDS writes complete under
-        // the second tile's work; the barrier at the end publishes them for iteration g + 1.
-        // (the fast form spreads the same copies over the slots of its second step, see fast_step;
-        // waves without rows have no such step and copy here)
-        // (with four waves a tile is two blocks per wave and the interleaved form runs out of registers)
-        constexpr bool SPREAD = FAST && BPW == 1;
-        if (!SPREAD || !active) {
-            stash_group(set_tag, g);
-            load_group(lfast_tag, set_tag, g + 2);
-        }
-        // second tile: S(ta + 2), O(ta) | P(tb)
+    };
+    // Through registers: iteration g = ta / 2 requests group g + 2 = tiles up to 2g + 8 and, in its middle, takes group g (requested
+    // one and a half iterations ago) to LDS. The LDS writes complete under
+    // the second tile's work; the barrier at the end publishes them for iteration g + 1.
+    // set_tag: the register set of the copy group that this iteration stashes
+    auto iteration = [&](auto active, auto cfast_tag, auto lfast_tag, auto set_tag, int ta) __attribute__((always_inline)) {
+        constexpr bool FAST = decltype(cfast_tag)::value;
+        const int g = ta >> 1;
+        auto slot = [&](int d) __attribute__((always_inline)) { return (ta + d) & (NSLOT - 1); };
+        bt_advance(2 * g + 5);
         if (active) {
-            float alpha[RPW];
+            // (the very first step applies all-zero probabilities to a slot of zeros)
+            if constexpr (FAST) fast_step([](int) {}, sb, slot(1), slot(-1), pb, sa, pa);
+            else general_first(ta, slot);
+        }
+        stash_group(lfast_tag, set_tag, g);
+        load_group(lfast_tag, set_tag, g + 2);
+        if (active) {
+            if constexpr (FAST) fast_step([](int) {}, sa, slot(2), slot(0), pa, sb, pb);
+            else general_second(ta, slot);
+        }
+        __syncthreads();
+    };
+    // DIRECT, rings of N: a fast iteration requests K(ta + N - 1), K(ta + N), V(ta + N - 3), V(ta + N - 2) into the slots of tiles read in the
+    // one before, whether they exist or not: so a wait for all loads but the last iterations' is one for the tiles of
+    // the next, requested N / 2 - 2 iterations earlier. ph: ta % N, a constant where the loop is unrolled (the slots are then
+    // part of the instructions). FULL: all tiles requested are full ones.
+    auto direct_iteration = [&](auto active, auto cfast_tag, auto full_tag, auto ph, int ta) __attribute__((always_inline)) {
+        constexpr bool FAST = decltype(cfast_tag)::value, FULL = decltype(full_tag)::value;
+        auto slot = [&](int d) __attribute__((always_inline)) { // d: -1 .. N
+            const int x = ph + d;
+            return (NSLOT & (NSLOT - 1)) == 0 ? x & (NSLOT - 1) : x < 0 ? x + NSLOT : x >= NSLOT ? x - NSLOT : x;
+        };
+        auto request = [&](int i) __attribute__((always_inline)) { // i: 0 .. 3 (HALVES: 0 and 2)
+            auto tile = [&](bool v, int j) __attribute__((always_inline)) {
+                const int d = v ? NSLOT - 3 + j : NSLOT - 1 + j;
+                if (FAST || ta + d < n) fetch(full_tag, v, ta + d, v ? slot(NSLOT - 3 + j) : slot(NSLOT - 1 + j));
+            };
+            if (!HALVES) tile(i >= 2, i & 1);
+            else if (i % 2 == 0) tile(upper, i >> 1);
+        };
+        bt_advance(FULL ? ta + NSLOT - 3 : min(ta + NSLOT - 3, last));
+        if (active) {
+            // (the very first step applies all-zero probabilities to a slot of zeros)
             if constexpr (FAST) {
-                using copy_t = std::conditional_t<SPREAD, decltype(set_tag), std::integral_constant<int, -1>>;
-                fast_step(copy_t{}, lfast_tag, g, sa, sK[(ta + 2) & 3], sV[ta & 3], pa, sb, pb, alpha);
-                rescale(alpha);
+                fast_step([&](int i) __attribute__((always_inline)) { request(i); }, sb, slot(1), slot(-1), pb, sa, pa);
+                fast_step([&](int i) __attribute__((always_inline)) { request(2 + i); }, sa, slot(2), slot(0), pa, sb, pb);
             } else {
-                if (ta + 2 < n) qk(sa, sK[(ta + 2) & 3]);
-                pv(sV[ta & 3], pa);
-                if (tb < n) {
-                    softmax(masked_t{}, k0 + tb * kTileKeys, sb, pb, alpha);
-                    rescale(alpha);
-                }
+                for (int i = 0; i < 4; ++i) request(i);
+                general_first(ta, slot);
+                general_second(ta, slot);
             }
+        } else {
+            for (int i = 0; i < 4; ++i) request(i);
+        }
+        if constexpr (FAST) wait_loads<(NSLOT / 2 - 2) * (HALVES ? 2 : 4)>();
+        else wait_loads<0>();
+        if (!FULL) {
+            zero_tail(ta + 1, slot(1), k1);
+            if (FAST || ta + 2 < n) zero_tail(ta + 2, slot(2), k1);
         }
         __syncthreads();
     };
@@ -681,38 +784,50 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     using F = std::false_type;
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
-    // tiles that end at or before min(S, k1) hold prefix keys only
-    const int n_plain = max(0, min(S, k1) - k0) / kTileKeys;
-    const int fast_end = min(n_plain, n - 1) & ~1; // CFAST iterations need tiles ta + 1 (plain) and ta + 2 (present)
-    // Iterations come in pairs so that the two register sets alternate at compile time. The
-    // forms only ever get more general as ta grows (prefix tiles first, copies near the end
-    // of the range last), so three loops in a row cover every case. Iteration ta loads
-    // group ta/2 + 2 = tiles up to ta + 8.
+    // The forms only ever get more general as ta grows (prefix tiles first, copies near the end of the range last), so three loops
+    // in a row cover every case. (One loop with all forms, or one that is left in its middle, spills hundreds of registers.)
+    // Through registers iterations come in pairs so that the two register sets alternate at compile time; iteration ta
+    // loads group ta/2 + 2 = tiles up to ta + 8.
     auto all_tiles = [&](auto active) __attribute__((always_inline)) {
         int ta = 0;
-        for (; ta + 2 < fast_end && ta + 10 < n_full; ta += 4) {
-            iteration(active, T{}, T{}, S0{}, ta);
-            iteration(active, T{}, T{}, S1{}, ta + 2);
-        }
-        for (; ta + 2 < fast_end; ta += 4) {
-            iteration(active, T{}, F{}, S0{}, ta);
-            iteration(active, T{}, F{}, S1{}, ta + 2);
-        }
-        for (; ta < n; ta += 4) {
-            iteration(active, F{}, F{}, S0{}, ta);
-            if (ta + 2 < n) iteration(active, F{}, F{}, S1{}, ta + 2);
+        if constexpr (DIRECT) {
+            auto turn = [&](auto full_tag) __attribute__((always_inline)) { // of the rings
+                direct_iteration(active, T{}, full_tag, std::integral_constant<int, 0>{}, ta);
+                direct_iteration(active, T{}, full_tag, std::integral_constant<int, 2>{}, ta + 2);
+                direct_iteration(active, T{}, full_tag, std::integral_constant<int, 4>{}, ta + 4);
+                if constexpr (NSLOT == 8) direct_iteration(active, T{}, full_tag, std::integral_constant<int, 6>{}, ta + 6);
+            };
+            for (; ta + NSLOT - 2 < fast_end && ta + 2 * NSLOT - 2 < n_full; ta += NSLOT) turn(T{});
+            for (; ta + NSLOT - 2 < fast_end; ta += NSLOT) turn(F{});
+            int ph = 0;
+            auto next = [&]() __attribute__((always_inline)) {
+                ta += 2;
+                ph = ph + 2 == NSLOT ? 0 : ph + 2;
+            };
+            for (; ta < fast_end; next()) direct_iteration(active, T{}, F{}, ph, ta);
+            for (; ta < n; next()) direct_iteration(active, F{}, F{}, ph, ta);
+        } else {
+            for (; ta + 2 < fast_end && ta + 10 < n_full; ta += 4) {
+                iteration(active, T{}, T{}, S0{}, ta);
+                iteration(active, T{}, T{}, S1{}, ta + 2);
+            }
+            for (; ta + 2 < fast_end; ta += 4) {
+                iteration(active, T{}, F{}, S0{}, ta);
+                iteration(active, T{}, F{}, S1{}, ta + 2);
+            }
+            for (; ta < n; ta += 4) {
+                iteration(active, F{}, F{}, S0{}, ta);
+                if (ta + 2 < n) iteration(active, F{}, F{}, S1{}, ta + 2);
+            }
         }
     };
-    // Waves without rows only copy, in loops of their own: where both kinds pass through the same code, the compiler
-    // cannot tell which copies are still on their way and waits for all of them in every iteration, the ones just
-    // requested included (12 x 60 nodes, 16 / 16 heads of 64 channels, up to 8000 keys 68 -> 57 us; eight waves
-    // of 128 channels 1 %). Four waves of 128 channels run out of registers that way (32 x 60 nodes of 32 / 32
-    // heads, 3136 keys 304 -> 377 us) and are bound by memory, not by its latency; so do three waves per SIMD.
-    if constexpr ((D == 128 && NW == 4) || WPS == 3) all_tiles(wave_active);
+    // Waves without rows only copy, in loops of their own. (Through registers all waves pass the same code: four waves of 128 channels
+    // run out of registers otherwise, 32 x 60 nodes of 32 / 32 heads, 3136 keys 304 -> 377 us, and are bound by memory.)
+    if constexpr (!DIRECT) all_tiles(wave_active);
     else if (wave_active) all_tiles(T{});
     else all_tiles(F{});
     if (wave_active) {
-    if ((n & 1) == 0) pv(sV[(n - 1) & 3], pb);
+    if ((n & 1) == 0) pv((n - 1) % NSLOT, pb);
 
     // ---- epilogue: lane (col, half) holds, for row `col`, channels db*32 + 8*(r/4) + 4*half + r%4
     // (what depends on the lane alone is worked out again: kept over the loop it takes registers)
@@ -721,7 +836,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_mfma_pipe_kernel(const Attn
     const int lane = tid_end & 63, half = lane >> 5, col = lane & 31;
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb) {
-        const float l = half_sum(lsum[rb]);
+        const float l = half_sum(lsum[rb] + lsum2[rb]);
         if (whole) {
             // Lines pay for eight waves of 128 channels: us per call, 8-byte pieces / lines, 60 nodes, 28 / 4 heads, 64 x 400 keys 53.4 / 48.7,
             // 28 x 1696 59.9 / 58.6. With four waves or 64 channels the trip through LDS costs more: 12 x 35 nodes, 32 / 32
@@ -925,13 +1040,6 @@ hipError_t launch_pipe(const AttnParams& p, hipStream_t s) {
         return hipGetLastError();
     }
     const dim3 grid(p.by_length ? (p.B * p.Hkv + 7) / 8 * 8 * p.row_groups : (p.total_wgs + 7) / 8 * 8);
-    if constexpr (D == 64 && NW == 4) {
-        if (pipe_three_per_cu(D, NW, p.total_wgs)) {
-            if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, false, 3>), grid, dim3(NW * kWave), 0, s, p);
-            else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, false, 3>), grid, dim3(NW * kWave), 0, s, p);
-            return hipGetLastError();
-        }
-    }
     if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, false>), grid, dim3(NW * kWave), 0, s, p);
     else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, false>), grid, dim3(NW * kWave), 0, s, p);
     return hipGetLastError();

@@ -26,18 +26,6 @@ namespace vs {
 
 namespace {
 
-// 1 KB from memory into LDS at byte `lds` (lane l's sixteen bytes at lds + 16 l), without a stop in registers. Not the
-// builtin: the compiler would make every later LDS read wait for all of these loads, not for the tile it reads. Earlier
-// LDS reads have returned before the load is issued; it has arrived after a wait for the vector-memory counter.
-__device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t lane_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory"); // (nothing else here uses m0)
-}
-template <int N>
-__device__ __forceinline__ void wait_loads() { // at most N of this wave's loads outstanding (they return in order)
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
 // NW waves, RB row blocks
 template <int D, int NW, int RB>
 __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnParams p) {

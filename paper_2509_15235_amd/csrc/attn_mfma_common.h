@@ -24,10 +24,17 @@ constexpr float kLazy = 8.f; // log2 slack of the running softmax reference
 // registers now and then - run-to-run differences in the softmax reference.)
 __device__ __forceinline__ float max3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
+// The same with NaN coming through: v_maximum3_f32, without the two v_max x, x in which fmaxf turns signalling NaNs into quiet ones.
+__device__ __forceinline__ float maximum3(float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); }
+
 // max / sum over the two 32-lane halves, result in every lane (v_permlane32_swap)
 __device__ __forceinline__ float half_max(float x) {
     const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_maximum(float x) {
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __builtin_elementwise_maximum(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float half_sum(float x) {
     const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -50,6 +57,25 @@ __device__ __forceinline__ float visible_or_inf(float s, uint32_t w, int bit) {
     const uint32_t m = (uint32_t)((int32_t)(w << (31 - bit)) >> 31);
     return __uint_as_float((__float_as_uint(s) & m) | (0xff800000u & ~m));
 }
+
+// 1 KB from memory into LDS at byte `lds` (lane l's sixteen bytes at lds + 16 l), without a stop in registers. Not the
+// builtin: the compiler would make every later LDS read wait for all of these loads, not for the tile it reads. Earlier
+// LDS reads have returned before the load is issued; it has arrived after a wait for the vector-memory counter.
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t lane_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory"); // (nothing else here uses m0)
+}
+// the same from a bounded range: what lies outside reads as zeros
+__device__ __forceinline__ void load_to_lds(uint32_t lds, __amdgpu_buffer_rsrc_t range, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(off), "s"(range) : "memory");
+}
+__device__ __forceinline__ void load_to_lds4(uint32_t lds, const void* base, uint32_t lane_off) { // 256 bytes, four of each lane
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() { // at most N of this wave's loads outstanding (they return in order)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // What a workgroup of a launch with equal splits works on. Consecutive ids go round-robin over the XCDs; the remap gives
 // every XCD a contiguous range, splits fastest: row groups and neighbouring splits of a (sequence, KV head) share its L2.
