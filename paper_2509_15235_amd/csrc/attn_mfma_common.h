@@ -61,8 +61,12 @@ __device__ __forceinline__ float visible_or_inf(float s, uint32_t w, int bit) {
 // 1 KB from memory into LDS at byte `lds` (lane l's sixteen bytes at lds + 16 l), without a stop in registers. Not the
 // builtin: the compiler would make every later LDS read wait for all of these loads, not for the tile it reads. Earlier
 // LDS reads have returned before the load is issued; it has arrived after a wait for the vector-memory counter.
+// (Nothing else here uses m0.) LANE_BASE: the base comes straight from v_readlane. Between a vector instruction that writes a scalar
+// register and a load that reads it lie five wait states, which the compiler minds for instructions that it can see.
+template <bool LANE_BASE = false>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t lane_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory"); // (nothing else here uses m0)
+    if constexpr (LANE_BASE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
 }
 // the same from a bounded range: what lies outside reads as zeros
 __device__ __forceinline__ void load_to_lds(uint32_t lds, __amdgpu_buffer_rsrc_t range, uint32_t off) {
