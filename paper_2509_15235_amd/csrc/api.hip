@@ -533,6 +533,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.group = desc->Hq / desc->Hkv;
     p.inv_group = 1.f / (float)p.group;
     p.node_stride = (int64_t)(desc->Hq - p.group) * desc->d;
+    p.row_skip = desc->Hq - p.group;
     p.rows = pl.rows;
     p.rows_pad = pl.rows_pad;
     p.max_prefix_len = desc->max_prefix_len;

@@ -55,6 +55,7 @@ __device__ __forceinline__ float row_all(float x, Op op) {
 
 template <int D, int SETS, bool PAGED>
 __global__ __launch_bounds__(kF32Waves * kWave, 2) void attn_f32_kernel(const AttnParams p) {
+    request_args(p);
     constexpr int KJ = D / 16; // 16-byte pieces of a key row per lane
     constexpr int VM = D / 64; // ... of a value row
     constexpr int ROWS = 4 * SETS; // query rows of the workgroup

@@ -37,6 +37,7 @@ namespace {
 // Waves of a SIMD that have registers at the same time: two, and three (workgroups of four waves on a CU) with 64 channels.
 template <int D, int RPW, int NW, bool PAGED, bool BAL>
 __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma_pipe_kernel(const AttnParams p) {
+    request_args(p);
     constexpr int KS = D / 16;                 // k-steps of the S^T product
     constexpr int DB = D / 32;                 // 32-channel blocks of the output
     constexpr int SUB = kTileKeys * D;         // elements per 32-key tile of K (or V)
@@ -225,8 +226,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     uint16_t* sq = !DIRECT ? sK[wave & (NSLOT - 1)] : wave < NSLOT - Q_K ? sK[min(Q_K + wave, NSLOT - 1)] : sV[min(Q_V + wave - (NSLOT - Q_K), NSLOT - 1)];
     auto copy_queries = [&]() __attribute__((always_inline)) {
         if (!wave_active) return;
-#pragma unroll
-        for (int i = 0; i < KS; ++i) copy_q_piece<D>(p, b, kvh, row_base, sq, i, lane);
+        copy_q_block<D>(p, b, kvh, row_base, sq, lane);
     };
     if (PAGED) { // the queries while the block ids are on their way
         copy_queries();

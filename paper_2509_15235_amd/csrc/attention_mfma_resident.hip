@@ -29,6 +29,7 @@ constexpr int kResWaves = 8;
 
 template <int D, int NRB, int NT, bool PAGED>
 __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(const AttnParams p) {
+    request_args(p);
     constexpr int KS = D / 16;          // k-steps of the S^T product
     constexpr int DB = D / 32;          // 32-channel blocks of the output
     constexpr int KQ = kResWaves / NRB; // key parts inside the workgroup
@@ -118,8 +119,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     const bool wave_active = row_base < p.rows;
     constexpr int QPW = (KS + KQ - 1) / KQ; // pieces per wave
     u32x4 qreg[QPW];
-#pragma unroll
-    for (int i = 0; i < QPW; ++i) qreg[i] = load_q_piece<D>(p, b, kvh, row_base, min(kq * QPW + i, KS - 1), lane);
+    load_q_pieces<D>(p, b, kvh, [&](int) { return row_base; }, [&](int i) { return min(kq * QPW + i, KS - 1); }, lane, qreg);
     // the gate of the row group (thread 0 opens it below)
     const MergeGate gate{p.gates ? p.gates + kGateWords * (int64_t)((b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
     MergeSeen seen{};

@@ -25,6 +25,7 @@ constexpr int kRndWaves = 8;
 
 template <int D, int NRB, bool PAGED>
 __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(const AttnParams p) {
+    request_args(p);
     constexpr int NT = kRoundKeys / kTileKeys; // tiles of a round
     constexpr int KS = D / 16;          // k-steps of the S^T product
     constexpr int DB = D / 32;          // 32-channel blocks of the output
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     __shared__ uint64_t sgen;
     uint16_t* sK = smem;
     uint16_t* sV = smem + NT * SUB;
-    uint16_t* sQ = smem + Q_AT / 2; // queries: row blocks of D-channel rows (see load_q_piece)
+    uint16_t* sQ = smem + Q_AT / 2; // queries: row blocks of D-channel rows (see load_q_pieces)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -129,8 +130,7 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     // the waves of a row block share the fetch of its queries
     constexpr int QPW = (KS + KQ - 1) / KQ; // pieces per wave
     u32x4 qreg[QPW];
-#pragma unroll
-    for (int i = 0; i < QPW; ++i) qreg[i] = load_q_piece<D>(p, b, kvh, row_base, min(kq * QPW + i, KS - 1), lane);
+    load_q_pieces<D>(p, b, kvh, [&](int) { return row_base; }, [&](int i) { return min(kq * QPW + i, KS - 1); }, lane, qreg);
     // the gate of the row group (thread 0 opens it below)
     const MergeGate gate{p.gates ? p.gates + kGateWords * (int64_t)((b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
     MergeSeen seen{};
@@ -446,9 +446,9 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
             for (int i = 0; i < PPK; ++i) {
                 const u32x2 w0 = pack_partial(r[i][0], r[i][1], r[i][2], r[i][3], inv), w1 = pack_partial(r[i][4], r[i][5], r[i][6], r[i][7], inv);
                 const u32x4 w = {w0[0], w0[1], w1[0], w1[1]};
-                uint16_t* dst = po + (MY * PPK + i) * piece_stride(p);
-                if (merge) __builtin_amdgcn_raw_buffer_store_b128(w, span_of(dst), lane * 16, 0, kDeviceScope);
-                else *(u32x4*)(dst + lane * 8) = w;
+                const uint32_t at = (uint32_t)(lane * 16 + (MY * PPK + i) * p.num_splits * 1024);
+                if (merge) store_piece<true>(po, at, w);
+                else store_piece<false>(po, at, w);
             }
         }
     };

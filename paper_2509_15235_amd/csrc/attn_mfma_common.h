@@ -95,15 +95,26 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
 }
 
 __device__ __forceinline__ int row_node(const AttnParams& p, int r) { return node_of_row(r, p.group, p.inv_group); }
-// Element offset of (sequence b, KV head kvh)'s first query row in q and out, uniform, and from there to 16-byte chunk `chunk`
-// of row r. A node's rows are adjacent, `node_stride` lies between two nodes' beyond that.
+// the nodes of N rows, behind one branch
+template <int N>
+__device__ __forceinline__ void row_nodes(const AttnParams& p, const int (&r)[N], int (&node)[N]) {
+    if (p.group <= kShortGroup) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) node[i] = node_of_row_short(r[i], p.inv_group);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) node[i] = node_of_row(r[i], p.group, p.inv_group);
+    }
+}
+// Element offset of (sequence b, KV head kvh)'s first query row in q and out, uniform
 template <int D>
 __device__ __forceinline__ int64_t row_start(const AttnParams& p, int b, int kvh) {
     return ((int64_t)b * p.T * p.Hq + (int64_t)kvh * p.group) * D;
 }
+// row r from there on
 template <int D>
-__device__ __forceinline__ int64_t row_in(const AttnParams& p, int r, int node, int chunk) {
-    return row_elements(r, node, p.node_stride, D) + chunk * 8;
+__device__ __forceinline__ const char* row_at(const AttnParams& p, const char* first, int r, int node) {
+    return first + (uint64_t)row_number(r, node, p.row_skip) * (uint32_t)(D * 2);
 }
 // the same as one offset
 __device__ __forceinline__ int64_t row_offset(const AttnParams& p, int b, int kvh, int r, int node) {
@@ -127,12 +138,17 @@ __device__ __forceinline__ int sequence_by_rank(const AttnParams& p, int rank, i
 // units busy for 0.2 us - with eight waves that is 1.7 us in which no key can be requested. So a row
 // block is fetched in whole rows (one load instruction = 1 KB of consecutive rows), stored with chunk c of
 // row r at position c ^ r % (chunks per row) - conflict-free both ways - and read back as operands.
-// Piece i of D / 16 pieces; the row block starts at row_base (rows past the end repeat the last one).
-template <int D>
-__device__ __forceinline__ u32x4 load_q_piece(const AttnParams& p, int b, int kvh, int row_base, int i, int lane) {
+// N of D / 16 pieces: number piece(i) of the row block that starts at row base(i) (rows past the end repeat the last one).
+template <int D, int N, typename Base, typename Piece>
+__device__ __forceinline__ void load_q_pieces(const AttnParams& p, int b, int kvh, Base base, Piece piece, int lane, u32x4 (&q)[N]) {
     constexpr int LPR = D / 8, RPI = 64 / LPR;
-    const int r = min(row_base + RPI * i + lane / LPR, p.rows - 1);
-    return *(const u32x4*)((const uint16_t*)p.q + row_start<D>(p, b, kvh) + row_in<D>(p, r, row_node(p, r), lane % LPR));
+    const char* first = (const char*)((const uint16_t*)p.q + row_start<D>(p, b, kvh) + lane % LPR * 8);
+    int r[N], node[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = min(base(i) + RPI * piece(i) + lane / LPR, p.rows - 1);
+    row_nodes(p, r, node);
+#pragma unroll
+    for (int i = 0; i < N; ++i) q[i] = *(const u32x4*)row_at<D>(p, first, r[i], node[i]);
 }
 template <int D>
 __device__ __forceinline__ void store_q_piece(uint16_t* sq, u32x4 v, int i, int lane) {
@@ -140,14 +156,19 @@ __device__ __forceinline__ void store_q_piece(uint16_t* sq, u32x4 v, int i, int 
     const int r = RPI * i + lane / LPR;
     *(u32x4*)(sq + r * D + ((lane % LPR) ^ (r % LPR)) * 8) = v;
 }
-// The same piece without a stop in registers: the fetching lanes take the chunks in the order they are stored in.
-// `sq` is uniform; the piece has arrived after a wait for the vector-memory counter.
+// All pieces of a row block without a stop in registers: the fetching lanes take the chunks in the order they are stored in.
+// `sq` is uniform; the pieces have arrived after a wait for the vector-memory counter.
 template <int D>
-__device__ __forceinline__ void copy_q_piece(const AttnParams& p, int b, int kvh, int row_base, uint16_t* sq, int i, int lane) {
-    constexpr int LPR = D / 8, RPI = 64 / LPR;
-    const int rl = RPI * i + lane / LPR, r = min(row_base + rl, p.rows - 1);
-    const uint16_t* src = (const uint16_t*)p.q + row_start<D>(p, b, kvh) + row_in<D>(p, r, row_node(p, r), (lane % LPR) ^ (rl % LPR));
-    __builtin_amdgcn_global_load_lds(src, (lds_void*)(sq + i * 512), 16, 0, 0);
+__device__ __forceinline__ void copy_q_block(const AttnParams& p, int b, int kvh, int row_base, uint16_t* sq, int lane) {
+    constexpr int LPR = D / 8, RPI = 64 / LPR, N = D / 16;
+    const char* first = (const char*)((const uint16_t*)p.q + row_start<D>(p, b, kvh));
+    int r[N], node[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = min(row_base + RPI * i + lane / LPR, p.rows - 1);
+    row_nodes(p, r, node);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        __builtin_amdgcn_global_load_lds((const uint16_t*)row_at<D>(p, first + ((lane % LPR) ^ ((RPI * i + lane / LPR) % LPR)) * 16, r[i], node[i]), (lds_void*)(sq + i * 512), 16, 0, 0);
 }
 template <int D>
 __device__ __forceinline__ bf16x8 read_q_frag(const uint16_t* sq, int ks, int col, int half) {
@@ -204,6 +225,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_of(const uint16_t* slice
     return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(slice) + (int64_t)k0 * stride, 0, (int)bytes, 0x00027000);
 }
 
+// 16 bytes of a lane at byte `at` behind a uniform base. (Never with a scalar offset instead: for such stores the compiler leaves out the wait
+// state that a 16-byte store needs before its data registers are written again, and later values were stored in their place.)
+template <bool MERGE>
+__device__ __forceinline__ void store_piece(const uint16_t* base, uint32_t at, u32x4 w) {
+    __builtin_amdgcn_raw_buffer_store_b128(w, span_of(base), at, 0, MERGE ? kDeviceScope : 0);
+}
 // One 32-channel accumulator block of a row block, divided by the rows' sums: two 16-byte pieces per
 // lane. `blk` = piece 0 of the (unit, split, row block), db = channel block.
 template <bool MERGE = false>
@@ -213,9 +240,7 @@ __device__ __forceinline__ void store_partial(const AttnParams& p, uint16_t* blk
         const u32x2 lo = pack_partial(a[8 * hp], a[8 * hp + 1], a[8 * hp + 2], a[8 * hp + 3], inv);
         const u32x2 hi = pack_partial(a[8 * hp + 4], a[8 * hp + 5], a[8 * hp + 6], a[8 * hp + 7], inv);
         const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
-        uint16_t* dst = blk + (db * 2 + hp) * piece_stride(p);
-        if constexpr (MERGE) __builtin_amdgcn_raw_buffer_store_b128(w, span_of(dst), lane * 16, 0, kDeviceScope);
-        else *(u32x4*)(dst + lane * 8) = w;
+        store_piece<MERGE>(blk, lane * 16 + (db * 2 + hp) * p.num_splits * 1024, w);
     }
 }
 // (max, sum) pairs are grouped per row block with the splits adjacent: index of the
@@ -304,7 +329,8 @@ __device__ __forceinline__ MergeItem merge_item(const AttnParams& p, int b, int 
     it.ml = (uint32_t)(rb * p.num_splits) * (kRowBlock * 8);
     it.po = (uint32_t)((rb * (D / 16) + piece) * p.num_splits) * 1024 + hl * 512;
     const int r = (rb0 + rb) * kRowBlock + (lane & 31);
-    it.out = r < p.rows ? (uint16_t*)p.out + row_offset(p, b, kvh, r, row_node(p, r)) + piece * 16 + 4 * hl + 8 * (lane >> 5) : nullptr;
+    const char* first = (const char*)((uint16_t*)p.out + row_start<D>(p, b, kvh) + piece * 16 + 4 * hl + 8 * (lane >> 5));
+    it.out = r < p.rows ? (uint16_t*)row_at<D>(p, first, r, row_node(p, r)) : nullptr;
     return it;
 }
 // Where a lane finds its splits of any item: lanes r and r + 32 share row r and take every other split (past the last

@@ -162,6 +162,7 @@ __device__ __forceinline__ void wave_topk(const uint64_t (&key)[NE], int K, uint
 // ranked a step and chunk lists of 64-bit keys took three such levels and the final selection from 43.2 to 37.8 us
 // (a list per wave, merged; value and index apart), 8 x 16 x 152064 in five levels from 238 to 192.
 __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const DraftExpandParams p) {
+    request_args(p);
     __shared__ float s_m[kExpandWaves], s_s[kExpandWaves];
     __shared__ __attribute__((aligned(16))) uint64_t s_list[kExpandWaves * kListLen];
     __shared__ uint64_t s_wave[kExpandWaves * kMaxDraftK];
@@ -450,6 +451,7 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
 
 // grid = B, block = 256.
 __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const DraftBuildParams p) {
+    request_args(p);
     constexpr int kWords = kMaxDraftTotal / 64;
     constexpr int kRounds = kMaxDraftTotal / kSelThreads; // candidates per thread, at most
     constexpr int kSelWaves = kSelThreads / kWave;

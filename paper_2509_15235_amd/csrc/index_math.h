@@ -25,8 +25,11 @@ constexpr uint32_t fast_div(uint32_t n, FastDiv by, uint32_t& rem) {
 // Node of query row r (r / group), inv_group = 1 / group. (r + 1/2) / group is 1 / (2 group) or more away from a whole number and the
 // quotient is below 64, so up to 16384 rows a node the fp32 error, 64 * 2^-23, is too small to matter; beyond, it is off by less
 // than one.
+constexpr int32_t kShortGroup = 16384;
+template <typename F> // (a constexpr function has to have a constant value for some arguments, a template has not)
+constexpr int32_t node_of_row_short(int32_t r, F inv_group) { return (int32_t)__builtin_fmaf((float)r, inv_group, 0.5f * inv_group); }
 constexpr int32_t node_of_row(int32_t r, int32_t group, float inv_group) {
-    if (group <= 16384) return (int32_t)__builtin_fmaf((float)r, inv_group, 0.5f * inv_group);
+    if (group <= kShortGroup) return node_of_row_short(r, inv_group);
     int32_t n = (int32_t)((float)r * inv_group);
     const int32_t rem = r - n * group;
     n += (rem >= group) - (rem < 0);
@@ -53,5 +56,10 @@ constexpr int32_t early_end(int64_t most_keys, int32_t k0, int32_t keys) {
 constexpr int64_t row_elements(int32_t r, int32_t node, int64_t node_stride, int32_t d) {
     return (int64_t)((uint64_t)(uint32_t)node * (uint64_t)node_stride + (uint64_t)(uint32_t)r * (uint32_t)d);
 }
+
+
+// The same in rows, `skip` = Hq - group of them between two nodes': below T * Hq and so below 2^31. What a kernel does for several rows
+// on its way to its first loads (a 64-bit product per row takes three more instructions).
+constexpr uint32_t row_number(int32_t r, int32_t node, int32_t skip) { return (uint32_t)node * (uint32_t)skip + (uint32_t)r; }
 
 } // namespace vs

@@ -31,6 +31,18 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return (uint32_t)float_to_bf16_bits(lo) | ((uint32_t)float_to_bf16_bits(hi) << 16);
 }
 
+// Asks for a kernel's arguments in one go. They lie in lines of 64 bytes that the scalar cache does not have yet, a trip to memory
+// each (450 - 560 cycles in a stream, 190 in a graph), and the compiler requests every argument where it is used first: the resident attention
+// kernel made three such trips in a row before its first key load. 28 layers of one sequence 322.6 -> 309.3 us, four images 10.3 -> 10.0.
+// (Not in attention_mfma_rows.hip: 4 x 60 nodes, 32 / 32 heads, 3100 keys 39.2 without, 39.5 us with it.)
+template <typename T>
+__device__ __forceinline__ void request_args(const T& p) {
+    const uint32_t* w = (const uint32_t*)&p;
+    constexpr int N = (sizeof(T) - 4) / 64;
+    static_assert(N <= 5, "lines");
+    asm volatile("" ::"s"(w[0]), "s"(w[N > 0 ? 16 : 0]), "s"(w[N > 1 ? 32 : 0]), "s"(w[N > 2 ? 48 : 0]), "s"(w[N > 3 ? 64 : 0]), "s"(w[N > 4 ? 80 : 0]), "s"(w[sizeof(T) / 4 - 1]));
+}
+
 // ---- Wave-wide reductions on the vector ALU (DPP and lane swaps; a shuffle goes through LDS and takes ten times
 // as long, six in a row about 0.3 us). Lanes pair up as in a xor butterfly from 32 down to 1.
 template <int CTRL>

@@ -64,6 +64,7 @@ struct AttnParams {
     int64_t stride_seq, stride_block, stride_head, stride_tok;
     float inv_group;            // 1 / group (row_node)
     int64_t node_stride;        // (Hq - group) * d (row_offset)
+    int32_t row_skip;           // Hq - group (row_number)
     float scale;                // softmax scale
     float scale_log2;           // softmax scale * log2(e)
     int32_t num_splits;         // grid extent over key splits
