@@ -21,7 +21,7 @@
 // that would be idle otherwise (the host's choice).
 // Before (one wave per row, plain fused multiply-adds): 2 x 31 nodes, 8 / 2 heads of 128 channels, 333 - 600
 // keys 188 us; 8 nodes over 64 keys, 4 / 1 heads of 64 channels 19 us. Now 10.6 and 4.7 us.
-#include "vs_device.h"
+#include "attn_mfma_common.h"
 
 namespace vs {
 
@@ -72,12 +72,10 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void attn_f32_kernel(const At
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = lane >> 4, cg = (lane >> 2) & 3, j = lane & 3;
 
-    // workgroup id -> (sequence, KV head, row group): the row groups of a unit run on one XCD and share its L2
-    const int per_xcd = (p.total_wgs + 7) >> 3;
-    const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (v >= p.total_wgs) return;
-    const int rg = v % p.row_groups, unit = v / p.row_groups;
-    const int kvh = unit % p.Hkv, b = unit / p.Hkv;
+    // the row groups of a unit run on one XCD and share its L2 (one split)
+    const WorkItem at = work_item(p);
+    if (at.none) return;
+    const int rg = at.rg, kvh = at.kvh, b = at.b;
 
     const int32_t S = p.prefix_len[b]; // requested first; the first tile and the queries do not wait for it
     const int64_t cache_tokens = PAGED ? (int64_t)p.max_blocks * p.block_size : p.capacity;
@@ -140,13 +138,13 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void attn_f32_kernel(const At
 
     // queries: set s, row rg * 8 + 4 s + j; rows past the end repeat the last one (results discarded)
     f32x4 qf[SETS][KJ];
-    int node[SETS], hq[SETS];
+    int row_of[SETS], node[SETS];
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) row_of[s] = min(rg * ROWS + 4 * s + j, p.rows - 1);
+    row_nodes(p, row_of, node);
 #pragma unroll
     for (int s = 0; s < SETS; ++s) {
-        const int r = min(rg * ROWS + 4 * s + j, p.rows - 1);
-        node[s] = r / p.group;
-        hq[s] = kvh * p.group + (r - node[s] * p.group);
-        const float* q = (const float*)p.q + (((int64_t)b * p.T + node[s]) * p.Hq + hq[s]) * D + 4 * cg;
+        const float* q = (const float*)p.q + row_start<D>(p, b, kvh) + (uint64_t)row_number(row_of[s], node[s], p.row_skip) * (uint32_t)D + 4 * cg;
 #pragma unroll
         for (int i = 0; i < KJ; ++i) qf[s][i] = *(const f32x4*)(q + 16 * i);
     }
@@ -364,8 +362,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, 2) void attn_f32_kernel(const At
         for (int w = 0; w < kF32Waves; ++w) // waves without a tile hold zeros
 #pragma unroll
             for (int e = 0; e < CPT; ++e) o[e] += so[(w * ROWS + row) * PITCH + c + e];
-        const int nd = r / p.group, h = kvh * p.group + (r - nd * p.group);
-        float* dst = (float*)p.out + (((int64_t)b * p.T + nd) * p.Hq + h) * D + c;
+        float* dst = (float*)p.out + row_start<D>(p, b, kvh) + (uint64_t)row_number(r, row_node(p, r), p.row_skip) * (uint32_t)D + c;
 #pragma unroll
         for (int e = 0; e < CPT; ++e) dst[e] = o[e];
     }
