@@ -283,11 +283,14 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
             topk_own(s_list + wave * kListLen, [&](int r, uint64_t k) { s_wave[wave * kMaxDraftK + r] = k; });
             __syncthreads();
         }
-        if (wave == 0) {
+        if (wave == 1) { // the chunk's statistics, while the first wave ranks its list: one after the other took a tree from 35.1 to 35.9 us
             const float wm = lane < kExpandWaves ? s_m[lane] : -INFINITY;
             const float cm = wave_max(wm);
             const float cs = wave_sum(wm > -INFINITY ? s_s[lane & (kExpandWaves - 1)] * __builtin_amdgcn_exp2f((wm - cm) * 1.4426950408889634f) : 0.f);
             if (lane == 0) store_device(p.part_ms + row * p.chunks + chunk, ((uint64_t)__float_as_uint(cs) << 32) | __float_as_uint(cm));
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // in memory
+        }
+        if (wave == 0) {
             uint64_t* const top = p.part_top + (row * p.chunks + chunk) * K;
             auto out = [&](int r, uint64_t k) { store_device(top + r, k); }; // 0 when the chunk has fewer than r + 1 entries
             if (one_wave) {
@@ -304,9 +307,10 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
                 }
                 wave_topk(key, K, s_list, out);
             }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this chunk's results are in memory
-            if (lane == 0) s_last = arrival_last(arrivals, (uint32_t)(F * p.chunks)) ? 1 : 0;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
+        __syncthreads(); // this chunk's results are in memory
+        if (tid == 0) s_last = arrival_last(arrivals, (uint32_t)(F * p.chunks)) ? 1 : 0;
         __syncthreads();
         if (s_last == 0) return;
     }
