@@ -116,7 +116,7 @@ int32_t check_desc(const vs_attn_desc* d, int tree = 1) {
     return VS_OK;
 }
 
-Plan make_plan(const vs_attn_desc* d, int tree = 1) {
+Plan plan_kernel(const vs_attn_desc* d, int tree) {
     Plan pl{};
     const int group = d->Hq / d->Hkv;
     pl.rows = d->T * group;
@@ -423,6 +423,62 @@ size_t workspace_bytes(const vs_attn_desc* d, const Plan& pl) {
            (merges_inside(d, pl) ? align_up((size_t)d->B * d->Hkv * pl.row_groups * kGateWords * sizeof(uint64_t)) : 0);
 }
 
+// How the resident kernel cuts a launch. Its eight waves are row blocks x key parts, so with fewer row blocks a wave has fewer
+// tiles one after the other, and taking up to four times the workgroups for the same rows costs nothing while CUs are idle.
+// us per call, 28 / 4 heads (1 to 4 sequences of 16 to 60 nodes, 100 .. 1700 keys), by row blocks of a workgroup (1, 2, 4) and
+// 64-key tiles of a split; a call that is one split takes 2.0 less, heads of 64 channels 1.0 less in nearly the same order.
+constexpr float kResidentCost[3][4] = {{6.5f, 6.95f, 7.5f, 8.1f}, {7.1f, 7.6f, 8.8f, 9.25f}, {8.1f, 8.9f, 10.7f, INFINITY}};
+float resident_cost(int row_blocks, int tps, int n) { return kResidentCost[row_blocks / 2][tps - 1] - (n == 1 ? 2.f : 0.f); }
+
+// The kernel and its cut as plan_kernel has them, or (AUTO without other knobs) the resident kernel's cheapest cut into no more
+// splits - a split's rows are rounded once more than the sums - whose workgroups all run at once. us per call before / with it:
+//   one split: 1 x 60 nodes, 28 / 4 heads, 130 keys 7.1 / 4.9, 4 x 60, 190 keys 9.0 / 5.7; 8 x 31, 32 / 8 heads of 64, 90 keys 5.6 / 4.4
+//   fewer row blocks: 1 x 25, 28 / 4, 325 keys, six splits 8.0 / 6.1; 1 x 42, 1291 keys, 21 / 11 splits 8.3 / 7.5; 8 x 29, 8 / 2, 410 keys 7.8 / 7.1
+//   fewer than the rounds of 128 keys had: 1 x 33, 8 / 2, 2025 keys 9.8 / 8.0; 2 x 29, 1911 .. 3822 keys, 31 splits 9.6 / 8.4
+//   in place of the pipelined kernel: 4 x 21, 28 / 4, 741 keys, three splits 15.9 / 8.2; 6 x 36, 32 / 8, 297 keys 15.0 / 11.3; 8 x 34, 32 / 8 heads of
+//     64, 240 keys 12.0 / 8.8
+// Of some 110 shapes drawn from the changed calls the slowest stayed within 1 % of what it was, and the gain is a little larger with K and
+// V cold in the caches. Up to 64 tiles, as far as was measured; twelve units and more up to 24 (from there on the rule for rounds ends too).
+Plan make_plan(const vs_attn_desc* d, int tree = 1) {
+    const Plan base = plan_kernel(d, tree);
+    const int nrb = base.rows_pad / kRowBlock;
+    const int tiles = ((int64_t)d->max_prefix_len + (tree ? d->T : 0) + kIterKeys - 1) / kIterKeys;
+    const int units = d->B * d->Hkv;
+    const bool knobs = d->schedule != VS_SCHED_AUTO || d->rows_per_wave != 0 || d->waves_per_group != 0 || d->num_splits > 0;
+    if (base.impl != VS_IMPL_MFMA || knobs || base.schedule == VS_SCHED_BALANCED || nrb < 2 || (int64_t)units * nrb > 4 * kNumCUs || tiles > (units < 12 ? 64 : 24))
+        return base;
+    // (the pipelined kernel, the loops and longer rounds cost more than any of these)
+    const float keep = 0.95f; // another number of splits has to bring more than the table is good for
+    const bool same_kernel = base.res_rb > 0 && base.keys_per_split <= resident_max_keys(base.res_rb);
+    float best = same_kernel ? keep * resident_cost(base.res_rb, base.keys_per_split / kIterKeys, base.num_splits) : INFINITY;
+    Plan pl = base;
+    for (int rb = 1; rb <= 4; rb *= 2) {
+        const int groups = (nrb + rb - 1) / rb;
+        const int most = kNumCUs / (units * groups) < base.num_splits ? kNumCUs / (units * groups) : base.num_splits;
+        for (int tps = 1; tps <= resident_max_keys(rb) / kIterKeys && tps <= tiles; ++tps) {
+            if (tps * most < tiles) continue;
+            const int n = (tiles + tps - 1) / tps;
+            const float cost = (n == base.num_splits ? keep : 1.f) * resident_cost(rb, tps, n);
+            if (!(cost < best)) continue;
+            Plan c = base;
+            c.schedule = base.schedule == VS_SCHED_LOOP ? VS_SCHED_LOOP : VS_SCHED_RESIDENT;
+            c.rounds = base.schedule == VS_SCHED_LOOP;
+            c.own_tiles = 0;
+            c.rpw = 1;
+            c.waves = 8;
+            c.res_rb = rb;
+            c.row_groups = groups;
+            c.keys_per_split = tps * kIterKeys;
+            c.num_splits = n;
+            c.total_wgs = units * groups * n;
+            if (n > 1 && !merges_inside(d, c)) continue;
+            best = cost;
+            pl = c;
+        }
+    }
+    return pl;
+}
+
 int32_t draft_chunks(int32_t V) { return (int32_t)(((int64_t)V + kDraftChunk - 1) / kDraftChunk); }
 int32_t accept_chunks(int32_t V) { return (V + kAcceptChunk - 1) / kAcceptChunk; }
 
@@ -506,7 +562,9 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
                           int32_t* status, void* workspace, size_t workspace_bytes_given, void* stream) {
     const int32_t rc = check_desc(desc, tree);
     if (rc != VS_OK) return rc;
-    const Plan pl = make_plan(desc, tree);
+    Plan pl = make_plan(desc, tree);
+    // (a finer cut has more gates, 256 bytes each: with less scratch than it asks for a call runs on the other one's)
+    if (workspace_bytes_given < workspace_bytes(desc, pl)) pl = plan_kernel(desc, tree);
     if (pl.impl == VS_IMPL_MFMA && !(aligned16(q) && aligned16(k_cache) && aligned16(v_cache) && aligned16(out)))
         return VS_ERR_LAYOUT;
     const size_t need = workspace_bytes(desc, pl);
