@@ -51,7 +51,7 @@ thread_local uint32_t merge_wait = 2000;
 
 struct Plan {
     int32_t impl, rpw, waves, row_groups, rows, rows_pad, num_splits, keys_per_split, total_wgs, schedule;
-    int32_t own_tiles;  // every wave has key tiles of its own (attention_mfma_rows.hip)
+    int32_t own_tiles;  // every wave has key tiles of its own (attention_mfma_rows.hip): row blocks per workgroup, else 0
     int32_t bal_chunks; // balanced schedule: shares per (KV head, row group); num_splits = slots per KV head
     int32_t f32_rows; // fp32 storage: query rows per workgroup
     int32_t rounds; // loop schedule on the LDS-resident kernel's form: splits in rounds of 128 keys
@@ -301,18 +301,21 @@ Plan plan_kernel(const vs_attn_desc* d, int tree) {
         }
     }
     if (pl.schedule == VS_SCHED_LOOP && own_ok) {
-        pl.own_tiles = 1;
+        // One short split of two row blocks: a workgroup for each where both find a CU (smaller launches keep the plan they had). us per call, both blocks in one / one each: 16 x 9
+        // nodes, 28 / 4 heads, 291 keys 9.3 / 6.6; 25 x 9, 290 keys, paged 9.9 / 7.0; 3 x 40, 32 / 32 heads, 250 keys 9.0 / 6.5. (Long sequences are read
+        // twice then, and few of them at a time keep half as many bytes in flight: 30 x 9, 600 .. 5000 keys, cold 47.2 / 52.5.)
+        pl.own_tiles = nrb == 2 && tiles <= 5 && units0 >= 16 && 2 * units0 <= kNumCUs ? 1 : nrb;
         pl.rpw = 1;
-        pl.row_groups = 1;
+        pl.row_groups = nrb / pl.own_tiles;
         pl.waves = units0 > kNumCUs ? 4 : 8;
         splits = tiles <= 8 ? 1 : tiles / 3;
-        if (splits > kNumCUs / units0) splits = kNumCUs / units0;
+        if (splits > kNumCUs / (units0 * pl.row_groups)) splits = kNumCUs / (units0 * pl.row_groups);
         if (splits > kMergeMaxSplits) splits = kMergeMaxSplits;
         if (splits < 1) splits = 1;
         const int tps = (tiles + splits - 1) / splits;
         pl.keys_per_split = tps * kIterKeys;
         pl.num_splits = (tiles + tps - 1) / tps;
-        pl.total_wgs = units0 * pl.num_splits;
+        pl.total_wgs = units0 * pl.row_groups * pl.num_splits;
         return pl;
     }
     if (pl.schedule == VS_SCHED_LOOP && rounds_ok) {
@@ -611,7 +614,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.num_splits = pl.num_splits;
     p.keys_per_split = pl.keys_per_split;
     p.row_groups = pl.row_groups;
-    p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.res_rb ? pl.res_rb : pl.waves * pl.rpw) * kRowBlock;
+    p.rows_per_group = pl.f32_rows ? pl.f32_rows : (pl.res_rb ? pl.res_rb : pl.own_tiles ? pl.own_tiles : pl.waves * pl.rpw) * kRowBlock;
     p.total_wgs = pl.total_wgs;
     if (pl.num_splits > 0 && pl.row_groups > 0) {
         p.by_splits = fast_div_by(pl.num_splits);

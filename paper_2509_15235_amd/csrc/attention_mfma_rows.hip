@@ -62,7 +62,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
 
     // workgroup id -> (sequence, KV head, split), splits fastest; same XCD-aware remap as the other kernels. More whole
     // sequences than run at once: the longest first, dealt over the XCDs (see attention_mfma_pipe.hip).
-    int b, kvh, split = 0;
+    int b, kvh, split = 0, rg = 0; // (longest first: one row group)
     if (p.by_length) { // one split each
         if (blockIdx.x >= (uint32_t)p.total_wgs) return;
         uint32_t head;
@@ -74,7 +74,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
         b = at.b;
         kvh = at.kvh;
         split = at.split;
+        rg = at.rg;
     }
+    const int block0 = rg * RB, row0 = block0 * kRowBlock; // first row block and row of the workgroup
     const int unit = b * p.Hkv + kvh;
 
     const int32_t S = p.prefix_len[b]; // requested first, needed last: the first tiles are requested before it arrives
@@ -145,17 +147,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     // the tiles (loads return in order, and whoever waits for the queries would wait for a tile in front of them)
     constexpr int PIECES = RB * KS, QPW = (PIECES + NW - 1) / NW;
     u32x4 qreg[QPW];
-    load_q_pieces<D>(p, b, kvh, [&](int i) { return min(wave + NW * i, PIECES - 1) / KS * kRowBlock; },
+    load_q_pieces<D>(p, b, kvh, [&](int i) { return row0 + min(wave + NW * i, PIECES - 1) / KS * kRowBlock; },
                      [&](int i) { return min(wave + NW * i, PIECES - 1) % KS; }, lane, qreg);
     int node[RB];
     uint64_t mask[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        node[rb] = row_node(p, min(rb * kRowBlock + col, p.rows - 1)); // rows past the end repeat the last row
+        node[rb] = row_node(p, min(row0 + rb * kRowBlock + col, p.rows - 1)); // rows past the end repeat the last row
         mask[rb] = p.tree_mask && p.tree_keys != 0 ? p.tree_mask[(int64_t)b * p.T + node[rb]] : 0ull;
     }
     // the gate of the (sequence, KV head), opened below
-    const MergeGate gate{p.gates ? p.gates + kGateWords * (int64_t)unit : nullptr, &sgen};
+    const MergeGate gate{p.gates ? p.gates + kGateWords * ((int64_t)unit * p.row_groups + rg) : nullptr, &sgen};
     MergeSeen seen{};
     if (p.gates && wave == 0) seen = merge_look(gate);
     if (first < kend) { // uniform per wave
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
         }
     }
     const bool s_ok = prefix_ok(p, S);
-    if (kvh == 0 && split == 0) report_status(p, b, tree_code, s_ok, S, &sflag);
+    if (kvh == 0 && split == 0 && rg == 0) report_status(p, b, tree_code, s_ok, S, &sflag);
     if (tree_code != VS_STATUS_OK || !s_ok) return;
     const int nk = S + p.tree_keys;
     if (k0 >= nk) return;
@@ -378,14 +380,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
                 const u32x2 w0 = pack_partial(r[i][0], r[i][1], r[i][2], r[i][3], inv), w1 = pack_partial(r[i][4], r[i][5], r[i][6], r[i][7], inv);
                 // lane (col, half) holds, for row `col`, channels pc * 16 + 8 * {0, 1} + 4 * half + 0..3
                 if (final_rows) {
-                    if (rb * kRowBlock + col < p.rows) {
-                        uint16_t* o = (uint16_t*)p.out + row_offset(p, b, kvh, rb * kRowBlock + col, node[rb]) + pc * 16 + 4 * half;
+                    if (row0 + rb * kRowBlock + col < p.rows) {
+                        uint16_t* o = (uint16_t*)p.out + row_offset(p, b, kvh, row0 + rb * kRowBlock + col, node[rb]) + pc * 16 + 4 * half;
                         *(u32x2*)o = w0;
                         *(u32x2*)(o + 8) = w1;
                     }
                 } else {
                     const u32x4 w = {w0[0], w0[1], w1[0], w1[1]};
-                    const uint16_t* to = p.part_o + part_block<D>(p, unit, split, rb);
+                    const uint16_t* to = p.part_o + part_block<D>(p, unit, split, block0 + rb);
                     const uint32_t at = (uint32_t)(lane * 16 + pc * p.num_splits * 1024);
                     if (merge) store_piece<true>(to, at, w);
                     else store_piece<false>(to, at, w);
@@ -393,13 +395,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
             }
             if (!final_rows && wave == 0 && half == 0) {
                 const f32x2 ml = {M, l};
-                float* to = p.part_ml + ml_block(p, unit, split, rb) * 2;
+                float* to = p.part_ml + ml_block(p, unit, split, block0 + rb) * 2;
                 if (merge) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), span_of(to), col * 8, 0, kDeviceScope);
                 else *(f32x2*)(to + col * 2) = ml;
             }
         }
     }
-    if (merge) merge_splits<D>(p, gate, b, kvh, 0, RB, split, (nk + p.keys_per_split - 1) / p.keys_per_split, NW, (uint32_t*)sp);
+    if (merge) merge_splits<D>(p, gate, b, kvh, block0, block0 + RB, split, (nk + p.keys_per_split - 1) / p.keys_per_split, NW, (uint32_t*)sp);
 }
 
 template <int D, int NW, int RB>
@@ -418,8 +420,9 @@ bool attention_rows_supported(int d, int row_blocks, int waves) {
 }
 
 hipError_t launch_attention_mfma_rows(const AttnParams& p, int waves, hipStream_t s) {
-    const int blocks = p.rows_pad / kRowBlock;
-    if (p.row_groups != 1 || p.keys_per_split % kIterKeys || !attention_rows_supported(p.d, blocks, waves)) return hipErrorInvalidValue;
+    const int blocks = p.rows_per_group / kRowBlock;
+    if (p.row_groups * p.rows_per_group != p.rows_pad || (p.by_length && p.row_groups != 1)) return hipErrorInvalidValue;
+    if (p.keys_per_split % kIterKeys || !attention_rows_supported(p.d, blocks, waves)) return hipErrorInvalidValue;
     if (p.d == 128) return blocks == 2 ? launch_rows<128, 8, 2>(p, s) : waves == 8 ? launch_rows<128, 8, 1>(p, s) : launch_rows<128, 4, 1>(p, s);
     if (p.d == 64) return waves == 8 ? launch_rows<64, 8, 1>(p, s) : launch_rows<64, 4, 1>(p, s);
     return hipErrorInvalidValue;

@@ -1,5 +1,5 @@
-"""Cuts of short calls into few row blocks per workgroup of the LDS-resident kernel: every number of row blocks with every number
-of tiles, one split or several merged by their workgroups, row blocks and keys that end inside the last one, on a workspace
+"""Cuts of short calls into few row blocks per workgroup of the LDS-resident kernel, or of the one whose waves have tiles of their
+own: every number of row blocks with every number of tiles, one split or several merged by their workgroups, row blocks and keys that end inside the last one, on a workspace
 of garbage and on one without room for the gates of the finer cut."""
 import numpy as np
 import pytest
@@ -29,6 +29,8 @@ CUTS = [  # B, T, Hq, Hkv, d, keys, (row groups, keys per split, splits)
     (4, 45, 40, 8, 128, 309, (4, 192, 2)),      # three, in place of the pipelined kernel,
     (4, 39, 28, 4, 128, 601, (5, 256, 3)),      # four
     (8, 47, 40, 8, 128, 369, (2, 192, 2)),      # four row blocks in place of the pipelined kernel
+    (16, 9, 28, 4, 128, 257, (2, 320, 1)),      # one row block, tiles of the wave's own
+    (4, 40, 32, 32, 128, 320, (2, 320, 1)),
 ]
 
 
