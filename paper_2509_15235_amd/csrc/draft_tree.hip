@@ -156,11 +156,12 @@ __device__ __forceinline__ void wave_topk(const uint64_t (&key)[NE], int K, uint
     }
 }
 
-// grid = B * F * chunks, block = 512. Bound by its serial chain: a level of 2 x 8 x 152064 logits takes 12.8 us, of which the
+// grid = B * F * chunks, block = 512. Bound by its serial chain: a level of 2 x 8 x 152064 logits takes 11.0 us, of which the
 // logits are 2.5 at the rate of a large copy; bound and list of a chunk's first entries are about 2.5 us of the rest, the
 // last workgroup's part 4. One list for the whole workgroup with the K-th largest of 32 groups as its bound, sixteen keys
 // ranked a step and chunk lists of 64-bit keys took three such levels and the final selection from 43.2 to 37.8 us
-// (a list per wave, merged; value and index apart), 8 x 16 x 152064 in five levels from 238 to 192.
+// (a list per wave, merged; value and index apart), 8 x 16 x 152064 in five levels from 238 to 192; the chunk's statistics on a second
+// wave beside the ranking took the tree from 35.9 to 35.1 us, the five levels from 190 to 185.5.
 __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const DraftExpandParams p) {
     request_args(p);
     __shared__ float s_m[kExpandWaves], s_s[kExpandWaves];
