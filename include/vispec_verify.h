@@ -87,7 +87,7 @@ typedef enum vs_attn_impl { VS_IMPL_AUTO = 0, VS_IMPL_GENERIC = 1, VS_IMPL_MFMA 
  * every wave's own, for few query rows, the one that runs a split in rounds of 128 keys, and RESIDENT's for short splits of
  * few rows. Only AUTO without any other knob takes those; a descriptor that names LOOP gets the straight loop); PIPELINED overlaps the matrix-core
  * work of the neighbouring tiles with the current tile's softmax (launches with many units);
- * RESIDENT keeps a split's whole key range (at most 192 keys) in LDS and splits the
+ * RESIDENT keeps a split's whole key range (at most 192 keys, 256 with one or two row blocks to a workgroup) in LDS and splits the
  * keys once more among the waves of a workgroup (latency-bound launches with few units);
  * BALANCED is the pipelined kernel on a batch whose sequences differ in length: the kernels read
  * the prefix lengths, lay all sequences' keys end to end and give every workgroup an equal share
