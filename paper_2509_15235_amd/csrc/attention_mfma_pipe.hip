@@ -287,7 +287,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     if (kvh == 0 && k0 == 0 && rg == 0) report_status(p, b, tree_code, s_ok, S, &sflag);
     const int nk = S + p.tree_keys;
     if (tree_code != VS_STATUS_OK || !s_ok || k0 >= nk) { // uniform
-        if (BAL && DIRECT) { // other pieces follow, or merges that take the rings' place
+        if (BAL) { // other pieces follow, or merges that take the rings' place: tiles (DIRECT) and queries on their way to LDS
             wait_loads<0>();
             __syncthreads();
         }

@@ -79,3 +79,18 @@ def test_shares_with_a_malformed_tree(oracle_mod, d, Hq, Hkv, T, waves, paged):
     for b in (1, 4):
         inp.parent[b, 5] = 9
     _check(oracle_mod, inp, skip=(1, 4), schedule=vs.VS_SCHED_BALANCED, waves_per_group=waves, num_splits=7)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d,Hq,Hkv,T,waves", [(128, 4, 2, 64, 4), (64, 4, 2, 64, 4), (128, 8, 2, 64, 8)])
+def test_merges_behind_a_malformed_tree(oracle_mod, d, Hq, Hkv, T, waves, paged):
+    """Shares that begin in a sequence which they share and end in a malformed one: all waves have rows, and merge them in LDS
+    where the last piece's queries and tiles were on their way to when its tree turned out to be malformed."""
+    lens = [n for i in range(8) for n in (700 + 64 * i, 130 + i)]
+    inp = _inputs(lens, d, Hq, Hkv, T, paged, 980 + d + waves)
+    inp.parent = inp.parent.copy()
+    bad = tuple(range(1, 16, 2))
+    for b in bad:
+        inp.parent[b, 5] = 9
+    for shares in (16, 23, 41):
+        _check(oracle_mod, inp, skip=bad, schedule=vs.VS_SCHED_BALANCED, waves_per_group=waves, num_splits=shares)
