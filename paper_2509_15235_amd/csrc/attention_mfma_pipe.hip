@@ -199,7 +199,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         const int w = HALVES ? 0 : is_v;
         const bool v = HALVES ? upper : is_v;
         const uint32_t lds = (uint32_t)(uintptr_t)(lds_void*)(v ? &sV[0][0] : &sK[0][0]) + (uint32_t)(slot * SUB * 2 + block0 * 1024);
-        if constexpr (PAGED) load_to_lds<true>(lds, bt_lookup(v, decltype(full_tag)::value ? t : min(t, last)), direct_off[w]);
+        if constexpr (PAGED) load_to_lds(lds, bt_lookup(v, decltype(full_tag)::value ? t : min(t, last)), direct_off[w]);
         else load_to_lds(lds, rows[w], direct_off[w] + (uint32_t)(t * kTileKeys + RPI * block0) * stride);
     };
     // rows of V tile t (this wave's, arrived) that no key has become zeros: whatever the cache holds there, NaN included,

@@ -61,19 +61,23 @@ __device__ __forceinline__ float visible_or_inf(float s, uint32_t w, int bit) {
 // 1 KB from memory into LDS at byte `lds` (lane l's sixteen bytes at lds + 16 l), without a stop in registers. Not the
 // builtin: the compiler would make every later LDS read wait for all of these loads, not for the tile it reads. Earlier
 // LDS reads have returned before the load is issued; it has arrived after a wait for the vector-memory counter.
-// (Nothing else here uses m0.) LANE_BASE: the base comes straight from v_readlane. Between a vector instruction that writes a scalar
-// register and a load that reads it lie five wait states, which the compiler minds for instructions that it can see.
-template <bool LANE_BASE = false>
+// Five wait states lie between a vector instruction that writes a scalar register - v_readlane, the reload of a spilled one
+// too - and a load that reads it, and the compiler minds them only for instructions that it can see. So the load goes by a copy
+// made on the scalar side, which has no such rule (an s_nop 4 instead: short calls of own tiles 6.0 -> 6.1 us).
+// m0 is an operand, so the compiler knows what it holds: its own loads into LDS go by it, too. The copy is the wait state
+// that a load needs behind a write of it.
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t lane_off) {
-    if constexpr (LANE_BASE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
+    const void* at;
+    asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(at) : "{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
 }
-// the same from a bounded range: what lies outside reads as zeros
+// the same from a bounded range: what lies outside reads as zeros (four registers, two moves that nothing here can write down: five wait
+// states. 20 x 60 nodes, 16 / 16 heads of 64, 1500 keys 32.0 us with two of them, 32.3 with five)
 __device__ __forceinline__ void load_to_lds(uint32_t lds, __amdgpu_buffer_rsrc_t range, uint32_t off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(off), "s"(range) : "memory");
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds), "v"(off), "s"(range) : "memory");
 }
 __device__ __forceinline__ void load_to_lds4(uint32_t lds, const void* base, uint32_t lane_off) { // 256 bytes, four of each lane
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
+    const void* at;
+    asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0" : "=&s"(at) : "{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { // at most N of this wave's loads outstanding (they return in order)
