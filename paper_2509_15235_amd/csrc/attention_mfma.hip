@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kWave) void attn_combine_kernel(const AttnParams p)
     const int lane = threadIdx.x, col = lane & 31, half = lane >> 5;
     const int32_t S = p.prefix_len[b];
     const f32x2* gml = (const f32x2*)p.part_ml + ml_block(p, unit, 0, rbk) + col; // + split * kRowBlock
-    const uint16_t* po0 = p.part_o + part_block<D>(p, unit, 0, rbk) + (db * 2) * piece_stride(p) + lane * 8;
+    const uint16_t* po0 = p.part_o + part_block<D>(p, unit, 0, rbk) + piece_at(p, db * 2) + lane * 8;
 
     float den = 0.f, M = -INFINITY;
     f32x4 num[4];
@@ -526,9 +526,9 @@ __global__ __launch_bounds__(kWave) void attn_combine_kernel(const AttnParams p)
 #pragma unroll
         for (int u = 0; u < kCombineBatch; ++u)
             if (s0 + u < nload) {
-                const uint16_t* po = po0 + (s0 + u) * 512;
+                const uint16_t* po = po0 + (int64_t)(s0 + u) * 512;
 #pragma unroll
-                for (int hp = 0; hp < 2; ++hp) o[u][hp] = __builtin_nontemporal_load((const u32x4*)(po + hp * piece_stride(p)));
+                for (int hp = 0; hp < 2; ++hp) o[u][hp] = __builtin_nontemporal_load((const u32x4*)(po + piece_at(p, hp)));
             }
         if (s0 == 0) {
             if (!prefix_ok(p, S)) return;

@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
             }
         } else {
             const int64_t unit = (int64_t)b * p.Hkv + kvh;
-            uint16_t* po = p.part_o + part_block<D>(p, unit, split, row_base >> 5) + kq * DBW * 2 * piece_stride(p);
+            uint16_t* po = p.part_o + part_block<D>(p, unit, split, row_base >> 5) + piece_at(p, kq * DBW * 2);
 #pragma unroll
             for (int db = 0; db < DBW; ++db) {
                 if (merge) store_partial<true>(p, po, db, lane, acc[db], inv);

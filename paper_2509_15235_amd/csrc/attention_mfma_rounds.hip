@@ -446,9 +446,8 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
             for (int i = 0; i < PPK; ++i) {
                 const u32x2 w0 = pack_partial(r[i][0], r[i][1], r[i][2], r[i][3], inv), w1 = pack_partial(r[i][4], r[i][5], r[i][6], r[i][7], inv);
                 const u32x4 w = {w0[0], w0[1], w1[0], w1[1]};
-                const uint32_t at = (uint32_t)(lane * 16 + (MY * PPK + i) * p.num_splits * 1024);
-                if (merge) store_piece<true>(po, at, w);
-                else store_piece<false>(po, at, w);
+                if (merge) store_piece<true>(p, po, MY * PPK + i, lane, w);
+                else store_piece<false>(p, po, MY * PPK + i, lane, w);
             }
         }
     };

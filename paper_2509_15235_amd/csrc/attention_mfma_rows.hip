@@ -387,10 +387,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
                     }
                 } else {
                     const u32x4 w = {w0[0], w0[1], w1[0], w1[1]};
-                    const uint16_t* to = p.part_o + part_block<D>(p, unit, split, block0 + rb);
-                    const uint32_t at = (uint32_t)(lane * 16 + pc * p.num_splits * 1024);
-                    if (merge) store_piece<true>(to, at, w);
-                    else store_piece<false>(to, at, w);
+                    uint16_t* to = p.part_o + part_block<D>(p, unit, split, block0 + rb);
+                    if (merge) store_piece<true>(p, to, pc, lane, w);
+                    else store_piece<false>(p, to, pc, lane, w);
                 }
             }
             if (!final_rows && wave == 0 && half == 0) {

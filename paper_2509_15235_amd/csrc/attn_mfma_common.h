@@ -204,12 +204,12 @@ __device__ __forceinline__ f32x4 unpack_partial(u32x2 w) {
                      __uint_as_float(w[1] & 0xffff0000u)};
     return r;
 }
-// elements: piece 0 of (unit, split, row block), and from one piece to the next
+// elements: piece 0 of (unit, split, row block), and from there to another piece
 template <int D>
 __device__ __forceinline__ int64_t part_block(const AttnParams& p, int64_t unit, int split, int rbk) {
     return ((unit * (p.rows_pad / kRowBlock) + rbk) * (D / 16) * p.num_splits + split) * 512;
 }
-__device__ __forceinline__ int64_t piece_stride(const AttnParams& p) { return (int64_t)p.num_splits * 512; }
+__device__ __forceinline__ int64_t piece_at(const AttnParams& p, int piece) { return piece_elements(piece, p.num_splits); }
 
 // Partial results travel between workgroups on different XCDs: stores that write through to memory and loads
 // that do not stop at this XCD's L2 (cache policy bit sc1 = device scope).
@@ -229,11 +229,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_of(const uint16_t* slice
     return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<uint16_t*>(slice) + (int64_t)k0 * stride, 0, (int)bytes, 0x00027000);
 }
 
-// 16 bytes of a lane at byte `at` behind a uniform base. (Never with a scalar offset instead: for such stores the compiler leaves out the wait
+// A lane's 16 bytes of piece `piece`, a constant, of a partial result that begins at `blk`. MERGE: at most 128 splits (balanced slots), so one
+// base and offsets of 32 bits do. (Never a scalar offset instead: for such stores the compiler leaves out the wait
 // state that a 16-byte store needs before its data registers are written again, and later values were stored in their place.)
+// For the combine kernel a caller may have the keys in any number of splits: 64 bits.
 template <bool MERGE>
-__device__ __forceinline__ void store_piece(const uint16_t* base, uint32_t at, u32x4 w) {
-    __builtin_amdgcn_raw_buffer_store_b128(w, span_of(base), at, 0, MERGE ? kDeviceScope : 0);
+__device__ __forceinline__ void store_piece(const AttnParams& p, uint16_t* blk, int piece, int lane, u32x4 w) {
+    if constexpr (MERGE) __builtin_amdgcn_raw_buffer_store_b128(w, span_of(blk), lane * 16 + piece * p.num_splits * 1024, 0, kDeviceScope);
+    else *(u32x4*)(blk + piece_at(p, piece) + lane * 8) = w;
 }
 // One 32-channel accumulator block of a row block, divided by the rows' sums: two 16-byte pieces per
 // lane. `blk` = piece 0 of the (unit, split, row block), db = channel block.
@@ -244,7 +247,7 @@ __device__ __forceinline__ void store_partial(const AttnParams& p, uint16_t* blk
         const u32x2 lo = pack_partial(a[8 * hp], a[8 * hp + 1], a[8 * hp + 2], a[8 * hp + 3], inv);
         const u32x2 hi = pack_partial(a[8 * hp + 4], a[8 * hp + 5], a[8 * hp + 6], a[8 * hp + 7], inv);
         const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
-        store_piece<MERGE>(blk, lane * 16 + (db * 2 + hp) * p.num_splits * 1024, w);
+        store_piece<MERGE>(p, blk, db * 2 + hp, lane, w);
     }
 }
 // (max, sum) pairs are grouped per row block with the splits adjacent: index of the

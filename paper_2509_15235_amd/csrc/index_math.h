@@ -62,4 +62,8 @@ constexpr int64_t row_elements(int32_t r, int32_t node, int64_t node_stride, int
 // on its way to its first loads (a 64-bit product per row takes three more instructions).
 constexpr uint32_t row_number(int32_t r, int32_t node, int32_t skip) { return (uint32_t)node * (uint32_t)skip + (uint32_t)r; }
 
+// Elements from the first piece (512 elements) of a partial result to another one: those of all splits lie in between. 64 bits: a
+// paged cache's table can name any number of keys, and so can the splits of 64 that a caller asks for.
+constexpr int64_t piece_elements(int32_t piece, int32_t num_splits) { return (int64_t)piece * num_splits * 512; }
+
 } // namespace vs
