@@ -166,7 +166,9 @@ typedef struct vs_attn_desc {
     int32_t schedule;       /* MFMA path: vs_attn_schedule; PIPELINED needs rows_per_wave 0 or 1
                                and waves_per_group 0, 4 or 8; RESIDENT needs rows_per_wave 0 or 1 and
                                waves_per_group 0 or 8, and never puts more than 192 keys into a split
-                               (num_splits is raised where it asks for more) */
+                               (num_splits is raised where it asks for more), but for AUTO's own plan
+                               where that is RESIDENT: num_splits 0 or the plan's number gets it, with up to
+                               256 keys where a workgroup has one or two row blocks */
 } vs_attn_desc;
 
 /* What a call with this descriptor would launch (for tests and reports). */

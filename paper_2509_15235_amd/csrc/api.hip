@@ -442,7 +442,16 @@ float resident_cost(int row_blocks, int tps, int n) { return kResidentCost[row_b
 //     64, 240 keys 12.0 / 8.8
 // Of some 110 shapes drawn from the changed calls the slowest stayed within 1 % of what it was, and the gain is a little larger with K and
 // V cold in the caches. Up to 64 tiles, as far as was measured; twelve units and more up to 24 (from there on the rule for rounds ends too).
+// RESIDENT by name, with no number of splits or with the one that AUTO reports, is AUTO's plan where that is RESIDENT too: the number
+// of row blocks is no knob, and a caller who asks for the plan that was reported gets it.
 Plan make_plan(const vs_attn_desc* d, int tree = 1) {
+    if (d->schedule == VS_SCHED_RESIDENT) {
+        vs_attn_desc any = *d;
+        any.schedule = VS_SCHED_AUTO;
+        any.num_splits = any.rows_per_wave = any.waves_per_group = 0;
+        const Plan pl = make_plan(&any, tree);
+        if (pl.schedule == VS_SCHED_RESIDENT && (d->num_splits == 0 || d->num_splits == pl.num_splits)) return pl;
+    }
     const Plan base = plan_kernel(d, tree);
     const int nrb = base.rows_pad / kRowBlock;
     const int tiles = ((int64_t)d->max_prefix_len + (tree ? d->T : 0) + kIterKeys - 1) / kIterKeys;
