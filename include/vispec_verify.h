@@ -57,7 +57,8 @@ typedef enum vs_error {
     VS_ERR_NULL = -1,      /* a required pointer is NULL */
     VS_ERR_SHAPE = -2,     /* B < 1, T outside [1,64], Hq % Hkv != 0, unsupported head_dim, V < 1 ... */
     VS_ERR_DTYPE = -3,     /* dtype is neither VS_BF16 nor VS_F32 */
-    VS_ERR_WORKSPACE = -4, /* workspace NULL or smaller than *_workspace_bytes reports */
+    VS_ERR_WORKSPACE = -4, /* workspace NULL or smaller than *_workspace_bytes reports (attention: or than the coarser cut's, see
+                              vs_tree_verify_attention) */
     VS_ERR_HIP = -5,       /* the HIP runtime refused a launch */
     VS_ERR_LAYOUT = -6,    /* strides / alignment / paging parameters not supported */
     VS_ERR_NO_DEVICE = -7  /* no usable gfx950 device */
@@ -202,7 +203,11 @@ size_t vs_attention_workspace_bytes(const vs_attn_desc* desc);           /* 0 on
  *   out         [B,T,Hq,d]  out, dense
  *   status      [B] int32   out, optional
  *   workspace   device scratch of at least vs_attention_workspace_bytes(desc) bytes
- *               (may be NULL when that is 0), 256-byte aligned
+ *               (may be NULL when that is 0), 256-byte aligned.
+ *               Short calls are cut into more workgroups than the kernel's usual ones where CUs are
+ *               idle, and need up to 256 bytes more for each. With less scratch than that, but enough
+ *               for the usual cut, the call is not refused and runs on the usual one: slower, its
+ *               splits and so its roundings other than those of the plan that vs_attention_plan gives
  * bf16 MFMA path needs 16-byte aligned q/k/v/out and strides that are multiples of 8.
  */
 int32_t vs_tree_verify_attention(const vs_attn_desc* desc, const void* q, const void* k_cache,
@@ -224,7 +229,8 @@ int32_t vs_tree_verify_attention(const vs_attn_desc* desc, const void* q, const 
  *   kv_len   [B] int32   in, number of image embeddings of each image, 1 <= kv_len <= max_prefix_len;
  *            anything else is reported as VS_STATUS_BAD_PREFIX
  *   out      [B,T,Hq,d]  out, the compressed image tokens before the output projection
- *   status, workspace (vs_compress_attention_workspace_bytes), stream: as above
+ *   status, workspace (vs_compress_attention_workspace_bytes; what is said above of less scratch
+ *            holds here too), stream: as above
  * Runs the same kernels as the verification call (no tree slots, no mask).
  */
 size_t vs_compress_attention_workspace_bytes(const vs_attn_desc* desc);     /* 0 on invalid desc */
