@@ -75,7 +75,6 @@ __device__ __forceinline__ uint64_t pair_of(Best b) { return ((uint64_t)(uint32_
 // grid = B*T*chunks, block = THREADS.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const AcceptParams p) {
-    request_args(p);
     __shared__ float sv[THREADS / kWave];
     __shared__ int32_t si[THREADS / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -146,7 +145,6 @@ __device__ __forceinline__ void accept_walk(const AcceptParams& p, int b, const 
 
 // grid = B, block = 512.
 __global__ __launch_bounds__(kScanThreads) void accept_walk_kernel(const AcceptParams p) {
-    request_args(p);
     __shared__ int32_t samax[VS_MAX_TREE];
     const int b = blockIdx.x;
     int32_t parent = -2, draft = -1;
@@ -164,7 +162,6 @@ __global__ __launch_bounds__(kScanThreads) void accept_walk_kernel(const AcceptP
 // grid = B, block = 1024.
 constexpr int kSmallThreads = 1024, kSmallItems = kSmallThreads / kWave, kSmallPiece = kWave * kScanVec * 4;
 __global__ __launch_bounds__(kSmallThreads) void accept_small_kernel(const AcceptParams p) {
-    request_args(p);
     __shared__ uint64_t s_pairs[kSmallItems];
     __shared__ int32_t samax[VS_MAX_TREE];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

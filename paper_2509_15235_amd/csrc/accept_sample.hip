@@ -31,7 +31,6 @@ static_assert(kScanThreads * kPerThread == kScanChunk && kScanChunk == 1 << 13, 
 // grid = B*T*chunks, block = THREADS: (max of the raw logits, sum of 2^((l - max) * k)) of a chunk, k = log2(e) / temperature.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS, 8) void softmax_stats_partial_kernel(const SampleParams p) {
-    request_args(p);
     constexpr int kWaves = THREADS / kWave;
     __shared__ float sred[2][kWaves];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -73,7 +72,6 @@ __global__ __launch_bounds__(THREADS, 8) void softmax_stats_partial_kernel(const
 // needed - from the copy of all rows' chunk statistics in LDS when those fit, else from memory. A chunk is 2^SHIFT logits.
 template <int SHIFT>
 __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const SampleParams p) {
-    request_args(p);
     __shared__ float sred[kScanWaves];
     __shared__ float sM[VS_MAX_TREE];      // row maxima
     __shared__ float sZ[VS_MAX_TREE];      // row masses relative to the maxima

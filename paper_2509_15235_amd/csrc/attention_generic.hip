@@ -10,7 +10,6 @@ namespace vs {
 // value product lane c owns channels c, c + 64, ...
 template <int D>
 __global__ __launch_bounds__(kWave) void attn_generic_kernel(const AttnParams p) {
-    request_args(p);
     constexpr int CPL = D / kWave; // channels per lane
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;

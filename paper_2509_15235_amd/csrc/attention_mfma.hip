@@ -36,7 +36,6 @@ namespace {
 
 template <int D, int RPW, int NW>
 __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const AttnParams p) {
-    request_args(p);
     constexpr int KS = D / 16;               // k-steps of the S^T product
     constexpr int DB = D / 32;               // 32-channel blocks of the output
     // Two waves per SIMD (NW == 8) share one barrier per iteration and would otherwise sit
@@ -484,7 +483,6 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const AttnParams p) 
 constexpr int kCombineBatch = 16; // splits whose partials are in flight together
 template <int D>
 __global__ __launch_bounds__(kWave) void attn_combine_kernel(const AttnParams p) {
-    request_args(p);
     constexpr int DB = D / 32;
     __shared__ __attribute__((aligned(16))) uint16_t so[kRowBlock][32 + 8];
     // Workgroup id -> (unit, row group, row block of the group, channel block), in contiguous ranges

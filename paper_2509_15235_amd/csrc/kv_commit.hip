@@ -13,7 +13,7 @@
 // A workgroup serves one sequence: it checks the path, the prefix length and (paged) the
 // block-table entries of every slot it may touch before anything moves; a sequence that
 // fails a check is reported through `status`, keeps its cache and its prefix length.
-#include "vs_device.h"
+#include "vs_internal.h"
 
 namespace vs {
 
@@ -24,7 +24,6 @@ constexpr int kCommitThreads = 256;
 constexpr int kCommitBatch = 8;
 
 __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(const CommitParams p) {
-    request_args(p);
     __shared__ int32_t spath[VS_MAX_TREE];
     __shared__ int32_t sflag;
     const int b = blockIdx.y;
