@@ -65,7 +65,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // Final rows of row block rb out of the accumulators' lanes (quad(e): this lane's channels 8 * e + 4 * half .. + 3 of its row), half of the
-    // channels at a time through this wave's eighth (quarter) of the K ring, which nobody reads behind the last tile:
+    // channels at a time through 4 KB (2 of 64 channels) of the K ring for this wave, which nobody reads behind the last tile:
     // a store of 16 bytes a lane then touches 8 lines of 128 bytes, not 32 lines in 8-byte pieces, sixteen times over.
     auto store_rows = [&](int b, int kvh, int rb, auto quad) __attribute__((always_inline)) {
         int t = threadIdx.x;
@@ -110,13 +110,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
 
     // ---- tile copies. One load instruction of a wave fetches 1 KB of consecutive memory:
     // RPI whole rows (tokens) of D channels, lane q -> row q / LPR, 16-byte chunk q % LPR, so
-    // every touched cache line is used completely. The 16-byte chunks are then scattered into
+    // every touched cache line is used completely. DIRECT: the rows lie in LDS as they are, their chunks in another order (kx,
+    // vx below), and what lies past the last valid token reads as zeros or is another row. Through registers: the chunks are scattered into
     // LDS so that the fragment reads are conflict-free; chunk c of tile row r lives at byte
     //   K: ((r/16)*DB + c/4) * 1024 + (c%4) * 256 + ((r%16) ^ 4*(c%4)) * 16
     //   V: ((r/16)*DB + c/4) * 1024 + (4*(r%16) + c%4) * 16
     // (the XOR spreads the chunks of one K row over the banks: 4-way instead of 16-way write
     // conflicts; reads of 16 rows at one chunk stay a permutation of 16 consecutive slots).
-    // Tokens past the last valid one re-read that token (finite values that get zero weight).
+    // Tokens past the last valid one re-read that token (finite values that get zero weight; paged: whatever the pool holds there, V's rows become zeros).
     constexpr int LPR = D / 8;        // lanes (16-byte chunks) per row
     constexpr int RPI = 64 / LPR;     // rows per load instruction
     static_assert(BPS * RPI == kTileKeys, "a tile is BPS blocks of RPI rows");
@@ -242,10 +243,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
     };
     const int64_t block_bytes = (int64_t)RPI * stride_tok * 2; // from one of this wave's blocks of a tile to the next
-    // The first four tiles - K(0), K(1), K(2), V(0), through register set 1 - are requested before
-    // the prefix length is known: clamped to the longest allowed sequence instead of this one (paged: to the block table), and
-    // rows that turn out to lie past the sequence's last key are zeroed when the tiles go into LDS
-    // (whatever the cache holds there, NaN included, must not meet a zero probability).
+    // The first four tiles - K(0), K(1), K(2), V(0) - are requested before the prefix length is known: up to the longest allowed
+    // sequence's end instead of this one's (paged: the block table's). Values of rows that turn out to lie past the sequence's last key
+    // become zeros in LDS (DIRECT: zero_tail) or on their way there from register set 1: whatever the cache holds there, NaN included,
+    // must not meet a zero probability.
     if constexpr (EARLY) {
         const int kend = early_end(most_keys(p), k0, klen);
         if constexpr (DIRECT) rows_up_to(kend);

@@ -16,7 +16,9 @@ CUTS = [  # B, T, Hq, Hkv, d, keys, (row groups, keys per split, splits)
     (3, 37, 32, 8, 64, 129, (5, 192, 1)),       # three,
     (1, 60, 32, 32, 128, 255, (2, 256, 1)),     # four
     (16, 28, 8, 2, 128, 250, (4, 256, 1)),
-    (8, 43, 28, 4, 128, 129, (5, 192, 1)),      # two row blocks, one split
+    (26, 37, 8, 1, 128, 39, (5, 64, 1)),        # two row blocks, one split: a tile,
+    (17, 61, 8, 1, 128, 72, (8, 128, 1)),       # two,
+    (8, 43, 28, 4, 128, 129, (5, 192, 1)),      # three, four
     (16, 31, 32, 8, 64, 256, (2, 256, 1)),
     (1, 25, 28, 4, 128, 350, (6, 64, 6)),       # one row block, splits of a tile,
     (2, 20, 28, 4, 128, 700, (5, 128, 6)),      # two,
@@ -28,7 +30,13 @@ CUTS = [  # B, T, Hq, Hkv, d, keys, (row groups, keys per split, splits)
     (2, 30, 28, 4, 128, 1000, (4, 128, 8)),     # two,
     (4, 45, 40, 8, 128, 309, (4, 192, 2)),      # three, in place of the pipelined kernel,
     (4, 39, 28, 4, 128, 601, (5, 256, 3)),      # four
-    (8, 47, 40, 8, 128, 369, (2, 192, 2)),      # four row blocks in place of the pipelined kernel
+    (8, 47, 40, 8, 128, 369, (2, 192, 2)),      # four row blocks in place of the pipelined kernel;
+    (10, 60, 28, 4, 64, 64, (4, 64, 1)),        # one split: a tile,
+    (34, 61, 8, 1, 128, 65, (4, 128, 1)),       # two,
+    (34, 62, 8, 1, 128, 134, (4, 192, 1)),      # three;
+    (11, 63, 8, 1, 128, 279, (4, 64, 5)),       # splits of a tile,
+    (11, 61, 8, 1, 128, 323, (4, 128, 3)),      # two,
+    (2, 60, 8, 1, 128, 2068, (4, 128, 17)),     # ... more than sixteen of them
     (16, 9, 28, 4, 128, 257, (2, 320, 1)),      # one row block, tiles of the wave's own
     (4, 40, 32, 32, 128, 320, (2, 320, 1)),
 ]
