@@ -56,6 +56,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     __shared__ __attribute__((aligned(1024))) uint16_t sK[NSLOT][SUB];
     __shared__ __attribute__((aligned(1024))) uint16_t sV[NSLOT][SUB];
     __shared__ int32_t sBt[DIRECT && PAGED ? NW : 1][kWave]; // block ids, see bt_advance
+    __shared__ int32_t sLen[DIRECT && !BAL ? NW : 1][kWave]; // the sequence's length, a copy for every wave
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
     __shared__ uint64_t sgen;
@@ -97,8 +98,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     // One piece of work: the rows of row group `rg` of (sequence b, KV head kvh) against the keys
     // [k0, k0 + klen) of that sequence (k0 lies inside the cache). `whole`: no other piece shares these
     // rows, they leave as final output; else as the partial result of slot `slot`.
+    // S_known: the sequence's prefix length, where the caller has read it (BAL).
     auto run_piece = [&](const int b, const int kvh, const int rg, const int k0, const int klen, const int slot,
-                         bool whole) __attribute__((always_inline)) {
+                         bool whole, const int32_t S_known) __attribute__((always_inline)) {
     int tid = threadIdx.x;
     // What depends on the lane alone is worked out for every piece: kept from one piece to the next it takes registers that the loop
     // needs. Four waves of 128 channels had 41 of them in scratch memory, and the wait for a spilled value in the
@@ -106,7 +108,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     // (8 of 1024 .. 8191 keys 159 / 147, paged 163 / 154; eight waves: no spills either, 1 %).
     if (BAL) asm volatile("" : "+v"(tid));
     const int lane = tid & 63, half = lane >> 5, col = lane & 31;
-    const int32_t S = p.prefix_len[b]; // requested first, needed last: the first tiles and the queries are requested before it arrives
+    // The prefix length is requested first and needed last: the first tiles and the queries are requested before it arrives. DIRECT: it and the
+    // first block ids come through LDS like the tiles and are waited for by counting loads, since the compiler, which does not know of loads
+    // straight into LDS - or takes those that it knows for flat ones - would wait for all of them with any of its own.
+    // (Before, the wave waited for the length, and paged for the queries, before it asked for the tiles: us per layer, 28 / 4 heads, before /
+    // so: 6 x 60 nodes, 2044 .. 4089 keys paged 33.2 / 32.3; 6 x 23, 903 .. 1806 keys 17.9 / 17.4; longer launches 0 - 1 %.)
+    int32_t S = S_known;
+    if constexpr (DIRECT && !BAL) load_to_lds4((uint32_t)(uintptr_t)(lds_void*)&sLen[wave][0], p.prefix_len + b, 0u);
+    else if constexpr (!BAL) S = p.prefix_len[b];
 
     // ---- tile copies. One load instruction of a wave fetches 1 KB of consecutive memory:
     // RPI whole rows (tokens) of D channels, lane q -> row q / LPR, 16-byte chunk q % LPR, so
@@ -170,10 +179,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         }
     };
     int32_t bt_first = 0;
-    if (PAGED) { // (with the prefix length: one trip)
+    if constexpr (PAGED && DIRECT) { // (with the prefix length: one trip)
+        load_to_lds4((uint32_t)(uintptr_t)(lds_void*)&sBt[wave][0], bt_row, bt_index(0) * 4u);
+    } else if constexpr (PAGED) {
         bt_first = bt_fetch(0);
-        if constexpr (DIRECT) load_to_lds4((uint32_t)(uintptr_t)(lds_void*)&sBt[wave][0], bt_row, bt_index(32) * 4u);
-        else bt_next = bt_fetch(32);
+        bt_next = bt_fetch(32);
     }
     auto bt_lookup = [&](bool is_v, int t) __attribute__((always_inline)) {
         const int rel = t - bt_base, w = WINS == 1 || !is_v ? 0 : 1; // rel: 0 .. 63
@@ -225,12 +235,19 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     // through a tile slot that nothing is on its way to yet. DIRECT: the last K slots from Q_K on and the last V slots from Q_V on
     constexpr int Q_K = NW == 8 ? 5 : NSLOT, Q_V = NSLOT - (NW - (NSLOT - Q_K));
     uint16_t* sq = !DIRECT ? sK[wave & (NSLOT - 1)] : wave < NSLOT - Q_K ? sK[min(Q_K + wave, NSLOT - 1)] : sV[min(Q_V + wave - (NSLOT - Q_K), NSLOT - 1)];
+    // (DIRECT: all waves, so that the loads can be counted; one without rows fetches the last one.)
     auto copy_queries = [&]() __attribute__((always_inline)) {
-        if (!wave_active) return;
-        copy_q_block<D>(p, b, kvh, row_base, sq, lane);
+        if constexpr (DIRECT) copy_q_block<D, true>(p, b, kvh, row_base, sq, lane);
+        else if (wave_active) copy_q_block<D>(p, b, kvh, row_base, sq, lane);
     };
-    if (PAGED) { // the queries while the block ids are on their way
+    if constexpr (PAGED) { // the queries while the block ids are on their way
         copy_queries();
+        if constexpr (DIRECT) {
+            wait_loads<KS>(); // all but the queries
+            bt_first = sBt[wave][lane];
+            wait_lds_reads();
+            load_to_lds4((uint32_t)(uintptr_t)(lds_void*)&sBt[wave][0], bt_row, bt_index(32) * 4u);
+        }
         bt_set(bt_first);
     }
     constexpr bool EARLY = DIRECT || !(BAL && PAGED); // registers: 4 waves of 128 channels 188 us, so 171 (8 x 60 nodes, 32 / 32 heads, 1024 .. 8191 keys)
@@ -243,12 +260,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
     };
     const int64_t block_bytes = (int64_t)RPI * stride_tok * 2; // from one of this wave's blocks of a tile to the next
-    // The first four tiles - K(0), K(1), K(2), V(0) - are requested before the prefix length is known: up to the longest allowed
-    // sequence's end instead of this one's (paged: the block table's). Values of rows that turn out to lie past the sequence's last key
-    // become zeros in LDS (DIRECT: zero_tail) or on their way there from register set 1: whatever the cache holds there, NaN included,
+    // The first four tiles - K(0), K(1), K(2), V(0) - and, DIRECT, all others that the queries leave room for are requested before
+    // the prefix length is known (BAL knows it): up to the longest allowed sequence's end instead of this one's (paged: the block
+    // table's). Values of rows that turn out to lie past the sequence's last key become zeros in LDS (DIRECT: zero_tail) or on their way there from register set 1: whatever the cache holds there, NaN included,
     // must not meet a zero probability.
     if constexpr (EARLY) {
-        const int kend = early_end(most_keys(p), k0, klen);
+        const int kend = early_end(BAL ? S_known + p.tree_keys : most_keys(p), k0, klen);
         if constexpr (DIRECT) rows_up_to(kend);
         auto load_tile_early = [&](auto is_v, int t, u32x4(&r)[BPW]) __attribute__((always_inline)) {
             const uint16_t* gbase = decltype(is_v)::value ? vbase : kbase;
@@ -264,9 +281,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         };
         if constexpr (DIRECT) {
             if (!upper) {
-                for (int t = 0; t < 3; ++t) fetch(std::false_type{}, false, t, t);
+                for (int t = 0; t < Q_K && t <= NSLOT - 2; ++t) fetch(std::false_type{}, false, t, t);
             }
-            if (!HALVES || upper) fetch(std::false_type{}, true, 0, 0);
+            if (!HALVES || upper) {
+                for (int t = 0; t < Q_V; ++t) fetch(std::false_type{}, true, t, t);
+            }
         } else {
             load_tile_early(std::false_type{}, 0, stage[1][0]);
             load_tile_early(std::false_type{}, 1, stage[1][1]);
@@ -275,23 +294,30 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         }
     }
 
-    if (!PAGED) copy_queries();
+    if constexpr (!PAGED) copy_queries();
 
     int32_t tree_code = VS_STATUS_OK;
+    const bool reports = kvh == 0 && k0 == 0 && rg == 0;
     if (p.tree_mask || p.tree_keys == 0) {
-        if (tid == 0) sflag = 0;
-        __syncthreads();
+        if (reports) {
+            if (tid == 0) sflag = 0;
+            __syncthreads();
+        }
     } else {
         tree_code = load_tree(p.parent + (int64_t)b * p.T, p.T, sp, &sflag);
     }
+    if constexpr (DIRECT && !BAL) {
+        // loads behind it: those above, the fewest of any wave
+        constexpr int TILES_K = Q_K < NSLOT - 1 ? Q_K : NSLOT - 1;
+        wait_loads<(PAGED ? 2 : 0) + KS + (HALVES ? (TILES_K < Q_V ? TILES_K : Q_V) : TILES_K + Q_V)>();
+        S = __builtin_amdgcn_readfirstlane(sLen[wave][0]);
+    }
     const bool s_ok = prefix_ok(p, S);
-    if (kvh == 0 && k0 == 0 && rg == 0) report_status(p, b, tree_code, s_ok, S, &sflag);
+    if (reports) report_status(p, b, tree_code, s_ok, S, &sflag);
     const int nk = S + p.tree_keys;
     if (tree_code != VS_STATUS_OK || !s_ok || k0 >= nk) { // uniform
-        if (BAL) { // other pieces follow, or merges that take the rings' place: tiles (DIRECT) and queries on their way to LDS
-            wait_loads<0>();
-            __syncthreads();
-        }
+        wait_loads<0>(); // tiles (DIRECT) and queries on their way to LDS
+        if (BAL) __syncthreads(); // other pieces follow, or merges that take the rings' place
         return;
     }
     if (!BAL && p.gates && nk <= klen) whole = true; // a sequence of one split has nothing to merge
@@ -386,15 +412,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         load_tile(std::false_type{}, std::false_type{}, 2, stage[1][2]);
         load_tile(std::false_type{}, std::true_type{}, 0, stage[1][3]);
     }
-    // the rest of the prologue copies: group 0 (set 0)
+    // through registers: the rest of the prologue copies, group 0 (set 0)
     if constexpr (DIRECT) {
         rows_up_to(k1);
-        if (!upper) {
-            for (int t = 3; t < Q_K && t <= NSLOT - 2; ++t) fetch(std::false_type{}, false, t, t);
-        }
-        if (!HALVES || upper) {
-            for (int t = 1; t < Q_V; ++t) fetch(std::false_type{}, true, t, t);
-        }
     } else {
         load_group(std::false_type{}, std::integral_constant<int, 0>{}, 0);
     }
@@ -911,7 +931,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
             split = at.split;
         }
         // the host keeps every split's first key below max_prefix_len + tree_keys, hence inside the cache
-        run_piece(b, kvh, rg, split * p.keys_per_split, p.keys_per_split, split, p.num_splits == 1);
+        run_piece(b, kvh, rg, split * p.keys_per_split, p.keys_per_split, split, p.num_splits == 1, 0);
     } else {
         // workgroup id -> (share, KV head, row group): the row groups of a (share, KV head) sit next to each
         // other on one XCD (they read the same keys), consecutive (share, KV head) pairs on different ones
@@ -934,9 +954,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         const int lo = __builtin_amdgcn_readlane(bounds, c);
         const int hi = c + 1 < p.bal_chunks ? __builtin_amdgcn_readlane(bounds, c + 1) : total;
         // (in LDS, every wave its own copy: registers that the loop over the tiles needs)
-        __shared__ int32_t s_start[NW][kBalMaxSeqs], s_steps[NW][kBalMaxSeqs], s_bounds[NW][kBalMaxChunks + 1];
+        __shared__ int32_t s_start[NW][kBalMaxSeqs], s_len[NW][kBalMaxSeqs], s_bounds[NW][kBalMaxChunks + 1];
         s_start[wave][lane] = start;
-        s_steps[wave][lane] = steps;
+        s_len[wave][lane] = S;
         s_bounds[wave][lane] = lane < p.bal_chunks ? bounds : total;
         if (lane == 0) s_bounds[wave][kBalMaxChunks] = total;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by all lanes of this wave
@@ -946,11 +966,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         if (has_rows && ((shared >> lane) & 1)) arrival_open(words + lane, seen);
         for (uint64_t left = pieces; left != 0; left &= left - 1) { // in the order of the line
             const int i = __builtin_ctzll(left);
-            const int s0 = __builtin_amdgcn_readfirstlane(s_start[wave][i]), t = __builtin_amdgcn_readfirstlane(s_steps[wave][i]);
+            const int len = __builtin_amdgcn_readfirstlane(s_len[wave][i]);
+            const int s0 = __builtin_amdgcn_readfirstlane(s_start[wave][i]), t = bal_steps(p, len);
             int t0, t1;
             bal_piece(lo, hi, s0, t, t0, t1);
             __syncthreads(); // the previous piece's last reads of the tile rings, the tree and the flag
-            run_piece(i, kvh, rg, t0 * kIterKeys, (t1 - t0) * kIterKeys, c + i, ((shared >> i) & 1) == 0);
+            run_piece(i, kvh, rg, t0 * kIterKeys, (t1 - t0) * kIterKeys, c + i, ((shared >> i) & 1) == 0, len);
         }
         if (shared == 0 || !has_rows) return;
 
@@ -962,7 +983,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         asm volatile("" : "+v"(tid));
         const int ln = tid & 63;
         auto shares_of = [&](int i) __attribute__((always_inline)) { // the shares that hold pieces of sequence i
-            const int s0 = __builtin_amdgcn_readfirstlane(s_start[wave][i]), t = __builtin_amdgcn_readfirstlane(s_steps[wave][i]);
+            const int s0 = __builtin_amdgcn_readfirstlane(s_start[wave][i]), t = bal_steps(p, __builtin_amdgcn_readfirstlane(s_len[wave][i]));
             int t0, t1;
             return __ballot(ln < p.bal_chunks && bal_piece(s_bounds[wave][ln], s_bounds[wave][ln + 1], s0, t, t0, t1));
         };

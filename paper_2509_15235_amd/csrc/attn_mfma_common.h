@@ -75,6 +75,10 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint
 __device__ __forceinline__ void load_to_lds(uint32_t lds, __amdgpu_buffer_rsrc_t range, uint32_t off) {
     asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds), "v"(off), "s"(range) : "memory");
 }
+// the same from every lane's own address (in vector registers; one wait state for m0)
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const void* lane_at) {
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(lds), "v"(lane_at) : "memory");
+}
 __device__ __forceinline__ void load_to_lds4(uint32_t lds, const void* base, uint32_t lane_off) { // 256 bytes, four of each lane
     const void* at;
     asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0" : "=&s"(at) : "{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
@@ -128,7 +132,8 @@ __device__ __forceinline__ int64_t row_offset(const AttnParams& p, int b, int kv
 // The sequence of rank `rank` when the longest come first (at most 64 sequences, a lane each; out-of-range lengths sort
 // like any other). The whole wave calls it.
 __device__ __forceinline__ int sequence_by_rank(const AttnParams& p, int rank, int lane) {
-    const int len = lane < p.B ? p.prefix_len[lane] : INT32_MIN;
+    int len = lane < p.B ? p.prefix_len[lane] : INT32_MIN;
+    asm volatile("" : "+v"(len)); // waited for here, not where its register is used again, with other loads on their way
     int above = 0; // sequences that come before this lane's
     for (int i = 0; i < p.B; ++i) {
         const int li = __builtin_amdgcn_readlane(len, i);
@@ -162,7 +167,8 @@ __device__ __forceinline__ void store_q_piece(uint16_t* sq, u32x4 v, int i, int 
 }
 // All pieces of a row block without a stop in registers: the fetching lanes take the chunks in the order they are stored in.
 // `sq` is uniform; the pieces have arrived after a wait for the vector-memory counter.
-template <int D>
+// COUNTED: loads that the compiler does not know of, for whoever waits for them by counting.
+template <int D, bool COUNTED = false>
 __device__ __forceinline__ void copy_q_block(const AttnParams& p, int b, int kvh, int row_base, uint16_t* sq, int lane) {
     constexpr int LPR = D / 8, RPI = 64 / LPR, N = D / 16;
     const char* first = (const char*)((const uint16_t*)p.q + row_start<D>(p, b, kvh));
@@ -171,8 +177,11 @@ __device__ __forceinline__ void copy_q_block(const AttnParams& p, int b, int kvh
     for (int i = 0; i < N; ++i) r[i] = min(row_base + RPI * i + lane / LPR, p.rows - 1);
     row_nodes(p, r, node);
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-        __builtin_amdgcn_global_load_lds((const uint16_t*)row_at<D>(p, first + ((lane % LPR) ^ ((RPI * i + lane / LPR) % LPR)) * 16, r[i], node[i]), (lds_void*)(sq + i * 512), 16, 0, 0);
+    for (int i = 0; i < N; ++i) {
+        const char* at = row_at<D>(p, first + ((lane % LPR) ^ ((RPI * i + lane / LPR) % LPR)) * 16, r[i], node[i]);
+        if constexpr (COUNTED) load_to_lds((uint32_t)(uintptr_t)(lds_void*)(sq + i * 512), at);
+        else __builtin_amdgcn_global_load_lds((const uint16_t*)at, (lds_void*)(sq + i * 512), 16, 0, 0);
+    }
 }
 template <int D>
 __device__ __forceinline__ bf16x8 read_q_frag(const uint16_t* sq, int ks, int col, int half) {
@@ -508,8 +517,9 @@ constexpr int kBalPieceCost = 6;
 constexpr int kBalSnap = 3; // no piece this short (in steps) is left behind at a sequence's end
 
 // this lane's sequence (of prefix length S; -1: none): its first step on the line and its number of steps (0: not usable)
+__device__ __forceinline__ int bal_steps(const AttnParams& p, int32_t S) { return (S + p.tree_keys + kIterKeys - 1) / kIterKeys; } // of a usable one
 __device__ __forceinline__ void bal_scan(const AttnParams& p, int32_t S, int& start, int& steps, int& total) {
-    steps = prefix_ok(p, S) ? (S + p.tree_keys + kIterKeys - 1) / kIterKeys : 0;
+    steps = prefix_ok(p, S) ? bal_steps(p, S) : 0;
     const int inc = wave_scan(steps);
     start = inc - steps;
     total = __builtin_amdgcn_readlane(inc, 63);
