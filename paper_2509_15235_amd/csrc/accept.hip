@@ -33,13 +33,6 @@ __device__ __forceinline__ void take(Best& b, float v, int32_t i) {
     }
 }
 
-__device__ __forceinline__ Best wave_best(Best b) {
-    return wave_all(b, [](Best x, Best y) {
-        take(x, y.v, y.i);
-        return x;
-    });
-}
-
 constexpr int kRowThreads = kScanThreads / VS_MAX_TREE; // threads of the walk that share a row's chunks
 static_assert(kRowThreads == 8, "three steps of a butterfly");
 
@@ -64,11 +57,8 @@ __device__ __forceinline__ Best chunk_best(const ScanChunk& c, int chunk, int ti
     }
     // a left-to-right '>' scan never displaces a NaN in column 0
     const float first = c.nvec > 0 ? c.a[0][0] : c.tail;
-    if (chunk == 0 && tid == 0 && first != first) {
-        m = INFINITY;
-        idx = 0;
-    }
-    return wave_best({m, idx}); // lanes without the wave's maximum keep INT32_MAX and lose the tie
+    if (__any(chunk == 0 && tid == 0 && first != first)) return {INFINITY, 0};
+    return {m, wave_min(idx)}; // lanes without the wave's maximum have INT32_MAX
 }
 __device__ __forceinline__ uint64_t pair_of(Best b) { return ((uint64_t)(uint32_t)b.i << 32) | __float_as_uint(b.v); }
 

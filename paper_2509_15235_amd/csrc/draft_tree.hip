@@ -36,15 +36,6 @@ __device__ __forceinline__ bool before(float av, int32_t ai, float bv, int32_t b
 
 constexpr int kGroups = kExpandThreads / 16; // rows of lanes of a workgroup
 static_assert(kMaxDraftK <= kGroups && kGroups == 32, "K groups, a lane each");
-// maximum over the 16 lanes of a row, in all of them (the first steps of wave_max, in another order)
-__device__ __forceinline__ float group_max(float x) {
-    auto with = [](float v, uint32_t u) __attribute__((always_inline)) { return fmaxf(v, __uint_as_float(u)); };
-    x = with(x, dpp<kDppXor8>(__float_as_uint(x)));
-    x = with(x, dpp<kDppXor7>(dpp<kDppXor3>(__float_as_uint(x))));
-    x = with(x, dpp<kDppXor2>(__float_as_uint(x)));
-    return with(x, dpp<kDppXor1>(__float_as_uint(x)));
-}
-
 constexpr int kCandCap = 128;        // entries of a wave's candidate list in LDS
 constexpr int kListPad = 16, kListLen = kCandCap + kListPad;
 
@@ -72,7 +63,7 @@ __device__ __forceinline__ int32_t entry_index(uint64_t k) { return (int32_t)~(u
 __device__ __forceinline__ uint32_t kth_bound(uint32_t key, int K) {
     auto reach = [&](uint32_t k) __attribute__((always_inline)) { return (int)__popcll(__ballot(key >= k)); };
     if (reach(1) < K) return 0;
-    uint32_t hi = wave_all(key, [](uint32_t a, uint32_t b) { return max(a, b); }), lo = 0;
+    uint32_t hi = wave_max(key), lo = 0;
     int n = kWave; // lanes that reach lo
     for (uint32_t step = 1u << 23; hi > step; step <<= 2) {
         const int c = reach(hi - step);
@@ -216,10 +207,10 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         float own = ev[0];
 #pragma unroll
         for (int q = 1; q <= 4 * kVec; ++q) own = fmaxf(own, ev[q]);
-        float m = group_max(own); // of the lane's row of 16
+        float m = row_max(own); // of the group
         if ((lane & 15) == 0) s_group[tid >> 4] = ((m == m ? order_key(m) : 0) & ~(kGroups - 1u)) | (tid >> 4); // all different
         if (!one_wave) {
-            m = wave_max(m);
+            m = max_of_rows(m);
             float s = 0.f;
             if (m > -INFINITY) {
 #pragma unroll

@@ -102,33 +102,67 @@ __device__ __forceinline__ T wave_all(T x, Op op) {
     join();
     return __builtin_bit_cast(T, w);
 }
-__device__ __forceinline__ float wave_max(float x) {
-    return wave_all(x, [](float a, float b) { return fmaxf(a, b); });
+// For 32-bit words and one operation of the vector ALU a step within rows of sixteen lanes is one instruction that reads its own register from
+// other lanes. (The compiler makes five of it: a copy, the wait states, a move between lanes, and for fmaxf one that quiets NaNs.) It
+// is written down, so the wait states in front of it are, too; x has not come straight from a matrix instruction. All lanes take part.
+#define VS_LANE_STEP(OP, X, LANES) asm("s_nop 1\n\t" OP " %0, %0, %0 " LANES " bank_mask:0xf" : "+v"(X))
+#define VS_ROW_ALL(OP, X)                                   \
+    VS_LANE_STEP(OP, X, "quad_perm:[1,0,3,2] row_mask:0xf"); \
+    VS_LANE_STEP(OP, X, "quad_perm:[2,3,0,1] row_mask:0xf"); \
+    VS_LANE_STEP(OP, X, "row_half_mirror row_mask:0xf");     \
+    VS_LANE_STEP(OP, X, "row_mirror row_mask:0xf")
+// across the four rows, `op` of two registers
+template <typename T, typename Op>
+__device__ __forceinline__ T rows_all(T x, Op op) {
+    u32x2 r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    x = op(__builtin_bit_cast(T, (uint32_t)r[0]), __builtin_bit_cast(T, (uint32_t)r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    return op(__builtin_bit_cast(T, (uint32_t)r[0]), __builtin_bit_cast(T, (uint32_t)r[1]));
 }
+// fmaxf without quieting its operands first (the instruction does)
+__device__ __forceinline__ float max_of(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// the maximum of the lane's row of sixteen, in all of them; then of the rows
+__device__ __forceinline__ float row_max(float x) {
+    VS_ROW_ALL("v_max_f32_dpp", x);
+    return x;
+}
+__device__ __forceinline__ float max_of_rows(float x) { return rows_all(x, max_of); }
+__device__ __forceinline__ float wave_max(float x) { return max_of_rows(row_max(x)); }
 __device__ __forceinline__ float wave_sum(float x) {
-    return wave_all(x, [](float a, float b) { return a + b; });
+    VS_ROW_ALL("v_add_f32_dpp", x);
+    return rows_all(x, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ int32_t wave_max(int32_t x) {
-    return wave_all(x, [](int32_t a, int32_t b) { return max(a, b); });
+    VS_ROW_ALL("v_max_i32_dpp", x);
+    return rows_all(x, [](int32_t a, int32_t b) { return max(a, b); });
 }
 __device__ __forceinline__ int32_t wave_min(int32_t x) {
-    return wave_all(x, [](int32_t a, int32_t b) { return min(a, b); });
+    VS_ROW_ALL("v_min_i32_dpp", x);
+    return rows_all(x, [](int32_t a, int32_t b) { return min(a, b); });
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+    VS_ROW_ALL("v_max_u32_dpp", x);
+    return rows_all(x, [](uint32_t a, uint32_t b) { return max(a, b); });
 }
 
-// Sum of the lanes up to and including one's own (DPP: within rows of sixteen, then across them). T: 32 bits.
-template <typename T>
-__device__ __forceinline__ T wave_scan(T x) {
-    auto add = [](T v, uint32_t u) __attribute__((always_inline)) { return v + __builtin_bit_cast(T, u); };
-    auto shifted = [](T v, auto ctrl, auto rows) __attribute__((always_inline)) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int32_t, v), decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
-    };
-    using std::integral_constant;
-    x = add(x, shifted(x, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{})); // row_shr 1, 2, 4, 8
-    x = add(x, shifted(x, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{}));
-    x = add(x, shifted(x, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{}));
-    x = add(x, shifted(x, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{}));
-    x = add(x, shifted(x, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{})); // row_bcast 15 into rows 1 and 3
-    x = add(x, shifted(x, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{})); // row_bcast 31 into rows 2 and 3
+// Sum of the lanes up to and including one's own: within rows of sixteen (lanes without a lane to read from keep theirs), then across them.
+#define VS_SCAN(OP, X)                                 \
+    VS_LANE_STEP(OP, X, "row_shr:1 row_mask:0xf");      \
+    VS_LANE_STEP(OP, X, "row_shr:2 row_mask:0xf");      \
+    VS_LANE_STEP(OP, X, "row_shr:4 row_mask:0xf");      \
+    VS_LANE_STEP(OP, X, "row_shr:8 row_mask:0xf");      \
+    VS_LANE_STEP(OP, X, "row_bcast:15 row_mask:0xa");   \
+    VS_LANE_STEP(OP, X, "row_bcast:31 row_mask:0xc")
+__device__ __forceinline__ float wave_scan(float x) {
+    VS_SCAN("v_add_f32_dpp", x);
+    return x;
+}
+__device__ __forceinline__ int32_t wave_scan(int32_t x) {
+    VS_SCAN("v_add_u32_dpp", x);
     return x;
 }
 
