@@ -491,7 +491,16 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     return pl;
 }
 
-int32_t draft_chunks(int32_t V) { return (int32_t)(((int64_t)V + kDraftChunk - 1) / kDraftChunk); }
+int32_t draft_chunks(int32_t V, int32_t vec) { return (int32_t)(((int64_t)V + vec * kDraftVec - 1) / (vec * kDraftVec)); }
+// Chunks of 8192 logits; of 10240 or 12288 where those of 8192 are more workgroups than there are CUs and these are not: the CUs with
+// two of them hold up the sequence's last part. us, three levels and the selection, chunks of 8192 / chosen so:
+//   2 x 8 x 152064 34.6 / 33.2, 3 x 8 x 98304 32.1 / 31.9, 5 x 8 x 60000 31.1 / 30.4, 8 x 8 x 36000 31.4 / 30.6, 8 x 8 x 45000 32.1 / 31.8,
+//   1 x 16 x 180000 52.7 / 48.3
+int32_t draft_vec(int32_t V, int64_t rows) {
+    for (int32_t vec = 4; vec <= 6; ++vec)
+        if (rows * draft_chunks(V, vec) <= kNumCUs) return vec;
+    return 4;
+}
 int32_t accept_chunks(int32_t V) { return (V + kAcceptChunk - 1) / kAcceptChunk; }
 
 } // namespace
@@ -794,7 +803,8 @@ int32_t vs_draft_expand(const float* logits, int64_t ld_logits, int32_t V, const
     p.cand_parent = cand_parent;
     p.next_frontier_cand = next_frontier_cand;
     p.next_cum = next_cum;
-    p.chunks = draft_chunks(V);
+    p.vec = draft_vec(V, (int64_t)B * F);
+    p.chunks = draft_chunks(V, p.vec);
     p.by_chunks = fast_div_by(p.chunks);
     p.by_F = fast_div_by(F);
     p.by_K = fast_div_by(K);

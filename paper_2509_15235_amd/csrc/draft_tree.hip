@@ -23,11 +23,10 @@ namespace vs {
 
 namespace {
 
-constexpr int kVec = 4;          // 16-byte loads per thread and chunk
 constexpr int kSelThreads = 256;
 constexpr int kExpandThreads = 512;
 constexpr int kExpandWaves = kExpandThreads / kWave;
-static_assert(kDraftChunk == kExpandThreads * kVec * 4, "a chunk is one set of loads");
+static_assert(kDraftVec == kExpandThreads * 4, "a load of every thread");
 
 // a comes strictly before b in (value descending, index ascending)
 __device__ __forceinline__ bool before(float av, int32_t ai, float bv, int32_t bi) {
@@ -153,8 +152,10 @@ __device__ __forceinline__ void wave_topk(const uint64_t (&key)[NE], int K, uint
 // ranked a step and chunk lists of 64-bit keys took three such levels and the final selection from 43.2 to 37.8 us
 // (a list per wave, merged; value and index apart), 8 x 16 x 152064 in five levels from 238 to 192; the chunk's statistics on a second
 // wave beside the ranking took the tree from 35.9 to 35.1 us, the five levels from 190 to 185.5.
+template <int VEC>
 __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const DraftExpandParams p) {
     request_args(p);
+    constexpr int CHUNK = VEC * kDraftVec;
     __shared__ float s_m[kExpandWaves], s_s[kExpandWaves];
     __shared__ __attribute__((aligned(16))) uint64_t s_list[kExpandWaves * kListLen];
     __shared__ uint64_t s_wave[kExpandWaves * kMaxDraftK];
@@ -175,27 +176,27 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         uint64_t seen = 0;
         if (wave == 0) seen = load_device(arrivals); // ahead of the logits: loads return in order
         const float* __restrict__ lg = p.logits + row * p.ld;
-        const int begin = chunk * kDraftChunk;
-        const int end = min(p.V, begin + kDraftChunk);
-        // every thread holds 16 entries and perhaps one of the up to three behind the last four; a chunk of at most 1024
+        const int begin = chunk * CHUNK;
+        const int end = min(p.V, begin + CHUNK);
+        // every thread holds 4 * VEC entries and perhaps one of the up to three behind the last four; a chunk of at most 256 * VEC
         // entries (the last of a row) lies in the first wave alone
         const int nvec = (end - begin) >> 2;
-        const bool one_wave = nvec <= kWave * kVec;
+        const bool one_wave = nvec <= kWave * VEC;
         const int stride = one_wave ? kWave : kExpandThreads, nmine = one_wave && wave != 0 ? 0 : nvec;
-        float ev[4 * kVec + 1];
+        float ev[4 * VEC + 1];
 #pragma unroll
-        for (int j = 0; j < kVec; ++j) {
+        for (int j = 0; j < VEC; ++j) {
             const int k = tid + j * stride;
             const f32x4 x = (k < nmine) ? load4_stream(lg + begin + 4 * k) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
             for (int e = 0; e < 4; ++e) ev[4 * j + e] = x[e];
         }
         const int tail = begin + 4 * nvec + tid;
-        ev[4 * kVec] = tail < end ? lg[tail] : -INFINITY;
+        ev[4 * VEC] = tail < end ? lg[tail] : -INFINITY;
         auto key_of = [&](int e) __attribute__((always_inline)) { // of ev[e]
             const int k = tid + (e >> 2) * stride;
-            const bool has = e == 4 * kVec ? tail < end : k < nmine;
-            return has ? child_key(ev[e], e == 4 * kVec ? tail : begin + 4 * k + (e & 3)) : 0;
+            const bool has = e == 4 * VEC ? tail < end : k < nmine;
+            return has ? child_key(ev[e], e == 4 * VEC ? tail : begin + 4 * k + (e & 3)) : 0;
         };
         if (tid == 0) {
             arrival_open(arrivals, seen);
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         // the maxima of 32 groups of 256 entries is a bound that K entries reach and few others do
         float own = ev[0];
 #pragma unroll
-        for (int q = 1; q <= 4 * kVec; ++q) own = fmaxf(own, ev[q]);
+        for (int q = 1; q <= 4 * VEC; ++q) own = fmaxf(own, ev[q]);
         float m = row_max(own); // of the group
         if ((lane & 15) == 0) s_group[tid >> 4] = ((m == m ? order_key(m) : 0) & ~(kGroups - 1u)) | (tid >> 4); // all different
         if (!one_wave) {
@@ -214,17 +215,17 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
             float s = 0.f;
             if (m > -INFINITY) {
 #pragma unroll
-                for (int q = 0; q <= 4 * kVec; ++q) s += __builtin_amdgcn_exp2f((ev[q] - m) * 1.4426950408889634f); // exp2(-inf) = 0
+                for (int q = 0; q <= 4 * VEC; ++q) s += __builtin_amdgcn_exp2f((ev[q] - m) * 1.4426950408889634f); // exp2(-inf) = 0
             }
             s = wave_sum(s);
             if (lane == 0) {
                 s_m[wave] = m;
                 s_s[wave] = s;
             }
-        } else if (wave == 0 || wave >= kVec) { // the same sums as of a long chunk: those of four waves
+        } else if (wave == 0 || wave >= VEC) { // the same sums as of a long chunk: those of VEC waves
 #pragma unroll
-            for (int j = 0; j < kVec; ++j) {
-                const float last = j == 0 ? ev[4 * kVec] : -INFINITY;
+            for (int j = 0; j < VEC; ++j) {
+                const float last = j == 0 ? ev[4 * VEC] : -INFINITY;
                 const float mj = wave_max(fmaxf(fmaxf(fmaxf(ev[4 * j], ev[4 * j + 1]), fmaxf(ev[4 * j + 2], ev[4 * j + 3])), last));
                 float s = 0.f;
                 if (mj > -INFINITY) {
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
                 if (tid == 0) s_n = kCandCap + 1;
             } else if (own >= tau) { // few lanes
 #pragma unroll
-                for (int e = 0; e <= 4 * kVec; ++e)
+                for (int e = 0; e <= 4 * VEC; ++e)
                     if (ev[e] >= tau) {
                         const int at = atomicAdd(&s_n, 1); // the order of the list does not matter
                         if (at < kCandCap) s_list[at] = key_of(e);
@@ -265,9 +266,9 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         }
         const int n = s_n;
         auto topk_own = [&](uint64_t* list, auto emit) __attribute__((always_inline)) {
-            uint64_t key[4 * kVec + 1];
+            uint64_t key[4 * VEC + 1];
 #pragma unroll
-            for (int e = 0; e <= 4 * kVec; ++e) key[e] = key_of(e);
+            for (int e = 0; e <= 4 * VEC; ++e) key[e] = key_of(e);
             wave_topk(key, K, list, emit);
         };
         if (n > kCandCap) { // a plateau of equal values: every wave's first K, then those of all
@@ -616,7 +617,11 @@ __global__ __launch_bounds__(kSelThreads) void draft_tree_build_kernel(const Dra
 } // namespace
 
 hipError_t launch_draft_expand(const DraftExpandParams& p, hipStream_t s) {
-    hipLaunchKernelGGL(draft_expand_kernel, dim3((unsigned)((int64_t)p.chunks * p.B * p.F)), dim3(kExpandThreads), 0, s, p);
+    const dim3 grid((unsigned)((int64_t)p.chunks * p.B * p.F)), block(kExpandThreads);
+    if (p.vec == 4) hipLaunchKernelGGL(draft_expand_kernel<4>, grid, block, 0, s, p);
+    else if (p.vec == 5) hipLaunchKernelGGL(draft_expand_kernel<5>, grid, block, 0, s, p);
+    else if (p.vec == 6) hipLaunchKernelGGL(draft_expand_kernel<6>, grid, block, 0, s, p);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -118,7 +118,7 @@ struct SampleParams {
     FastDiv by_chunks;
 };
 
-constexpr int kDraftChunk = 8192;     // floats of a logits row per workgroup of an expansion: 512 threads x 4 x 16 bytes
+constexpr int kDraftVec = 2048;       // floats of a logits row per 16-byte load of an expansion's workgroup: 512 threads
 constexpr int kArrivalWords = 16;     // 64-bit words from one arrival counter to the next: a cache line
 constexpr int kMaxDraftK = 16;        // children per frontier node
 constexpr int kMaxDraftCand = 1024;   // F * K candidates of one expansion step
@@ -142,6 +142,7 @@ struct DraftExpandParams {
     uint64_t* arrivals;           // a word per sequence, kArrivalWords apart
     int32_t chunks;
     FastDiv by_chunks, by_F, by_K;
+    int32_t vec;                  // loads per thread: a chunk is vec * kDraftVec logits (4, 5 or 6)
 };
 
 struct DraftBuildParams {

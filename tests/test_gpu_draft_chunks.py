@@ -21,6 +21,16 @@ def test_last_chunk(gu, oracle_mod, V, K):
     _check_build(gu, oracle_mod, dd, 20)
 
 
+@pytest.mark.parametrize("B,K,V", [
+    (3, 16, 4 * 10240 + 1283), (3, 16, 4 * 10240 + 1284), (3, 16, 5 * 10240),     # the second level's 48 rows: chunks of 10240 logits
+    (5, 8, 5 * 12288 + 1539), (5, 8, 5 * 12288 + 1540), (5, 8, 5 * 12288 + 1),    # ... 40 rows: chunks of 12288
+    (1, 7, 33 * 8192 - 5), (1, 9, 17 * 8192 + 2), (2, 1, 30000),                  # more lists than are on their way at once; lists of one
+])
+def test_long_chunks(gu, oracle_mod, B, K, V):
+    dd = _grow_both(gu, oracle_mod, 330 + K, B, V, K, 2)
+    _check_build(gu, oracle_mod, dd, min(40, K + K * K))
+
+
 @pytest.mark.parametrize("V,count", [(8192, 127), (8192, 128), (8192, 129), (1000, 129), (9000, 8192)])
 def test_plateaus(gu, oracle_mod, V, count):
     """`count` equal maxima in the first chunk: around the list's 128 entries."""
