@@ -146,12 +146,143 @@ __device__ __forceinline__ void wave_topk(const uint64_t (&key)[NE], int K, uint
     }
 }
 
-// grid = B * F * chunks, block = 512. Bound by its serial chain: a level of 2 x 8 x 152064 logits takes 11.0 us, of which the
-// logits are 2.5 at the rate of a large copy; bound and list of a chunk's first entries are about 2.5 us of the rest, the
-// last workgroup's part 4. One list for the whole workgroup with the K-th largest of 32 groups as its bound, sixteen keys
-// ranked a step and chunk lists of 64-bit keys took three such levels and the final selection from 43.2 to 37.8 us
-// (a list per wave, merged; value and index apart), 8 x 16 x 152064 in five levels from 238 to 192; the chunk's statistics on a second
-// wave beside the ranking took the tree from 35.9 to 35.1 us, the five levels from 190 to 185.5.
+// ---- Sorted lists side by side: every P lanes (8 or 16) of a register hold a list of P keys, largest first, zeros behind the last one. The P
+// largest of two such lists are the larger ones of a[i] and b[P - 1 - i], which rise and fall once and so are sorted by log2 P steps of
+// comparing with the lane at distance P / 2 .. 1. A step is six to eight instructions without a branch, so 16 lists of 8 become one
+// in 0.4 us; bound, list in LDS and ranks (wave_topk) took 1.3.
+template <int CTRL>
+__device__ __forceinline__ uint64_t lanes_of(uint64_t x) { // every lane has a lane to read from
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, CTRL, 0xf, 0xf, true), hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, true);
+    return ((uint64_t)hi << 32) | lo;
+}
+template <int D>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t x) {
+    if constexpr (D == 1) return lanes_of<kDppXor1>(x);
+    else if constexpr (D == 2) return lanes_of<kDppXor2>(x);
+    else if constexpr (D == 8) return lanes_of<kDppXor8>(x);
+    else { // 4: the lower quads of each eight from the upper ones and back
+        auto word = [](uint32_t w) __attribute__((always_inline)) {
+            const int up = __builtin_amdgcn_update_dpp((int)w, (int)w, 0x104, 0xf, 0x5, false); // row_shl:4
+            return (uint32_t)__builtin_amdgcn_update_dpp(up, (int)w, 0x114, 0xf, 0xa, false);   // row_shr:4
+        };
+        return ((uint64_t)word((uint32_t)(x >> 32)) << 32) | word((uint32_t)x);
+    }
+}
+template <int D>
+__device__ __forceinline__ uint64_t sort_step(uint64_t x) {
+    const uint64_t y = lane_xor<D>(x);
+    return (y > x) != ((threadIdx.x & D) != 0) ? y : x;
+}
+template <int P>
+__device__ __forceinline__ uint64_t sort_list(uint64_t x) { // of keys that rise and fall once, or fall and rise
+    if constexpr (P == 16) x = sort_step<8>(x);
+    x = sort_step<4>(x);
+    x = sort_step<2>(x);
+    return sort_step<1>(x);
+}
+template <int P>
+__device__ __forceinline__ uint64_t merge_lists(uint64_t a, uint64_t b) {
+    b = lanes_of<P == 8 ? 0x141 : 0x140>(b); // the list backwards: row_half_mirror, row_mirror
+    return sort_list<P>(a > b ? a : b);
+}
+// all lists of a register into one, in each of them
+template <int P>
+__device__ __forceinline__ uint64_t merge_register(uint64_t x) {
+    if constexpr (P == 8) {
+        const uint64_t y = lanes_of<0x140>(x); // the neighbouring list backwards
+        x = sort_list<8>(x > y ? x : y);
+    }
+    u32x2 lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false), hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+    x = merge_lists<P>(((uint64_t)hi[0] << 32) | lo[0], ((uint64_t)hi[1] << 32) | lo[1]);
+    lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+    return merge_lists<P>(((uint64_t)hi[0] << 32) | lo[0], ((uint64_t)hi[1] << 32) | lo[1]);
+}
+
+// What the last workgroup of a sequence asks for and makes of one frontier row, P >= K lanes to a chunk's list.
+constexpr int kRowRegs = 4; // registers of lists on their way
+struct RowInput {
+    uint64_t ms, key[kRowRegs];
+    float cum;
+};
+template <int P>
+__device__ __forceinline__ void fetch_lists(const DraftExpandParams& p, int64_t row, int c0, uint64_t (&key)[kRowRegs]) {
+    constexpr int G = kWave / P;
+    const int lane = threadIdx.x & 63, list = lane / P, r = lane % P;
+    const uint64_t* top = p.part_top + row * p.chunks * p.K;
+#pragma unroll
+    for (int q = 0; q < kRowRegs; ++q) {
+        key[q] = 0;
+        if (c0 + q * G < p.chunks) { // uniform
+            const int c = c0 + q * G + list;
+            const uint64_t k = load_device(top + min(c, p.chunks - 1) * p.K + min(r, p.K - 1));
+            key[q] = c < p.chunks && r < p.K ? k : 0;
+        }
+    }
+}
+template <int P>
+__device__ __forceinline__ RowInput row_request(const DraftExpandParams& p, int64_t row) {
+    RowInput in;
+    in.ms = load_device(p.part_ms + row * p.chunks + min((int)(threadIdx.x & 63), p.chunks - 1)); // (no branch around a load)
+    fetch_lists<P>(p, row, 0, in.key);
+    in.cum = p.cum_in ? p.cum_in[row] : 0.f;
+    return in;
+}
+// lanes 0 .. K - 1: the row's first K entries; lse: its log-sum-exp
+template <int P>
+__device__ __forceinline__ uint64_t row_top(const DraftExpandParams& p, int64_t row, RowInput in, float& lse) {
+    constexpr int G = kWave / P;
+    const int lane = threadIdx.x & 63;
+    const uint64_t* pms = p.part_ms + row * p.chunks;
+    auto max_part = [](uint64_t ms) { return __uint_as_float((uint32_t)ms); };
+    auto sum_part = [](uint64_t ms) { return __uint_as_float((uint32_t)(ms >> 32)); };
+    const float m0 = lane < p.chunks ? max_part(in.ms) : -INFINITY;
+    float m = m0;
+    for (int c = lane + kWave; c < p.chunks; c += kWave) m = fmaxf(m, max_part(load_device(pms + c)));
+    m = wave_max(m);
+    float z = (m0 > -INFINITY) ? sum_part(in.ms) * __builtin_amdgcn_exp2f((m0 - m) * 1.4426950408889634f) : 0.f;
+    for (int c = lane + kWave; c < p.chunks; c += kWave) {
+        const uint64_t ms = load_device(pms + c);
+        if (max_part(ms) > -INFINITY) z += sum_part(ms) * __builtin_amdgcn_exp2f((max_part(ms) - m) * 1.4426950408889634f);
+    }
+    lse = m + __logf(wave_sum(z));
+    uint64_t top = in.key[0];
+    for (int c0 = 0;;) {
+#pragma unroll
+        for (int q = 1; q < kRowRegs; ++q)
+            if (c0 + q * G < p.chunks) top = merge_lists<P>(top, in.key[q]);
+        c0 += kRowRegs * G;
+        if (c0 >= p.chunks) break;
+        fetch_lists<P>(p, row, c0, in.key);
+        top = merge_lists<P>(top, in.key[0]);
+    }
+    return merge_register<P>(top);
+}
+// The `keep` first of the rows' candidates in (score descending, index ascending) order, in lanes 0 .. keep - 1: their keys, 0 past the last. One
+// wave. A row's candidates stand in that order already: cum + (entry - lse) falls with the entry, equal ones come in the order of their
+// index, and NaN is the score of all of them or of the last (an infinite sum plus an entry of -inf).
+template <int P>
+__device__ __forceinline__ uint64_t frontier_top(const float* score, int F, int K) {
+    constexpr int G = kWave / P;
+    const int lane = threadIdx.x & 63, r = lane % P;
+    uint64_t top = 0;
+    for (int f0 = 0; f0 < F; f0 += G) {
+        const int f = f0 + lane / P, c = min(f, F - 1) * K + min(r, K - 1);
+        const uint64_t key = f < F && r < K ? child_key(score[c], c) : 0;
+        top = f0 == 0 ? key : merge_lists<P>(top, key);
+    }
+    return merge_register<P>(top);
+}
+
+// grid = B * F * chunks, block = 512. Bound by its serial chain. Stamps of a level of 2 x 8 x 152064 logits (us after the first wave's entry,
+// median and last): logits 0.9 / 1.3, statistics 1.7 / 2.1, bound and list 3.1 / 3.6, ranks in memory 4.0 / 4.6, last arrival known 5.7,
+// the chunks' results read 6.9, rows merged 7.7, frontier written 8.3; 1.4 between two levels. What that took before:
+//   a workgroup on every CU and two on some instead (chunks of 8192 logits): all ranks in memory at 5.8
+//   the chunks' lists and the frontier by bound, list and ranks (wave_topk) instead of merges of sorted lists: 2.0 and 1.0 instead of 0.8
+//   and 0.6, every eight rows
+// Three levels and the selection, us: 2 x 8 x 152064 35.0 -> 31.8, K = 16 64.7 -> 47.4 (1 x 16 x 152064), 8 x 10 x 32000 39.9 -> 33.7.
+// (Earlier: one list for the whole workgroup with the K-th largest of 32 groups as its bound, sixteen keys ranked a step and chunk lists
+// of 64-bit keys 43.2 -> 37.8; the chunk's statistics on a second wave beside the ranking 35.9 -> 35.1.)
 template <int VEC>
 __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const DraftExpandParams p) {
     request_args(p);
@@ -320,56 +451,25 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         par_own[i] = (c < C && p.frontier_cand) ? p.frontier_cand[(int64_t)b * F + fast_div(c, p.by_K, r)] : -1;
     }
 
-    // ---- per row: log-sum-exp and the K first entries of the merged chunk lists
-    // (chunk statistics, score and the first 256 list entries are requested before anything is used; longer
-    // lists come in further batches, the K best so far among them)
-    const int n = p.chunks * K;
-    for (int f = wave; f < F; f += kExpandWaves) {
-        const int64_t row = (int64_t)b * F + f;
-        const uint64_t* pms = p.part_ms + row * p.chunks;
-        const uint64_t* top = p.part_top + row * n;
-        constexpr int NE = 4;
-        uint64_t key[NE + 1];
-        auto fetch = [&](int e0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int q = 0; q < NE; ++q) {
-                const int e = e0 + lane + q * kWave;
-                key[q] = 0;
-                if (e0 + q * kWave < n) { // uniform
-                    const uint64_t k = load_device(top + min(e, n - 1));
-                    key[q] = e < n ? k : 0;
-                }
+    // ---- per row: log-sum-exp and the K first entries of the merged chunk lists. The next row's are asked for before the row's are used.
+    auto rows = [&](auto width) __attribute__((always_inline)) {
+        constexpr int P = decltype(width)::value;
+        RowInput in = {};
+        if (wave < F) in = row_request<P>(p, (int64_t)b * F + wave);
+        for (int f = wave; f < F; f += kExpandWaves) {
+            RowInput next = {};
+            if (f + kExpandWaves < F) next = row_request<P>(p, (int64_t)b * F + f + kExpandWaves);
+            float lse;
+            const uint64_t k = row_top<P>(p, (int64_t)b * F + f, in, lse);
+            if (lane < K) {
+                s_token[f * K + lane] = k != 0 ? entry_index(k) : INT32_MAX;
+                s_score[f * K + lane] = in.cum + ((k != 0 ? entry_value(k) : -INFINITY) - lse);
             }
-        };
-        auto max_of = [](uint64_t ms) { return __uint_as_float((uint32_t)ms); };
-        auto sum_of = [](uint64_t ms) { return __uint_as_float((uint32_t)(ms >> 32)); };
-        const uint64_t ms0 = load_device(pms + min(lane, p.chunks - 1)); // (no branch around a load)
-        fetch(0);
-        const float cum = p.cum_in ? p.cum_in[row] : 0.f;
-        const float m0 = lane < p.chunks ? max_of(ms0) : -INFINITY;
-        float m = m0;
-        for (int c = lane + kWave; c < p.chunks; c += kWave) m = fmaxf(m, max_of(load_device(pms + c)));
-        m = wave_max(m);
-        float z = (m0 > -INFINITY) ? sum_of(ms0) * __builtin_amdgcn_exp2f((m0 - m) * 1.4426950408889634f) : 0.f;
-        for (int c = lane + kWave; c < p.chunks; c += kWave) {
-            const uint64_t ms = load_device(pms + c);
-            if (max_of(ms) > -INFINITY) z += sum_of(ms) * __builtin_amdgcn_exp2f((max_of(ms) - m) * 1.4426950408889634f);
+            in = next;
         }
-        z = wave_sum(z);
-        const float lse = m + __logf(z);
-        uint64_t* const best = s_wave + wave * kMaxDraftK;
-        for (int e0 = 0; e0 < n; e0 += NE * kWave) {
-            if (e0 > 0) fetch(e0);
-            key[NE] = e0 > 0 && lane < K ? best[lane] : 0;
-            wave_topk(key, K, s_list + wave * kListLen, [&](int r, uint64_t k) { best[r] = k; });
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by other lanes of this wave
-        }
-        if (lane < K) {
-            const uint64_t k = best[lane];
-            s_token[f * K + lane] = k != 0 ? entry_index(k) : INT32_MAX;
-            s_score[f * K + lane] = cum + ((k != 0 ? entry_value(k) : -INFINITY) - lse);
-        }
-    }
+    };
+    if (K <= 8) rows(std::integral_constant<int, 8>{});
+    else rows(std::integral_constant<int, 16>{});
     __syncthreads();
 
     // ---- the candidates, and the next frontier: the `keep` first of them in (score descending, index ascending),
@@ -391,52 +491,9 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         }
         return;
     }
-    if (C <= kWave) { // one wave, a lane per candidate: rank by counting, listed in the order of the lanes
-        if (wave != 0) return;
-        const float sc = lane < C ? s_score[lane] : 0.f;
-        const uint64_t k = lane < C ? child_key(sc, lane) : 0;
-        s_list[lane] = k;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // read by all lanes of this wave
-        int rank = 0;
-#pragma unroll 8
-        for (int o = 0; o < kWave; o += 2) {
-            const u64x2 x = *(const u64x2*)&s_list[o];
-            rank += (x[0] > k ? 1 : 0) + (x[1] > k ? 1 : 0);
-        }
-        const bool kept = k != 0 && rank < keep;
-        const uint64_t mask = __ballot(kept);
-        if (kept) {
-            const int pos = __popcll(mask & ((1ull << lane) - 1ull));
-            p.next_frontier_cand[(int64_t)b * keep + pos] = p.cand_base + lane;
-            p.next_cum[(int64_t)b * keep + pos] = sc;
-        }
-        return;
-    }
-    uint64_t* const list = s_list + wave * kListLen;
-    { // every wave's share first
-        uint64_t key[CPT];
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-            const int c = tid + q * kExpandThreads;
-            key[q] = c < C ? child_key(s_score[c], c) : 0;
-        }
-        wave_topk(key, keep, list, [&](int r, uint64_t k) { s_wave[wave * kMaxDraftK + r] = k; });
-        __syncthreads();
-    }
     if (wave != 0) return;
-    {
-        constexpr int NE = kExpandWaves * kMaxDraftK / kWave;
-        uint64_t key[NE];
-#pragma unroll
-        for (int q = 0; q < NE; ++q) {
-            const int e = lane + q * kWave;
-            key[q] = (e & (kMaxDraftK - 1)) < keep ? s_wave[e] : 0;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); // the lists have been read
-        wave_topk(key, keep, list, [&](int r, uint64_t k) { s_wave[r] = k; });
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    const uint64_t k = lane < keep ? s_wave[lane] : 0;
+    const uint64_t first = K <= 8 ? frontier_top<8>(s_score, F, K) : frontier_top<16>(s_score, F, K);
+    const uint64_t k = lane < keep ? first : 0;
     const int32_t c = k != 0 ? entry_index(k) : INT32_MAX;
     int pos = 0;
     for (int o = 0; o < keep; ++o) pos += __builtin_amdgcn_readlane(c, o) < c ? 1 : 0;
