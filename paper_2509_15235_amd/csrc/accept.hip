@@ -84,18 +84,25 @@ __global__ __launch_bounds__(THREADS, 8) void argmax_partial_kernel(const Accept
 }
 
 // The walk over sequence b's tree, `pairs` its rows' (all threads of a workgroup of 512 or more). Eight threads share a row's chunks,
-// four pairs each in flight; the first wave holds the tree, a lane per node, asked for before (parent, draft).
-__device__ __forceinline__ void accept_walk(const AcceptParams& p, int b, const uint64_t* pairs, int32_t parent, int32_t draft, int32_t* samax) {
+// four pairs each in flight; the first wave holds the tree, a lane per node: asked for by `tree` behind the first pairs.
+template <typename Tree>
+__device__ __forceinline__ void accept_walk(const AcceptParams& p, int b, const uint64_t* pairs, Tree tree, int32_t* samax) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int T = p.T, i = tid / kRowThreads, sub = tid % kRowThreads;
+    int32_t parent = -2, draft = -1;
     {
         constexpr int kPre = 4;
         pairs += (int64_t)min(i, T - 1) * p.chunks;
-        Best best = {-INFINITY, INT32_MAX};
-        for (int c0 = sub; c0 < p.chunks; c0 += kRowThreads * kPre) {
-            uint64_t w[kPre];
+        uint64_t w[kPre];
+        auto fetch = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < kPre; ++q) w[q] = pairs[min(c0 + kRowThreads * q, p.chunks - 1)]; // (the last one again: no harm)
+        };
+        fetch(sub);
+        tree(parent, draft);
+        Best best = {-INFINITY, INT32_MAX};
+        for (int c0 = sub; c0 < p.chunks; c0 += kRowThreads * kPre) {
+            if (c0 != sub) fetch(c0);
 #pragma unroll
             for (int q = 0; q < kPre; ++q) take(best, __uint_as_float((uint32_t)w[q]), (int32_t)(w[q] >> 32));
         }
@@ -137,12 +144,11 @@ __device__ __forceinline__ void accept_walk(const AcceptParams& p, int b, const 
 __global__ __launch_bounds__(kScanThreads) void accept_walk_kernel(const AcceptParams p) {
     __shared__ int32_t samax[VS_MAX_TREE];
     const int b = blockIdx.x;
-    int32_t parent = -2, draft = -1;
-    if (threadIdx.x < kWave) {
+    accept_walk(p, b, p.pairs + (int64_t)b * p.T * p.chunks, [&](int32_t& parent, int32_t& draft) __attribute__((always_inline)) {
+        if (threadIdx.x >= kWave) return;
         parent = tree_lane(p.parent + (int64_t)b * p.T, p.T);
         draft = p.draft[(int64_t)b * p.T + min((int)threadIdx.x, p.T - 1)];
-    }
-    accept_walk(p, b, p.pairs + (int64_t)b * p.T * p.chunks, parent, draft, samax);
+    }, samax);
 }
 
 // Both in one for few logits: a workgroup of sixteen waves per sequence scans all of its rows, a piece of 1024 logits a wave, and
@@ -168,7 +174,10 @@ __global__ __launch_bounds__(kSmallThreads) void accept_small_kernel(const Accep
         if (lane == 0) s_pairs[wave] = pair_of(best);
     }
     __syncthreads();
-    accept_walk(p, b, s_pairs, parent, draft, samax);
+    accept_walk(p, b, s_pairs, [&](int32_t& to_parent, int32_t& to_draft) __attribute__((always_inline)) {
+        to_parent = parent;
+        to_draft = draft;
+    }, samax);
 }
 
 constexpr int kMaxDevices = 64;

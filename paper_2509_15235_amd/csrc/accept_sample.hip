@@ -84,15 +84,12 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T = p.T;
-    // the first wave holds the tree and its draws, a lane per node, asked for ahead of the statistics
-    int32_t own_parent = -2, own_token = -1;
-    float own_u = 2.f;
-    if (wave == 0) {
-        own_parent = tree_lane(p.parent + (int64_t)b * T, T);
-        own_token = p.draft[(int64_t)b * T + min(lane, T - 1)];
-        own_u = p.u_accept[(int64_t)b * T + min(lane, T - 1)];
-    }
-    const float u_bonus = p.u_bonus[b];
+    // the tree and its draws, a lane per node, asked for ahead of the statistics (by all waves, and the parents used behind those: at the end of
+    // a branch or where they are compared the compiler waits for them, before the statistics are asked for)
+    const int64_t at = (int64_t)b * T + min(lane, T - 1);
+    int32_t own_parent = p.parent[at];
+    const int32_t own_token = p.draft[at];
+    const float own_u = p.u_accept[at], u_bonus = p.u_bonus[b];
     const int ri = tid / kRowThreads, sub = tid % kRowThreads;
     const uint64_t* pairs = p.pairs + (int64_t)b * T * p.chunks;
     constexpr int kPre = 4;
@@ -102,7 +99,9 @@ __global__ __launch_bounds__(kScanThreads) void accept_sample_walk_kernel(const 
         for (int q = 0; q < kPre; ++q) w[q] = pairs[min(ri, T - 1) * p.chunks + min(c0 + kRowThreads * q, p.chunks - 1)];
     };
     fetch(sub);
+    asm volatile("" : "+v"(own_parent)::"memory"); // used from here on
     if (wave == 0) {
+        own_parent = lane < T ? own_parent : -2;
         // the candidates' logits (parent index clamped: a malformed tree is reported below and must not steer a load out of bounds)
         const bool has = lane >= 1 && lane < T && own_token >= 0 && own_token < p.V;
         float l = -INFINITY;
