@@ -57,6 +57,8 @@ struct Plan {
     int32_t rounds; // loop schedule on the LDS-resident kernel's form: splits in rounds of 128 keys
     int32_t res_rb; // resident schedule: row blocks per workgroup (4, 2 or 1)
 };
+bool merges_inside(const vs_attn_desc* d, const Plan& pl);
+int pipe_splits(const vs_attn_desc* d, Plan pl, int nrb, int waves, int tiles, bool coarse);
 
 // Shape / dtype / layout checks that need no device. Returns VS_OK or a vs_error.
 int32_t check_desc(const vs_attn_desc* d, int tree = 1) {
@@ -116,7 +118,7 @@ int32_t check_desc(const vs_attn_desc* d, int tree = 1) {
     return VS_OK;
 }
 
-Plan plan_kernel(const vs_attn_desc* d, int tree) {
+Plan plan_kernel(const vs_attn_desc* d, int tree, bool coarse) {
     Plan pl{};
     const int group = d->Hq / d->Hkv;
     pl.rows = d->T * group;
@@ -222,7 +224,12 @@ Plan plan_kernel(const vs_attn_desc* d, int tree) {
     // - / 89 / 68, 2750 .. 5500 - / 101 / 91, all of 5500 - / 112 / 118; 33 x 11, 1000 .. 8000 - / 121 / 95, all of 8000 - / 132 / 122;
     // 52 x 11, 4000 .. 8000 - / 181 / 161; 58 x 18, 1000 .. 8000 - / 181 / 154, all of 8000 - / 241 / 241; and from 240 workgroups on 62 x 18, 400 .. 3200
     // 79 / - / 96, 1000 .. 8000 168 / - / 153, all of 8000 216 / - / 236.
+    // More than four row blocks have no rounds: the pipelined kernel with splits, where those fill three quarters of the CUs and shares
+    // at most half. us per call, shares / splits: 8 / 1 heads, 56 x 29 nodes, 7025 keys 141.6 / 58.1, 45 x 19, 1536 .. 3073 53.8 / 26.9, 47 x 19,
+    // 875 .. 7005 74.0 / 44.3; 50 x 51, 694 .. 5554 72.6 / 70.4; 8 / 2 heads, 28 x 53, 6695 keys 79.5 / 52.3, 38 x 41, 916 .. 7333 69.6 / 65.7.
+    // Filling less, 8 / 1 heads, 45 x 34 nodes, 779 .. 6235 keys (180 workgroups) 70.4 / 73.2.
     const bool bal_capped = bal_w_auto * d->Hkv * bal_rg < bal_places * 7 / 8;
+    const bool split_fills = !coarse && !waves && nrb > 4 && bal_wgs <= kNumCUs / 2 && bal_wgs * (kNumCUs / bal_wgs) >= kNumCUs * 3 / 4;
     const bool rnd_fills = 2 * rnd_wgs <= kNumCUs || rnd_wgs >= 240;
     const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
     const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || one_split || (nrb <= 4 && (nrb > 2 || d->B > 1 || d->d == 64 || tiles <= 24)));
@@ -236,7 +243,7 @@ Plan plan_kernel(const vs_attn_desc* d, int tree) {
                                                 ((many && (int64_t)units0 * tiles >= 16 * kNumCUs) || tiles <= 5)));
     pl.schedule = d->schedule != VS_SCHED_AUTO ? d->schedule
                   : own_ok                     ? VS_SCHED_LOOP
-                  : balanced_ok && !(bal_capped && rounds_ok && rnd_fills) ? VS_SCHED_BALANCED
+                  : balanced_ok && !(bal_capped && (rounds_ok ? rnd_fills : split_fills)) ? VS_SCHED_BALANCED
                   : many && resident_ok        ? VS_SCHED_RESIDENT
                   : many && rounds_ok          ? VS_SCHED_LOOP
                   : many && pipe_ok            ? VS_SCHED_PIPELINED
@@ -338,12 +345,7 @@ Plan plan_kernel(const vs_attn_desc* d, int tree) {
     if (pl.schedule == VS_SCHED_PIPELINED) {
         rpw = 1;
         if (!waves) waves = nrb > 4 ? 8 : 4;
-        if (splits <= 0) {
-            const int wgs = units0 * ((nrb + waves - 1) / waves);
-            splits = wgs >= 200 ? 1 : kNumCUs / wgs;
-            const int max_splits = (tiles + 3) / 4; // at least four iterations per split
-            if (splits > max_splits) splits = max_splits;
-        }
+        if (splits <= 0) splits = pipe_splits(d, pl, nrb, waves, tiles, coarse);
     } else {
         if (!rpw) rpw = 1;
         if (!waves) {
@@ -418,6 +420,52 @@ bool merges_inside(const vs_attn_desc* d, const Plan& pl) {
            pl.rows_pad <= (1 << 16); // offsets inside a row group's partial results are 32 bits wide
 }
 
+// Key splits of the pipelined kernel, where a caller names none. coarse: enough to fill the CUs, of four iterations or more
+// each. Otherwise, with eight waves, as many as a model of the kernel's time prefers (3 % rms of 394 timings of 12 .. 200
+// units x row groups, 5 .. 60 iterations, 1 .. 20 splits): a share is a serial chain of iterations, so that short splits pay as long
+// as they find a CU each, and what they cost is the merge. us per call, n splits of the coarse rule / n of the model:
+//   28 / 4 heads: 12 x 21 nodes, 481 keys 2 17.1 / 4 13.4; 7 x 21, 1052 keys 5 17.7 / 9 14.9; 24 x 25, 61 .. 490 keys 2 21.9 / 1 19.6
+//   10 x 64 nodes, 25 .. 203 keys 2 19.4 / 1 15.1; 5 x 62, 80 .. 642 keys 3 17.6 / 5 15.4; 22 x 35, 615 keys 2 26.7 / 1 23.2
+//   32 / 8 heads of 64: 4 x 57 nodes, 395 .. 790 keys 4 14.7 / 7 12.1; 4 x 40, 1073 keys 5 14.7 / 6 12.4
+// Relative error against 64 bits, mean of 206 drawn calls whose plan differs from the coarse rule's: 2.73e-3 / 2.64e-3 (partial rows are
+// bf16, so that a sequence in one piece is the closer one, 2.3e-3, and the number of pieces makes no difference from two on: 2.8e-3).
+// 64 channels get no fewer than the coarse rule's (16 x 40 nodes, 48 .. 388 keys 2 14.1 / 1 15.1). Two row groups and more, which read
+// K and V once each, get no more where those find 100 CUs (9 x 41 nodes, 186 .. 372 keys 2 18.8 / 3 18.5; with more keys up to 0.87 of
+// the time, for twice the scratch). Launches that fill 200 CUs with whole sequences stay whole; four waves, two workgroups of
+// which share a CU, keep the coarse rule.
+int pipe_splits(const vs_attn_desc* d, Plan pl, int nrb, int waves, int tiles, bool coarse) {
+    pl.schedule = VS_SCHED_PIPELINED;
+    pl.waves = waves;
+    pl.row_groups = (nrb + waves - 1) / waves;
+    const int wgs = d->B * d->Hkv * pl.row_groups, room = kNumCUs / wgs;
+    const int few = wgs >= 200 ? 1 : room < (tiles + 3) / 4 ? room : (tiles + 3) / 4;
+    if (coarse || few <= 1 || waves == 4) return few;
+    const bool wide = d->d == 128;
+    const float fixed = wide ? 8.f : 6.3f; // us: everything outside the iterations and the merge
+    const float tile = wide ? 1.2f : 0.93f, full = wide ? 0.28f : 0.03f; // an iteration, and what it takes longer with all CUs at work
+    const float inside[2] = {wide ? 0.9f : 0.2f, wide ? 0.35f : 0.63f}, combine[2] = {wide ? 2.1f : 2.3f, wide ? 0.48f : 0.74f}; // and per MB of partial rows
+    const auto cost = [&](int n) {
+        pl.num_splits = n;
+        pl.total_wgs = n * wgs;
+        const float mb = (float)n * (d->B * d->Hkv) * pl.rows_pad * d->d * 2e-6f;
+        const float* merge = merges_inside(d, pl) ? inside : combine;
+        return fixed + (tiles + n - 1) / n * (tile + full * pl.total_wgs / kNumCUs) + (n > 1 ? merge[0] + merge[1] * mb : 0.f);
+    };
+    const int least = wide ? 1 : few, most = pl.row_groups > 1 && few * wgs >= 100 ? few : room < kMergeMaxSplits ? room : kMergeMaxSplits;
+    int chosen = few;
+    float best = 0.95f * cost(few); // another number has to bring more than the model is good for
+    for (int n = least; n <= most && n <= tiles; ++n) {
+        const int tps = (tiles + n - 1) / n;
+        if ((tiles + tps - 1) / tps != n) continue;
+        const float c = cost(n);
+        if (c < best) {
+            best = c;
+            chosen = n;
+        }
+    }
+    return chosen;
+}
+
 size_t workspace_bytes(const vs_attn_desc* d, const Plan& pl) {
     if (pl.impl != VS_IMPL_MFMA || pl.num_splits <= 1) return 0;
     const size_t prow = partial_rows(d, pl);
@@ -444,21 +492,30 @@ float resident_cost(int row_blocks, int tps, int n) { return kResidentCost[row_b
 // V cold in the caches. Up to 64 tiles, as far as was measured; twelve units and more up to 24 (from there on the rule for rounds ends too).
 // RESIDENT by name, with no number of splits or with the one that AUTO reports, is AUTO's plan where that is RESIDENT too: the number
 // of row blocks is no knob, and a caller who asks for the plan that was reported gets it.
-Plan make_plan(const vs_attn_desc* d, int tree = 1) {
+Plan make_plan(const vs_attn_desc* d, int tree = 1, bool coarse = false) {
     if (d->schedule == VS_SCHED_RESIDENT) {
         vs_attn_desc any = *d;
         any.schedule = VS_SCHED_AUTO;
         any.num_splits = any.rows_per_wave = any.waves_per_group = 0;
-        const Plan pl = make_plan(&any, tree);
-        if (pl.schedule == VS_SCHED_RESIDENT && (d->num_splits == 0 || d->num_splits == pl.num_splits)) return pl;
+        for (const bool c : {coarse, true}) {
+            const Plan pl = make_plan(&any, tree, c);
+            if (pl.schedule == VS_SCHED_RESIDENT && (d->num_splits == 0 || d->num_splits == pl.num_splits)) return pl;
+        }
     }
-    const Plan base = plan_kernel(d, tree);
+    const Plan base = plan_kernel(d, tree, coarse);
     const int nrb = base.rows_pad / kRowBlock;
     const int tiles = ((int64_t)d->max_prefix_len + (tree ? d->T : 0) + kIterKeys - 1) / kIterKeys;
     const int units = d->B * d->Hkv;
     const bool knobs = d->schedule != VS_SCHED_AUTO || d->rows_per_wave != 0 || d->waves_per_group != 0 || d->num_splits > 0;
-    if (base.impl != VS_IMPL_MFMA || knobs || base.schedule == VS_SCHED_BALANCED || nrb < 2 || (int64_t)units * nrb > 4 * kNumCUs || tiles > (units < 12 ? 64 : 24))
+    const bool pipelined = base.schedule == VS_SCHED_PIPELINED;
+    // (32 tiles instead of the pipelined kernel's splits, us: 28 / 4 heads, 3 x 24 nodes, 1669 keys 17.5 / 11.4, 8 / 2 heads, 7 x 33 nodes,
+    // 223 .. 1788 keys 17.2 / 12.4; four waves of it stay)
+    const int most_tiles = units < 12 ? 64 : pipelined && base.waves == 8 && !coarse ? 32 : 24;
+    if (base.impl != VS_IMPL_MFMA || knobs || base.schedule == VS_SCHED_BALANCED || nrb < 2 || (int64_t)units * nrb > 4 * kNumCUs || tiles > most_tiles)
         return base;
+    // (the pipelined kernel may prefer fewer splits than this one is good for: 2 resident ones for one pipelined 10.1 / 14 us and the like)
+    const int usual = pipelined ? pipe_splits(d, base, nrb, base.waves, tiles, true) : base.num_splits;
+    const int allowed = base.num_splits > usual ? base.num_splits : usual;
     // (the pipelined kernel, the loops and longer rounds cost more than any of these)
     const float keep = 0.95f; // another number of splits has to bring more than the table is good for
     const bool same_kernel = base.res_rb > 0 && base.keys_per_split <= resident_max_keys(base.res_rb);
@@ -466,11 +523,11 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     Plan pl = base;
     for (int rb = 1; rb <= 4; rb *= 2) {
         const int groups = (nrb + rb - 1) / rb;
-        const int most = kNumCUs / (units * groups) < base.num_splits ? kNumCUs / (units * groups) : base.num_splits;
+        const int most = kNumCUs / (units * groups) < allowed ? kNumCUs / (units * groups) : allowed;
         for (int tps = 1; tps <= resident_max_keys(rb) / kIterKeys && tps <= tiles; ++tps) {
             if (tps * most < tiles) continue;
             const int n = (tiles + tps - 1) / tps;
-            const float cost = (n == base.num_splits ? keep : 1.f) * resident_cost(rb, tps, n);
+            const float cost = (n == usual ? keep : 1.f) * resident_cost(rb, tps, n);
             if (!(cost < best)) continue;
             Plan c = base;
             c.schedule = base.schedule == VS_SCHED_LOOP ? VS_SCHED_LOOP : VS_SCHED_RESIDENT;
@@ -584,8 +641,9 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     const int32_t rc = check_desc(desc, tree);
     if (rc != VS_OK) return rc;
     Plan pl = make_plan(desc, tree);
-    // (a finer cut has more gates, 256 bytes each: with less scratch than it asks for a call runs on the other one's)
-    if (workspace_bytes_given < workspace_bytes(desc, pl)) pl = plan_kernel(desc, tree);
+    // (more splits need more partial rows and gates: with less scratch than they ask for a call runs on the coarser ones)
+    if (workspace_bytes_given < workspace_bytes(desc, pl)) pl = make_plan(desc, tree, true);
+    if (workspace_bytes_given < workspace_bytes(desc, pl)) pl = plan_kernel(desc, tree, true);
     if (pl.impl == VS_IMPL_MFMA && !(aligned16(q) && aligned16(k_cache) && aligned16(v_cache) && aligned16(out)))
         return VS_ERR_LAYOUT;
     const size_t need = workspace_bytes(desc, pl);
