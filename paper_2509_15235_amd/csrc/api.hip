@@ -712,6 +712,25 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.by_length = (pl.schedule == VS_SCHED_PIPELINED || pl.own_tiles) && desc->max_prefix_len >= by_length_from && pl.num_splits == 1 &&
                   desc->B >= 2 && desc->B <= kBalMaxSeqs && pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2) &&
                   !(pl.schedule == VS_SCHED_PIPELINED && pipe_three_per_cu(desc->d, pl.waves, pl.total_wgs));
+    // K and V as data that is read once (nt loads), where one workgroup alone reads a tile. Such loads come faster from memory and leave
+    // less of their data in the caches: faster for who finds nothing there, as the layers of a model, each with a cache of its own, do; not
+    // always for who goes over one layer again and again that the 256 MB cache in front of the memory would have held - least so
+    // where CUs are idle and each of the others waits for its own loads. Time relative to plain loads, over other data each time / over the
+    // same, 6500 drawn calls, by the megabytes of K and V up to the longest allowed prefix and by the CUs' places taken in the last round:
+    //   own tiles of one row block < 20 MB 1.1 / 1.00; .. 40 0.96 / 1.00; .. 96 all but a tenth of the places 0.94 / 0.92, less 0.95 / 0.95 (up to 1.10);
+    //   .. 192 0.93 / 1.00, less 0.94 / 1.04 (1.24); .. 512 0.91 / 1.01, less 0.92 / 1.04 (1.31); above 0.90 / 0.90 either way;
+    //   of two row blocks (long ones have 128 MB or more) .. 512 0.94 / 1.01, less 0.95 / 1.05 (1.26), above 0.90 / 0.90;
+    //   four waves of the pipelined kernel .. 256 0.97 / 1.00, .. 512 0.93 / 0.99, above 0.90 / 0.90.
+    // (Two row groups of eight waves, which share what they read, 1.03 / 1.04.) So what is too large for any cache, and of the rest what repeats
+    // no slower; of two row blocks, whose repetition with all sequences as long takes 1.00, all that fills the CUs. us per call: 64 x 4 nodes, 28 / 4 heads, 8000 keys 178 / 157;
+    // 4 x 60 nodes, 32 / 32 heads, 2880 .. 3392 keys, one layer of 32 45.1 / 40.7; 8 x 60, 1024 .. 8191 keys 108 / 91; 20 x 60, 2000 keys 152 / 129
+    const bool four = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) && pl.waves == 4;
+    if (pl.row_groups == 1 && (pl.own_tiles || four)) {
+        const double mb = (double)desc->B * desc->Hkv * ((double)desc->max_prefix_len + p.tree_keys) * desc->d * 4e-6;
+        const int places = kNumCUs * (pl.waves == 8 ? 1 : 2), rounds = (pl.total_wgs + places - 1) / places;
+        const bool filled = pl.total_wgs >= 0.9 * rounds * places;
+        p.once = mb >= (filled ? 512 : 768) || (filled && ((pl.own_tiles == 1 && mb >= 40 && mb < 96) || (pl.own_tiles == 2 && mb >= 128)));
+    }
     if (need > 0) {
         const size_t prow = partial_rows(desc, pl);
         p.part_o = (uint16_t*)workspace;

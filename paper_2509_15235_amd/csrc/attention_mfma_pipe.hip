@@ -35,7 +35,7 @@ namespace vs {
 namespace {
 
 // Waves of a SIMD that have registers at the same time: two, and three (workgroups of four waves on a CU) with 64 channels.
-template <int D, int RPW, int NW, bool PAGED, bool BAL>
+template <int D, int RPW, int NW, bool PAGED, bool BAL, bool ONCE>
 __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma_pipe_kernel(const AttnParams p) {
     request_args(p);
     constexpr int KS = D / 16;                 // k-steps of the S^T product
@@ -210,8 +210,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         const int w = HALVES ? 0 : is_v;
         const bool v = HALVES ? upper : is_v;
         const uint32_t lds = (uint32_t)(uintptr_t)(lds_void*)(v ? &sV[0][0] : &sK[0][0]) + (uint32_t)(slot * SUB * 2 + block0 * 1024);
-        if constexpr (PAGED) load_to_lds(lds, bt_lookup(v, decltype(full_tag)::value ? t : min(t, last)), direct_off[w]);
-        else load_to_lds(lds, rows[w], direct_off[w] + (uint32_t)(t * kTileKeys + RPI * block0) * stride);
+        if constexpr (PAGED) load_to_lds<ONCE>(lds, bt_lookup(v, decltype(full_tag)::value ? t : min(t, last)), direct_off[w]);
+        else load_to_lds<ONCE>(lds, rows[w], direct_off[w] + (uint32_t)(t * kTileKeys + RPI * block0) * stride);
     };
     // rows of V tile t (this wave's, arrived) that no key has become zeros: whatever the cache holds there, NaN included,
     // must not meet a zero probability
@@ -257,7 +257,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
         const __attribute__((address_space(1))) char* base = (const __attribute__((address_space(1))) char*)block;
         asm("" : "+s"(base));
         asm volatile("" : "+v"(lane_off));
-        return *(const __attribute__((address_space(1))) u32x4*)(base + lane_off);
+        const auto* at = (const __attribute__((address_space(1))) u32x4*)(base + lane_off);
+        return ONCE ? __builtin_nontemporal_load(at) : *at;
     };
     const int64_t block_bytes = (int64_t)RPI * stride_tok * 2; // from one of this wave's blocks of a tile to the next
     // The first four tiles - K(0), K(1), K(2), V(0) - and, DIRECT, all others that the queries leave room for are requested before
@@ -1053,17 +1054,24 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     }
 }
 
+template <int D, int RPW, int NW, bool BAL, bool ONCE>
+void launch_pipe(const AttnParams& p, dim3 grid, hipStream_t s) {
+    if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, BAL, ONCE>), grid, dim3(NW * kWave), 0, s, p);
+    else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, BAL, ONCE>), grid, dim3(NW * kWave), 0, s, p);
+}
 template <int D, int RPW, int NW>
 hipError_t launch_pipe(const AttnParams& p, hipStream_t s) {
+    constexpr bool MAY = NW == 4; // eight waves gain 1 - 2 % from it where they are one row group, and lose 3 - 5 % where they are two
+    if (p.once && !MAY) return hipErrorInvalidValue;
     if (p.bal_chunks > 0) {
         const dim3 grid(((p.bal_chunks * p.Hkv + 7) / 8) * 8 * p.row_groups);
-        if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, true>), grid, dim3(NW * kWave), 0, s, p);
-        else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, true>), grid, dim3(NW * kWave), 0, s, p);
-        return hipGetLastError();
+        if (p.once) launch_pipe<D, RPW, NW, true, MAY>(p, grid, s);
+        else launch_pipe<D, RPW, NW, true, false>(p, grid, s);
+    } else {
+        const dim3 grid(p.by_length ? (p.B * p.Hkv + 7) / 8 * 8 * p.row_groups : (p.total_wgs + 7) / 8 * 8);
+        if (p.once) launch_pipe<D, RPW, NW, false, MAY>(p, grid, s);
+        else launch_pipe<D, RPW, NW, false, false>(p, grid, s);
     }
-    const dim3 grid(p.by_length ? (p.B * p.Hkv + 7) / 8 * 8 * p.row_groups : (p.total_wgs + 7) / 8 * 8);
-    if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, false>), grid, dim3(NW * kWave), 0, s, p);
-    else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, false>), grid, dim3(NW * kWave), 0, s, p);
     return hipGetLastError();
 }
 

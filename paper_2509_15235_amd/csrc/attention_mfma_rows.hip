@@ -28,7 +28,9 @@ namespace {
 
 // NW waves, RB row blocks. (PAGED is part of the kernel for the scalar registers: with a branch 14 of them were spilled, in the loop over the
 // tiles too: 4 x 60 nodes, 32 / 32 heads, 3100 keys 39.7 -> 39.2 us, one sequence of 484 keys and four nodes 7.4 -> 7.2.)
-template <int D, int NW, int RB, bool PAGED>
+// ONCE: tiles as data that is read once (the host's rule says when). Part of the kernel as well: a branch at every load 5 % of two row blocks'
+// time, a loop of its own for either kind 3 % of a short call's.
+template <int D, int NW, int RB, bool PAGED, bool ONCE>
 __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnParams p) {
     constexpr int KS = D / 16;          // k-steps of the S^T product
     constexpr int DB = D / 32;          // 32-channel blocks of the output
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
             for (int i = 0; i < BPS; ++i) {
                 const int h = 2 * i / BPS;
                 const char* from = (const char*)base[h] + (uint32_t)(row0[h] + RPI * (i % (BPS / 2))) * stride;
-                load_to_lds(lds + 1024 * i, from, ISV ? v_off : k_off[i % KV]);
+                load_to_lds<ONCE>(lds + 1024 * i, from, ISV ? v_off : k_off[i % KV]);
             }
         } else {
 #pragma unroll
@@ -403,12 +405,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     if (merge) merge_splits<D>(p, gate, b, kvh, block0, block0 + RB, split, (nk + p.keys_per_split - 1) / p.keys_per_split, NW, (uint32_t*)sp);
 }
 
-template <int D, int NW, int RB>
+template <int D, int NW, int RB, bool ONCE>
 hipError_t launch_rows(const AttnParams& p, hipStream_t s) {
     const dim3 grid(((p.total_wgs + 7) / 8) * 8);
-    if (p.paged) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, true>), grid, dim3(NW * kWave), 0, s, p);
-    else hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false>), grid, dim3(NW * kWave), 0, s, p);
+    if (p.paged) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, true, ONCE>), grid, dim3(NW * kWave), 0, s, p);
+    else hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false, ONCE>), grid, dim3(NW * kWave), 0, s, p);
     return hipGetLastError();
+}
+template <int D, int NW, int RB>
+hipError_t launch_rows(const AttnParams& p, hipStream_t s) {
+    return p.once ? launch_rows<D, NW, RB, true>(p, s) : launch_rows<D, NW, RB, false>(p, s);
 }
 
 } // namespace

@@ -66,14 +66,19 @@ __device__ __forceinline__ float visible_or_inf(float s, uint32_t w, int bit) {
 // made on the scalar side, which has no such rule (an s_nop 4 instead: short calls of own tiles 6.0 -> 6.1 us).
 // m0 is an operand, so the compiler knows what it holds: its own loads into LDS go by it, too. The copy is the wait state
 // that a load needs behind a write of it.
+// ONCE: data that nobody reads a second time (nt: it need not stay in a cache), here and below.
+template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t lane_off) {
     const void* at;
-    asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(at) : "{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
+    if constexpr (ONCE) asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0 nt" : "=&s"(at) : "{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
+    else asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(at) : "{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
 }
 // the same from a bounded range: what lies outside reads as zeros (four registers, two moves that nothing here can write down: five wait
 // states. 20 x 60 nodes, 16 / 16 heads of 64, 1500 keys 32.0 us with two of them, 32.3 with five)
+template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, __amdgpu_buffer_rsrc_t range, uint32_t off) {
-    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds), "v"(off), "s"(range) : "memory");
+    if constexpr (ONCE) asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"{m0}"(lds), "v"(off), "s"(range) : "memory");
+    else asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds), "v"(off), "s"(range) : "memory");
 }
 // the same from every lane's own address (in vector registers; one wait state for m0)
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const void* lane_at) {

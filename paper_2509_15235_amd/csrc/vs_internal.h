@@ -73,6 +73,7 @@ struct AttnParams {
     int32_t rows_per_group;     // waves_per_group * row blocks per wave * kRowBlock
     int32_t total_wgs;          // B * Hkv * num_splits * row_groups
     FastDiv by_splits, by_groups, by_heads; // workgroup id -> (sequence, KV head, row group, split)
+    int32_t once;               // own tiles, four waves of the pipelined kernel: K and V as data that is read once
     int32_t by_length;          // pipelined kernel without key splits: workgroups take the sequences longest first
     int32_t bal_chunks;         // balanced schedule: equal shares of the batch's keys per (KV head, row group); else 0.
                                 // num_splits then counts partial-result slots per KV head (shares + sequences)
