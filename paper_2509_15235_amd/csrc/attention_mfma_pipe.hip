@@ -59,7 +59,6 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     __shared__ int32_t sLen[DIRECT && !BAL ? NW : 1][kWave]; // the sequence's length, a copy for every wave
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
-    __shared__ uint64_t sgen;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -323,8 +322,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     }
     if (!BAL && p.gates && nk <= klen) whole = true; // a sequence of one split has nothing to merge
     const bool merge = !BAL && p.gates && !whole;
-    const MergeGate gate{merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
-    if (merge && tid == 0) merge_open(gate);
+    uint64_t* const gate = merge ? p.gates + kGateWords * (((int64_t)b * p.Hkv + kvh) * p.row_groups + rg) : nullptr;
+    if (merge && tid == 0) merge_open(gate, gate_load(gate));
     const int k1 = min(nk, k0 + klen);
     const int n = (k1 - k0 + kTileKeys - 1) / kTileKeys; // tiles of this split
 

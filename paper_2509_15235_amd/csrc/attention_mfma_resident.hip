@@ -54,7 +54,6 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     __shared__ float s_max[NRB][KQ][kRowBlock], s_sum[NRB][KQ][kRowBlock]; // every part's maxima and sums
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
-    __shared__ uint64_t sgen;
     uint16_t* sK = smem;
     uint16_t* sV = smem + NT * SUB;
     uint16_t* sQ = smem + Q_AT;
@@ -121,9 +120,9 @@ __global__ __launch_bounds__(kResWaves * 64, 2) void attn_mfma_resident_kernel(c
     u32x4 qreg[QPW];
     load_q_pieces<D>(p, b, kvh, [&](int) { return row_base; }, [&](int i) { return min(kq * QPW + i, KS - 1); }, lane, qreg);
     // the gate of the row group (thread 0 opens it below)
-    const MergeGate gate{p.gates ? p.gates + kGateWords * (int64_t)((b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
-    MergeSeen seen{};
-    if (p.gates && wave == 0) seen = merge_look(gate);
+    uint64_t* const gate = p.gates ? p.gates + kGateWords * (int64_t)((b * p.Hkv + kvh) * p.row_groups + rg) : nullptr;
+    uint64_t seen = 0;
+    if (p.gates && wave == 0) seen = gate_load(gate);
     // the row's ancestor mask, when the caller supplies the masks
     const int r = min(row_base + col, p.rows - 1); // rows past the end repeat the last row (results discarded)
     const int node = row_node(p, r);

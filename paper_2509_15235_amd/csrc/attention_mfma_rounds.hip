@@ -52,7 +52,6 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     __shared__ __attribute__((aligned(1024))) uint16_t smem[SMEM_ELEMS];
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
-    __shared__ uint64_t sgen;
     uint16_t* sK = smem;
     uint16_t* sV = smem + NT * SUB;
     uint16_t* sQ = smem + Q_AT / 2; // queries: row blocks of D-channel rows (see load_q_pieces)
@@ -132,9 +131,9 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     u32x4 qreg[QPW];
     load_q_pieces<D>(p, b, kvh, [&](int) { return row_base; }, [&](int i) { return min(kq * QPW + i, KS - 1); }, lane, qreg);
     // the gate of the row group (thread 0 opens it below)
-    const MergeGate gate{p.gates ? p.gates + kGateWords * (int64_t)((b * p.Hkv + kvh) * p.row_groups + rg) : nullptr, &sgen};
-    MergeSeen seen{};
-    if (p.gates && wave == 0) seen = merge_look(gate);
+    uint64_t* const gate = p.gates ? p.gates + kGateWords * (int64_t)((b * p.Hkv + kvh) * p.row_groups + rg) : nullptr;
+    uint64_t seen = 0;
+    if (p.gates && wave == 0) seen = gate_load(gate);
     // the row's ancestor mask, when the caller supplies the masks: requested ahead of the later stages
     uint64_t mask_given = 0;
     if (p.tree_mask && p.tree_keys != 0) mask_given = p.tree_mask[(int64_t)b * p.T + node];

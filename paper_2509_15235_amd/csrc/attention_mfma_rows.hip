@@ -51,7 +51,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     __shared__ __attribute__((aligned(1024))) uint16_t smem[SMEM_ELEMS];
     __shared__ int32_t sp[VS_MAX_TREE];
     __shared__ int32_t sflag;
-    __shared__ uint64_t sgen;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -159,9 +158,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
         mask[rb] = p.tree_mask && p.tree_keys != 0 ? p.tree_mask[(int64_t)b * p.T + node[rb]] : 0ull;
     }
     // the gate of the (sequence, KV head), opened below
-    const MergeGate gate{p.gates ? p.gates + kGateWords * ((int64_t)unit * p.row_groups + rg) : nullptr, &sgen};
-    MergeSeen seen{};
-    if (p.gates && wave == 0) seen = merge_look(gate);
+    uint64_t* const gate = p.gates ? p.gates + kGateWords * ((int64_t)unit * p.row_groups + rg) : nullptr;
+    uint64_t seen = 0;
+    if (p.gates && wave == 0) seen = gate_load(gate);
     if (first < kend) { // uniform per wave
         issue(std::false_type{}, sK, first, kend - 1);
         issue(std::true_type{}, sV, first, kend - 1);

@@ -277,64 +277,52 @@ __device__ __forceinline__ int64_t ml_block(const AttnParams& p, int64_t unit, i
 // arguments, lengths, the same trip, drain: 5 us). A barrier between workgroups only ends when all of
 // them get to run, which nobody promises while other streams hold CUs. So the wait is bounded: who waits
 // longer than p.merge_wait hands its share over to the workgroup that arrives last and leaves.
-//   word 0  kMergeTag << 40 | abandoned shares << 8 | arrivals. Anything else (first use of the workspace)
-//           counts as zero and is replaced before the first arrival; the last arrival puts it back to zero.
-//   word 1  changes when all have arrived (any initial value)
-// The call before on the same workspace has ended (calls that share one are ordered), so both words are at rest.
+// The gate's word is kMergeTag << 40 | abandoned shares << 8 | arrivals. Anything else (first use of the workspace) counts as zero
+// and is replaced before the first arrival; the last arrival puts it back to zero. So who has arrived and finds n arrivals, or
+// none, knows that all have. (They waited for a second word that the last one changed once its own arrival had returned: us per
+// call, before / so, 28 / 4 heads, 60 nodes, 1696 keys, 28 layers 291.0 / 284.5; 32 / 8 heads of 64, 8 x 31 nodes, up to 2047 keys
+// 12.41 / 12.27; 3600 drawn calls with two and more splits, geometric mean 0.974, one in a hundred of them - many splits that come in one
+// by one, where the looks hold up the arrivals - 1.01 to 1.04. Fewer looks while many are still missing were 0.3 % slower in the mean.)
+// The call before on the same workspace has ended (calls that share one are ordered), so the word is at rest.
 static_assert(kMergeMaxSplits == 32, "bits of the abandoned set");
 constexpr uint64_t kMergeTag = 0xffc3a9ull;           // no partial result or (max, sum) pair looks like this (a NaN)
 static_assert(kMergeTag != kArrivalZero >> 40, "an arrival word that vs_draft_expand left in a shared workspace is no gate");
 constexpr uint64_t kMergeZero = kMergeTag << 40;
 
-struct MergeGate {
-    uint64_t* word; // null: the splits are merged by the combine kernel
-    uint64_t* gen;  // LDS: word 1 before anybody arrived (thread 0 only)
-};
 __device__ __forceinline__ uint64_t gate_load(const uint64_t* w) {
     return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Thread 0 of every workgroup of the row group, any time before it arrives. In two parts, because loads return in order:
-// asked for behind the tiles, the words come behind the tiles.
-struct MergeSeen {
-    uint64_t gen, word;
-};
-__device__ __forceinline__ MergeSeen merge_look(const MergeGate& g) { return {gate_load(g.word + kGateFlag), gate_load(g.word)}; }
-__device__ __forceinline__ void merge_open(const MergeGate& g, MergeSeen seen) {
-    *g.gen = seen.gen;
-    uint64_t w = seen.word;
-    if ((w >> 40) != kMergeTag) // lost to another workgroup: then it did the same
-        __hip_atomic_compare_exchange_strong(g.word, &w, kMergeZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Thread 0 of every workgroup of the row group, any time before it arrives; `seen`: the word, asked for earlier (loads return in
+// order: asked for behind the tiles, it comes behind the tiles). null: the splits are merged by the combine kernel.
+__device__ __forceinline__ void merge_open(uint64_t* gate, uint64_t seen) {
+    if ((seen >> 40) != kMergeTag) // lost to another workgroup: then it did the same
+        __hip_atomic_compare_exchange_strong(gate, &seen, kMergeZero, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Thread 0, after every wave's partial results are in memory. Returns the splits whose shares this workgroup
 // has to merge besides its own; `go` false: its own share was handed over.
-__device__ __forceinline__ uint32_t merge_meet(const MergeGate& g, uint32_t wait, int split, int n, bool& go) {
+__device__ __forceinline__ uint32_t merge_meet(uint64_t* gate, uint32_t wait, int split, int n, bool& go) {
     go = true;
-    const uint64_t gen = *g.gen;
-    const uint64_t old = __hip_atomic_fetch_add(g.word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t old = __hip_atomic_fetch_add(gate, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((int)(old & 0xff) == n - 1) {
-        __hip_atomic_store(g.word, kMergeZero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(g.word + kGateFlag, gen + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(gate, kMergeZero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return (uint32_t)(old >> 8);
     }
+    const auto all = [&](uint64_t w) { return (int)(w & 0xff) == 0 || (int)(w & 0xff) == n; };
     const uint64_t t0 = wall_clock64();
-    while (gate_load(g.word + kGateFlag) == gen) {
-        __builtin_amdgcn_s_sleep(1);
-        if (wall_clock64() - t0 > wait) {
-            uint64_t w = gate_load(g.word);
-            // zero or n arrivals: the last one has come in the meantime
-            while ((int)(w & 0xff) != 0 && (int)(w & 0xff) != n) {
-                if (__hip_atomic_compare_exchange_strong(g.word, &w, w | (256ull << split), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT)) {
-                    go = false;
-                    return 0;
-                }
+    uint32_t looks = 0;
+    for (uint64_t w; !all(w = gate_load(gate));) {
+        if ((++looks & 7) != 0 || wall_clock64() - t0 <= wait) continue; // (the clock takes as long as a look)
+        do {
+            if (__hip_atomic_compare_exchange_strong(gate, &w, w | (256ull << split), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)) {
+                go = false;
+                return 0;
             }
-            break;
-        }
+        } while (!all(w));
+        break; // the last one has come in the meantime
     }
     return 0;
 }
-__device__ __forceinline__ void merge_open(const MergeGate& g) { merge_open(g, merge_look(g)); }
 // Half a piece (eight channels of the 32 rows of a row block, see store_partial: the 32 lanes of one half of the
 // accumulators): where it is read and written. The addresses are worked out before the wait, the rest after it.
 constexpr int kMergeGroup = 4; // items a wave merges at once, at most
@@ -448,7 +436,7 @@ __device__ __forceinline__ void merge_run_few(const MergeItem (&it)[kMergeGroup]
 // to memory (0.7 us), so a wave that has several - few splits, many rows - takes up to four at once: 192 rows in two
 // splits 23.6 -> 19.2 us (23 sequences of up to 290 keys); one sequence of five row blocks and splits 12.3 -> 11.4.
 template <int D>
-__device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGate& g, int b, int kvh, int rb0, int rb1, int split, int n,
+__device__ __forceinline__ void merge_splits(const AttnParams& p, uint64_t* gate, int b, int kvh, int rb0, int rb1, int split, int n,
                                              int waves, uint32_t* s_word) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int NP = D / 8; // half pieces per row block
@@ -478,7 +466,7 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, const MergeGat
     __syncthreads();
     if (tid == 0) {
         bool go;
-        s_word[0] = merge_meet(g, p.merge_wait, split, n, go);
+        s_word[0] = merge_meet(gate, p.merge_wait, split, n, go);
         s_word[1] = go;
     }
     __syncthreads();

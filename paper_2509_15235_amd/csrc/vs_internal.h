@@ -30,9 +30,7 @@ constexpr int kScanChunk = kScanThreads * kScanVec * 4;      // ... and the floa
 constexpr int kBalMaxSeqs = 64;   // balanced schedule: sequences per call (a lane each)
 constexpr int kBalMaxChunks = 64; // ... and shares per (KV head, row group)
 constexpr int kMergeMaxSplits = 32; // key splits that the workgroups themselves merge (attn_mfma_common.h)
-constexpr int kGateWords = 32;      // 64-bit words of a row group's gate: two cache lines, so that neither gates nor the two words of one
-                                    // gate wait for each other
-constexpr int kGateFlag = 16;       // its second word
+constexpr int kGateWords = 32;      // 64-bit words of a row group's gate, the first of which counts: gates share no cache line
 constexpr int kRoundKeys = 128;       // keys of a round (attention_mfma_rounds.hip)
 constexpr int kResidentMaxKeys = 192; // keys of one split that the resident attention kernel keeps in LDS
 constexpr int resident_max_keys(int row_blocks) { return row_blocks <= 2 ? 256 : kResidentMaxKeys; } // ... with so many row blocks to a workgroup
@@ -50,7 +48,7 @@ struct AttnParams {
     int32_t* status;            // may be null
     uint16_t* part_o;           // partial outputs, each row normalised by its own sum, bf16 (layout: attn_mfma_common.h)
     float* part_ml;             // [unit][row block][split][32][2] running max (log2 domain), sum
-    uint64_t* gates;            // two words per (unit, row group): the splits are merged by the workgroups that
+    uint64_t* gates;            // a word per (unit, row group): the splits are merged by the workgroups that
                                 // computed them (attn_mfma_common.h); null: by the combine kernel
     uint32_t merge_wait;        // how long a workgroup waits for the others at a gate (ticks of 10 ns)
     int32_t B, T, Hq, Hkv, d, group;
