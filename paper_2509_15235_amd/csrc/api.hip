@@ -958,6 +958,8 @@ int32_t vs_tree_kv_commit(const vs_kv_desc* d, void* k_cache, void* v_cache, con
     p.Hkv = d->Hkv;
     p.chunks_per_row = (int32_t)(d->d * eb / 16);
     p.items_per_seq = (int64_t)d->num_layers * 2 * d->Hkv * p.chunks_per_row;
+    p.by_chunks = fast_div_by(p.chunks_per_row);
+    p.by_heads = fast_div_by(d->Hkv);
     p.paged = d->paged ? 1 : 0;
     p.block_size = d->paged ? d->block_size : 1;
     p.block_shift = 0;

@@ -37,7 +37,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // fp32: 2 x 31 nodes, 8 / 2 heads, 600 keys 11.28 -> 10.86. Pipelined kernel: 64 x 400 keys paged 46.2 -> 45.8, 19 x 110 of 64 channels 6.2 -> 6.3.
 // Draft tree of four launches 37.0 -> 36.8.
 // (Not in attention_mfma_rows.hip: 4 x 60 nodes, 32 / 32 heads, 3100 keys 39.2 without, 39.5 us with it. Nor where it changed nothing: acceptance
-// of either kind, 30 sizes, mean 1.000; commit, the straight loop with its combine kernel, bf16 without matrix cores.)
+// of either kind, 30 sizes, mean 1.000; the straight loop with its combine kernel, bf16 without matrix cores.)
 template <typename T>
 __device__ __forceinline__ void request_args(const T& p) {
     const uint32_t* w = (const uint32_t*)&p;

@@ -169,6 +169,7 @@ struct CommitParams {
     int32_t B, T, Hkv;
     int32_t chunks_per_row;      // 16-byte pieces per row of d elements
     int64_t items_per_seq;       // layers * 2 * Hkv * chunks_per_row
+    FastDiv by_chunks, by_heads; // piece -> chunk of the row, KV head
     int32_t paged, block_size, block_shift, max_blocks, num_blocks;
     int64_t capacity;
     int64_t stride_layer_bytes, stride_seq_bytes, stride_block_bytes, stride_head_bytes, stride_tok_bytes;

@@ -101,6 +101,25 @@ def test_fuzz_bit_exact(gu, oracle_mod, dtype, d, paged, T, B, hkv, S, k):
     assert _same_bytes(gk, ek) and _same_bytes(gv, ev)
 
 
+@pytest.mark.parametrize("T", [27, 64])
+@pytest.mark.parametrize("paged", [False, True])
+def test_every_number_of_moves(gu, oracle_mod, paged, T):
+    """0 .. 13 accepted nodes, rows 2k or k + 1 moved to k: every mix of eight, four and two moves; caches that end at, before and
+    behind a block's edge."""
+    B = 14
+    alen = np.minimum(np.arange(B), T // 2).astype(np.int32)
+    k = np.arange(T)
+    at = np.where((np.arange(B) % 3 == 0)[:, None], k + (k > 0), 2 * k)
+    path = np.where(k <= alen[:, None], at, -1).astype(np.int32)
+    cfg = gen.Config(f"moves{T}", B, 2, 2, 64, T, 7, 4, 100, 0.5, 1, "bf16", prefix=None if paged else [b * 5 for b in range(B)],
+                     prefix_range=(9, 40) if paged else None, paged=paged)
+    inp, kk, vv = _layers(cfg, 4000 + T, 3)
+    gk, gv, newp, status = gu.DeviceCommit(cfg, kk, vv, inp.prefix_len, path, alen, inp.block_table).run()
+    ek, ev, enp = _oracle_commit(oracle_mod, inp, kk, vv, path, alen)
+    assert (status == 0).all() and np.array_equal(newp, enp)
+    assert _same_bytes(gk, ek) and _same_bytes(gv, ev) and not _same_bytes(gk, kk)
+
+
 def test_long_paths_cross_the_batch_of_eight(gu, oracle_mod):
     """Chain-like trees: up to 63 accepted tokens, several batches of moves per thread."""
     T, B = 64, 3
