@@ -224,12 +224,12 @@ Plan plan_kernel(const vs_attn_desc* d, int tree, bool coarse) {
     // - / 89 / 68, 2750 .. 5500 - / 101 / 91, all of 5500 - / 112 / 118; 33 x 11, 1000 .. 8000 - / 121 / 95, all of 8000 - / 132 / 122;
     // 52 x 11, 4000 .. 8000 - / 181 / 161; 58 x 18, 1000 .. 8000 - / 181 / 154, all of 8000 - / 241 / 241; and from 240 workgroups on 62 x 18, 400 .. 3200
     // 79 / - / 96, 1000 .. 8000 168 / - / 153, all of 8000 216 / - / 236.
-    // More than four row blocks have no rounds: the pipelined kernel with splits, where those fill three quarters of the CUs and shares
-    // at most half. us per call, shares / splits: 8 / 1 heads, 56 x 29 nodes, 7025 keys 141.6 / 58.1, 45 x 19, 1536 .. 3073 53.8 / 26.9, 47 x 19,
-    // 875 .. 7005 74.0 / 44.3; 50 x 51, 694 .. 5554 72.6 / 70.4; 8 / 2 heads, 28 x 53, 6695 keys 79.5 / 52.3, 38 x 41, 916 .. 7333 69.6 / 65.7.
-    // Filling less, 8 / 1 heads, 45 x 34 nodes, 779 .. 6235 keys (180 workgroups) 70.4 / 73.2.
+    // (More than four row blocks have no rounds, and the pipelined kernel's splits are no choice for them, though faster where shares fill at
+    // most half of the CUs - us per call, shares / splits: 8 / 1 heads, 56 x 29 nodes, 7025 keys 141.6 / 58.1; 50 x 51, 694 .. 5554 72.6 / 70.4 -:
+    // with about as many shares as sequences most of those are one piece, fp32 up to the final rounding, and every split is a bf16 partial row.
+    // Relative error against 64 bits, 40 drawn calls of them, shares / splits: mean 2.77e-3 / 2.80e-3, at most 2.54e-3 / 2.74e-3 (62 x 62
+    // nodes, 8 / 2 heads, 331 .. 2652 keys).)
     const bool bal_capped = bal_w_auto * d->Hkv * bal_rg < bal_places * 7 / 8;
-    const bool split_fills = !coarse && !waves && nrb > 4 && bal_wgs <= kNumCUs / 2 && bal_wgs * (kNumCUs / bal_wgs) >= kNumCUs * 3 / 4;
     const bool rnd_fills = 2 * rnd_wgs <= kNumCUs || rnd_wgs >= 240;
     const bool knobs = d->schedule != VS_SCHED_AUTO || rpw != 0 || waves != 0 || splits > 0;
     const bool rounds_ok = !knobs && nrb >= 2 && rnd_wgs <= kNumCUs && (!many || one_split || (nrb <= 4 && (nrb > 2 || d->B > 1 || d->d == 64 || tiles <= 24)));
@@ -243,7 +243,7 @@ Plan plan_kernel(const vs_attn_desc* d, int tree, bool coarse) {
                                                 ((many && (int64_t)units0 * tiles >= 16 * kNumCUs) || tiles <= 5)));
     pl.schedule = d->schedule != VS_SCHED_AUTO ? d->schedule
                   : own_ok                     ? VS_SCHED_LOOP
-                  : balanced_ok && !(bal_capped && (rounds_ok ? rnd_fills : split_fills)) ? VS_SCHED_BALANCED
+                  : balanced_ok && !(bal_capped && rounds_ok && rnd_fills) ? VS_SCHED_BALANCED
                   : many && resident_ok        ? VS_SCHED_RESIDENT
                   : many && rounds_ok          ? VS_SCHED_LOOP
                   : many && pipe_ok            ? VS_SCHED_PIPELINED

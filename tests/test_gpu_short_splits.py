@@ -15,7 +15,6 @@ pytestmark = pytest.mark.gpu
     (4, 37, 32, 8, 64, 801, vs.VS_SCHED_PIPELINED, 7, 224, 2785280),       # four
     (24, 19, 28, 4, 128, 366, vs.VS_SCHED_PIPELINED, 1, 96, 8110080),      # two
     (6, 35, 8, 2, 128, 1567, vs.VS_SCHED_RESIDENT, 7, 252, 3551232),       # seven of the pipelined kernel
-    (36, 18, 8, 1, 128, 3650, vs.VS_SCHED_PIPELINED, 7, 252, 4224256),     # balanced shares
 ])
 def test_against_the_oracle(oracle_mod, B, T, Hq, Hkv, d, longest, schedule, splits, wgs, coarser):
     import gpu_util as gu
