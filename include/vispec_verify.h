@@ -204,11 +204,10 @@ size_t vs_attention_workspace_bytes(const vs_attn_desc* desc);           /* 0 on
  *   status      [B] int32   out, optional
  *   workspace   device scratch of at least vs_attention_workspace_bytes(desc) bytes
  *               (may be NULL when that is 0), 256-byte aligned.
- *               Calls are cut into more workgroups than the kernel's usual ones where CUs are idle,
- *               and need their partial rows and up to 256 bytes more for each. With less scratch than
- *               that, but enough for the usual cut, the call is not refused and runs on the usual one:
- *               slower, its splits and so its roundings other than those of the plan that
- *               vs_attention_plan gives
+ *               Short calls are cut into more workgroups than the kernel's usual ones where CUs are
+ *               idle, and need up to 256 bytes more for each. With less scratch than that, but enough
+ *               for the usual cut, the call is not refused and runs on the usual one: slower, its
+ *               splits and so its roundings other than those of the plan that vs_attention_plan gives
  * bf16 MFMA path needs 16-byte aligned q/k/v/out and strides that are multiples of 8.
  */
 int32_t vs_tree_verify_attention(const vs_attn_desc* desc, const void* q, const void* k_cache,

@@ -58,7 +58,8 @@ struct Plan {
     int32_t res_rb; // resident schedule: row blocks per workgroup (4, 2 or 1)
 };
 bool merges_inside(const vs_attn_desc* d, const Plan& pl);
-int pipe_splits(const vs_attn_desc* d, Plan pl, int nrb, int waves, int tiles, bool coarse);
+int filling_splits(int wgs, int tiles);
+int pipe_splits(const vs_attn_desc* d, Plan pl, int nrb, int waves, int tiles);
 
 // Shape / dtype / layout checks that need no device. Returns VS_OK or a vs_error.
 int32_t check_desc(const vs_attn_desc* d, int tree = 1) {
@@ -118,7 +119,7 @@ int32_t check_desc(const vs_attn_desc* d, int tree = 1) {
     return VS_OK;
 }
 
-Plan plan_kernel(const vs_attn_desc* d, int tree, bool coarse) {
+Plan plan_kernel(const vs_attn_desc* d, int tree) {
     Plan pl{};
     const int group = d->Hq / d->Hkv;
     pl.rows = d->T * group;
@@ -345,7 +346,7 @@ Plan plan_kernel(const vs_attn_desc* d, int tree, bool coarse) {
     if (pl.schedule == VS_SCHED_PIPELINED) {
         rpw = 1;
         if (!waves) waves = nrb > 4 ? 8 : 4;
-        if (splits <= 0) splits = pipe_splits(d, pl, nrb, waves, tiles, coarse);
+        if (splits <= 0) splits = pipe_splits(d, pl, nrb, waves, tiles);
     } else {
         if (!rpw) rpw = 1;
         if (!waves) {
@@ -420,50 +421,33 @@ bool merges_inside(const vs_attn_desc* d, const Plan& pl) {
            pl.rows_pad <= (1 << 16); // offsets inside a row group's partial results are 32 bits wide
 }
 
-// Key splits of the pipelined kernel, where a caller names none. coarse: enough to fill the CUs, of four iterations or more
-// each. Otherwise, with eight waves, as many as a model of the kernel's time prefers (3 % rms of 394 timings of 12 .. 200
-// units x row groups, 5 .. 60 iterations, 1 .. 20 splits): a share is a serial chain of iterations, so that short splits pay as long
-// as they find a CU each, and what they cost is the merge. us per call, n splits of the coarse rule / n of the model:
-//   28 / 4 heads: 12 x 21 nodes, 481 keys 2 17.1 / 4 13.4; 7 x 21, 1052 keys 5 17.7 / 9 14.9; 24 x 25, 61 .. 490 keys 2 21.9 / 1 19.6
-//   10 x 64 nodes, 25 .. 203 keys 2 19.4 / 1 15.1; 5 x 62, 80 .. 642 keys 3 17.6 / 5 15.4; 22 x 35, 615 keys 2 26.7 / 1 23.2
-//   32 / 8 heads of 64: 4 x 57 nodes, 395 .. 790 keys 4 14.7 / 7 12.1; 4 x 40, 1073 keys 5 14.7 / 6 12.4
-// Relative error against 64 bits, mean of 206 drawn calls whose plan differs from the coarse rule's: 2.73e-3 / 2.64e-3 (partial rows are
-// bf16, so that a sequence in one piece is the closer one, 2.3e-3, and the number of pieces makes no difference from two on: 2.8e-3).
-// 64 channels get no fewer than the coarse rule's (16 x 40 nodes, 48 .. 388 keys 2 14.1 / 1 15.1). Two row groups and more, which read
-// K and V once each, get no more where those find 100 CUs (9 x 41 nodes, 186 .. 372 keys 2 18.8 / 3 18.5; with more keys up to 0.87 of
-// the time, for twice the scratch). Launches that fill 200 CUs with whole sequences stay whole; four waves, two workgroups of
-// which share a CU, keep the coarse rule.
-int pipe_splits(const vs_attn_desc* d, Plan pl, int nrb, int waves, int tiles, bool coarse) {
+// Key splits that fill the CUs with `wgs` workgroups each, of four iterations or more; launches that fill 200 CUs with whole sequences stay whole.
+int filling_splits(int wgs, int tiles) {
+    const int n = wgs >= 200 ? 1 : kNumCUs / wgs, most = (tiles + 3) / 4;
+    return n < most ? n : most;
+}
+
+// Key splits of the pipelined kernel, where a caller names none: as many as fill the CUs, or with eight waves of 128 channels whole sequences, where
+// a model of the kernel's time (3 % rms of 394 timings of 12 .. 200 units x row groups, 5 .. 60 iterations, 1 .. 20 splits) says that
+// the iterations saved are not worth the merge. us per call, 28 / 4 heads, filling / whole: 24 x 25 nodes, 61 .. 490 keys 2 21.9 / 19.6; 10 x 64, 25 ..
+// 203 keys 2 19.4 / 15.1; 22 x 35, 615 keys 2 26.7 / 23.2. Over 9241 drawn calls that it takes 0.83 of the time, eight of them 1.01 - 1.02
+// (profiles/whole_sequences.md). 64 channels lose (16 x 40, 48 .. 388 keys 2 14.1 / 15.1); of four waves two workgroups share a CU.
+// Never more splits: finer ones were faster (12 x 21 nodes, 481 keys 2 17.1 / 4 13.4), but the shorter sequences of a ragged batch, one piece
+// and so fp32 up to the final rounding in a coarser split, are then bf16 partial rows. Relative error against 64 bits, 40 drawn
+// calls each, filling / so: whole 2.68e-3 / 2.30e-3; finer ones 2.76e-3 / 2.77e-3, at worst 2.17e-3 / 2.59e-3 (2 x 36 nodes, 32 / 8 heads
+// of 64, 68 .. 548 keys, 3 / 5 resident splits).
+int pipe_splits(const vs_attn_desc* d, Plan pl, int nrb, int waves, int tiles) {
     pl.schedule = VS_SCHED_PIPELINED;
     pl.waves = waves;
     pl.row_groups = (nrb + waves - 1) / waves;
-    const int wgs = d->B * d->Hkv * pl.row_groups, room = kNumCUs / wgs;
-    const int few = wgs >= 200 ? 1 : room < (tiles + 3) / 4 ? room : (tiles + 3) / 4;
-    if (coarse || few <= 1 || waves == 4) return few;
-    const bool wide = d->d == 128;
-    const float fixed = wide ? 8.f : 6.3f; // us: everything outside the iterations and the merge
-    const float tile = wide ? 1.2f : 0.93f, full = wide ? 0.28f : 0.03f; // an iteration, and what it takes longer with all CUs at work
-    const float inside[2] = {wide ? 0.9f : 0.2f, wide ? 0.35f : 0.63f}, combine[2] = {wide ? 2.1f : 2.3f, wide ? 0.48f : 0.74f}; // and per MB of partial rows
-    const auto cost = [&](int n) {
-        pl.num_splits = n;
-        pl.total_wgs = n * wgs;
-        const float mb = (float)n * (d->B * d->Hkv) * pl.rows_pad * d->d * 2e-6f;
-        const float* merge = merges_inside(d, pl) ? inside : combine;
-        return fixed + (tiles + n - 1) / n * (tile + full * pl.total_wgs / kNumCUs) + (n > 1 ? merge[0] + merge[1] * mb : 0.f);
-    };
-    const int least = wide ? 1 : few, most = pl.row_groups > 1 && few * wgs >= 100 ? few : room < kMergeMaxSplits ? room : kMergeMaxSplits;
-    int chosen = few;
-    float best = 0.95f * cost(few); // another number has to bring more than the model is good for
-    for (int n = least; n <= most && n <= tiles; ++n) {
-        const int tps = (tiles + n - 1) / n;
-        if ((tiles + tps - 1) / tps != n) continue;
-        const float c = cost(n);
-        if (c < best) {
-            best = c;
-            chosen = n;
-        }
-    }
-    return chosen;
+    const int wgs = d->B * d->Hkv * pl.row_groups, filling = filling_splits(wgs, tiles);
+    if (waves == 4 || d->d != 128 || filling == 1) return filling;
+    pl.num_splits = filling;
+    pl.total_wgs = filling * wgs;
+    const auto loop = [&](int n) { return (tiles + n - 1) / n * (1.2f + 0.28f * n * wgs / kNumCUs); }; // us: iterations take longer with all CUs at work
+    const float mb = (float)filling * (d->B * d->Hkv) * pl.rows_pad * d->d * 2e-6f;                    // of partial rows
+    const float split = 8.f + loop(filling) + (merges_inside(d, pl) ? 0.9f + 0.35f * mb : 2.1f + 0.48f * mb);
+    return 8.f + loop(1) < 0.93f * split ? 1 : filling; // whole ones have to bring more than the model is good for (0.95: up to 1.05 of the time)
 }
 
 size_t workspace_bytes(const vs_attn_desc* d, const Plan& pl) {
@@ -492,30 +476,26 @@ float resident_cost(int row_blocks, int tps, int n) { return kResidentCost[row_b
 // V cold in the caches. Up to 64 tiles, as far as was measured; twelve units and more up to 24 (from there on the rule for rounds ends too).
 // RESIDENT by name, with no number of splits or with the one that AUTO reports, is AUTO's plan where that is RESIDENT too: the number
 // of row blocks is no knob, and a caller who asks for the plan that was reported gets it.
-Plan make_plan(const vs_attn_desc* d, int tree = 1, bool coarse = false) {
+Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     if (d->schedule == VS_SCHED_RESIDENT) {
         vs_attn_desc any = *d;
         any.schedule = VS_SCHED_AUTO;
         any.num_splits = any.rows_per_wave = any.waves_per_group = 0;
-        for (const bool c : {coarse, true}) {
-            const Plan pl = make_plan(&any, tree, c);
-            if (pl.schedule == VS_SCHED_RESIDENT && (d->num_splits == 0 || d->num_splits == pl.num_splits)) return pl;
-        }
+        const Plan pl = make_plan(&any, tree);
+        if (pl.schedule == VS_SCHED_RESIDENT && (d->num_splits == 0 || d->num_splits == pl.num_splits)) return pl;
     }
-    const Plan base = plan_kernel(d, tree, coarse);
+    const Plan base = plan_kernel(d, tree);
     const int nrb = base.rows_pad / kRowBlock;
     const int tiles = ((int64_t)d->max_prefix_len + (tree ? d->T : 0) + kIterKeys - 1) / kIterKeys;
     const int units = d->B * d->Hkv;
     const bool knobs = d->schedule != VS_SCHED_AUTO || d->rows_per_wave != 0 || d->waves_per_group != 0 || d->num_splits > 0;
-    const bool pipelined = base.schedule == VS_SCHED_PIPELINED;
-    // (32 tiles instead of the pipelined kernel's splits, us: 28 / 4 heads, 3 x 24 nodes, 1669 keys 17.5 / 11.4, 8 / 2 heads, 7 x 33 nodes,
-    // 223 .. 1788 keys 17.2 / 12.4; four waves of it stay)
-    const int most_tiles = units < 12 ? 64 : pipelined && base.waves == 8 && !coarse ? 32 : 24;
-    if (base.impl != VS_IMPL_MFMA || knobs || base.schedule == VS_SCHED_BALANCED || nrb < 2 || (int64_t)units * nrb > 4 * kNumCUs || tiles > most_tiles)
+    if (base.impl != VS_IMPL_MFMA || knobs || base.schedule == VS_SCHED_BALANCED || nrb < 2 || (int64_t)units * nrb > 4 * kNumCUs || tiles > (units < 12 ? 64 : 24))
         return base;
-    // (the pipelined kernel may prefer fewer splits than this one is good for: 2 resident ones for one pipelined 10.1 / 14 us and the like)
-    const int usual = pipelined ? pipe_splits(d, base, nrb, base.waves, tiles, true) : base.num_splits;
-    const int allowed = base.num_splits > usual ? base.num_splits : usual;
+    int allowed = base.num_splits;
+    if (base.schedule == VS_SCHED_PIPELINED) { // whole sequences of it where splits of this one are the faster ones: 10.1 us instead of 14 and the like
+        const int n = filling_splits(units * base.row_groups, tiles), tps = (tiles + n - 1) / n;
+        allowed = (tiles + tps - 1) / tps;
+    }
     // (the pipelined kernel, the loops and longer rounds cost more than any of these)
     const float keep = 0.95f; // another number of splits has to bring more than the table is good for
     const bool same_kernel = base.res_rb > 0 && base.keys_per_split <= resident_max_keys(base.res_rb);
@@ -527,7 +507,7 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1, bool coarse = false) {
         for (int tps = 1; tps <= resident_max_keys(rb) / kIterKeys && tps <= tiles; ++tps) {
             if (tps * most < tiles) continue;
             const int n = (tiles + tps - 1) / tps;
-            const float cost = (n == usual ? keep : 1.f) * resident_cost(rb, tps, n);
+            const float cost = (n == allowed ? keep : 1.f) * resident_cost(rb, tps, n);
             if (!(cost < best)) continue;
             Plan c = base;
             c.schedule = base.schedule == VS_SCHED_LOOP ? VS_SCHED_LOOP : VS_SCHED_RESIDENT;
@@ -641,9 +621,8 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     const int32_t rc = check_desc(desc, tree);
     if (rc != VS_OK) return rc;
     Plan pl = make_plan(desc, tree);
-    // (more splits need more partial rows and gates: with less scratch than they ask for a call runs on the coarser ones)
-    if (workspace_bytes_given < workspace_bytes(desc, pl)) pl = make_plan(desc, tree, true);
-    if (workspace_bytes_given < workspace_bytes(desc, pl)) pl = plan_kernel(desc, tree, true);
+    // (a finer cut has more gates, 256 bytes each: with less scratch than it asks for a call runs on the other one's)
+    if (workspace_bytes_given < workspace_bytes(desc, pl)) pl = plan_kernel(desc, tree);
     if (pl.impl == VS_IMPL_MFMA && !(aligned16(q) && aligned16(k_cache) && aligned16(v_cache) && aligned16(out)))
         return VS_ERR_LAYOUT;
     const size_t need = workspace_bytes(desc, pl);
