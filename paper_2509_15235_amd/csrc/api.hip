@@ -528,6 +528,35 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
     return pl;
 }
 
+// K and V as data that is read once (nt loads), where one workgroup alone reads a tile: kernels without row groups that share it, and a contiguous
+// cache in which no two rows are the same memory. Sequences that share a prompt's rows read them from the caches, which such loads
+// pass by, and a block table, of which the host knows nothing, may have it so: us per call, plain / such loads, all
+// sequences on the same rows: 64 x 4 nodes, 28 / 4 heads, 8000 keys paged 56 / 90, half of the keys 121 / 130, contiguous with a sequence stride of 0 53 / 85;
+// 64 x 9, 1024 .. 8191 keys paged 73 / 92; 8 x 60 nodes, 32 / 32 heads, 1024 .. 8191 keys paged 105 / 119. (Paged caches without common blocks gain
+// as much as contiguous ones do; such launches go without.)
+// Such loads come faster from memory and leave less of their data in the caches: faster for who finds nothing there, as the layers of a model, each with
+// a cache of its own, do; not always for who goes over one layer again and again that the 256 MB cache in front of the memory would have held - least so
+// where CUs are idle and each of the others waits for its own loads. Time relative to plain loads, over other data each time / over the
+// same, 6500 drawn calls, by the megabytes of K and V up to the longest allowed prefix and by the CUs' places taken in the last round:
+//   own tiles of one row block < 20 MB 1.1 / 1.00; .. 40 0.96 / 1.00; .. 96 all but a tenth of the places 0.94 / 0.92, less 0.95 / 0.95 (up to 1.10);
+//   .. 192 0.93 / 1.00, less 0.94 / 1.04 (1.24); .. 512 0.91 / 1.01, less 0.92 / 1.04 (1.31); above 0.90 / 0.90 either way;
+//   of two row blocks (long ones have 128 MB or more) .. 512 0.94 / 1.01, less 0.95 / 1.05 (1.26), above 0.90 / 0.90;
+//   four waves of the pipelined kernel .. 256 0.97 / 1.00, .. 512 0.93 / 0.99, above 0.90 / 0.90.
+// (Two row groups of eight waves, which share what they read, 1.03 / 1.04.) So what is too large for any cache, and of the rest what repeats
+// no slower; of two row blocks, whose repetition with all sequences as long takes 1.00
+// (1.12 where all are half as long as allowed and half of the splits have no keys), all that fills the CUs. us per call: 64 x 4 nodes, 28 / 4 heads, 8000 keys 184 / 162;
+// 4 x 60 nodes, 32 / 32 heads, 2880 .. 3392 keys, one layer of 32 45.1 / 40.7; 8 x 60, 1024 .. 8191 keys 159 / 139; 20 x 60, 2000 keys 155 / 132
+bool reads_once(const vs_attn_desc* d, const Plan& pl, int tree) {
+    const bool four = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) && pl.waves == 4;
+    if (d->paged || pl.row_groups != 1 || !(pl.own_tiles || four)) return false;
+    const int64_t keys = (int64_t)d->max_prefix_len + (tree ? d->T : 0);
+    if (!rows_apart(d->d, keys, d->stride_tok, d->Hkv, d->stride_head, d->B, d->stride_seq)) return false;
+    const double mb = (double)d->B * d->Hkv * keys * d->d * 4e-6;
+    const int places = kNumCUs * (pl.waves == 8 ? 1 : 2), rounds = (pl.total_wgs + places - 1) / places;
+    const bool filled = pl.total_wgs >= 0.9 * rounds * places;
+    return mb >= (filled ? 512 : 768) || (filled && ((pl.own_tiles == 1 && mb >= 40 && mb < 96) || (pl.own_tiles == 2 && mb >= 128)));
+}
+
 int32_t draft_chunks(int32_t V, int32_t vec) { return (int32_t)(((int64_t)V + vec * kDraftVec - 1) / (vec * kDraftVec)); }
 // Chunks of 8192 logits; of 10240 or 12288 where those of 8192 are more workgroups than there are CUs and these are not: the CUs with
 // two of them hold up the sequence's last part. us, three levels and the selection, chunks of 8192 / chosen so:
@@ -545,6 +574,10 @@ int32_t accept_chunks(int32_t V) { return (V + kAcceptChunk - 1) / kAcceptChunk;
 extern "C" {
 
 void vs_internal_set_merge_wait(uint32_t ticks) { merge_wait = ticks; }
+int32_t vs_internal_reads_once(const vs_attn_desc* desc, int32_t tree) {
+    const int32_t rc = check_desc(desc, tree);
+    return rc != VS_OK ? rc : reads_once(desc, make_plan(desc, tree), tree);
+}
 
 int32_t vs_version(void) { return VS_VERSION; }
 
@@ -691,25 +724,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
     p.by_length = (pl.schedule == VS_SCHED_PIPELINED || pl.own_tiles) && desc->max_prefix_len >= by_length_from && pl.num_splits == 1 &&
                   desc->B >= 2 && desc->B <= kBalMaxSeqs && pl.total_wgs > kNumCUs * (pl.waves == 8 ? 1 : 2) &&
                   !(pl.schedule == VS_SCHED_PIPELINED && pipe_three_per_cu(desc->d, pl.waves, pl.total_wgs));
-    // K and V as data that is read once (nt loads), where one workgroup alone reads a tile. Such loads come faster from memory and leave
-    // less of their data in the caches: faster for who finds nothing there, as the layers of a model, each with a cache of its own, do; not
-    // always for who goes over one layer again and again that the 256 MB cache in front of the memory would have held - least so
-    // where CUs are idle and each of the others waits for its own loads. Time relative to plain loads, over other data each time / over the
-    // same, 6500 drawn calls, by the megabytes of K and V up to the longest allowed prefix and by the CUs' places taken in the last round:
-    //   own tiles of one row block < 20 MB 1.1 / 1.00; .. 40 0.96 / 1.00; .. 96 all but a tenth of the places 0.94 / 0.92, less 0.95 / 0.95 (up to 1.10);
-    //   .. 192 0.93 / 1.00, less 0.94 / 1.04 (1.24); .. 512 0.91 / 1.01, less 0.92 / 1.04 (1.31); above 0.90 / 0.90 either way;
-    //   of two row blocks (long ones have 128 MB or more) .. 512 0.94 / 1.01, less 0.95 / 1.05 (1.26), above 0.90 / 0.90;
-    //   four waves of the pipelined kernel .. 256 0.97 / 1.00, .. 512 0.93 / 0.99, above 0.90 / 0.90.
-    // (Two row groups of eight waves, which share what they read, 1.03 / 1.04.) So what is too large for any cache, and of the rest what repeats
-    // no slower; of two row blocks, whose repetition with all sequences as long takes 1.00, all that fills the CUs. us per call: 64 x 4 nodes, 28 / 4 heads, 8000 keys 178 / 157;
-    // 4 x 60 nodes, 32 / 32 heads, 2880 .. 3392 keys, one layer of 32 45.1 / 40.7; 8 x 60, 1024 .. 8191 keys 108 / 91; 20 x 60, 2000 keys 152 / 129
-    const bool four = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) && pl.waves == 4;
-    if (pl.row_groups == 1 && (pl.own_tiles || four)) {
-        const double mb = (double)desc->B * desc->Hkv * ((double)desc->max_prefix_len + p.tree_keys) * desc->d * 4e-6;
-        const int places = kNumCUs * (pl.waves == 8 ? 1 : 2), rounds = (pl.total_wgs + places - 1) / places;
-        const bool filled = pl.total_wgs >= 0.9 * rounds * places;
-        p.once = mb >= (filled ? 512 : 768) || (filled && ((pl.own_tiles == 1 && mb >= 40 && mb < 96) || (pl.own_tiles == 2 && mb >= 128)));
-    }
+    p.once = reads_once(desc, pl, tree);
     if (need > 0) {
         const size_t prow = partial_rows(desc, pl);
         p.part_o = (uint16_t*)workspace;

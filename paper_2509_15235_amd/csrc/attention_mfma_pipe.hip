@@ -1053,23 +1053,22 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void attn_mfma
     }
 }
 
-template <int D, int RPW, int NW, bool BAL, bool ONCE>
+template <int D, int RPW, int NW, bool BAL, bool MAY>
 void launch_pipe(const AttnParams& p, dim3 grid, hipStream_t s) {
-    if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, BAL, ONCE>), grid, dim3(NW * kWave), 0, s, p);
-    else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, BAL, ONCE>), grid, dim3(NW * kWave), 0, s, p);
+    if (p.once) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, BAL, MAY>), grid, dim3(NW * kWave), 0, s, p);
+    else if (p.paged) hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, true, BAL, false>), grid, dim3(NW * kWave), 0, s, p);
+    else hipLaunchKernelGGL((attn_mfma_pipe_kernel<D, RPW, NW, false, BAL, false>), grid, dim3(NW * kWave), 0, s, p);
 }
 template <int D, int RPW, int NW>
 hipError_t launch_pipe(const AttnParams& p, hipStream_t s) {
     constexpr bool MAY = NW == 4; // eight waves gain 1 - 2 % from it where they are one row group, and lose 3 - 5 % where they are two
-    if (p.once && !MAY) return hipErrorInvalidValue;
+    if (p.once && (p.paged || !MAY)) return hipErrorInvalidValue;
     if (p.bal_chunks > 0) {
         const dim3 grid(((p.bal_chunks * p.Hkv + 7) / 8) * 8 * p.row_groups);
-        if (p.once) launch_pipe<D, RPW, NW, true, MAY>(p, grid, s);
-        else launch_pipe<D, RPW, NW, true, false>(p, grid, s);
+        launch_pipe<D, RPW, NW, true, MAY>(p, grid, s);
     } else {
         const dim3 grid(p.by_length ? (p.B * p.Hkv + 7) / 8 * 8 * p.row_groups : (p.total_wgs + 7) / 8 * 8);
-        if (p.once) launch_pipe<D, RPW, NW, false, MAY>(p, grid, s);
-        else launch_pipe<D, RPW, NW, false, false>(p, grid, s);
+        launch_pipe<D, RPW, NW, false, MAY>(p, grid, s);
     }
     return hipGetLastError();
 }

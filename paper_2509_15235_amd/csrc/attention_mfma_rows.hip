@@ -404,16 +404,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     if (merge) merge_splits<D>(p, gate, b, kvh, block0, block0 + RB, split, (nk + p.keys_per_split - 1) / p.keys_per_split, NW, (uint32_t*)sp);
 }
 
-template <int D, int NW, int RB, bool ONCE>
-hipError_t launch_rows(const AttnParams& p, hipStream_t s) {
-    const dim3 grid(((p.total_wgs + 7) / 8) * 8);
-    if (p.paged) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, true, ONCE>), grid, dim3(NW * kWave), 0, s, p);
-    else hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false, ONCE>), grid, dim3(NW * kWave), 0, s, p);
-    return hipGetLastError();
-}
 template <int D, int NW, int RB>
 hipError_t launch_rows(const AttnParams& p, hipStream_t s) {
-    return p.once ? launch_rows<D, NW, RB, true>(p, s) : launch_rows<D, NW, RB, false>(p, s);
+    const dim3 grid(((p.total_wgs + 7) / 8) * 8);
+    if (p.once && p.paged) return hipErrorInvalidValue;
+    if (p.once) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false, true>), grid, dim3(NW * kWave), 0, s, p);
+    else if (p.paged) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, true, false>), grid, dim3(NW * kWave), 0, s, p);
+    else hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false, false>), grid, dim3(NW * kWave), 0, s, p);
+    return hipGetLastError();
 }
 
 } // namespace

@@ -66,4 +66,24 @@ constexpr uint32_t row_number(int32_t r, int32_t node, int32_t skip) { return (u
 // paged cache's table can name any number of keys, and so can the splits of 64 that a caller asks for.
 constexpr int64_t piece_elements(int32_t piece, int32_t num_splits) { return (int64_t)piece * num_splits * 512; }
 
+// Whether no two rows of `row` elements are the same memory, or parts of it, that lie at a * sa + b * sb + c * sc elements, a < na and so on:
+// in the order of their strides, each index has to step over all that the ones before it reach. (Rows that interleave otherwise count as
+// not apart.) In double: exact below 2^53, and no stride wraps.
+constexpr bool rows_apart(int64_t row, int64_t na, int64_t sa, int64_t nb, int64_t sb, int64_t nc, int64_t sc) {
+    int64_t n[3] = {na, nb, nc}, s[3] = {sa, sb, sc};
+    double reach = (double)row;
+    for (int i = 0; i < 3; ++i) {
+        int least = i;
+        for (int j = i + 1; j < 3; ++j)
+            if (s[j] < s[least]) least = j;
+        const int64_t count = n[least], stride = s[least];
+        n[least] = n[i];
+        s[least] = s[i];
+        if (count <= 1) continue;
+        if ((double)stride < reach) return false;
+        reach += (double)stride * (double)(count - 1);
+    }
+    return true;
+}
+
 } // namespace vs

@@ -71,7 +71,7 @@ struct AttnParams {
     int32_t rows_per_group;     // waves_per_group * row blocks per wave * kRowBlock
     int32_t total_wgs;          // B * Hkv * num_splits * row_groups
     FastDiv by_splits, by_groups, by_heads; // workgroup id -> (sequence, KV head, row group, split)
-    int32_t once;               // own tiles, four waves of the pipelined kernel: K and V as data that is read once
+    int32_t once;               // own tiles, four waves of the pipelined kernel, no block table: K and V as data that is read once
     int32_t by_length;          // pipelined kernel without key splits: workgroups take the sequences longest first
     int32_t bal_chunks;         // balanced schedule: equal shares of the batch's keys per (KV head, row group); else 0.
                                 // num_splits then counts partial-result slots per KV head (shares + sequences)
@@ -186,6 +186,8 @@ inline int32_t validate_tree_host(const int32_t* parent, int32_t T) {
 
 // How long a workgroup waits at a gate before it hands its share over, in launches of the calling thread: 20 us. Tests set it to 0.
 extern "C" void vs_internal_set_merge_wait(uint32_t ticks);
+// Whether a call with this descriptor loads K and V as data that is read once (1 or 0; or a vs_error): for tests, the plan does not say.
+extern "C" int32_t vs_internal_reads_once(const vs_attn_desc* desc, int32_t tree);
 
 int32_t check_device(); // VS_OK when the current device is a gfx950, else VS_ERR_NO_DEVICE (api.hip)
 

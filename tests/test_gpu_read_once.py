@@ -1,6 +1,8 @@
 """Launches that load K and V as data that is read once (large ones whose tiles one workgroup alone reads): own tiles of one and two row
-blocks, four waves of the pipelined kernel on whole sequences and on balanced shares. Against fp64 sums of some (sequence, KV head) units;
-what the caches hold behind a sequence's last key is NaN."""
+blocks, four waves of the pipelined kernel on whole sequences and on balanced shares; and the same launches on paged caches, which load them
+as any other data. Against fp64 sums of some (sequence, KV head) units; what the caches hold behind a sequence's last key is NaN."""
+import ctypes
+
 import pytest
 
 import paper_2509_15235_amd as vs
@@ -43,6 +45,7 @@ def test_against_fp64(B, T, Hq, Hkv, d, longest, paged, schedule, waves):
         desc.capacity, desc.stride_seq, desc.stride_head = longest + T, Hkv * (longest + T) * d, (longest + T) * d
     rc, plan = vs.vs_attention_plan(desc)
     assert rc == 0 and plan.schedule == schedule and plan.waves_per_group == waves and plan.row_groups == 1
+    assert vs.lib().vs_internal_reads_once(ctypes.byref(desc), 1) == (0 if paged else 1)
     need = vs.vs_attention_workspace_bytes(desc)
     ws = torch.empty(max(need, 256), device="cuda", dtype=torch.uint8).random_(0, 256)
     out = torch.full((B, T, Hq, d), float("nan"), device="cuda", dtype=torch.bfloat16)
