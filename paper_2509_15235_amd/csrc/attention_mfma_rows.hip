@@ -178,13 +178,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
         }
     }
     const bool s_ok = prefix_ok(p, S);
-    if (kvh == 0 && split == 0 && rg == 0) report_status(p, b, tree_code, s_ok, S, &sflag);
+    if (kvh == 0 && split == 0 && rg == 0) report_status<PAGED>(p, b, tree_code, s_ok, S, &sflag);
     if (tree_code != VS_STATUS_OK || !s_ok) return;
     const int nk = S + p.tree_keys;
     if (k0 >= nk) return;
     const bool final_rows = p.num_splits == 1 || (p.gates && nk <= p.keys_per_split); // a sequence of one split has nothing to merge
     const bool merge = p.gates && !final_rows;
-    if (merge && tid == 0) merge_open(gate, seen);
+    if (merge && tid == 0) [[unlikely]] merge_open(gate, seen); // (most waves only jump over it)
     const int k1 = min(nk, k0 + p.keys_per_split);
 
 #pragma unroll
@@ -203,15 +203,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
         v_lane[db] = v_row * D + ((4 * db + 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1)) ^ vx(v_row)) * 8 + (lane & 1) * 4;
     float m2[RB], lsum[RB]; // reference (log2 domain, scaled; -inf: no visible key yet), this lane's share of the sum
     f32x16 acc[RB][DB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        m2[rb] = -INFINITY;
-        lsum[rb] = 0.f;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[rb][db][q] = 0.f;
-    }
     bf16x8 qf[QREG ? RB : 1][KS];
     if constexpr (QREG) {
 #pragma unroll
@@ -274,7 +265,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
                         for (int q = 0; q < 16; ++q) acc[rb][db][q] *= alpha;
                 }
             }
-            lsum[rb] += ps0 + ps1;
+            lsum[rb] = FIRST ? ps0 + ps1 : lsum[rb] + (ps0 + ps1);
             m2[rb] = m_new;
 #pragma unroll
             for (int sl = 0; sl < 2; ++sl) {
@@ -304,7 +295,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(sV + v_lane[db] + sl * (16 * D) + 8 * D));
                 const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) acc[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[rb][sl], acc[rb][db], 0, 0, 0);
+                for (int rb = 0; rb < RB; ++rb)
+                    acc[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[rb][sl], FIRST && sl == 0 ? f32x16{} : acc[rb][db], 0, 0, 0);
             }
         if (next < k1) {
             wait_lds_reads();
@@ -314,6 +306,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
     if (first < k1) {
         tile(std::true_type{}, first);
         for (int kt = first + ROUND; kt < k1; kt += ROUND) tile(std::false_type{}, kt);
+    } else {
+        // A wave without a tile adds nothing. Written here and from a register that the compiler knows nothing about: constants it wrote in front
+        // of the branch, where every wave with a tile waited for 64 of them (128 for two row blocks). Those and the code that rarely runs,
+        // in the way to the first tile, took 0.1 - 0.2 us of the shortest calls: us per call with both / without, 28 / 4 heads, 2 x 3 nodes, 201
+        // keys 6.06 / 5.89; 7 x 3, 378 keys 6.47 / 6.36; 1 x 4, 484 keys 7.28 / 7.12; 40 x 2, 32 / 32 heads, 250 keys 26.5 / 26.3.
+        float zero = 0.f;
+        asm volatile("" : "+v"(zero));
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            m2[rb] = -INFINITY;
+            lsum[rb] = 0.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) acc[rb][db][q] = zero;
+        }
     }
     wait_loads<0>(); // (a wave without a live tile may have requested one)
 

@@ -248,12 +248,14 @@ __device__ __forceinline__ int64_t token_offset(const AttnParams& p, int b, int 
 
 // The workgroup that owns a sequence's status entry calls this (all of its threads):
 // writes tree / prefix problems, otherwise scans the block-table entries in use.
+// PAGED false: a kernel for contiguous caches, without the code for a block table.
+template <bool PAGED = true>
 __device__ __forceinline__ void report_status(const AttnParams& p, int b, int32_t tree_code,
                                               bool s_ok, int32_t S, int32_t* sflag) {
     if (!p.status) return;
     int32_t code = tree_code;
     if (code == VS_STATUS_OK && !s_ok) code = VS_STATUS_BAD_PREFIX;
-    if (code == VS_STATUS_OK && p.paged) {
+    if (PAGED && code == VS_STATUS_OK && p.paged) {
         // *sflag is 0 here (load_tree leaves it 0 for a valid tree)
         const int nblk = (S + p.tree_keys + p.block_size - 1) >> p.block_shift;
         for (int i = threadIdx.x; i < nblk; i += blockDim.x) {
