@@ -284,6 +284,7 @@ __device__ __forceinline__ int64_t ml_block(const AttnParams& p, int64_t unit, i
 // 12.41 / 12.27; 3600 drawn calls with two and more splits, geometric mean 0.974, one in a hundred of them - many splits that come in one
 // by one, where the looks hold up the arrivals - 1.01 to 1.04. Fewer looks while many are still missing were 0.3 % slower in the mean.)
 // The call before on the same workspace has ended (calls that share one are ordered), so the word is at rest.
+// Word kGateHanded of the gate counts the shares handed over (from any value, not read here: for tests and whoever looks for slow merges).
 static_assert(kMergeMaxSplits == 32, "bits of the abandoned set");
 constexpr uint64_t kMergeTag = 0xffc3a9ull;           // no partial result or (max, sum) pair looks like this (a NaN)
 static_assert(kMergeTag != kArrivalZero >> 40, "an arrival word that vs_draft_expand left in a shared workspace is no gate");
@@ -309,18 +310,18 @@ __device__ __forceinline__ uint32_t merge_meet(uint64_t* gate, uint32_t wait, in
     }
     const auto all = [&](uint64_t w) { return (int)(w & 0xff) == 0 || (int)(w & 0xff) == n; };
     const uint64_t t0 = wall_clock64();
-    uint32_t looks = 0;
-    for (uint64_t w; !all(w = gate_load(gate));) {
-        if ((++looks & 7) != 0 || wall_clock64() - t0 <= wait) continue; // (the clock takes as long as a look)
-        do {
-            if (__hip_atomic_compare_exchange_strong(gate, &w, w | (256ull << split), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT)) {
-                go = false;
-                return 0;
-            }
-        } while (!all(w));
-        break; // the last one has come in the meantime
+    uint64_t w = old + 1;
+    for (uint32_t looks = 0; wait != 0;) { // (a wait of zero: without a look)
+        if (all(w = gate_load(gate))) return 0;
+        if ((++looks & 7) == 0 && wall_clock64() - t0 > wait) break; // (the clock takes as long as a look)
     }
+    do {
+        if (__hip_atomic_compare_exchange_strong(gate, &w, w | (256ull << split), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            __hip_atomic_fetch_add(gate + kGateHanded, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            go = false;
+            return 0;
+        }
+    } while (!all(w)); // else the last one has come in the meantime
     return 0;
 }
 // Half a piece (eight channels of the 32 rows of a row block, see store_partial: the 32 lanes of one half of the

@@ -31,6 +31,7 @@ constexpr int kBalMaxSeqs = 64;   // balanced schedule: sequences per call (a la
 constexpr int kBalMaxChunks = 64; // ... and shares per (KV head, row group)
 constexpr int kMergeMaxSplits = 32; // key splits that the workgroups themselves merge (attn_mfma_common.h)
 constexpr int kGateWords = 32;      // 64-bit words of a row group's gate, the first of which counts: gates share no cache line
+constexpr int kGateHanded = 16;     // ... and the one that counts shares handed over, in a line of its own
 constexpr int kRoundKeys = 128;       // keys of a round (attention_mfma_rounds.hip)
 constexpr int kResidentMaxKeys = 192; // keys of one split that the resident attention kernel keeps in LDS
 constexpr int resident_max_keys(int row_blocks) { return row_blocks <= 2 ? 256 : kResidentMaxKeys; } // ... with so many row blocks to a workgroup

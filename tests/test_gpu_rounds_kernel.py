@@ -101,6 +101,25 @@ def test_merge_words_between_calls(oracle_mod):
                     gu.check_close(got[b], ref[b], *TIGHT_SHORT, what=f"pass {rep} sequence {b}")
 
 
+def _hand_over(da, gates, want):
+    """Four calls in which nobody waits, equal to `want`, shares handed over in each; and one as usual."""
+    import torch
+    words = da.ws[da.ws_bytes - gates * 256:da.ws_bytes].view(torch.int64).view(gates, 32)   # behind the partial results, 256 bytes each
+    handed = []
+    try:
+        vs.lib().vs_internal_set_merge_wait(0)
+        for _ in range(4):
+            words.zero_()
+            np.testing.assert_array_equal(da.run(), want)
+            handed.append(int(words[:, 16].sum()))   # every gate's count of shares handed over
+            at_rest = words[:, 0] == (0xffc3a9 << 40) - (1 << 64)
+            assert (at_rest | (words[:, 0] == 0)).all() and at_rest.any()   # (sequences of one split leave theirs alone)
+    finally:
+        vs.lib().vs_internal_set_merge_wait(2000)
+    assert min(handed) > 0, handed
+    np.testing.assert_array_equal(da.run(), want)
+
+
 @pytest.mark.parametrize("kw", [{}, dict(schedule=vs.VS_SCHED_RESIDENT), dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=8, num_splits=10),
                                 dict(schedule=vs.VS_SCHED_PIPELINED, waves_per_group=4, num_splits=7)])
 def test_shares_handed_over(oracle_mod, kw):
@@ -113,13 +132,7 @@ def test_shares_handed_over(oracle_mod, kw):
     assert pl.num_splits > 1 and pl.combine == 1
     assert da.ws_bytes == 2 * 4 * pl.num_splits * 448 * (128 * 2 + 8) + 2 * 4 * pl.row_groups * 256   # partial results and gates
     want = da.run()
-    try:
-        vs.lib().vs_internal_set_merge_wait(0)
-        for _ in range(4):
-            np.testing.assert_array_equal(da.run(), want)
-    finally:
-        vs.lib().vs_internal_set_merge_wait(2000)
-    np.testing.assert_array_equal(da.run(), want)
+    _hand_over(da, 2 * 4 * pl.row_groups, want)
 
 
 @pytest.mark.parametrize("Hq,Hkv,T,lens,wgs", [(28, 4, 60, [1100, 421, 2000], 216),      # eight waves, nine splits, two row groups
@@ -140,10 +153,4 @@ def test_shares_of_the_pipelined_kernel_handed_over(oracle_mod, Hq, Hkv, T, lens
     ref = oracle_mod.tree_attention(inp, threads=8)
     for b in range(len(lens)):
         gu.check_close(want[b], ref[b], *(TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT), what=f"sequence {b} of {lens[b]}")
-    try:
-        vs.lib().vs_internal_set_merge_wait(0)
-        for _ in range(4):
-            np.testing.assert_array_equal(da.run(), want)
-    finally:
-        vs.lib().vs_internal_set_merge_wait(2000)
-    np.testing.assert_array_equal(da.run(), want)
+    _hand_over(da, len(lens) * Hkv * pl.row_groups, want)
