@@ -731,6 +731,7 @@ int32_t enqueue_attention(const vs_attn_desc* desc, int tree, const void* q, con
         p.part_ml = (float*)((char*)workspace + align_up(prow * desc->d * sizeof(uint16_t)));
         char* behind = (char*)p.part_ml + align_up(prow * 2 * sizeof(float));
         if (merges_inside(desc, pl)) p.gates = (uint64_t*)behind;
+        p.crowd = pl.num_splits >= 28 && pl.total_wgs >= 224 && (pl.rounds || (pl.own_tiles == 1 && pl.waves == 8)); // why there: attn_mfma_common.h
         p.merge_wait = merge_wait;
     }
     hipStream_t s = (hipStream_t)stream;

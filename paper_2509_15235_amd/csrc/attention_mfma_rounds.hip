@@ -23,7 +23,8 @@ namespace {
 
 constexpr int kRndWaves = 8;
 
-template <int D, int NRB, bool PAGED>
+// CROWD: many splits on nearly all CUs, whose workgroups wait for each other at another word (merge_meet).
+template <int D, int NRB, bool PAGED, bool CROWD>
 __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(const AttnParams p) {
     request_args(p);
     constexpr int NT = kRoundKeys / kTileKeys; // tiles of a round
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
     }
     if (merge) {
         const int nrb = p.rows_pad / kRowBlock, rb0 = rg * NRB;
-        merge_splits<D>(p, gate, b, kvh, rb0, min(rb0 + NRB, nrb), split, (nk + p.keys_per_split - 1) / p.keys_per_split, kRndWaves,
+        merge_splits<D, CROWD>(p, gate, b, kvh, rb0, min(rb0 + NRB, nrb), split, (nk + p.keys_per_split - 1) / p.keys_per_split, kRndWaves,
                         (uint32_t*)sp);
     }
 }
@@ -478,8 +479,11 @@ __global__ __launch_bounds__(kRndWaves * 64, 2) void attn_mfma_rounds_kernel(con
 template <int D, int NRB>
 hipError_t launch_rnd(const AttnParams& p, hipStream_t s) {
     const dim3 grid(((p.total_wgs + 7) / 8) * 8);
-    if (p.paged) hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, true>), grid, dim3(kRndWaves * kWave), 0, s, p);
-    else hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, false>), grid, dim3(kRndWaves * kWave), 0, s, p);
+    const dim3 block(kRndWaves * kWave);
+    if (p.paged && p.crowd) hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, true, true>), grid, block, 0, s, p);
+    else if (p.paged) hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, true, false>), grid, block, 0, s, p);
+    else if (p.crowd) hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, false, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((attn_mfma_rounds_kernel<D, NRB, false, false>), grid, block, 0, s, p);
     return hipGetLastError();
 }
 

@@ -30,7 +30,8 @@ namespace {
 // tiles too: 4 x 60 nodes, 32 / 32 heads, 3100 keys 39.7 -> 39.2 us, one sequence of 484 keys and four nodes 7.4 -> 7.2.)
 // ONCE: tiles as data that is read once (the host's rule says when). Part of the kernel as well: a branch at every load 5 % of two row blocks'
 // time, a loop of its own for either kind 3 % of a short call's.
-template <int D, int NW, int RB, bool PAGED, bool ONCE>
+// CROWD: many splits on nearly all CUs, whose workgroups wait for each other at another word (merge_meet).
+template <int D, int NW, int RB, bool PAGED, bool ONCE, bool CROWD = false>
 __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnParams p) {
     constexpr int KS = D / 16;          // k-steps of the S^T product
     constexpr int DB = D / 32;          // 32-channel blocks of the output
@@ -409,13 +410,19 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_mfma_rows_kernel(const AttnPa
             }
         }
     }
-    if (merge) merge_splits<D>(p, gate, b, kvh, block0, block0 + RB, split, (nk + p.keys_per_split - 1) / p.keys_per_split, NW, (uint32_t*)sp);
+    if (merge) merge_splits<D, CROWD>(p, gate, b, kvh, block0, block0 + RB, split, (nk + p.keys_per_split - 1) / p.keys_per_split, NW, (uint32_t*)sp);
 }
 
 template <int D, int NW, int RB>
 hipError_t launch_rows(const AttnParams& p, hipStream_t s) {
     const dim3 grid(((p.total_wgs + 7) / 8) * 8);
     if (p.once && p.paged) return hipErrorInvalidValue;
+    if constexpr (NW == 8 && RB == 1)
+        if (p.crowd) {
+            if (p.paged) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, true, false, true>), grid, dim3(NW * kWave), 0, s, p);
+            else hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false, false, true>), grid, dim3(NW * kWave), 0, s, p);
+            return hipGetLastError();
+        }
     if (p.once) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false, true>), grid, dim3(NW * kWave), 0, s, p);
     else if (p.paged) hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, true, false>), grid, dim3(NW * kWave), 0, s, p);
     else hipLaunchKernelGGL((attn_mfma_rows_kernel<D, NW, RB, false, false>), grid, dim3(NW * kWave), 0, s, p);

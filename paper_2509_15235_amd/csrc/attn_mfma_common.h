@@ -281,8 +281,13 @@ __device__ __forceinline__ int64_t ml_block(const AttnParams& p, int64_t unit, i
 // and is replaced before the first arrival; the last arrival puts it back to zero. So who has arrived and finds n arrivals, or
 // none, knows that all have. (They waited for a second word that the last one changed once its own arrival had returned: us per
 // call, before / so, 28 / 4 heads, 60 nodes, 1696 keys, 28 layers 291.0 / 284.5; 32 / 8 heads of 64, 8 x 31 nodes, up to 2047 keys
-// 12.41 / 12.27; 3600 drawn calls with two and more splits, geometric mean 0.974, one in a hundred of them - many splits that come in one
-// by one, where the looks hold up the arrivals - 1.01 to 1.04. Fewer looks while many are still missing were 0.3 % slower in the mean.)
+// 12.41 / 12.27; 4757 drawn calls with two and more splits, geometric mean 0.976. Fewer looks while many are still missing, or pauses between
+// them, were slower in the mean.)
+// Where many wait on nearly all CUs, their looks hold up those who arrive. So 28 splits and more on 224 workgroups (CROWD) have a second word to look
+// at, in another cache line, which the last one changes, from any value; it is read ahead of the wait for the partial results. Drawn calls, time
+// relative to two words from the start, one word / two so: rounds of four row blocks, 16 .. 19 splits 0.989 / 0.992, 24 .. 27 1.004 / 1.002, 28 .. 31
+// 1.023 (up to 1.15) / 1.002, 32 1.047 / 1.001; own tiles 16 .. 19 0.991 / 1.020, 28 .. 31 1.029 (1.11) / 1.000. The resident kernel's merges wait
+// less and gain by one word to the end (28 .. 31 splits 0.986). One sequence, 58 nodes, 16 / 1 heads, 7960 keys 17.2 / 15.2 us.
 // The call before on the same workspace has ended (calls that share one are ordered), so the word is at rest.
 // Word kGateHanded of the gate counts the shares handed over (from any value, not read here: for tests and whoever looks for slow merges).
 static_assert(kMergeMaxSplits == 32, "bits of the abandoned set");
@@ -301,20 +306,24 @@ __device__ __forceinline__ void merge_open(uint64_t* gate, uint64_t seen) {
 }
 // Thread 0, after every wave's partial results are in memory. Returns the splits whose shares this workgroup
 // has to merge besides its own; `go` false: its own share was handed over.
-__device__ __forceinline__ uint32_t merge_meet(uint64_t* gate, uint32_t wait, int split, int n, bool& go) {
+// CROWD: who waits looks at word kGateFlag, which was `flag` before this workgroup arrived and which the last one changes, see above.
+template <bool CROWD>
+__device__ __forceinline__ uint32_t merge_meet(uint64_t* gate, uint64_t flag, uint32_t wait, int split, int n, bool& go) {
     go = true;
     const uint64_t old = __hip_atomic_fetch_add(gate, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((int)(old & 0xff) == n - 1) {
         __hip_atomic_store(gate, kMergeZero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (CROWD) __hip_atomic_store(gate + kGateFlag, flag + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return (uint32_t)(old >> 8);
     }
     const auto all = [&](uint64_t w) { return (int)(w & 0xff) == 0 || (int)(w & 0xff) == n; };
     const uint64_t t0 = wall_clock64();
     uint64_t w = old + 1;
     for (uint32_t looks = 0; wait != 0;) { // (a wait of zero: without a look)
-        if (all(w = gate_load(gate))) return 0;
+        if (CROWD ? gate_load(gate + kGateFlag) != flag : all(w = gate_load(gate))) return 0;
         if ((++looks & 7) == 0 && wall_clock64() - t0 > wait) break; // (the clock takes as long as a look)
     }
+    if (CROWD && wait != 0 && all(w = gate_load(gate))) return 0;
     do {
         if (__hip_atomic_compare_exchange_strong(gate, &w, w | (256ull << split), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
             __hip_atomic_fetch_add(gate + kGateHanded, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -436,7 +445,7 @@ __device__ __forceinline__ void merge_run_few(const MergeItem (&it)[kMergeGroup]
 // the row group, n >= 2; `s_word` is two words of LDS that nobody else uses any more. What an item costs is the trip
 // to memory (0.7 us), so a wave that has several - few splits, many rows - takes up to four at once: 192 rows in two
 // splits 23.6 -> 19.2 us (23 sequences of up to 290 keys); one sequence of five row blocks and splits 12.3 -> 11.4.
-template <int D>
+template <int D, bool CROWD = false>
 __device__ __forceinline__ void merge_splits(const AttnParams& p, uint64_t* gate, int b, int kvh, int rb0, int rb1, int split, int n,
                                              int waves, uint32_t* s_word) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -463,11 +472,13 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, uint64_t* gate
     const uint16_t* po = p.part_o + part_block<D>(p, unit, 0, rb0);
     int i = split + n * wave;
     if (i < items) gather(i);
+    uint64_t flag = 0;
+    if (CROWD && wave == 0) flag = gate_load(gate + kGateFlag); // arrives with what the partial results are waited for
     __builtin_amdgcn_s_waitcnt(wait_vm(0)); // this wave's partial results are in memory
     __syncthreads();
     if (tid == 0) {
         bool go;
-        s_word[0] = merge_meet(gate, p.merge_wait, split, n, go);
+        s_word[0] = merge_meet<CROWD>(gate, flag, p.merge_wait, split, n, go);
         s_word[1] = go;
     }
     __syncthreads();

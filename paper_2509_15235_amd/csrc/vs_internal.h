@@ -31,7 +31,8 @@ constexpr int kBalMaxSeqs = 64;   // balanced schedule: sequences per call (a la
 constexpr int kBalMaxChunks = 64; // ... and shares per (KV head, row group)
 constexpr int kMergeMaxSplits = 32; // key splits that the workgroups themselves merge (attn_mfma_common.h)
 constexpr int kGateWords = 32;      // 64-bit words of a row group's gate, the first of which counts: gates share no cache line
-constexpr int kGateHanded = 16;     // ... and the one that counts shares handed over, in a line of its own
+constexpr int kGateFlag = 16;       // ... what many who wait look at instead, in another cache line
+constexpr int kGateHanded = 24;     // ... the count of shares handed over
 constexpr int kRoundKeys = 128;       // keys of a round (attention_mfma_rounds.hip)
 constexpr int kResidentMaxKeys = 192; // keys of one split that the resident attention kernel keeps in LDS
 constexpr int resident_max_keys(int row_blocks) { return row_blocks <= 2 ? 256 : kResidentMaxKeys; } // ... with so many row blocks to a workgroup
@@ -51,6 +52,7 @@ struct AttnParams {
     float* part_ml;             // [unit][row block][split][32][2] running max (log2 domain), sum
     uint64_t* gates;            // a word per (unit, row group): the splits are merged by the workgroups that
                                 // computed them (attn_mfma_common.h); null: by the combine kernel
+    int32_t crowd;              // rounds, own tiles of one row block: a second word to look at, see attn_mfma_common.h
     uint32_t merge_wait;        // how long a workgroup waits for the others at a gate (ticks of 10 ns)
     int32_t B, T, Hq, Hkv, d, group;
     int32_t tree_keys;          // T when the queries' own K/V sit behind the prefix (verification), 0 when they

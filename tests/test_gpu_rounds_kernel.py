@@ -111,7 +111,7 @@ def _hand_over(da, gates, want):
         for _ in range(4):
             words.zero_()
             np.testing.assert_array_equal(da.run(), want)
-            handed.append(int(words[:, 16].sum()))   # every gate's count of shares handed over
+            handed.append(int(words[:, 24].sum()))   # every gate's count of shares handed over
             at_rest = words[:, 0] == (0xffc3a9 << 40) - (1 << 64)
             assert (at_rest | (words[:, 0] == 0)).all() and at_rest.any()   # (sequences of one split leave theirs alone)
     finally:
@@ -153,4 +153,27 @@ def test_shares_of_the_pipelined_kernel_handed_over(oracle_mod, Hq, Hkv, T, lens
     ref = oracle_mod.tree_attention(inp, threads=8)
     for b in range(len(lens)):
         gu.check_close(want[b], ref[b], *(TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT), what=f"sequence {b} of {lens[b]}")
+    _hand_over(da, len(lens) * Hkv * pl.row_groups, want)
+
+
+@pytest.mark.parametrize("T,Hq,Hkv,d,paged,lens", [(62, 16, 1, 128, True, [7875]), (58, 8, 1, 64, False, [7879, 1001]),        # four row blocks,
+                                                   (19, 28, 4, 128, True, [7662]),                                             # a last split of one key
+                                                   (8, 8, 1, 128, False, [11897, 3, 640, 11513, 1000, 7850, 2, 5000]),         # two
+                                                   (3, 28, 4, 128, True, [7750, 1200]), (4, 8, 1, 64, False, [7745 + 192 * (b == 3) for b in range(8)])])  # own tiles
+def test_crowds_at_a_gate(oracle_mod, T, Hq, Hkv, d, paged, lens):
+    """28 splits and more on nearly all CUs, whose workgroups look at a second word."""
+    import gpu_util as gu
+    cfg = gen.Config("crowd", len(lens), Hq, Hkv, d, T, min(6, T - 1), 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2), paged=paged)
+    inp = gen.attention_inputs(cfg, 980, prefix_len=np.array(lens, dtype=np.int32))
+    da = gu.DeviceAttn(inp)
+    pl = da.plan()
+    assert pl.schedule == vs.VS_SCHED_LOOP and pl.waves_per_group == 8 and pl.num_splits >= 28 and pl.workgroups >= 224
+    assert pl.keys_per_split >= (320 if T == 8 else 256)   # fewer keys are the resident kernel's
+    da.ws.random_(0, 256)
+    want = da.run()
+    ref = oracle_mod.tree_attention(inp, threads=8)
+    for b in range(len(lens)):
+        gu.check_close(want[b], ref[b], *(TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT), what=f"sequence {b} of {lens[b]}")
+    for _ in range(3):
+        np.testing.assert_array_equal(want, da.run())
     _hand_over(da, len(lens) * Hkv * pl.row_groups, want)

@@ -11,7 +11,7 @@ from paper_2509_15235_amd import build
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """(channels, waves, row blocks, paged, read once) -> instructions."""
+    """(channels, waves, row blocks, paged, read once, crowd) -> instructions."""
     to = tmp_path_factory.mktemp("rows") / "k.s"
     flags = [f for f in build.FLAGS if f != "-shared"]
     subprocess.check_call([build.HIPCC, "--offload-device-only", "-S"] + flags + [os.path.join(build.CSRC, "attention_mfma_rows.hip"), "-o", str(to)],
@@ -19,7 +19,7 @@ def kernels(tmp_path_factory):
     found, code = {}, None
     for line in to.read_text().splitlines():
         line = line.split(";")[0].strip()
-        name = re.fullmatch(r"_ZN2vs.*attn_mfma_rows_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELb([01])E.*:", line)
+        name = re.fullmatch(r"_ZN2vs.*attn_mfma_rows_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELb([01])ELb([01])E.*:", line)
         if name:
             code = found.setdefault(tuple(int(x) for x in name.groups()), [])
         elif line == "s_endpgm":
@@ -30,8 +30,8 @@ def kernels(tmp_path_factory):
 
 
 def test_all_kernels_are_here(kernels):
-    assert set(kernels) == {(d, w, rb, paged, once) for d, w, rb in [(128, 8, 1), (128, 8, 2), (128, 4, 1), (64, 8, 1), (64, 4, 1)]
-                            for paged, once in [(0, 0), (0, 1), (1, 0)]}
+    assert set(kernels) == {(d, w, rb, paged, once, crowd) for d, w, rb in [(128, 8, 1), (128, 8, 2), (128, 4, 1), (64, 8, 1), (64, 4, 1)]
+                            for paged, once, crowd in [(0, 0, 0), (0, 1, 0), (1, 0, 0), (0, 0, 1), (1, 0, 1)] if not crowd or (w, rb) == (8, 1)}
 
 
 def test_no_zeros_for_the_results_before_the_first_tile(kernels):
