@@ -37,8 +37,10 @@ __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(const CommitP
     const int tid = threadIdx.x, lane = tid & 63;
     const int32_t node = p.path[(int64_t)b * p.T + min(lane, p.T - 1)];
     int32_t S = p.prefix_len[b], alen = p.accepted_len[b];
-    // ---- this thread's piece: (layer, K or V, KV head, 16-byte chunk of the row)
-    const int64_t item = (int64_t)blockIdx.x * kCommitThreads + tid;
+    // ---- this thread's piece: (layer, K or V, KV head, 16-byte chunk of the row). A wave's lanes past the last piece stay, since
+    // path and block ids are read from lanes, whose registers nobody keeps up once they have left: they do what the last piece's lane, one of the
+    // same wave, does in the same instructions. (Without their stores 1 - 6 % slower.)
+    const int64_t own = (int64_t)blockIdx.x * kCommitThreads + tid, item = min(own, p.items_per_seq - 1);
     int64_t layer;
     uint32_t chunk, kvh, which;
     if (p.items_per_seq <= 0xffffffffll) { // (the 45 instructions of a division, three times, stood between the checks and the rows)
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(const CommitP
         if (p.status) p.status[b] = code;
         p.new_prefix_len[b] = code == VS_STATUS_OK ? S + alen + 1 : S;
     }
-    if (code != VS_STATUS_OK || item >= p.items_per_seq) return;
+    if (code != VS_STATUS_OK || own - lane >= p.items_per_seq) return; // the whole wave
 
     auto row = [&](int32_t tok) -> char* { // tok is the same for all lanes
         if constexpr (PAGED) {
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(const CommitP
         asm volatile("" ::: "memory"); // or a load sinks to the only place that needs it, behind a condition
 #pragma unroll
         for (int u = 0; u < N; ++u)
-            if (k0 + u <= alen && __builtin_amdgcn_readlane(node, k0 + u) != k0 + u) *(u32x4*)row(S + k0 + u) = r[u];
+            if (k0 + u <= alen && __builtin_amdgcn_readlane(node, k0 + u) != k0 + u) *(u32x4*)row(S + k0 + u) = r[u]; // the same for all lanes
     };
     int k0 = 1;
     for (; alen - k0 >= 4; k0 += kCommitBatch) move(std::integral_constant<int, kCommitBatch>{}, k0);

@@ -120,6 +120,24 @@ def test_every_number_of_moves(gu, oracle_mod, paged, T):
     assert _same_bytes(gk, ek) and _same_bytes(gv, ev) and not _same_bytes(gk, kk)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d,hkv,layers", [(8, 1, 1), (8, 1, 3), (64, 2, 3), (64, 1, 5)])      # 2, 6, 96 and 80 pieces
+def test_long_paths_of_few_pieces(gu, oracle_mod, d, hkv, layers, paged):
+    """Waves with fewer pieces than a path has nodes: what the lanes without a piece hold of the path and the block table counts too."""
+    T, B = 64, 4
+    alen = np.array([40, 60, 47, 31], dtype=np.int32)
+    k = np.arange(T)
+    at = np.stack([np.minimum(k + (k > 2), T - 1), np.minimum(k + (k > 5), T - 1), np.minimum(k + 5 * (k > 0), T - 1), 2 * k])
+    path = np.where(k <= alen[:, None], at, -1).astype(np.int32)
+    cfg = gen.Config("pieces", B, hkv, hkv, d, T, 7, 4, 100, 0.5, 1, "bf16", prefix=None if paged else [0, 3, 15, 17],
+                     prefix_range=(9, 40) if paged else None, paged=paged)
+    inp, kk, vv = _layers(cfg, 4100 + d, layers)
+    gk, gv, newp, status = gu.DeviceCommit(cfg, kk, vv, inp.prefix_len, path, alen, inp.block_table).run()
+    ek, ev, enp = _oracle_commit(oracle_mod, inp, kk, vv, path, alen)
+    assert (status == 0).all() and np.array_equal(newp, enp)
+    assert _same_bytes(gk, ek) and _same_bytes(gv, ev) and not _same_bytes(gk, kk)
+
+
 def test_long_paths_cross_the_batch_of_eight(gu, oracle_mod):
     """Chain-like trees: up to 63 accepted tokens, several batches of moves per thread."""
     T, B = 64, 3
