@@ -344,8 +344,9 @@ int32_t vs_tree_accept_sample(const float* logits, int64_t ld_logits, int32_t V,
  *                 index ascending), listed in ascending candidate index
  *   next_cum      [B,min(K,F*K)] fp32 out: their scores (the next step's cum_in)
  *   workspace     at least vs_draft_expand_workspace_bytes(B,F,V,K) bytes, 256-byte aligned
- * Tokens are exact; scores are fp32 (log-sum-exp over 8192-entry chunks), so two candidates
- * whose exact scores differ by less than ~1e-5 may swap places at the cut.
+ * Tokens are exact; scores are fp32 (log-sum-exp over chunks of 8192, 10240 or 12288 entries), so two candidates
+ * whose exact scores differ by less than ~1e-5 may swap places at the cut. The chunks' length goes by V and B * F: a
+ * sequence's scores may differ in their last bits, and such a pair swap, beside another number of sequences.
  *
  * vs_draft_tree_build, the final selection over the first M candidates (1 <= M <= 2048,
  * 1 <= N <= 63; scores without NaN): the min(N, M) best by (score descending, index ascending)

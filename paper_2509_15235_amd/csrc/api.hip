@@ -562,6 +562,7 @@ int32_t draft_chunks(int32_t V, int32_t vec) { return (int32_t)(((int64_t)V + ve
 // two of them hold up the sequence's last part. us, three levels and the selection, chunks of 8192 / chosen so:
 //   2 x 8 x 152064 34.6 / 33.2, 3 x 8 x 98304 32.1 / 31.9, 5 x 8 x 60000 31.1 / 30.4, 8 x 8 x 36000 31.4 / 30.6, 8 x 8 x 45000 32.1 / 31.8,
 //   1 x 16 x 180000 52.7 / 48.3
+// (So the order of a row's sums, and with it the last bits of its scores, depends on the number of rows in the call, which the header says.)
 int32_t draft_vec(int32_t V, int64_t rows) {
     for (int32_t vec = 4; vec <= 6; ++vec)
         if (rows * draft_chunks(V, vec) <= kNumCUs) return vec;

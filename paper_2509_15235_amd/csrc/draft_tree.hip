@@ -5,16 +5,16 @@
 // children as the next frontier; at the end the N best-scored candidates of all levels are
 // the tree. The draft model's forward pass is not part of this: its logits are inputs.
 //
-// Two kernels. (1) An expansion: every workgroup reduces an 8192-float chunk of a logits row to (maximum, sum of
+// Two kernels. (1) An expansion: every workgroup reduces a chunk of a logits row (8192 floats, or 10240 or 12288) to (maximum, sum of
 // exp, the chunk's K largest entries); the workgroup of a sequence that finishes last merges the chunks into each
 // row's top K and log-sum-exp, scores the F*K candidates and picks the next frontier. (That second part used to
 // be a kernel of its own: 7.8 us for one trip to memory and half a microsecond of work, three times per tree.)
 // (2) One workgroup per sequence for the final selection, which emits parent[] / tokens[] in candidate order.
 //
 // Selection without bookkeeping: entries are taken in the strict total order (value descending, index
-// ascending), as integers of 64 bits, also between the workgroups. A bound that at least K entries reach is found
-// from the largest of every lane or group of lanes, the few entries at or above it are compacted and ranked by
-// counting; nothing has to be marked as taken.
+// ascending), as integers of 64 bits, also between the workgroups. In a chunk a bound that at least K entries reach is found
+// from the largest of every group of lanes, the few entries at or above it are compacted and ranked by
+// counting; the chunks' lists, and a frontier's rows, stand in order already and are merged in registers. Nothing has to be marked as taken.
 #include <type_traits>
 
 #include "vs_device.h"
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(kExpandThreads) void draft_expand_kernel(const Draf
         }
 
         // ---- the chunk's maximum and sum of exp (per wave, then of the waves), and its K first entries: the K-th largest of
-        // the maxima of 32 groups of 256 entries is a bound that K entries reach and few others do
+        // the maxima of 32 groups of 64 * VEC entries is a bound that K entries reach and few others do
         float own = ev[0];
 #pragma unroll
         for (int q = 1; q <= 4 * VEC; ++q) own = fmaxf(own, ev[q]);

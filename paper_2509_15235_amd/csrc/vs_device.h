@@ -119,7 +119,8 @@ __device__ __forceinline__ T rows_all(T x, Op op) {
     r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
     return op(__builtin_bit_cast(T, (uint32_t)r[0]), __builtin_bit_cast(T, (uint32_t)r[1]));
 }
-// fmaxf without quieting its operands first (the instruction does)
+// fmaxf of operands that are no signaling NaN, as results of arithmetic and of fmaxf never are: no instruction that quiets them stands in front. (Of a
+// signaling NaN and a number v_max_f32 makes a quiet NaN, fmaxf the number: not for values as they come from memory. The same below.)
 __device__ __forceinline__ float max_of(float a, float b) {
     float r;
     asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
