@@ -430,8 +430,8 @@ int filling_splits(int wgs, int tiles) {
 // Key splits of the pipelined kernel, where a caller names none: as many as fill the CUs, or with eight waves of 128 channels whole sequences, where
 // a model of the kernel's time (3 % rms of 394 timings of 12 .. 200 units x row groups, 5 .. 60 iterations, 1 .. 20 splits) says that
 // the iterations saved are not worth the merge. us per call, 28 / 4 heads, filling / whole: 24 x 25 nodes, 61 .. 490 keys 2 21.9 / 19.6; 10 x 64, 25 ..
-// 203 keys 2 19.4 / 15.1; 22 x 35, 615 keys 2 26.7 / 23.2. Over 9241 drawn calls that it takes 0.83 of the time, eight of them 1.01 - 1.02
-// (profiles/whole_sequences.md). 64 channels lose (16 x 40, 48 .. 388 keys 2 14.1 / 15.1); of four waves two workgroups share a CU.
+// 203 keys 2 19.4 / 15.1; 22 x 35, 615 keys 2 26.7 / 23.2. Over 9241 drawn calls that it takes 0.83 of the time, eight of them 1.01 -
+// 1.02. 64 channels lose (16 x 40, 48 .. 388 keys 2 14.1 / 15.1); of four waves two workgroups share a CU.
 // Never more splits: finer ones were faster (12 x 21 nodes, 481 keys 2 17.1 / 4 13.4), but the shorter sequences of a ragged batch, one piece
 // and so fp32 up to the final rounding in a coarser split, are then bf16 partial rows. Relative error against 64 bits, 40 drawn
 // calls each, filling / so: whole 2.68e-3 / 2.30e-3; finer ones 2.76e-3 / 2.77e-3, at worst 2.17e-3 / 2.59e-3 (2 x 36 nodes, 32 / 8 heads
@@ -537,14 +537,15 @@ Plan make_plan(const vs_attn_desc* d, int tree = 1) {
 // Such loads come faster from memory and leave less of their data in the caches: faster for who finds nothing there, as the layers of a model, each with
 // a cache of its own, do; not always for who goes over one layer again and again that the 256 MB cache in front of the memory would have held - least so
 // where CUs are idle and each of the others waits for its own loads. Time relative to plain loads, over other data each time / over the
-// same, 6500 drawn calls, by the megabytes of K and V up to the longest allowed prefix and by the CUs' places taken in the last round:
-//   own tiles of one row block < 20 MB 1.1 / 1.00; .. 40 0.96 / 1.00; .. 96 all but a tenth of the places 0.94 / 0.92, less 0.95 / 0.95 (up to 1.10);
-//   .. 192 0.93 / 1.00, less 0.94 / 1.04 (1.24); .. 512 0.91 / 1.01, less 0.92 / 1.04 (1.31); above 0.90 / 0.90 either way;
-//   of two row blocks (long ones have 128 MB or more) .. 512 0.94 / 1.01, less 0.95 / 1.05 (1.26), above 0.90 / 0.90;
-//   four waves of the pipelined kernel .. 256 0.97 / 1.00, .. 512 0.93 / 0.99, above 0.90 / 0.90.
+// same, 30379 drawn calls on contiguous caches, by the megabytes of K and V up to the longest allowed prefix; filled: all but a tenth of the CUs' places
+// taken in the last round, 99 in 100 calls over the same data in brackets:
+//   own tiles of one row block, filled 20 .. 40 0.95 / 0.98 (1.05), .. 96 0.93 / 0.94 (1.04), .. 256 0.91 / 0.99 (1.15), .. 512 0.90 / 0.94 (1.12), above 0.89 / 0.89;
+//   not filled .. 96 0.94 / 0.97 (1.08), .. 256 0.91 / 1.03 (1.22), .. 512 0.89 / 0.95 (1.16), above 0.89 / 0.88;
+//   of two row blocks, filled 128 .. 256 0.92 / 1.00 (1.10), .. 512 0.91 / 0.95 (1.13), above 0.91 / 0.91; not filled .. 256 0.93 / 1.04 (1.18);
+//   four waves of the pipelined kernel, filled .. 256 0.98 / 1.00 (1.09), .. 512 0.92 / 0.96 (1.06), .. 768 0.91 / 0.90, above 0.89 / 0.89; not filled, above 768 0.92 / 0.91.
 // (Two row groups of eight waves, which share what they read, 1.03 / 1.04.) So what is too large for any cache, and of the rest what repeats
-// no slower; of two row blocks, whose repetition with all sequences as long takes 1.00
-// (1.12 where all are half as long as allowed and half of the splits have no keys), all that fills the CUs. us per call: 64 x 4 nodes, 28 / 4 heads, 8000 keys 184 / 162;
+// no slower; of two row blocks, whose repetition takes 1.00 (1.12 where all are half as long as allowed and half of the splits have no keys), all that fills
+// the CUs. All that the rule takes 0.906 / 0.908, 39 of 8124 over 1.05 of the same data's time. us per call: 64 x 4 nodes, 28 / 4 heads, 8000 keys 184 / 162;
 // 4 x 60 nodes, 32 / 32 heads, 2880 .. 3392 keys, one layer of 32 45.1 / 40.7; 8 x 60, 1024 .. 8191 keys 159 / 139; 20 x 60, 2000 keys 155 / 132
 bool reads_once(const vs_attn_desc* d, const Plan& pl, int tree) {
     const bool four = (pl.schedule == VS_SCHED_PIPELINED || pl.schedule == VS_SCHED_BALANCED) && pl.waves == 4;
