@@ -162,6 +162,7 @@ def test_shares_of_the_pipelined_kernel_handed_over(oracle_mod, Hq, Hkv, T, lens
                                                    (3, 28, 4, 128, True, [15870, 1200]), (4, 8, 1, 64, False, [15869] * 3 + [900, 1, 15357, 15356, 3000])])  # own tiles
 def test_crowds_at_a_gate(oracle_mod, T, Hq, Hkv, d, paged, lens):
     """28 splits and more on nearly all CUs, whose workgroups look at a second word."""
+    import torch
     import gpu_util as gu
     cfg = gen.Config("crowd", len(lens), Hq, Hkv, d, T, min(6, T - 1), 4, 100, 0.5, 1, "bf16", prefix=None, prefix_range=(1, 2), paged=paged)
     inp = gen.attention_inputs(cfg, 980, prefix_len=np.array(lens, dtype=np.int32))
@@ -175,5 +176,19 @@ def test_crowds_at_a_gate(oracle_mod, T, Hq, Hkv, d, paged, lens):
     for b in range(len(lens)):
         gu.check_close(want[b], ref[b], *(TIGHT_LONG if lens[b] >= 256 else TIGHT_SHORT), what=f"sequence {b} of {lens[b]}")
     for _ in range(3):
+        np.testing.assert_array_equal(want, da.run())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        for _ in range(2):                           # the second one finds the words as the first one left them
+            assert vs.vs_tree_verify_attention(da.desc, da.q, da.k, da.v, da.prefix, da.parent, None, da.out, da.status, da.ws, da.ws_bytes,
+                                               torch.cuda.current_stream().cuda_stream) == 0
+    for rep in range(4):
+        da.out.fill_(float("nan"))
+        if rep % 2:
+            da.ws.random_(0, 256)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(want, da.out.float().cpu().numpy().astype(np.float64), err_msg=f"replay {rep}")
         np.testing.assert_array_equal(want, da.run())
     _hand_over(da, len(lens) * Hkv * pl.row_groups, want)
